@@ -2,8 +2,10 @@
 
 Argument marshalling only: every step of the sampling path runs in the library's HIP
 kernels.  PyTorch supplies device memory for the inputs, the current stream, and
-zero-copy tensor views of the result buffers.  There is no CPU fallback: if the
-library has not been built, importing any entry point raises.
+zero-copy tensor views of the result buffers.  What happens on every call of a training
+loop (the sampling call itself, the views of a hop or minibatch) goes through the
+extension module _native (csrc_py/native.cpp), the rest through ctypes.  There is no CPU
+fallback: if the libraries have not been built, the first use of an entry point raises.
 """
 from __future__ import annotations
 
@@ -130,25 +132,27 @@ def lib() -> C.CDLL:
     return _lib
 
 
+_native = None
+
+
+def native():
+    """The loaded extension module; raises if it has not been built (no fallback path exists)."""
+    global _native
+    if _native is None:
+        lib()
+        path = os.path.join(_HERE, "_native.so")
+        if not os.path.exists(path):
+            raise ImportError("%s is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
+                              "or `python -m paper_2311_02909_amd.build` first" % path)
+        from . import _native as module
+        _native = module
+    return _native
+
+
 def _check(rc: int):
     if rc != OK:
         detail = lib().bms_last_error().decode() or lib().bms_strerror(rc).decode()
         raise BmsError(rc, detail)
-
-
-class _DevArray:
-    """A device buffer owned by a result, exposed through the CUDA array interface."""
-
-    def __init__(self, ptr: int, count: int, typestr: str, owner):
-        self.owner = owner
-        self.__cuda_array_interface__ = {"shape": (count,), "typestr": typestr, "data": (ptr, False), "version": 2}
-
-
-def _view(ptr, count: int, dtype: torch.dtype, owner) -> torch.Tensor:
-    if count == 0 or not ptr:
-        return torch.empty(0, dtype=dtype, device="cuda")
-    typestr = {torch.int32: "<i4", torch.int64: "<i8"}[dtype]
-    return torch.as_tensor(_DevArray(int(ptr), int(count), typestr, owner), device="cuda")
 
 
 @dataclass
@@ -278,36 +282,17 @@ class Result:
         return v.value
 
     def hop(self, h: int) -> Hop:
-        v = _HopView()
-        _check(lib().bms_result_hop(self.handle, h, C.byref(v)))
-        k = self.k
-        has_p = bool(v.p_off)
-        return Hop(
-            rows=v.rows, nnz=v.nnz, ncols=v.ncols, pnnz=v.pnnz,
-            mb_rowoff=_view(v.mb_rowoff, k + 1, torch.int64, self),
-            row_vertex=_view(v.row_vertex, v.rows, torch.int32, self),
-            rowptr=_view(v.rowptr, v.rows + 1, torch.int64, self),
-            col=_view(v.col, v.nnz, torch.int32, self),
-            mb_coloff=_view(v.mb_coloff, k + 1, torch.int64, self),
-            col_vertex=_view(v.col_vertex, v.ncols, torch.int32, self),
-            p_off=_view(v.p_off, k + 1, torch.int64, self) if has_p else None,
-            p_col=_view(v.p_col, v.pnnz, torch.int32, self) if has_p else None,
-            p_cnt=_view(v.p_cnt, v.pnnz, torch.int32, self) if has_p else None,
-            row_self=_view(v.row_self, v.rows, torch.int32, self) if v.row_self else None,
-        )
+        t = native().hop(self.handle.value if self.handle else 0, h, self.k, torch.cuda.current_device(), self)
+        if type(t) is int:
+            _check(t)
+        return Hop(*t)
 
     def minibatch(self, h: int, i: int) -> Minibatch:
         """bms_result_minibatch: minibatch i of hop h cut out of the stack (no copies of the arrays)."""
-        v = _MbView()
-        _check(lib().bms_result_minibatch(self.handle, h, i, C.byref(v)))
-        return Minibatch(
-            rows=v.rows, nnz=v.nnz, ncols=v.ncols, row0=v.row0, edge0=v.edge0, col0=v.col0,
-            row_vertex=_view(v.row_vertex, v.rows, torch.int32, self),
-            rowptr=_view(v.rowptr, v.rows + 1, torch.int64, self),
-            col=_view(v.col, v.nnz, torch.int32, self),
-            col_vertex=_view(v.col_vertex, v.ncols, torch.int32, self),
-            row_self=_view(v.row_self, v.rows, torch.int32, self) if v.row_self else None,
-        )
+        t = native().minibatch(self.handle.value if self.handle else 0, h, i, torch.cuda.current_device(), self)
+        if type(t) is int:
+            _check(t)
+        return Minibatch(*t)
 
     def minibatch_offsets(self, h: int, out: Optional[np.ndarray] = None, stream=None) -> np.ndarray:
         """bms_result_minibatch_offsets: the (row, entry, column) offsets of every minibatch of hop h as a
@@ -362,28 +347,29 @@ def _profile_flag(profile) -> int:
     return PROFILE if profile else 0
 
 
-def _sample(fn, csr: Csr, batches, params: Sequence[int], seed: int, mb_base, stream, recycle, flags, scratch_limit,
-            allocator=None):
+def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, mb_base, stream, recycle, flags,
+            scratch_limit, allocator=None):
     if isinstance(batches, np.ndarray):
         batches = torch.from_numpy(np.ascontiguousarray(batches, dtype=np.int32))
     if batches.dtype != torch.int32 or batches.dim() != 2:
         raise TypeError("batches must be a k x b int32 tensor")
     batches = batches.contiguous()
     k, b = batches.shape
-    par = (C.c_int32 * len(params))(*[int(p) for p in params])
     if stream is None:
-        stream = torch.cuda.current_stream().cuda_stream
-    opts = _Opts(stream=stream, mb_base=mb_base, flags=flags,
-                 recycle=recycle.handle if recycle is not None else None, scratch_limit=scratch_limit)
-    if allocator is not None:
-        opts.alloc, opts.dealloc = allocator.alloc, allocator.dealloc
-    out = C.c_void_p()
-    _check(fn(csr.handle, batches.data_ptr(), k, b, par, len(params), seed & 0xFFFFFFFFFFFFFFFF, C.byref(opts),
-              C.byref(out)))
+        stream = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    alloc = dealloc = old = None
+    if recycle is not None:
+        old = recycle.handle.value if recycle.handle else 0  # a recycled result keeps the allocator it was created with
+    elif allocator is not None:
+        alloc, dealloc = C.cast(allocator.alloc, C.c_void_p).value, C.cast(allocator.dealloc, C.c_void_p).value
+    rc, out = native().sample(ladies, csr.handle.value if csr.handle else 0, batches.data_ptr(), k, b, tuple(int(p) for p in params), seed,
+                              stream or 0, mb_base, flags, old or 0, scratch_limit, alloc or 0, dealloc or 0)
+    if rc != OK:
+        _check(rc)
     if recycle is not None:
         recycle.k, recycle.L = k, len(params)
         return recycle
-    r = Result(out)
+    r = Result(C.c_void_p(out))
     r._allocator = allocator   # the callbacks must outlive the result
     return r
 
@@ -401,7 +387,7 @@ def sample_nodewise(csr: Csr, batches, fanouts: Sequence[int], seed: int, *, mb_
     flags = _profile_flag(profile) | {None: 0, "buckets": EXTRACT_BUCKETS, "bitmap": EXTRACT_BITMAP,
                                            "sort": EXTRACT_SORT}[extract] | (UNION_DST if union_dst else 0) | (
         NODEWISE_REPLACE if replace else 0) | (ASYNC if async_ else 0)
-    return _sample(lib().bms_sample_nodewise, csr, batches, fanouts, seed, mb_base, stream, recycle, flags,
+    return _sample(False, csr, batches, fanouts, seed, mb_base, stream, recycle, flags,
                    scratch_limit, allocator)
 
 
@@ -412,7 +398,7 @@ def sample_ladies(csr: Csr, batches, s_per_layer: Sequence[int], seed: int, *, m
 
     dense=True picks the kernel path with per-minibatch counters in HBM (same results)."""
     flags = _profile_flag(profile) | (LADIES_SQUARED if squared else 0) | (LADIES_DENSE if dense else 0) | (0 if index else LADIES_NO_INDEX)
-    return _sample(lib().bms_sample_ladies, csr, batches, s_per_layer, seed, mb_base, stream, recycle, flags,
+    return _sample(True, csr, batches, s_per_layer, seed, mb_base, stream, recycle, flags,
                    scratch_limit, allocator)
 
 

@@ -54,6 +54,30 @@ def build_lib(verbose: bool = False, incremental: bool = False) -> str:
     return LIB
 
 
+NATIVE_SRC = os.path.join(HERE, "csrc_py", "native.cpp")
+NATIVE = os.path.join(HERE, "_native.so")
+
+
+def build_native(verbose: bool = False) -> str:
+    """The Python binding's per-call host work (g++; torch's headers and libraries, libbms.so beside it)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-o", tmp, NATIVE_SRC,
+           "-L", HERE, "-l:libbms.so", "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(root, "lib")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 PROBE_SRC = os.path.join(HERE, "csrc_probe", "probes.hip")
 PROBE_LIB = os.path.join(HERE, "libbms_probe.so")
 
@@ -90,5 +114,6 @@ def build_c_client(verbose: bool = False) -> str:
 if __name__ == "__main__":
     import sys
     print(build_lib(verbose=True, incremental="--incremental" in sys.argv))
+    print(build_native(verbose=True))
     print(build_probes(verbose=True))
     print(build_c_client(verbose=True))
