@@ -221,9 +221,10 @@ typedef struct bms_mb_view {
 } bms_mb_view;
 
 /*
- * Fill *view for minibatch 0 <= i < k of hop 0 <= hop < L.  The first call on a result copies the per-minibatch
- * offsets of every hop to the host (three arrays of k+1 integers per hop; it waits for that copy); later calls on
- * the same result only do pointer arithmetic.  BMS_EINVAL for a bad handle, hop or minibatch index.
+ * Fill *view for minibatch 0 <= i < k of hop 0 <= hop < L.  The per-minibatch offsets of every hop (three arrays of
+ * k+1 integers per hop) are written to pinned host memory by the sampling call's last kernel, so that this call only
+ * does pointer arithmetic; where they are not (more than 65536 of them, BMS_LADIES_DENSE) the first call on a result
+ * copies them to the host and waits for that copy.  BMS_EINVAL for a bad handle, hop or minibatch index.
  */
 int bms_result_minibatch(bms_result *res, int32_t hop, int32_t i, bms_mb_view *view);
 

@@ -25,6 +25,9 @@ constexpr int32_t kMaxMinibatches = 65535; // some kernels take the minibatch fr
 constexpr int64_t kNoWaitEntries = 32LL << 20; // result buffers up to this many entries may be sized by a bound
 constexpr double kBitmapIdsPerEntry = 128.0; // EXTRACT ranks by bitmap when a minibatch samples at least n / this many ids
                                             // (measured: by bitmap wins at 4..15 ids of [0, n) per sampled id, by counting at 580)
+constexpr int32_t kHostScalars = 72; // the 64 scalars of a call, then the seed flags of the calls that check seeds in their
+                                    // first kernel: two 32-bit words that it sets in host memory (range, repeat)
+constexpr size_t kMostHostOffsets = 1 << 16; // per-minibatch offsets that a call leaves in host memory: at most (512 KB)
 constexpr int64_t kScanTmpLen = 1 << 17; // partial sums of multi-workgroup scans: arrays up to 2^29 values
 
 thread_local char g_err[512] = "";
@@ -167,12 +170,14 @@ struct bms_csr {
     BMS_BUF(row_cnt);                    // BMS_NODEWISE_REPLACE with a fanout above 32: distinct picks per row
     BMS_BUF(lw_bounds); BMS_BUF(lw_win); BMS_BUF(lw_tmpcol); BMS_BUF(lw_parts); BMS_BUF(lw_sel); BMS_BUF(lw_xtmp);
     BMS_BUF(lw_count); BMS_BUF(lw_tiles); BMS_BUF(lw_rowcnt); // LADIES by LDS windows
+    BMS_BUF(sm_status); BMS_BUF(sm_ticket); // hops done by one workgroup per minibatch: sizes published, next minibatch
+    uint32_t sm_epoch = 0, sm_taken = 0;     // launches so far, minibatches handed out by them
     BMS_BUF(lw_index);           // where every vertex's adjacency list crosses the window boundaries: n * (nwin + 1)
     bool lw_index_ready = false; // built by the first layer-wise call that finds room for it
     bool lw_index_tried = false;
 #undef BMS_BUF
     bool ld_clean = false; // all dense counters zero
-    int64_t *host_pinned = nullptr; // 64 int64
+    int64_t *host_pinned = nullptr; // 64 values
 };
 
 struct HopBufs {
@@ -226,7 +231,11 @@ struct bms_result {
     // BMS_ASYNC: the call has returned, its kernels may still run
     bool pending = false;
     hipEvent_t done_ev = nullptr;
-    int64_t *host_scalars = nullptr; // pinned, 64 values: where the call's sizes and flags arrive
+    // pinned: kHostScalars values, where the call's sizes and flags arrive; then, when host_off says so, the
+    // per-minibatch offsets as in mb_offsets
+    int64_t *host = nullptr;
+    size_t host_cap = 0;
+    bool host_off = false;
     PendingNodewise deferred;
 };
 
@@ -254,9 +263,10 @@ void result_release(bms_result *r)
     if (r->done_ev)
         (void)hipEventDestroy(r->done_ev);
     r->done_ev = nullptr;
-    if (r->host_scalars)
-        (void)hipHostFree(r->host_scalars);
-    r->host_scalars = nullptr;
+    if (r->host)
+        (void)hipHostFree(r->host);
+    r->host = nullptr;
+    r->host_cap = 0;
     for (auto e : r->event_pool)
         (void)hipEventDestroy(e);
     r->event_pool.clear();
@@ -466,6 +476,18 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
     c.res->mb_offsets.clear();
     if (!csr->host_pinned)
         HIP_TRY(hipHostMalloc((void **)&csr->host_pinned, 64 * sizeof(int64_t), hipHostMallocDefault));
+    const size_t noff = (size_t)L * 3 * ((size_t)k + 1);
+    const size_t values = kHostScalars + (noff <= kMostHostOffsets ? noff : 0);
+    if (c.res->host_cap < values) {
+        if (c.res->host)
+            (void)hipHostFree(c.res->host);
+        c.res->host = nullptr;
+        c.res->host_cap = 0;
+        HIP_TRY(hipHostMalloc((void **)&c.res->host, values * sizeof(int64_t), hipHostMallocMapped));
+        c.res->host_cap = values;
+    }
+    c.res->host_off = false;
+    c.res->host[64] = 0;
     BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
     return BMS_OK;
 }
@@ -523,14 +545,43 @@ int read_scalars(CallCtx &c)
     return BMS_OK;
 }
 
-int seed_flag_error(CallCtx &c)
+// where the minibatches' offsets go in the result's pinned block (null: there are too many of them)
+int64_t *host_offsets(const CallCtx &c)
 {
-    const int32_t flag = (int32_t)(c.csr->host_pinned[63] & 0xFFFFFFFF);
-    if (flag & 1)
-        return fail(BMS_ERANGE, "a seed vertex lies outside [0, %lld)", (long long)c.csr->n);
-    if (flag & 2)
+    const size_t noff = (size_t)c.L * 3 * ((size_t)c.k + 1);
+    return noff <= kMostHostOffsets ? c.res->host + kHostScalars : nullptr;
+}
+
+// scalars: the call's scalars on the host; first_kernel: the result's pinned block, where the kernels that check the
+// seeds themselves raise their flags
+int seed_flag_error(const bms_csr *csr, const int64_t *scalars, const int64_t *first_kernel)
+{
+    const int32_t flag = (int32_t)(scalars[63] & 0xFFFFFFFF);
+    const int32_t *flags = reinterpret_cast<const int32_t *>(first_kernel + 64);
+    if ((flag & 1) || flags[0])
+        return fail(BMS_ERANGE, "a seed vertex lies outside [0, %lld)", (long long)csr->n);
+    if ((flag & 2) || flags[1])
         return fail(BMS_ERANGE, "a seed vertex is repeated inside one minibatch");
     return BMS_OK;
+}
+
+// The call's scalars and the minibatches' offsets -> pinned memory of the result, in stream order.
+void publish(CallCtx &c)
+{
+    PublishArgs p{};
+    p.k = c.k;
+    p.L = c.L;
+    p.scalars = c.csr->scalars.as<int64_t>();
+    p.host = c.res->host;
+    p.off = host_offsets(c);
+    for (int32_t h = 0; h < c.L; ++h) {
+        const bms_hop_view &v = c.res->hops[h].view;
+        p.rowptr[h] = v.rowptr;
+        p.rowoff[h] = v.mb_rowoff;
+        p.coloff[h] = v.mb_coloff;
+    }
+    launch_publish(c.launch, p);
+    c.res->host_off = p.off != nullptr;
 }
 
 // scalar slots: per hop 4 int64: [0] nnz, [1] ncols, [2] pnnz, [3] gathered D ; slot 63 = seed flag
@@ -543,13 +594,8 @@ constexpr int32_t kMaxHops = 15; // 4 scalar slots per hop in a 64-entry block
 // gave up (*redo), the views' sizes, what the result remembers for the next call of this shape, the stage times.
 int finish_nodewise(bms_result *res, const PendingNodewise &pn, const int64_t *host, bool check_seeds, uint32_t *redo)
 {
-    if (check_seeds) {
-        const int32_t flag = (int32_t)(host[63] & 0xFFFFFFFF);
-        if (flag & 1)
-            return fail(BMS_ERANGE, "a seed vertex lies outside [0, %lld)", (long long)pn.csr->n);
-        if (flag & 2)
-            return fail(BMS_ERANGE, "a seed vertex is repeated inside one minibatch");
-    }
+    if (check_seeds)
+        BMS_TRY(seed_flag_error(pn.csr, host, host));
     for (int32_t h = 0; h < pn.L; ++h)
         if (host[h * 4 + 2] & 0xFFFFFFFFLL)
             *redo |= 1u << h;
@@ -596,7 +642,7 @@ int settle_result(bms_result *res)
     HIP_TRY(hipSetDevice(res->device));
     HIP_TRY(hipEventSynchronize(res->done_ev));
     uint32_t redo = 0;
-    const int rc = finish_nodewise(res, res->deferred, res->host_scalars, true, &redo);
+    const int rc = finish_nodewise(res, res->deferred, res->host, true, &redo);
     if (rc != BMS_OK) {
         empty_result(res, false);
         return rc;
@@ -620,6 +666,121 @@ std::vector<int32_t> nodewise_shape(const CallCtx &c, const int32_t *fanouts)
     std::vector<int32_t> shape{c.k, c.b, ((c.flags & BMS_UNION_DST) ? 1 : 0) | ((c.flags & BMS_NODEWISE_REPLACE) ? 2 : 0)};
     shape.insert(shape.end(), fanouts, fanouts + c.L);
     return shape;
+}
+
+// The leading hops of the call whose minibatches fit one workgroup each, whatever the draws give.  With a profile flag
+// or a chosen EXTRACT path the hops run stage by stage (they have no stages of their own in the one kernel).
+int32_t leading_small_hops(const CallCtx &c, const int32_t *fanouts)
+{
+    if (c.flags & (BMS_PROFILE | BMS_PROFILE_MAIN | BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP))
+        return 0;
+    if (c.k > kSmallMaxMb || c.b > kMaxSortedSeeds)
+        return 0;
+    int64_t rows = c.b;
+    int32_t h = 0;
+    for (; h < c.L && h < kSmallHopsMax; ++h) {
+        const int64_t per_row = std::min<int64_t>(fanouts[h], std::max<int64_t>(c.csr->max_degree, 1)) + ((c.flags & BMS_UNION_DST) ? 1 : 0);
+        if (fanouts[h] > kSmallMaxFanout || rows * per_row > kSmallCap)
+            break;
+        rows = std::max<int64_t>(std::min<int64_t>(rows * per_row, c.csr->n), 1);
+    }
+    return h;
+}
+
+// Hops 0 .. nhops - 1 in one launch, seeds included; buffers by upper bounds.  *rows_bound: rows of the hop after them.
+int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, int32_t nhops, int64_t *host, int64_t *rows_bound)
+{
+    bms_csr *csr = c.csr;
+    const int32_t self = (c.flags & BMS_UNION_DST) ? 1 : 0;
+    NwSmall a{};
+    a.A_rowptr = csr->rowptr;
+    a.A_col = csr->col;
+    a.n = csr->n;
+    a.k = c.k;
+    a.b = c.b;
+    a.nhops = nhops;
+    a.L = c.L;
+    a.mb_base = c.mb_base;
+    a.self_entry = self;
+    HopBufs &h0 = c.res->hops[0];
+    BMS_TRY(h0.row_vertex.ensure((size_t)c.k * c.b * sizeof(int32_t)));
+    BMS_TRY(h0.mb_rowoff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
+    a.row_vertex0 = h0.row_vertex.as<int32_t>();
+    a.mb_rowoff0 = h0.mb_rowoff.as<int64_t>();
+    a.batches = batches;
+    if (!is_device_pointer(batches)) {
+        HIP_TRY(hipMemcpyAsync(a.row_vertex0, batches, (size_t)c.k * c.b * sizeof(int32_t), hipMemcpyHostToDevice, c.stream));
+        a.batches = a.row_vertex0;
+    }
+    int64_t rows = c.b, cap = 64;
+    for (int32_t h = 0; h < nhops; ++h) {
+        HopBufs &hb = c.res->hops[h];
+        const int64_t per_row = std::min<int64_t>(fanouts[h], std::max<int64_t>(csr->max_degree, 1)) + self;
+        const int64_t entries = rows * per_row, cols = std::max<int64_t>(std::min<int64_t>(entries, csr->n), 1);
+        BMS_TRY(hb.rowptr.ensure((size_t)(c.k * rows + 1) * sizeof(int64_t)));
+        BMS_TRY(hb.col.ensure((size_t)std::max<int64_t>(c.k * entries, 1) * sizeof(int32_t)));
+        BMS_TRY(hb.mb_coloff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
+        BMS_TRY(hb.col_vertex.ensure((size_t)std::max<int64_t>(c.k * cols, 1) * sizeof(int32_t)));
+        if (self)
+            BMS_TRY(hb.row_self.ensure((size_t)std::max<int64_t>(c.k * rows, 1) * sizeof(int32_t)));
+        NwSmallHop &x = a.hop[h];
+        x.s = (int32_t)std::min<int64_t>(fanouts[h], kSmallMaxFanout);
+        x.hopkey = hop_key(c.seed, h);
+        x.rowptr = hb.rowptr.as<int64_t>();
+        x.col = hb.col.as<int32_t>();
+        x.mb_coloff = hb.mb_coloff.as<int64_t>();
+        x.col_vertex = hb.col_vertex.as<int32_t>();
+        x.row_self = hb.row_self.as<int32_t>();
+        hb.view = bms_hop_view{};
+        hb.view.row_self = self ? x.row_self : nullptr;
+        hb.view.mb_rowoff = h ? a.hop[h - 1].mb_coloff : a.mb_rowoff0;
+        hb.view.row_vertex = h ? a.hop[h - 1].col_vertex : a.row_vertex0;
+        hb.view.rowptr = x.rowptr;
+        hb.view.col = x.col;
+        hb.view.mb_coloff = x.mb_coloff;
+        hb.view.col_vertex = x.col_vertex;
+        rows = cols;
+        cap = std::max(cap, entries);
+    }
+    a.seed_slots = 64;
+    a.seed_shift = 26;
+    while (a.seed_slots < 2 * c.b) {
+        a.seed_slots <<= 1;
+        --a.seed_shift;
+    }
+    a.cap = (int32_t)((std::max<int64_t>(cap, a.seed_slots) + 63) / 64 * 64);
+    while (csr->n > 1 && a.idbits < 31 && ((csr->n - 1) >> a.idbits) != 0)
+        ++a.idbits;
+    if (csr->n > kSmallBuckets)
+        a.bucket_mul = (uint32_t)(((uint64_t)kSmallBuckets << 32) / (uint64_t)csr->n);
+    a.seed_flags = reinterpret_cast<int32_t *>(host + 64);
+    a.slots = csr->scalars.as<int64_t>();
+    if (nhops == c.L) { // nothing follows: the kernel leaves the sizes and offsets for the host itself
+        a.host_slots = host;
+        a.host_off = host_offsets(c);
+        c.res->host_off = a.host_off != nullptr;
+        host[63] = 0;
+    }
+    a.next_tileoff = nhops < c.L ? csr->mb_tileoff.as<int64_t>() : nullptr;
+    BMS_TRY(csr->sm_ticket.ensure(256));
+    if (csr->sm_ticket.grew) {
+        HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
+        csr->sm_taken = 0;
+    }
+    BMS_TRY(csr->sm_status.ensure((size_t)nhops * c.k * sizeof(uint64_t)));
+    if (csr->sm_status.grew || csr->sm_epoch == 0xFFFFFFFFu) {
+        HIP_TRY(hipMemsetAsync(csr->sm_status.p, 0, csr->sm_status.cap, c.stream));
+        csr->sm_epoch = 0;
+    }
+    a.status = csr->sm_status.as<unsigned long long>();
+    a.epoch = ++csr->sm_epoch;
+    a.ticket = csr->sm_ticket.as<uint32_t>();
+    a.ticket0 = csr->sm_taken;
+    if (launch_nw_small(c.launch, a, (c.flags & BMS_NODEWISE_REPLACE) != 0) != 0)
+        return fail(BMS_EHIP, "launch of the one-workgroup hop kernel was refused");
+    csr->sm_taken += (uint32_t)c.k;
+    *rows_bound = c.k * rows;
+    return BMS_OK;
 }
 
 // One attempt.  *redo receives the hops (bits) whose EXTRACT by id-range segments gave up (ids crowded into a narrow
@@ -646,14 +807,17 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     if (nbuckets > kMaxBuckets)
         buckets = false;
     const bool seeds_by_sort = buckets && c.b <= kMaxSortedSeeds;
-    if (!buckets || !seeds_by_sort)
+    const bool union_dst = (c.flags & BMS_UNION_DST) != 0;
+    const bool replace = (c.flags & BMS_NODEWISE_REPLACE) != 0;
+    const int32_t small_hops = leading_small_hops(c, fanouts);
+    if (!buckets || !(seeds_by_sort || small_hops))
         BMS_TRY(setup_vset(c));
-    BMS_TRY(stage_seeds(c, batches, prof, !seeds_by_sort));
-    if (buckets) {
+    if (buckets && small_hops < c.L) {
         BMS_TRY(csr->dd_edgeoff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
         BMS_TRY(csr->dd_count.ensure((size_t)c.k * sizeof(int64_t)));
         BMS_TRY(csr->dd_done.ensure(256));
-        HIP_TRY(hipMemsetAsync(csr->dd_done.p, 0, 256, c.stream));
+        if (csr->dd_done.grew || !csr->segcnt_clean) // back at zero after every hop, unless a call was interrupted
+            HIP_TRY(hipMemsetAsync(csr->dd_done.p, 0, 256, c.stream));
     }
     std::vector<int32_t> table_built((size_t)c.L, 0); // per hop: segments of the table in use (0: none)
     int32_t table_pending = -1;
@@ -662,15 +826,11 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     csr->segcnt_clean = false;              // read; a fresh buffer, or one an interrupted call left behind, is cleared here
 
     int64_t rows_bound = (int64_t)c.k * c.b;
-    const int32_t *row_vertex = c.res->hops[0].row_vertex.as<int32_t>();
-    const int64_t *mb_rowoff = c.res->hops[0].mb_rowoff.as<int64_t>();
     BMS_TRY(csr->mb_tileoff.ensure(((size_t)c.k + 2) * sizeof(int64_t)));
 
     // Steady state: a recycled result that remembers the sizes of the same call shape lets every hop
     // be enqueued without a host round trip.  Buffers are then sized by the upper bound
     // rows * min(s, max degree) (always enough), tuning parameters by the remembered sizes.
-    const bool union_dst = (c.flags & BMS_UNION_DST) != 0;
-    const bool replace = (c.flags & BMS_NODEWISE_REPLACE) != 0;
     const std::vector<int32_t> shape = nodewise_shape(c, fanouts);
     bool no_wait = buckets && !c.fresh_result && c.res->hint_csr == csr && c.res->hint_shape == shape &&
                    (int32_t)c.res->hint_nnz.size() == c.L;
@@ -683,8 +843,20 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         }
         no_wait = total < (double)c.scratch_limit;
     }
+    const bool async = (c.flags & BMS_ASYNC) && no_wait && (seeds_by_sort || small_hops);
+    int64_t *host = c.res->host;
 
-    for (int32_t h = 0; h < c.L; ++h) {
+    bool seeds_checked = false;
+    if (small_hops > 0) {
+        BMS_TRY(run_small_hops(c, batches, fanouts, small_hops, host, &rows_bound));
+        tiles_planned = true;
+    } else {
+        BMS_TRY(stage_seeds(c, batches, prof, !seeds_by_sort));
+    }
+    const int32_t *row_vertex = (small_hops ? c.res->hops[small_hops - 1].col_vertex : c.res->hops[0].row_vertex).as<int32_t>();
+    const int64_t *mb_rowoff = (small_hops ? c.res->hops[small_hops - 1].mb_coloff : c.res->hops[0].mb_rowoff).as<int64_t>();
+
+    for (int32_t h = small_hops; h < c.L; ++h) {
         HopBufs &hb = c.res->hops[h];
         const int64_t tiles_bound = rows_bound / kRowTile + c.k;
         BMS_TRY(csr->row_beg.ensure((size_t)std::max<int64_t>(rows_bound, 1) * sizeof(int64_t)));
@@ -741,8 +913,9 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             nnz_tune = std::max<int64_t>(c.res->hint_nnz[h], 1);
         } else {
             BMS_TRY(read_scalars(c));
-            if (h == 0)
-                BMS_TRY(seed_flag_error(c));
+            if (!seeds_checked)
+                BMS_TRY(seed_flag_error(csr, csr->host_pinned, c.res->host));
+            seeds_checked = true;
             nnz = nnz_tune = host_slot(c, h, 0);
         }
         const int64_t ncols_bound = std::min<int64_t>(nnz, (int64_t)c.k * csr->n);
@@ -933,22 +1106,20 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     pn.shape = shape;
     pn.mode = mode;
     pn.table_built = table_built;
-    if ((c.flags & BMS_ASYNC) && no_wait && seeds_by_sort) {
-        // steady state, asynchronous: the sizes and flags travel to pinned memory of the result behind the kernels,
+    if (small_hops < c.L)
+        publish(c);
+    if (async) {
         // an event marks their arrival, and the first look at the result does what follows below
-        if (!c.res->host_scalars)
-            HIP_TRY(hipHostMalloc((void **)&c.res->host_scalars, 64 * sizeof(int64_t), hipHostMallocDefault));
         if (!c.res->done_ev)
             HIP_TRY(hipEventCreateWithFlags(&c.res->done_ev, hipEventDisableTiming));
-        HIP_TRY(hipMemcpyAsync(c.res->host_scalars, csr->scalars.p, 64 * sizeof(int64_t), hipMemcpyDeviceToHost, c.stream));
         HIP_TRY(hipEventRecord(c.res->done_ev, c.stream));
         c.res->deferred = std::move(pn);
         c.res->pending = true;
         return BMS_OK;
     }
-    BMS_TRY(read_scalars(c));
-    BMS_TRY(finish_nodewise(c.res, pn, csr->host_pinned, no_wait, redo));
-    if (!*redo && (!buckets || !seeds_by_sort))
+    HIP_TRY(hipStreamSynchronize(c.stream));
+    BMS_TRY(finish_nodewise(c.res, pn, host, !seeds_checked, redo));
+    if (!*redo && (!buckets || !(seeds_by_sort || small_hops)))
         csr->vs_clean = true;
     return BMS_OK;
 }
@@ -1158,7 +1329,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         } else {
             BMS_TRY(read_scalars(c));
             if (h == 0)
-                BMS_TRY(seed_flag_error(c));
+                BMS_TRY(seed_flag_error(csr, csr->host_pinned, c.res->host));
             D = host_slot(c, h, 3);
         }
         w.giveup = giveup;
@@ -1255,10 +1426,12 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         mb_rowoff = hb.mb_coloff.as<int64_t>();
         rows_bound = std::max<int64_t>(ncols_bound, 1);
     }
-    BMS_TRY(read_scalars(c));
+    publish(c);
+    HIP_TRY(hipStreamSynchronize(c.stream));
+    const int64_t *host = c.res->host;
     if (no_wait) {
-        BMS_TRY(seed_flag_error(c));
-        if ((int32_t)(csr->host_pinned[60] & 0xFFFFFFFF)) { // a size went past what the remembered call needed
+        BMS_TRY(seed_flag_error(csr, host, host));
+        if ((int32_t)(host[60] & 0xFFFFFFFF)) { // a size went past what the remembered call needed
             *redo = true;
             return BMS_OK;
         }
@@ -1268,13 +1441,13 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     c.res->hint_nnz.assign((size_t)c.L, 0);
     for (int32_t h = 0; h < c.L; ++h) {
         bms_hop_view &v = c.res->hops[h].view;
-        v.nnz = host_slot(c, h, 0);
-        v.ncols = host_slot(c, h, 1);
-        v.pnnz = host_slot(c, h, 2);
+        v.nnz = host[4 * h];
+        v.ncols = host[4 * h + 1];
+        v.pnnz = host[4 * h + 2];
         v.rows = h == 0 ? (int64_t)c.k * c.b : c.res->hops[h - 1].view.ncols;
         c.res->hint_nnz[h] = v.nnz;
         c.res->hint_pnnz[h] = v.pnnz;
-        c.res->hint_gathered[h] = host_slot(c, h, 3);
+        c.res->hint_gathered[h] = host[4 * h + 3];
     }
     c.res->hint_csr = csr;
     c.res->hint_shape = shape;
@@ -1369,7 +1542,7 @@ int sample_ladies_impl(CallCtx &c, const int32_t *batches, const int32_t *s_per_
         BMS_TRY(prof.end());
         BMS_TRY(read_scalars(c)); // D sizes the tile arrays of the gathered order
         if (h == 0)
-            BMS_TRY(seed_flag_error(c));
+            BMS_TRY(seed_flag_error(csr, csr->host_pinned, c.res->host));
         const int64_t D = host_slot(c, h, 3);
         BMS_TRY(csr->tile_off.ensure((size_t)(D / kGatherTile + 3) * sizeof(int64_t)));
         a.tile_off = csr->tile_off.as<int64_t>();
@@ -1654,7 +1827,7 @@ int bms_result_minibatch(bms_result *res, int32_t hop, int32_t i, bms_mb_view *v
     if (i < 0 || i >= res->k)
         return fail(BMS_EINVAL, "minibatch %d outside [0, %d)", i, res->k);
     const size_t stride = (size_t)res->k + 1;
-    if (res->mb_offsets.empty()) {
+    if (!res->host_off && res->mb_offsets.empty()) {
         HIP_TRY(hipSetDevice(res->device));
         std::vector<int64_t> host((size_t)res->L * 3 * stride);
         BMS_TRY(res->mb_edge_tmp.ensure(stride * sizeof(int64_t)));
@@ -1669,7 +1842,7 @@ int bms_result_minibatch(bms_result *res, int32_t hop, int32_t i, bms_mb_view *v
         res->mb_offsets.swap(host);
     }
     const bms_hop_view &v = res->hops[hop].view;
-    const int64_t *off = res->mb_offsets.data() + (size_t)hop * 3 * stride;
+    const int64_t *off = (res->host_off ? res->host + kHostScalars : res->mb_offsets.data()) + (size_t)hop * 3 * stride;
     bms_mb_view m{};
     m.row0 = off[i];
     m.rows = off[i + 1] - off[i];

@@ -26,6 +26,18 @@ struct Launch {
     int64_t scan_tmp_len = 0;
 };
 
+// What a call leaves for the host, written by its last kernel into host-visible memory: the call's 64 scalars, and per
+// hop the first row, entry and column of every minibatch (3 x (k + 1) values; off == nullptr: not wanted)
+constexpr int kPublishHops = 15;
+struct PublishArgs {
+    int32_t k, L;
+    const int64_t *scalars;
+    int64_t *host;
+    int64_t *off;
+    const int64_t *rowptr[kPublishHops], *rowoff[kPublishHops], *coloff[kPublishHops];
+};
+void launch_publish(const Launch &, const PublishArgs &);
+
 int grid_for(const Launch &L, int64_t blocks, int per_cu);
 // called by multi-kernel launchers before each kernel (group) so that it can be timed on its own
 using StageMark = std::function<void(const char *)>;
@@ -93,6 +105,48 @@ void launch_nw_relabel(const Launch &, const NwHop &, const VSet &);
 void launch_nw_strip_self(const Launch &, const int64_t *rowptr_in, const int32_t *col_in, const int64_t *rows,
                           int64_t rows_bound, int64_t *rowptr_out, int32_t *col_out, int32_t *row_self,
                           int64_t *nnz_slot);
+
+// Leading hops of a call whose minibatches fit one workgroup each (kernels_small.hip)
+constexpr int32_t kSmallCap = 16384;      // sampled edges (plus rows, with self_entry) of a minibatch's hop, at most
+constexpr int32_t kSmallMaxMb = 1024;     // minibatches: each adds up the sizes of the ones before it by itself
+constexpr int32_t kSmallMaxFanout = 32;   // one row per lane
+constexpr int kSmallHopsMax = 15;
+constexpr int kSmallBuckets = 16384;
+struct NwSmallHop {
+    int32_t s;
+    uint64_t hopkey;
+    int64_t *rowptr;     // rows + 1
+    int32_t *col;
+    int64_t *mb_coloff;  // k + 1
+    int32_t *col_vertex;
+    int32_t *row_self;   // with self_entry
+};
+struct NwSmall {
+    const int64_t *A_rowptr;
+    const int32_t *A_col;
+    int64_t n;
+    int32_t k, b, nhops, L;
+    uint32_t mb_base;
+    int32_t self_entry;
+    int32_t cap;              // LDS entries: no hop of a minibatch has more
+    int32_t seed_slots, seed_shift; // hash table of the seed check: a power of two >= 2 b and <= cap, 32 - its log2
+    int32_t idbits;           // bits of the largest vertex id
+    uint32_t bucket_mul;      // bucket of an id = id * bucket_mul >> 32 (0: the id itself), below kSmallBuckets
+    const int32_t *batches;   // device, k * b (may be row_vertex0)
+    int32_t *row_vertex0;     // k * b
+    int64_t *mb_rowoff0;      // k + 1
+    int32_t *seed_flags;      // host-visible: [0] set when a seed is out of range, [1] when one is repeated
+    unsigned long long *status; // nhops * k: epoch << 32 | entries << 16 | columns of the minibatch's hop
+    uint32_t epoch;
+    uint32_t *ticket;         // device counter: the next minibatch nobody works on
+    uint32_t ticket0;         // its value before this launch
+    int64_t *slots;           // the call's scalars, 4 per hop
+    int64_t *host_slots;      // the same in host-visible memory (null: not wanted)
+    int64_t *host_off;        // first row, entry and column of every minibatch, 3 x (k + 1) per hop, there as well (or null)
+    int64_t *next_tileoff;    // k + 2: row tiles of hop nhops (null: there is none)
+    NwSmallHop hop[kSmallHopsMax];
+};
+int launch_nw_small(const Launch &, const NwSmall &, bool replace); // -1: launch refused
 
 // EXTRACT ("remove empty columns", Sec. 4.1.3).  Main path: the sampled ids of every minibatch are cut into C
 // id-range segments, the segments are ranked in LDS, and the ranks travel back to the entries' positions through the

@@ -13,6 +13,27 @@ int grid_for(const Launch &L, int64_t blocks, int per_cu)
     return (int)(blocks < cap ? blocks : cap);
 }
 
+__global__ __launch_bounds__(256) void publish_kernel(PublishArgs a)
+{
+    const int h = blockIdx.x;
+    if (h == 0 && threadIdx.x < 64)
+        a.host[threadIdx.x] = a.scalars[threadIdx.x];
+    if (!a.off)
+        return;
+    int64_t *to = a.off + (int64_t)h * 3 * (a.k + 1);
+    for (int32_t i = threadIdx.x; i <= a.k; i += 256) {
+        const int64_t r = a.rowoff[h][i];
+        to[i] = r;
+        to[a.k + 1 + i] = a.rowptr[h][r];
+        to[2 * (a.k + 1) + i] = a.coloff[h][i];
+    }
+}
+
+void launch_publish(const Launch &L, const PublishArgs &a)
+{
+    hipLaunchKernelGGL(publish_kernel, dim3(a.L), dim3(256), 0, L.stream, a);
+}
+
 // ---------------------------------------------------------------------------------------------
 // CSR verification at load time.  flag bit 0: rowptr not monotone / wrong ends, bit 1: column out
 // of range, bit 2: row not strictly ascending.

@@ -19,38 +19,13 @@
 // the distinct picks; its length is only known after the draws, so nw_rows makes them too.
 #include "bms_device.h"
 #include "bms_internal.h"
+#include "nw_draws.h"
 
 #include <algorithm>
 
 namespace bms {
 
-// Independent draws (ITS with replacement on the unit weights of a row): s integers in [0, deg), kept sorted
-// in c[0..s) by one bubble pass per draw.  Returns the number of distinct values.
-template <int S>
-__device__ __forceinline__ int32_t replace_draws(uint64_t key, uint32_t deg, int32_t s, uint32_t (&c)[S])
-{
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-        if (j < s) {
-            c[j] = bounded32(draw32(key, (uint32_t)j), deg);
-#pragma unroll
-            for (int q = j; q > 0; --q) {
-                const uint32_t lo = min(c[q - 1], c[q]);
-                const uint32_t hi = max(c[q - 1], c[q]);
-                c[q - 1] = lo;
-                c[q] = hi;
-            }
-        }
-    }
-    int32_t m = 0;
-#pragma unroll
-    for (int j = 0; j < S; ++j)
-        if (j < s)
-            m += (j == 0 || c[j] != c[j - 1]) ? 1 : 0;
-    return m;
-}
-
-// The same for any s <= kMaxSampledFanout by one wave: the draws are written to `buf` (LDS, room for the next
+// Independent draws (replace_draws) for any s <= kMaxSampledFanout by one wave: the draws are written to `buf` (LDS, room for the next
 // power of two >= max(s, 64)), sorted there by a bitonic network, and the distinct values moved down to
 // buf[0..m) in ascending order.  Returns m (the same value in every lane).
 __device__ inline int32_t wave_replace_draws(volatile uint32_t *buf, uint64_t key, uint32_t deg, int32_t s, int lane)
@@ -231,11 +206,7 @@ void launch_nw_rows(const Launch &L, const NwHop &a)
 // ---------------------------------------------------------------------------------------------
 // SAMPLE, one row per lane, fanout <= S (compile-time capacity of the per-lane position list).
 //
-// Without-replacement rule: draw j is an integer x in [0, deg - j), the index of the pick among
-// the positions not chosen so far in ascending order (inverse-transform sampling on the unit
-// weights with the chosen entries zeroed).  Stepping x over every chosen position <= x, in
-// ascending order, turns it into the position; the list is kept sorted by one bubble pass,
-// which also leaves the row's output in ascending column order.
+// Draws: nw_draws.h.
 // ---------------------------------------------------------------------------------------------
 template <int S, bool SET, bool REPLACE>
 __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
@@ -318,23 +289,7 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
                     c[j] = (uint32_t)j;
             } else {
                 const uint64_t key = row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)a.row_vertex[r]);
-#pragma unroll
-                for (int j = 0; j < S; ++j) {
-                    if (j < s) {
-                        uint32_t x = bounded32(draw32(key, (uint32_t)j), (uint32_t)deg - (uint32_t)j);
-#pragma unroll
-                        for (int q = 0; q < j; ++q)
-                            x += (x >= c[q]) ? 1u : 0u;
-                        c[j] = x;
-#pragma unroll
-                        for (int q = j; q > 0; --q) {
-                            const uint32_t lo = min(c[q - 1], c[q]);
-                            const uint32_t hi = max(c[q - 1], c[q]);
-                            c[q - 1] = lo;
-                            c[q] = hi;
-                        }
-                    }
-                }
+                distinct_draws<S>(key, (uint32_t)deg, s, c);
             }
             const int32_t *__restrict__ src = a.A_col + beg;
 #pragma unroll
