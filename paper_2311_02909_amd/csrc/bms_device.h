@@ -99,6 +99,21 @@ __device__ inline T wave_sum(T v)
     return v;
 }
 
+// 64-lane bitonic sorting network, ascending by lane
+__device__ inline uint32_t wave_sort_u32(uint32_t c, int lane)
+{
+#pragma unroll
+    for (int kk = 2; kk <= kWave; kk <<= 1) {
+#pragma unroll
+        for (int j = kk >> 1; j > 0; j >>= 1) {
+            const uint32_t o = __shfl_xor(c, j, kWave);
+            const bool keep_min = ((lane & j) == 0) == ((lane & kk) == 0);
+            c = keep_min ? min(c, o) : max(c, o);
+        }
+    }
+    return c;
+}
+
 // Exclusive scan over the NT threads of a workgroup.  `smem` holds NT/64 values of T.
 // Contains two barriers; smem may be reused after the call returns on all threads
 // only after another barrier (the callers loop with barriers in between).

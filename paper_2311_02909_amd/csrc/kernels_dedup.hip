@@ -63,21 +63,6 @@ __device__ inline uint32_t bm_word_index(uint32_t W) { return ((((W >> 2) & 3u) 
 // per-word prefix (uint16): word q of lane l at halfword index q*64 + l
 __device__ inline uint32_t pre_index(uint32_t W) { return ((W & 15u) << 6) + (W >> 4); }
 
-// 64-lane bitonic sorting network, ascending by lane
-__device__ inline uint32_t wave_sort_u32(uint32_t c, int lane)
-{
-#pragma unroll
-    for (int kk = 2; kk <= kWave; kk <<= 1) {
-#pragma unroll
-        for (int j = kk >> 1; j > 0; j >>= 1) {
-            const uint32_t o = __shfl_xor(c, j, kWave);
-            const bool keep_min = ((lane & j) == 0) == ((lane & kk) == 0);
-            c = keep_min ? min(c, o) : max(c, o);
-        }
-    }
-    return c;
-}
-
 // A bin with more than 64 pairs: bitmap over its 2^15 ids in the wave's LDS.
 __device__ inline uint32_t rank_big_bin(uint32_t *wbm, uint16_t *wpre, uint64_t *__restrict__ pairs,
                                         uint64_t *__restrict__ utmp, uint32_t bin, uint32_t s, uint32_t e, int lane)

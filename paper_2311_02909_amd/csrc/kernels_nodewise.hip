@@ -122,16 +122,19 @@ __global__ __launch_bounds__(kRowTile) void nw_rows_kernel(NwHop a)
     }
 }
 
-// Independent draws with s > 32: extents by one row per lane as above, then one row per wave: draws sorted in
-// LDS, distinct ones counted; the count is kept per row (row_cnt) so that the sampling kernel can place the
-// rows before it repeats the draws.
-__global__ __launch_bounds__(kRowTile) void nw_rows_replace_wide_kernel(NwHop a)
+// Independent draws with s > 32: extents by one row per lane as above, then one row per wave: draws sorted (across the
+// lanes for s <= 64, in LDS above), distinct ones counted; the count is kept per row (row_cnt) so that the sampling
+// kernel can place the rows before it repeats the draws.
+constexpr int kWideRowsThreads = 1024;
+template <bool LANES>
+__global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(NwHop a)
 {
-    __shared__ uint32_t chosen_all[(kRowTile / kWave) * kMaxSampledFanout];
+    constexpr int NW = kWideRowsThreads / kWave;
+    __shared__ uint32_t chosen_all[LANES ? 1 : NW * kMaxSampledFanout];
     __shared__ int64_t wsum[kRowTile / kWave];
     __shared__ int32_t deg_of[kRowTile], vert_of[kRowTile], cnt_of[kRowTile];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    volatile uint32_t *buf = chosen_all + wave * kMaxSampledFanout;
+    volatile uint32_t *buf = chosen_all + (LANES ? 0 : wave * kMaxSampledFanout);
     const int64_t most = a.mb_tileoff[a.k + 1];
     for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x) {
         const int i = (int)(v % a.k);
@@ -156,23 +159,28 @@ __global__ __launch_bounds__(kRowTile) void nw_rows_replace_wide_kernel(NwHop a)
             vert_of[tid] = vtx;
         }
         __syncthreads();
-        for (int q = wave; q < nr; q += kRowTile / kWave) {
+        for (int q = wave; q < nr; q += NW) {
             int32_t m = 0;
-            if (deg_of[q] > 0)
-                m = wave_replace_draws(buf, row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)vert_of[q]),
-                                       (uint32_t)deg_of[q], a.s, lane);
+            if (deg_of[q] > 0) {
+                const uint64_t key = row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)vert_of[q]);
+                uint32_t pos;
+                m = LANES ? wave_replace_draws64(key, (uint32_t)deg_of[q], a.s, lane, pos)
+                          : wave_replace_draws(buf, key, (uint32_t)deg_of[q], a.s, lane);
+            }
             if (lane == 0)
                 cnt_of[q] = m;
         }
         __syncthreads();
-        int64_t cnt = 0;
-        if (tid < nr) {
-            a.row_cnt[r] = cnt_of[tid];
-            cnt = cnt_of[tid] + a.self_entry;
+        if (tid < kRowTile) {
+            int64_t cnt = 0;
+            if (tid < nr) {
+                a.row_cnt[r] = cnt_of[tid];
+                cnt = cnt_of[tid] + a.self_entry;
+            }
+            cnt = wave_sum(cnt);
+            if (lane == 0)
+                wsum[wave] = cnt;
         }
-        cnt = wave_sum(cnt);
-        if (lane == 0)
-            wsum[wave] = cnt;
         __syncthreads();
         if (tid == 0) {
             int64_t tot = 0;
@@ -199,8 +207,10 @@ void launch_nw_rows(const Launch &L, const NwHop &a)
         hipLaunchKernelGGL(nw_rows_kernel<16>, grid, block, 0, L.stream, a);
     else if (a.s <= 32)
         hipLaunchKernelGGL(nw_rows_kernel<32>, grid, block, 0, L.stream, a);
+    else if (a.s <= kWave)
+        hipLaunchKernelGGL(nw_rows_replace_wide_kernel<true>, dim3(grid_for(L, tiles, 2)), dim3(kWideRowsThreads), 0, L.stream, a);
     else
-        hipLaunchKernelGGL(nw_rows_replace_wide_kernel, dim3(grid_for(L, tiles, 2)), block, 0, L.stream, a);
+        hipLaunchKernelGGL(nw_rows_replace_wide_kernel<false>, dim3(grid_for(L, tiles, 1)), dim3(kWideRowsThreads), 0, L.stream, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -318,22 +328,30 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
 }
 
 // ---------------------------------------------------------------------------------------------
-// SAMPLE, one row per wave, any fanout: rows with degree <= s are copied whole; longer rows keep
-// their sorted chosen list in LDS (s <= kMaxSampledFanout).  For draw j the number c of chosen
-// positions that the pick steps over is the count of list entries p_t with p_t - t <= x
-// (p_t - t = unchosen positions before p_t, non-decreasing in t), found by binary search.
+// SAMPLE, one row per wave, any fanout: rows with degree <= s are copied whole; longer rows keep their sorted chosen
+// list across the wave's lanes in K registers (s <= 64 K; nw_draws.h), or, K = 0, in LDS (s <= kMaxSampledFanout).  In
+// LDS, for draw j the number c of chosen positions that the pick steps over is the count of list entries p_t with
+// p_t - t <= x (p_t - t = unchosen positions before p_t, non-decreasing in t), found by binary search.
+// A row's draws are one chain, so what counts is the instructions per draw and how many rows are in progress: across the
+// lanes a draw takes about 8 vector instructions and no trip to LDS, and `parts` workgroups share the rows of a tile so
+// that hops of few rows still fill the chip.  8 minibatches of 512, fanouts (40, 40), 2.4 M vertices: the two hops took
+// 547 + 1353 us with the list in LDS and one workgroup per tile, 9 + 73 us so.
 // ---------------------------------------------------------------------------------------------
-template <bool SET, bool REPLACE>
-__global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet vs)
+template <bool SET, bool REPLACE, int K>
+__global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet vs, int32_t parts)
 {
-    __shared__ uint32_t chosen_all[(kRowTile / kWave) * kMaxSampledFanout];
-    __shared__ int64_t wsum[kRowTile / kWave];
+    constexpr int NW = kRowTile / kWave;
+    __shared__ uint32_t chosen_all[K ? 1 : NW * kMaxSampledFanout];
+    __shared__ int64_t wsum[NW];
     __shared__ int64_t row_loc[kRowTile];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    volatile uint32_t *chosen = chosen_all + wave * kMaxSampledFanout;
-    const int64_t ntiles = a.mb_tileoff[a.k];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    volatile uint32_t *chosen = chosen_all + (K ? 0 : wave * kMaxSampledFanout);
+    const int64_t nwork = a.mb_tileoff[a.k] * parts;
     const int32_t s = a.s;
-    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    for (int64_t v = blockIdx.x; v < nwork; v += gridDim.x) {
+        const int64_t t = v / parts;
+        const int part = (int)(v % parts);
         const int i = locate_segment(a.mb_tileoff, a.k, t);
         const int64_t r0 = a.mb_rowoff[i] + (t - a.mb_tileoff[i]) * kRowTile;
         const int64_t rend = a.mb_rowoff[i + 1];
@@ -346,12 +364,12 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
         int64_t tot;
         const int64_t loc = block_exclusive_scan<int64_t, kRowTile>(cnt, wsum, tot);
         const int64_t base = a.tile_off[t];
-        if (r < rend)
+        if (r < rend && part == 0)
             a.out_rowptr[r] = base + loc;
         row_loc[tid] = base + loc;
         __syncthreads();
         uint32_t *__restrict__ words = vs.words + (int64_t)i * vs.nw;
-        for (int q = wave; q < kRowTile; q += kRowTile / kWave) { // rows of this tile, one per wave
+        for (int q = part * NW + wave; q < kRowTile; q += NW * parts) { // rows of this tile, one per wave
             const int64_t rr = r0 + q;
             if (rr >= rend)
                 break;
@@ -359,40 +377,47 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
             const int32_t deg = a.row_deg[rr];
             int32_t *__restrict__ dst = a.out_col + row_loc[q];
             const int32_t *__restrict__ src = a.A_col + beg;
+            auto put = [&](int32_t e, int32_t g) {
+                dst[e] = g;
+                if (SET)
+                    atomicOr(&words[g >> 5], 1u << (g & 31));
+            };
             if (a.self_entry && lane == 0) { // the row's own vertex, after its sampled ones (kept inside [0, n):
                                              // a bad seed is reported by the seed check, EXTRACT still gets a valid id)
                 int32_t g = a.row_vertex[rr];
                 if (g < 0 || (int64_t)g >= a.n)
                     g = 0;
-                dst[REPLACE ? a.row_cnt[rr] : (deg < s ? deg : s)] = g;
-                if (SET)
-                    atomicOr(&words[g >> 5], 1u << (g & 31));
+                put(REPLACE ? a.row_cnt[rr] : (deg < s ? deg : s), g);
             }
-            if (REPLACE) { // independent draws: the distinct picks, sorted by the wave in LDS
-                if (deg > 0) {
-                    const int32_t m = wave_replace_draws(
-                        chosen, row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)a.row_vertex[rr]), (uint32_t)deg, s,
-                        lane);
-                    for (int32_t e = lane; e < m; e += kWave) {
-                        const int32_t g = src[chosen[e]];
-                        dst[e] = g;
-                        if (SET)
-                            atomicOr(&words[g >> 5], 1u << (g & 31));
-                    }
+            if (REPLACE ? deg <= 0 : deg <= s) {
+                for (int32_t e = lane; e < deg; e += kWave)
+                    put(e, src[e]);
+                continue;
+            }
+            const uint64_t key = row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)a.row_vertex[rr]);
+            if (REPLACE) { // independent draws: the distinct picks, sorted by the wave
+                if (K == 1) {
+                    uint32_t pos;
+                    const int32_t m = wave_replace_draws64(key, (uint32_t)deg, s, lane, pos);
+                    if (lane < m)
+                        put(lane, src[pos]);
+                } else {
+                    const int32_t m = wave_replace_draws(chosen, key, (uint32_t)deg, s, lane);
+                    for (int32_t e = lane; e < m; e += kWave)
+                        put(e, src[chosen[e]]);
                     __builtin_amdgcn_wave_barrier();
                 }
                 continue;
             }
-            if (deg <= s) {
-                for (int32_t e = lane; e < deg; e += kWave) {
-                    const int32_t g = src[e];
-                    dst[e] = g;
-                    if (SET)
-                        atomicOr(&words[g >> 5], 1u << (g & 31));
-                }
+            if (K > 0) {
+                uint32_t pos[K ? K : 1];
+                wave_distinct_draws<(K ? K : 1)>(key, (uint32_t)deg, s, lane, pos);
+#pragma unroll
+                for (int u = 0; u < K; ++u)
+                    if (64 * u + lane < s)
+                        put(64 * u + lane, src[pos[u]]);
                 continue;
             }
-            const uint64_t key = row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)a.row_vertex[rr]);
             for (int32_t j = 0; j < s; ++j) {
                 const uint32_t x = bounded32(draw32(key, (uint32_t)j), (uint32_t)deg - (uint32_t)j);
                 // c = number of t in [0,j) with chosen[t] - t <= x   (all lanes compute the same value)
@@ -420,16 +445,32 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
                     chosen[c] = x + (uint32_t)c;
                 __builtin_amdgcn_wave_barrier();
             }
-            for (int32_t e = lane; e < s; e += kWave) {
-                const int32_t g = src[chosen[e]];
-                dst[e] = g;
-                if (SET)
-                    atomicOr(&words[g >> 5], 1u << (g & 31));
-            }
+            for (int32_t e = lane; e < s; e += kWave)
+                put(e, src[chosen[e]]);
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
     }
+}
+
+// Registers per lane by fanout; above 256 positions the list's upkeep costs more than the binary search in LDS.  With
+// independent draws only the one-register form is used (64 draws sorted across the lanes).
+template <bool SET, bool REPLACE>
+static void launch_nw_sample_wide(const Launch &L, const NwHop &a, const VSet &vs, int64_t tiles)
+{
+    const int64_t wanted = (int64_t)L.num_cu * 8;
+    int32_t parts = 1;
+    while (parts < kRowTile / (kRowTile / kWave) && tiles * parts < wanted)
+        parts <<= 1;
+    const dim3 block(kRowTile);
+    if (a.s <= kWave)
+        hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, 1>), dim3(grid_for(L, tiles * parts, 8)), block, 0, L.stream, a, vs, parts);
+    else if (!REPLACE && a.s <= 2 * kWave)
+        hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, REPLACE ? 0 : 2>), dim3(grid_for(L, tiles * parts, 8)), block, 0, L.stream, a, vs, parts);
+    else if (!REPLACE && a.s <= 4 * kWave)
+        hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, REPLACE ? 0 : 4>), dim3(grid_for(L, tiles * parts, 8)), block, 0, L.stream, a, vs, parts);
+    else
+        hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, 0>), dim3(grid_for(L, tiles * parts, 4)), block, 0, L.stream, a, vs, parts);
 }
 
 template <bool SET, bool REPLACE>
@@ -439,7 +480,7 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     const int64_t tiles = a.rows_bound / kRowTile + a.k;
     if (a.s > 32) {
         a.seg_cnt = nullptr; // one row per wave: its workgroups walk the tiles in stacked order, across minibatches
-        hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE>), dim3(grid_for(L, tiles, 2)), dim3(kRowTile), 0, L.stream, a, vs);
+        launch_nw_sample_wide<SET, REPLACE>(L, a, vs, tiles);
         return false;
     }
     int grid = grid_for(L, tiles, a.s <= 16 ? 8 : 4);

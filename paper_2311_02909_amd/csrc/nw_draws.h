@@ -55,4 +55,57 @@ __device__ __forceinline__ void distinct_draws(uint64_t key, uint32_t deg, int32
     }
 }
 
+// Draws without replacement by one wave, s < deg, s <= 64 K.  The sorted positions lie across the lanes (position t in
+// lane t % 64 of register t / 64), kept as e_t = position_t - t: the number of unchosen positions before it, which never
+// decreases with t.  A draw x steps over the c positions with e_t <= x and becomes position c, with e_c = x; those after it
+// move up by one place, which lowers their e by one.  All draws' x are computed at once, one per lane and register.
+// On return e[q] is the position of place 64 q + lane (places >= s: undefined).
+template <int K>
+__device__ __forceinline__ void wave_distinct_draws(uint64_t key, uint32_t deg, int32_t s, int lane, uint32_t (&e)[K])
+{
+    uint32_t x_of[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        const uint32_t j = (uint32_t)(64 * q + lane);
+        x_of[q] = bounded32(draw32(key, j), deg - j); // draws j >= s are never used
+        e[q] = 0xFFFFFFFFu; // no position: above every x, also 64 K places lower
+    }
+#pragma unroll
+    for (int qj = 0; qj < K; ++qj) {
+        const int32_t jn = min(64, s - 64 * qj);
+        for (int32_t j = 0; j < jn; ++j) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)x_of[qj], j);
+            int c = 0;
+#pragma unroll
+            for (int q = 0; q <= qj; ++q)
+                c += __popcll(__ballot(e[q] <= x));
+#pragma unroll
+            for (int q = qj; q >= 0; --q) {
+                const int carry = q ? __builtin_amdgcn_readlane((int)e[q - 1 >= 0 ? q - 1 : 0], kWave - 1) : 0;
+                const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp(carry, (int)e[q], 0x138 /* wave_shr:1 */, 0xF, 0xF, false) - 1u;
+                const int t = 64 * q + lane;
+                e[q] = t > c ? up : t == c ? x : e[q];
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+        e[q] += (uint32_t)(64 * q + lane);
+}
+
+// Independent draws by one wave, s <= 64: sorted across the lanes, lane 0 .. m - 1 of the result hold the distinct
+// positions in ascending order.  Returns m.
+__device__ __forceinline__ int32_t wave_replace_draws64(uint64_t key, uint32_t deg, int32_t s, int lane, uint32_t &pos)
+{
+    uint32_t v = lane < s ? bounded32(draw32(key, (uint32_t)lane), deg) : 0xFFFFFFFFu;
+    v = wave_sort_u32(v, lane);
+    const uint32_t prev = __shfl_up(v, 1, kWave);
+    const bool head = lane < s && (lane == 0 || v != prev);
+    const uint64_t heads = __ballot(head);
+    // lane x takes the value of the (x + 1)-th head
+    const int at = __popcll(heads & ((1ull << lane) - 1ull)); // heads before this lane
+    pos = (uint32_t)__builtin_amdgcn_ds_permute((head ? at : kWave - 1) * 4, (int)v);
+    return __popcll(heads);
+}
+
 } // namespace bms

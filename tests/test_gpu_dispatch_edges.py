@@ -1,0 +1,61 @@
+"""Sizes at which a call changes kernels, and the largest and smallest each kernel takes, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from conftest import random_batches, random_csr, skewed_csr
+from parity import assert_hops_equal
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(rowptr, col, batches, fanouts, seed=3, calls=2, **variant):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    ref = O.sample_nodewise(rowptr, col, batches, fanouts, seed, 5, **variant)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(calls):   # the first call of a shape and a recycled one
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, seed, mb_base=5, recycle=res, **variant)
+        assert_hops_equal(res.hops(), ref, what="k=%d b=%d fanouts=%s %s call %d" % (*batches.shape, fanouts, variant, call))
+    return res
+
+
+@pytest.mark.parametrize("variant", [{}, {"replace": True}, {"union_dst": True}])
+@pytest.mark.parametrize("s", [33, 63, 64, 65, 128, 129, 256, 257])
+def test_wide_fanouts_at_the_limits_of_the_lists_in_registers(s, variant):
+    rng = np.random.default_rng(500 + s)
+    rowptr, col = skewed_csr(3000, 200_000, rng)
+    _check(rowptr, col, random_batches(3000, 3, 70, rng), (s, 2), **variant)
+
+
+# b * s around the 16384 entries that one workgroup sorts; the hop after it on the chip-wide path or in the same launch
+@pytest.mark.parametrize("k,b,fanouts", [(2, 1024, (16,)), (2, 1025, (16, 2)), (3, 4096, (4, 3)), (1, 8192, (2, 2)),
+                                         (2, 8193, (1, 1)), (5, 1, (1, 1, 1)), (1024, 3, (5, 4)), (1025, 3, (5, 4)),
+                                         (4, 128, (8, 8, 2)), (4, 129, (8, 8, 2, 2)), (3, 512, (32, 2)), (3, 481, (17, 2))])
+def test_hops_of_one_workgroup_per_minibatch(k, b, fanouts):
+    rng = np.random.default_rng(b + k)
+    n = 20_000
+    rowptr, col = random_csr(n, 40.0, rng)
+    _check(rowptr, col, random_batches(n, k, b, rng), fanouts)
+    if b * (fanouts[0] + 1) <= 16400:
+        _check(rowptr, col, random_batches(n, min(k, 8), b, rng), fanouts, union_dst=True, calls=1)
+        _check(rowptr, col, random_batches(n, min(k, 8), b, rng), fanouts, replace=True, calls=1)
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 16384, 16385, 70_000, 3_000_000])
+def test_one_workgroup_hops_over_vertex_ranges_and_hubs(n):
+    # a few hubs that every row samples crowd one bucket of ids: the counting passes take over
+    rng = np.random.default_rng(n)
+    m = min(20 * n, 300_000)
+    hubs = rng.integers(0, n, size=3)
+    src = rng.integers(0, n, size=m)
+    dst = np.where(rng.random(m) < 0.5, hubs[rng.integers(0, 3, size=m)], rng.integers(0, n, size=m))
+    key = np.unique(src * n + dst)
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    np.add.at(rowptr, key // n + 1, 1)
+    rowptr, col = np.cumsum(rowptr), (key % n).astype(np.int32)
+    b = min(n, 300)
+    for variant in ({}, {"union_dst": True}):
+        _check(rowptr, col, random_batches(n, 3, b, rng, candidates=np.unique(key // n) if len(np.unique(key // n)) >= b else None),
+               (6, 3), **variant)
