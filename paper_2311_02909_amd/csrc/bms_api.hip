@@ -702,6 +702,7 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
     a.L = c.L;
     a.mb_base = c.mb_base;
     a.self_entry = self;
+    a.flat = csr->nnz < (1LL << 32) ? 1 : 0;
     HopBufs &h0 = c.res->hops[0];
     BMS_TRY(h0.row_vertex.ensure((size_t)c.k * c.b * sizeof(int32_t)));
     BMS_TRY(h0.mb_rowoff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
@@ -889,6 +890,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         a.rows_bound = rows_bound;
         a.self_entry = union_dst ? 1 : 0;
         a.replace = replace ? 1 : 0;
+        a.flat = csr->nnz < (1LL << (union_dst ? 31 : 32)) ? 1 : 0;
         if (replace && a.s > 32) {
             BMS_TRY(csr->row_cnt.ensure((size_t)std::max<int64_t>(rows_bound, 1) * sizeof(int32_t)));
             a.row_cnt = csr->row_cnt.as<int32_t>();

@@ -86,6 +86,7 @@ struct NwHop {
     int32_t max_degree;
     int32_t self_entry;        // 1: every row carries its own vertex as one more entry after the sampled ones
     int32_t replace;           // 1: the s draws of a row are independent, the row keeps the distinct picks
+    int32_t flat;              // 1: places in A_col fit the 32-bit words that the sampling kernel stages (31 with self_entry)
     int32_t *row_cnt;          // scratch, rows: distinct picks per row (only with replace and s > 32)
     // EXTRACT's count of sampled ids per (minibatch, id-range segment), taken while the ids are staged in LDS
     // (nullptr: not wanted); the caller has zeroed the counters
@@ -128,6 +129,7 @@ struct NwSmall {
     int32_t k, b, nhops, L;
     uint32_t mb_base;
     int32_t self_entry;
+    int32_t flat;             // 1: places in A_col fit 32 bits
     int32_t cap;              // LDS entries: no hop of a minibatch has more
     int32_t seed_slots, seed_shift; // hash table of the seed check: a power of two >= 2 b and <= cap, 32 - its log2
     int32_t idbits;           // bits of the largest vertex id

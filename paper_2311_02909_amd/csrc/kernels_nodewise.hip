@@ -217,11 +217,20 @@ void launch_nw_rows(const Launch &L, const NwHop &a)
 // SAMPLE, one row per lane, fanout <= S (compile-time capacity of the per-lane position list).
 //
 // Draws: nw_draws.h.
+//
+// What bounds it is the number of memory lines that a compute unit can wait for at a time (about 92, by the counters: reads
+// times latency over time), so what counts is how few lines are asked for, and how near they are.  The chosen positions are
+// laid out in LDS first and read with the picks of a row in neighbouring lanes: picks on one line are one request, where a
+// lane that reads its row's picks one after the other asks for the line again unless the compute unit's 32 KB still hold it.
+// Last hop of 256 x 1024 seeds, (15, 10, 5), 111 M vertices: 943 us so far, 856 us by the layout, 742 us with four workgroups
+// per compute unit as well (launch_nw_sample_impl); 128 minibatches on 8.7 M vertices of 154 times the degree: 1429 -> 1123 us.
 // ---------------------------------------------------------------------------------------------
+constexpr uint32_t kSelfMark = 0x80000000u; // staged entry: a vertex id, not a place in A_col
+constexpr int kGatherUnroll = 5;
 template <int S, bool SET, bool REPLACE>
 __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
 {
-    __shared__ int32_t stage[kRowTile * (S + 1)]; // + 1: the row's own vertex when rows carry it
+    __shared__ uint32_t stage[kRowTile * (S + 1)]; // + 1: the row's own vertex when rows carry it
     __shared__ int32_t wsum[kRowTile / kWave];
     __shared__ uint32_t seg_hist[kMaxFusedSegments]; // sampled ids per id-range segment, of this workgroup's minibatch
     __shared__ uint16_t seg_tab_l[kMaxCells + 1];    // segment of every cell of ids, when the segments differ in width
@@ -231,6 +240,8 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
     const bool count = a.seg_cnt != nullptr; // then gridDim.x is a multiple of k: every tile of this workgroup belongs
                                              // to minibatch blockIdx.x % k
     const bool by_table = count && a.seg_tab != nullptr;
+    const bool flat = a.flat != 0;
+    const uint32_t self_mark = a.self_entry ? kSelfMark : 0u;
     if (count) {
         for (int c = tid; c < a.seg_C; c += kRowTile)
             seg_hist[c] = 0;
@@ -281,41 +292,44 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
             a.out_rowptr[r] = base + loc;
         if (valid && a.self_entry) { // a seed outside [0, n) is reported by the seed check; EXTRACT still gets a valid id
             const int32_t self = a.row_vertex[r];
-            stage[loc + cnt] = (self >= 0 && (int64_t)self < a.n) ? self : 0;
+            stage[loc + cnt] = ((self >= 0 && (int64_t)self < a.n) ? (uint32_t)self : 0u) | (flat ? kSelfMark : 0u);
         }
-        if (REPLACE) {
-            if (cnt > 0) {
-                const int32_t *__restrict__ src = a.A_col + beg;
-                int32_t m = 0;
-#pragma unroll
-                for (int j = 0; j < S; ++j)
-                    if (j < s && (j == 0 || c[j] != c[j - 1]))
-                        stage[loc + m++] = src[c[j]];
-            }
-        } else if (cnt > 0) {
-            if (deg <= s) {
-#pragma unroll
-                for (int j = 0; j < S; ++j)
-                    c[j] = (uint32_t)j;
-            } else {
-                const uint64_t key = row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)a.row_vertex[r]);
-                distinct_draws<S>(key, (uint32_t)deg, s, c);
-            }
+        if (cnt > 0) {
+            if (!REPLACE && deg > s)
+                distinct_draws<S>(row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)a.row_vertex[r]), (uint32_t)deg, s, c);
             const int32_t *__restrict__ src = a.A_col + beg;
+            int32_t m = 0;
 #pragma unroll
-            for (int j = 0; j < S; ++j)
-                if (j < cnt)
-                    stage[loc + j] = src[c[j]];
+            for (int j = 0; j < S; ++j) {
+                const uint32_t at = !REPLACE && deg <= s ? (uint32_t)j : c[j];
+                if (REPLACE ? (j < s && (j == 0 || c[j] != c[j - 1])) : j < cnt)
+                    stage[loc + m++] = flat ? (uint32_t)beg + at : (uint32_t)src[at];
+            }
         }
         __syncthreads();
         uint32_t *__restrict__ words = vs.words + (int64_t)i * vs.nw;
-        for (int32_t e = tid; e < tot; e += kRowTile) {
-            const int32_t g = stage[e];
-            a.out_col[base + e] = g;
-            if (SET)
-                atomicOr(&words[g >> 5], 1u << (g & 31));
-            if (count)
-                atomicAdd(&seg_hist[by_table ? (uint32_t)seg_tab_l[(uint32_t)g >> a.seg_shift] : (uint32_t)g >> a.seg_shift], 1u);
+        for (int32_t e0 = tid; e0 < tot; e0 += kGatherUnroll * kRowTile) {
+            uint32_t g[kGatherUnroll];
+#pragma unroll
+            for (int u = 0; u < kGatherUnroll; ++u) {
+                const int32_t e = e0 + u * kRowTile;
+                if (e < tot) {
+                    g[u] = stage[e];
+                    if (flat)
+                        g[u] = (g[u] & self_mark) ? g[u] & ~kSelfMark : (uint32_t)a.A_col[g[u]];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kGatherUnroll; ++u) {
+                const int32_t e = e0 + u * kRowTile;
+                if (e < tot) {
+                    a.out_col[base + e] = (int32_t)g[u];
+                    if (SET)
+                        atomicOr(&words[g[u] >> 5], 1u << (g[u] & 31u));
+                    if (count)
+                        atomicAdd(&seg_hist[by_table ? (uint32_t)seg_tab_l[g[u] >> a.seg_shift] : g[u] >> a.seg_shift], 1u);
+                }
+            }
         }
         __syncthreads();
     }
@@ -483,10 +497,13 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
         launch_nw_sample_wide<SET, REPLACE>(L, a, vs, tiles);
         return false;
     }
-    int grid = grid_for(L, tiles, a.s <= 16 ? 8 : 4);
+    // Four workgroups per compute unit: their 1024 rows hold more reads than the unit keeps in flight (about 92), and the
+    // fewer rows are in progress on the chip, the narrower the part of A that the minibatches read at the same time: with
+    // eight, it no longer fits the 256 MB last-level cache on the larger graphs.
+    int grid = grid_for(L, tiles, 4);
     // counting per segment needs every workgroup to stay with one minibatch: tile v belongs to minibatch v % k,
     // so a grid that is a multiple of k does it
-    if (a.seg_cnt && a.seg_C <= kMaxFusedSegments && a.k <= L.num_cu * (a.s <= 16 ? 8 : 4))
+    if (a.seg_cnt && a.seg_C <= kMaxFusedSegments && a.k <= L.num_cu * 8)
         grid = std::max(grid / a.k, 1) * a.k;
     else
         a.seg_cnt = nullptr;

@@ -28,6 +28,7 @@ constexpr int kSmBins = 256;                   // a counting pass takes 8 bits
 constexpr int kSmBuckets = kSmallBuckets;
 constexpr int kSmCrowd = 64;                   // ids per bucket, at most
 constexpr int kSmWork = kSmBuckets / 4 + kSmBuckets / 8; // words: bucket counters and starts, or the counters of the passes
+constexpr int kSmGather = 8;                    // reads of A_col in flight per lane
 constexpr uint32_t kSmEmpty = 0xFFFFFFFFu;
 static_assert(kSmWork >= kSmWaves * kSmBins && kSmWork >= 2 * kSmallCap / kWave && kSmBuckets == 16 * kSmThreads, "work area out of step");
 
@@ -62,34 +63,42 @@ __device__ __forceinline__ int32_t small_sample_rows(const NwSmall &a, uint64_t 
                 key[r] = (v >= 0 && (int64_t)v < a.n) ? (uint32_t)v : 0u;
         }
         if (cnt > 0) {
-            const int32_t *__restrict__ src = a.A_col + beg;
             uint32_t *dst = key + (a.self_entry ? R : 0) + loc;
-            if (REPLACE) {
+            if (!REPLACE && deg > s)
+                distinct_draws<S>(row_key(hopkey, mb, (uint32_t)v), (uint32_t)deg, s, c);
+            if (a.flat) { // the neighbours follow below
                 int32_t m = 0;
 #pragma unroll
                 for (int j = 0; j < S; ++j)
-                    if (j < s && (j == 0 || c[j] != c[j - 1]))
-                        dst[m++] = (uint32_t)src[c[j]];
+                    if (REPLACE ? (j < s && (j == 0 || c[j] != c[j - 1])) : j < cnt)
+                        dst[m++] = (uint32_t)beg + (!REPLACE && deg <= s ? (uint32_t)j : c[j]);
             } else {
-                if (deg <= s) {
+                const int32_t *__restrict__ src = a.A_col + beg;
+                int32_t m = 0;
 #pragma unroll
-                    for (int j = 0; j < S; ++j)
-                        c[j] = (uint32_t)j;
-                } else {
-                    distinct_draws<S>(row_key(hopkey, mb, (uint32_t)v), (uint32_t)deg, s, c);
-                }
-#pragma unroll
-                for (int j0 = 0; j0 < S; j0 += 16) { // 16 loads in flight per lane: more addresses than that do not fit
-#pragma unroll
-                    for (int j = j0; j < j0 + 16 && j < S; ++j)
-                        if (j < cnt)
-                            dst[j] = (uint32_t)src[c[j]];
-                    if (S > 16)
-                        __builtin_amdgcn_sched_barrier(0);
+                for (int j = 0; j < S; ++j) {
+                    if (REPLACE ? (j < s && (j == 0 || c[j] != c[j - 1])) : j < cnt)
+                        dst[m++] = (uint32_t)src[!REPLACE && deg <= s ? (uint32_t)j : c[j]];
+                    __builtin_amdgcn_sched_barrier(0); // addresses one at a time: they do not all fit the registers
                 }
             }
         }
         run += (int32_t)total;
+    }
+    if (a.flat) { // places in A_col -> the neighbours there, the picks of a row in neighbouring lanes (one request per line)
+        uint32_t *entry = key + (a.self_entry ? R : 0);
+        __syncthreads();
+        for (int32_t e0 = tid; e0 < run; e0 += kSmGather * kSmThreads) {
+            uint32_t g[kSmGather];
+#pragma unroll
+            for (int u = 0; u < kSmGather; ++u)
+                if (e0 + u * kSmThreads < run)
+                    g[u] = (uint32_t)a.A_col[entry[e0 + u * kSmThreads]];
+#pragma unroll
+            for (int u = 0; u < kSmGather; ++u)
+                if (e0 + u * kSmThreads < run)
+                    entry[e0 + u * kSmThreads] = g[u];
+        }
     }
     return run;
 }

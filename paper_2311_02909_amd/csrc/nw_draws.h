@@ -39,18 +39,19 @@ __device__ __forceinline__ void distinct_draws(uint64_t key, uint32_t deg, int32
 {
 #pragma unroll
     for (int j = 0; j < S; ++j) {
-        uint32_t x = bounded32(draw32(key, (uint32_t)j), deg - (uint32_t)j);
+        if (j < s) { // the same for all lanes
+            uint32_t x = bounded32(draw32(key, (uint32_t)j), deg - (uint32_t)j);
 #pragma unroll
-        for (int q = 0; q < j; ++q)
-            x += (x >= c[q]) ? 1u : 0u;
-        x = j < s ? x : 0xFFFFFFFFu;
-        c[j] = x;
+            for (int q = 0; q < j; ++q)
+                x += (x >= c[q]) ? 1u : 0u;
+            c[j] = x;
 #pragma unroll
-        for (int q = j; q > 0; --q) {
-            const uint32_t lo = min(c[q - 1], c[q]);
-            const uint32_t hi = max(c[q - 1], c[q]);
-            c[q - 1] = lo;
-            c[q] = hi;
+            for (int q = j; q > 0; --q) {
+                const uint32_t lo = min(c[q - 1], c[q]);
+                const uint32_t hi = max(c[q - 1], c[q]);
+                c[q - 1] = lo;
+                c[q] = hi;
+            }
         }
     }
 }

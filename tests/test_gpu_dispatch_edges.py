@@ -59,3 +59,28 @@ def test_one_workgroup_hops_over_vertex_ranges_and_hubs(n):
     for variant in ({}, {"union_dst": True}):
         _check(rowptr, col, random_batches(n, 3, b, rng, candidates=np.unique(key // n) if len(np.unique(key // n)) >= b else None),
                (6, 3), **variant)
+
+
+def test_places_beyond_32_bits():
+    # a closed set of vertices whose lists lie behind 2^32 entries: the kernels cannot stage their places in 32-bit words.
+    # The entries before it are the lists of vertices that nothing leads to, so the oracle gets the graph without them.
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(77)
+    pad, m = 65536, 3000
+    rowptr, col = skewed_csr(m, 90_000, rng)
+    n = pad + m
+    small_rowptr = np.concatenate([np.zeros(pad, dtype=np.int64), rowptr])
+    small_col = (col + pad).astype(np.int32)
+    big_rowptr = np.concatenate([np.arange(pad, dtype=np.int64) * pad, rowptr + pad * pad])
+    big_col = torch.empty(pad * pad + len(col), dtype=torch.int32, device="cuda")
+    big_col[:pad * pad].view(pad, pad)[:] = torch.arange(pad, dtype=torch.int32, device="cuda")
+    big_col[pad * pad:] = torch.from_numpy(small_col).cuda()
+    csr = bms.Csr(torch.from_numpy(big_rowptr).cuda(), big_col)
+    candidates = np.arange(pad, n)
+    for b, fanouts in ((64, (5, 5)), (700, (20, 10)), (300, (40, 30))):
+        batches = random_batches(n, 3, b, rng, candidates=candidates)
+        for variant in ({}, {"union_dst": True}, {"replace": True}):
+            ref = O.sample_nodewise(small_rowptr, small_col, batches, fanouts, 9, **variant)
+            got = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 9, **variant)
+            assert_hops_equal(got.hops(), ref, what="b=%d fanouts=%s %s" % (b, fanouts, variant))
