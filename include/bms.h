@@ -19,9 +19,9 @@
  *     L (the batch vertices), params[0] applies there.
  *   - Pointers marked "device" are HIP device pointers on the current device; "host"
  *     are ordinary host pointers.  `batches` may be either (detected).
- *   - Work is enqueued on opts->stream; a call returns after the stream has drained
- *     (it reads the output sizes back), so result pointers are immediately readable
- *     by any stream that is ordered after that point.
+ *   - Work is enqueued on opts->stream; a call returns when its last kernel has left the
+ *     output sizes in host memory and every kernel before it is done, so result pointers
+ *     are immediately readable by any stream that is ordered after that point.
  *   - With BMS_ASYNC a node-wise call that recycles a result of the same call shape (same csr, k, b,
  *     fanouts, variant flags) returns as soon as its kernels are enqueued: the sizes, the seed check and
  *     the device times are read when the result is first looked at -- every accessor of a result

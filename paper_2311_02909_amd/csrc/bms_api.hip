@@ -4,6 +4,8 @@
 #include "bms_internal.h"
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -26,7 +28,10 @@ constexpr int64_t kNoWaitEntries = 32LL << 20; // result buffers up to this many
 constexpr double kBitmapIdsPerEntry = 128.0; // EXTRACT ranks by bitmap when a minibatch samples at least n / this many ids
                                             // (measured: by bitmap wins at 4..15 ids of [0, n) per sampled id, by counting at 580)
 constexpr int32_t kHostScalars = 72; // the 64 scalars of a call, then the seed flags of the calls that check seeds in their
-                                    // first kernel: two 32-bit words that it sets in host memory (range, repeat)
+                                    // first kernel: two 32-bit words that it sets in host memory (range, repeat); then
+                                    // the word that says that all of it has arrived
+constexpr int kArrivedSlot = 66;
+constexpr int64_t kSpinMicros = 20000; // how long a call looks at that word before it leaves the waiting to the runtime
 constexpr size_t kMostHostOffsets = 1 << 16; // per-minibatch offsets that a call leaves in host memory: at most (512 KB)
 constexpr int64_t kScanTmpLen = 1 << 17; // partial sums of multi-workgroup scans: arrays up to 2^29 values
 
@@ -237,6 +242,7 @@ struct bms_result {
     size_t host_cap = 0;
     bool host_off = false;
     PendingNodewise deferred;
+    int64_t arrival = 0; // what the last kernel of the current attempt writes to the block's kArrivedSlot
 };
 
 namespace {
@@ -486,9 +492,15 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
         HIP_TRY(hipHostMalloc((void **)&c.res->host, values * sizeof(int64_t), hipHostMallocMapped));
         c.res->host_cap = values;
     }
+        c.res->host[kArrivedSlot] = c.res->arrival;
     c.res->host_off = false;
     c.res->host[64] = 0;
     BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
+    BMS_TRY(csr->sm_ticket.ensure(256));
+    if (csr->sm_ticket.grew) {
+        HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
+        csr->sm_taken = 0;
+    }
     return BMS_OK;
 }
 
@@ -566,10 +578,44 @@ int seed_flag_error(const bms_csr *csr, const int64_t *scalars, const int64_t *f
 }
 
 // The call's scalars and the minibatches' offsets -> pinned memory of the result, in stream order.
+// Waits for what the call's last kernel writes to the result's pinned block.  The runtime's own wait sleeps: it costs 10 to
+// 50 us more than looking at the word (a call of 4 x 64 seeds takes 25 us on the device).  A fault or a stream that is
+// done for another reason ends the wait as well: the stream is asked now and then.
+int wait_arrival(CallCtx &c)
+{
+    const volatile int64_t *word = c.res->host + kArrivedSlot;
+    const auto start = std::chrono::steady_clock::now();
+    int64_t asked = 0;
+    for (uint32_t turn = 1; *word != c.res->arrival; ++turn) {
+        __builtin_ia32_pause();
+        if (turn % 64)
+            continue;
+        const int64_t us = std::chrono::duration_cast<std::chrono::microseconds>(std::chrono::steady_clock::now() - start).count();
+        if (us > kSpinMicros)
+            break;
+        if (us - asked > 5000) {
+            asked = us;
+            const hipError_t e = hipStreamQuery(c.stream);
+            if (e != hipErrorNotReady)
+                break;
+            (void)hipGetLastError();
+        }
+    }
+    if (*word != c.res->arrival || !c.res->stages.empty()) // (the events of a profile have to be done)
+        HIP_TRY(hipStreamSynchronize(c.stream));
+    std::atomic_thread_fence(std::memory_order_acquire);
+    if (*word != c.res->arrival)
+        return fail(BMS_EHIP, "the call's kernels did not run to their end");
+    return BMS_OK;
+}
+
 void publish(CallCtx &c)
 {
     PublishArgs p{};
     p.k = c.k;
+    p.arrived = c.res->host + kArrivedSlot;
+    p.arrival = c.res->arrival;
+    p.done = reinterpret_cast<uint32_t *>(c.csr->sm_ticket.as<uint32_t>() + 1);
     p.L = c.L;
     p.scalars = c.csr->scalars.as<int64_t>();
     p.host = c.res->host;
@@ -762,12 +808,9 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
         c.res->host_off = a.host_off != nullptr;
         host[63] = 0;
     }
+        a.arrived = host + kArrivedSlot;
+        a.arrival = c.res->arrival;
     a.next_tileoff = nhops < c.L ? csr->mb_tileoff.as<int64_t>() : nullptr;
-    BMS_TRY(csr->sm_ticket.ensure(256));
-    if (csr->sm_ticket.grew) {
-        HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
-        csr->sm_taken = 0;
-    }
     BMS_TRY(csr->sm_status.ensure((size_t)nhops * c.k * sizeof(uint64_t)));
     if (csr->sm_status.grew || csr->sm_epoch == 0xFFFFFFFFu) {
         HIP_TRY(hipMemsetAsync(csr->sm_status.p, 0, csr->sm_status.cap, c.stream));
@@ -811,6 +854,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     const bool union_dst = (c.flags & BMS_UNION_DST) != 0;
     const bool replace = (c.flags & BMS_NODEWISE_REPLACE) != 0;
     const int32_t small_hops = leading_small_hops(c, fanouts);
+    ++c.res->arrival;
     if (!buckets || !(seeds_by_sort || small_hops))
         BMS_TRY(setup_vset(c));
     if (buckets && small_hops < c.L) {
@@ -1119,7 +1163,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         c.res->pending = true;
         return BMS_OK;
     }
-    HIP_TRY(hipStreamSynchronize(c.stream));
+    BMS_TRY(wait_arrival(c));
     BMS_TRY(finish_nodewise(c.res, pn, host, !seeds_checked, redo));
     if (!*redo && (!buckets || !(seeds_by_sort || small_hops)))
         csr->vs_clean = true;
@@ -1301,6 +1345,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.bounds_t = csr->lw_bounds.as<uint32_t>();
         w.win_wt = csr->lw_win.as<uint64_t>();
         w.win_woff = w.win_wt + nw;
+    ++c.res->arrival;
         w.win_poff = reinterpret_cast<int64_t *>(w.win_woff + nw);
         w.win_cnt = reinterpret_cast<uint32_t *>(w.win_poff + nw);
         w.win_added = w.win_cnt + nw;
@@ -1429,7 +1474,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         rows_bound = std::max<int64_t>(ncols_bound, 1);
     }
     publish(c);
-    HIP_TRY(hipStreamSynchronize(c.stream));
+    BMS_TRY(wait_arrival(c));
     const int64_t *host = c.res->host;
     if (no_wait) {
         BMS_TRY(seed_flag_error(csr, host, host));

@@ -140,6 +140,21 @@ __device__ inline T block_exclusive_scan(T v, T *smem, T &total)
     return before + inc - v;
 }
 
+// Called by all threads of each of a launch's `parts` workgroups when the workgroup has written everything: the last of
+// them writes `arrival` to *arrived, in host memory, behind all the writes.  *done is zero before and after.
+__device__ inline void announce(uint32_t *done, uint32_t parts, int64_t *arrived, int64_t arrival)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // every wave's writes have left it; one thread then releases them all
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence_system();
+        if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == parts - 1u) {
+            __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(arrived, arrival, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
 // Largest i in [0,k) with off[i] <= t, given off[0] <= t < off[k] (off ascending, k >= 1).
 __device__ inline int locate_segment(const int64_t *__restrict__ off, int k, int64_t t)
 {

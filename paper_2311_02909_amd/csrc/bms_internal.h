@@ -27,13 +27,16 @@ struct Launch {
 };
 
 // What a call leaves for the host, written by its last kernel into host-visible memory: the call's 64 scalars, and per
-// hop the first row, entry and column of every minibatch (3 x (k + 1) values; off == nullptr: not wanted)
+// hop the first row, entry and column of every minibatch (3 x (k + 1) values; off == nullptr: not wanted); when all of it
+// is there, the value `arrival` in *arrived.  `done`: a device word that is zero between launches
 constexpr int kPublishHops = 15;
 struct PublishArgs {
     int32_t k, L;
     const int64_t *scalars;
     int64_t *host;
     int64_t *off;
+    int64_t *arrived, arrival;
+    uint32_t *done;
     const int64_t *rowptr[kPublishHops], *rowoff[kPublishHops], *coloff[kPublishHops];
 };
 void launch_publish(const Launch &, const PublishArgs &);
@@ -140,7 +143,8 @@ struct NwSmall {
     int32_t *seed_flags;      // host-visible: [0] set when a seed is out of range, [1] when one is repeated
     unsigned long long *status; // nhops * k: epoch << 32 | entries << 16 | columns of the minibatch's hop
     uint32_t epoch;
-    uint32_t *ticket;         // device counter: the next minibatch nobody works on
+    int64_t *arrived, arrival; // with host_slots: the value that says that everything is written, and where it goes
+    uint32_t *ticket;         // device counter: the next minibatch nobody works on; the word after it: minibatches done
     uint32_t ticket0;         // its value before this launch
     int64_t *slots;           // the call's scalars, 4 per hop
     int64_t *host_slots;      // the same in host-visible memory (null: not wanted)

@@ -18,15 +18,16 @@ __global__ __launch_bounds__(256) void publish_kernel(PublishArgs a)
     const int h = blockIdx.x;
     if (h == 0 && threadIdx.x < 64)
         a.host[threadIdx.x] = a.scalars[threadIdx.x];
-    if (!a.off)
-        return;
-    int64_t *to = a.off + (int64_t)h * 3 * (a.k + 1);
-    for (int32_t i = threadIdx.x; i <= a.k; i += 256) {
-        const int64_t r = a.rowoff[h][i];
-        to[i] = r;
-        to[a.k + 1 + i] = a.rowptr[h][r];
-        to[2 * (a.k + 1) + i] = a.coloff[h][i];
+    if (a.off) {
+        int64_t *to = a.off + (int64_t)h * 3 * (a.k + 1);
+        for (int32_t i = threadIdx.x; i <= a.k; i += 256) {
+            const int64_t r = a.rowoff[h][i];
+            to[i] = r;
+            to[a.k + 1 + i] = a.rowptr[h][r];
+            to[2 * (a.k + 1) + i] = a.coloff[h][i];
+        }
     }
+    announce(a.done, (uint32_t)a.L, a.arrived, a.arrival);
 }
 
 void launch_publish(const Launch &L, const PublishArgs &a)

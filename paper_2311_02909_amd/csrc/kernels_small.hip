@@ -445,6 +445,8 @@ __global__ __launch_bounds__(kSmThreads) void nw_small_kernel(NwSmall a)
         R = (int32_t)U;
         __syncthreads(); // the next frontier is in memory for every wave of this workgroup; LDS is free
     }
+    if (a.arrived)
+        announce(a.ticket + 1, (uint32_t)a.k, a.arrived, a.arrival);
 }
 
 int launch_nw_small(const Launch &L, const NwSmall &a, bool replace)
