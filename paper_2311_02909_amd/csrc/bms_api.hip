@@ -171,6 +171,7 @@ struct bms_csr {
     BMS_BUF(dd_pairs); BMS_BUF(dd_utmp); BMS_BUF(dd_uniq); BMS_BUF(dd_edgeoff); BMS_BUF(dd_count); BMS_BUF(dd_back);
     BMS_BUF(dd_tileoff); BMS_BUF(dd_cursor); BMS_BUF(dd_seg); BMS_BUF(dd_runs); BMS_BUF(dd_segcnt); BMS_BUF(dd_done); BMS_BUF(dd_hist); // EXTRACT
     bool segcnt_clean = false; // every segment counter zero (kept so by the kernels; lost when a call is interrupted)
+    BMS_BUF(rg_bits); BMS_BUF(rg_pre); BMS_BUF(rg_count); // EXTRACT by vertex ranges
     BMS_BUF(un_rowptr); BMS_BUF(un_col); // BMS_UNION_DST: the hop's CSR while its rows still carry their own vertex
     BMS_BUF(row_cnt);                    // BMS_NODEWISE_REPLACE with a fanout above 32: distinct picks per row
     BMS_BUF(lw_bounds); BMS_BUF(lw_win); BMS_BUF(lw_tmpcol); BMS_BUF(lw_parts); BMS_BUF(lw_sel); BMS_BUF(lw_xtmp);
@@ -241,8 +242,8 @@ struct bms_result {
     int64_t *host = nullptr;
     size_t host_cap = 0;
     bool host_off = false;
-    PendingNodewise deferred;
     int64_t arrival = 0; // what the last kernel of the current attempt writes to the block's kArrivedSlot
+    PendingNodewise deferred;
 };
 
 namespace {
@@ -489,18 +490,18 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
             (void)hipHostFree(c.res->host);
         c.res->host = nullptr;
         c.res->host_cap = 0;
-        HIP_TRY(hipHostMalloc((void **)&c.res->host, values * sizeof(int64_t), hipHostMallocMapped));
+        HIP_TRY(hipHostMalloc((void **)&c.res->host, values * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent));
         c.res->host_cap = values;
-    }
         c.res->host[kArrivedSlot] = c.res->arrival;
+    }
     c.res->host_off = false;
     c.res->host[64] = 0;
-    BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
     BMS_TRY(csr->sm_ticket.ensure(256));
     if (csr->sm_ticket.grew) {
         HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
         csr->sm_taken = 0;
     }
+    BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
     return BMS_OK;
 }
 
@@ -577,7 +578,6 @@ int seed_flag_error(const bms_csr *csr, const int64_t *scalars, const int64_t *f
     return BMS_OK;
 }
 
-// The call's scalars and the minibatches' offsets -> pinned memory of the result, in stream order.
 // Waits for what the call's last kernel writes to the result's pinned block.  The runtime's own wait sleeps: it costs 10 to
 // 50 us more than looking at the word (a call of 4 x 64 seeds takes 25 us on the device).  A fault or a stream that is
 // done for another reason ends the wait as well: the stream is asked now and then.
@@ -609,13 +609,14 @@ int wait_arrival(CallCtx &c)
     return BMS_OK;
 }
 
+// The call's scalars and the minibatches' offsets -> pinned memory of the result, in stream order.
 void publish(CallCtx &c)
 {
     PublishArgs p{};
-    p.k = c.k;
     p.arrived = c.res->host + kArrivedSlot;
     p.arrival = c.res->arrival;
     p.done = reinterpret_cast<uint32_t *>(c.csr->sm_ticket.as<uint32_t>() + 1);
+    p.k = c.k;
     p.L = c.L;
     p.scalars = c.csr->scalars.as<int64_t>();
     p.host = c.res->host;
@@ -807,9 +808,9 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
         a.host_off = host_offsets(c);
         c.res->host_off = a.host_off != nullptr;
         host[63] = 0;
-    }
         a.arrived = host + kArrivedSlot;
         a.arrival = c.res->arrival;
+    }
     a.next_tileoff = nhops < c.L ? csr->mb_tileoff.as<int64_t>() : nullptr;
     BMS_TRY(csr->sm_status.ensure((size_t)nhops * c.k * sizeof(uint64_t)));
     if (csr->sm_status.grew || csr->sm_epoch == 0xFFFFFFFFu) {
@@ -827,12 +828,33 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
     return BMS_OK;
 }
 
+// Which hops of about `entries` entries EXTRACT by bitmaps of vertex ranges: 0 none of this, 1 the sampling kernel sets the
+// bits, 2 the mark kernel does.
+//   1  few minibatches and entries: setting a bit in memory (12 ps per entry, in the shadow of the sampling) and fetching an
+//      entry's word (30 ps) beat kernels that let every workgroup see all of a minibatch's entries
+//   2  the ranges take up to 8 tables (4.9 million ids: a look-up costs about 0.5 ps per entry and table, the cut into segments
+//      9), and the bitmaps are no larger than what the entries themselves move in a few passes (16 bytes of ids and counts
+//      per 128 ids, against the segments' 30 bytes per entry)
+int ranges_apply(const CallCtx &c, double entries)
+{
+    const int64_t n = c.csr->n;
+    if (n < 1 || (c.flags & (BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP | BMS_PROFILE)))
+        return 0;
+    const int64_t most_quads = (n + 127) / 128 + 9 * 1024; // with what rounds the last range up
+    if ((int64_t)c.k * most_quads * 20 > c.scratch_limit / 4)
+        return 0;
+    if (c.k <= kRangesFewMb && entries <= 1.5e6)
+        return 1;
+    return ranges_passes(n) <= 8 && (double)c.k * (double)n <= 64.0 * entries ? 2 : 0;
+}
+
 // One attempt.  *redo receives the hops (bits) whose EXTRACT by id-range segments gave up (ids crowded into a narrow
 // range): the result is then incomplete and the caller repeats the call with those hops moved to the next mode.
 int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fanouts, const std::vector<uint8_t> &mode,
                          uint32_t *redo)
 {
     bms_csr *csr = c.csr;
+    ++c.res->arrival;
     Profiler prof{c.res, c.stream, (c.flags & (BMS_PROFILE | BMS_PROFILE_MAIN)) != 0, (c.flags & BMS_PROFILE) == 0};
     // EXTRACT strategy: LDS sorts of id-range segments (with the per-minibatch bin kernel as the
     // fallback for crowded id ranges) whenever the bin table of that fallback fits in LDS; the
@@ -854,7 +876,6 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     const bool union_dst = (c.flags & BMS_UNION_DST) != 0;
     const bool replace = (c.flags & BMS_NODEWISE_REPLACE) != 0;
     const int32_t small_hops = leading_small_hops(c, fanouts);
-    ++c.res->arrival;
     if (!buckets || !(seeds_by_sort || small_hops))
         BMS_TRY(setup_vset(c));
     if (buckets && small_hops < c.L) {
@@ -909,6 +930,37 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         BMS_TRY(csr->tile_off.ensure((size_t)(tiles_bound + 2) * sizeof(int64_t)));
         BMS_TRY(hb.rowptr.ensure((size_t)(rows_bound + 1) * sizeof(int64_t)));
         BMS_TRY(hb.mb_coloff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
+        const int64_t most_per_row = std::min<int64_t>(fanouts[h], std::max<int64_t>(csr->max_degree, 1));
+        const double expected = no_wait ? (double)std::max<int64_t>(c.res->hint_nnz[h], 1)
+                                        : (double)rows_bound * (double)(most_per_row + (union_dst ? 1 : 0));
+        const int ranges = buckets ? ranges_apply(c, expected) : 0;
+        RangeArgs g{};
+        if (ranges) {
+            g.n = csr->n;
+            g.k = c.k;
+            g.quads = (csr->n + 127) / 128;
+            g.qw = kRangeQuads;
+            g.parts = 1;
+            if (ranges == 2)
+                plan_ranges(g, csr->num_cu, expected / c.k);
+            g.qw_inverse = (uint32_t)((0x100000000ULL + g.qw - 1) / g.qw);
+            g.H = (int32_t)((g.quads + g.qw - 1) / g.qw);
+            g.stride = (int64_t)g.H * g.qw;
+            BMS_TRY(csr->rg_bits.ensure((size_t)g.parts * c.k * g.stride * sizeof(uint4)));
+            BMS_TRY(csr->rg_pre.ensure((size_t)c.k * g.stride * sizeof(uint32_t)));
+            BMS_TRY(csr->rg_count.ensure(((size_t)c.k * g.H + 1) * (sizeof(int64_t) + sizeof(uint32_t)) + 64));
+            g.bits = csr->rg_bits.as<uint4>();
+            g.pre = csr->rg_pre.as<uint32_t>();
+            g.first = csr->rg_count.as<int64_t>();
+            g.cnt = reinterpret_cast<uint32_t *>(g.first + (int64_t)c.k * g.H + 1);
+            g.mb_rowoff = mb_rowoff;
+            g.row_vertex = row_vertex;
+            g.mb_coloff = hb.mb_coloff.as<int64_t>();
+            g.ncols_out = slot(c, h, 1);
+            g.next_tileoff = csr->mb_tileoff.as<int64_t>();
+            g.done = csr->dd_done.as<uint32_t>();
+        }
+        const bool self_in_rows = union_dst && !ranges; // the rows carry their own vertex through EXTRACT
         if (union_dst) {
             BMS_TRY(csr->un_rowptr.ensure((size_t)(rows_bound + 1) * sizeof(int64_t)));
             BMS_TRY(hb.row_self.ensure((size_t)std::max<int64_t>(rows_bound, 1) * sizeof(int32_t)));
@@ -930,11 +982,16 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         a.tile_off = csr->tile_off.as<int64_t>();
         // with BMS_UNION_DST the hop is built with one more entry per row (the row's own vertex) in scratch
         // and moved to the result's arrays without it at the end of the hop
-        a.out_rowptr = union_dst ? csr->un_rowptr.as<int64_t>() : hb.rowptr.as<int64_t>();
+        a.out_rowptr = self_in_rows ? csr->un_rowptr.as<int64_t>() : hb.rowptr.as<int64_t>();
         a.rows_bound = rows_bound;
-        a.self_entry = union_dst ? 1 : 0;
+        a.self_entry = self_in_rows ? 1 : 0;
+        a.mark_self = union_dst && ranges == 1 ? 1 : 0;
+        if (ranges == 1) {
+            a.zero = g.bits;
+            a.zero_quads = (int64_t)c.k * g.stride;
+        }
         a.replace = replace ? 1 : 0;
-        a.flat = csr->nnz < (1LL << (union_dst ? 31 : 32)) ? 1 : 0;
+        a.flat = csr->nnz < (1LL << (self_in_rows ? 31 : 32)) ? 1 : 0;
         if (replace && a.s > 32) {
             BMS_TRY(csr->row_cnt.ensure((size_t)std::max<int64_t>(rows_bound, 1) * sizeof(int32_t)));
             a.row_cnt = csr->row_cnt.as<int32_t>();
@@ -955,7 +1012,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         // steady state bounded from above; nnz_tune only picks tuning parameters
         int64_t nnz, nnz_tune;
         if (no_wait) { // with BMS_UNION_DST nnz counts the rows' own entries too, until the hop's last step
-            nnz = rows_bound * (std::min<int64_t>(fanouts[h], std::max<int64_t>(csr->max_degree, 1)) + a.self_entry);
+            nnz = rows_bound * (most_per_row + a.self_entry);
             nnz_tune = std::max<int64_t>(c.res->hint_nnz[h], 1);
         } else {
             BMS_TRY(read_scalars(c));
@@ -964,16 +1021,16 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             seeds_checked = true;
             nnz = nnz_tune = host_slot(c, h, 0);
         }
-        const int64_t ncols_bound = std::min<int64_t>(nnz, (int64_t)c.k * csr->n);
+        const int64_t ncols_bound = std::min<int64_t>(nnz + (union_dst && ranges ? rows_bound : 0), (int64_t)c.k * csr->n);
         BMS_TRY(hb.col.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(int32_t)));
         BMS_TRY(hb.col_vertex.ensure((size_t)std::max<int64_t>(ncols_bound, 1) * sizeof(int32_t)));
-        if (union_dst)
+        if (self_in_rows)
             BMS_TRY(csr->un_col.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(int32_t)));
-        a.out_col = union_dst ? csr->un_col.as<int32_t>() : hb.col.as<int32_t>();
+        a.out_col = self_in_rows ? csr->un_col.as<int32_t>() : hb.col.as<int32_t>();
 
         DedupArgs d{};
         bool counted = false;
-        if (buckets) {
+        if (buckets && !ranges) {
             BMS_TRY(csr->dd_pairs.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t)));
             BMS_TRY(csr->dd_utmp.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t)));
             // segments = id ranges of 2^cshift ids holding 1500..3000 sampled ids each on average (one workgroup ranks
@@ -1086,7 +1143,12 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
                 table_pending = h;
         }
         BMS_TRY(prof.begin("nw_sample", h));
-        counted = launch_nw_sample(c.launch, a, c.vs, !buckets);
+        VSet vs = c.vs;
+        if (ranges == 1) {
+            vs.words = reinterpret_cast<uint32_t *>(g.bits);
+            vs.nw = g.stride * 4;
+        }
+        counted = launch_nw_sample(c.launch, a, vs, !buckets || ranges == 1);
         BMS_TRY(prof.end());
         if (table_pending == h) { // the table of this hop's segments, from a sample of the ids just staged
             BMS_TRY(prof.begin("dd_table", h));
@@ -1095,7 +1157,27 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
                                   const_cast<uint16_t *>(d.tab), const_cast<uint32_t *>(d.seg_first));
             BMS_TRY(prof.end());
         }
-        if (buckets) {
+        if (ranges) {
+            g.rowptr = a.out_rowptr;
+            g.col = a.out_col;
+            g.row_self = union_dst ? hb.row_self.as<int32_t>() : nullptr;
+            BMS_TRY(prof.begin("rg_mark", h));
+            if (ranges == 1)
+                launch_ranges_count(c.launch, g);
+            else if (launch_ranges_mark(c.launch, g) != 0)
+                return fail(BMS_EHIP, "launch of the range bitmap kernel was refused");
+            BMS_TRY(prof.mark("rg_emit", h));
+            if (ranges == 1) {
+                launch_ranges_emit_gather(c.launch, g, hb.col_vertex.as<int32_t>(), (int64_t)expected);
+            } else {
+                launch_ranges_emit(c.launch, g, hb.col_vertex.as<int32_t>());
+                BMS_TRY(prof.mark("rg_lookup", h));
+                if (launch_ranges_lookup(c.launch, g, expected / c.k) != 0)
+                    return fail(BMS_EHIP, "launch of the range look-up kernel was refused");
+            }
+            BMS_TRY(prof.end());
+            tiles_planned = true;
+        } else if (buckets) {
             const StageMark mark = [&](const char *name) { (void)prof.mark(name, h); };
             if (d.C > 0) {
                 launch_nw_extract_segments(c.launch, d, a.out_rowptr, mb_rowoff, hb.mb_coloff.as<int64_t>(),
@@ -1121,7 +1203,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             BMS_TRY(prof.end());
         }
 
-        if (union_dst) {
+        if (self_in_rows) {
             BMS_TRY(prof.begin("nw_strip_self", h));
             launch_nw_strip_self(c.launch, a.out_rowptr, a.out_col, mb_rowoff + c.k, rows_bound, hb.rowptr.as<int64_t>(),
                                  hb.col.as<int32_t>(), hb.row_self.as<int32_t>(), slot(c, h, 0));
@@ -1266,6 +1348,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
 {
     bms_csr *csr = c.csr;
     *redo = false;
+    ++c.res->arrival;
     Profiler prof{c.res, c.stream, (c.flags & (BMS_PROFILE | BMS_PROFILE_MAIN)) != 0, (c.flags & BMS_PROFILE) == 0};
     const int64_t n1 = std::max<int64_t>(csr->n, 1);
     const int32_t nwin = (int32_t)((n1 + (1LL << kWinShift) - 1) >> kWinShift);
@@ -1345,7 +1428,6 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.bounds_t = csr->lw_bounds.as<uint32_t>();
         w.win_wt = csr->lw_win.as<uint64_t>();
         w.win_woff = w.win_wt + nw;
-    ++c.res->arrival;
         w.win_poff = reinterpret_cast<int64_t *>(w.win_woff + nw);
         w.win_cnt = reinterpret_cast<uint32_t *>(w.win_poff + nw);
         w.win_added = w.win_cnt + nw;

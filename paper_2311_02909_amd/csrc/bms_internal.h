@@ -89,6 +89,9 @@ struct NwHop {
     int32_t max_degree;
     int32_t self_entry;        // 1: every row carries its own vertex as one more entry after the sampled ones
     int32_t replace;           // 1: the s draws of a row are independent, the row keeps the distinct picks
+    int32_t mark_self;         // 1: the sampling kernel, when it sets bits, also sets those of the rows' own vertices
+    uint4 *zero;               // cleared by launch_nw_rows: zero_quads x 16 bytes (null: nothing)
+    int64_t zero_quads;
     int32_t flat;              // 1: places in A_col fit the 32-bit words that the sampling kernel stages (31 with self_entry)
     int32_t *row_cnt;          // scratch, rows: distinct picks per row (only with replace and s > 32)
     // EXTRACT's count of sampled ids per (minibatch, id-range segment), taken while the ids are staged in LDS
@@ -153,6 +156,38 @@ struct NwSmall {
     NwSmallHop hop[kSmallHopsMax];
 };
 int launch_nw_small(const Launch &, const NwSmall &, bool replace); // -1: launch refused
+
+// EXTRACT by bitmaps of vertex ranges (kernels_ranges.hip)
+constexpr int32_t kRangeQuads = 4096;  // quads of 128 ids per range of the count kernel
+constexpr int32_t kRangesFewMb = 4;    // so few minibatches: the sampling kernel sets the bits in memory
+struct RangeArgs {
+    int64_t n;
+    int32_t k;
+    int32_t H, qw;             // ranges per minibatch, quads per range
+    uint32_t qw_inverse;       // ceil(2^32 / qw)
+    int32_t parts;             // bitmaps per minibatch that the count kernel merges (1: mark counts, or the bits are set already)
+    int64_t quads, stride;     // ceil(n / 128); H * qw: quads per minibatch in bits and pre
+    const int64_t *rowptr;     // rows + 1
+    const int64_t *mb_rowoff;  // k + 1
+    const int32_t *row_vertex;
+    int32_t *col;              // in: sampled ids, 16-byte aligned; out: local columns
+    int32_t *row_self;         // out: local column of every row's own vertex, which is a column then (null: not wanted)
+    uint4 *bits;               // parts * k * stride, the first of them the merged ones
+    uint32_t *pre;             // k * stride: set bits of the range before the quad
+    uint32_t *cnt;             // k * H: set bits of the range
+    int64_t *first;            // k * H + 1: stacked columns before the range
+    int64_t *mb_coloff;        // k + 1
+    int64_t *ncols_out;
+    int64_t *next_tileoff;     // k + 2: the next hop's row tiles (as launch_plan_tiles with max_out gives them)
+    uint32_t *done;            // a device word, zero between launches
+};
+int ranges_passes(int64_t n);  // tables of launch_ranges_lookup
+void plan_ranges(RangeArgs &, int num_cu, double per_mb); // n, k, quads -> qw and parts for launch_ranges_mark
+int launch_ranges_mark(const Launch &, const RangeArgs &); // -1: launch refused
+void launch_ranges_count(const Launch &, const RangeArgs &); // bits set already: qw = kRangeQuads, parts = 1
+void launch_ranges_emit(const Launch &, const RangeArgs &, int32_t *col_vertex);
+void launch_ranges_emit_gather(const Launch &, const RangeArgs &, int32_t *col_vertex, int64_t entries);
+int launch_ranges_lookup(const Launch &, const RangeArgs &, double per_mb); // -1: launch refused
 
 // EXTRACT ("remove empty columns", Sec. 4.1.3).  Main path: the sampled ids of every minibatch are cut into C
 // id-range segments, the segments are ranked in LDS, and the ranks travel back to the entries' positions through the

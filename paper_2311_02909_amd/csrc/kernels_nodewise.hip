@@ -81,6 +81,8 @@ __global__ __launch_bounds__(kRowTile) void nw_rows_kernel(NwHop a)
     // Tile j of every minibatch before tile j + 1 of any: the rows of a minibatch ascend by vertex id, so the
     // workgroups that run at the same time touch the same part of the id range in all minibatches, and lines of
     // rowptr / col that several minibatches need are still in the last-level cache when the next one asks.
+    for (int64_t q = (int64_t)blockIdx.x * kRowTile + tid; q < a.zero_quads; q += (int64_t)gridDim.x * kRowTile)
+        a.zero[q] = make_uint4(0, 0, 0, 0);
     const int64_t most = a.mb_tileoff[a.k + 1]; // tiles of the minibatch that has most
     for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x) {
         const int i = (int)(v % a.k);
@@ -135,6 +137,8 @@ __global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(
     __shared__ int32_t deg_of[kRowTile], vert_of[kRowTile], cnt_of[kRowTile];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     volatile uint32_t *buf = chosen_all + (LANES ? 0 : wave * kMaxSampledFanout);
+    for (int64_t q = (int64_t)blockIdx.x * kWideRowsThreads + tid; q < a.zero_quads; q += (int64_t)gridDim.x * kWideRowsThreads)
+        a.zero[q] = make_uint4(0, 0, 0, 0);
     const int64_t most = a.mb_tileoff[a.k + 1];
     for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x) {
         const int i = (int)(v % a.k);
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(
 
 void launch_nw_rows(const Launch &L, const NwHop &a)
 {
-    const int64_t tiles = a.rows_bound / kRowTile + a.k;
+    const int64_t tiles = std::max(a.rows_bound / kRowTile + a.k, a.zero_quads / (8 * kRowTile));
     const dim3 grid(grid_for(L, tiles, 16)), block(kRowTile);
     if (!a.replace)
         hipLaunchKernelGGL(nw_rows_kernel<0>, grid, block, 0, L.stream, a);
@@ -290,6 +294,11 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
         const int64_t base = a.tile_off[t];
         if (valid)
             a.out_rowptr[r] = base + loc;
+        if (SET && valid && a.mark_self) {
+            const int32_t self = a.row_vertex[r];
+            if (self >= 0 && (int64_t)self < a.n)
+                atomicOr(&vs.words[(int64_t)i * vs.nw + (self >> 5)], 1u << (self & 31));
+        }
         if (valid && a.self_entry) { // a seed outside [0, n) is reported by the seed check; EXTRACT still gets a valid id
             const int32_t self = a.row_vertex[r];
             stage[loc + cnt] = ((self >= 0 && (int64_t)self < a.n) ? (uint32_t)self : 0u) | (flat ? kSelfMark : 0u);
@@ -396,6 +405,11 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
                 if (SET)
                     atomicOr(&words[g >> 5], 1u << (g & 31));
             };
+            if (SET && a.mark_self && lane == 0) {
+                const int32_t self = a.row_vertex[rr];
+                if (self >= 0 && (int64_t)self < a.n)
+                    atomicOr(&words[self >> 5], 1u << (self & 31));
+            }
             if (a.self_entry && lane == 0) { // the row's own vertex, after its sampled ones (kept inside [0, n):
                                              // a bad seed is reported by the seed check, EXTRACT still gets a valid id)
                 int32_t g = a.row_vertex[rr];

@@ -84,3 +84,15 @@ def test_places_beyond_32_bits():
             ref = O.sample_nodewise(small_rowptr, small_col, batches, fanouts, 9, **variant)
             got = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 9, **variant)
             assert_hops_equal(got.hops(), ref, what="b=%d fanouts=%s %s" % (b, fanouts, variant))
+
+
+# EXTRACT by bitmaps of vertex ranges: quads of 128 ids, ranges of 1024 quads and more, tables of 4864; minibatches in groups of
+# 8; up to 4 of them with their bits set by the sampling kernel, more by a kernel of their own
+@pytest.mark.parametrize("n,b", [(1, 1), (127, 100), (129, 129), (131_073, 900), (622_592, 1400), (622_593, 1400), (1_300_001, 2600)])
+def test_extract_by_vertex_ranges(n, b):
+    rng = np.random.default_rng(n)
+    rowptr, col = random_csr(n, min(14.0, n / 2), rng)
+    for k, variant in ((4, {}), (5, {"union_dst": True}), (9, {}), (1, {"union_dst": True}), (16, {"replace": True})):
+        _check(rowptr, col, random_batches(n, k, b, rng), (40, 2), **variant)
+    if n > 100_000:  # the sampled ids of the rows in one launch, then ranges
+        _check(rowptr, col, random_batches(n, 6, b, rng), (3, 13), union_dst=True)
