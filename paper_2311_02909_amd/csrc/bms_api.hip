@@ -578,15 +578,14 @@ int seed_flag_error(const bms_csr *csr, const int64_t *scalars, const int64_t *f
     return BMS_OK;
 }
 
-// Waits for what the call's last kernel writes to the result's pinned block.  The runtime's own wait sleeps: it costs 10 to
-// 50 us more than looking at the word (a call of 4 x 64 seeds takes 25 us on the device).  A fault or a stream that is
-// done for another reason ends the wait as well: the stream is asked now and then.
-int wait_arrival(CallCtx &c)
+// Waits until *word, in host memory, holds `value`, which a kernel on `stream` writes.  The runtime's own wait sleeps: it
+// costs 10 to 50 us more than looking at the word (a call of 4 x 64 seeds takes 25 us on the device).  A fault or a stream
+// that is done for another reason ends the wait as well: the stream is asked now and then.
+int wait_word(const volatile int64_t *word, int64_t value, hipStream_t stream)
 {
-    const volatile int64_t *word = c.res->host + kArrivedSlot;
     const auto start = std::chrono::steady_clock::now();
     int64_t asked = 0;
-    for (uint32_t turn = 1; *word != c.res->arrival; ++turn) {
+    for (uint32_t turn = 1; *word != value; ++turn) {
         __builtin_ia32_pause();
         if (turn % 64)
             continue;
@@ -595,17 +594,26 @@ int wait_arrival(CallCtx &c)
             break;
         if (us - asked > 5000) {
             asked = us;
-            const hipError_t e = hipStreamQuery(c.stream);
+            const hipError_t e = hipStreamQuery(stream);
             if (e != hipErrorNotReady)
                 break;
             (void)hipGetLastError();
         }
     }
-    if (*word != c.res->arrival || !c.res->stages.empty()) // (the events of a profile have to be done)
-        HIP_TRY(hipStreamSynchronize(c.stream));
+    if (*word != value)
+        HIP_TRY(hipStreamSynchronize(stream));
     std::atomic_thread_fence(std::memory_order_acquire);
-    if (*word != c.res->arrival)
+    if (*word != value)
         return fail(BMS_EHIP, "the call's kernels did not run to their end");
+    return BMS_OK;
+}
+
+// ... for what the call's last kernel writes to the result's pinned block
+int wait_arrival(CallCtx &c)
+{
+    BMS_TRY(wait_word(c.res->host + kArrivedSlot, c.res->arrival, c.stream));
+    if (!c.res->stages.empty()) // the events of a profile have to be done
+        HIP_TRY(hipStreamSynchronize(c.stream));
     return BMS_OK;
 }
 
@@ -2067,23 +2075,24 @@ int bms_fetch_features(const float *H, int64_t n, int32_t f, const int32_t *ids,
     int device = 0;
     HIP_TRY(hipGetDevice(&device));
     // error flags in host memory that the kernel can write (nothing to allocate per call): a ring of kFlagSlots
-    // words per device, one slot per call, so that fetches running at the same time on different streams do not
-    // share a flag (a slot is reused after kFlagSlots further calls on the device)
+    // pairs per device (flag, number of the call that is done), one slot per call, so that fetches running at the same time
+    // on different streams do not share a flag (a slot is reused after kFlagSlots further calls on the device)
     constexpr int kFlagSlots = 64;
-    static int32_t *flags[64] = {nullptr};
-    static uint32_t next_slot[64] = {0};
+    static int64_t *flags[64] = {nullptr};
+    static int64_t calls[64] = {0};
     static std::mutex flags_lock;
-    int32_t *flag = nullptr;
+    int64_t *slot = nullptr, call = 0;
     {
         std::lock_guard<std::mutex> guard(flags_lock);
         if (device < 0 || device >= 64)
             return fail(BMS_EINVAL, "device ordinal %d not supported", device);
         if (!flags[device])
-            HIP_TRY(hipHostMalloc((void **)&flags[device], kFlagSlots * sizeof(int32_t), hipHostMallocMapped));
-        flag = flags[device] + (next_slot[device]++ % kFlagSlots);
+            HIP_TRY(hipHostMalloc((void **)&flags[device], 2 * kFlagSlots * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent));
+        slot = flags[device] + 2 * (calls[device] % kFlagSlots);
+        call = ++calls[device];
     }
-    int32_t *flag_dev = nullptr;
-    HIP_TRY(hipHostGetDevicePointer((void **)&flag_dev, flag, 0));
+    int64_t *slot_dev = nullptr;
+    HIP_TRY(hipHostGetDevicePointer((void **)&slot_dev, slot, 0));
     hipDeviceProp_t prop;
     int num_cu = 256;
     static int cached_cu[64] = {0};
@@ -2091,11 +2100,11 @@ int bms_fetch_features(const float *H, int64_t n, int32_t f, const int32_t *ids,
         cached_cu[device] = prop.multiProcessorCount;
     if (cached_cu[device])
         num_cu = cached_cu[device];
-    *flag = 0;
-    launch_feature_fetch(Launch{(hipStream_t)stream, num_cu}, H, n, f, ids, m, out, flag_dev);
+    slot[0] = slot[1] = 0;
+    launch_feature_fetch(Launch{(hipStream_t)stream, num_cu}, H, n, f, ids, m, out, reinterpret_cast<int32_t *>(slot_dev), slot_dev + 1, call);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
-    if (*flag)
+    BMS_TRY(wait_word(slot + 1, call, (hipStream_t)stream));
+    if (slot[0])
         return fail(BMS_ERANGE, "a vertex id lies outside [0, %lld)", (long long)n);
     return BMS_OK;
 }

@@ -73,3 +73,25 @@ def test_errors_and_empty(mods):
             assert host[j].tolist() == (H[v].cpu().numpy().tolist() if 0 <= v < 4 else [0.0, 0.0, 0.0])
     good = bms.fetch_features(H, torch.tensor([3, 3, 0], dtype=torch.int32, device="cuda"))
     assert good.cpu().numpy().tolist() == [[9, 10, 11], [9, 10, 11], [0, 1, 2]]
+
+
+@pytest.mark.parametrize("lengths", [(70000, 1, 69000, 71000), (40000, 41000), (1000,) * 90, (90000,), (5,) * 3 + (80000, 300), None])
+def test_large_fetches_of_stacked_runs(mods, lengths):
+    # fetches of 100 MB and more go over the ascending runs of the ids side by side: equal and unequal runs, some between two of
+    # the samples that find them, one run, no order at all
+    O, bms = mods
+    rng = np.random.default_rng(12)
+    n, f = 150_000, 401
+    H = rng.standard_normal((n, f)).astype(np.float32)
+    if lengths is None:
+        ids = rng.integers(0, n, size=70_000).astype(np.int32)
+    else:
+        ids = np.concatenate([np.sort(rng.choice(n, size=x, replace=False)) for x in lengths]).astype(np.int32)
+    assert ids.size * f * 4 >= 100 << 20 and ids.size >= 65536
+    Hd = torch.from_numpy(H).cuda()
+    out = bms.fetch_features(Hd, torch.from_numpy(ids).cuda())
+    assert torch.equal(out, Hd[torch.from_numpy(ids).cuda().long()])
+    ids[[7, ids.size // 2]] = -5, n
+    with pytest.raises(bms.BmsError):
+        bms.fetch_features(Hd, torch.from_numpy(ids).cuda(), out=out)
+    assert not out[7].any() and not out[ids.size // 2].any() and torch.equal(out[8], Hd[int(ids[8])])
