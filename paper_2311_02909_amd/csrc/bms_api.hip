@@ -176,8 +176,11 @@ struct bms_csr {
     BMS_BUF(row_cnt);                    // BMS_NODEWISE_REPLACE with a fanout above 32: distinct picks per row
     BMS_BUF(lw_bounds); BMS_BUF(lw_win); BMS_BUF(lw_tmpcol); BMS_BUF(lw_parts); BMS_BUF(lw_sel); BMS_BUF(lw_xtmp);
     BMS_BUF(lw_count); BMS_BUF(lw_tiles); BMS_BUF(lw_rowcnt); // LADIES by LDS windows
-    BMS_BUF(sm_status); BMS_BUF(sm_ticket); // hops done by one workgroup per minibatch: sizes published, next minibatch
+    BMS_BUF(sm_status); // hops done by one workgroup per minibatch: sizes published
+    BMS_BUF(sm_ticket); // counters: 0 next minibatch of those, 1 workgroups done (announce), 2 numbers (Lookback), 3 done (layer-wise)
     uint32_t sm_epoch = 0, sm_taken = 0;     // launches so far, minibatches handed out by them
+    BMS_BUF(lb_status);                      // values that workgroups of a launch bring (Lookback)
+    uint32_t lb_epoch = 0, lb_taken = 0;     // launches so far (24 bits), numbers taken by them
     BMS_BUF(lw_index);           // where every vertex's adjacency list crosses the window boundaries: n * (nwin + 1)
     bool lw_index_ready = false; // built by the first layer-wise call that finds room for it
     bool lw_index_tried = false;
@@ -499,7 +502,7 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
     BMS_TRY(csr->sm_ticket.ensure(256));
     if (csr->sm_ticket.grew) {
         HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
-        csr->sm_taken = 0;
+        csr->sm_taken = csr->lb_taken = 0;
     }
     BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
     return BMS_OK;
@@ -526,25 +529,50 @@ int abort_call(CallCtx &c, int rc)
     return rc;
 }
 
-// Copies the seeds into hop 0's row_vertex, builds mb_rowoff = i*b and verifies the seeds.
-int stage_seeds(CallCtx &c, const int32_t *batches, Profiler &prof, bool use_vset = true)
+// What a launch whose workgroups add up the values before their own gets; lookback_used counts the numbers they take.
+int next_lookback(CallCtx &c, Lookback &lb)
+{
+    bms_csr *csr = c.csr;
+    BMS_TRY(csr->lb_status.ensure(kMostLookback * sizeof(uint64_t)));
+    if (csr->lb_status.grew || csr->lb_epoch == 0xFFFFFFu) {
+        HIP_TRY(hipMemsetAsync(csr->lb_status.p, 0, csr->lb_status.cap, c.stream));
+        csr->lb_epoch = 0;
+    }
+    lb.status = csr->lb_status.as<unsigned long long>();
+    lb.ticket = csr->sm_ticket.as<uint32_t>() + 2;
+    lb.ticket0 = csr->lb_taken;
+    lb.epoch = ++csr->lb_epoch;
+    return BMS_OK;
+}
+void lookback_used(CallCtx &c, uint32_t workgroups) { c.csr->lb_taken += workgroups; }
+
+// Copies the seeds into hop 0's row_vertex, builds mb_rowoff = i*b and verifies the seeds; tileoff (without a vertex set): the
+// hop's row tiles as well.
+int stage_seeds(CallCtx &c, const int32_t *batches, Profiler &prof, bool use_vset = true, int64_t *tileoff = nullptr)
 {
     HopBufs &h0 = c.res->hops[0];
     const size_t nb = (size_t)c.k * c.b;
     BMS_TRY(h0.row_vertex.ensure(nb * sizeof(int32_t)));
     BMS_TRY(h0.mb_rowoff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
     BMS_TRY(prof.begin("seeds", 0));
+    if (!use_vset) {
+        const int32_t *seeds = batches;
+        if (!is_device_pointer(batches)) {
+            HIP_TRY(hipMemcpyAsync(h0.row_vertex.p, batches, nb * sizeof(int32_t), hipMemcpyHostToDevice, c.stream));
+            seeds = h0.row_vertex.as<int32_t>();
+        }
+        launch_stage_seeds(c.launch, seeds, c.k, c.b, c.csr->n, h0.row_vertex.as<int32_t>(), h0.mb_rowoff.as<int64_t>(),
+                           c.csr->scalars.as<int64_t>(), reinterpret_cast<int32_t *>(c.res->host + 64), tileoff);
+        BMS_TRY(prof.end());
+        return BMS_OK;
+    }
     HIP_TRY(hipMemcpyAsync(h0.row_vertex.p, batches, nb * sizeof(int32_t),
                            is_device_pointer(batches) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c.stream));
     launch_iota_offsets(c.launch, h0.mb_rowoff.as<int64_t>(), c.k, c.b);
     int32_t *flag = reinterpret_cast<int32_t *>(c.csr->scalars.as<int64_t>() + 63);
     HIP_TRY(hipMemsetAsync(c.csr->scalars.p, 0, 64 * sizeof(int64_t), c.stream));
-    if (use_vset) {
-        launch_validate_seeds(c.launch, h0.row_vertex.as<int32_t>(), c.k, c.b, c.csr->n, c.vs, flag);
-        launch_clear_seed_bits(c.launch, h0.row_vertex.as<int32_t>(), c.k, c.b, c.csr->n, c.vs);
-    } else {
-        launch_validate_seeds_sorted(c.launch, h0.row_vertex.as<int32_t>(), c.k, c.b, c.csr->n, flag);
-    }
+    launch_validate_seeds(c.launch, h0.row_vertex.as<int32_t>(), c.k, c.b, c.csr->n, c.vs, flag);
+    launch_clear_seed_bits(c.launch, h0.row_vertex.as<int32_t>(), c.k, c.b, c.csr->n, c.vs);
     BMS_TRY(prof.end());
     return BMS_OK;
 }
@@ -925,7 +953,8 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         BMS_TRY(run_small_hops(c, batches, fanouts, small_hops, host, &rows_bound));
         tiles_planned = true;
     } else {
-        BMS_TRY(stage_seeds(c, batches, prof, !seeds_by_sort));
+        BMS_TRY(stage_seeds(c, batches, prof, !seeds_by_sort, csr->mb_tileoff.as<int64_t>()));
+        tiles_planned = seeds_by_sort;
     }
     const int32_t *row_vertex = (small_hops ? c.res->hops[small_hops - 1].col_vertex : c.res->hops[0].row_vertex).as<int32_t>();
     const int64_t *mb_rowoff = (small_hops ? c.res->hops[small_hops - 1].mb_coloff : c.res->hops[0].mb_rowoff).as<int64_t>();
@@ -1325,8 +1354,8 @@ int build_window_index(CallCtx &c, int32_t nwin)
     g.mb_goff = small + 2;
     g.mb_gtileoff = small + 4;
     g.rows_bound = csr->n;
-    g.gather_off = csr->rowptr; // the gathered order of all rows is the adjacency itself
-    g.row_beg = csr->rowptr;
+    g.gather_off = const_cast<int64_t *>(csr->rowptr); // the gathered order of all rows is the adjacency itself (only read)
+    g.row_beg = g.gather_off;
     g.tile_row = csr->lw_tiles.as<int64_t>();
     g.bounds = csr->lw_index.as<uint32_t>();
     HIP_TRY(hipMemsetAsync(g.bounds, 0, ibytes, c.stream)); // vertices without neighbours get no list
@@ -1439,6 +1468,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.win_poff = reinterpret_cast<int64_t *>(w.win_woff + nw);
         w.win_cnt = reinterpret_cast<uint32_t *>(w.win_poff + nw);
         w.win_added = w.win_cnt + nw;
+        w.done = csr->sm_ticket.as<uint32_t>() + 3;
         w.part_woff = csr->lw_parts.as<uint64_t>();
         w.part_wt = w.part_woff + nw * kWinParts;
         w.part_base = reinterpret_cast<int64_t *>(w.part_wt + nw * kWinParts);
@@ -1458,7 +1488,15 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
 
         // P = Q A
         BMS_TRY(prof.begin("ld_rows", h));
-        launch_ld_rows(c.launch, a, slot(c, h, 3));
+        Lookback lb{};
+        uint32_t workgroups = 0;
+        BMS_TRY(next_lookback(c, lb));
+        if (launch_ldw_rows(c.launch, w, lb, slot(c, h, 3), &workgroups) == 0) {
+            lookback_used(c, workgroups);
+        } else { // too many rows for that
+            launch_ld_rows(c.launch, a, slot(c, h, 3));
+            launch_ldw_zero_added(c.launch, w);
+        }
         BMS_TRY(prof.end());
         int64_t D; // gathered neighbours: sizes the staging of P and of the kept neighbours
         if (no_wait) {
@@ -1499,9 +1537,8 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         launch_ldw_bounds(c.launch, w);
         BMS_TRY(prof.end());
         BMS_TRY(prof.begin("ldw_accumulate", h));
-        if (launch_ldw_accumulate(c.launch, w) != 0)
+        if (launch_ldw_accumulate(c.launch, w, slot(c, h, 2)) != 0)
             return fail(BMS_EHIP, "launch of the LDS accumulation kernel was refused");
-        launch_offsets_from_counts(c.launch, w.mb_count, c.k, w.p_off, slot(c, h, 2));
         BMS_TRY(prof.end());
         // nnz(P) sizes P and its prefix sums.  When its bound min(D, k n) is modest the buffers take the bound
         // and the size is read back with everything else at the end of the call; else it is read back now.
@@ -1524,20 +1561,28 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         BMS_TRY(prof.end());
         // NORM (implicit) + SAMPLE
         BMS_TRY(prof.begin("ldw_draw", h));
-        launch_ldw_draw(c.launch, w);
-        launch_offsets_from_counts(c.launch, w.mb_count, c.k, w.mb_coloff, slot(c, h, 1));
-        launch_ldw_sel_copy(c.launch, w);
+        if (c.k <= kMostLookback) {
+            BMS_TRY(next_lookback(c, lb));
+            launch_ldw_draw(c.launch, w, &lb, slot(c, h, 1));
+            lookback_used(c, (uint32_t)c.k);
+        } else {
+            launch_ldw_draw(c.launch, w, nullptr, nullptr);
+            launch_offsets_from_counts(c.launch, w.mb_count, c.k, w.mb_coloff, slot(c, h, 1));
+            launch_ldw_sel_copy(c.launch, w);
+        }
         BMS_TRY(prof.end());
         // EXTRACT
         BMS_TRY(prof.begin("ldw_extract", h));
         launch_ldw_extract(c.launch, w);
-        launch_scan_i64(c.launch, w.out_rowptr, mb_rowoff + c.k, slot(c, h, 0), nullptr, nullptr, rows_bound);
-        BMS_TRY(prof.end());
         // nnz sizes the column buffer: same rule with the bound min(D, rows * s)
         int64_t nnz = std::min<int64_t>(D, rows_bound * std::min<int64_t>(s, n1));
-        if (no_wait) {
+        if (no_wait)
             nnz = std::min<int64_t>(nnz, with_margin(c.res->hint_nnz[h]));
-        } else if (nnz > kNoWaitEntries) {
+        const bool placed = (no_wait || nnz <= kNoWaitEntries) && (rows_bound + 255) / 256 <= kMostLookback; // scan and copy in one
+        if (!placed)
+            launch_scan_i64(c.launch, w.out_rowptr, mb_rowoff + c.k, slot(c, h, 0), nullptr, nullptr, rows_bound);
+        BMS_TRY(prof.end());
+        if (!no_wait && nnz > kNoWaitEntries) {
             BMS_TRY(read_scalars(c));
             nnz = host_slot(c, h, 0);
         }
@@ -1545,7 +1590,13 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         BMS_TRY(hb.col.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(int32_t)));
         w.out_col = hb.col.as<int32_t>();
         BMS_TRY(prof.begin("ldw_extract_copy", h));
-        launch_ldw_extract_copy(c.launch, w);
+        if (placed) {
+            BMS_TRY(next_lookback(c, lb));
+            (void)launch_ldw_extract_place(c.launch, w, lb, slot(c, h, 0), &workgroups);
+            lookback_used(c, workgroups);
+        } else {
+            launch_ldw_extract_copy(c.launch, w);
+        }
         BMS_TRY(prof.end());
 
         hb.view = bms_hop_view{}; // the sizes follow after the last read-back

@@ -61,6 +61,15 @@ __device__ inline uint64_t bounded64(uint64_t x, uint64_t w) { return __umul64hi
 
 constexpr uint32_t kNoVertex = 0xFFFFFFFFu;
 
+// Sums over the workgroups before one's own, inside a launch (take_number, sum_before): at most kMostLookback workgroups
+constexpr int kMostLookback = 1024;
+struct Lookback {
+    unsigned long long *status; // kMostLookback words: epoch << 40 | value
+    uint32_t *ticket;           // device counter: workgroups that have started
+    uint32_t ticket0;           // its value before the launch
+    uint32_t epoch;             // of the launch, 24 bits, never 0
+};
+
 // ---------------------------------------------------------------------------------------------
 // Scans
 // ---------------------------------------------------------------------------------------------
@@ -138,6 +147,54 @@ __device__ inline T block_exclusive_scan(T v, T *smem, T &total)
     }
     total = all;
     return before + inc - v;
+}
+
+// A workgroup's number in its launch, in the order of starting: whoever waits for lower numbers waits for workgroups that
+// have started.  smem: one word of LDS.
+__device__ inline uint32_t take_number(const Lookback &lb, uint32_t *smem)
+{
+    if (threadIdx.x == 0)
+        *smem = atomicAdd(lb.ticket, 1u) - lb.ticket0;
+    __syncthreads();
+    return *smem;
+}
+
+// Sum of the values that workgroups 0 .. i - 1 of the launch bring, for workgroup number i, which brings `value` (below 2^40);
+// all threads of the workgroup call it.  Every workgroup leaves its value before it waits for anyone.
+template <int NT>
+__device__ inline int64_t sum_before(const Lookback &lb, uint32_t i, int64_t value, int64_t *smem /* NT / 64 */)
+{
+    if (threadIdx.x == 0)
+        __hip_atomic_store(lb.status + i, ((unsigned long long)lb.epoch << 40) | (unsigned long long)value, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    int64_t sum = 0;
+    for (uint32_t j = threadIdx.x; j < i; j += NT) {
+        unsigned long long w;
+        while ((uint32_t)((w = __hip_atomic_load(lb.status + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 40) != lb.epoch)
+            __builtin_amdgcn_s_sleep(1);
+        sum += (int64_t)(w & ((1ull << 40) - 1ull));
+    }
+    sum = wave_sum(sum);
+    __syncthreads();
+    if ((threadIdx.x & (kWave - 1)) == 0)
+        smem[threadIdx.x / kWave] = sum;
+    __syncthreads();
+    sum = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w)
+        sum += smem[w];
+    return sum;
+}
+
+// One thread of every workgroup of a launch, after its atomic stores of what the last one is to read: true for the one that
+// comes here last.  *done is zero before and after.
+__device__ inline bool arrive_last(uint32_t *done, uint32_t workgroups)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // what was stored is where other dies see it
+    if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != workgroups - 1u)
+        return false;
+    __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
 }
 
 // Called by all threads of each of a launch's `parts` workgroups when the workgroup has written everything: the last of

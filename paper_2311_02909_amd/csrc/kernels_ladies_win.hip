@@ -3,6 +3,7 @@
 //
 // The rows of A are sorted by column, so the neighbours of a frontier row that fall into a window
 // of 2^16 vertex ids form one contiguous piece of its adjacency list.  One hop, all k minibatches:
+//   ldw_rows        extents of the frontier's rows, exclusive scan of their degrees = the gathered order
 //   ldw_plan, ldw_tile_rows
 //                   the gathered order (the neighbour lists of the stacked frontier laid end to end) cut into
 //                   tiles of 1024..4096 positions (few gathered neighbours: small tiles, so that every wave still
@@ -11,8 +12,9 @@
 //                   depends on its vertex alone: when the lists of all n vertices fit in memory they are computed
 //                   once per graph (one wave per tile streams its pieces of rows, the "hop" being the whole
 //                   graph) and a hop only copies the lists of its rows; else the hop streams its rows for them.
-//                   Either way the lists are turned window-major for the next kernel
-//   ldw_win_added   neighbours of every (minibatch, window): the lengths of its pieces added up
+//                   Either way the lists are turned window-major for the next kernel, and the neighbours of every
+//                   (minibatch, window), the lengths of its pieces, are added up (with the index and k < 1024 plan, tile
+//                   rows and this are one launch, ldw_plan_bounds)
 //   ldw_accumulate  one workgroup per (minibatch, window): 2^16 packed 16-bit counters in LDS (128 KB); every
 //                   row's piece of the window adds 1 per neighbour (e_v cannot exceed the number of frontier
 //                   rows, which this path keeps below 2^16); each wave then compacts its sixteenth of the window
@@ -23,12 +25,15 @@
 //                   weights (e_v or e_v^2) on the way, one kept per 16 entries (NORM stays implicit: draws are
 //                   integers below the row sum)
 //   ldw_draw        SAMPLE (Sec. 4.2.2): one workgroup per minibatch: s draws, each the smallest t
-//                   with prefix[t] > r, sorted in LDS, duplicates dropped -> sampled columns
+//                   with prefix[t] > r, sorted in LDS, duplicates dropped -> sampled columns, at their place in the stack
 //   ldw_extract     EXTRACT (Sec. 4.2.3): the sampled columns of the minibatch sit in an LDS hash
 //                   table (column -> local index); one wave per tile streams the gathered order a
 //                   second time and keeps the neighbours found in the table ((Q_R A) Q_C), in
 //                   row order, piece by piece; rows are then sized by a scan and their pieces
-//                   copied to their place
+//                   copied to their place (ldw_extract_place)
+// A launch costs about 5 us on the device however little it does, and most of these do little: where a kernel needs sums over
+// its own workgroups (rows, minibatches), the workgroups add up those before them (sum_before) instead of leaving it to a
+// kernel in between.  32 x 512 seeds, 3 x 512 samples, 2.4 M vertices: 18 -> 8 launches a hop.
 // A call that sizes its buffers from an earlier call of the same shape runs all of these behind LwHop::giveup.
 #include "bms_device.h"
 #include "bms_internal.h"
@@ -58,6 +63,52 @@ constexpr int kDrawTop = 2048;                    // recorded weight sums of P t
 __device__ inline uint64_t ldw_weight(uint32_t cnt, int squared)
 {
     return squared ? (uint64_t)cnt * (uint64_t)cnt : (uint64_t)cnt;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Rows: extents, the gathered order (exclusive scan of the degrees), 256 rows per workgroup; win_added cleared
+// ---------------------------------------------------------------------------------------------
+constexpr int kLwRows = 256;
+__global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb, int64_t *gathered_out)
+{
+    __shared__ int64_t smem[kLwRows / kWave];
+    __shared__ uint32_t number_s;
+    const int tid = threadIdx.x;
+    const uint32_t t = take_number(lb, &number_s);
+    for (int64_t x = (int64_t)t * kLwRows + tid; x < (int64_t)a.k * a.nwin; x += (int64_t)gridDim.x * kLwRows)
+        a.win_added[x] = 0;
+    const int64_t R = a.mb_rowoff[a.k];
+    if (t > 0 && (int64_t)t * kLwRows >= R)
+        return; // nobody with rows comes after
+    const int64_t r = (int64_t)t * kLwRows + tid;
+    int64_t beg = 0, deg = 0;
+    if (r < R) {
+        const int32_t v = a.row_vertex[r];
+        if (v >= 0 && (int64_t)v < a.n) {
+            beg = a.A_rowptr[v];
+            deg = a.A_rowptr[v + 1] - beg;
+        }
+    }
+    int64_t total;
+    const int64_t ex = block_exclusive_scan<int64_t, kLwRows>(deg, smem, total);
+    const int64_t before = sum_before<kLwRows>(lb, t, total, smem);
+    if (r < R) {
+        a.row_beg[r] = beg;
+        a.gather_off[r] = before + ex;
+        a.row_mb[r] = locate_segment(a.mb_rowoff, a.k, r);
+        a.out_rowptr[r] = 0; // per-row counters of the extraction pass
+    }
+    if ((int64_t)(t + 1) * kLwRows >= R && tid == 0) {
+        a.gather_off[R] = before + total;
+        a.out_rowptr[R] = 0;
+        *gathered_out = before + total;
+    }
+}
+
+__global__ __launch_bounds__(256) void ldw_zero_added_kernel(LwHop a)
+{
+    for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < (int64_t)a.k * a.nwin; x += (int64_t)gridDim.x * 256)
+        a.win_added[x] = 0;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -203,67 +254,145 @@ __global__ __launch_bounds__(256) void ldw_bounds_kernel(LwHop a)
 }
 
 // The boundary lists turned window-major (bounds_t[w * rows_bound + r]): the accumulation reads one window of
-// all rows at a time.  64 x 64 tiles through LDS, both sides coalesced.  The list of row r comes from this
+// all rows at a time.  64 rows x 63 windows at a time through LDS, both sides coalesced.  The list of row r comes from this
 // hop's boundary pass, or, when the graph carries an index of every vertex's list, from the index entry of
-// the row's vertex.
-__global__ __launch_bounds__(256) void ldw_bounds_transpose_kernel(LwHop a)
+// the row's vertex.  On the way: win_added[i * nwin + w] += neighbours of minibatch i's rows inside window w (the lengths of
+// their pieces).  Workgroup x of nx.
+constexpr int kBtWindows = 63;
+__device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65], int32_t (&mb_l)[64], int64_t x, int64_t nx)
 {
-    __shared__ uint32_t tile[64][65];
-    if (a.giveup && *a.giveup)
-        return;
     const int64_t ncols = a.nwin + 1;
-    const int64_t nrows = a.index ? a.mb_rowoff[a.k] : a.rows_bound;
-    const int64_t tiles_c = (ncols + 63) / 64, tiles_r = (nrows + 63) / 64;
+    const int64_t nrows = a.mb_rowoff[a.k];
+    const int64_t tiles_c = (a.nwin + kBtWindows - 1) / kBtWindows, tiles_r = (nrows + 63) / 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int64_t t = blockIdx.x; t < tiles_c * tiles_r; t += gridDim.x) {
-        const int64_t r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * 64;
+    for (int64_t t = x; t < tiles_c * tiles_r; t += nx) {
+        const int64_t r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * kBtWindows;
         if (a.index) { // the rows' vertices first, then all of a thread's 16 reads of the index in flight together
             int64_t v[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q)
                 v[q] = r0 + ty + 4 * q < nrows ? (int64_t)a.row_vertex[r0 + ty + 4 * q] : -1;
-            uint32_t x[16];
+            uint32_t y[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) // a seed outside [0, n) is an error reported elsewhere; its row has no neighbours
-                x[q] = (v[q] >= 0 && v[q] < a.n && c0 + tx < ncols) ? a.index[v[q] * ncols + c0 + tx] : 0u;
+                y[q] = (v[q] >= 0 && v[q] < a.n && c0 + tx < ncols) ? a.index[v[q] * ncols + c0 + tx] : 0u;
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                tile[ty + 4 * q][tx] = x[q];
+                tile[ty + 4 * q][tx] = y[q];
         } else {
             for (int y = ty; y < 64; y += 4)
                 if (r0 + y < nrows && c0 + tx < ncols)
                     tile[y][tx] = a.bounds[(r0 + y) * ncols + c0 + tx];
         }
+        if (ty == 0) { // minibatch of the row; -1: no neighbours (its boundaries may not be on record)
+            const int64_t r = r0 + tx;
+            mb_l[tx] = r < nrows && a.gather_off[r + 1] != a.gather_off[r] ? a.row_mb[r] : -1;
+        }
         __syncthreads();
         for (int y = ty; y < 64; y += 4)
-            if (c0 + y < ncols && r0 + tx < nrows)
+            if (c0 + y < ncols && (y < kBtWindows || c0 + y == a.nwin) && r0 + tx < nrows)
                 a.bounds_t[(c0 + y) * a.rows_bound + r0 + tx] = tile[tx][y];
+        if (tx < kBtWindows && c0 + tx < a.nwin) {
+            uint32_t sum = 0; // < 2^32: at most 65535 rows with at most 2^16 neighbours in a window each
+            int mb = -1;
+#pragma unroll 4
+            for (int q = 0; q < 16; ++q) {
+                const int row = ty * 16 + q, i = mb_l[row]; // the same in all lanes
+                if (i < 0)
+                    continue;
+                if (i != mb) {
+                    if (sum)
+                        atomicAdd(&a.win_added[(int64_t)mb * a.nwin + c0 + tx], sum);
+                    sum = 0;
+                    mb = i;
+                }
+                sum += tile[row][tx + 1] - tile[row][tx];
+            }
+            if (sum)
+                atomicAdd(&a.win_added[(int64_t)mb * a.nwin + c0 + tx], sum);
+        }
         __syncthreads();
     }
 }
 
-// win_added[i * nwin + w] = neighbours of minibatch i's rows inside window w (the lengths of their pieces)
-__global__ __launch_bounds__(256) void ldw_win_added_kernel(LwHop a)
+__global__ __launch_bounds__(256) void ldw_bounds_transpose_kernel(LwHop a)
 {
-    __shared__ uint32_t wsum[4];
+    __shared__ uint32_t tile[64][65];
+    __shared__ int32_t mb_l[64];
     if (a.giveup && *a.giveup)
         return;
+    transpose_bounds(a, tile, mb_l, blockIdx.x, gridDim.x);
+}
+
+// Plan, tile rows and the transposed lists in one launch, when the lists come from the index and k < kPlanMb: the first
+// `planners` workgroups each make the plan for themselves (the first one leaves it for the kernels that follow) and then find
+// tile rows, the others transpose.
+constexpr int kPlanMb = 1024;
+__global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int planners)
+{
+    __shared__ union {
+        struct {
+            uint32_t tile[64][65];
+            int32_t mb_l[64];
+        } t;
+        struct {
+            int64_t goff[kPlanMb], tileoff[kPlanMb];
+        } p;
+    } u;
+    __shared__ int64_t smem[4];
+    __shared__ int32_t up_s; // the flag as this workgroup sees it: it may go up meanwhile
+    if (threadIdx.x == 0)
+        up_s = a.giveup ? *a.giveup : 0;
+    __syncthreads();
+    if (up_s)
+        return;
+    if ((int)blockIdx.x >= planners) {
+        transpose_bounds(a, u.t.tile, u.t.mb_l, (int64_t)blockIdx.x - planners, (int64_t)gridDim.x - planners);
+        return;
+    }
     const int tid = threadIdx.x;
-    const int64_t nblk = (int64_t)a.k * a.nwin;
-    for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-        const int i = (int)(blk / a.nwin), w = (int)(blk % a.nwin);
-        const uint32_t *__restrict__ lo_b = a.bounds_t + (int64_t)w * a.rows_bound;
-        uint32_t sum = 0; // < 2^32: at most 65535 rows with at most 2^16 neighbours in a window each
-        for (int64_t r = a.mb_rowoff[i] + tid; r < a.mb_rowoff[i + 1]; r += 256)
-            if (a.gather_off[r + 1] != a.gather_off[r]) // rows without neighbours have no boundaries on record
-                sum += lo_b[a.rows_bound + r] - lo_b[r];
-        sum = wave_sum(sum);
-        __syncthreads();
-        if ((tid & (kWave - 1)) == 0)
-            wsum[tid / kWave] = sum;
-        __syncthreads();
+    const bool first = blockIdx.x == 0;
+    for (int32_t i = tid; i <= a.k; i += 256)
+        u.p.goff[i] = a.gather_off[a.mb_rowoff[i]];
+    __syncthreads();
+    if (a.giveup && u.p.goff[a.k] > a.gathered_cap) { // the kernels after this one see it
+        if (first && tid == 0)
+            *a.giveup = 1;
+        return;
+    }
+    int64_t carry = 0;
+    for (int32_t base = 0; base <= a.k; base += 256) {
+        const int32_t i = base + tid;
+        const int64_t cnt = i < a.k ? (u.p.goff[i + 1] - u.p.goff[i] + a.tile - 1) / a.tile : 0;
+        int64_t total;
+        const int64_t ex = carry + block_exclusive_scan<int64_t, 256>(cnt, smem, total);
+        if (i <= a.k)
+            u.p.tileoff[i] = ex; // entry k: all tiles
+        carry += total;
+    }
+    __syncthreads();
+    if (first) {
         if (tid == 0)
-            a.win_added[blk] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+            *a.cursor = 0;
+        for (int32_t i = tid; i <= a.k; i += 256) {
+            a.mb_goff[i] = u.p.goff[i];
+            a.mb_gtileoff[i] = u.p.tileoff[i];
+            a.tile_queue[i] = 0;
+        }
+    }
+    const int64_t ntiles = u.p.tileoff[a.k];
+    for (int64_t x = (int64_t)blockIdx.x * 256 + tid; x < ntiles; x += (int64_t)planners * 256) {
+        const int i = locate_segment(u.p.tileoff, a.k, x);
+        const int64_t g0 = u.p.goff[i] + (x - u.p.tileoff[i]) * a.tile;
+        int64_t lo = a.mb_rowoff[i], hi = a.mb_rowoff[i + 1];
+        while (hi - lo > 1) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (a.gather_off[mid] <= g0)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        a.tile_row[x] = lo;
     }
 }
 
@@ -486,14 +615,38 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
 
 // one workgroup per minibatch: columns and weight of every window (the sums of its parts), before each of its
 // parts, and before each window; columns of the minibatch
-__global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a)
+__global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a, int64_t *pnnz_out)
 {
     __shared__ uint64_t smem[4];
     __shared__ uint64_t carry_c, carry_w;
+    __shared__ uint32_t last_s;
     const int i = blockIdx.x, tid = threadIdx.x;
+    // the workgroup that comes here last turns the minibatches' counts into p_off
+    auto finish = [&](int64_t count) {
+        if (tid == 0) {
+            __hip_atomic_store(a.mb_count + i, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last_s = arrive_last(a.done, (uint32_t)a.k) ? 1u : 0u;
+        }
+        __syncthreads();
+        if (!last_s)
+            return;
+        uint64_t carry = 0;
+        for (int32_t base = 0; base < a.k; base += 256) {
+            const int32_t j = base + tid;
+            const uint64_t v = j < a.k ? (uint64_t)__hip_atomic_load(a.mb_count + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+            uint64_t total;
+            const uint64_t ex = carry + block_exclusive_scan<uint64_t, 256>(v, smem, total);
+            if (j < a.k)
+                a.p_off[j] = (int64_t)ex;
+            carry += total;
+        }
+        if (tid == 0) {
+            a.p_off[a.k] = (int64_t)carry;
+            *pnnz_out = (int64_t)carry;
+        }
+    };
     if (a.giveup && *a.giveup) {
-        if (tid == 0)
-            a.mb_count[i] = 0;
+        finish(0);
         return;
     }
     if (tid == 0) {
@@ -531,8 +684,7 @@ __global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a)
         }
         __syncthreads();
     }
-    if (tid == 0)
-        a.mb_count[i] = (int64_t)carry_c;
+    finish((int64_t)carry_c);
 }
 
 // Windows to their place in P, with the inclusive prefix sums of the weights.  A window left the accumulation in
@@ -601,14 +753,32 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 // ---------------------------------------------------------------------------------------------
 // SAMPLE: one workgroup per minibatch
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void ldw_draw_kernel(LwHop a)
+// PLACE: the sampled columns go to their place in the stack at once, behind those of the minibatches before (sum_before)
+template <bool PLACE>
+__global__ __launch_bounds__(1024) void ldw_draw_kernel(LwHop a, Lookback lb, int64_t *ncols_out)
 {
     __shared__ uint32_t key[kMaxWinSampled];
     __shared__ uint32_t smem[16];
     __shared__ uint64_t top[kDrawTop];
-    const int i = blockIdx.x, tid = threadIdx.x;
+    __shared__ int64_t smem64[16];
+    __shared__ uint32_t number_s;
+    const int tid = threadIdx.x, i = PLACE ? (int)take_number(lb, &number_s) : (int)blockIdx.x;
+    // where the minibatch's `count` columns begin
+    auto place = [&](uint32_t count) {
+        const int64_t before = sum_before<1024>(lb, (uint32_t)i, count, smem64);
+        if (tid == 0) {
+            a.mb_coloff[i] = before;
+            if (i == a.k - 1) {
+                a.mb_coloff[a.k] = before + count;
+                *ncols_out = before + count;
+            }
+        }
+        return before;
+    };
     if (a.giveup && (*a.giveup || a.p_off[a.k] > a.p_cap)) { // no P: the minibatch gets no columns
-        if (tid == 0)
+        if (PLACE)
+            place(0);
+        else if (tid == 0)
             a.mb_count[i] = 0;
         return;
     }
@@ -690,11 +860,11 @@ __global__ __launch_bounds__(1024) void ldw_draw_kernel(LwHop a)
         heads += (key[j] != kEmptySlot && (j == 0 || key[j] != key[j - 1])) ? 1u : 0u;
     uint32_t total;
     uint32_t rank = block_exclusive_scan<uint32_t, 1024>(heads, smem, total);
-    int32_t *__restrict__ out = a.sel_tmp + (int64_t)i * a.s;
+    int32_t *__restrict__ out = PLACE ? a.col_vertex + place(total) : a.sel_tmp + (int64_t)i * a.s;
     for (uint32_t j = tid * per; j < (tid + 1) * per; ++j)
         if (key[j] != kEmptySlot && (j == 0 || key[j] != key[j - 1]))
             out[rank++] = (int32_t)key[j];
-    if (tid == 0)
+    if (!PLACE && tid == 0)
         a.mb_count[i] = total;
 }
 
@@ -883,6 +1053,72 @@ __global__ __launch_bounds__(256) void ldw_extract_copy_kernel(LwHop a)
     }
 }
 
+// The scan of the rows' counts and the copy in one launch: 256 rows per workgroup, the rows before summed up by sum_before,
+// then one entry per lane and step, whose row is found in the offsets in LDS.
+__global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Lookback lb, int64_t *nnz_out)
+{
+    __shared__ int64_t smem[kLwRows / kWave];
+    __shared__ uint32_t number_s;
+    __shared__ int64_t gather_l[kLwRows];
+    __shared__ uint32_t off_l[kLwRows + 1], first_l[kLwRows];
+    const int tid = threadIdx.x;
+    const uint32_t t = take_number(lb, &number_s);
+    const int64_t R = a.mb_rowoff[a.k];
+    const int64_t r0 = (int64_t)t * kLwRows, r = r0 + tid;
+    if (t > 0 && r0 >= R)
+        return;
+    __shared__ int32_t up_s; // the flag as this workgroup sees it: it may go up meanwhile
+    if (tid == 0)
+        up_s = a.giveup ? *a.giveup : 0;
+    __syncthreads();
+    int64_t cnt = 0;
+    if (!up_s && r < R) {
+        cnt = a.out_rowptr[r];
+        gather_l[tid] = a.gather_off[r];
+        first_l[tid] = a.first_cnt[r];
+    }
+    int64_t total;
+    const int64_t ex = block_exclusive_scan<int64_t, kLwRows>(cnt, smem, total);
+    off_l[tid] = (uint32_t)ex; // < 2^32: at most 256 rows of at most 4096 entries
+    if (tid == 0)
+        off_l[kLwRows] = (uint32_t)total;
+    const int64_t before = sum_before<kLwRows>(lb, t, total, smem);
+    if (r < R)
+        a.out_rowptr[r] = before + ex;
+    if (r0 + kLwRows >= R && tid == 0) {
+        a.out_rowptr[R] = before + total;
+        *nnz_out = before + total;
+    }
+    if (a.giveup && before + total > a.col_cap) { // the kept neighbours do not fit what was provided
+        if (tid == 0)
+            *a.giveup = 1;
+        return;
+    }
+    for (uint32_t e = tid; e < (uint32_t)total; e += kLwRows) {
+        int lo = 0, hi = kLwRows; // last row whose entries begin at or before e: rows without entries share their begin
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (off_l[mid] <= e)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        uint32_t x = e - off_l[lo], piece = first_l[lo];
+        int64_t g = gather_l[lo];
+        if (x >= piece) { // in a later piece of the row: one per tile that it reaches into
+            const int i = a.row_mb[r0 + lo];
+            const int64_t gm = a.mb_goff[i], xm = a.mb_gtileoff[i];
+            int64_t tile = (g - gm) / a.tile;
+            do {
+                x -= piece;
+                piece = a.tile_cnt[xm + ++tile];
+            } while (x >= piece);
+            g = gm + tile * a.tile;
+        }
+        a.out_col[before + e] = a.xtmp[g + x];
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------
@@ -897,12 +1133,32 @@ static void launch_ldw_tiles(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_tile_rows_kernel, dim3(grid_for(L, (a.tiles_bound + 255) / 256, 8)), dim3(256), 0, L.stream, a);
 }
 
+int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *gathered_out, uint32_t *workgroups)
+{
+    const int64_t tiles = (a.rows_bound + kLwRows - 1) / kLwRows;
+    if (tiles > kMostLookback)
+        return -1;
+    *workgroups = (uint32_t)tiles;
+    hipLaunchKernelGGL(ldw_rows_kernel, dim3((unsigned)tiles), dim3(kLwRows), 0, L.stream, a, lb, gathered_out);
+    return 0;
+}
+
+void launch_ldw_zero_added(const Launch &L, const LwHop &a)
+{
+    hipLaunchKernelGGL(ldw_zero_added_kernel, dim3(grid_for(L, ((int64_t)a.k * a.nwin + 255) / 256, 2)), dim3(256), 0, L.stream, a);
+}
+
 void launch_ldw_bounds(const Launch &L, const LwHop &a)
 {
+    const int64_t ttiles = ((a.nwin + kBtWindows - 1) / kBtWindows) * ((a.rows_bound + 63) / 64);
+    if (a.index && a.k < kPlanMb) {
+        const int planners = grid_for(L, (a.tiles_bound + 255) / 256, 1);
+        hipLaunchKernelGGL(ldw_plan_bounds_kernel, dim3(planners + grid_for(L, ttiles, 8)), dim3(256), 0, L.stream, a, planners);
+        return;
+    }
     launch_ldw_tiles(L, a);
     if (!a.index)
         hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
-    const int64_t ttiles = ((a.nwin + 1 + 63) / 64) * ((a.rows_bound + 63) / 64);
     hipLaunchKernelGGL(ldw_bounds_transpose_kernel, dim3(grid_for(L, ttiles, 8)), dim3(256), 0, L.stream, a);
 }
 
@@ -912,7 +1168,7 @@ void launch_ldw_index(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
 
-int launch_ldw_accumulate(const Launch &L, const LwHop &a)
+int launch_ldw_accumulate(const Launch &L, const LwHop &a, int64_t *pnnz_out)
 {
     static bool attr_set = false;
     if (!attr_set) {
@@ -921,12 +1177,11 @@ int launch_ldw_accumulate(const Launch &L, const LwHop &a)
             (void)hipGetLastError(); // not required on every runtime; the launch below reports real failures
         attr_set = true;
     }
-    hipLaunchKernelGGL(ldw_win_added_kernel, dim3(grid_for(L, (int64_t)a.k * a.nwin, 8)), dim3(256), 0, L.stream, a);
     hipLaunchKernelGGL(ldw_accumulate_kernel, dim3(grid_for(L, (int64_t)a.k * a.nwin, 1)), dim3(kAccThreads),
                        ldw_accumulate_lds_bytes(), L.stream, a);
     if (hipGetLastError() != hipSuccess)
         return -1;
-    hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k), dim3(256), 0, L.stream, a);
+    hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k), dim3(256), 0, L.stream, a, pnnz_out);
     return 0;
 }
 
@@ -935,9 +1190,12 @@ void launch_ldw_p_copy(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_p_copy_kernel, dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
 
-void launch_ldw_draw(const Launch &L, const LwHop &a)
+void launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)
 {
-    hipLaunchKernelGGL(ldw_draw_kernel, dim3(a.k), dim3(1024), 0, L.stream, a);
+    if (lb)
+        hipLaunchKernelGGL(ldw_draw_kernel<true>, dim3(a.k), dim3(1024), 0, L.stream, a, *lb, ncols_out);
+    else
+        hipLaunchKernelGGL(ldw_draw_kernel<false>, dim3(a.k), dim3(1024), 0, L.stream, a, Lookback{}, ncols_out);
 }
 
 void launch_ldw_sel_copy(const Launch &L, const LwHop &a)
@@ -951,6 +1209,16 @@ void launch_ldw_extract(const Launch &L, const LwHop &a)
     per_mb = std::min<int64_t>(per_mb, (a.tiles_bound + kExtWaves - 1) / kExtWaves); // never more than there are tiles
     per_mb = std::max<int64_t>(per_mb, 1);
     hipLaunchKernelGGL(ldw_extract_kernel, dim3((unsigned)per_mb, a.k), dim3(kExtThreads), 0, L.stream, a);
+}
+
+int launch_ldw_extract_place(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *nnz_out, uint32_t *workgroups)
+{
+    const int64_t tiles = (a.rows_bound + kLwRows - 1) / kLwRows;
+    if (tiles > kMostLookback)
+        return -1;
+    *workgroups = (uint32_t)tiles;
+    hipLaunchKernelGGL(ldw_extract_place_kernel, dim3((unsigned)tiles), dim3(kLwRows), 0, L.stream, a, lb, nnz_out);
+    return 0;
 }
 
 void launch_ldw_extract_copy(const Launch &L, const LwHop &a)

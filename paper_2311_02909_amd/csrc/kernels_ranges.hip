@@ -100,11 +100,7 @@ __device__ inline void ranges_place(const RangeArgs &a)
 __device__ inline bool count_arrives(uint32_t *cnt, uint32_t count, uint32_t *done, uint32_t workgroups)
 {
     __hip_atomic_store(cnt, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the count is where other dies see it
-    if (__hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != workgroups - 1u)
-        return false;
-    __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    return arrive_last(done, workgroups);
 }
 
 // Workgroups go to the chip's 8 dies in turn.  Of a launch with `per` workgroups for every minibatch, those of one minibatch
