@@ -1392,7 +1392,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     const size_t nw = (size_t)c.k * nwin;
     BMS_TRY(csr->lw_win.ensure(nw * (2 * sizeof(uint32_t) + 3 * sizeof(int64_t)) + 64));
     BMS_TRY(csr->lw_parts.ensure(nw * kWinParts * (2 * sizeof(uint32_t) + 3 * sizeof(uint64_t))));
-    BMS_TRY(csr->lw_count.ensure((4 * (size_t)c.k + 4) * sizeof(int64_t)));
+    BMS_TRY(csr->lw_count.ensure(((3 + kQueueStride) * ((size_t)c.k + 1) + 16) * sizeof(int64_t)));
     if (!csr->lw_index_tried && !(c.flags & BMS_LADIES_NO_INDEX))
         BMS_TRY(build_window_index(c, nwin));
     const uint32_t *index = csr->lw_index_ready && !(c.flags & BMS_LADIES_NO_INDEX) ? csr->lw_index.as<uint32_t>() : nullptr;
@@ -1478,7 +1478,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.mb_count = csr->lw_count.as<int64_t>();
         w.mb_goff = w.mb_count + c.k + 1;
         w.mb_gtileoff = w.mb_goff + c.k + 1;
-        w.tile_queue = reinterpret_cast<unsigned long long *>(w.mb_gtileoff + c.k + 1);
+        w.tile_queue = reinterpret_cast<unsigned long long *>(csr->lw_count.as<int64_t>() + (3 * ((size_t)c.k + 1) + 15) / 16 * 16);
         w.row_mb = a.row_mb;
         w.p_off = hb.p_off.as<int64_t>();
         w.sel_tmp = csr->lw_sel.as<int32_t>();

@@ -325,6 +325,7 @@ constexpr int kWinShift = 16;            // a window = 2^16 vertex ids = 2^16 16
 constexpr int kWinParts = 16;            // a window leaves the accumulation in this many parts of equal id range
 constexpr int32_t kMaxWinRows = 65535;   // frontier rows per minibatch (a 16-bit counter cannot overflow)
 constexpr int32_t kMaxWinSampled = 4096; // columns sampled per minibatch (sorted, then hashed, in LDS)
+constexpr int kQueueStride = 16;         // a counter per 128-byte line
 constexpr int kLwTileMax = 4096;         // positions of the gathered order streamed by one wave at a time: at most
 constexpr int kLwTileMin = 1024;         // ... and at least (hops that gather little use small tiles to fill the chip)
 struct LwHop {
@@ -350,7 +351,7 @@ struct LwHop {
     uint32_t *first_cnt;       // rows: neighbours kept from the piece the row starts with
     int64_t tiles_bound;       // host-side upper bound of the number of tiles
     int32_t tile;              // positions per tile of this hop (power of two in [kLwTileMin, kLwTileMax])
-    unsigned long long *tile_queue; // k+1 counters, zeroed per hop: next tile of each minibatch (extraction), of the hop (boundaries)
+    unsigned long long *tile_queue; // counters kQueueStride apart, zeroed per hop: next tile of each minibatch (extraction)
     int32_t nwin;              // ceil(n / 2^kWinShift)
     uint32_t *bounds;          // rows_bound * (nwin+1), one list per row
     const uint32_t *index;     // n * (nwin+1): the list of every vertex's whole row, built once per graph; or null

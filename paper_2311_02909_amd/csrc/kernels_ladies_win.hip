@@ -56,8 +56,8 @@ struct AccPiece {                          // one nonempty piece of a wave's 64 
     int64_t origin;                        // byte address of its first line - 128 * lines of the wave before it
     uint32_t lo_rel, hi_rel;               // its bytes, relative to origin
 };
+constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
 constexpr int kStreamUnroll = 8; // neighbours per lane in flight in the two streaming passes
-constexpr int kHashSlots = 2 * kMaxWinSampled;    // load factor <= 1/2
 constexpr int kDrawTop = 2048;                    // recorded weight sums of P that a drawing workgroup keeps in LDS
 
 __device__ inline uint64_t ldw_weight(uint32_t cnt, int squared)
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(1024) void ldw_plan_kernel(LwHop a)
             const int64_t g0 = a.gather_off[a.mb_rowoff[i]];
             a.mb_goff[i] = g0;
             if (a.tile_queue)
-                a.tile_queue[i] = 0;
+                a.tile_queue[i * kQueueStride] = 0;
             if (i < a.k)
                 cnt = (a.gather_off[a.mb_rowoff[i + 1]] - g0 + a.tile - 1) / a.tile;
         }
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int plann
         for (int32_t i = tid; i <= a.k; i += 256) {
             a.mb_goff[i] = u.p.goff[i];
             a.mb_gtileoff[i] = u.p.tileoff[i];
-            a.tile_queue[i] = 0;
+            a.tile_queue[i * kQueueStride] = 0;
         }
     }
     const int64_t ntiles = u.p.tileoff[a.k];
@@ -691,7 +691,6 @@ __global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a, int64_t *pnn
 // kWinParts parts (one per wave) whose sizes and weights are on record, so every part has a known place and a
 // known weight before it: one wave per part streams it, 64 entries at a time, with lane scans for the sums and
 // no workgroup barrier.
-constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
 constexpr int kCopyUnroll = 4;
 __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 {
@@ -879,137 +878,208 @@ __global__ __launch_bounds__(256) void ldw_sel_copy_kernel(LwHop a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// EXTRACT: blockIdx.y = minibatch; the workgroups of a minibatch share its rows wave by wave
+// EXTRACT: blockIdx.y = minibatch; the workgroups of a minibatch share its tiles wave by wave
 // ---------------------------------------------------------------------------------------------
-// kFilterBits hash bits: all of them index the filter bitmap (16 KB: with up to 4096 sampled columns about 1.5 % of
-// the neighbours pass, half of what a 2^16-bit filter lets through; twice the size would cost the second workgroup
-// per compute unit), the low 13 the table
-constexpr int kFilterBits = 17;
-__device__ inline uint32_t ldw_hash(uint32_t v) { return (v * 0x9E3779B1u) >> (32 - kFilterBits); }
-static_assert(kHashSlots == 1 << 13, "hash width out of step");
-constexpr int kFilterWords = (1 << kFilterBits) / 32;
+// Hash of a column: its leading bits index the filter bitmap (2^17 bits, 16 KB: with 2048 sampled columns about 1.5 % of the
+// neighbours pass; 2^16 above that, so that two workgroups fit a compute unit), its low ones the table (load factor <= 1/2).
+__device__ inline uint32_t ldw_hash(uint32_t v, int filter_bits) { return (v * 0x9E3779B1u) >> (32 - filter_bits); }
 
-__global__ __launch_bounds__(kExtThreads) void ldw_extract_kernel(LwHop a)
+// A wave takes the positions of its tile 512 at a time, whatever rows they lie in: a row list of 64 rows at a time is held
+// across the lanes, and where it matters (a step with more than one row) the row of a position follows from counting row
+// starts up to it, as in the accumulation.  Going row by row instead left a wave with one short row's few lines in flight
+// (two trips to memory of 2 us each per row: 75 k neighbours in rows of 49 took 55 us, 15 us so).
+struct ExtWave {
+    int64_t shift[kWave];     // by rank among the list's rows with neighbours: A_col index of tile position 0 if it lay in the row
+    uint32_t starts[kStreamUnroll * 2]; // one bit per position of a step: a row starts there
+    uint32_t queue[2 * kWave];          // neighbours that passed the filter, in order
+    uint16_t begin[kWave];    // by rank: where the row's piece begins in the tile
+    uint16_t kept[kWave];     // by rank: neighbours of the piece found among the sampled columns
+    uint8_t queue_rank[2 * kWave];
+};
+
+__global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, int32_t slots, int filter_bits)
 {
-    __shared__ uint32_t hkey[kHashSlots];
-    __shared__ uint16_t hval[kHashSlots];
-    __shared__ uint32_t maybe[kFilterWords]; // bit h set: some sampled column hashes to h
-    __shared__ uint32_t queue_all[kExtWaves * 2 * kWave]; // per wave: neighbours that passed the filter, in row order
+    extern __shared__ int64_t ext_lds[];
+    ExtWave *waves = reinterpret_cast<ExtWave *>(ext_lds);
+    uint32_t *hkey = reinterpret_cast<uint32_t *>(waves + kExtWaves); // [slots]
+    uint32_t *maybe = hkey + slots;                                   // bit h set: some sampled column hashes to h
+    uint16_t *hval = reinterpret_cast<uint16_t *>(maybe + (1 << filter_bits) / 32); // [slots]
     if (a.giveup && *a.giveup)
         return;
     const int i = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
-    uint32_t *queue = queue_all + (tid / kWave) * 2 * kWave;
+    ExtWave &me = waves[tid / kWave];
     const int64_t c0 = a.mb_coloff[i];
     const int32_t ns = (int32_t)(a.mb_coloff[i + 1] - c0);
     const int64_t x0 = a.mb_gtileoff[i], ntiles = a.mb_gtileoff[i + 1] - x0;
     if (ns == 0 || (int64_t)blockIdx.x * kExtWaves >= ntiles)
         return; // nothing sampled: every row stays empty (the counters start at zero)
-    for (int x = tid; x < kHashSlots; x += kExtThreads)
+    for (int x = tid; x < slots; x += kExtThreads)
         hkey[x] = kEmptySlot;
-    for (int x = tid; x < kFilterWords; x += kExtThreads)
+    for (int x = tid; x < (1 << filter_bits) / 32; x += kExtThreads)
         maybe[x] = 0;
     __syncthreads();
     for (int j = tid; j < ns; j += kExtThreads) {
-        const uint32_t v = (uint32_t)a.col_vertex[c0 + j];
-        atomicOr(&maybe[ldw_hash(v) >> 5], 1u << (ldw_hash(v) & 31u));
-        uint32_t slot = ldw_hash(v) & (kHashSlots - 1);
+        const uint32_t v = (uint32_t)a.col_vertex[c0 + j], h = ldw_hash(v, filter_bits);
+        atomicOr(&maybe[h >> 5], 1u << (h & 31u));
+        uint32_t slot = h & (uint32_t)(slots - 1);
         while (atomicCAS(&hkey[slot], kEmptySlot, v) != kEmptySlot)
-            slot = (slot + 1) & (kHashSlots - 1);
+            slot = (slot + 1) & (uint32_t)(slots - 1);
         hval[slot] = (uint16_t)j;
     }
     __syncthreads();
-    const uint64_t below = (1ull << lane) - 1ull;
+    const uint64_t below = (1ull << lane) - 1ull, below_incl = below | (1ull << lane);
     unsigned long long *rowcnt = reinterpret_cast<unsigned long long *>(a.out_rowptr);
     const int64_t nrows = a.mb_rowoff[a.k];
-    // tiles cost very different amounts (one long piece, or many short rows): the minibatch's tiles go to
+    // tiles cost very different amounts: the minibatch's tiles go to
     // whichever of its waves is free, off a shared counter, until none is left
     // A wave's first tile is its own number among the minibatch's waves; the counter hands out the tiles after
     // those.  The next tile is asked for before the current one is worked on, so that the answer (a trip to the
-    // counter's home in memory, shared by all waves of the minibatch) is there when it is needed.
+    // counter's home in memory, shared by all waves of the minibatch) is there when it is needed.  (Additions to one memory
+    // line follow one another at about 8 ns each, so every counter has a line of its own, and waves that are at least as
+    // many as tiles do not ask: 32 x 512, 7.6 M neighbours: 62 us when the counters shared lines, 27 so.)
     const int64_t nwaves = (int64_t)gridDim.x * kExtWaves;
     int64_t t = (int64_t)blockIdx.x * kExtWaves + tid / kWave;
     while (t < ntiles) {
-        int64_t t_next = 0;
-        if (lane == 0)
-            t_next = nwaves + (int64_t)atomicAdd(a.tile_queue + i, 1ull);
+        int64_t t_next = ntiles;
+        if (lane == 0 && nwaves < ntiles)
+            t_next = nwaves + (int64_t)atomicAdd(a.tile_queue + i * kQueueStride, 1ull);
         const int64_t g0 = a.mb_goff[i] + t * a.tile;
-        const int64_t g1 = min(g0 + a.tile, a.mb_goff[i + 1]);
-        ldw_walk_tile(a, g0, g1, a.tile_row[x0 + t], nrows,
-                      [&](int64_t r, int64_t rs, int64_t re, int64_t shift, int64_t g, int64_t pe) {
-            (void)re;
-            int32_t *__restrict__ out = a.xtmp + g; // the kept neighbours of a piece start where the piece starts
-            uint32_t kept = 0;
+        const int32_t len = (int32_t)(min(g0 + a.tile, a.mb_goff[i + 1]) - g0); // positions 0 .. len of the tile
+        int64_t rw = a.tile_row[x0 + t]; // first row of the list
+        int32_t p = 0;
+        while (p < len) {
+            const int64_t start = a.gather_off[min(rw + lane, nrows)], stop = a.gather_off[min(rw + lane + 1, nrows)];
+            const bool row = stop > start; // with neighbours
+            // in the tile; rows of other tiles are clamped to its ends
+            const int32_t rs = (int32_t)max<int64_t>(min<int64_t>(start - g0, len), -1);
+            const int32_t list_end = (int32_t)min<int64_t>(__shfl(stop, kWave - 1, kWave) - g0, len);
+            const bool fresh = start >= g0, in_tile = row && start - g0 < len; // the piece is the row's first; there is one
+            const int rank = __popcll(__ballot(row) & below);
+            __builtin_amdgcn_wave_barrier();
+            if (row) {
+                me.shift[rank] = a.row_beg[rw + lane] - start + g0;
+                me.begin[rank] = (uint16_t)max(rs, 0);
+            }
+            me.kept[lane] = 0;
+            __builtin_amdgcn_wave_barrier();
             uint32_t qn = 0; // neighbours waiting in the wave's queue (the same in every lane)
             // looks the first n <= 64 queued neighbours up in the table, appends the local columns of those found
-            // to the piece's output in queue order, and moves the rest of the queue down
+            // to their pieces' output in queue order, and moves the rest of the queue down
             auto drain = [&](uint32_t n) {
                 __builtin_amdgcn_wave_barrier();
-                const uint32_t val = (uint32_t)lane < n ? queue[lane] : kEmptySlot;
+                const bool mine = (uint32_t)lane < n;
+                const uint32_t val = mine ? me.queue[lane] : kEmptySlot;
+                const int rk = mine ? (int)me.queue_rank[lane] : -1;
                 int32_t local = -1;
-                if (val != kEmptySlot) {
-                    uint32_t slot = ldw_hash(val) & (kHashSlots - 1);
+                if (mine) {
+                    uint32_t slot = ldw_hash(val, filter_bits) & (uint32_t)(slots - 1);
                     uint32_t kx;
                     while ((kx = hkey[slot]) != kEmptySlot) {
                         if (kx == val) {
                             local = hval[slot];
                             break;
                         }
-                        slot = (slot + 1) & (kHashSlots - 1);
+                        slot = (slot + 1) & (uint32_t)(slots - 1);
                     }
                 }
                 const uint64_t found = __ballot(local >= 0);
-                if (local >= 0)
-                    out[kept + __popcll(found & below)] = local;
-                kept += __popcll(found);
+                if (found) {
+                    const int prev = __shfl_up(rk, 1, kWave), next = __shfl_down(rk, 1, kWave);
+                    const uint64_t firsts = __ballot(mine && (lane == 0 || prev != rk)); // first queued one of every row
+                    const uint64_t same = below & ~((1ull << (63 - __clzll((long long)(firsts & below_incl)))) - 1ull); // before this one, same row
+                    const uint32_t at = mine ? me.kept[rk] + (uint32_t)__popcll(found & same) : 0u;
+                    if (local >= 0)
+                        a.xtmp[g0 + me.begin[rk] + at] = local; // the kept neighbours of a piece start where the piece starts
+                    __builtin_amdgcn_wave_barrier();
+                    if (mine && ((uint32_t)lane == n - 1u || next != rk)) // last queued one of its row
+                        me.kept[rk] = (uint16_t)(at + (local >= 0 ? 1u : 0u));
+                }
                 const uint32_t rest = qn - n;
-                const uint32_t moved = (uint32_t)lane < rest ? queue[kWave + lane] : 0u;
+                const bool move = (uint32_t)lane < rest;
+                const uint32_t moved = move ? me.queue[kWave + lane] : 0u;
+                const uint8_t moved_rank = move ? me.queue_rank[kWave + lane] : 0;
                 __builtin_amdgcn_wave_barrier();
-                if ((uint32_t)lane < rest)
-                    queue[lane] = moved;
+                if (move) {
+                    me.queue[lane] = moved;
+                    me.queue_rank[lane] = moved_rank;
+                }
                 qn = rest;
                 __builtin_amdgcn_wave_barrier();
             };
-            for (int64_t p0 = g; p0 < pe; p0 += kStreamUnroll * kWave) {
-                const int32_t *__restrict__ from = a.A_col + (shift + p0); // slot x of the step is position p0 + x
-                const int32_t nslots = (int32_t)min<int64_t>(pe - p0, kStreamUnroll * kWave);
+            for (; p < list_end; p += kStreamUnroll * kWave) {
+                const int32_t n = min(list_end - p, kStreamUnroll * kWave);
+                int rank0 = __popcll(__ballot(row && rs <= p)) - 1; // row of position p
+                const bool inside = row && rs > p && rs < p + n;
+                const bool one = __ballot(inside) == 0; // one row
+                const int32_t left = n - lane;
                 uint32_t v[kStreamUnroll];
+                uint32_t ranks[kStreamUnroll / 4] = {}; // 8 bits each
+                if (one) {
+                    const int32_t *__restrict__ from = a.A_col + (me.shift[rank0] + p) + lane;
 #pragma unroll
-                for (int u = 0; u < kStreamUnroll; ++u) {
-                    const int32_t x = u * kWave + lane;
-                    v[u] = x < nslots ? (uint32_t)from[x] : kEmptySlot;
+                    for (int u = 0; u < kStreamUnroll; ++u) {
+                        v[u] = kEmptySlot;
+                        if (left > u * kWave)
+                            v[u] = (uint32_t)from[u * kWave];
+                    }
+                } else {
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < 2 * kStreamUnroll)
+                        me.starts[lane] = 0;
+                    __builtin_amdgcn_wave_barrier();
+                    if (inside)
+                        atomicOr(&me.starts[(rs - p) >> 5], 1u << ((rs - p) & 31));
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int u = 0; u < kStreamUnroll; ++u) {
+                        const uint64_t m = reinterpret_cast<const uint64_t *>(me.starts)[u];
+                        const int rk = rank0 + __popcll(m & below_incl);
+                        rank0 += __popcll(m);
+                        v[u] = kEmptySlot;
+                        if (left > u * kWave)
+                            v[u] = (uint32_t)a.A_col[me.shift[rk] + (p + lane + u * kWave)];
+                        ranks[u / 4] |= (uint32_t)rk << (8 * (u % 4));
+                    }
                 }
                 // almost no neighbour is a sampled column: one bit per hash value answers "certainly not" for
                 // nearly all of them with a single LDS read each (all of a step's reads in flight together).
                 // The few that pass are queued in row order; the table is searched a full wave of them at a
-                // time (and at the end of the piece), not step by step
+                // time (and at the end of the row list), not step by step
                 uint32_t word[kStreamUnroll];
 #pragma unroll
                 for (int u = 0; u < kStreamUnroll; ++u)
-                    word[u] = maybe[ldw_hash(v[u]) >> 5];
+                    word[u] = maybe[ldw_hash(v[u], filter_bits) >> 5];
 #pragma unroll
                 for (int u = 0; u < kStreamUnroll; ++u) {
-                    const bool pass = v[u] != kEmptySlot && ((word[u] >> (ldw_hash(v[u]) & 31u)) & 1u);
+                    const bool pass = v[u] != kEmptySlot && ((word[u] >> (ldw_hash(v[u], filter_bits) & 31u)) & 1u);
                     const uint64_t pm = __ballot(pass);
                     if (pm == 0)
                         continue;
-                    if (pass)
-                        queue[qn + __popcll(pm & below)] = v[u];
+                    if (pass) {
+                        const uint32_t at = qn + __popcll(pm & below);
+                        me.queue[at] = v[u];
+                        me.queue_rank[at] = (uint8_t)(one ? (uint32_t)rank0 : ranks[u / 4] >> (8 * (u % 4)));
+                    }
                     qn += __popcll(pm);
                     if (qn >= (uint32_t)kWave)
                         drain(kWave);
                 }
             }
+            p = list_end;
             while (qn)
                 drain(qn < (uint32_t)kWave ? qn : (uint32_t)kWave);
-            if (lane == 0) {
-                if (g == rs)
+            if (in_tile) { // the pieces of the list's rows in this tile are done
+                const uint32_t kept = me.kept[rank];
+                const int64_t r = rw + lane;
+                if (fresh)
                     a.first_cnt[r] = kept; // the piece a row starts with
                 else
                     a.tile_cnt[x0 + t] = kept; // the piece a tile starts with, of a row begun earlier
                 if (kept)
                     atomicAdd(&rowcnt[r], (unsigned long long)kept);
             }
-        });
+            rw += kWave;
+        }
         t = __shfl(t_next, 0, kWave);
     }
 }
@@ -1208,7 +1278,19 @@ void launch_ldw_extract(const Launch &L, const LwHop &a)
     int64_t per_mb = (L.num_cu * 2 + a.k - 1) / a.k; // workgroups per minibatch: about 2 per compute unit in all
     per_mb = std::min<int64_t>(per_mb, (a.tiles_bound + kExtWaves - 1) / kExtWaves); // never more than there are tiles
     per_mb = std::max<int64_t>(per_mb, 1);
-    hipLaunchKernelGGL(ldw_extract_kernel, dim3((unsigned)per_mb, a.k), dim3(kExtThreads), 0, L.stream, a);
+    int32_t slots = 1024;
+    while (slots < 2 * a.s)
+        slots *= 2;
+    const int filter_bits = a.s <= 2048 ? 17 : 16;
+    const size_t lds = kExtWaves * sizeof(ExtWave) + (size_t)slots * 6 + ((size_t)1 << filter_bits) / 8;
+    static bool attr_set = false;
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(ldw_extract_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                80 * 1024) != hipSuccess)
+            (void)hipGetLastError(); // not required on every runtime
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(ldw_extract_kernel, dim3((unsigned)per_mb, a.k), dim3(kExtThreads), lds, L.stream, a, slots, filter_bits);
 }
 
 int launch_ldw_extract_place(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *nnz_out, uint32_t *workgroups)

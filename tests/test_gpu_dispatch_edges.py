@@ -96,3 +96,23 @@ def test_extract_by_vertex_ranges(n, b):
         _check(rowptr, col, random_batches(n, k, b, rng), (40, 2), **variant)
     if n > 100_000:  # the sampled ids of the rows in one launch, then ranges
         _check(rowptr, col, random_batches(n, 6, b, rng), (3, 13), union_dst=True)
+
+
+# layer-wise: rows and minibatches up to which workgroups add up those before them (262144 and 1024), k from which the plan is a
+# launch of its own (1024), table sizes of the extraction, lists of 64 rows in which most have no neighbours or one
+@pytest.mark.parametrize("n,deg,k,b,s", [(3000, 6.0, 1024, 3, (4, 3)), (3000, 6.0, 1023, 3, (3,)), (3000, 6.0, 1025, 2, (3, 4)),
+                                         (30_000, 4.0, 291, 900, (5, 7)), (30_000, 4.0, 293, 900, (5, 7)), (90_000, 0.8, 3, 5000, (2048, 60)),
+                                         (90_000, 0.8, 2, 5000, (2049, 4096)), (70_000, 60.0, 2, 700, (4096, 513))])
+def test_layerwise_limits(n, deg, k, b, s):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(n + k + b)
+    rowptr, col = random_csr(n, deg, rng)
+    batches = random_batches(n, k, b, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    for squared in (False, True):
+        ref = O.sample_ladies(rowptr, col, batches, s, 17, 5, squared)
+        res = None
+        for index in (True, True, False):
+            res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), s, 17, mb_base=5, squared=squared, recycle=res, index=index)
+            assert_hops_equal(res.hops(), ref, with_p=True, what="k=%d b=%d s=%s squared=%s index=%s" % (k, b, s, squared, index))
