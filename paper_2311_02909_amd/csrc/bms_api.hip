@@ -1078,10 +1078,11 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             if (seg_sort && mode[h] < 2) {
                 const double per_mb = (double)nnz_tune / c.k + 1.0;
                 // ids dense enough in [0, n) that a pass over a bitmap of a segment's id range costs less than sorting
-                // its ids: segments as wide as the bitmap kernel takes, as long as they hold well under 2^16 ids
+                // its ids: segments as wide as the bitmap kernel takes with two workgroups on a compute unit, as long as
+                // they hold well under 2^16 ids
                 by_bitmap = (double)csr->n <= kBitmapIdsPerEntry * per_mb ? 1 : 0;
                 const double target = by_bitmap ? 16384.0 : 3000.0;
-                const int32_t most = by_bitmap ? kMaxBitmapShift : 31;
+                const int32_t most = by_bitmap ? kPlacedBitmapShift : 31;
                 cshift = 0;
                 while (cshift < most && (double)(2LL << cshift) * per_mb <= target * (double)csr->n)
                     ++cshift;

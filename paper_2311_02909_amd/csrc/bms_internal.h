@@ -239,6 +239,7 @@ constexpr int kSegCap = 65535;      // most entries a segment may hold: the rank
 constexpr int kMaxSegments = 2560;  // 3 words each beside the staging of the split / un-split kernels must fit in 160 KB of LDS
 constexpr int kMaxCells = 4096;      // cells of the table that maps ids to segments of unequal width
 constexpr int kMaxBitmapShift = 20; // the bitmap ranking kernel holds 2^cshift bits in LDS (128 KB)
+constexpr int kPlacedBitmapShift = 18; // ... and up to here two workgroups' bitmaps and their distinct ids on a compute unit
 // EXTRACT of a hop by id-range segments (C > 0).  counted: the per-segment counts are there already.  Also writes
 // the next hop's row tiles (next_tileoff, k + 2 entries as launch_plan_tiles with max_out gives them).  `done` is a
 // device word that is zero between launches.

@@ -299,13 +299,15 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
 //      place in ascending order
 //   5  popcount prefix over the head bits: the rank of an id among the distinct ones = heads before its run
 //   6  ranks leave in slot order; the heads leave their ids at their rank, copied out as the distinct ids
+// A chain of dependent LDS steps, so what counts is how many workgroups share a compute unit: 80 registers let three do so (two
+// before).  256 x 240 k ids of 111 M: 343 us with two, 296 with three, 309 with four, which spill and cannot fetch ahead.
 constexpr int kRankCap = 4096;    // ids of a segment that one workgroup of the ranking kernel takes
 constexpr int kRankThreads = 512;
 constexpr int kRankBucketBits = 12; // at most 4096 buckets
 constexpr int kRankMaxInBucket = 32;
 static_assert(kRankCap == kRankCapFwd, "segment capacity out of step");
 
-__global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
+__global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
 {
     constexpr int NT = kRankThreads, NW = NT / kWave, PER = kRankCap / NT, NB = 1 << kRankBucketBits;
     __shared__ uint4 cnt4[NB / 4 + 1];           // bucket sizes, then bucket starts; start[nb] = m
@@ -315,7 +317,8 @@ __global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
     uint32_t *cnt = reinterpret_cast<uint32_t *>(cnt4);
     if (*a.fallback)
         return;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int64_t nseg = (int64_t)a.k * a.C;
     // The ids of the segment after this one are fetched while this one is ranked (a workgroup's segments follow one
     // another as chains of dependent steps, and only two workgroups fit a compute unit).
@@ -348,6 +351,7 @@ __global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
     where(blockIdx.x, s0, m, e0);
     fetch(s0, m, e0, key);
     for (int64_t w = blockIdx.x; w < nseg; w += gridDim.x, s0 = s0_next, m = m_next, e0 = e0_next) {
+        asm volatile("" : "+v"(tid), "+v"(lane)); // (places: computed anew for every segment, not kept in registers)
         where(w + gridDim.x, s0_next, m_next, e0_next);
         const int64_t i = w % a.k;
         const uint32_t cseg = (uint32_t)(w / a.k);
@@ -384,11 +388,11 @@ __global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
             hbits[x] = 0;
         __syncthreads();
         fetch(s0_next, m_next, e0_next, key_next);
-        uint32_t slot[PER];
+        uint32_t at[PER]; // slot in the bucket << 16; then start of the bucket below it; from step 4 on: place of the id's run
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (key[q] != 0xFFFFFFFFu)
-                slot[q] = atomicAdd(&cnt[key[q] >> bshift], 1u);
+                at[q] = atomicAdd(&cnt[key[q] >> bshift], 1u);
         __syncthreads();
         // exclusive scan of the bucket sizes, in place
         uint4 cv[2];
@@ -441,35 +445,34 @@ __global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
         if (tid == 0)
             cnt[nb] = m;
         __syncthreads();
-        uint32_t bs[PER]; // start of the id's bucket; from step 4 on: place of its run
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (key[q] != 0xFFFFFFFFu) {
-                bs[q] = cnt[key[q] >> bshift];
-                sorted[bs[q] + slot[q]] = key[q];
+                const uint32_t bs = cnt[key[q] >> bshift];
+                sorted[bs + at[q]] = key[q];
+                at[q] = at[q] << 16 | bs;
             }
         __syncthreads();
         // place of every id's run of equal ids in ascending order; heads
         if (bshift == 0) { // one id per bucket: the run is the bucket
 #pragma unroll
             for (int q = 0; q < PER; ++q)
-                if (key[q] != 0xFFFFFFFFu && slot[q] == 0)
-                    atomicOr(&hbits[bs[q] >> 5], 1u << (bs[q] & 31u));
+                if (key[q] != 0xFFFFFFFFu && at[q] < 0x10000u)
+                    atomicOr(&hbits[at[q] >> 5], 1u << (at[q] & 31u));
         } else {
 #pragma unroll
             for (int q = 0; q < PER; ++q)
                 if (key[q] != 0xFFFFFFFFu) {
-                    const uint32_t be = cnt[(key[q] >> bshift) + 1u], me = bs[q] + slot[q];
+                    const uint32_t be = cnt[(key[q] >> bshift) + 1u], bs = at[q] & 0xFFFFu, me = bs + (at[q] >> 16);
                     uint32_t less = 0, eqb = 0;
-                    for (uint32_t t = bs[q]; t < be; ++t) {
+                    for (uint32_t t = bs; t < be; ++t) {
                         const uint32_t o = sorted[t];
                         less += o < key[q] ? 1u : 0u;
                         eqb += (o == key[q] && t < me) ? 1u : 0u;
                     }
-                    bs[q] += less;
-                    slot[q] = eqb; // from here on: 0 marks the head of a run
+                    at[q] = eqb << 16 | (bs + less); // from here on: 0 in the upper half marks the head of a run
                     if (eqb == 0)
-                        atomicOr(&hbits[bs[q] >> 5], 1u << (bs[q] & 31u));
+                        atomicOr(&hbits[at[q] >> 5], 1u << (at[q] & 31u));
                 }
         }
         __syncthreads();
@@ -496,10 +499,10 @@ __global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (key[q] != 0xFFFFFFFFu) {
-                const uint32_t p = bs[q];
+                const uint32_t p = at[q] & 0xFFFFu;
                 const uint32_t r = hpre[p >> 5] + __popc(hbits[p >> 5] & ((1u << (p & 31u)) - 1u));
                 ranks[q * NT + tid] = (uint16_t)r;
-                if (slot[q] == 0)
+                if (at[q] < 0x10000u)
                     sorted[r] = key[q]; // every id has been looked at (step 4): their place now takes the distinct ones
             }
         __syncthreads();
@@ -514,45 +517,54 @@ __global__ __launch_bounds__(kRankThreads) void dd_rank_kernel(DedupArgs a)
 }
 
 // Ranking through a bitmap of the segment's id range in LDS (2^cshift bits, at most 128 KB): no sort.  The rank
-// of an id among the segment's distinct ids is the number of set bits below it, the distinct ids in rank order are
-// the set bits in order.  Work per segment = one pass over the bitmap (16 bytes per lane and access, no bank
-// conflicts) + a few operations per id, whatever the ids' multiplicities; a segment may hold up to kSegCap ids (a
-// rank has 16 bits).  LISTED = false: every segment of the hop (hops whose ids are dense enough that the pass over
-// the bitmap costs less than sorting); LISTED = true: the segments that the sorting kernel handed over.
+// of an id among the segment's distinct ids is the number of set bits below it.  Work per segment = one pass over the bitmap
+// (16 bytes per lane and access, no bank conflicts) + a few operations per id, whatever the ids' multiplicities; a segment may
+// hold up to kSegCap ids (a rank has 16 bits).  LISTED = false: every segment of the hop (hops whose ids are dense enough that
+// the pass over the bitmap costs less than sorting); LISTED = true: the segments that the sorting kernel handed over.
 //   1  the ids' bits are set (LDS atomics); the first kBmKeep ids of every thread stay in registers
 //   2  every wave owns a contiguous part of the bitmap, in "quads" of 128 bits, quad it*64 + lane of the part in
 //      iteration it: popcounts, wave totals -> set bits before the wave's part; running count before every quad
-//      (16 bits, kept in LDS); the set bits of the quads leave as the distinct ids
-//   3  rank of an id = count before its quad + set bits below it inside the quad
+//      (16 bits, kept in LDS)
+//   3  rank of an id = count before its quad + set bits below it inside the quad; every id goes to its rank's place in LDS
+//      (equal ids to the same one), from where the distinct ids leave in order
 //   4  the bitmap is cleared again: word by word through the ids when they are few, else as a whole
+// What bounds it is latency: trips to memory for ids that are not in registers, and, before step 3 did it, the stores of the
+// distinct ids straight from the bitmap, scattered over a wave's lanes.  128 x 586 k ids of 8.7 M: 475 us so, 262 us now.
 constexpr int kBmThreads = 1024;
 constexpr int kBmWaves = kBmThreads / kWave;
-constexpr int kBmKeep = 4;  // ids per thread kept in registers between the passes (segments up to 4096 ids)
+constexpr int kBmKeep = 10; // ids per thread kept in registers between the passes (segments up to 10240 ids)
 constexpr int kBmIts = 8;   // quads per lane: 16 waves x 64 lanes x 8 quads x 128 bits = 2^20 bits
+constexpr int kBmPlaces = 10240; // distinct ids that go through LDS, where it has room for them
 static_assert(kBmWaves * kWave * kBmIts * 128 == (1 << kMaxBitmapShift), "bitmap geometry out of step");
+static uint32_t bm_quads(int cshift)
+{
+    uint32_t quads = (uint32_t)(((size_t)1 << cshift) / 128);
+    return quads < (uint32_t)(kBmWaves * kWave) ? (uint32_t)(kBmWaves * kWave) : quads; // every lane owns at least one quad
+}
+// places for distinct ids beside the bitmap: all of kBmPlaces as long as two workgroups share a compute unit
+static int bm_places(int cshift) { return (size_t)bm_quads(cshift) * 18 + (size_t)kBmPlaces * 4 <= 78 * 1024 ? kBmPlaces : 0; }
 size_t dd_bitmap_lds_bytes(int cshift)
 {
-    size_t quads = ((size_t)1 << cshift) / 128;
-    if (quads < (size_t)kBmWaves * kWave)
-        quads = (size_t)kBmWaves * kWave; // every lane owns at least one quad
-    return quads * 16 + quads * sizeof(uint16_t);
+    return (size_t)bm_quads(cshift) * 18 + (size_t)bm_places(cshift) * 4;
 }
 
 template <bool LISTED>
-__global__ __launch_bounds__(kBmThreads) void dd_bitmap_kernel(DedupArgs a)
+__global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, uint32_t places)
 {
-    extern __shared__ uint4 bm_lds[]; // quads, then one 16-bit running count per quad
+    extern __shared__ uint4 bm_lds[]; // quads, then `places` ids, then one 16-bit running count per quad
     __shared__ uint32_t wtot[kBmWaves];
     if (*a.fallback || a.wbits_max > kMaxBitmapShift)
         return;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint32_t nq = (1u << a.wbits_max) / 128u;
     if (nq < (uint32_t)(kBmWaves * kWave))
         nq = kBmWaves * kWave;
     const int its = (int)(nq / (kBmWaves * kWave)); // quads per lane: 1, 2, 4 or 8
     uint4 *quads = bm_lds;
     uint32_t *words = reinterpret_cast<uint32_t *>(bm_lds);
-    uint16_t *qpre = reinterpret_cast<uint16_t *>(bm_lds + nq);
+    uint32_t *place = reinterpret_cast<uint32_t *>(bm_lds + nq);
+    uint16_t *qpre = reinterpret_cast<uint16_t *>(place + places);
     const uint32_t q_wave = (uint32_t)wave * (uint32_t)(its * kWave); // first quad of this wave's part
     const int64_t nwork = LISTED ? (int64_t)*a.big_count : (int64_t)a.k * a.C;
     if ((int64_t)blockIdx.x >= nwork)
@@ -560,15 +572,14 @@ __global__ __launch_bounds__(kBmThreads) void dd_bitmap_kernel(DedupArgs a)
     for (int it = 0; it < its; ++it)
         quads[q_wave + it * kWave + lane] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    // a segment's first ids are fetched while the segment before it is worked on
+    // where a segment lies; its first ids are fetched while the segment before it is worked on
     struct Seg {
         int64_t sg, e0;
-        uint32_t s0, m, c, id0;
-        uint32_t keep[kBmKeep]; // the first kBmKeep ids of this thread, relative to the segment's first id
+        uint32_t s0, m, id0;
     };
-    auto fetch = [&](int64_t x, Seg &g) {
-        g.m = 0;
-        g.sg = -1;
+    auto locate = [&](int64_t x, Seg &g) {
+        g.m = g.s0 = g.id0 = 0;
+        g.sg = g.e0 = 0;
         if (x >= nwork)
             return;
         if (LISTED)
@@ -576,39 +587,42 @@ __global__ __launch_bounds__(kBmThreads) void dd_bitmap_kernel(DedupArgs a)
         else // workgroups that run at the same time take segments of different minibatches
             g.sg = (x % a.k) * a.C + x / a.k;
         const int64_t i = g.sg / a.C;
-        g.c = (uint32_t)(g.sg % a.C);
+        const uint32_t c = (uint32_t)(g.sg % a.C);
         const uint32_t *__restrict__ soff = a.seg_off + i * (a.C + 1);
-        g.s0 = soff[g.c];
-        g.m = soff[g.c + 1] - g.s0;
+        g.s0 = soff[c];
+        g.m = soff[c + 1] - g.s0;
         g.e0 = a.mb_edgeoff[i];
-        const uint32_t *__restrict__ ids = a.ids_seg + g.e0 + g.s0;
-        uint32_t id0;
         int wbits;
-        seg_range(a, g.c, id0, wbits);
-        g.id0 = id0;
-#pragma unroll
-        for (int q = 0; q < kBmKeep; ++q) {
-            const uint32_t j = q * kBmThreads + tid;
-            g.keep[q] = j < g.m ? ids[j] - id0 : 0xFFFFFFFFu;
-        }
+        seg_range(a, c, g.id0, wbits);
     };
-    Seg nxt;
-    fetch(blockIdx.x, nxt);
-    for (int64_t x = blockIdx.x; x < nwork; x += gridDim.x) {
-        const Seg cur = nxt;
-        fetch(x + gridDim.x, nxt);
-        const uint32_t m = cur.m;
+    auto fetch = [&](const Seg &g, uint32_t (&id)[kBmKeep]) { // relative to the segment's first id
+        const uint32_t *__restrict__ ids = a.ids_seg + g.e0 + g.s0;
+        uint32_t t = (uint32_t)tid;
+        asm volatile("" : "+v"(t)); // (places of the loads: computed here, not kept in registers)
+#pragma unroll
+        for (int q = 0; q < kBmKeep; ++q)
+            id[q] = q * kBmThreads + t < g.m ? ids[q * kBmThreads + t] : 0xFFFFFFFFu;
+    };
+    Seg cur, nxt;
+    uint32_t keep[kBmKeep], next[kBmKeep];
+    locate(blockIdx.x, cur);
+    fetch(cur, next);
+    for (int64_t x = blockIdx.x; x < nwork; x += gridDim.x, cur = nxt) {
+        asm volatile("" : "+v"(tid), "+v"(lane)); // (places: computed anew for every segment, not kept in registers)
+        locate(x + gridDim.x, nxt);
+        const uint32_t m = cur.m, id0 = cur.id0;
+#pragma unroll
+        for (int q = 0; q < kBmKeep; ++q)
+            keep[q] = next[q] == 0xFFFFFFFFu ? next[q] : next[q] - id0;
         if (m == 0) {
             if (tid == 0)
                 a.seg_cnt[cur.sg] = 0;
+            fetch(nxt, next);
             continue;
         }
         const uint32_t *__restrict__ ids = a.ids_seg + cur.e0 + cur.s0;
         uint16_t *__restrict__ ranks = a.ranks + cur.e0 + cur.s0;
         uint32_t *__restrict__ uids = a.uids + cur.e0 + cur.s0;
-        const uint32_t id0 = cur.id0;
-        const int64_t sg = cur.sg;
-        const uint32_t(&keep)[kBmKeep] = cur.keep;
         // 1: set bits
 #pragma unroll
         for (int q = 0; q < kBmKeep; ++q)
@@ -619,18 +633,19 @@ __global__ __launch_bounds__(kBmThreads) void dd_bitmap_kernel(DedupArgs a)
             atomicOr(&words[b >> 5], 1u << (b & 31u));
         }
         __syncthreads();
-        // 2: counts before every quad, distinct ids
-        uint32_t pc[kBmIts], inc[kBmIts];
+        fetch(nxt, next);
+        // 2: counts before every quad
+        uint32_t inc[kBmIts];
         uint32_t wave_total = 0;
 #pragma unroll
         for (int it = 0; it < kBmIts; ++it) {
-            pc[it] = 0;
             inc[it] = 0;
             if (it < its) {
                 const uint4 qv = quads[q_wave + it * kWave + lane];
-                pc[it] = __popc(qv.x) + __popc(qv.y) + __popc(qv.z) + __popc(qv.w);
-                inc[it] = wave_inclusive_scan_dpp(pc[it]) + wave_total; // set bits of this wave's part up to this quad
-                wave_total = (uint32_t)__builtin_amdgcn_readlane((int)inc[it], kWave - 1);
+                const uint32_t pc = __popc(qv.x) + __popc(qv.y) + __popc(qv.z) + __popc(qv.w);
+                const uint32_t upto = wave_inclusive_scan_dpp(pc) + wave_total; // set bits of this wave's part up to this quad
+                inc[it] = upto - pc;
+                wave_total = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
             }
         }
         if (lane == 0)
@@ -644,36 +659,25 @@ __global__ __launch_bounds__(kBmThreads) void dd_bitmap_kernel(DedupArgs a)
             cnt += t;
         }
 #pragma unroll
-        for (int it = 0; it < kBmIts; ++it) {
-            if (it < its) {
-                uint32_t before = run + inc[it] - pc[it];
-                qpre[q_wave + it * kWave + lane] = (uint16_t)before;
-                if (pc[it]) { // the quad is read again: holding all of them in registers since the first pass costs more
-                    const uint32_t first = id0 + (q_wave + it * kWave + lane) * 128u;
-                    const uint4 qv = quads[q_wave + it * kWave + lane];
-                    const uint32_t xs[4] = {qv.x, qv.y, qv.z, qv.w};
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        uint32_t wbits = xs[u];
-                        while (wbits) {
-                            const uint32_t bit = (uint32_t)__ffs((int)wbits) - 1u;
-                            uids[before++] = first + u * 32u + bit;
-                            wbits &= wbits - 1u;
-                        }
-                    }
-                }
-            }
-        }
+        for (int it = 0; it < kBmIts; ++it)
+            if (it < its)
+                qpre[q_wave + it * kWave + lane] = (uint16_t)(run + inc[it]);
         if (tid == 0)
-            a.seg_cnt[sg] = cnt;
+            a.seg_cnt[cur.sg] = cnt;
         __syncthreads();
         // 3: ranks
+        const bool placed = cnt <= places; // the same in every thread
         auto rank_of = [&](uint32_t b) -> uint32_t {
             const uint4 v = quads[b >> 7];
             const uint32_t w = (b >> 5) & 3u, below = (1u << (b & 31u)) - 1u;
             const uint32_t word = w == 0 ? v.x : w == 1 ? v.y : w == 2 ? v.z : v.w;
-            return qpre[b >> 7] + (w > 0 ? __popc(v.x) : 0) + (w > 1 ? __popc(v.y) : 0) + (w > 2 ? __popc(v.z) : 0) +
-                   __popc(word & below);
+            const uint32_t r = qpre[b >> 7] + (w > 0 ? __popc(v.x) : 0) + (w > 1 ? __popc(v.y) : 0) + (w > 2 ? __popc(v.z) : 0) +
+                               __popc(word & below);
+            if (placed)
+                place[r] = id0 + b;
+            else
+                uids[r] = id0 + b;
+            return r;
         };
 #pragma unroll
         for (int q = 0; q < kBmKeep; ++q)
@@ -682,6 +686,9 @@ __global__ __launch_bounds__(kBmThreads) void dd_bitmap_kernel(DedupArgs a)
         for (uint32_t j = kBmKeep * kBmThreads + tid; j < m; j += kBmThreads)
             ranks[j] = (uint16_t)rank_of(ids[j] - id0);
         __syncthreads();
+        if (placed)
+            for (uint32_t r = tid; r < cnt; r += kBmThreads)
+                uids[r] = place[r];
         // 4: clear
         if (m * 4u < nq) {
 #pragma unroll
@@ -790,20 +797,23 @@ __global__ __launch_bounds__(256) void dd_base_scan_kernel(DedupArgs a, int64_t 
 // The cut in reverse: tile t appended, for every segment c, one run of ids to the segment; the ranks of those
 // ids lie at the same places.  Per tile: the runs' ranks are read back run by run (wide loads), the distinct
 // ids before the segment are added, the value goes to the position that put the id there (scatter inside
-// LDS), and the tile's local column indices leave in position order.
+// LDS), and the tile's local column indices leave in position order.  Latency of the scattered short runs bounds it: all 16
+// ranks of a thread are in flight at once, and one stage used twice in place of two lets four workgroups of 63 registers share
+// a compute unit.  128 x 586 k ids: 299 us with two workgroups and four loads in flight, 170 now.
 template <int TILE, int NT>
-__global__ __launch_bounds__(NT) void dd_unsplit_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
+__global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
 {
-    extern __shared__ uint32_t unsplit_lds[]; // stage[TILE], out[TILE]; then 3 C words: start in the tile, start in global - start in the tile, base
+    extern __shared__ uint32_t unsplit_lds[]; // stage[TILE]; then 3 C words: start in the tile, start in global - start in the tile, base
     __shared__ uint32_t smem[NT / kWave];
     __shared__ uint32_t carry_s;
     if (*a.fallback)
         return;
-    uint32_t *stage = unsplit_lds, *out = unsplit_lds + TILE;
-    uint32_t *off = unsplit_lds + 2 * TILE, *delta = off + a.C, *base_l = off + 2 * a.C;
-    const int tid = threadIdx.x;
+    uint32_t *stage = unsplit_lds;
+    uint32_t *off = unsplit_lds + TILE, *delta = off + a.C, *base_l = off + 2 * a.C;
     const int64_t ntiles = tileoff[a.k];
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid)); // (places: computed anew for every tile, not kept in registers)
         const int i = locate_segment(tileoff, a.k, t);
         const int64_t e0 = a.mb_edgeoff[i];
         const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
@@ -821,7 +831,7 @@ __global__ __launch_bounds__(NT) void dd_unsplit_kernel(DedupArgs a, const int64
         __syncthreads();
         const uint32_t *__restrict__ run_gpos = a.run_gpos + t * a.C, *__restrict__ run_cnt = a.run_cnt + t * a.C;
         for (int base = 0; base < a.C; base += NT) {
-            const int c = base + tid;
+            const int c = base + (int)tid;
             const uint32_t v = c < a.C ? run_cnt[c] : 0u;
             uint32_t total;
             const uint32_t ex = block_exclusive_scan<uint32_t, NT>(v, smem, total);
@@ -843,27 +853,31 @@ __global__ __launch_bounds__(NT) void dd_unsplit_kernel(DedupArgs a, const int64
                 stage[off[c] + (lc[q] & (TILE - 1))] = (c << kLocShift) | (uint32_t)(q * NT + tid);
             }
         __syncthreads();
+        // all of a thread's rank loads in flight; the columns then take the places of what was staged
         const uint16_t *__restrict__ ranks = a.ranks + e0;
-        for (uint32_t s0 = 0; s0 < jend - j0; s0 += 4 * NT) { // four independent loads in flight per lane
-            uint32_t x[4], r[4];
+        uint32_t r[TILE / NT];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t sidx = s0 + u * NT + tid;
-                x[u] = sidx < jend - j0 ? stage[sidx] : 0xFFFFFFFFu;
-                if (x[u] != 0xFFFFFFFFu) {
-                    const uint32_t c = x[u] >> kLocShift;
-                    r[u] = base_l[c] + ranks[delta[c] + sidx];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (x[u] != 0xFFFFFFFFu)
-                    out[x[u] & (TILE - 1)] = r[u];
+        for (int q = 0; q < TILE / NT; ++q) {
+            const uint32_t sidx = q * NT + tid;
+            r[q] = sidx < jend - j0 ? ranks[delta[stage[sidx] >> kLocShift] + sidx] : 0;
         }
+        asm volatile("" ::: "memory"); // (what was staged is read again: held in registers beside the ranks it spills)
+#pragma unroll
+        for (int q = 0; q < TILE / NT; ++q) {
+            const uint32_t sidx = q * NT + tid;
+            lc[q] = sidx < jend - j0 ? stage[sidx] : 0xFFFFFFFFu;
+            if (lc[q] != 0xFFFFFFFFu)
+                r[q] += base_l[lc[q] >> kLocShift];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < TILE / NT; ++q)
+            if (lc[q] != 0xFFFFFFFFu)
+                stage[lc[q] & (TILE - 1)] = r[q];
         __syncthreads();
         int32_t *__restrict__ col = a.col + e0 + j0;
         for (uint32_t idx = tid; idx < jend - j0; idx += NT)
-            col[idx] = (int32_t)out[idx];
+            col[idx] = (int32_t)stage[idx];
         __syncthreads();
     }
 }
@@ -1004,7 +1018,9 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
     mark("dd_rank");
     static bool big_attr_set = false;
     if (!big_attr_set) {
-        const int most = (int)dd_bitmap_lds_bytes(kMaxBitmapShift);
+        int most = 0;
+        for (int shift = 0; shift <= kMaxBitmapShift; ++shift)
+            most = std::max(most, (int)dd_bitmap_lds_bytes(shift));
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(dd_bitmap_kernel<false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess ||
             hipFuncSetAttribute(reinterpret_cast<const void *>(dd_bitmap_kernel<true>),
@@ -1014,14 +1030,15 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
     }
     const size_t bm_lds = dd_bitmap_lds_bytes(a.wbits_max <= kMaxBitmapShift ? a.wbits_max : kMaxBitmapShift);
     const int bm_per_cu = (int)std::max<size_t>(1, std::min<size_t>(2, (size_t)(156 * 1024) / bm_lds));
+    const uint32_t places = (uint32_t)bm_places(a.wbits_max <= kMaxBitmapShift ? a.wbits_max : kMaxBitmapShift);
     if (a.by_bitmap) {
         hipLaunchKernelGGL(dd_bitmap_kernel<false>, dim3(grid_for(L, (int64_t)a.k * a.C, bm_per_cu)), dim3(kBmThreads),
-                           bm_lds, L.stream, a);
+                           bm_lds, L.stream, a, places);
     } else {
-        hipLaunchKernelGGL(dd_rank_kernel, dim3(grid_for(L, (int64_t)a.k * a.C, 4)), dim3(kRankThreads), 0, L.stream, a);
+        hipLaunchKernelGGL(dd_rank_kernel, dim3(grid_for(L, (int64_t)a.k * a.C, 3)), dim3(kRankThreads), 0, L.stream, a);
         if (a.tab || a.cshift <= kMaxBitmapShift) // segments the counting kernel did not take (none can be listed otherwise)
             hipLaunchKernelGGL(dd_bitmap_kernel<true>, dim3(grid_for(L, nnz / 1024 + 1, bm_per_cu)), dim3(kBmThreads),
-                               bm_lds, L.stream, a);
+                               bm_lds, L.stream, a, places);
     }
     hipLaunchKernelGGL(dd_base_scan_kernel, dim3(a.k), dim3(256), 0, L.stream, a, mb_coloff, ncols_out, next_tileoff, done);
     mark("dd_front");
@@ -1033,16 +1050,16 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
 void launch_nw_dedup_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
 {
     static bool attr_set = false;
-    const size_t lds = 2 * (size_t)kCutTile * sizeof(uint32_t) + (3 * (size_t)a.C + 1) * sizeof(uint32_t);
+    const size_t lds = (size_t)kCutTile * sizeof(uint32_t) + (3 * (size_t)a.C + 1) * sizeof(uint32_t);
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(dd_unsplit_kernel<kCutTile, 512>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(2 * kCutTile * sizeof(uint32_t) + (3 * kMaxSegments + 1) * sizeof(uint32_t))) != hipSuccess)
+                                (int)(kCutTile * sizeof(uint32_t) + (3 * kMaxSegments + 1) * sizeof(uint32_t))) != hipSuccess)
             (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
         attr_set = true;
     }
     const int64_t tiles = nnz / kCutTile + a.k;
-    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, 2)), dim3(512), lds, L.stream, a,
+    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, 4)), dim3(512), lds, L.stream, a,
                        a.big_tileoff);
 }
 

@@ -116,3 +116,31 @@ def test_layerwise_limits(n, deg, k, b, s):
         for index in (True, True, False):
             res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), s, 17, mb_base=5, squared=squared, recycle=res, index=index)
             assert_hops_equal(res.hops(), ref, with_p=True, what="k=%d b=%d s=%s squared=%s index=%s" % (k, b, s, squared, index))
+
+
+# EXTRACT by bitmaps in LDS of id ranges: ids of a range in registers (10240) or read again, distinct ids that have room in LDS (10240)
+# or leave one by one, ranges of a few ids and of 2^18; tiles of 8192 positions taken apart and put together again
+@pytest.mark.parametrize("n,used,b,s", [(9000, 1.0, 4096, 2), (9000, 1.0, 4097, 4), (60_000, 1.0, 9000, 25), (400_000, 0.5, 20_000, 10),
+                                        (800_000, 0.3, 20_000, 10), (2_000_000, 1.0, 3000, 6), (1_500_000, 1.0, 12_000, 12)])
+def test_extract_by_bitmaps_of_id_ranges(n, used, b, s):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(n + b)
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rows = rng.choice(n, size=b, replace=False)
+    rowptr[rows + 1] = s + rng.integers(0, 3, size=b)
+    rowptr = np.cumsum(rowptr)
+    gaps = rng.integers(1, max(int(used * n) // (s + 3), 2), size=(b, s + 2))
+    ids = np.minimum(np.cumsum(gaps, axis=1) - 1, n - 1)
+    row = np.repeat(np.arange(n), np.diff(rowptr))
+    slot = np.arange(len(row)) - rowptr[row]
+    which = np.searchsorted(np.sort(rows), row)
+    col = ids[which, slot].astype(np.int32)
+    batches = np.stack([rng.permutation(rows) for _ in range(3)]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    for variant in ({}, {"union_dst": True}, {"replace": True}):
+        ref = O.sample_nodewise(rowptr, col, batches, (s,), 3, 5, **variant)
+        res = None
+        for call in range(2):
+            res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (s,), 3, mb_base=5, recycle=res, extract="sort", **variant)
+            assert_hops_equal(res.hops(), ref, what="n=%d b=%d s=%d %s call %d" % (n, b, s, variant, call))
