@@ -33,36 +33,36 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 3_308_734_816,
-    ("dense_ladies", "ldw_extract"): 2_026_395_190,
-    ("dense_sage", "nw_sample"): 10_619_753_760,
-    ("dense_sage", "nw_rows"): 1_379_272_096,
-    ("dense_sage", "dd_split"): 1_138_991_268,
-    ("dense_sage", "dd_unsplit"): 1_001_343_017,
-    ("dense_sage", "dd_rank"): 875_271_634,
-    ("dense_sage", "dd_front"): 616_770_066,
-    ("large_sage", "nw_sample"): 5_716_071_922,
-    ("large_sage", "nw_rows"): 1_649_649_339,
-    ("large_sage", "dd_split"): 753_356_804,
-    ("large_sage", "dd_unsplit"): 682_846_788,
-    ("large_sage", "dd_rank"): 599_108_329,
-    ("large_sage", "dd_front"): 473_554_418,
-    ("mid_ladies", "ldw_accumulate"): 148_771_117,
-    ("mid_ladies", "ldw_extract"): 85_080_091,
-    ("mid_sage", "nw_sample"): 3_060_700_205,
-    ("mid_sage", "dd_split"): 426_376_214,
-    ("mid_sage", "dd_unsplit"): 366_985_101,
-    ("mid_sage", "nw_rows"): 351_932_041,
-    ("mid_sage", "dd_rank"): 314_712_068,
-    ("mid_sage", "dd_front"): 204_159_766,
+    ("dense_ladies", "ldw_accumulate"): 3_301_639_264,
+    ("dense_ladies", "ldw_extract"): 2_618_182_368,
+    ("dense_sage", "nw_sample"): 9_827_472_672,
+    ("dense_sage", "dd_rank"): 1_790_340_928,
+    ("dense_sage", "nw_rows"): 1_379_019_648,
+    ("dense_sage", "dd_split"): 1_140_845_152,
+    ("dense_sage", "dd_unsplit"): 1_008_368_096,
+    ("dense_sage", "dd_front"): 617_262_528,
+    ("large_sage", "nw_sample"): 5_063_255_520,
+    ("large_sage", "nw_rows"): 1_648_596_000,
+    ("large_sage", "dd_split"): 753_540_960,
+    ("large_sage", "dd_unsplit"): 687_598_624,
+    ("large_sage", "dd_rank"): 599_026_592,
+    ("large_sage", "dd_front"): 473_494_816,
+    ("mid_ladies", "ldw_extract"): 183_568_256,
+    ("mid_ladies", "ldw_accumulate"): 148_762_688,
+    ("mid_sage", "nw_sample"): 2_618_566_528,
+    ("mid_sage", "dd_rank"): 574_085_888,
+    ("mid_sage", "dd_split"): 426_436_736,
+    ("mid_sage", "dd_unsplit"): 367_494_240,
+    ("mid_sage", "nw_rows"): 352_057_472,
+    ("mid_sage", "dd_front"): 204_140_000,
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 9_685_282_825,
-    "dense_sage": 15_634_668_434,
-    "large_sage": 9_878_498_779,
-    "mid_ladies": 486_247_881,
-    "mid_sage": 4_725_634_948,
+    "dense_ladies": 9_880_152_832,
+    "dense_sage": 15_766_869_696,
+    "large_sage": 9_229_908_640,
+    "mid_ladies": 562_838_592,
+    "mid_sage": 4_544_347_968,
 }
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 
