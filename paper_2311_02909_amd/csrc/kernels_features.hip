@@ -6,6 +6,7 @@
 // through and dealt to the lanes in that order, so no lane is idle because f is no power of two.
 #include "bms_device.h"
 #include "bms_internal.h"
+#include "feature_runs.h"
 
 #include <algorithm>
 
@@ -14,11 +15,9 @@ namespace bms {
 constexpr int kFeatThreads = 256;
 constexpr int kFeatRows = 64;    // rows per tile
 constexpr int kFetchUnroll = 4;  // accesses in flight per lane
-constexpr int kFetchSamples = 1024;
-constexpr int kFetchMostRuns = 512;
 constexpr int kFetchBlock = 16;  // consecutive tiles on one die
-constexpr int kFetchRows = 128;  // rows per tile of the fetch
-static_assert(kFetchRows <= kFeatThreads && kFeatRows < kFeatThreads, "one thread per row of a tile loads its id or extent");
+static_assert(kFetchLanes == kWave && kFetchSamples % kFeatThreads == 0 && kFetchProbes == kFeatThreads, "feature_runs.h");
+static_assert(kFetchTile <= kFeatThreads && kFeatRows < kFeatThreads, "one thread per row of a tile loads its id or extent");
 
 // 16 bytes (or 4) of a row in memory
 template <int VEC>
@@ -54,19 +53,20 @@ __device__ inline uint32_t first_float(uint32_t part, int32_t f)
 // Where the minibatches begin in the stacked ids.  The ids of a minibatch ascend, so its first one is smaller than the one
 // before it: kFetchSamples ids at equal distances show between which of them that happens, a binary search where.  Every
 // workgroup finds the same.  bounds: kFetchMostRuns + 1 places.  Returns the number of runs; 1 (no structure to use) when
-// nothing descends, too much does, or the runs differ too much in length.  A minibatch that lies between two samples is
-// missed and ids that do not ascend give runs without a meaning: both only cost speed.
+// nothing descends, too much does, the ids between two ascending samples are not in order (feature_runs.h), or the runs differ
+// too much in length.
 __device__ inline int find_runs(const int32_t *__restrict__ ids, int64_t m, int64_t *bounds, int32_t *samples, int32_t *wsum)
 {
     constexpr int PER = kFetchSamples / kFeatThreads;
-    __shared__ int32_t longest_s;
+    __shared__ int32_t longest_s, off_s;
     const int tid = threadIdx.x;
-    auto place = [&](int s) { return (int64_t)s * (m - 1) / (kFetchSamples - 1); };
+    const int probed = probed_sample(tid);
+    const int32_t probe = ids[probe_place(probed, m)];
 #pragma unroll
     for (int q = 0; q < PER; ++q)
-        samples[q * kFeatThreads + tid] = ids[place(q * kFeatThreads + tid)];
+        samples[q * kFeatThreads + tid] = ids[sample_place(q * kFeatThreads + tid, m)];
     if (tid == 0)
-        longest_s = 0;
+        longest_s = off_s = 0;
     __syncthreads();
     int32_t descents = 0;
 #pragma unroll
@@ -74,16 +74,21 @@ __device__ inline int find_runs(const int32_t *__restrict__ ids, int64_t m, int6
         const int s = tid * PER + q;
         descents += s + 1 < kFetchSamples && samples[s + 1] < samples[s] ? 1 : 0;
     }
+    const bool ascends = samples[probed] <= samples[probed + 1];
+    const bool off = ascends && probe_off(samples[probed], probe, samples[probed + 1]);
+    const int counts = __popcll(__ballot(ascends)) << 16 | __popcll(__ballot(off));
+    if ((tid & (kWave - 1)) == 0)
+        atomicAdd(&off_s, counts);
     int32_t total;
-    int32_t at = block_exclusive_scan<int32_t, kFeatThreads>(descents, wsum, total);
+    int32_t at = block_exclusive_scan<int32_t, kFeatThreads>(descents, wsum, total); // (waits for the additions, too)
     const int runs = total + 1;
-    if (total == 0 || runs > kFetchMostRuns)
+    if (!runs_likely(total, off_s >> 16, off_s & 0xFFFF))
         return 1; // the same in every thread
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const int s = tid * PER + q;
         if (s + 1 < kFetchSamples && samples[s + 1] < samples[s]) {
-            int64_t lo = place(s), hi = place(s + 1); // the first id below samples[s] in (lo, hi]
+            int64_t lo = sample_place(s, m), hi = sample_place(s + 1, m); // the first id below samples[s] in (lo, hi]
             while (hi - lo > 1) {
                 const int64_t mid = (lo + hi) >> 1;
                 if (ids[mid] < samples[s])
@@ -100,47 +105,9 @@ __device__ inline int find_runs(const int32_t *__restrict__ ids, int64_t m, int6
     }
     __syncthreads();
     for (int r = tid; r < runs; r += kFeatThreads) // (in tiles: fits 32 bits)
-        atomicMax(&longest_s, (int32_t)((bounds[r + 1] - bounds[r]) / kFeatRows));
+        atomicMax(&longest_s, (int32_t)((bounds[r + 1] - bounds[r]) / kFetchTile));
     __syncthreads();
-    return (int64_t)longest_s * kFeatRows <= 4 * (m / runs) ? runs : 1;
-}
-
-// First row of tile j of run r, by one wave: the first row of the run whose id is not below that of run 0's row at the same
-// share j / tiles of its length.  It lies near the same share of this run, so 64 ids around there are looked at, then the
-// 64 after the last one below; only when it does not, the whole run is searched.  A function of (r, j) alone, run's begin
-// and end for the first tile and the one past the last: whatever the ids, the tiles of a run cover it.
-__device__ inline int64_t tile_begin(const int32_t *__restrict__ ids, const int64_t *bounds, int64_t r, int64_t j, int64_t tiles)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t b = bounds[r], e = bounds[r + 1];
-    if (j == 0 || j == tiles)
-        return j ? e : b;
-    const int64_t guess = b + (e - b) * j / tiles;
-    if (r == 0)
-        return guess;
-    const int32_t v = ids[bounds[0] + (bounds[1] - bounds[0]) * j / tiles];
-    const int64_t w = max<int64_t>(guess - kWave * kWave / 2, b);
-    const int64_t p = w + lane * kWave;
-    const int below = __popcll(__ballot(p < e && ids[min<int64_t>(p, e - 1)] < v));
-    int64_t lo = b, hi = e; // the answer is in [lo, hi]
-    if (below == 0) {
-        if (w == b)
-            return b;
-        hi = w;
-    } else if (below == kWave) {
-        lo = w + (kWave - 1) * kWave + 1;
-    } else {
-        const int64_t q = w + (below - 1) * kWave + 1;
-        return min<int64_t>(q + __popcll(__ballot(q + lane < e && ids[min<int64_t>(q + lane, e - 1)] < v)), e);
-    }
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (ids[mid] < v)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    return lo;
+    return runs_balanced((int64_t)longest_s * kFetchTile, runs, m) ? runs : 1;
 }
 
 // out[j, :] = H[ids[j], :].  An id outside [0, n) gives a row of zeros and raises *flag.
@@ -150,6 +117,8 @@ __device__ inline int64_t tile_begin(const int32_t *__restrict__ ids, const int6
 // the tile's rows of H pass through that die's L2 once.  What is written does not stay there (nontemporal stores).
 // 32 minibatches of 295 k rows of 100 floats out of 2.4 M (3.8 GB written): 1647 us and 4.8 GB read in the order of the
 // stack (1370 with nontemporal stores), 1255 us and 1.3 GB read so.  More work in flight per wave or compute unit gains nothing.
+// Ids without an order take the order of the stack: 10 million of 2.4 million ids, 100 floats, 1.53 ms whatever the draw (while
+// descents alone decided, every fourth draw took 14.6 ms).
 template <int VEC, bool LARGE>
 __global__ __launch_bounds__(kFeatThreads, 8) void feature_fetch_kernel(const float *__restrict__ H, int64_t n, int32_t f,
                                                                      const int32_t *__restrict__ ids, int64_t m,
@@ -160,73 +129,84 @@ __global__ __launch_bounds__(kFeatThreads, 8) void feature_fetch_kernel(const fl
     __shared__ int32_t samples[kFetchSamples];
     __shared__ int64_t bounds[kFetchMostRuns + 1];
     __shared__ int32_t wsum[kFeatThreads / kWave];
-    __shared__ int32_t id_l[kFetchRows];
-    __shared__ int64_t tile_s[2];
+    __shared__ int32_t id_l[kFetchTile];
+    __shared__ int64_t tile_s[kFeatThreads / kWave];
+    __shared__ double scale[2]; // 1 / tiles per run, samples per row
     const int tid = threadIdx.x;
     const uint32_t per_row = (uint32_t)((f + VEC - 1) / VEC);
-    const int64_t runs = LARGE ? find_runs(ids, m, bounds, samples, wsum) : 1;
-    if (runs == 1) {
-        __syncthreads();
-        if (tid == 0) {
-            bounds[0] = 0;
-            bounds[1] = m;
-        }
-        __syncthreads();
+    // (in 32 bits: a GPU's memory holds fewer than 2^37 floats, so there are fewer than 2^32 tiles)
+    const uint32_t runs = LARGE ? (uint32_t)find_runs(ids, m, bounds, samples, wsum) : 1u;
+    const uint32_t tiles = (uint32_t)tiles_per_run(runs, m);
+    if (LARGE && tid == 0) {
+        scale[0] = 1.0 / (double)tiles;
+        scale[1] = (double)(kFetchSamples - 1) / (double)(m - 1);
     }
-    const int64_t tiles = max<int64_t>((m / runs + kFetchRows - 1) / kFetchRows, 1); // per run
-    const int64_t block = min<int64_t>(max<int64_t>(tiles / 64, 1), kFetchBlock);  // consecutive tiles on one die
-    const int64_t rounds = (tiles + 8 * block - 1) / (8 * block) * block * runs;   // units per die
-    for (int64_t u = blockIdx.x >> 3; u < rounds; u += gridDim.x >> 3) {
-        const int64_t r = u % runs, t = u / runs;
-        const int64_t j = (t / block * 8 + (blockIdx.x & 7)) * block + t % block;
-        if (j >= tiles)
-            continue;
+    const uint32_t block = min(max(tiles / 64, 1u), (uint32_t)kFetchBlock);        // consecutive tiles on one die
+    const uint32_t rounds = (tiles + 8 * block - 1) / (8 * block) * block * runs; // units per die
+    const uint32_t stride = gridDim.x >> 3, wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid / kWave);
+    for (uint32_t u0 = blockIdx.x >> 3; u0 < rounds; u0 += 2 * stride) {
+        // two units at a time, a wave for each begin and end
+        const uint32_t u = u0 + wave / 2 * stride;
+        const uint32_t t = u / runs, r = u - t * runs;
+        const uint32_t j = (t / block * 8 + (blockIdx.x & 7)) * block + t % block;
+        int64_t x = 0;
         __syncthreads();
-        if (tid < 2 * kWave) {
-            const int64_t x = tile_begin(ids, bounds, r, j + tid / kWave, tiles);
-            if (tid % kWave == 0)
-                tile_s[tid / kWave] = x;
+        if (u < rounds && j < tiles) {
+            const uint32_t at = j + (wave & 1);
+            if (!LARGE || runs == 1)
+                x = min<int64_t>((int64_t)at * kFetchTile, m);
+            else if (at == 0 || at == tiles)
+                x = bounds[at ? r + 1 : r];
+            else
+                x = tile_begin(bounds, r, at, scale[0], tile_value(ids, samples, bounds, at, scale[0], scale[1], m),
+                               [&](int64_t p, int64_t step, int64_t e, int64_t v) {
+                                   p += (tid & (kWave - 1)) * step;
+                                   return (uint64_t)__ballot(p < e && ids[min<int64_t>(p, e - 1)] < v);
+                               });
         }
+        if (tid % kWave == 0)
+            tile_s[wave] = x;
         __syncthreads();
-        const int64_t j1 = tile_s[1];
-        for (int64_t j0 = tile_s[0]; j0 < j1; j0 += kFetchRows) {
-            const int nr = (int)min<int64_t>(kFetchRows, j1 - j0);
-            __syncthreads();
-            if (tid < nr) {
-                int32_t id = ids[j0 + tid];
-                if (id < 0 || (int64_t)id >= n) {
-                    *flag = 1;
-                    id = -1;
-                }
-                id_l[tid] = id;
-            }
-            __syncthreads();
-            const uint32_t accesses = (uint32_t)nr * per_row;
-            float *__restrict__ to = out + j0 * f;
-            RowWalk walk(per_row, tid);
-            for (uint32_t x = tid; x < accesses; x += kFetchUnroll * kFeatThreads) {
-                Vec v[kFetchUnroll];
-                uint32_t dst[kFetchUnroll];
-#pragma unroll
-                for (int q = 0; q < kFetchUnroll; ++q) {
-                    if (x + q * kFeatThreads < accesses) {
-                        const int32_t id = id_l[walk.row];
-                        const uint32_t at = first_float<VEC>(walk.part, f);
-                        v[q] = 0.0f;
-                        if (id >= 0)
-                            v[q] = *reinterpret_cast<const InMemory *>(H + (int64_t)id * f + at);
-                        dst[q] = walk.row * (uint32_t)f + at;
+        for (int unit = 0; unit < 4; unit += 2) {
+            for (int64_t j0 = tile_s[unit], j1 = tile_s[unit + 1]; j0 < j1; j0 += kFetchTile) {
+                const int nr = (int)min<int64_t>(kFetchTile, j1 - j0);
+                __syncthreads();
+                if (tid < nr) {
+                    int32_t id = ids[j0 + tid];
+                    if (id < 0 || (int64_t)id >= n) {
+                        *flag = 1;
+                        id = -1;
                     }
-                    walk.next();
+                    id_l[tid] = id;
                 }
+                __syncthreads();
+                const uint32_t accesses = (uint32_t)nr * per_row;
+                float *__restrict__ to = out + j0 * f;
+                RowWalk walk(per_row, tid);
+                for (uint32_t x = tid; x < accesses; x += kFetchUnroll * kFeatThreads) {
+                    Vec v[kFetchUnroll];
+                    uint32_t dst[kFetchUnroll];
 #pragma unroll
-                for (int q = 0; q < kFetchUnroll; ++q)
-                    if (x + q * kFeatThreads < accesses) {
-                        if (LARGE)
-                            __builtin_nontemporal_store(v[q], reinterpret_cast<InMemory *>(to + dst[q]));
-                        else
-                            *reinterpret_cast<InMemory *>(to + dst[q]) = v[q];
+                    for (int q = 0; q < kFetchUnroll; ++q) {
+                        if (x + q * kFeatThreads < accesses) {
+                            const int32_t id = id_l[walk.row];
+                            const uint32_t at = first_float<VEC>(walk.part, f);
+                            v[q] = 0.0f;
+                            if (id >= 0)
+                                v[q] = *reinterpret_cast<const InMemory *>(H + (int64_t)id * f + at);
+                            dst[q] = walk.row * (uint32_t)f + at;
+                        }
+                        walk.next();
                     }
+#pragma unroll
+                    for (int q = 0; q < kFetchUnroll; ++q)
+                        if (x + q * kFeatThreads < accesses) {
+                            if (LARGE)
+                                __builtin_nontemporal_store(v[q], reinterpret_cast<InMemory *>(to + dst[q]));
+                            else
+                                *reinterpret_cast<InMemory *>(to + dst[q]) = v[q];
+                        }
+                }
             }
         }
     }
@@ -245,7 +225,7 @@ void launch_feature_fetch(const Launch &L, const float *H, int64_t n, int32_t f,
     // Finding the runs takes a workgroup about 15 us: worth it from some 100 MB on.  Less than that is left in the caches for
     // whoever reads it next.
     const bool large = m >= 64 * kFetchSamples && m * (int64_t)f * 4 >= (100LL << 20);
-    const int grid = (grid_for(L, (m + kFetchRows - 1) / kFetchRows, 8) + 7) / 8 * 8;
+    const int grid = (grid_for(L, (m + kFetchTile - 1) / kFetchTile, 8) + 7) / 8 * 8;
     void (*const kernels[2][2])(const float *, int64_t, int32_t, const int32_t *, int64_t, float *, int32_t *) = {
         {feature_fetch_kernel<1, false>, feature_fetch_kernel<1, true>}, {feature_fetch_kernel<4, false>, feature_fetch_kernel<4, true>}};
     hipLaunchKernelGGL(kernels[f >= 4][large], dim3(grid), dim3(kFeatThreads), 0, L.stream, H, n, f, ids, m, out, flag);
