@@ -149,6 +149,20 @@ __device__ inline T block_exclusive_scan(T v, T *smem, T &total)
     return before + inc - v;
 }
 
+// A value that is the same in all of a wave's lanes, in scalar registers.  The compiler does not see it of values loaded from
+// memory that the kernel writes to, or that follow from the wave's number, and keeps a copy of them in every lane.
+__device__ inline int64_t lane_value(int64_t x, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ inline uint32_t scalar(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ inline int64_t scalar(int64_t x)
+{
+    return (int64_t)((uint64_t)scalar((uint32_t)((uint64_t)x >> 32)) << 32 | scalar((uint32_t)x));
+}
+
 // A workgroup's number in its launch, in the order of starting: whoever waits for lower numbers waits for workgroups that
 // have started.  smem: one word of LDS.
 __device__ inline uint32_t take_number(const Lookback &lb, uint32_t *smem)

@@ -529,7 +529,10 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
 //      (equal ids to the same one), from where the distinct ids leave in order
 //   4  the bitmap is cleared again: word by word through the ids when they are few, else as a whole
 // What bounds it is latency: trips to memory for ids that are not in registers, and, before step 3 did it, the stores of the
-// distinct ids straight from the bitmap, scattered over a wave's lanes.  128 x 586 k ids of 8.7 M: 475 us so, 262 us now.
+// distinct ids straight from the bitmap, scattered over a wave's lanes (128 x 586 k ids of 8.7 M: 475 us so, 262 us without).
+// Two workgroups share a compute unit, which leaves 64 registers: enough as long as what the lanes have in common is in scalar
+// ones.  With a segment's place and length in every lane 14 registers went to memory and back, as many bytes again as the ids
+// themselves: the last two hops of 128 x 1024 seeds, (15, 10, 5), took 373 us so and 281 us without.
 constexpr int kBmThreads = 1024;
 constexpr int kBmWaves = kBmThreads / kWave;
 constexpr int kBmKeep = 10; // ids per thread kept in registers between the passes (segments up to 10240 ids)
@@ -566,34 +569,35 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
     uint32_t *place = reinterpret_cast<uint32_t *>(bm_lds + nq);
     uint16_t *qpre = reinterpret_cast<uint16_t *>(place + places);
     const uint32_t q_wave = (uint32_t)wave * (uint32_t)(its * kWave); // first quad of this wave's part
-    const int64_t nwork = LISTED ? (int64_t)*a.big_count : (int64_t)a.k * a.C;
-    if ((int64_t)blockIdx.x >= nwork)
+    const uint32_t nwork = LISTED ? *a.big_count : (uint32_t)a.k * (uint32_t)a.C; // (fits: the list holds segments in 32 bits)
+    if (blockIdx.x >= nwork)
         return; // usually nothing is listed
     for (int it = 0; it < its; ++it)
         quads[q_wave + it * kWave + lane] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     // where a segment lies; its first ids are fetched while the segment before it is worked on
     struct Seg {
-        int64_t sg, e0;
-        uint32_t s0, m, id0;
+        int64_t e0;
+        uint32_t sg, s0, m, id0;
     };
-    auto locate = [&](int64_t x, Seg &g) {
-        g.m = g.s0 = g.id0 = 0;
-        g.sg = g.e0 = 0;
+    auto locate = [&](uint32_t x, Seg &g) {
+        g.m = g.s0 = g.id0 = g.sg = 0;
+        g.e0 = 0;
         if (x >= nwork)
             return;
         if (LISTED)
-            g.sg = a.big_list[x];
+            g.sg = scalar(a.big_list[x]);
         else // workgroups that run at the same time take segments of different minibatches
-            g.sg = (x % a.k) * a.C + x / a.k;
-        const int64_t i = g.sg / a.C;
-        const uint32_t c = (uint32_t)(g.sg % a.C);
-        const uint32_t *__restrict__ soff = a.seg_off + i * (a.C + 1);
-        g.s0 = soff[c];
-        g.m = soff[c + 1] - g.s0;
-        g.e0 = a.mb_edgeoff[i];
+            g.sg = (x % (uint32_t)a.k) * (uint32_t)a.C + x / (uint32_t)a.k;
+        const uint32_t i = g.sg / (uint32_t)a.C, c = g.sg % (uint32_t)a.C;
+        const uint32_t *__restrict__ soff = a.seg_off + (int64_t)i * (a.C + 1);
         int wbits;
         seg_range(a, c, g.id0, wbits);
+        // the same in every lane: kept in scalar registers
+        g.e0 = scalar(a.mb_edgeoff[i]);
+        g.s0 = scalar(soff[c]);
+        g.m = scalar(soff[c + 1]) - g.s0;
+        g.id0 = scalar(g.id0);
     };
     auto fetch = [&](const Seg &g, uint32_t (&id)[kBmKeep]) { // relative to the segment's first id
         const uint32_t *__restrict__ ids = a.ids_seg + g.e0 + g.s0;
@@ -607,7 +611,7 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
     uint32_t keep[kBmKeep], next[kBmKeep];
     locate(blockIdx.x, cur);
     fetch(cur, next);
-    for (int64_t x = blockIdx.x; x < nwork; x += gridDim.x, cur = nxt) {
+    for (uint32_t x = blockIdx.x; x < nwork; x += gridDim.x, cur = nxt) {
         asm volatile("" : "+v"(tid), "+v"(lane)); // (places: computed anew for every segment, not kept in registers)
         locate(x + gridDim.x, nxt);
         const uint32_t m = cur.m, id0 = cur.id0;

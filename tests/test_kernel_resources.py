@@ -1,0 +1,46 @@
+"""Kernels keep their working set in registers: what a spill costs is memory traffic that no table of bytes accounts for."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2311_02909_amd", "libbms.so")
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+KERNELS = ["feature_fetch_kernel", "dd_bitmap_kernel"]
+
+
+def _scratch_bytes(tmp_path):
+    """kernel name -> bytes of scratch per lane, from the notes of the gfx950 code objects in the library"""
+    data = open(LIB, "rb").read()
+    found = {}
+    at = data.find(MAGIC)
+    while at >= 0:
+        entries, = struct.unpack_from("<Q", data, at + len(MAGIC))
+        p = at + len(MAGIC) + 8
+        for _ in range(entries):
+            offset, size, name_len = struct.unpack_from("<QQQ", data, p)
+            name = data[p + 24:p + 24 + name_len].decode()
+            p += 24 + name_len
+            if "gfx950" not in name or not size:
+                continue
+            obj = tmp_path / ("code%d" % len(found))
+            obj.write_bytes(data[at + offset:at + offset + size])
+            notes = subprocess.run([READELF, "--notes", str(obj)], check=True, capture_output=True, text=True).stdout
+            for kernel in re.split(r"\n\s*- \.", notes):
+                name = re.search(r"\.?name:\s+(_ZN3bms\S+)\n", kernel)
+                bytes_ = re.search(r"private_segment_fixed_size:\s+(\d+)", kernel)
+                if name and bytes_:
+                    found[name.group(1)] = int(bytes_.group(1))
+        at = data.find(MAGIC, at + 1)
+    return found
+
+
+@pytest.mark.skipif(not (os.path.exists(LIB) and os.path.exists(READELF)), reason="library or tools not here")
+@pytest.mark.parametrize("kernel", KERNELS)
+def test_kernel_does_not_spill(kernel, tmp_path):
+    found = {name: size for name, size in _scratch_bytes(tmp_path).items() if kernel in name}
+    assert found and not any(found.values())
