@@ -888,6 +888,9 @@ __device__ inline uint32_t ldw_hash(uint32_t v, int filter_bits) { return (v * 0
 // across the lanes, and where it matters (a step with more than one row) the row of a position follows from counting row
 // starts up to it, as in the accumulation.  Going row by row instead left a wave with one short row's few lines in flight
 // (two trips to memory of 2 us each per row: 75 k neighbours in rows of 49 took 55 us, 15 us so).
+// Two workgroups per compute unit leave 64 registers.  The tile, its rows and what else a wave's lanes have in common are scalar;
+// in every lane they cost 12 registers more, which went to memory and back (0.6 of 2.6 GB on 64 x 1024 seeds of 8.7 M vertices; 32 x
+// 512 seeds, 3 layers of 512 of 2.4 M vertices: 86 us with, 69 us without).
 struct ExtWave {
     int64_t shift[kWave];     // by rank among the list's rows with neighbours: A_col index of tile position 0 if it lay in the row
     uint32_t starts[kStreamUnroll * 2]; // one bit per position of a step: a row starts there
@@ -907,10 +910,11 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
     if (a.giveup && *a.giveup)
         return;
     const int i = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
-    ExtWave &me = waves[tid / kWave];
+    const uint32_t wave = scalar((uint32_t)tid / kWave); // what is the same in a wave's lanes lies in scalar registers
+    ExtWave &me = waves[wave];
     const int64_t c0 = a.mb_coloff[i];
     const int32_t ns = (int32_t)(a.mb_coloff[i + 1] - c0);
-    const int64_t x0 = a.mb_gtileoff[i], ntiles = a.mb_gtileoff[i + 1] - x0;
+    const int64_t x0 = a.mb_gtileoff[i], ntiles = scalar(a.mb_gtileoff[i + 1] - x0);
     if (ns == 0 || (int64_t)blockIdx.x * kExtWaves >= ntiles)
         return; // nothing sampled: every row stays empty (the counters start at zero)
     for (int x = tid; x < slots; x += kExtThreads)
@@ -938,21 +942,22 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
     // line follow one another at about 8 ns each, so every counter has a line of its own, and waves that are at least as
     // many as tiles do not ask: 32 x 512, 7.6 M neighbours: 62 us when the counters shared lines, 27 so.)
     const int64_t nwaves = (int64_t)gridDim.x * kExtWaves;
-    int64_t t = (int64_t)blockIdx.x * kExtWaves + tid / kWave;
+    const int64_t g_first = scalar(a.mb_goff[i]), g_end = scalar(a.mb_goff[i + 1]);
+    int64_t t = (int64_t)blockIdx.x * kExtWaves + wave;
     while (t < ntiles) {
         int64_t t_next = ntiles;
         if (lane == 0 && nwaves < ntiles)
             t_next = nwaves + (int64_t)atomicAdd(a.tile_queue + i * kQueueStride, 1ull);
-        const int64_t g0 = a.mb_goff[i] + t * a.tile;
-        const int32_t len = (int32_t)(min(g0 + a.tile, a.mb_goff[i + 1]) - g0); // positions 0 .. len of the tile
-        int64_t rw = a.tile_row[x0 + t]; // first row of the list
+        const int64_t g0 = g_first + t * a.tile;
+        const int32_t len = (int32_t)(min(g0 + a.tile, g_end) - g0); // positions 0 .. len of the tile
+        int64_t rw = scalar(a.tile_row[x0 + t]); // first row of the list
         int32_t p = 0;
         while (p < len) {
             const int64_t start = a.gather_off[min(rw + lane, nrows)], stop = a.gather_off[min(rw + lane + 1, nrows)];
             const bool row = stop > start; // with neighbours
             // in the tile; rows of other tiles are clamped to its ends
             const int32_t rs = (int32_t)max<int64_t>(min<int64_t>(start - g0, len), -1);
-            const int32_t list_end = (int32_t)min<int64_t>(__shfl(stop, kWave - 1, kWave) - g0, len);
+            const int32_t list_end = (int32_t)min<int64_t>(lane_value(stop, kWave - 1) - g0, len);
             const bool fresh = start >= g0, in_tile = row && start - g0 < len; // the piece is the row's first; there is one
             const int rank = __popcll(__ballot(row) & below);
             __builtin_amdgcn_wave_barrier();
@@ -1080,7 +1085,7 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
             }
             rw += kWave;
         }
-        t = __shfl(t_next, 0, kWave);
+        t = lane_value(t_next, 0);
     }
 }
 
