@@ -237,7 +237,8 @@ void launch_feature_fetch(const Launch &L, const float *H, int64_t n, int32_t f,
 // mean != 0 divides by the number of entries (rows without entries give zeros).
 // Bound by the traffic of the gathered rows (an entry moves whole 128-byte lines).  A tile's row extents and columns go to LDS
 // first, so that the gathered rows are one trip to memory away; up to 8 entries of a row are in flight, and registers are
-// held to 8 waves per SIMD.  2.8 M rows of 5 entries, 100 floats: 1563 -> 1150 us (8.3 GB between L2 and memory, 7.2 TB/s).
+// held to 8 waves per SIMD (places in the tile in 32 bits: in 64 two registers spill).  2.8 M rows of 5 entries, 100 floats: 1563
+// -> 1150 us (8.3 GB between L2 and memory, 7.2 TB/s).
 constexpr int kAggUnroll = 8;
 constexpr int kAggCols = 2048; // columns of a tile in LDS; longer tiles read them from memory
 template <int VEC>
@@ -267,25 +268,26 @@ __global__ __launch_bounds__(kFeatThreads, 8) void aggregate_kernel(AggArgs a, i
         const uint32_t accesses = (uint32_t)nr * per_row;
         RowWalk walk(per_row, tid);
         for (uint32_t x = tid; x < accesses; x += kFeatThreads, walk.next()) {
-            const int64_t b = rowptr_l[walk.row], end = rowptr_l[walk.row + 1];
+            const int64_t b = rowptr_l[walk.row];
+            const uint32_t length = (uint32_t)(rowptr_l[walk.row + 1] - b); // (fewer than n)
             const uint32_t at = first_float<VEC>(walk.part, f);
             const float *__restrict__ X = a.X + first_l[walk.row] * f + at;
             Vec acc = 0.0f;
-            for (int64_t e = b; e < end; e += kAggUnroll) {
+            for (uint32_t e = 0; e < length; e += kAggUnroll) {
                 Vec v[kAggUnroll];
 #pragma unroll
                 for (int u = 0; u < kAggUnroll; ++u)
-                    if (e + u < end) {
-                        const int32_t c = staged ? col_l[e + u] : a.col[e0 + e + u];
+                    if (e + u < length) {
+                        const int32_t c = staged ? col_l[(uint32_t)b + e + u] : a.col[e0 + b + e + u];
                         v[u] = *reinterpret_cast<const InMemory *>(X + (int64_t)c * f);
                     }
 #pragma unroll
                 for (int u = 0; u < kAggUnroll; ++u)
-                    if (e + u < end) // entry order
+                    if (e + u < length) // entry order
                         acc += v[u];
             }
-            if (a.mean && end > b)
-                acc /= (float)(end - b);
+            if (a.mean && length)
+                acc /= (float)length;
             *reinterpret_cast<InMemory *>(a.out + (r0 + walk.row) * f + at) = acc;
         }
     }

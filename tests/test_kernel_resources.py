@@ -10,7 +10,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_2311_02909_amd", "libbms.so")
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
-KERNELS = ["feature_fetch_kernel", "dd_bitmap_kernel", "ldw_extract_kernel"]
+KERNELS = ["feature_fetch_kernel", "dd_bitmap_kernel", "ldw_extract_kernel", "aggregate_kernel"]
 
 
 def _scratch_bytes(tmp_path):
