@@ -8,9 +8,9 @@ seed batches already resident in HBM.  Prints ONE JSON line:
   roofline   the dominant kernel's algorithmic bytes / its measured duration vs 8 TB/s
   cpu_baseline  the CPU oracle timed on this machine's host cores on the same workload
 The dominant kernel's durations come from HIP events that the library records on the call's
-own stream around its launches during the timed steps (BMS_PROFILE_MAIN); the other stages are
-timed the same way in a few extra steps (BMS_PROFILE), because bracketing every stage costs
-about 0.2 ms per call.
+own stream around its launches during the timed steps (BMS_PROFILE_MAIN | BMS_PROFILE_AS_RUN); the
+other stages are timed the same way in a few extra steps (BMS_PROFILE), because bracketing every stage
+costs about 0.2 ms per call.  Both time the kernels that a call without these flags runs.
 """
 from __future__ import annotations
 
@@ -92,6 +92,12 @@ def algorithmic_bytes(stage: str, rows: int, nnz: int, ncols: int, pnnz: int = 0
         "dd_split": 4 * E,
         "dd_unsplit": 4 * E,
         "dd_front": 4 * U,
+        # ... by bitmaps of vertex ranges: the ids are read to set their bits and become local columns in place
+        "rg_mark": 4 * E,
+        "rg_emit": 4 * U,
+        "rg_lookup": 4 * E,
+        "rg_emit_gather": 4 * U + 8 * E,   # few minibatches: the bits were set by nw_sample, rg_count moves scratch only
+        "nw_small": 28 * R + 16 * E + 4 * U,   # whole hops in one launch
         "dd_bins": 4 * E,
         "dd_place": 4 * E,
         "ld_rows": 20 * R,
@@ -288,17 +294,18 @@ def run_workload(workload: str, steps: int, warmup: int, variant: str, cpu: bool
 
     res = None
     for _ in range(args.warmup):
-        res = fn(csr, batches, w["params"], seed, recycle=res, profile="main")
+        res = fn(csr, batches, w["params"], seed, recycle=res, profile="main_as_run")
     torch.cuda.synchronize()
     # timed region: exactly `steps` bulk calls, inputs resident in HBM.  The sampler's main kernel stage
-    # (nw_sample / ldw_accumulate) is bracketed by HIP events on the call's stream in every timed step; timing
-    # every stage costs ~0.2 ms per call in event records, so the full breakdown is taken in extra steps below.
+    # (nw_sample / ldw_accumulate) is bracketed by HIP events on the call's stream in every timed step (a call whose
+    # hops all run in one launch has none); timing every stage costs ~0.2 ms per call in event records, so the full
+    # breakdown is taken in extra steps below.
     main_ms, main_n = {}, {}
     t_start = time.perf_counter()
     step_ms = []   # a call returns after its stream has drained, so the host clock around it times the step
     for _ in range(args.steps):
         t_step = time.perf_counter()
-        res = fn(csr, batches, w["params"], seed, recycle=res, profile="main")
+        res = fn(csr, batches, w["params"], seed, recycle=res, profile="main_as_run")
         step_ms.append((time.perf_counter() - t_step) * 1e3)
         for name, hop, ms in res.stages():
             main_ms[(name, hop)] = main_ms.get((name, hop), 0.0) + ms
@@ -310,7 +317,7 @@ def run_workload(workload: str, steps: int, warmup: int, variant: str, cpu: bool
     # per-stage breakdown: a few more steps with every stage timed (not part of `value`)
     stage_ms, stage_n = {}, {}
     for _ in range(max(3, min(args.steps, 10))):
-        res = fn(csr, batches, w["params"], seed, recycle=res, profile=True)
+        res = fn(csr, batches, w["params"], seed, recycle=res, profile="as_run")
         for name, hop, ms in res.stages():
             stage_ms[(name, hop)] = stage_ms.get((name, hop), 0.0) + ms
             stage_n[(name, hop)] = stage_n.get((name, hop), 0) + 1
@@ -333,13 +340,15 @@ def run_workload(workload: str, steps: int, warmup: int, variant: str, cpu: bool
         deg = (g.rowptr[1:] - g.rowptr[:-1])
         for hop in range(len(sizes)):
             gathered_of_hop[hop] = int(deg[res.hop(hop).row_vertex.long()].sum().item())
+    staged = {hop for name, hop in stage_ms if name in ("nw_rows", "ld_rows")}   # the others are in nw_small, recorded at hop 0
     for (name, hop), ms in stage_ms.items():
         d = per_stage.setdefault(name, {"ms": 0.0, "launches": 0, "bytes": 0.0})
         d["ms"] += ms / stage_n[(name, hop)]
         d["launches"] += 1
-        hv = res.hop(hop)
         gathered = gathered_of_hop.get(hop, 0)
-        d["bytes"] += algorithmic_bytes(name, hv.rows, hv.nnz, hv.ncols, hv.pnnz, gathered)
+        for h in (hop,) if name != "nw_small" else (x for x in range(len(sizes)) if x not in staged):
+            hv = res.hop(h)
+            d["bytes"] += algorithmic_bytes(name, hv.rows, hv.nnz, hv.ncols, hv.pnnz, gathered)
     dominant = max(per_stage, key=lambda s: per_stage[s]["ms"])
     dom = per_stage[dominant]
     achieved = dom["bytes"] / (dom["ms"] * 1e-3) / 1e9 if dom["ms"] > 0 else 0.0
@@ -353,7 +362,8 @@ def run_workload(workload: str, steps: int, warmup: int, variant: str, cpu: bool
         "avg_launch_ms": round(dom["ms"] / dom["launches"], 4), "launches_per_step": dom["launches"],
         "algorithmic_bytes_per_step": int(dom["bytes"]),
         "timed_in": "the timed steps" if any(name == dominant for name, _ in main_ms) else "extra steps after the timed ones",
-        "timed_with_events": True,   # the timed steps carry the event records of the main stage (the value is conservative)
+        # whether the timed steps carry the event records of the main stage (the value is then conservative)
+        "timed_with_events": bool(main_ms),
         "all_kernels_ms_per_step": {s: round(v["ms"], 4) for s, v in sorted(per_stage.items())},
     }
     if dominant == "nw_sample":

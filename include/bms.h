@@ -66,11 +66,19 @@ extern "C" {
 
 /* bms_opts.flags */
 #define BMS_LADIES_SQUARED 1u /* LADIES column weight e_v^2 (definition in Sec. 2.2) instead of e_v   */
-#define BMS_PROFILE 2u        /* record per-stage device times, see bms_result_stage                  */
+#define BMS_PROFILE 2u        /* record per-stage device times, see bms_result_stage.  A node-wise call then runs its */
+                               /* hops stage by stage with EXTRACT by id-range segments, also where it would choose */
+                               /* other kernels without the flag; see BMS_PROFILE_AS_RUN                          */
 #define BMS_EXTRACT_BUCKETS 4u /* node-wise EXTRACT by one workgroup per minibatch over id-range bins      */
 #define BMS_EXTRACT_BITMAP 8u  /* node-wise EXTRACT by per-minibatch bitmaps in HBM (default above 2.6e8 vertices) */
-#define BMS_EXTRACT_SORT 16u   /* node-wise EXTRACT by LDS sorts of id-range segments (default)              */
-#define BMS_PROFILE_MAIN 64u   /* as BMS_PROFILE, but only the sampler's main kernel stage (nw_sample, ldw_accumulate)   */
+#define BMS_EXTRACT_SORT 16u   /* node-wise EXTRACT by LDS sorts of id-range segments, hop by hop.  Default: chosen by the */
+                               /* call's sizes -- hops of up to 16384 entries per minibatch in one launch by one        */
+                               /* workgroup per minibatch, graphs of a few million vertices by bitmaps of vertex       */
+                               /* ranges, everything else by these segments                                      */
+#define BMS_PROFILE_MAIN 64u   /* only the sampler's main kernel stage (nw_sample, ldw_accumulate) is timed; a node-wise   */
+                               /* call runs all its hops stage by stage, with the EXTRACT it would choose without the flag */
+#define BMS_PROFILE_AS_RUN 2048u /* with BMS_PROFILE or BMS_PROFILE_MAIN: the call runs the kernels that it runs without      */
+                               /* them.  Hops done in one launch are one stage, nw_small (hop 0); they have no nw_sample  */
 #define BMS_LADIES_DENSE 32u   /* LADIES with dense per-minibatch counters in HBM instead of LDS windows     */
                                /* all give identical results; the flags only pick the kernel path          */
 #define BMS_UNION_DST 128u     /* node-wise variant: the frontier's own vertices stay columns of the sampled     */
@@ -278,8 +286,8 @@ int bms_aggregate_hop(const bms_result *res, int32_t hop, const float *X, int32_
                       void *stream);
 
 /*
- * Per-stage device time of the call that produced `res` (only with BMS_PROFILE; measured with HIP
- * events on the call's stream).  idx enumerates the recorded stages in launch order; returns
+ * Per-stage device time of the call that produced `res` (only with BMS_PROFILE or BMS_PROFILE_MAIN; measured with
+ * HIP events on the call's stream).  idx enumerates the recorded stages in launch order; returns
  * BMS_EINVAL past the end.  *name points to a static string such as "nw_sample", *hop to the hop.
  */
 int bms_result_stage(const bms_result *res, int32_t idx, const char **name, int32_t *hop, float *ms);

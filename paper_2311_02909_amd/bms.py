@@ -23,7 +23,7 @@ LIB_PATH = os.path.join(_HERE, "libbms.so")
 OK, EINVAL, ERANGE, EFORMAT, ENOMEM, EHIP, EAGAIN = 0, -1, -2, -3, -4, -5, -6
 HOST, DEVICE_BORROW, DEVICE_COPY = 0, 1, 2
 LADIES_SQUARED, PROFILE, EXTRACT_BUCKETS, EXTRACT_BITMAP, EXTRACT_SORT, LADIES_DENSE, PROFILE_MAIN = 1, 2, 4, 8, 16, 32, 64
-UNION_DST, NODEWISE_REPLACE, ASYNC, LADIES_NO_INDEX = 128, 256, 512, 1024
+UNION_DST, NODEWISE_REPLACE, ASYNC, LADIES_NO_INDEX, PROFILE_AS_RUN = 128, 256, 512, 1024, 2048
 NOALLOC_MAX_K = 16383
 
 
@@ -320,7 +320,7 @@ class Result:
         return out
 
     def stages(self) -> List[Tuple[str, int, float]]:
-        """(stage name, hop, milliseconds) in launch order; empty unless sampled with profile=True."""
+        """(stage name, hop, milliseconds) in launch order; empty unless sampled with a profile."""
         out, i = [], 0
         name, hop, ms = C.c_char_p(), C.c_int32(), C.c_float()
         while lib().bms_result_stage(self.handle, i, C.byref(name), C.byref(hop), C.byref(ms)) == OK:
@@ -341,9 +341,12 @@ class Result:
 
 
 def _profile_flag(profile) -> int:
-    """profile=True: every stage timed; profile="main": only the sampler's main kernel stage (cheaper)."""
-    if profile == "main":
-        return PROFILE_MAIN
+    """profile=True: every stage timed; "main": only the sampler's main kernel stage (cheaper); "as_run" and
+    "main_as_run": the same of the kernels that run without a profile (BMS_PROFILE_AS_RUN)."""
+    if profile in ("main", "main_as_run"):
+        return PROFILE_MAIN | (PROFILE_AS_RUN if profile != "main" else 0)
+    if profile == "as_run":
+        return PROFILE | PROFILE_AS_RUN
     return PROFILE if profile else 0
 
 

@@ -398,7 +398,7 @@ int check_common(const bms_csr *csr, const int32_t *batches, int32_t k, int32_t 
         if (params[h] < 1)
             return fail(BMS_EINVAL, "sampling parameter of hop %d is %d, must be >= 1", h, params[h]);
     if (opts) {
-        if (opts->flags & ~(BMS_LADIES_SQUARED | BMS_PROFILE | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP | BMS_EXTRACT_SORT | BMS_LADIES_DENSE | BMS_PROFILE_MAIN | BMS_UNION_DST | BMS_NODEWISE_REPLACE | BMS_ASYNC | BMS_LADIES_NO_INDEX))
+        if (opts->flags & ~(BMS_LADIES_SQUARED | BMS_PROFILE | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP | BMS_EXTRACT_SORT | BMS_LADIES_DENSE | BMS_PROFILE_MAIN | BMS_UNION_DST | BMS_NODEWISE_REPLACE | BMS_ASYNC | BMS_LADIES_NO_INDEX | BMS_PROFILE_AS_RUN))
             return fail(BMS_EINVAL, "unknown flag bits 0x%x", opts->flags);
         if (opts->recycle && opts->recycle->tag != kTagResult)
             return fail(BMS_EINVAL, "opts->recycle is not a result handle");
@@ -751,11 +751,14 @@ std::vector<int32_t> nodewise_shape(const CallCtx &c, const int32_t *fanouts)
     return shape;
 }
 
+// The profile flags that make a call run stage by stage; none when it is timed as it runs.
+uint32_t staged_by(const CallCtx &c, uint32_t flags) { return (c.flags & BMS_PROFILE_AS_RUN) ? 0u : c.flags & flags; }
+
 // The leading hops of the call whose minibatches fit one workgroup each, whatever the draws give.  With a profile flag
 // or a chosen EXTRACT path the hops run stage by stage (they have no stages of their own in the one kernel).
 int32_t leading_small_hops(const CallCtx &c, const int32_t *fanouts)
 {
-    if (c.flags & (BMS_PROFILE | BMS_PROFILE_MAIN | BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP))
+    if (staged_by(c, BMS_PROFILE | BMS_PROFILE_MAIN) || (c.flags & (BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP)))
         return 0;
     if (c.k > kSmallMaxMb || c.b > kMaxSortedSeeds)
         return 0;
@@ -874,7 +877,7 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
 int ranges_apply(const CallCtx &c, double entries)
 {
     const int64_t n = c.csr->n;
-    if (n < 1 || (c.flags & (BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP | BMS_PROFILE)))
+    if (n < 1 || (c.flags & (BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP)) || staged_by(c, BMS_PROFILE))
         return 0;
     const int64_t most_quads = (n + 127) / 128 + 9 * 1024; // with what rounds the last range up
     if ((int64_t)c.k * most_quads * 20 > c.scratch_limit / 4)
@@ -950,7 +953,9 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
 
     bool seeds_checked = false;
     if (small_hops > 0) {
+        BMS_TRY(prof.begin("nw_small", 0));
         BMS_TRY(run_small_hops(c, batches, fanouts, small_hops, host, &rows_bound));
+        BMS_TRY(prof.end());
         tiles_planned = true;
     } else {
         BMS_TRY(stage_seeds(c, batches, prof, !seeds_by_sort, csr->mb_tileoff.as<int64_t>()));
@@ -1199,12 +1204,12 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             g.rowptr = a.out_rowptr;
             g.col = a.out_col;
             g.row_self = union_dst ? hb.row_self.as<int32_t>() : nullptr;
-            BMS_TRY(prof.begin("rg_mark", h));
+            BMS_TRY(prof.begin(ranges == 1 ? "rg_count" : "rg_mark", h));
             if (ranges == 1)
                 launch_ranges_count(c.launch, g);
             else if (launch_ranges_mark(c.launch, g) != 0)
                 return fail(BMS_EHIP, "launch of the range bitmap kernel was refused");
-            BMS_TRY(prof.mark("rg_emit", h));
+            BMS_TRY(prof.mark(ranges == 1 ? "rg_emit_gather" : "rg_emit", h));
             if (ranges == 1) {
                 launch_ranges_emit_gather(c.launch, g, hb.col_vertex.as<int32_t>(), (int64_t)expected);
             } else {

@@ -478,3 +478,26 @@ def test_sort_extract_minibatches_that_fill_tiles_of_the_cut_exactly(mods, b):
     for _ in range(2):
         res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (8, 2), 31, extract="sort", recycle=res)
         assert_hops_equal(res.hops(), ref, what="b=%d" % b)
+
+
+@pytest.mark.parametrize("n,k,b,fanouts,stages", [
+    (4000, 4, 64, (5, 5), ["nw_small"]),                                          # every hop in one launch
+    (4000, 40, 500, (20, 10), ["nw_small", "nw_rows", "scan_tiles", "nw_sample", "rg_mark", "rg_emit", "rg_lookup"]),
+    (200_000, 2, 900, (15, 10), ["nw_small", "nw_rows", "scan_tiles", "nw_sample", "rg_count", "rg_emit_gather"])])
+def test_calls_timed_as_they_run(mods, n, k, b, fanouts, stages):
+    # the stages are those of the kernels that a call without a profile runs
+    O, bms, _ = mods
+    rng = np.random.default_rng(n + k)
+    rowptr, col = random_csr(n, 14.0, rng)
+    batches = random_batches(n, k, b, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, fanouts, 3)
+    res = None
+    for profile in ("as_run", "as_run", "main_as_run", False):
+        res = bms.sample_nodewise(csr, batches, fanouts, 3, profile=profile, recycle=res)
+        names = [s[0] for s in res.stages()]
+        if profile == "as_run":
+            assert [x for x in names if x != "seeds"] == stages and all(s[2] >= 0 for s in res.stages())
+        else:
+            assert names == (["nw_sample"] if profile and "nw_sample" in stages else [])
+        assert_hops_equal(res.hops(), ref, what="n=%d k=%d profile=%s" % (n, k, profile))
