@@ -144,3 +144,31 @@ def test_extract_by_bitmaps_of_id_ranges(n, used, b, s):
         for call in range(2):
             res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (s,), 3, mb_base=5, recycle=res, extract="sort", **variant)
             assert_hops_equal(res.hops(), ref, what="n=%d b=%d s=%d %s call %d" % (n, b, s, variant, call))
+
+
+# ... and the forms that few, many and large minibatches of such graphs take: bitmaps set by several workgroups and merged (parts 4 to
+# 32) or by one, over ranges of 1024 to 5120 quads; look-ups of 8, 16, 32 and 56 ids per thread in 1, 3, 4, 6 and 8 tables
+@pytest.mark.parametrize("n,k,b,s", [(300_000, 5, 1500, 150), (300_000, 64, 500, 100), (300_000, 64, 1500, 150), (600_000, 16, 1500, 150),
+                                     (1_000_000, 70, 600, 60), (1_300_001, 24, 1500, 150), (2_450_000, 64, 500, 100),
+                                     (3_700_000, 16, 2000, 300), (4_900_000, 6, 1500, 150)])
+def test_forms_of_extract_by_vertex_ranges(n, k, b, s):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(n + k)
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rows = np.sort(rng.choice(n, size=b + 7, replace=False))
+    rowptr[rows + 1] = s + rng.integers(0, 3, size=b + 7)
+    rowptr = np.cumsum(rowptr)
+    steps = rng.integers(1, 2 * n // (s + 3), size=(b + 7, s + 2))   # of a row's list, over [0, n)
+    ids = np.sort(np.cumsum(steps, axis=1) % (n - s - 2), axis=1) + np.arange(s + 2)   # strictly ascending
+    row = np.repeat(np.arange(n), np.diff(rowptr))
+    col = ids[np.searchsorted(rows, row), np.arange(len(row)) - rowptr[row]].astype(np.int32)
+    batches = np.stack([rng.permutation(rows)[:b] for _ in range(k)]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    for variant in ({}, {"union_dst": True}):
+        ref = O.sample_nodewise(rowptr, col, batches, (s,), 3, 5, **variant)
+        res = None
+        for profile in (False, False, "as_run"):
+            res = bms.sample_nodewise(csr, batches, (s,), 3, mb_base=5, recycle=res, profile=profile, **variant)
+            assert_hops_equal(res.hops(), ref, what="n=%d k=%d b=%d s=%d %s" % (n, k, b, s, variant))
+        assert "rg_mark" in {x for x, _, _ in res.stages()}

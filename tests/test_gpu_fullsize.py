@@ -35,6 +35,15 @@ def test_workload_matches_oracle(name):
     ref = ofn(rp, cl, bt, w["params"], synth.SAMPLING_SEED)
     print("  oracle %.1f s on %d threads" % (time.time() - t0, O.set_threads(0)), flush=True)
     assert_hops_equal(res.hops(), ref, with_p=not nodewise, what=name)
+    # ... and as calls without a profile run: leading hops in one launch, graphs of the middle size by vertex ranges
+    for call in range(2 if nodewise else 0):
+        res = fn(csr, batches, w["params"], synth.SAMPLING_SEED, recycle=res)
+        assert_hops_equal(res.hops(), ref, what="%s, plain call %d" % (name, call))
+    if nodewise:
+        res = fn(csr, batches, w["params"], synth.SAMPLING_SEED, recycle=res, profile="as_run")
+        stages = {s for s, _, _ in res.stages()}
+        assert "nw_small" in stages and ("rg_lookup" in stages) == (name == "mid_sage"), sorted(stages)
+        assert_hops_equal(res.hops(), ref, what=name + ", timed as it runs")
     # properties that hold at any size
     for h, hop in enumerate(ref):
         assert hop.rows <= w["k"] * w["batch"] * (1 if h == 0 else max(w["params"][:h]) ** h * 10**6)
