@@ -27,6 +27,7 @@ constexpr int32_t kMaxMinibatches = 65535; // some kernels take the minibatch fr
 constexpr int64_t kNoWaitEntries = 32LL << 20; // result buffers up to this many entries may be sized by a bound
 constexpr double kBitmapIdsPerEntry = 128.0; // EXTRACT ranks by bitmap when a minibatch samples at least n / this many ids
                                             // (measured: by bitmap wins at 4..15 ids of [0, n) per sampled id, by counting at 580)
+constexpr double kMostIdsInMemory = 96e6; // EXTRACT by bitmaps that the sampling kernel sets: vertices of all minibatches, at most
 constexpr int32_t kHostScalars = 72; // the 64 scalars of a call, then the seed flags of the calls that check seeds in their
                                     // first kernel: two 32-bit words that it sets in host memory (range, repeat); then
                                     // the word that says that all of it has arrived
@@ -870,7 +871,10 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
 // Which hops of about `entries` entries EXTRACT by bitmaps of vertex ranges: 0 none of this, 1 the sampling kernel sets the
 // bits, 2 the mark kernel does.
 //   1  few minibatches and entries: setting a bit in memory (12 ps per entry, in the shadow of the sampling) and fetching an
-//      entry's word (30 ps) beat kernels that let every workgroup see all of a minibatch's entries
+//      entry's word (30 ps) beat kernels that let every workgroup see all of a minibatch's entries.  The bitmaps are cleared,
+//      counted and read as a whole, 0.45 bytes per minibatch and vertex: level with the cut into segments at k n = 90 to
+//      110 million whatever the entries (calls of 1024 seeds, (15, 10, 5), against the segments: 1 x 30 M vertices 127 and 163 us,
+//      3 x 30 M 174 and 177, 1 x 111 M 159 and 162, 4 x 30 M 199 and 179, 4 x 111 M 316 and 175)
 //   2  the ranges take up to 8 tables (4.9 million ids: a look-up costs about 0.5 ps per entry and table, the cut into segments
 //      9), and the bitmaps are no larger than what the entries themselves move in a few passes (16 bytes of ids and counts
 //      per 128 ids, against the segments' 30 bytes per entry)
@@ -882,7 +886,7 @@ int ranges_apply(const CallCtx &c, double entries)
     const int64_t most_quads = (n + 127) / 128 + 9 * 1024; // with what rounds the last range up
     if ((int64_t)c.k * most_quads * 20 > c.scratch_limit / 4)
         return 0;
-    if (c.k <= kRangesFewMb && entries <= 1.5e6)
+    if (c.k <= kRangesFewMb && entries <= 1.5e6 && (double)c.k * (double)n <= kMostIdsInMemory)
         return 1;
     return ranges_passes(n) <= 8 && (double)c.k * (double)n <= 64.0 * entries ? 2 : 0;
 }

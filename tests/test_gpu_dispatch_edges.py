@@ -172,3 +172,31 @@ def test_forms_of_extract_by_vertex_ranges(n, k, b, s):
             res = bms.sample_nodewise(csr, batches, (s,), 3, mb_base=5, recycle=res, profile=profile, **variant)
             assert_hops_equal(res.hops(), ref, what="n=%d k=%d b=%d s=%d %s" % (n, k, b, s, variant))
         assert "rg_mark" in {x for x, _, _ in res.stages()}
+
+
+def _few_long_rows(n, b, s, rng):
+    """A graph of n vertices of which b, spread over [0, n), have s random neighbours each; on the device."""
+    from paper_2311_02909_amd import bms
+    rows = np.sort(rng.choice(n, size=b, replace=False))
+    degree = torch.zeros(n, dtype=torch.int64, device="cuda")
+    degree[torch.from_numpy(rows).cuda()] = s
+    rowptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(degree, 0, out=rowptr[1:])
+    col = np.sort(rng.integers(0, n - s, size=(b, s)), axis=1) + np.arange(s)
+    return bms.Csr(rowptr, torch.from_numpy(col.astype(np.int32).reshape(-1)).cuda()), rows
+
+
+@pytest.mark.parametrize("n,k,by_bits", [(2_000_000, 4, True), (31_000_000, 3, True), (33_000_000, 3, False), (95_000_000, 1, True),
+                                         (97_000_000, 1, False)])
+def test_few_minibatches_of_large_graphs_go_by_segments(n, k, by_bits):
+    # bitmaps in memory are cleared, counted and read as a whole: 96 million bits, in all minibatches, is where that ends
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(k)
+    csr, rows = _few_long_rows(n, 1200, 60, rng)
+    batches = torch.from_numpy(np.stack([rng.permutation(rows)[:1000] for _ in range(k)]).astype(np.int32)).cuda()
+    got, by_segments = (bms.sample_nodewise(csr, batches, (50,), 3, profile="as_run", extract=x) for x in (None, "sort"))
+    assert ("rg_count" in {x for x, _, _ in got.stages()}) == by_bits
+    assert "dd_split" in {x for x, _, _ in by_segments.stages()}
+    for a, b in zip(got.hops(), by_segments.hops()):
+        assert torch.equal(a.rowptr, b.rowptr) and torch.equal(a.col, b.col) and torch.equal(a.col_vertex, b.col_vertex)
+        assert torch.equal(a.mb_coloff, b.mb_coloff)
