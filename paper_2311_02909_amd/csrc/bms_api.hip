@@ -884,7 +884,7 @@ int ranges_apply(const CallCtx &c, double entries)
     if (n < 1 || (c.flags & (BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP)) || staged_by(c, BMS_PROFILE))
         return 0;
     const int64_t most_quads = (n + 127) / 128 + 9 * 1024; // with what rounds the last range up
-    if ((int64_t)c.k * most_quads * 20 > c.scratch_limit / 4)
+    if ((int64_t)c.k * most_quads * 20 > c.scratch_limit / 4) // one bitmap per minibatch; plan_ranges takes more as they fit
         return 0;
     if (c.k <= kRangesFewMb && entries <= 1.5e6 && (double)c.k * (double)n <= kMostIdsInMemory)
         return 1;
@@ -988,7 +988,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             g.qw = kRangeQuads;
             g.parts = 1;
             if (ranges == 2)
-                plan_ranges(g, csr->num_cu, expected / c.k);
+                plan_ranges(g, csr->num_cu, expected / c.k, c.scratch_limit / 4);
             g.qw_inverse = (uint32_t)((0x100000000ULL + g.qw - 1) / g.qw);
             g.H = (int32_t)((g.quads + g.qw - 1) / g.qw);
             g.stride = (int64_t)g.H * g.qw;

@@ -182,7 +182,7 @@ struct RangeArgs {
     uint32_t *done;            // a device word, zero between launches
 };
 int ranges_passes(int64_t n);  // tables of launch_ranges_lookup
-void plan_ranges(RangeArgs &, int num_cu, double per_mb); // n, k, quads -> qw and parts for launch_ranges_mark
+void plan_ranges(RangeArgs &, int num_cu, double per_mb, int64_t most_bytes); // n, k, quads -> qw and parts for launch_ranges_mark
 int launch_ranges_mark(const Launch &, const RangeArgs &); // -1: launch refused
 void launch_ranges_count(const Launch &, const RangeArgs &); // bits set already: qw = kRangeQuads, parts = 1
 void launch_ranges_emit(const Launch &, const RangeArgs &, int32_t *col_vertex);

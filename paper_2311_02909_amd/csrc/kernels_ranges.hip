@@ -487,7 +487,8 @@ static int64_t mark_ranges(int64_t n) { return ((n + 127) / 128 + kMarkQuads - 1
 // Measured on 0.1 to 0.6 million entries per minibatch and 2.4 million vertices, one workgroup per compute unit: a mark
 // workgroup that counts takes 10 us and 76 ps per entry, one that does not 5 us and 150 ps (its range is wider: more ids set
 // bits), the merging count 10 us and 4 TB/s.  Both run in whole rounds of the chip.
-void plan_ranges(RangeArgs &a, int num_cu, double per_mb)
+// most_bytes: of all bitmaps and counts together.
+void plan_ranges(RangeArgs &a, int num_cu, double per_mb, int64_t most_bytes)
 {
     double least = 0.0;
     for (int its = 1; its <= kMarkIts; ++its) {
@@ -499,7 +500,8 @@ void plan_ranges(RangeArgs &a, int num_cu, double per_mb)
             a.parts = 1;
         }
     }
-    for (int32_t parts = 2; parts <= kMostParts; parts *= 2) {
+    const int64_t stride = (a.quads + kRangeQuads - 1) / kRangeQuads * kRangeQuads;
+    for (int32_t parts = 2; parts <= kMostParts && a.k * stride * (parts * 16 + 4) <= most_bytes; parts *= 2) {
         const double rounds = (double)((a.k * mark_ranges(a.n) * parts + num_cu - 1) / num_cu);
         const double cost = rounds * (per_mb / parts * 150e-6 + 5.0) + 10.0 + (double)a.k * parts * (double)a.n / 8 / 4e6;
         if (cost < least) {

@@ -200,3 +200,21 @@ def test_few_minibatches_of_large_graphs_go_by_segments(n, k, by_bits):
     for a, b in zip(got.hops(), by_segments.hops()):
         assert torch.equal(a.rowptr, b.rowptr) and torch.equal(a.col, b.col) and torch.equal(a.col_vertex, b.col_vertex)
         assert torch.equal(a.mb_coloff, b.mb_coloff)
+
+
+def test_bitmaps_of_vertex_ranges_stay_inside_the_scratch_limit():
+    # few large minibatches have their ids marked by up to 32 workgroups with a bitmap each: only as many as the limit has room for
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(4)
+    n, k = 300_000, 5
+    csr, rows = _few_long_rows(n, 1600, 160, rng)
+    batches = torch.from_numpy(np.stack([rng.permutation(rows)[:1500] for _ in range(k)]).astype(np.int32)).cuda()
+    limit, ref = 6_000_000, None
+    for scratch_limit in (limit, limit, 0):
+        res = bms.sample_nodewise(csr, batches, (150,), 3, profile="as_run", scratch_limit=scratch_limit)
+        assert "rg_mark" in {x for x, _, _ in res.stages()}
+        assert (csr.held_bytes() <= limit) == (scratch_limit == limit), csr.held_bytes()
+        got = [(h.rowptr.cpu(), h.col.cpu(), h.col_vertex.cpu(), h.mb_coloff.cpu()) for h in res.hops()]
+        ref = ref or got
+        for a, b in zip(got, ref):
+            assert all(torch.equal(x, y) for x, y in zip(a, b))
