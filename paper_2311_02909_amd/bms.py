@@ -234,6 +234,7 @@ class Csr:
         h = C.c_void_p()
         _check(lib().bms_csr_load(rowptr.data_ptr(), col.data_ptr() if nnz else None, n, nnz, loc, C.byref(h)))
         self.handle = h
+        self.device = torch.cuda.current_device()   # the one the library put the handle on
         if loc == HOST:
             self._keep = None
         a, b, c = C.c_int64(), C.c_int64(), C.c_int64()
@@ -261,8 +262,8 @@ class Csr:
 class Result:
     """Owner of the device buffers of one bulk sample (bms_result)."""
 
-    def __init__(self, handle):
-        self.handle = handle
+    def __init__(self, handle, device: int):
+        self.handle, self.device = handle, device
         k, L = C.c_int32(), C.c_int32()
         _check(lib().bms_result_info(handle, C.byref(k), C.byref(L)))
         self.k, self.L = k.value, L.value
@@ -282,14 +283,14 @@ class Result:
         return v.value
 
     def hop(self, h: int) -> Hop:
-        t = native().hop(self.handle.value if self.handle else 0, h, self.k, torch.cuda.current_device(), self)
+        t = native().hop(self.handle.value if self.handle else 0, h, self.k, self.device, self)
         if type(t) is int:
             _check(t)
         return Hop(*t)
 
     def minibatch(self, h: int, i: int) -> Minibatch:
         """bms_result_minibatch: minibatch i of hop h cut out of the stack (no copies of the arrays)."""
-        t = native().minibatch(self.handle.value if self.handle else 0, h, i, torch.cuda.current_device(), self)
+        t = native().minibatch(self.handle.value if self.handle else 0, h, i, self.device, self)
         if type(t) is int:
             _check(t)
         return Minibatch(*t)
@@ -359,7 +360,7 @@ def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, m
     batches = batches.contiguous()
     k, b = batches.shape
     if stream is None:
-        stream = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        stream = torch._C._cuda_getCurrentRawStream(csr.device)
     alloc = dealloc = old = None
     if recycle is not None:
         old = recycle.handle.value if recycle.handle else 0  # a recycled result keeps the allocator it was created with
@@ -370,9 +371,9 @@ def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, m
     if rc != OK:
         _check(rc)
     if recycle is not None:
-        recycle.k, recycle.L = k, len(params)
+        recycle.k, recycle.L, recycle.device = k, len(params), csr.device
         return recycle
-    r = Result(C.c_void_p(out))
+    r = Result(C.c_void_p(out), csr.device)
     r._allocator = allocator   # the callbacks must outlive the result
     return r
 

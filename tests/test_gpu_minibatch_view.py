@@ -73,3 +73,18 @@ def test_minibatch_views_ladies_and_aggregation_per_minibatch():
         lens = (m.rowptr[1:] - m.rowptr[:-1])
         A[torch.arange(m.rows, device="cuda").repeat_interleave(lens), m.col.long()] = 1.0
         assert torch.equal(A @ Xi, Y[m.row0:m.row0 + m.rows])
+
+
+def test_views_are_on_the_device_of_the_result(monkeypatch):
+    # ... not on the one that is current when they are made
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(63)
+    rowptr, col = random_csr(500, 9.0, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = bms.sample_nodewise(csr, torch.from_numpy(random_batches(500, 2, 30, rng)).cuda(), (4, 3), 5, union_dst=True)
+    device = torch.device("cuda", torch.cuda.current_device())
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: device.index + 1)
+    hop, mb = res.hop(1), res.minibatch(1, 1)
+    for x in (hop.mb_rowoff, hop.row_vertex, hop.rowptr, hop.col, hop.mb_coloff, hop.col_vertex, hop.row_self,
+              mb.row_vertex, mb.rowptr, mb.col, mb.col_vertex, mb.row_self):
+        assert x.device == device
