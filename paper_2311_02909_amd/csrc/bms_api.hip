@@ -179,6 +179,7 @@ struct bms_csr {
     BMS_BUF(lw_count); BMS_BUF(lw_tiles); BMS_BUF(lw_rowcnt); // LADIES by LDS windows
     BMS_BUF(sm_status); // hops done by one workgroup per minibatch: sizes published
     BMS_BUF(sm_ticket); // counters: 0 next minibatch of those, 1 workgroups done (announce), 2 numbers (Lookback), 3 done (layer-wise)
+    bool tickets_known = false;              // ... are what sm_taken and lb_taken say; lost when a call fails
     uint32_t sm_epoch = 0, sm_taken = 0;     // launches so far, minibatches handed out by them
     BMS_BUF(lb_status);                      // values that workgroups of a launch bring (Lookback)
     uint32_t lb_epoch = 0, lb_taken = 0;     // launches so far (24 bits), numbers taken by them
@@ -458,6 +459,7 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
     c.flags = opts ? opts->flags : 0u;
     c.scratch_limit = (opts && opts->scratch_limit > 0) ? opts->scratch_limit : kDefaultScratchLimit;
     HIP_TRY(hipSetDevice(csr->device));
+    (void)hipGetLastError(); // of an earlier call, of whoever made it: the checks after launches are to see this call's
     BMS_TRY(csr->scan_tmp.ensure(kScanTmpLen * sizeof(int64_t)));
     c.launch = Launch{c.stream, csr->num_cu, csr->scan_tmp.as<int64_t>(), kScanTmpLen};
     c.fresh_result = !(opts && opts->recycle);
@@ -501,9 +503,10 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
     c.res->host_off = false;
     c.res->host[64] = 0;
     BMS_TRY(csr->sm_ticket.ensure(256));
-    if (csr->sm_ticket.grew) {
+    if (!csr->tickets_known) { // (a workgroup's number decides what it writes: never one of another launch)
         HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
         csr->sm_taken = csr->lb_taken = 0;
+        csr->tickets_known = true;
     }
     BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
     return BMS_OK;
@@ -512,6 +515,8 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
 int abort_call(CallCtx &c, int rc)
 {
     (void)hipStreamSynchronize(c.stream);
+    if (c.csr)
+        c.csr->tickets_known = false; // a launch that was reported as refused may have run all the same
     if (c.fresh_result && c.res) {
         result_release(c.res);
         delete c.res;
@@ -2077,6 +2082,7 @@ int bms_result_minibatch_offsets(const bms_result *res, int32_t hop, int64_t *ro
     const bms_hop_view &v = res->hops[hop].view;
     const size_t bytes = ((size_t)res->k + 1) * sizeof(int64_t);
     hipStream_t st = (hipStream_t)stream;
+    (void)hipGetLastError(); // of an earlier call
     launch_mb_edge_offsets(st, v.rowptr, v.mb_rowoff, res->k, tmp); // writes all k+1 values: nothing to clear
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(edge_off, tmp, bytes, hipMemcpyDeviceToHost, st));
@@ -2162,6 +2168,7 @@ int bms_fetch_features(const float *H, int64_t n, int32_t f, const int32_t *ids,
     if (cached_cu[device])
         num_cu = cached_cu[device];
     slot[0] = slot[1] = 0;
+    (void)hipGetLastError(); // of an earlier call
     launch_feature_fetch(Launch{(hipStream_t)stream, num_cu}, H, n, f, ids, m, out, reinterpret_cast<int32_t *>(slot_dev), slot_dev + 1, call);
     HIP_TRY(hipGetLastError());
     BMS_TRY(wait_word(slot + 1, call, (hipStream_t)stream));
@@ -2198,6 +2205,7 @@ int bms_aggregate_hop(const bms_result *res, int32_t hop, const float *X, int32_
     int device = 0, num_cu = 256;
     HIP_TRY(hipGetDevice(&device));
     HIP_TRY(hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, device));
+    (void)hipGetLastError(); // of an earlier call
     launch_aggregate(Launch{(hipStream_t)stream, num_cu > 0 ? num_cu : 256}, a);
     HIP_TRY(hipGetLastError());
     return BMS_OK;

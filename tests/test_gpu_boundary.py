@@ -168,3 +168,31 @@ def test_async_call_that_meets_crowded_ids_asks_to_be_repeated(mods):
         except bms.BmsError as err:
             assert err.code == bms.EAGAIN and attempt < 2
     assert_hops_equal(res.hops(), ref, what="after the repeat")
+
+
+def test_calls_after_one_that_ran_out_of_memory():
+    # the HIP runtime keeps an error until someone asks for it: it is not the following call's, whose launches are all right and whose
+    # workgroups have taken their numbers
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(71)
+    rowptr, col = random_csr(3000, 12.0, rng)
+    batches = random_batches(3000, 4, 64, rng)
+    wide = torch.zeros(50_000_001, dtype=torch.int64, device="cuda")   # no edges: vertex sets of 375 GB, refused by the runtime
+    large = bms.Csr(wide, torch.zeros(0, dtype=torch.int32, device="cuda"))
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, (5, 5), 3)
+    lad = O.sample_ladies(rowptr, col, batches, (20, 20), 3)
+    H = torch.ones((3000, 8), device="cuda")
+    res = None
+    for _ in range(2):
+        with pytest.raises(bms.BmsError) as e:
+            bms.sample_nodewise(large, np.zeros((60_000, 1), dtype=np.int32), (2,), 3, extract="bitmap", scratch_limit=1 << 50)
+        assert e.value.code == bms.ENOMEM
+        for _ in range(2):
+            res = bms.sample_nodewise(csr, batches, (5, 5), 3, recycle=res)
+            assert_hops_equal(res.hops(), ref, what="after an error")
+        with pytest.raises(bms.BmsError):
+            bms.sample_nodewise(large, np.zeros((60_000, 1), dtype=np.int32), (2,), 3, extract="bitmap", scratch_limit=1 << 50)
+        assert bool((bms.fetch_features(H, res.hop(1).col_vertex) == 1).all())
+        assert_hops_equal(bms.sample_ladies(csr, batches, (20, 20), 3).hops(), lad, with_p=True, what="after an error")
