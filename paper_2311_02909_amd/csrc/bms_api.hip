@@ -144,6 +144,12 @@ int scratch_address(int device, int64_t **out)
     return BMS_OK;
 }
 
+uint64_t next_csr_serial()
+{
+    static std::atomic<uint64_t> last{0};
+    return ++last;
+}
+
 struct StageTime {
     const char *name;
     int32_t hop;
@@ -155,6 +161,7 @@ struct StageTime {
 
 struct bms_csr {
     uint32_t tag = kTagCsr;
+    uint64_t serial = next_csr_serial(); // what results know the handle by: its address may be another's after bms_free
     int device = 0;
     int num_cu = 256;
     int64_t n = 0, nnz = 0, max_degree = 0;
@@ -204,9 +211,10 @@ struct HopBufs {
     }
 };
 
-// what a BMS_ASYNC node-wise call leaves for the first look at its result
+// what a BMS_ASYNC node-wise call leaves for the first look at its result (the handle may be gone by then)
 struct PendingNodewise {
-    bms_csr *csr = nullptr;
+    uint64_t csr = 0; // its serial number
+    int64_t n = 0;
     int32_t k = 0, b = 0, L = 0;
     bool union_dst = false;
     std::vector<int32_t> shape;
@@ -224,7 +232,7 @@ struct bms_result {
     size_t events_used = 0;
     // sizes the previous node-wise call with the same shape produced; a recycled result lets the
     // next call enqueue every hop without waiting for the device (buffers sized by upper bounds)
-    const bms_csr *hint_csr = nullptr;
+    uint64_t hint_csr = 0; // serial number of the handle; 0: none
     std::vector<int32_t> hint_shape; // k, b, fanouts...
     std::vector<int64_t> hint_nnz;   // per hop
     int32_t attempts = 1; // how often the call that wrote this result enqueued its kernels
@@ -527,7 +535,7 @@ int abort_call(CallCtx &c, int rc)
             h.view = bms_hop_view{};
         c.res->L = 0;
         c.res->k = 0;
-        c.res->hint_csr = nullptr;
+        c.res->hint_csr = 0;
         c.res->mb_offsets.clear();
         c.res->stages.clear();
     }
@@ -601,12 +609,12 @@ int64_t *host_offsets(const CallCtx &c)
 
 // scalars: the call's scalars on the host; first_kernel: the result's pinned block, where the kernels that check the
 // seeds themselves raise their flags
-int seed_flag_error(const bms_csr *csr, const int64_t *scalars, const int64_t *first_kernel)
+int seed_flag_error(int64_t n, const int64_t *scalars, const int64_t *first_kernel)
 {
     const int32_t flag = (int32_t)(scalars[63] & 0xFFFFFFFF);
     const int32_t *flags = reinterpret_cast<const int32_t *>(first_kernel + 64);
     if ((flag & 1) || flags[0])
-        return fail(BMS_ERANGE, "a seed vertex lies outside [0, %lld)", (long long)csr->n);
+        return fail(BMS_ERANGE, "a seed vertex lies outside [0, %lld)", (long long)n);
     if ((flag & 2) || flags[1])
         return fail(BMS_ERANGE, "a seed vertex is repeated inside one minibatch");
     return BMS_OK;
@@ -684,7 +692,7 @@ constexpr int32_t kMaxHops = 15; // 4 scalar slots per hop in a 64-entry block
 int finish_nodewise(bms_result *res, const PendingNodewise &pn, const int64_t *host, bool check_seeds, uint32_t *redo)
 {
     if (check_seeds)
-        BMS_TRY(seed_flag_error(pn.csr, host, host));
+        BMS_TRY(seed_flag_error(pn.n, host, host));
     for (int32_t h = 0; h < pn.L; ++h)
         if (host[h * 4 + 2] & 0xFFFFFFFFLL)
             *redo |= 1u << h;
@@ -718,7 +726,7 @@ void empty_result(bms_result *r, bool keep_hints)
     r->L = 0;
     r->k = 0;
     if (!keep_hints)
-        r->hint_csr = nullptr;
+        r->hint_csr = 0;
     r->mb_offsets.clear();
 }
 
@@ -946,7 +954,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     // be enqueued without a host round trip.  Buffers are then sized by the upper bound
     // rows * min(s, max degree) (always enough), tuning parameters by the remembered sizes.
     const std::vector<int32_t> shape = nodewise_shape(c, fanouts);
-    bool no_wait = buckets && !c.fresh_result && c.res->hint_csr == csr && c.res->hint_shape == shape &&
+    bool no_wait = buckets && !c.fresh_result && c.res->hint_csr == csr->serial && c.res->hint_shape == shape &&
                    (int32_t)c.res->hint_nnz.size() == c.L;
     if (no_wait) {
         double bound = (double)rows_bound, total = 0.0;
@@ -1068,7 +1076,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         } else {
             BMS_TRY(read_scalars(c));
             if (!seeds_checked)
-                BMS_TRY(seed_flag_error(csr, csr->host_pinned, c.res->host));
+                BMS_TRY(seed_flag_error(csr->n, csr->host_pinned, c.res->host));
             seeds_checked = true;
             nnz = nnz_tune = host_slot(c, h, 0);
         }
@@ -1278,7 +1286,8 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
     }
     csr->segcnt_clean = true; // every hop's kernels are enqueued: they leave the counters at zero again
     PendingNodewise pn;
-    pn.csr = csr;
+    pn.csr = csr->serial;
+    pn.n = csr->n;
     pn.k = c.k;
     pn.b = c.b;
     pn.L = c.L;
@@ -1308,7 +1317,7 @@ int sample_nodewise_impl(CallCtx &c, const int32_t *batches, const int32_t *fano
 {
     // hops that gave up on a kernel path in an earlier call of this shape start with the path that worked then
     std::vector<uint8_t> mode((size_t)c.L, 0);
-    if (!c.fresh_result && c.res->hint_csr == c.csr && c.res->hint_shape == nodewise_shape(c, fanouts) &&
+    if (!c.fresh_result && c.res->hint_csr == c.csr->serial && c.res->hint_shape == nodewise_shape(c, fanouts) &&
         (int32_t)c.res->hint_mode.size() == c.L)
         mode = c.res->hint_mode;
     for (int32_t attempt = 0; attempt <= 2 * c.L; ++attempt) {
@@ -1421,7 +1430,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     // Steady state: a recycled result that remembers what the same call shape needed lets every hop be enqueued
     // without a host round trip; the kernels check the sizes they find against what was provided (LwHop::giveup)
     const std::vector<int32_t> shape = ladies_shape(c, s_per_layer);
-    const bool no_wait = may_skip_waits && !c.fresh_result && c.res->hint_csr == csr && c.res->hint_shape == shape &&
+    const bool no_wait = may_skip_waits && !c.fresh_result && c.res->hint_csr == csr->serial && c.res->hint_shape == shape &&
                          (int32_t)c.res->hint_gathered.size() == c.L && (int32_t)c.res->hint_pnnz.size() == c.L &&
                          (int32_t)c.res->hint_nnz.size() == c.L;
     int32_t *giveup = reinterpret_cast<int32_t *>(csr->scalars.as<int64_t>() + 60);
@@ -1519,7 +1528,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         } else {
             BMS_TRY(read_scalars(c));
             if (h == 0)
-                BMS_TRY(seed_flag_error(csr, csr->host_pinned, c.res->host));
+                BMS_TRY(seed_flag_error(csr->n, csr->host_pinned, c.res->host));
             D = host_slot(c, h, 3);
         }
         w.giveup = giveup;
@@ -1633,7 +1642,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     BMS_TRY(wait_arrival(c));
     const int64_t *host = c.res->host;
     if (no_wait) {
-        BMS_TRY(seed_flag_error(csr, host, host));
+        BMS_TRY(seed_flag_error(csr->n, host, host));
         if ((int32_t)(host[60] & 0xFFFFFFFF)) { // a size went past what the remembered call needed
             *redo = true;
             return BMS_OK;
@@ -1652,7 +1661,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         c.res->hint_pnnz[h] = v.pnnz;
         c.res->hint_gathered[h] = host[4 * h + 3];
     }
-    c.res->hint_csr = csr;
+    c.res->hint_csr = csr->serial;
     c.res->hint_shape = shape;
     BMS_TRY(prof.finish());
     return BMS_OK;
@@ -1745,7 +1754,7 @@ int sample_ladies_impl(CallCtx &c, const int32_t *batches, const int32_t *s_per_
         BMS_TRY(prof.end());
         BMS_TRY(read_scalars(c)); // D sizes the tile arrays of the gathered order
         if (h == 0)
-            BMS_TRY(seed_flag_error(csr, csr->host_pinned, c.res->host));
+            BMS_TRY(seed_flag_error(csr->n, csr->host_pinned, c.res->host));
         const int64_t D = host_slot(c, h, 3);
         BMS_TRY(csr->tile_off.ensure((size_t)(D / kGatherTile + 3) * sizeof(int64_t)));
         a.tile_off = csr->tile_off.as<int64_t>();

@@ -196,3 +196,27 @@ def test_calls_after_one_that_ran_out_of_memory():
             bms.sample_nodewise(large, np.zeros((60_000, 1), dtype=np.int32), (2,), 3, extract="bitmap", scratch_limit=1 << 50)
         assert bool((bms.fetch_features(H, res.hop(1).col_vertex) == 1).all())
         assert_hops_equal(bms.sample_ladies(csr, batches, (20, 20), 3).hops(), lad, with_p=True, what="after an error")
+
+
+def test_asynchronous_result_looked_at_after_its_graph_is_gone(mods):
+    O, bms = mods
+    rng = np.random.default_rng(84)
+    rowptr, col = random_csr(30000, 14.0, rng)
+    batches = random_batches(30000, 6, 500, rng)
+    rp, cl = torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda()
+    ref = O.sample_nodewise(rowptr, col, batches, (6, 5, 4), 3)
+    csr = bms.Csr(rp, cl)
+    res = bms.sample_nodewise(csr, batches, (6, 5, 4), 3)
+    bad = batches.copy()
+    bad[3, 7] = 30000
+    for seeds in (batches, bad):
+        for _ in range(2):   # a recycled call of a remembered shape returns before its kernels have run
+            res = bms.sample_nodewise(csr, seeds if _ else batches, (6, 5, 4), 3, recycle=res, async_=_ == 1)
+        csr.free()
+        if seeds is batches:
+            assert_hops_equal(res.hops(), ref, what="after bms_free of the graph")
+        else:
+            with pytest.raises(bms.BmsError) as e:
+                res.wait()
+            assert e.value.code == bms.ERANGE and "30000" in str(e.value)
+        csr = bms.Csr(rp, cl)

@@ -501,3 +501,39 @@ def test_calls_timed_as_they_run(mods, n, k, b, fanouts, stages):
         else:
             assert names == (["nw_sample"] if profile and "nw_sample" in stages else [])
         assert_hops_equal(res.hops(), ref, what="n=%d k=%d profile=%s" % (n, k, profile))
+
+
+def test_result_recycled_with_another_graph_at_the_address_of_the_old_one(mods):
+    # what a result remembers (sizes, kernel paths, the table of unequal segments) belongs to the handle, not to its address, which
+    # the next handle gets after bms_free
+    O, bms, _ = mods
+    rng = np.random.default_rng(52)
+
+    def hubs_first(n, m):
+        rowptr, col = skewed_csr(n, m, rng)
+        deg = np.diff(rowptr)
+        order = np.argsort(-deg, kind="stable")
+        newid = np.empty(n, dtype=np.int64)
+        newid[order] = np.arange(n)
+        key = np.sort(newid[np.repeat(np.arange(n), deg)] * n + newid[col])
+        rowptr = np.zeros(n + 1, dtype=np.int64)
+        np.add.at(rowptr, key // n + 1, 1)
+        return np.cumsum(rowptr), (key % n).astype(np.int32)
+
+    graphs = []
+    for n, m in ((6_000_000, 5_000_000), (9_000_000, 7_000_000), (5_500_000, 5_000_000)):
+        rowptr, col = hubs_first(n, m)
+        batches = random_batches(n, 3, 2000, rng, candidates=np.nonzero(np.diff(rowptr) > 0)[0])
+        graphs.append((torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda(), batches,
+                       O.sample_nodewise(rowptr, col, batches, (10, 8, 6), 13)))
+    res, address = None, None
+    for g, (rowptr, col, batches, ref) in enumerate(graphs):
+        handles = [bms.Csr(rowptr, col) for _ in range(20)]
+        pick = [c for c in handles if c.handle.value == address] or handles[:1]
+        address = pick[0].handle.value
+        for call in range(3):
+            res = bms.sample_nodewise(pick[0], batches, (10, 8, 6), 13, extract="sort", recycle=res)
+            assert (res.attempts() > 1) == (call == 0), "graph %d, call %d: %d attempts" % (g, call, res.attempts())
+            assert_hops_equal(res.hops(), ref, what="graph %d call %d" % (g, call))
+        for c in handles:
+            c.free()
