@@ -9,6 +9,7 @@ fallback: if the libraries have not been built, the first use of an entry point 
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import os
 from dataclasses import dataclass
@@ -351,8 +352,17 @@ def _profile_flag(profile) -> int:
     return PROFILE if profile else 0
 
 
+def _on(stream):
+    """The raw stream as torch's current one: what is allocated or copied for work on it (a contiguous copy of the
+    inputs, outputs, the buffers of a TorchAllocator) is ordered with that work, and its memory is not reused before."""
+    return torch.cuda.stream(torch.cuda.ExternalStream(int(stream)))
+
+
 def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, mb_base, stream, recycle, flags,
             scratch_limit, allocator=None):
+    if stream is not None and torch.cuda.current_stream().cuda_stream != int(stream):
+        with _on(stream):
+            return _sample(ladies, csr, batches, params, seed, mb_base, stream, recycle, flags, scratch_limit, allocator)
     if isinstance(batches, np.ndarray):
         batches = torch.from_numpy(np.ascontiguousarray(batches, dtype=np.int32))
     if batches.dtype != torch.int32 or batches.dim() != 2:
@@ -415,7 +425,8 @@ def fetch_features(H: torch.Tensor, ids: torch.Tensor, out: Optional[torch.Tenso
     n, f = H.shape
     m = ids.shape[0]
     if out is None:
-        out = torch.empty((m, f), dtype=torch.float32, device=H.device)
+        with _on(stream) if stream is not None else contextlib.nullcontext():
+            out = torch.empty((m, f), dtype=torch.float32, device=H.device)
     elif out.dtype != torch.float32 or tuple(out.shape) != (m, f) or not out.is_cuda or not out.is_contiguous():
         raise TypeError("out must be a contiguous m x f float32 device tensor")
     if stream is None:
@@ -434,7 +445,8 @@ def aggregate_hop(res: "Result", hop: int, X: torch.Tensor, mean: bool = True, o
         raise ValueError("X has %d rows, the hop has %d columns" % (X.shape[0], ncols))
     f = X.shape[1]
     if out is None:
-        out = torch.empty((rows, f), dtype=torch.float32, device=X.device)
+        with _on(stream) if stream is not None else contextlib.nullcontext():
+            out = torch.empty((rows, f), dtype=torch.float32, device=X.device)
     elif out.dtype != torch.float32 or tuple(out.shape) != (rows, f) or not out.is_cuda or not out.is_contiguous():
         raise TypeError("out must be a contiguous rows x f float32 device tensor")
     if stream is None:

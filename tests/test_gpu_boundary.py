@@ -220,3 +220,32 @@ def test_asynchronous_result_looked_at_after_its_graph_is_gone(mods):
                 res.wait()
             assert e.value.code == bms.ERANGE and "30000" in str(e.value)
         csr = bms.Csr(rp, cl)
+
+
+def test_work_on_a_stream_that_is_not_current(mods):
+    # the copy of a strided batch and the output buffers belong to the call's stream: the current one is busy, and what it frees is
+    # still in use
+    O, bms = mods
+    rng = np.random.default_rng(85)
+    rowptr, col = random_csr(20000, 14.0, rng)
+    seeds = random_batches(20000, 6, 400, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    wide = torch.full((6, 800), 1, dtype=torch.int32, device="cuda")
+    wide[:, ::2] = torch.from_numpy(seeds).cuda()
+    H = torch.randn((20000, 16), device="cuda")
+    ref = O.sample_nodewise(rowptr, col, seeds, (6, 5), 3)
+    side = torch.cuda.Stream()
+    res, allocator = None, bms.TorchAllocator()
+    for call in range(3):
+        torch.cuda.synchronize()
+        wanted = H[torch.from_numpy(ref[1].col_vertex).cuda().long()]
+        torch.cuda.synchronize()
+        old = torch.full(wanted.shape, float(call), device="cuda")
+        torch.cuda._sleep(40_000_000)
+        kept = old + 0.0     # reads `old` when the sleep is over
+        del old
+        res = bms.sample_nodewise(csr, wide[:, ::2], (6, 5), 3, stream=side.cuda_stream, recycle=res, allocator=allocator)
+        out = bms.fetch_features(H, res.hop(1).col_vertex, stream=side.cuda_stream)
+        torch.cuda.synchronize()
+        assert_hops_equal(res.hops(), ref, what="strided seeds on a side stream, call %d" % call)
+        assert torch.equal(out, wanted) and bool((kept == call).all())
