@@ -62,6 +62,11 @@ int fail(int code, const char *fmt, ...)
             return rc_;                                                                                                \
     } while (0)
 
+// Ends a function that is a try block: host memory that runs out is an error code like any other, not an exception through C.
+#define BMS_CATCH                                                                                                      \
+    catch (const std::bad_alloc &) { return fail(BMS_ENOMEM, "host allocation failed"); }                              \
+    catch (...) { return fail(BMS_EHIP, "unexpected exception"); }
+
 // Where a result's buffers come from (bms_opts.alloc / dealloc / alloc_ctx); both null = hipMalloc / hipFree
 struct Allocator {
     void *(*alloc)(size_t, void *) = nullptr;
@@ -456,7 +461,7 @@ int setup_vset(CallCtx &c)
 int settle_result(bms_result *res);
 
 int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64_t seed, const bms_opts *opts)
-{
+try {
     c.csr = csr;
     c.k = k;
     c.b = b;
@@ -519,6 +524,7 @@ int begin_call(CallCtx &c, bms_csr *csr, int32_t k, int32_t b, int32_t L, uint64
     BMS_TRY(csr->scalars.ensure(64 * sizeof(int64_t)));
     return BMS_OK;
 }
+BMS_CATCH
 
 int abort_call(CallCtx &c, int rc)
 {
@@ -1314,7 +1320,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
 }
 
 int sample_nodewise_impl(CallCtx &c, const int32_t *batches, const int32_t *fanouts)
-{
+try {
     // hops that gave up on a kernel path in an earlier call of this shape start with the path that worked then
     std::vector<uint8_t> mode((size_t)c.L, 0);
     if (!c.fresh_result && c.res->hint_csr == c.csr->serial && c.res->hint_shape == nodewise_shape(c, fanouts) &&
@@ -1334,6 +1340,7 @@ int sample_nodewise_impl(CallCtx &c, const int32_t *batches, const int32_t *fano
     }
     return fail(BMS_EHIP, "EXTRACT did not settle on a kernel path");
 }
+BMS_CATCH
 
 // LADIES with the column counts of P accumulated in LDS, one window of 2^16 vertex ids at a time.
 bool ladies_windows_apply(const CallCtx &c, const int32_t *s_per_layer)
@@ -1682,7 +1689,7 @@ int sample_ladies_windows_impl(CallCtx &c, const int32_t *batches, const int32_t
 }
 
 int sample_ladies_impl(CallCtx &c, const int32_t *batches, const int32_t *s_per_layer)
-{
+try {
     if (ladies_windows_apply(c, s_per_layer))
         return sample_ladies_windows_impl(c, batches, s_per_layer);
     bms_csr *csr = c.csr;
@@ -1831,13 +1838,14 @@ int sample_ladies_impl(CallCtx &c, const int32_t *batches, const int32_t *s_per_
     csr->ld_clean = true;
     return BMS_OK;
 }
+BMS_CATCH
 
 } // namespace
 
 extern "C" {
 
 int bms_csr_load(const int64_t *rowptr, const int32_t *col, int64_t n, int64_t nnz, int location, bms_csr **out)
-{
+try {
     if (!rowptr || !out || (!col && nnz > 0))
         return fail(BMS_EINVAL, "null argument");
     if (n < 0 || nnz < 0 || n > 0x7FFFFFFFLL)
@@ -1906,6 +1914,7 @@ int bms_csr_load(const int64_t *rowptr, const int32_t *col, int64_t n, int64_t n
     *out = c;
     return BMS_OK;
 }
+BMS_CATCH
 
 int bms_csr_info(const bms_csr *csr, int64_t *n, int64_t *nnz, int64_t *max_degree)
 {
@@ -1977,11 +1986,12 @@ int bms_sample_ladies(bms_csr *csr, const int32_t *batches, int32_t k, int32_t b
 }
 
 int bms_result_wait(bms_result *res)
-{
+try {
     if (!res || res->tag != kTagResult)
         return fail(BMS_EINVAL, "not a result handle");
     return settle_result(res);
 }
+BMS_CATCH
 
 int bms_result_ready(const bms_result *res)
 {
@@ -1998,16 +2008,17 @@ int bms_result_ready(const bms_result *res)
 }
 
 int bms_result_attempts(const bms_result *res, int32_t *attempts)
-{
+try {
     if (!res || res->tag != kTagResult || !attempts)
         return fail(BMS_EINVAL, "not a result handle, or no place for the answer");
     BMS_TRY(settle_result(const_cast<bms_result *>(res)));
     *attempts = res->attempts;
     return BMS_OK;
 }
+BMS_CATCH
 
 int bms_result_info(const bms_result *res, int32_t *k, int32_t *L)
-{
+try {
     if (!res || res->tag != kTagResult)
         return fail(BMS_EINVAL, "not a result handle");
     BMS_TRY(settle_result(const_cast<bms_result *>(res)));
@@ -2017,9 +2028,10 @@ int bms_result_info(const bms_result *res, int32_t *k, int32_t *L)
         *L = res->L;
     return BMS_OK;
 }
+BMS_CATCH
 
 int bms_result_hop(const bms_result *res, int32_t hop, bms_hop_view *view)
-{
+try {
     if (!res || res->tag != kTagResult || !view)
         return fail(BMS_EINVAL, "not a result handle, or null view");
     BMS_TRY(settle_result(const_cast<bms_result *>(res)));
@@ -2028,9 +2040,10 @@ int bms_result_hop(const bms_result *res, int32_t hop, bms_hop_view *view)
     *view = res->hops[hop].view;
     return BMS_OK;
 }
+BMS_CATCH
 
 int bms_result_minibatch(bms_result *res, int32_t hop, int32_t i, bms_mb_view *view)
-{
+try {
     if (!res || res->tag != kTagResult || !view)
         return fail(BMS_EINVAL, "not a result handle, or null view");
     BMS_TRY(settle_result(res));
@@ -2070,10 +2083,11 @@ int bms_result_minibatch(bms_result *res, int32_t hop, int32_t i, bms_mb_view *v
     *view = m;
     return BMS_OK;
 }
+BMS_CATCH
 
 int bms_result_minibatch_offsets(const bms_result *res, int32_t hop, int64_t *row_off, int64_t *edge_off,
                                  int64_t *col_off, void *stream)
-{
+try {
     if (!res || res->tag != kTagResult || !row_off || !edge_off || !col_off)
         return fail(BMS_EINVAL, "not a result handle, or null output array");
     BMS_TRY(settle_result(const_cast<bms_result *>(res)));
@@ -2100,9 +2114,10 @@ int bms_result_minibatch_offsets(const bms_result *res, int32_t hop, int64_t *ro
     HIP_TRY(hipStreamSynchronize(st));
     return BMS_OK;
 }
+BMS_CATCH
 
 int bms_result_stage(const bms_result *res, int32_t idx, const char **name, int32_t *hop, float *ms)
-{
+try {
     if (!res || res->tag != kTagResult)
         return fail(BMS_EINVAL, "not a result handle");
     BMS_TRY(settle_result(const_cast<bms_result *>(res)));
@@ -2117,6 +2132,7 @@ int bms_result_stage(const bms_result *res, int32_t idx, const char **name, int3
         *ms = st.ms;
     return BMS_OK;
 }
+BMS_CATCH
 
 void bms_free(void *handle)
 {
@@ -2187,7 +2203,7 @@ int bms_fetch_features(const float *H, int64_t n, int32_t f, const int32_t *ids,
 }
 
 int bms_aggregate_hop(const bms_result *res, int32_t hop, const float *X, int32_t f, int mean, float *out, void *stream)
-{
+try {
     if (!res || res->tag != kTagResult)
         return fail(BMS_EINVAL, "not a result handle");
     BMS_TRY(settle_result(const_cast<bms_result *>(res)));
@@ -2219,6 +2235,7 @@ int bms_aggregate_hop(const bms_result *res, int32_t hop, const float *X, int32_
     HIP_TRY(hipGetLastError());
     return BMS_OK;
 }
+BMS_CATCH
 
 const char *bms_strerror(int code)
 {

@@ -94,3 +94,13 @@ def test_probe_library_exports_its_two_entry_points():
     P.bms_probe_random_rows.restype = ctypes.c_int
     assert P.bms_probe_random_rows(None, 0, None, 0, 3, 0, None, None) == -1
     assert P.bms_probe_lds_ops(None, 0, 0, 5, 0, None) == -1
+
+
+def test_no_exception_leaves_the_library_when_host_memory_runs_out(tmp_path):
+    import subprocess
+    exe = str(tmp_path / "no_host_memory")
+    here = os.path.dirname(bms.LIB_PATH)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "include"), "-o", exe,
+                           os.path.join(ROOT, "tests", "host", "no_host_memory.cpp"), "-L", here, "-l:libbms.so", "-Wl,-rpath," + here])
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0, run.stdout + run.stderr
