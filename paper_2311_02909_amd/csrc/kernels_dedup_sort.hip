@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int64_t nseg = (int64_t)a.k * a.C;
     // The ids of the segment after this one are fetched while this one is ranked (a workgroup's segments follow one
-    // another as chains of dependent steps, and only two workgroups fit a compute unit).
+    // another as chains of dependent steps, and only three workgroups fit a compute unit).
     // where segment w lies: first slot, ids, where its minibatch's ids start
     auto where = [&](int64_t w, uint32_t &s0, uint32_t &m, int64_t &e0) {
         s0 = m = 0;

@@ -1,9 +1,9 @@
 // Node-wise hops small enough for one workgroup per minibatch, Sec. 4.1 of arxiv 2311.02909: a whole hop -- P = Q A,
 // SAMPLE, EXTRACT -- and every following hop that still fits, in one launch for all minibatches.
 //
-// What bounds these hops is not memory but the chain: the chip-wide path takes about 15 launches per hop, each of
-// which costs its launch (2.4 us of host time, about 4 us of device time) however little it moves.  Here a minibatch's
-// sampled ids never leave LDS:
+// What bounds these hops is not memory but the chain: the chip-wide path takes 6 to 10 launches per hop, each of which costs its
+// launch (2.4 us of host time, about 4 us of device time) however little it moves.  Here a minibatch's sampled ids never leave
+// LDS:
 //   seeds    checked against an LDS hash table (range, repeats), copied to the first frontier
 //   sample   one row per lane: extent, draws, the chosen neighbours gathered into LDS
 //   sort     the positions by id: through 16384 buckets of about one id each, or, when the ids crowd some of them, by
@@ -13,9 +13,14 @@
 //            minibatches before it.  Every workgroup publishes its hop's sizes in one word and adds up the words before
 //            its own.  A workgroup takes its minibatch off a counter when it starts, so the ones it waits for have
 //            started earlier and wait for nobody after them: every wait ends, whatever else runs on the chip.
-// Measured: a call of 4 minibatches of 64 with fanouts (5, 5) 142 -> 45 us (44 launches -> 1); the first hop of b = 1024,
-// s = 15 (15 k edges per minibatch, the largest this kernel takes) one launch of 45 us for 1 to 256 minibatches, where the
-// chip-wide path takes 17 launches and about 110 us.
+// Measured on 2.4 M vertices, one hop per call, s = 16, whole calls: k minibatches of b seeds here and by the chip-wide path
+//   k     b = 64     b = 256    b = 512    b = 1000 (11 k entries per minibatch)
+//   1     26, 42     28, 50     34, 50     46, 51 us
+//   4     26, 51     28, 61     34, 63     48, 63
+//   16    25, 67     29, 81     35, 74     48, 76
+//   64    27, 68     31, 84     37, 78     52, 85
+//   256   37, 80     45, 96     54, 98     73, 123
+// so it takes every hop that fits its LDS (kSmallCap), whatever the number of minibatches; two hops (5, 5) of 4 x 64: 57 us.
 #include "bms_device.h"
 #include "bms_internal.h"
 #include "nw_draws.h"
