@@ -33,36 +33,37 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 3_301_639_264,
-    ("dense_ladies", "ldw_extract"): 2_618_182_368,
-    ("dense_sage", "nw_sample"): 9_827_472_672,
-    ("dense_sage", "dd_rank"): 1_790_340_928,
-    ("dense_sage", "nw_rows"): 1_379_019_648,
-    ("dense_sage", "dd_split"): 1_140_845_152,
-    ("dense_sage", "dd_unsplit"): 1_008_368_096,
-    ("dense_sage", "dd_front"): 617_262_528,
-    ("large_sage", "nw_sample"): 5_063_255_520,
-    ("large_sage", "nw_rows"): 1_648_596_000,
-    ("large_sage", "dd_split"): 753_540_960,
-    ("large_sage", "dd_unsplit"): 687_598_624,
-    ("large_sage", "dd_rank"): 599_026_592,
-    ("large_sage", "dd_front"): 473_494_816,
-    ("mid_ladies", "ldw_extract"): 183_568_256,
-    ("mid_ladies", "ldw_accumulate"): 148_762_688,
-    ("mid_sage", "nw_sample"): 2_618_566_528,
-    ("mid_sage", "dd_rank"): 574_085_888,
-    ("mid_sage", "dd_split"): 426_436_736,
-    ("mid_sage", "dd_unsplit"): 367_494_240,
-    ("mid_sage", "nw_rows"): 352_057_472,
-    ("mid_sage", "dd_front"): 204_140_000,
+    ("dense_ladies", "ldw_accumulate"): 3_314_966_720,
+    ("dense_ladies", "ldw_p_copy"): 3_143_346_976,
+    ("dense_ladies", "ldw_extract"): 2_022_134_848,
+    ("dense_sage", "nw_sample"): 9_763_640_864,
+    ("dense_sage", "nw_rows"): 1_355_784_128,
+    ("dense_sage", "dd_split"): 1_121_184_672,
+    ("dense_sage", "dd_unsplit"): 991_191_232,
+    ("dense_sage", "dd_rank"): 845_958_336,
+    ("dense_sage", "dd_front"): 603_921_568,
+    ("large_sage", "nw_sample"): 5_021_632_416,
+    ("large_sage", "nw_rows"): 1_607_832_576,
+    ("large_sage", "dd_split"): 740_146_848,
+    ("large_sage", "dd_unsplit"): 676_007_648,
+    ("large_sage", "dd_rank"): 587_625_664,
+    ("large_sage", "dd_front"): 464_219_072,
+    ("mid_ladies", "ldw_p_copy"): 172_208_800,
+    ("mid_ladies", "ldw_accumulate"): 150_433_568,
+    ("mid_ladies", "ldw_extract"): 85_108_928,
+    ("mid_sage", "nw_sample"): 2_607_554_240,
+    ("mid_sage", "nw_rows"): 342_199_840,
+    ("mid_sage", "rg_lookup"): 329_944_928,
+    ("mid_sage", "rg_mark"): 190_089_152,
+    ("mid_sage", "rg_emit"): 147_362_912,
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 9_880_152_832,
-    "dense_sage": 15_766_869_696,
-    "large_sage": 9_229_908_640,
-    "mid_ladies": 562_838_592,
-    "mid_sage": 4_544_347_968,
+    "dense_ladies": 9_286_762_752,
+    "dense_sage": 14_776_709_536,
+    "large_sage": 9_185_574_016,
+    "mid_ladies": 464_460_416,
+    "mid_sage": 3_651_671_040,
 }
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 
