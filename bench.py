@@ -135,7 +135,7 @@ def main() -> int:
     ap.add_argument("--relabel", default=None, choices=["degree"],
                     help="renumber the graph's vertices by descending degree (hubs first) instead of the recipe's random ids")
     ap.add_argument("--others", default="auto", choices=["auto", "yes", "no"],
-                    help="also run the other workloads of the build's configs (fewer steps) and report them under "
+                    help="also run the other five workloads (fewer steps) and report them under "
                          "other_workloads; auto = only with the default workload")
     ap.add_argument("--copy-probe", type=int, default=0, metavar="MIB",
                     help="instead of the benchmark, run a plain device copy of MIB mebibytes 5 times "
@@ -245,7 +245,7 @@ def main() -> int:
                        fetch=not args.no_feature_fetch, relabel=args.relabel)
     if out is None:
         return 2
-    # the other workloads of the build's configs, each with its own dominant kernel, roofline and oracle time
+    # the other workloads, each with its own dominant kernel, roofline and oracle time
     # (fewer steps; not part of `value`)
     if args.others == "yes" or (args.others == "auto" and args.workload == "large_sage" and args.variant == "none" and not args.relabel):
         others = {}

@@ -355,7 +355,8 @@ def _profile_flag(profile) -> int:
 def _on(stream):
     """The raw stream as torch's current one: what is allocated or copied for work on it (a contiguous copy of the
     inputs, outputs, the buffers of a TorchAllocator) is ordered with that work, and its memory is not reused before."""
-    return torch.cuda.stream(torch.cuda.ExternalStream(int(stream)))
+    # (torch takes a null pointer for a request of a stream from its pool)
+    return torch.cuda.stream(torch.cuda.ExternalStream(int(stream)) if int(stream) else torch.cuda.default_stream())
 
 
 def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, mb_base, stream, recycle, flags,

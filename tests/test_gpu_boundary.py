@@ -222,7 +222,8 @@ def test_asynchronous_result_looked_at_after_its_graph_is_gone(mods):
         csr = bms.Csr(rp, cl)
 
 
-def test_work_on_a_stream_that_is_not_current(mods):
+@pytest.mark.parametrize("given", ["side", "null"])
+def test_work_on_a_stream_that_is_not_current(mods, given):
     # the copy of a strided batch and the output buffers belong to the call's stream: the current one is busy, and what it frees is
     # still in use
     O, bms = mods
@@ -235,17 +236,20 @@ def test_work_on_a_stream_that_is_not_current(mods):
     H = torch.randn((20000, 16), device="cuda")
     ref = O.sample_nodewise(rowptr, col, seeds, (6, 5), 3)
     side = torch.cuda.Stream()
+    stream, current = (side.cuda_stream, torch.cuda.default_stream()) if given == "side" else (0, side)
     res, allocator = None, bms.TorchAllocator()
-    for call in range(3):
-        torch.cuda.synchronize()
-        wanted = H[torch.from_numpy(ref[1].col_vertex).cuda().long()]
-        torch.cuda.synchronize()
-        old = torch.full(wanted.shape, float(call), device="cuda")
-        torch.cuda._sleep(40_000_000)
-        kept = old + 0.0     # reads `old` when the sleep is over
-        del old
-        res = bms.sample_nodewise(csr, wide[:, ::2], (6, 5), 3, stream=side.cuda_stream, recycle=res, allocator=allocator)
-        out = bms.fetch_features(H, res.hop(1).col_vertex, stream=side.cuda_stream)
-        torch.cuda.synchronize()
-        assert_hops_equal(res.hops(), ref, what="strided seeds on a side stream, call %d" % call)
-        assert torch.equal(out, wanted) and bool((kept == call).all())
+    torch.cuda.synchronize()
+    with torch.cuda.stream(current):
+        for call in range(3):
+            torch.cuda.synchronize()
+            wanted = H[torch.from_numpy(ref[1].col_vertex).cuda().long()]
+            torch.cuda.synchronize()
+            old = torch.full(wanted.shape, float(call), device="cuda")
+            torch.cuda._sleep(40_000_000)
+            kept = old + 0.0     # reads `old` when the sleep is over
+            del old
+            res = bms.sample_nodewise(csr, wide[:, ::2], (6, 5), 3, stream=stream, recycle=res, allocator=allocator)
+            out = bms.fetch_features(H, res.hop(1).col_vertex, stream=stream)
+            torch.cuda.synchronize()
+            assert_hops_equal(res.hops(), ref, what="strided seeds on a side stream, call %d" % call)
+            assert torch.equal(out, wanted) and bool((kept == call).all())

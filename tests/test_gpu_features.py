@@ -95,3 +95,37 @@ def test_large_fetches_of_stacked_runs(mods, lengths):
     with pytest.raises(bms.BmsError):
         bms.fetch_features(Hd, torch.from_numpy(ids).cuda(), out=out)
     assert not out[7].any() and not out[ids.size // 2].any() and torch.equal(out[8], Hd[int(ids[8])])
+
+
+@pytest.mark.parametrize("order", ["400 runs", "520 runs", "one in a hundred", "half a run", "descending", "shuffled", "negative and beyond"])
+def test_large_fetches_of_ids_in_other_orders(mods, order):
+    # every row is in one tile, whatever passes for runs
+    O, bms = mods
+    rng = np.random.default_rng(len(order))
+    n, f, m = 400_000, 67, 450_000
+    k = {"400 runs": 400, "520 runs": 520}.get(order, 30)
+    ids = np.sort(rng.integers(0, n, size=(k, m // k)), axis=1).astype(np.int32)
+    if order == "half a run":
+        ids[3, :m // k // 2] = rng.permutation(ids[3, :m // k // 2])
+        ids[0] = rng.permutation(ids[0])
+    ids = ids.reshape(-1)
+    if order == "one in a hundred":
+        at = rng.random(ids.size) < 0.01
+        ids[at] = rng.integers(0, n, size=int(at.sum()))
+    elif order == "descending":
+        ids = np.sort(ids)[::-1].copy()
+    elif order == "shuffled":
+        ids = rng.permutation(ids)
+    elif order == "negative and beyond":
+        ids[::1000], ids[1::1000] = -2**31, 2**31 - 1
+    assert ids.size * f * 4 >= 100 << 20
+    H = torch.randn((n, f), device="cuda")
+    dev = torch.from_numpy(ids).cuda()
+    out = torch.full((ids.size, f), 7.0, device="cuda")
+    if order == "negative and beyond":
+        with pytest.raises(bms.BmsError):
+            bms.fetch_features(H, dev, out=out)
+    else:
+        bms.fetch_features(H, dev, out=out)
+    good = (dev >= 0) & (dev < n)
+    assert torch.equal(out, torch.where(good[:, None], H[dev.clamp(0, n - 1).long()], torch.zeros((), device="cuda")))
