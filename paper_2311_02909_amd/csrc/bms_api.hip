@@ -1421,7 +1421,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     const int64_t n1 = std::max<int64_t>(csr->n, 1);
     const int32_t nwin = (int32_t)((n1 + (1LL << kWinShift) - 1) >> kWinShift);
     const size_t nw = (size_t)c.k * nwin;
-    BMS_TRY(csr->lw_win.ensure(nw * (2 * sizeof(uint32_t) + 3 * sizeof(int64_t)) + 64));
+    BMS_TRY(csr->lw_win.ensure(nw * (sizeof(uint32_t) + 3 * sizeof(int64_t)) + 64));
     BMS_TRY(csr->lw_parts.ensure(nw * kWinParts * (2 * sizeof(uint32_t) + 3 * sizeof(uint64_t))));
     BMS_TRY(csr->lw_count.ensure(((3 + kQueueStride) * ((size_t)c.k + 1) + 16) * sizeof(int64_t)));
     if (!csr->lw_index_tried && !(c.flags & BMS_LADIES_NO_INDEX))
@@ -1498,7 +1498,6 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.win_woff = w.win_wt + nw;
         w.win_poff = reinterpret_cast<int64_t *>(w.win_woff + nw);
         w.win_cnt = reinterpret_cast<uint32_t *>(w.win_poff + nw);
-        w.win_added = w.win_cnt + nw;
         w.done = csr->sm_ticket.as<uint32_t>() + 3;
         w.part_woff = csr->lw_parts.as<uint64_t>();
         w.part_wt = w.part_woff + nw * kWinParts;
@@ -1526,7 +1525,6 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
             lookback_used(c, workgroups);
         } else { // too many rows for that
             launch_ld_rows(c.launch, a, slot(c, h, 3));
-            launch_ldw_zero_added(c.launch, w);
         }
         BMS_TRY(prof.end());
         int64_t D; // gathered neighbours: sizes the staging of P and of the kept neighbours
@@ -1540,8 +1538,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         }
         w.giveup = giveup;
         w.gathered_cap = D;
-        // every part of a window claims room for as many columns as it has ids, or as the window has neighbours
-        const int64_t tmp_cap = std::max<int64_t>(std::min<int64_t>(kWinParts * D, (int64_t)nw << kWinShift), 1);
+        const int64_t tmp_cap = std::max<int64_t>(std::min<int64_t>(D, (int64_t)c.k * n1), 1); // entries of P
         const size_t tbytes = (size_t)tmp_cap * 4 + (size_t)std::max<int64_t>(D, 1) * 4;
         if (no_wait && (int64_t)(tbytes + blists * bbytes) > c.scratch_limit) {
             *redo = true; // the margin does not fit the limit; the exact sizes may

@@ -163,6 +163,20 @@ __device__ inline int64_t scalar(int64_t x)
     return (int64_t)((uint64_t)scalar((uint32_t)((uint64_t)x >> 32)) << 32 | scalar((uint32_t)x));
 }
 
+// A value read at an address that is the same in all lanes, of an array that nothing writes during the launch: through the
+// scalar unit, which the compiler does not choose by itself when the kernel writes to other arrays.
+template <class T>
+__device__ inline T uniform_load(const T *p)
+{
+    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+
+// Bits of `mask` below the lane's own, without a mask of them in registers
+__device__ inline uint32_t bits_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
 // A workgroup's number in its launch, in the order of starting: whoever waits for lower numbers waits for workgroups that
 // have started.  smem: one word of LDS.
 __device__ inline uint32_t take_number(const Lookback &lb, uint32_t *smem)

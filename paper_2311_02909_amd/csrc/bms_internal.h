@@ -357,7 +357,6 @@ struct LwHop {
     uint32_t *bounds;          // rows_bound * (nwin+1), one list per row
     const uint32_t *index;     // n * (nwin+1): the list of every vertex's whole row, built once per graph; or null
     uint32_t *bounds_t;        // (nwin+1) * rows_bound, the same window-major
-    uint32_t *win_added;       // k * nwin: neighbours of the minibatch's rows inside the window
     uint32_t *win_cnt;         // k * nwin: columns of P inside the window
     uint64_t *win_wt;          // k * nwin: their weight
     int64_t *win_poff;         // k * nwin: columns of the minibatch before the window
@@ -391,7 +390,6 @@ struct LwHop {
 struct Lookback; // bms_device.h
 // the launches with a Lookback: at most kMostLookback workgroups, else -1 (nothing launched); *workgroups: how many
 int launch_ldw_rows(const Launch &, const LwHop &, const Lookback &, int64_t *gathered_out, uint32_t *workgroups);
-void launch_ldw_zero_added(const Launch &, const LwHop &); // win_added = 0 (launch_ldw_rows does it as well)
 void launch_ldw_bounds(const Launch &, const LwHop &); // with an index: the rows' lists are copied from it
 void launch_ldw_index(const Launch &, const LwHop &);  // boundary lists of the rows of a hop that is the whole graph
 int launch_ldw_accumulate(const Launch &, const LwHop &, int64_t *pnnz_out); // also scans the windows, p_off; -1: launch refused

@@ -12,13 +12,12 @@
 //                   depends on its vertex alone: when the lists of all n vertices fit in memory they are computed
 //                   once per graph (one wave per tile streams its pieces of rows, the "hop" being the whole
 //                   graph) and a hop only copies the lists of its rows; else the hop streams its rows for them.
-//                   Either way the lists are turned window-major for the next kernel, and the neighbours of every
-//                   (minibatch, window), the lengths of its pieces, are added up (with the index and k < 1024 plan, tile
-//                   rows and this are one launch, ldw_plan_bounds)
+//                   Either way the lists are turned window-major for the next kernel (with the index and k < 1024 plan,
+//                   tile rows and this are one launch, ldw_plan_bounds)
 //   ldw_accumulate  one workgroup per (minibatch, window): 2^16 packed 16-bit counters in LDS (128 KB); every
 //                   row's piece of the window adds 1 per neighbour (e_v cannot exceed the number of frontier
-//                   rows, which this path keeps below 2^16); each wave then compacts its sixteenth of the window
-//                   (a part): the nonzero counters leave in ascending column order as 4-byte entries
+//                   rows, which this path keeps below 2^16); each wave then takes its sixteenth of the window
+//                   (a part) out: the nonzero counters leave in ascending column order as 4-byte entries
 //                   (column - window start, e_v) into room claimed from a device-wide cursor
 //   ldw_win_scan    per minibatch: columns and weight of every window, before each of its parts, before the window
 //   ldw_p_copy      parts copied to their place in P, one wave per part; inclusive prefix sums of the integer
@@ -50,11 +49,25 @@ constexpr int kWaveWords = kWinWords / kAccWaves; // counter words compacted by 
 constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;
 constexpr int kExtThreads = 1024; // the waves of a workgroup share one hash table
 constexpr int kExtWaves = kExtThreads / kWave;
-constexpr int kAccUnroll = 8;              // 16-byte loads per lane in flight while a wave gathers
+constexpr int kAccUnroll = 8;              // 16-byte loads per lane and span
 constexpr int kAccChunks = kWave * kAccUnroll; // aligned 16-byte chunks per span: one per lane and load
-struct AccPiece {                          // one nonempty piece of a wave's 64 rows
-    int64_t origin;                        // byte address of its first line - 128 * lines of the wave before it
+constexpr int kAccFlush = 4;               // entries per lane on their way out at a time
+constexpr int kAccListed = 896;            // counters in use that a wave lists in LDS at a time
+struct AccPiece {                          // one nonempty piece of a wave's rows
+    int64_t origin;                        // byte address of its first chunk - 16 * chunks of the batch before it
     uint32_t lo_rel, hi_rel;               // its bytes, relative to origin
+};
+struct AccWave {
+    union { // in turn
+        AccPiece piece[kWave];     // one record per nonempty piece of a batch, by rank
+        uint16_t list[kAccListed];
+    };
+    uint32_t starts[2 * kAccUnroll]; // a bit per chunk of a span: a piece starts there
+};
+struct AccShared {
+    AccWave wave[kAccWaves];
+    unsigned long long claimed; // where the pair's entries start in the staging array
+    uint32_t cnt[kAccWaves];    // columns in the waves' parts
 };
 constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
 constexpr int kStreamUnroll = 8; // neighbours per lane in flight in the two streaming passes
@@ -66,7 +79,7 @@ __device__ inline uint64_t ldw_weight(uint32_t cnt, int squared)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rows: extents, the gathered order (exclusive scan of the degrees), 256 rows per workgroup; win_added cleared
+// Rows: extents, the gathered order (exclusive scan of the degrees), 256 rows per workgroup
 // ---------------------------------------------------------------------------------------------
 constexpr int kLwRows = 256;
 __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb, int64_t *gathered_out)
@@ -75,8 +88,6 @@ __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb,
     __shared__ uint32_t number_s;
     const int tid = threadIdx.x;
     const uint32_t t = take_number(lb, &number_s);
-    for (int64_t x = (int64_t)t * kLwRows + tid; x < (int64_t)a.k * a.nwin; x += (int64_t)gridDim.x * kLwRows)
-        a.win_added[x] = 0;
     const int64_t R = a.mb_rowoff[a.k];
     if (t > 0 && (int64_t)t * kLwRows >= R)
         return; // nobody with rows comes after
@@ -103,12 +114,6 @@ __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb,
         a.out_rowptr[R] = 0;
         *gathered_out = before + total;
     }
-}
-
-__global__ __launch_bounds__(256) void ldw_zero_added_kernel(LwHop a)
-{
-    for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < (int64_t)a.k * a.nwin; x += (int64_t)gridDim.x * 256)
-        a.win_added[x] = 0;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -254,19 +259,17 @@ __global__ __launch_bounds__(256) void ldw_bounds_kernel(LwHop a)
 }
 
 // The boundary lists turned window-major (bounds_t[w * rows_bound + r]): the accumulation reads one window of
-// all rows at a time.  64 rows x 63 windows at a time through LDS, both sides coalesced.  The list of row r comes from this
+// all rows at a time.  64 rows x 64 windows at a time through LDS, both sides coalesced.  The list of row r comes from this
 // hop's boundary pass, or, when the graph carries an index of every vertex's list, from the index entry of
-// the row's vertex.  On the way: win_added[i * nwin + w] += neighbours of minibatch i's rows inside window w (the lengths of
-// their pieces).  Workgroup x of nx.
-constexpr int kBtWindows = 63;
-__device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65], int32_t (&mb_l)[64], int64_t x, int64_t nx)
+// the row's vertex (all zeros for vertices without neighbours, and so here for their rows).  Workgroup x of nx.
+__device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65], int64_t x, int64_t nx)
 {
     const int64_t ncols = a.nwin + 1;
     const int64_t nrows = a.mb_rowoff[a.k];
-    const int64_t tiles_c = (a.nwin + kBtWindows - 1) / kBtWindows, tiles_r = (nrows + 63) / 64;
+    const int64_t tiles_c = (ncols + 63) / 64, tiles_r = (nrows + 63) / 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int64_t t = x; t < tiles_c * tiles_r; t += nx) {
-        const int64_t r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * kBtWindows;
+        const int64_t r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * 64;
         if (a.index) { // the rows' vertices first, then all of a thread's 16 reads of the index in flight together
             int64_t v[16];
 #pragma unroll
@@ -280,37 +283,14 @@ __device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65]
             for (int q = 0; q < 16; ++q)
                 tile[ty + 4 * q][tx] = y[q];
         } else {
-            for (int y = ty; y < 64; y += 4)
+            for (int y = ty; y < 64; y += 4) // (a row without neighbours has no boundaries on record)
                 if (r0 + y < nrows && c0 + tx < ncols)
-                    tile[y][tx] = a.bounds[(r0 + y) * ncols + c0 + tx];
-        }
-        if (ty == 0) { // minibatch of the row; -1: no neighbours (its boundaries may not be on record)
-            const int64_t r = r0 + tx;
-            mb_l[tx] = r < nrows && a.gather_off[r + 1] != a.gather_off[r] ? a.row_mb[r] : -1;
+                    tile[y][tx] = a.gather_off[r0 + y + 1] != a.gather_off[r0 + y] ? a.bounds[(r0 + y) * ncols + c0 + tx] : 0u;
         }
         __syncthreads();
         for (int y = ty; y < 64; y += 4)
-            if (c0 + y < ncols && (y < kBtWindows || c0 + y == a.nwin) && r0 + tx < nrows)
+            if (c0 + y < ncols && r0 + tx < nrows)
                 a.bounds_t[(c0 + y) * a.rows_bound + r0 + tx] = tile[tx][y];
-        if (tx < kBtWindows && c0 + tx < a.nwin) {
-            uint32_t sum = 0; // < 2^32: at most 65535 rows with at most 2^16 neighbours in a window each
-            int mb = -1;
-#pragma unroll 4
-            for (int q = 0; q < 16; ++q) {
-                const int row = ty * 16 + q, i = mb_l[row]; // the same in all lanes
-                if (i < 0)
-                    continue;
-                if (i != mb) {
-                    if (sum)
-                        atomicAdd(&a.win_added[(int64_t)mb * a.nwin + c0 + tx], sum);
-                    sum = 0;
-                    mb = i;
-                }
-                sum += tile[row][tx + 1] - tile[row][tx];
-            }
-            if (sum)
-                atomicAdd(&a.win_added[(int64_t)mb * a.nwin + c0 + tx], sum);
-        }
         __syncthreads();
     }
 }
@@ -318,10 +298,9 @@ __device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65]
 __global__ __launch_bounds__(256) void ldw_bounds_transpose_kernel(LwHop a)
 {
     __shared__ uint32_t tile[64][65];
-    __shared__ int32_t mb_l[64];
     if (a.giveup && *a.giveup)
         return;
-    transpose_bounds(a, tile, mb_l, blockIdx.x, gridDim.x);
+    transpose_bounds(a, tile, blockIdx.x, gridDim.x);
 }
 
 // Plan, tile rows and the transposed lists in one launch, when the lists come from the index and k < kPlanMb: the first
@@ -331,10 +310,7 @@ constexpr int kPlanMb = 1024;
 __global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int planners)
 {
     __shared__ union {
-        struct {
-            uint32_t tile[64][65];
-            int32_t mb_l[64];
-        } t;
+        uint32_t tile[64][65];
         struct {
             int64_t goff[kPlanMb], tileoff[kPlanMb];
         } p;
@@ -347,7 +323,7 @@ __global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int plann
     if (up_s)
         return;
     if ((int)blockIdx.x >= planners) {
-        transpose_bounds(a, u.t.tile, u.t.mb_l, (int64_t)blockIdx.x - planners, (int64_t)gridDim.x - planners);
+        transpose_bounds(a, u.tile, (int64_t)blockIdx.x - planners, (int64_t)gridDim.x - planners);
         return;
     }
     const int tid = threadIdx.x;
@@ -397,219 +373,304 @@ __global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int plann
 }
 
 // ---------------------------------------------------------------------------------------------
-// P = Q A for one (minibatch, window) per workgroup
+// P = Q A, one (minibatch, window) pair per workgroup at a time
 // ---------------------------------------------------------------------------------------------
+// both 16-bit halves, each min(half, 1)
+__device__ inline uint32_t at_most_one(uint32_t x)
+{
+    using Halves = uint16_t __attribute__((ext_vector_type(2)));
+    union {
+        uint32_t whole;
+        Halves halves;
+    } v{x};
+    const Halves one = {1, 1};
+    v.halves = __builtin_elementwise_min(v.halves, one);
+    return v.whole;
+}
+
+// A compute unit holds one workgroup (the counters fill its LDS), so nothing but its own waves hides what they wait for, and
+// all of them are in the same phase:
+//   gather   a pair's first span of chunks is asked for while the counters of the pair before it leave
+//   count    64 consecutive counters per lane: a bit for each that is in use, columns and weight of the wave's part
+//   write    a lane lists its counters in use, in column order, in LDS; the entries leave 64 to a store, into room claimed for
+//            exactly as many (the claim is on its way while the lists are made)
+// Bound by the lines of the pieces, which arrive in bursts (dense: 9 of 18 us per pair for 2900 of them), then by vector
+// instructions.  Few rows lie in half waves, so that all waves have some.  Weights e_v and e_v^2 are kernels of their own: decided
+// inside, at every word, the branch kept the LDS reads from overlapping.  Three layers of 32 x 512 seeds, 512 samples, 2.4 M
+// vertices: 171 -> 127 us (and 55 -> 44 in the copy of P, as parts lie one after the other); 64 x 1024 seeds, 2048 samples,
+// 8.7 M vertices (27 k neighbours per pair): 1600 -> 1540.
+// Tried and slower: two spans of fewer loads in flight (1.15 times on the latter), the next pair's loads dealt out between the
+// steps of the count (1.14), all 64 lanes adding, those without an entry nothing (1.04: an LDS addition costs by active lanes),
+// P written here at its final place, found by looking back over the sizes of the pairs before (1.2 to 1.7 times accumulation
+// and copy together: it ties all workgroups to the slowest one of every round).
+template <bool SQUARED>
 __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
 {
-    extern __shared__ uint32_t lds[];
+    extern __shared__ uint4 acc_lds[];
     if (a.giveup && *a.giveup)
         return;
-    uint32_t *cnt = lds;                   // kWinWords packed counters
-    unsigned long long *claim_s = reinterpret_cast<unsigned long long *>(lds + kWinWords); // [2], in turn: where the
-                                           // entries of the current (minibatch, window) start in the staging array
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    // per wave: one record per nonempty piece (by rank) and the start bits of one span of chunks
-    AccPiece *piece_rec = reinterpret_cast<AccPiece *>(lds + kWinWords + 3 * kAccWaves + 4) + wave * (kWave + kAccUnroll / 2);
-    uint32_t *starts = reinterpret_cast<uint32_t *>(piece_rec + kWave); // kAccChunks bits
-    const uint64_t below = (1ull << lane) - 1ull, below_incl = below | (1ull << lane);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(acc_lds); // kWinWords packed counters
+    AccShared &sh = *reinterpret_cast<AccShared *>(cnt + kWinWords);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = (int)scalar((uint32_t)tid / kWave);
+    AccWave &me = sh.wave[wave];
     const int64_t A0 = (int64_t)reinterpret_cast<uintptr_t>(a.A_col);
-    const int64_t nblk = (int64_t)a.k * a.nwin;
-    // the counters start at zero and every (minibatch, window) leaves them at zero: the pass that emits the
-    // nonzero ones clears them
-    for (int x = tid; x < kWinWords; x += kAccThreads)
-        cnt[x] = 0;
+    const uint32_t nwin = (uint32_t)a.nwin, nblk = (uint32_t)a.k * nwin; // (at most 2^16 minibatches and 2^15 windows)
+    for (int x = tid; x < kWinWords / 4; x += kAccThreads)
+        acc_lds[x] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    int turn = 0;
     // Workgroups are handed to the chip's 8 dies in turn, and each die has its own last-level cache.  Within a
     // round of gridDim.x (minibatch, window) pairs, die x takes a run of consecutive windows, so the memory
     // lines that hold the end of one window's piece and the start of the next one's are fetched once.
-    const int64_t G = gridDim.x;
-    const bool by_die = (G % 8) == 0;
-    auto block_of = [&](int64_t slot) {
-        int64_t blk = slot;
-        if (by_die) {
-            const int64_t p = slot % G;
-            blk = slot - p + (p % 8) * (G / 8) + p / 8;
-        }
-        return blk;
+    const uint32_t G = gridDim.x;
+    auto pair_of = [&](uint32_t round) -> uint32_t { // of the workgroup; nblk: none (nor in later rounds)
+        const uint32_t p = blockIdx.x, at = G % 8 == 0 ? (p % 8) * (G / 8) + p / 8 : p;
+        const uint64_t blk = (uint64_t)round * G + at;
+        return blk < nblk ? (uint32_t)blk : nblk;
     };
-    // the piece of window w in row r, r < r1: (length, address of its first neighbour); rows without
-    // neighbours have no boundaries on record: whatever is read there is dropped
-    auto piece_at = [&](int w, int64_t r, int64_t r1, uint32_t &len, int64_t &addr) {
-        len = 0;
-        addr = 0;
-        if (r < r1) {
-            const uint32_t *__restrict__ lo_b = a.bounds_t + (int64_t)w * a.rows_bound; // boundary w of every row
-            const uint32_t b0 = lo_b[r];
-            const uint32_t b1 = lo_b[a.rows_bound + r];
-            const bool empty = a.gather_off[r + 1] == a.gather_off[r];
-            len = empty ? 0u : b1 - b0;
-            addr = a.row_beg[r] + b0;
+    // A batch: the wave's rows first .. first + rows - 1 of a pair's minibatch, rows <= 64.  With few rows all waves get some.
+    uint32_t window = 0;             // of the pair
+    int32_t first = 0, rows = 0, all = 0; // all: rows of the minibatch
+    int64_t r0 = 0;                  // its first row
+    // the piece of the batch's row of this lane: boundaries in the row, where the row begins (the values are looked at where
+    // they are used: the loads have until then)
+    uint32_t bound0 = 0, bound1 = 0;
+    int64_t row_beg = 0;
+    uint32_t u0 = 0, total = 0, ustart = 0; // chunks of the batch: those asked for, all, before the lane's piece
+    auto fetch_pieces = [&]() {
+        bound0 = bound1 = 0;
+        row_beg = 0;
+        u0 = 0;
+        if (lane < min(rows, all - first)) {
+            const int64_t r = r0 + first;
+            const uint32_t *__restrict__ lo_b = a.bounds_t + (int64_t)window * a.rows_bound + r; // boundary w of the rows
+            bound0 = lo_b[lane];
+            bound1 = lo_b[a.rows_bound + lane];
+            row_beg = (a.row_beg + r)[lane];
         }
     };
-    // the first pieces of a (minibatch, window) pair are fetched while the pair before it is compacted
-    auto first_pieces = [&](int64_t slot, uint32_t &len, int64_t &addr) {
-        const int64_t blk = block_of(slot);
-        len = 0;
-        addr = 0;
+    auto begin_pair = [&](uint32_t blk) {
+        first = rows = all = 0;
         if (blk < nblk) {
-            const int i = (int)(blk / a.nwin);
-            piece_at((int)(blk % a.nwin), a.mb_rowoff[i] + (int64_t)wave * kWave + lane, a.mb_rowoff[i + 1], len, addr);
+            const uint32_t i = blk / nwin;
+            window = blk - i * nwin;
+            r0 = uniform_load(a.mb_rowoff + i);
+            all = (int32_t)(uniform_load(a.mb_rowoff + i + 1) - r0);
+            rows = all <= kAccWaves * (kWave / 2) ? kWave / 2 : kWave;
+            first = wave * rows;
         }
+        fetch_pieces();
     };
-    uint32_t len, next_len;
-    int64_t addr, next_addr;
-    first_pieces(blockIdx.x, len, addr);
-    for (int64_t slot = blockIdx.x; slot < (nblk + G - 1) / G * G; slot += G) {
-        const int64_t blk = block_of(slot);
-        if (blk >= nblk) { // no later slot of this workgroup holds a pair either
-            first_pieces(slot + G, len, addr);
-            continue;
-        }
-        const int i = (int)(blk / a.nwin), w = (int)(blk % a.nwin);
-        const int64_t r0 = a.mb_rowoff[i], r1 = a.mb_rowoff[i + 1];
-        const int32_t id0 = w << kWinShift;
-        auto piece_of = [&](int64_t r, uint32_t &l, int64_t &ad) { piece_at(w, r, r1, l, ad); };
-        // A part of the window (one wave's kWaveWords words) cannot hold more columns than it has counters, nor
-        // than the window gets neighbours: room for that many entries per part is claimed from the device-wide
-        // cursor now, and the answer is back long before the counters are compacted
-        const uint32_t added_blk = a.win_added[blk];
-        const uint32_t room = min(added_blk, (uint32_t)(2 * kWaveWords));
-        if (tid == 0)
-            claim_s[turn] = room ? atomicAdd(a.cursor, (unsigned long long)room * kWinParts) : 0ull;
-        for (int64_t base = r0 + (int64_t)wave * kWave; base < r1; base += (int64_t)kAccWaves * kWave) {
-            // the next 64 pieces are on their way while these are walked
-            piece_of(base + (int64_t)kAccWaves * kWave + lane, next_len, next_addr);
-            // A piece is read as the aligned 16-byte chunks it touches, one chunk per lane and load (four neighbours
-            // per lane keep the number of load instructions, and of the LDS additions behind them, at a quarter of
-            // what one neighbour per lane costs; a compute unit retires such instructions at a fixed pace whatever
-            // number of their lanes is active).  The chunks of the wave's 64 pieces are numbered end to end; which
-            // piece a chunk belongs to follows from counting piece starts up to it: the starts inside the current
-            // span of chunks are bits in LDS, the pieces' records a small table in LDS indexed by their rank among
-            // the nonempty ones.  The entries of a piece's first and last chunk that lie outside the piece (the
-            // neighbouring windows' or rows') are masked; an aligned 16-byte read that holds at least one entry of
-            // the piece stays inside that entry's page.
-            const int64_t lo_byte = A0 + addr * 4, hi_byte = lo_byte + (int64_t)len * 4;
+    // A piece is read as the aligned 16-byte chunks it touches, one chunk per lane and load (four neighbours
+    // per lane keep the number of load instructions, and of the LDS additions behind them, at a quarter of
+    // what one neighbour per lane costs; a compute unit retires such instructions at a fixed pace whatever
+    // number of their lanes is active).  The chunks of the batch's pieces are numbered end to end; which
+    // piece a chunk belongs to follows from counting piece starts up to it: the starts inside the current
+    // span of chunks are bits in LDS, the pieces' records a small table in LDS indexed by their rank among
+    // the nonempty ones.  The entries of a piece's first and last chunk that lie outside the piece (the
+    // neighbouring windows' or rows') are masked; an aligned 16-byte read that holds at least one entry of
+    // the piece stays inside that entry's page.
+    struct Span {
+        uint4 v[kAccUnroll];
+        uint32_t keep;  // 4 bits per load: which of the 4 entries belong to the piece
+        uint32_t chunks;
+    };
+    Span s0;
+    s0.chunks = 0;
+    auto more = [&]() { return first < all; };
+    auto ask = [&](Span &s) { // the pair's next span, if it has one
+        s.keep = s.chunks = 0;
+        while (more()) {
+            const uint32_t len = bound1 - bound0;
+            const int64_t lo_byte = A0 + (row_beg + bound0) * 4, hi_byte = lo_byte + (int64_t)len * 4;
             const int64_t chunk0 = lo_byte & ~(int64_t)15;
             const uint32_t nc = len ? (uint32_t)((hi_byte - 1 - chunk0) >> 4) + 1u : 0u;
-            const uint32_t inc = wave_inclusive_scan(nc);
-            const uint32_t total = __shfl(inc, kWave - 1, kWave);
-            const uint32_t ustart = inc - nc;
             const bool nonempty = nc != 0;
-            const uint64_t ne_mask = __ballot(nonempty);
-            __builtin_amdgcn_wave_barrier();
-            if (nonempty) {
-                AccPiece rec;
-                rec.origin = chunk0 - (int64_t)ustart * 16; // chunk j of the wave's order starts at origin + 16 j
-                rec.lo_rel = (uint32_t)(lo_byte - rec.origin);
-                rec.hi_rel = (uint32_t)(hi_byte - rec.origin);
-                piece_rec[__popcll(ne_mask & below)] = rec;
+            if (u0 == 0) {
+                const uint32_t inc = wave_inclusive_scan_dpp(nc);
+                total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+                ustart = inc - nc;
             }
-            for (uint32_t u0 = 0; u0 < total; u0 += kAccChunks) {
+            if (total > u0) {
+                s.chunks = min(total - u0, (uint32_t)kAccChunks);
+                const uint64_t ne_mask = __ballot(nonempty);
                 __builtin_amdgcn_wave_barrier();
+                if (nonempty) {
+                    AccPiece rec;
+                    rec.origin = chunk0 - (int64_t)ustart * 16; // chunk j of the batch starts at origin + 16 j
+                    rec.lo_rel = (uint32_t)(lo_byte - rec.origin);
+                    rec.hi_rel = (uint32_t)(hi_byte - rec.origin);
+                    me.piece[bits_below(ne_mask)] = rec;
+                }
                 if (lane < 2 * kAccUnroll)
-                    starts[lane] = 0;
+                    me.starts[lane] = 0;
                 __builtin_amdgcn_wave_barrier();
                 const uint32_t rel = ustart - u0; // wraps for pieces that start before the span
                 if (nonempty && rel < (uint32_t)kAccChunks)
-                    atomicOr(starts + (rel >> 5), 1u << (rel & 31u));
+                    atomicOr(me.starts + (rel >> 5), 1u << (rel & 31u));
                 __builtin_amdgcn_wave_barrier();
                 int rank = __popcll(__ballot(nonempty && ustart < u0)) - 1; // piece that holds chunk u0 - 1
-                uint4 v[kAccUnroll] = {};
-                uint32_t keep = 0; // 4 bits per step: which of the 4 entries belong to the piece
+                uint32_t j0 = (uint32_t)lane;
+                asm volatile("" : "+v"(j0)); // (places: computed here, not kept in registers)
 #pragma unroll
                 for (int u = 0; u < kAccUnroll; ++u) {
-                    if (u0 + (uint32_t)(u * kWave) >= total) // (the same for all lanes)
+                    if ((uint32_t)(u * kWave) >= s.chunks) // (the same for all lanes)
                         break;
-                    const uint32_t j = u0 + (uint32_t)(u * kWave + lane);
-                    const uint64_t m = reinterpret_cast<const uint64_t *>(starts)[u];
-                    const int mine = rank + __popcll(m & below_incl);
+                    const uint64_t m = (uint64_t)scalar(reinterpret_cast<const int64_t *>(me.starts)[u]);
+                    const int mine = rank + (int)(m & 1u) + (int)bits_below(m >> 1);
                     rank += __popcll(m);
-                    v[u] = make_uint4(0, 0, 0, 0);
-                    if (j < total) {
-                        const AccPiece rec = piece_rec[mine];
-                        const uint32_t off = j * 16u; // of the lane's 16 bytes, from origin
+                    if (j0 + u * kWave < s.chunks) {
+                        const AccPiece rec = me.piece[mine];
+                        const uint32_t off = (u0 + j0 + u * kWave) * 16u; // of the lane's 16 bytes, from origin
                         uint32_t k4 = 0;
 #pragma unroll
                         for (uint32_t e = 0; e < 4; ++e)
                             k4 |= (off + 4u * e >= rec.lo_rel && off + 4u * e < rec.hi_rel) ? 1u << e : 0u;
-                        v[u] = *reinterpret_cast<const uint4 *>(rec.origin + (int64_t)off);
-                        keep |= k4 << (4 * u);
+                        s.v[u] = *reinterpret_cast<const uint4 *>(rec.origin + (int64_t)off);
+                        s.keep |= k4 << (4 * u);
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < kAccUnroll; ++u) {
-                    if (u0 + (uint32_t)(u * kWave) >= total)
-                        break;
-                    const uint32_t xs[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if ((keep >> (4 * u + e)) & 1u) {
-                            const uint32_t x = xs[e] - (uint32_t)id0;
-                            atomicAdd(&cnt[x >> 1], 1u << ((x & 1u) * 16));
-                        }
-                }
+                __builtin_amdgcn_wave_barrier();
+                u0 += kAccChunks;
             }
-            len = next_len;
-            addr = next_addr;
+            if (u0 >= total) { // the next batch's pieces are fetched for the next call
+                first += kAccWaves * rows;
+                fetch_pieces();
+            }
+            if (s.chunks)
+                break;
         }
-        first_pieces(slot + G, len, addr);
+    };
+    auto add = [&](const Span &s, uint32_t id0) {
+#pragma unroll
+        for (int u = 0; u < kAccUnroll; ++u) {
+            if ((uint32_t)(u * kWave) >= s.chunks)
+                break;
+            const uint32_t xs[4] = {s.v[u].x, s.v[u].y, s.v[u].z, s.v[u].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((s.keep >> (4 * u + e)) & 1u) {
+                    const uint32_t x = xs[e] - id0;
+                    atomicAdd(&cnt[x >> 1], 1u << ((x & 1u) * 16));
+                }
+        }
+    };
+
+    uint32_t round = 0, blk = pair_of(0);
+    begin_pair(blk);
+    ask(s0);
+    while (blk < nblk) {
+        const uint32_t id0 = window << kWinShift, blk_next = pair_of(++round);
+        add(s0, id0);
+        while (more()) {
+            ask(s0);
+            add(s0, id0);
+        }
         __syncthreads();
-        // Each wave compacts its part of the window, kWaveWords consecutive words, in one pass: the nonzero counters
-        // leave in ascending column order as (column - id0) << 16 | e_v, and are cleared; the wave records where its
-        // part went, how many entries it holds and what they weigh.
-        const int64_t claimed = (int64_t)claim_s[turn] + (int64_t)wave * room;
-        turn ^= 1;
-        const int64_t part = blk * kWinParts + wave;
-        uint32_t nz = 0;
-        uint32_t w32 = 0; // e_v: at most 64 values below 2^16 per lane
-        uint64_t w64 = 0; // e_v^2
-        if (added_blk) {
-            // 16 bytes (8 counters) per lane and access: the lanes' counts of nonzero counters are scanned, every lane
-            // writes its own run; a group of 64 such quads without any counter costs one LDS read.  (Packing the
-            // nonzero counters of 64 consecutive words by ballots instead, so that a store instruction writes one
-            // run of consecutive entries, took four times the steps and more instructions per counter: 9 us
-            // against 6 per full window.)
-            constexpr int kQuadIts = kWaveWords / 4 / kWave; // quads per lane
-            uint4 *mine4 = reinterpret_cast<uint4 *>(cnt + wave * kWaveWords);
-            uint32_t *__restrict__ out = a.tmp_ent + claimed;
+        // A bit per counter in use; lane x of the wave has counters 64 x .. 64 x + 63 of its part, 16 bytes at a time, and
+        // begins elsewhere among them than the lanes 2 .. 14 further on: all of LDS's banks have work.
+        constexpr int kQuads = kWaveWords / 4 / kWave;
+        static_assert(kQuads == 8, "64 counters per lane");
+        uint32_t lane_now = (uint32_t)lane;
+        asm volatile("" : "+v"(lane_now)); // (places: computed here, not kept in registers)
+        const uint4 *mine4 = reinterpret_cast<const uint4 *>(cnt + wave * kWaveWords) + lane_now * kQuads;
+        uint32_t used[2] = {0, 0}, w32 = 0; // e_v: 64 values below 2^16
+        uint64_t w64 = 0;                   // e_v^2
 #pragma unroll
-            for (int it = 0; it < kQuadIts; ++it) {
-                const uint4 q = mine4[it * kWave + lane];
-                const uint32_t xs[4] = {q.x, q.y, q.z, q.w};
-                uint32_t c = 0;
+        for (int it = 0; it < kQuads; ++it) {
+            const uint32_t at = (it + lane_now / 2) & (kQuads - 1);
+            const uint4 q = mine4[at];
+            const uint32_t xs[4] = {q.x, q.y, q.z, q.w};
+            uint32_t bits = 0; // of the lower counters at 0, 2, 4, 6, of the upper ones at 16, 18, 20, 22
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    c += ((xs[u] & 0xFFFFu) != 0) + ((xs[u] >> 16) != 0);
-                if (__ballot(c != 0) == 0)
-                    continue;
-                if (c)
-                    mine4[it * kWave + lane] = make_uint4(0, 0, 0, 0);
-                const uint32_t inc = wave_inclusive_scan_dpp(c);
-                uint32_t pos = nz + (inc - c);
-                nz += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
-                const uint32_t col0 = 2u * (uint32_t)(wave * kWaveWords + 4 * (it * kWave + lane)); // within the window
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 4; ++u) {
+                bits |= at_most_one(xs[u]) << (2 * u);
+                if (SQUARED) {
                     const uint32_t lo = xs[u] & 0xFFFFu, hi = xs[u] >> 16;
-                    if (a.squared)
-                        w64 += (uint64_t)(lo * lo) + (uint64_t)(hi * hi);
-                    else
-                        w32 += lo + hi;
-                    if (lo)
-                        out[pos++] = (col0 + 2 * u) << 16 | lo;
-                    if (hi)
-                        out[pos++] = (col0 + 2 * u + 1) << 16 | hi;
+                    w64 += (uint64_t)(lo * lo) + (uint64_t)(hi * hi);
+                } else {
+                    w32 = __builtin_amdgcn_sad_u16(xs[u], 0u, w32); // + both halves
                 }
             }
+            bits = ((bits & 0x55u) | ((bits >> 15) & 0xAAu)) << (8 * (at & 3u));
+            used[0] |= at < 4 ? bits : 0u;
+            used[1] |= at < 4 ? 0u : bits;
         }
-        const uint64_t wt = wave_sum(a.squared ? w64 : (uint64_t)w32);
-        if (lane == 0) {
-            a.part_base[part] = claimed;
-            a.part_cnt[part] = nz;
-            a.part_wt[part] = wt;
-        }
+        const uint32_t mine = __popc(used[0]) + __popc(used[1]);
+        const uint32_t upto = wave_inclusive_scan_dpp(mine);
+        const uint32_t wave_c = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+        if (lane == 0)
+            sh.cnt[wave] = wave_c;
         __syncthreads();
+        // room for the pair's entries; the parts lie in it one after the other
+        const uint32_t sums = wave_inclusive_scan_dpp(lane < kAccWaves ? sh.cnt[lane] : 0u);
+        const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)sums, kAccWaves - 1);
+        const uint32_t before_c = (uint32_t)__builtin_amdgcn_readlane((int)sums, wave) - wave_c;
+        unsigned long long claim = 0;
+        if (tid == 0 && pair_c) {
+            unsigned long long *cursor = a.cursor;
+            asm volatile("" : "+v"(cursor)); // (an address known to be the same in all lanes has the wave wait for the answer here)
+            claim = atomicAdd(cursor, (unsigned long long)pair_c);
+        }
+        begin_pair(blk_next);
+        // All lanes' counters are listed at once, or, of a part with more in use, those of 8 lanes at a time.
+        static_assert(8 * 64 <= kAccListed, "8 lanes' counters");
+        const int lanes = wave_c <= (uint32_t)kAccListed ? kWave : 8;
+        auto list_up = [&](int lane0, uint32_t listed) {
+            __builtin_amdgcn_wave_barrier();
+            if (lane >= lane0 && lane < lane0 + lanes) {
+                uint16_t *to = me.list + (upto - mine - listed);
+                for (uint32_t m = used[0]; m; m &= m - 1u)
+                    *to++ = (uint16_t)(lane * 64 + __ffs((int)m) - 1);
+                for (uint32_t m = used[1]; m; m &= m - 1u)
+                    *to++ = (uint16_t)(lane * 64 + 31 + __ffs((int)m));
+            }
+            __builtin_amdgcn_wave_barrier();
+        };
+        list_up(0, 0);
+        const uint64_t wave_w = wave_sum(SQUARED ? w64 : (uint64_t)w32);
+        if (tid == 0)
+            sh.claimed = claim;
+        __syncthreads();
+        const int64_t claimed = scalar((int64_t)sh.claimed) + before_c;
+        if (lane == 0) {
+            const int64_t part = (int64_t)blk * kWinParts + wave;
+            a.part_base[part] = claimed;
+            a.part_cnt[part] = wave_c;
+            a.part_wt[part] = wave_w;
+        }
+        if (wave_c) {
+            uint32_t *__restrict__ out = a.tmp_ent + claimed;
+            const uint16_t *cnt16 = reinterpret_cast<const uint16_t *>(cnt + wave * kWaveWords);
+            const uint32_t part_id = (uint32_t)wave * (2 * kWaveWords);
+            for (int lane0 = 0; lane0 < kWave; lane0 += lanes) {
+                const uint32_t listed = lane0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, lane0 - 1) : 0u;
+                const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, lane0 + lanes - 1) - listed;
+                if (lane0)
+                    list_up(lane0, listed);
+                for (uint32_t x0 = lane; x0 < n; x0 += kAccFlush * kWave) {
+                    uint32_t id[kAccFlush], c[kAccFlush];
+#pragma unroll
+                    for (int u = 0; u < kAccFlush; ++u)
+                        id[u] = me.list[min(x0 + u * kWave, n - 1u)];
+#pragma unroll
+                    for (int u = 0; u < kAccFlush; ++u)
+                        c[u] = cnt16[id[u]];
+#pragma unroll
+                    for (int u = 0; u < kAccFlush; ++u)
+                        if (x0 + u * kWave < n)
+                            out[listed + x0 + u * kWave] = (part_id + id[u]) << 16 | c[u];
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            uint4 *part4 = reinterpret_cast<uint4 *>(cnt + wave * kWaveWords) + lane_now;
+#pragma unroll
+            for (int it = 0; it < kQuads; ++it) // the next pair begins at zero
+                part4[it * kWave] = make_uint4(0, 0, 0, 0);
+        }
+        ask(s0); // of the next pair
+        __syncthreads();
+        blk = blk_next;
     }
 }
 
@@ -692,6 +753,7 @@ __global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a, int64_t *pnn
 // known weight before it: one wave per part streams it, 64 entries at a time, with lane scans for the sums and
 // no workgroup barrier.
 constexpr int kCopyUnroll = 4;
+template <bool SQUARED>
 __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 {
     if (a.giveup) {
@@ -729,7 +791,7 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
                 const uint32_t c = ent[u] & 0xFFFFu;
                 // e_v < 2^16: sums of 64 weights e_v fit 32 bits; e_v^2 is summed as two 16-bit halves
                 uint64_t inc;
-                if (a.squared) {
+                if (SQUARED) {
                     const uint32_t wq = c * c;
                     inc = ((uint64_t)wave_inclusive_scan_dpp(wq >> 16) << 16) + wave_inclusive_scan_dpp(wq & 0xFFFFu);
                 } else {
@@ -1199,8 +1261,10 @@ __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Loo
 // ---------------------------------------------------------------------------------------------
 size_t ldw_accumulate_lds_bytes()
 {
-    return (size_t)(kWinWords + 3 * kAccWaves + 4) * sizeof(uint32_t) + (size_t)kAccWaves * (kWave + kAccUnroll / 2) * sizeof(AccPiece);
+    return (size_t)kWinWords * sizeof(uint32_t) + sizeof(AccShared);
 }
+
+static_assert((size_t)kWinWords * sizeof(uint32_t) + sizeof(AccShared) <= 160 * 1024, "does not fit a compute unit");
 
 static void launch_ldw_tiles(const Launch &L, const LwHop &a)
 {
@@ -1218,14 +1282,9 @@ int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t
     return 0;
 }
 
-void launch_ldw_zero_added(const Launch &L, const LwHop &a)
-{
-    hipLaunchKernelGGL(ldw_zero_added_kernel, dim3(grid_for(L, ((int64_t)a.k * a.nwin + 255) / 256, 2)), dim3(256), 0, L.stream, a);
-}
-
 void launch_ldw_bounds(const Launch &L, const LwHop &a)
 {
-    const int64_t ttiles = ((a.nwin + kBtWindows - 1) / kBtWindows) * ((a.rows_bound + 63) / 64);
+    const int64_t ttiles = (((int64_t)a.nwin + 64) / 64) * ((a.rows_bound + 63) / 64);
     if (a.index && a.k < kPlanMb) {
         const int planners = grid_for(L, (a.tiles_bound + 255) / 256, 1);
         hipLaunchKernelGGL(ldw_plan_bounds_kernel, dim3(planners + grid_for(L, ttiles, 8)), dim3(256), 0, L.stream, a, planners);
@@ -1245,14 +1304,16 @@ void launch_ldw_index(const Launch &L, const LwHop &a)
 
 int launch_ldw_accumulate(const Launch &L, const LwHop &a, int64_t *pnnz_out)
 {
+    void (*const kernels[2])(LwHop) = {ldw_accumulate_kernel<false>, ldw_accumulate_kernel<true>};
     static bool attr_set = false;
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(ldw_accumulate_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldw_accumulate_lds_bytes()) != hipSuccess)
-            (void)hipGetLastError(); // not required on every runtime; the launch below reports real failures
+        for (auto *kernel : kernels)
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)ldw_accumulate_lds_bytes()) != hipSuccess)
+                (void)hipGetLastError(); // not required on every runtime; the launch below reports real failures
         attr_set = true;
     }
-    hipLaunchKernelGGL(ldw_accumulate_kernel, dim3(grid_for(L, (int64_t)a.k * a.nwin, 1)), dim3(kAccThreads),
+    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, (int64_t)a.k * a.nwin, 1)), dim3(kAccThreads),
                        ldw_accumulate_lds_bytes(), L.stream, a);
     if (hipGetLastError() != hipSuccess)
         return -1;
@@ -1262,7 +1323,8 @@ int launch_ldw_accumulate(const Launch &L, const LwHop &a, int64_t *pnnz_out)
 
 void launch_ldw_p_copy(const Launch &L, const LwHop &a)
 {
-    hipLaunchKernelGGL(ldw_p_copy_kernel, dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256), 0, L.stream, a);
+    void (*const kernels[2])(LwHop) = {ldw_p_copy_kernel<false>, ldw_p_copy_kernel<true>};
+    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
 
 void launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)

@@ -239,3 +239,19 @@ def test_shapes_around_the_window_and_part_boundaries(mods):
             res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), s, seed, squared=bool(b & 1), recycle=res)
             assert_hops_equal(res.hops(), O.sample_ladies(rowptr, col, batches, s, seed, 0, bool(b & 1)), with_p=True,
                               what="n=%d k=%d b=%d s=%s seed=%d" % (n, k, b, s, seed))
+
+
+@pytest.mark.parametrize("rows,degree,squared", [(512, 300, False), (513, 300, True), (1025, 12, False), (600, 4000, False)])
+def test_windows_from_empty_to_nearly_full(mods, rows, degree, squared):
+    # a wave's rows are 32 (up to 512 in all) or 64; its 4096 counters are listed at once up to 896 in use, else 8 lanes at a time:
+    # no neighbours beyond id 90000, `degree` a row below 20000 (crowded: up to every counter), two a row in between
+    rng = np.random.default_rng(rows + degree)
+    n = 140_000
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:rows + 1] = np.arange(1, rows + 1) * (degree + 2)
+    rowptr[rows + 1:] = rowptr[rows]
+    col = np.concatenate([np.concatenate([np.sort(rng.choice(20_000, degree, replace=False)),
+                                          np.sort(rng.choice(70_000, 2, replace=False)) + 20_000])
+                          for _ in range(rows)]).astype(np.int32)
+    batches = np.stack([rng.permutation(rows), rng.permutation(rows)]).astype(np.int32)
+    _run_both(mods, rowptr, col, batches, (64,), 31, squared=squared)
