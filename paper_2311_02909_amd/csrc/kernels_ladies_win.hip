@@ -814,19 +814,154 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 // ---------------------------------------------------------------------------------------------
 // SAMPLE: one workgroup per minibatch
 // ---------------------------------------------------------------------------------------------
-// PLACE: the sampled columns go to their place in the stack at once, behind those of the minibatches before (sum_before)
-template <bool PLACE>
-__global__ __launch_bounds__(1024) void ldw_draw_kernel(LwHop a, Lookback lb, int64_t *ncols_out)
+constexpr int kDrawThreads = 1024;
+// The value of lane ^ X: by the vector unit where it can, else through LDS's crossbar
+template <int X>
+__device__ inline uint32_t lane_xor(uint32_t v)
 {
-    __shared__ uint32_t key[kMaxWinSampled];
-    __shared__ uint32_t smem[16];
+    if (X == 1)
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1 /* quad_perm:[1,0,3,2] */, 0xF, 0xF, true);
+    if (X == 2)
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E /* quad_perm:[2,3,0,1] */, 0xF, 0xF, true);
+    if (X == 8)
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xF, 0xF, true);
+    return __shfl_xor(v, X, kWave);
+}
+
+// Bitonic sort, ascending, of the first n of PER x 1024 places (the rest hold kEmptySlot): thread t holds places t, t + 1024, ...
+// Partners in the thread itself and in its wave need no barrier; of the 55 steps for 1024 keys 10 go through LDS (ex: two buffers
+// in turn, PER x 1024 words each).
+template <int PER, int SIZE, int STRIDE>
+__device__ inline void sort_step(uint32_t (&key)[PER], int n, uint32_t *ex, int &turn)
+{
+    const uint32_t tid = threadIdx.x;
+    uint32_t other[PER];
+    if (STRIDE >= kDrawThreads) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            other[q] = key[(q ^ (STRIDE / kDrawThreads)) % PER];
+    } else if (STRIDE >= kWave) {
+        uint32_t *to = ex + turn * PER * kDrawThreads;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            to[q * kDrawThreads + tid] = key[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            other[q] = to[q * kDrawThreads + (tid ^ (uint32_t)STRIDE)];
+        turn ^= 1;
+    } else {
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            other[q] = lane_xor<STRIDE < kWave ? STRIDE : 1>(key[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const uint32_t at = (uint32_t)(q * kDrawThreads) + tid;
+        const bool low = ((at & (uint32_t)STRIDE) == 0) == ((at & (uint32_t)SIZE) == 0);
+        key[q] = low ? min(key[q], other[q]) : max(key[q], other[q]);
+    }
+    if constexpr (STRIDE > 1)
+        sort_step<PER, SIZE, STRIDE / 2>(key, n, ex, turn);
+    else if constexpr (SIZE < PER * kDrawThreads)
+        if (SIZE < n)
+            sort_step<PER, SIZE * 2, SIZE>(key, n, ex, turn);
+}
+
+// N draws of a thread: the smallest entries of P (absolute index) whose sums in the minibatch exceed r[]; side by side, as each is
+// a chain of trips to memory.  pre: recorded sums of the nb blocks that end in the minibatch's row [p0, p0 + C); top: the sums at
+// the ends of the ntop groups of 2^st blocks; pnnz >= 16.
+struct DrawRow {
+    int64_t p0, C, B0, nb, ntop, pnnz;
+    const uint64_t *pre;
+    int st, squared;
+};
+template <int N>
+__device__ inline void find_entries(const LwHop &a, const DrawRow &d, const uint64_t *top, const uint64_t (&r)[N], int64_t (&e)[N])
+{
+    int64_t pos[N]; // groups, then blocks, whose sums do not exceed r
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        pos[x] = 0;
+#pragma unroll
+    for (int step = kDrawTop; step > 0; step >>= 1)
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+            const int64_t at = pos[x] + step;
+            if (at <= d.ntop && top[at <= d.ntop ? at - 1 : 0] <= r[x])
+                pos[x] = at;
+        }
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        pos[x] <<= d.st;
+    for (int w = d.st; w > 0;) { // three bits of the place in the group at a time: 7 sums in flight
+        const int bits = min(w, 3);
+        w -= bits;
+        uint64_t sum[N][7];
+#pragma unroll
+        for (int x = 0; x < N; ++x)
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                const int64_t at = pos[x] + ((int64_t)(i + 1) << w) - 1;
+                sum[x][i] = i + 1 < 1 << bits && at < d.nb ? d.pre[at] : ~0ull;
+            }
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < 7; ++i)
+                n += sum[x][i] <= r[x] ? 1 : 0;
+            pos[x] += (int64_t)n << w;
+        }
+    }
+    // the 16 entries of the block (the minibatch's ones among them): the last block of all is read from 16 entries before its end
+    using Four = uint32_t __attribute__((ext_vector_type(4), aligned(4)));
+    uint64_t acc[N];
+    Four v[N][kPrefixBlock / 4];
+    int64_t from[N];
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+        acc[x] = pos[x] > 0 ? d.pre[pos[x] - 1] : 0ull;
+        e[x] = (d.B0 + pos[x]) * kPrefixBlock;
+        from[x] = min<int64_t>(e[x], d.pnnz - kPrefixBlock);
+#pragma unroll
+        for (int i = 0; i < kPrefixBlock / 4; ++i)
+            v[x][i] = *reinterpret_cast<const Four *>(a.p_cnt + from[x] + 4 * i);
+    }
+    const int64_t end = d.p0 + d.C - 1; // the smallest t with prefix[t] > r exists below the row's end: W > r
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+        const int32_t first = (int32_t)(max(e[x], d.p0) - from[x]), last = (int32_t)min<int64_t>(end - from[x], kPrefixBlock);
+        int32_t n = 0; // of the entries first .. last - 1 those whose sums do not exceed r
+#pragma unroll
+        for (int i = 0; i < kPrefixBlock; ++i) {
+            const uint32_t c = i >= first ? v[x][i / 4][i % 4] : 0u;
+            acc[x] += d.squared ? (uint64_t)c * c : (uint64_t)c;
+            n += i >= first && i < last && acc[x] <= r[x] ? 1 : 0;
+        }
+        e[x] = from[x] + first + n;
+    }
+}
+
+// PLACE: the sampled columns go to their place in the stack at once, behind those of the minibatches before (sum_before).
+// PER: places of the sort per thread, 1024 PER >= s.  A chain of trips to memory and barriers on one compute unit: the
+// draws of a thread search side by side, the 16 entries of a block arrive together, and most steps of the sort need no barrier.
+// 3 minibatches, 512 draws: 21 -> 9 us (sort 11 -> 2.5, entries of a block one by one 3 -> 1).  64 minibatches, 2048 draws from
+// 115 thousand blocks: 75 -> 71 us; there the sums and entries looked up, some 14 thousand lines per compute unit, are the bound
+// (50 us of it, whatever their order), and the sort went from 16 to 5 us.
+template <bool PLACE, int PER>
+__global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookback lb, int64_t *ncols_out)
+{
+    __shared__ uint32_t ex[2 * PER * kDrawThreads];
     __shared__ uint64_t top[kDrawTop];
-    __shared__ int64_t smem64[16];
+    __shared__ int64_t smem64[kDrawThreads / kWave];
+    __shared__ uint32_t heads_of[PER * kDrawThreads / kWave];
     __shared__ uint32_t number_s;
-    const int tid = threadIdx.x, i = PLACE ? (int)take_number(lb, &number_s) : (int)blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int i = PLACE ? (int)scalar(take_number(lb, &number_s)) : (int)blockIdx.x;
     // where the minibatch's `count` columns begin
     auto place = [&](uint32_t count) {
-        const int64_t before = sum_before<1024>(lb, (uint32_t)i, count, smem64);
+        const int64_t before = sum_before<kDrawThreads>(lb, (uint32_t)i, count, smem64);
         if (tid == 0) {
             a.mb_coloff[i] = before;
             if (i == a.k - 1) {
@@ -836,95 +971,103 @@ __global__ __launch_bounds__(1024) void ldw_draw_kernel(LwHop a, Lookback lb, in
         }
         return before;
     };
-    if (a.giveup && (*a.giveup || a.p_off[a.k] > a.p_cap)) { // no P: the minibatch gets no columns
+    DrawRow d;
+    d.pnnz = uniform_load(a.p_off + a.k);
+    if (a.giveup && (uniform_load(a.giveup) || d.pnnz > a.p_cap)) { // no P: the minibatch gets no columns
         if (PLACE)
             place(0);
         else if (tid == 0)
             a.mb_count[i] = 0;
         return;
     }
-    const int64_t p0 = a.p_off[i], C = a.p_off[i + 1] - p0;
-    uint32_t M = 1024; // sorted size: a power of two >= s, at least one slot per thread
-    while (M < (uint32_t)a.s)
-        M <<= 1;
+    d.p0 = uniform_load(a.p_off + i);
+    d.C = uniform_load(a.p_off + i + 1) - d.p0;
     // inclusive weight sums are on record at the last entry of every block of kPrefixBlock entries (absolute
     // index in P): blocks B0 .. B0 + nb - 1 end inside this minibatch's row; W = the row sum
-    const int64_t B0 = p0 / kPrefixBlock, nb = (p0 + C) / kPrefixBlock - B0;
-    const uint64_t *__restrict__ pre = a.prefix + B0;
+    d.B0 = d.p0 / kPrefixBlock;
+    d.nb = (d.p0 + d.C) / kPrefixBlock - d.B0;
+    d.pre = a.prefix + d.B0;
+    d.squared = a.squared;
     const int64_t last_win = (int64_t)i * a.nwin + a.nwin - 1;
-    const uint64_t W = a.win_woff[last_win] + a.win_wt[last_win];
+    const uint64_t W = uniform_load(a.win_woff + last_win) + uniform_load(a.win_wt + last_win);
     const uint64_t rk = row_key(a.hopkey, a.mb_base + (uint32_t)i, kNoVertex);
-    // Every draw searches the recorded sums; probes far apart in memory cost a trip to memory each and follow one
-    // another.  The sums at the end of every group of 2^st blocks (at most kDrawTop groups) are copied to LDS
-    // first: a draw finds its group there and only the last st probes go to memory, close to one another.
-    int st = 0;
-    while ((nb >> st) > kDrawTop)
-        ++st;
-    const int64_t ntop = nb >> st;
-    for (int64_t t = tid; t < ntop; t += 1024)
-        top[t] = pre[((t + 1) << st) - 1];
-    __syncthreads();
-    for (uint32_t j = tid; j < M; j += 1024) {
-        uint32_t v = kEmptySlot;
-        if (j < (uint32_t)a.s && C > 0) { // an empty aggregated neighbourhood samples nothing
-            const uint64_t r = bounded64(draw64(rk, j), W);
-            int64_t lo = 0, hi = ntop; // first group whose last recorded sum exceeds r (ntop: the blocks after the groups)
-            while (lo < hi) {
-                const int64_t mid = lo + ((hi - lo) >> 1);
-                if (top[mid] > r)
-                    hi = mid;
-                else
-                    lo = mid + 1;
-            }
-            hi = lo < ntop ? ((lo + 1) << st) - 1 : nb; // first block whose recorded sum exceeds r (nb: the unrecorded tail)
-            lo <<= st;
-            while (lo < hi) {
-                const int64_t mid = lo + ((hi - lo) >> 1);
-                if (pre[mid] > r)
-                    hi = mid;
-                else
-                    lo = mid + 1;
-            }
-            uint64_t acc = lo > 0 ? pre[lo - 1] : 0ull;
-            int64_t e = (B0 + lo) * kPrefixBlock;
-            if (e < p0)
-                e = p0;
-            const int64_t end = p0 + C - 1; // the smallest t with prefix[t] > r exists below the row's end: W > r
-            for (; e < end; ++e) {
-                acc += ldw_weight(a.p_cnt[e], a.squared);
-                if (acc > r)
-                    break;
-            }
-            v = (uint32_t)a.p_col[e];
-        }
-        key[j] = v;
+    // Every draw searches the recorded sums.  Those at the end of every group of 2^st blocks (at most kDrawTop groups) are copied
+    // to LDS first: a draw finds its group there and only the last st bits are looked for in memory.
+    d.st = 0;
+    while ((d.nb >> d.st) > kDrawTop)
+        ++d.st;
+    d.ntop = d.nb >> d.st;
+    uint64_t sums[kDrawTop / kDrawThreads];
+#pragma unroll
+    for (int q = 0; q < kDrawTop / kDrawThreads; ++q) {
+        const int64_t t = q * kDrawThreads + tid;
+        sums[q] = t < d.ntop ? d.pre[((t + 1) << d.st) - 1] : 0ull;
     }
+#pragma unroll
+    for (int q = 0; q < kDrawTop / kDrawThreads; ++q)
+        top[q * kDrawThreads + tid] = sums[q];
     __syncthreads();
-    for (uint32_t size = 2; size <= M; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            for (uint32_t t = tid; t < (M >> 1); t += 1024) {
-                const uint32_t lo = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
-                const uint32_t hi = lo | stride;
-                const uint32_t x = key[lo], y = key[hi];
-                if ((x > y) == ((lo & size) == 0)) {
-                    key[lo] = y;
-                    key[hi] = x;
-                }
+    uint32_t key[PER];
+    if (d.C > 0 && d.pnnz >= kPrefixBlock) {
+        constexpr int N = PER < 2 ? PER : 2; // draws side by side
+#pragma unroll
+        for (int q = 0; q < PER; q += N) {
+#pragma unroll
+            for (int x = 0; x < N; ++x)
+                key[q + x] = kEmptySlot;
+            if (q * kDrawThreads + (int)scalar((uint32_t)wave) * kWave >= a.s)
+                continue;
+            uint64_t r[N];
+            int64_t e[N];
+#pragma unroll
+            for (int x = 0; x < N; ++x)
+                r[x] = bounded64(draw64(rk, (uint32_t)((q + x) * kDrawThreads + tid)), W);
+            find_entries<N>(a, d, top, r, e);
+#pragma unroll
+            for (int x = 0; x < N; ++x)
+                key[q + x] = (q + x) * kDrawThreads + tid < a.s ? (uint32_t)a.p_col[e[x]] : kEmptySlot;
+        }
+    } else { // hardly any P at all, or an empty aggregated neighbourhood, which samples nothing
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const uint32_t j = (uint32_t)(q * kDrawThreads + tid);
+            key[q] = kEmptySlot;
+            if (j < (uint32_t)a.s && d.C > 0) {
+                const uint64_t r = bounded64(draw64(rk, j), W);
+                int64_t e = d.p0;
+                for (uint64_t acc = ldw_weight(a.p_cnt[e], a.squared); acc <= r; acc += ldw_weight(a.p_cnt[e], a.squared))
+                    ++e;
+                key[q] = (uint32_t)a.p_col[e];
             }
-            __syncthreads();
         }
     }
-    // thread t owns sorted slots [t per, (t+1) per); the first of every run of equal columns stays
-    const uint32_t per = M >> 10;
-    uint32_t heads = 0;
-    for (uint32_t j = tid * per; j < (tid + 1) * per; ++j)
-        heads += (key[j] != kEmptySlot && (j == 0 || key[j] != key[j - 1])) ? 1u : 0u;
-    uint32_t total;
-    uint32_t rank = block_exclusive_scan<uint32_t, 1024>(heads, smem, total);
+    int turn = 0;
+    sort_step<PER, 2, 1>(key, a.s, ex, turn);
+    // the first of every run of equal columns stays
+    uint32_t *sorted = ex + turn * PER * kDrawThreads;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        sorted[q * kDrawThreads + tid] = key[q];
+    __syncthreads();
+    uint64_t heads[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int at = q * kDrawThreads + tid;
+        heads[q] = __ballot(key[q] != kEmptySlot && (at == 0 || sorted[at > 0 ? at - 1 : 0] != key[q]));
+        if (lane == 0)
+            heads_of[at / kWave] = (uint32_t)__popcll(heads[q]);
+    }
+    __syncthreads();
+    const uint32_t upto = wave_inclusive_scan_dpp(lane < PER * kDrawThreads / kWave ? heads_of[lane] : 0u);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
     int32_t *__restrict__ out = PLACE ? a.col_vertex + place(total) : a.sel_tmp + (int64_t)i * a.s;
-    for (uint32_t j = tid * per; j < (tid + 1) * per; ++j)
-        if (key[j] != kEmptySlot && (j == 0 || key[j] != key[j - 1]))
-            out[rank++] = (int32_t)key[j];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)upto, q * (kDrawThreads / kWave) + (int)scalar((uint32_t)wave)) -
+                                (uint32_t)__popcll(heads[q]);
+        if ((heads[q] >> lane) & 1ull)
+            out[before + bits_below(heads[q])] = (int32_t)key[q];
+    }
     if (!PLACE && tid == 0)
         a.mb_count[i] = total;
 }
@@ -1329,10 +1472,12 @@ void launch_ldw_p_copy(const Launch &L, const LwHop &a)
 
 void launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)
 {
-    if (lb)
-        hipLaunchKernelGGL(ldw_draw_kernel<true>, dim3(a.k), dim3(1024), 0, L.stream, a, *lb, ncols_out);
-    else
-        hipLaunchKernelGGL(ldw_draw_kernel<false>, dim3(a.k), dim3(1024), 0, L.stream, a, Lookback{}, ncols_out);
+    void (*const kernels[2][3])(LwHop, Lookback, int64_t *) = {
+        {ldw_draw_kernel<false, 1>, ldw_draw_kernel<false, 2>, ldw_draw_kernel<false, 4>},
+        {ldw_draw_kernel<true, 1>, ldw_draw_kernel<true, 2>, ldw_draw_kernel<true, 4>}};
+    static_assert(kMaxWinSampled <= 4 * kDrawThreads, "the sort is too short");
+    const int per = a.s <= kDrawThreads ? 0 : a.s <= 2 * kDrawThreads ? 1 : 2;
+    hipLaunchKernelGGL(kernels[lb ? 1 : 0][per], dim3(a.k), dim3(kDrawThreads), 0, L.stream, a, lb ? *lb : Lookback{}, ncols_out);
 }
 
 void launch_ldw_sel_copy(const Launch &L, const LwHop &a)

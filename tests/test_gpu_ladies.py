@@ -255,3 +255,15 @@ def test_windows_from_empty_to_nearly_full(mods, rows, degree, squared):
                           for _ in range(rows)]).astype(np.int32)
     batches = np.stack([rng.permutation(rows), rng.permutation(rows)]).astype(np.int32)
     _run_both(mods, rowptr, col, batches, (64,), 31, squared=squared)
+
+
+@pytest.mark.parametrize("s", [64, 513, 1024, 1025, 2049, 4096])
+@pytest.mark.parametrize("n,degree,squared", [(12, 1, False), (40, 2, True), (60_000, 80, False)])
+def test_draws_from_hardly_any_entries_to_many_blocks(mods, n, degree, squared, s):
+    # 1, 2 or 4 draws per thread; P of fewer than 16 entries in all, of a few blocks of 16 that minibatches share, and of more
+    # blocks than the 2048 groups the search keeps (a row of weight sums at every block's end)
+    rng = np.random.default_rng(n + s)
+    rowptr = np.arange(n + 1, dtype=np.int64) * degree
+    col = np.concatenate([np.sort(rng.choice(n, degree, replace=False)) for _ in range(n)]).astype(np.int32)
+    batches = random_batches(n, 3, min(n // 4, 900), rng)
+    _run_both(mods, rowptr, col, batches, (s,), 7, mb_base=1, squared=squared)
