@@ -177,6 +177,13 @@ __device__ inline uint32_t bits_below(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Entries v and v + 1 of a CSR's row pointers in one read (8-byte aligned)
+using int64x2_a8 = int64_t __attribute__((ext_vector_type(2), aligned(8)));
+__device__ inline int64x2_a8 row_extent(const int64_t *rowptr, int64_t v)
+{
+    return *reinterpret_cast<const int64x2_a8 *>(rowptr + v);
+}
+
 // A workgroup's number in its launch, in the order of starting: whoever waits for lower numbers waits for workgroups that
 // have started.  smem: one word of LDS.
 __device__ inline uint32_t take_number(const Lookback &lb, uint32_t *smem)

@@ -71,56 +71,104 @@ __device__ inline int32_t wave_replace_draws(volatile uint32_t *buf, uint64_t ke
     return m;
 }
 
+// The row tiles that a wave visits.  Tiles of all minibatches are put in order of their place in the minibatch (of `most` steps,
+// the number that the largest has, those of a smaller one are spread evenly), minibatch by minibatch within a step, and each die
+// takes an eighth of that order.  The rows of a minibatch ascend by vertex id, so what runs at the same time on a die touches one
+// part of the id range in all minibatches: a line of rowptr that several minibatches need is fetched once and is in the die's own
+// cache when the next one asks.
+constexpr int kDies = 8;
+struct TileWalk {
+    int32_t k, i, step_i, left; // i: minibatch
+    int64_t j, most, step_j;
+    // workgroups are dealt to the dies in turn; wave `part` of `parts` in the workgroup; gridDim.x is a multiple of kDies
+    __device__ TileWalk(const NwHop &a, uint32_t part, uint32_t parts) : k(a.k), most(uniform_load(a.mb_tileoff + a.k + 1))
+    {
+        const int64_t items = most * k, per = (items + kDies - 1) / kDies;
+        const int64_t lo = (blockIdx.x % kDies) * per, hi = min<int64_t>(lo + per, items);
+        const int64_t pos = lo + (blockIdx.x / kDies) * parts + part;
+        const int32_t step = gridDim.x / kDies * parts;
+        left = pos < hi ? (int32_t)((hi - pos + step - 1) / step) : 0;
+        i = (int32_t)(pos % k);
+        j = pos / k;
+        step_i = step % k;
+        step_j = step / k;
+    }
+    __device__ bool more() const { return left > 0; }
+    __device__ void next()
+    {
+        --left;
+        i += step_i;
+        j += step_j;
+        if (i >= k) {
+            i -= k;
+            ++j;
+        }
+    }
+    // number of the tile among all, or -1 when the minibatch has none at this step; its rows
+    __device__ int64_t tile(const NwHop &a, int64_t &r0, int32_t &rows) const
+    {
+        const int64_t t0 = uniform_load(a.mb_tileoff + i), tiles = uniform_load(a.mb_tileoff + i + 1) - t0;
+        int64_t jj = j;
+        if (tiles != most && most < 65536) // tile q is visited in step floor(q most / tiles) (larger ones: in step q)
+            jj = ((uint32_t)j * (uint32_t)tiles + (uint32_t)most - 1u) / (uint32_t)most;
+        if (jj >= tiles || (tiles != most && most < 65536 && ((uint32_t)jj * (uint32_t)most) / (uint32_t)tiles != j))
+            return -1;
+        r0 = uniform_load(a.mb_rowoff + i) + jj * kRowTile;
+        rows = (int32_t)min<int64_t>(uniform_load(a.mb_rowoff + i + 1) - r0, kRowTile);
+        return t0 + jj;
+    }
+};
+
 // S = 0: rows keep min(degree, s) entries.  S > 0: independent draws, s <= S; the row's length is the number
 // of distinct picks.
+// What bounds it is the number of rowptr lines on their way.  A wave takes a tile of its own, four rows per lane, and needs no
+// barrier.  Two hops each: 256 x 1024 seeds, (15, 10, 5), 111 M vertices: 265 -> 235 us; 128 minibatches on 8.7 M vertices:
+// 236 -> 186 us; 32 on 2.4 M: 71 -> 56 us.  Of workgroups per compute unit, 4 are best: 1, 2, 4 and 16 take 238, 199, 186 and
+// 193 us (8.7 M vertices), 77, 63, 56 us (2.4 M): fewer have too few lines on their way, more touch a larger part of the ids.
+constexpr int kTileRounds = kRowTile / kWave;
 template <int S>
 __global__ __launch_bounds__(kRowTile) void nw_rows_kernel(NwHop a)
 {
-    __shared__ int64_t wsum[kRowTile / kWave];
-    const int tid = threadIdx.x;
-    // Tile j of every minibatch before tile j + 1 of any: the rows of a minibatch ascend by vertex id, so the
-    // workgroups that run at the same time touch the same part of the id range in all minibatches, and lines of
-    // rowptr / col that several minibatches need are still in the last-level cache when the next one asks.
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
     for (int64_t q = (int64_t)blockIdx.x * kRowTile + tid; q < a.zero_quads; q += (int64_t)gridDim.x * kRowTile)
         a.zero[q] = make_uint4(0, 0, 0, 0);
-    const int64_t most = a.mb_tileoff[a.k + 1]; // tiles of the minibatch that has most
-    for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x) {
-        const int i = (int)(v % a.k);
-        const int64_t j = v / a.k;
-        if (j >= a.mb_tileoff[i + 1] - a.mb_tileoff[i])
+    for (TileWalk walk(a, scalar((uint32_t)(tid / kWave)), kRowTile / kWave); walk.more(); walk.next()) {
+        int64_t r0;
+        int32_t rows;
+        const int64_t t = walk.tile(a, r0, rows);
+        if (t < 0)
             continue;
-        const int64_t t = a.mb_tileoff[i] + j;
-        const int64_t r = a.mb_rowoff[i] + j * kRowTile + tid;
+        const int32_t *__restrict__ from = a.row_vertex + r0;
+        int32_t v[kTileRounds];
+#pragma unroll
+        for (int u = 0; u < kTileRounds; ++u)
+            v[u] = u * kWave + lane < rows ? from[u * kWave + lane] : -1;
+        int64x2_a8 extent[kTileRounds];
+#pragma unroll
+        for (int u = 0; u < kTileRounds; ++u) {
+            extent[u] = int64x2_a8{0, 0};
+            if (v[u] >= 0 && (int64_t)v[u] < a.n) // seeds are verified separately; never read out of bounds
+                extent[u] = row_extent(a.A_rowptr, v[u]);
+        }
         int64_t cnt = 0;
-        if (r < a.mb_rowoff[i + 1]) {
-            const int32_t v = a.row_vertex[r];
-            int64_t beg = 0, deg = 0;
-            if (v >= 0 && (int64_t)v < a.n) { // seeds are verified separately; never read out of bounds
-                beg = a.A_rowptr[v];
-                deg = a.A_rowptr[v + 1] - beg;
-            }
-            a.row_beg[r] = beg;
-            a.row_deg[r] = (int32_t)deg;
+#pragma unroll
+        for (int u = 0; u < kTileRounds; ++u) {
+            if (u * kWave + lane >= rows)
+                continue;
+            const int32_t deg = (int32_t)(extent[u][1] - extent[u][0]);
+            a.row_beg[r0 + u * kWave + lane] = extent[u][0];
+            a.row_deg[r0 + u * kWave + lane] = deg;
             if (S == 0) {
-                cnt = deg < a.s ? deg : a.s;
+                cnt += deg < a.s ? deg : a.s;
             } else if (deg > 0) {
                 uint32_t c[S > 0 ? S : 1];
-                cnt = replace_draws(row_key(a.hopkey, a.mb_base + (uint32_t)i, (uint32_t)v), (uint32_t)deg, a.s, c);
+                cnt += replace_draws(row_key(a.hopkey, a.mb_base + (uint32_t)walk.i, (uint32_t)v[u]), (uint32_t)deg, a.s, c);
             }
             cnt += a.self_entry;
         }
-        cnt = wave_sum(cnt);
-        __syncthreads();
-        if ((tid & (kWave - 1)) == 0)
-            wsum[tid / kWave] = cnt;
-        __syncthreads();
-        if (tid == 0) {
-            int64_t tot = 0;
-#pragma unroll
-            for (int w = 0; w < kRowTile / kWave; ++w)
-                tot += wsum[w];
-            a.tile_off[t] = tot;
-        }
+        const uint32_t low = wave_inclusive_scan_dpp((uint32_t)cnt & 0xFFFFFFu), high = wave_inclusive_scan_dpp((uint32_t)(cnt >> 24));
+        if (lane == kWave - 1)
+            a.tile_off[t] = ((int64_t)high << 24) + low;
     }
 }
 
@@ -200,7 +248,8 @@ __global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(
 void launch_nw_rows(const Launch &L, const NwHop &a)
 {
     const int64_t tiles = std::max(a.rows_bound / kRowTile + a.k, a.zero_quads / (8 * kRowTile));
-    const dim3 grid(grid_for(L, tiles, 16)), block(kRowTile);
+    const int64_t wgs = std::max((a.rows_bound / kRowTile + a.k) / (kRowTile / kWave) + 1, a.zero_quads / (8 * kRowTile));
+    const dim3 grid((grid_for(L, wgs, 4) + kDies - 1) / kDies * kDies), block(kRowTile);
     if (!a.replace)
         hipLaunchKernelGGL(nw_rows_kernel<0>, grid, block, 0, L.stream, a);
     else if (a.s <= 4)
@@ -271,7 +320,8 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
     int64_t beg, beg_next;
     int32_t deg, deg_next;
     extent(blockIdx.x, beg, deg);
-    for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x, beg = beg_next, deg = deg_next) { // same order as nw_rows_kernel
+    for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x, beg = beg_next, deg = deg_next) {
+        // tile j of every minibatch before tile j + 1 of any (TileWalk's order brings nothing here)
         extent(v + gridDim.x, beg_next, deg_next);
         const int i = (int)(v % a.k);
         const int64_t j = v / a.k;

@@ -537,3 +537,24 @@ def test_result_recycled_with_another_graph_at_the_address_of_the_old_one(mods):
             assert_hops_equal(res.hops(), ref, what="graph %d call %d" % (g, call))
         for c in handles:
             c.free()
+
+
+@pytest.mark.parametrize("k,replace", [(1, False), (7, False), (7, True), (40, False)])
+def test_row_tiles_of_minibatches_of_very_different_size(mods, k, replace):
+    # second-hop frontiers of no row, one tile and dozens side by side: every tile is visited once, whatever the share of steps
+    # that its minibatch has
+    O, bms, _ = mods
+    rng = np.random.default_rng(k)
+    n, b = 60_000, 500
+    degree = np.zeros(n, dtype=np.int64)
+    for i in range(k): # seeds of minibatch i: ids from i b on
+        degree[i * b:(i + 1) * b] = [0, 1, 3, 40, 40, 0, 12][(i + 3) % 7]
+    degree[k * b:] = rng.integers(0, 6, n - k * b)
+    rowptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, d, replace=False)) for d in degree]).astype(np.int32)
+    batches = np.arange(k * b, dtype=np.int32).reshape(k, b)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, (30, 4, 3), 5, replace=replace)
+    for extract in ("sort", "bitmap"):
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (30, 4, 3), 5, extract=extract, replace=replace)
+        assert_hops_equal(res.hops(), ref, what="extract=%s" % extract)
