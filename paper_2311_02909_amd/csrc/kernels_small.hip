@@ -5,10 +5,10 @@
 // launch (2.4 us of host time, about 4 us of device time) however little it moves.  Here a minibatch's sampled ids never leave
 // LDS:
 //   seeds    checked against an LDS hash table (range, repeats), copied to the first frontier
-//   sample   one row per lane: extent, draws, the chosen neighbours gathered into LDS
-//   sort     the positions by id: through 16384 buckets of about one id each, or, when the ids crowd some of them, by
-//            counting passes of 8 bits, as many as n has
-//   rank     heads of the runs of equal ids, counted: local column of every position, distinct ids ascending
+//   sample   one row per lane: extent, draws, the chosen neighbours fetched into registers, all at once
+//   rank     the entries' places by id: through 16384 buckets of about one id each, or, when the ids crowd some of them, by
+//            a sort in counting passes of 8 bits, as many as n has; distinct ids counted: local column of every entry
+//            and, in LDS, the distinct ids ascending, which are the next hop's rows
 //   place    where the minibatch's rows, entries and columns lie in the stacked arrays follows from the sizes of the
 //            minibatches before it.  Every workgroup publishes its hop's sizes in one word and adds up the words before
 //            its own.  A workgroup takes its minibatch off a counter when it starts, so the ones it waits for have
@@ -25,6 +25,8 @@
 #include "bms_internal.h"
 #include "nw_draws.h"
 
+#include <type_traits>
+
 namespace bms {
 
 constexpr int kSmThreads = 1024;
@@ -32,46 +34,54 @@ constexpr int kSmWaves = kSmThreads / kWave;
 constexpr int kSmBins = 256;                   // a counting pass takes 8 bits
 constexpr int kSmBuckets = kSmallBuckets;
 constexpr int kSmCrowd = 64;                   // ids per bucket, at most
-constexpr int kSmWork = kSmBuckets / 4 + kSmBuckets / 8; // words: bucket counters and starts, or the counters of the passes
-constexpr int kSmGather = 8;                    // reads of A_col in flight per lane
+constexpr int kSmRounds = kSmallCap / kSmThreads; // entries per thread, at most: entry e is thread e mod 1024's
+constexpr int kSmMaskWords = kSmallCap / 32;
+// words: bucket counters and starts, or the counters of the passes; one bit per place, set bits before each word
+constexpr int kSmSort = kSmBuckets / 4 + kSmBuckets / 8, kSmWork = kSmSort + 2 * kSmMaskWords;
 constexpr uint32_t kSmEmpty = 0xFFFFFFFFu;
-static_assert(kSmWork >= kSmWaves * kSmBins && kSmWork >= 2 * kSmallCap / kWave && kSmBuckets == 16 * kSmThreads, "work area out of step");
+static_assert(kSmSort >= kSmWaves * kSmBins && kSmSort >= 2 * kSmallCap / kWave && kSmBuckets == 16 * kSmThreads &&
+              kSmMaskWords <= kSmThreads && kSmallCap <= 16384, "work area out of step");
 
-// rows r0 .. r0 + nr - 1 (one per lane) of a hop: local offsets of the rows, chosen neighbours into key[R + offset ..]
+__device__ __forceinline__ int64x2_a8 small_extent(const NwSmall &a, int32_t v)
+{
+    int64x2_a8 extent = {0, 0};
+    if (v >= 0 && (int64_t)v < a.n) // a seed outside [0, n) is reported by the seed check: never read out of bounds
+        extent = row_extent(a.A_rowptr, v);
+    return extent;
+}
+
+// The R rows of a hop, one per lane: front[r], the row's vertex, becomes its offset in the minibatch's entries; chosen neighbours,
+// or their places in A_col (flat), go to key[R + offset ..].  v, extent: of row threadIdx.x (v < 0: there is none).
 template <int S, bool REPLACE>
-__device__ __forceinline__ int32_t small_sample_rows(const NwSmall &a, uint64_t hopkey, int32_t s, uint32_t mb,
-                                                     const int32_t *__restrict__ rows, int32_t R, int64_t *__restrict__ rowptr,
-                                                     uint32_t *key, uint32_t *wsum)
+__device__ __forceinline__ int32_t small_sample_rows(const NwSmall &a, uint64_t hopkey, int32_t s, uint32_t mb, int32_t R, int32_t v,
+                                                     int64x2_a8 extent, uint32_t *front, uint32_t *key, uint32_t *wsum)
 {
     const int tid = threadIdx.x;
     int32_t run = 0;
     for (int32_t r0 = 0; r0 < R; r0 += kSmThreads) {
-        const int32_t r = r0 + tid;
-        int32_t v = -1, deg = 0, cnt = 0;
-        int64_t beg = 0;
-        uint32_t c[S];
-        if (r < R) {
-            v = rows[r];
-            if (v >= 0 && (int64_t)v < a.n) { // a seed outside [0, n) is reported by the seed check: never read out of bounds
-                beg = a.A_rowptr[v];
-                deg = (int32_t)(a.A_rowptr[v + 1] - beg);
-            }
-            cnt = deg < s ? deg : s;
-            if (REPLACE && deg > 0)
-                cnt = replace_draws<S>(row_key(hopkey, mb, (uint32_t)v), (uint32_t)deg, s, c);
+        const int32_t r = r0 + tid, now = v;
+        const int64_t beg = extent[0];
+        const int32_t deg = (int32_t)(extent[1] - extent[0]);
+        if (r0 + kSmThreads < R) {
+            v = r + kSmThreads < R ? (int32_t)front[r + kSmThreads] : -1;
+            extent = small_extent(a, v);
         }
+        int32_t cnt = deg < s ? deg : s;
+        uint32_t c[S];
+        if (REPLACE && deg > 0)
+            cnt = replace_draws<S>(row_key(hopkey, mb, (uint32_t)now), (uint32_t)deg, s, c);
         uint32_t total;
         const int32_t loc = run + (int32_t)block_exclusive_scan<uint32_t, kSmThreads>((uint32_t)cnt, wsum, total);
         if (r < R) {
-            rowptr[r] = loc; // the entries of the minibatches before this one are added when they are known
+            front[r] = (uint32_t)loc;
             if (a.self_entry)
-                key[r] = (v >= 0 && (int64_t)v < a.n) ? (uint32_t)v : 0u;
+                key[r] = (now >= 0 && (int64_t)now < a.n) ? (uint32_t)now : 0u;
         }
         if (cnt > 0) {
             uint32_t *dst = key + (a.self_entry ? R : 0) + loc;
             if (!REPLACE && deg > s)
-                distinct_draws<S>(row_key(hopkey, mb, (uint32_t)v), (uint32_t)deg, s, c);
-            if (a.flat) { // the neighbours follow below
+                distinct_draws<S>(row_key(hopkey, mb, (uint32_t)now), (uint32_t)deg, s, c);
+            if (a.flat) { // the neighbours follow when all rows have chosen theirs
                 int32_t m = 0;
 #pragma unroll
                 for (int j = 0; j < S; ++j)
@@ -90,51 +100,46 @@ __device__ __forceinline__ int32_t small_sample_rows(const NwSmall &a, uint64_t 
         }
         run += (int32_t)total;
     }
-    if (a.flat) { // places in A_col -> the neighbours there, the picks of a row in neighbouring lanes (one request per line)
-        uint32_t *entry = key + (a.self_entry ? R : 0);
-        __syncthreads();
-        for (int32_t e0 = tid; e0 < run; e0 += kSmGather * kSmThreads) {
-            uint32_t g[kSmGather];
-#pragma unroll
-            for (int u = 0; u < kSmGather; ++u)
-                if (e0 + u * kSmThreads < run)
-                    g[u] = (uint32_t)a.A_col[entry[e0 + u * kSmThreads]];
-#pragma unroll
-            for (int u = 0; u < kSmGather; ++u)
-                if (e0 + u * kSmThreads < run)
-                    entry[e0 + u * kSmThreads] = g[u];
-        }
-    }
     return run;
 }
 
-// Sorted order of N ids by 16384 buckets of equal id ranges (about one id each when n is large): counted (8 bits per
-// bucket), scanned, every id to its bucket's places, and there to its final one by comparing it with the few others.
-// Returns the array that holds the order, or null when a bucket holds more than kSmCrowd ids (a hub that many rows
-// sampled, ids crowded into a narrow range): the counting passes take those.
-__device__ __forceinline__ uint16_t *small_sort_buckets(const NwSmall &a, const uint32_t *key, uint16_t *pa, uint16_t *pb,
-                                                        uint32_t *work, int32_t N, uint32_t *wsum, uint32_t *crowded_s)
+// Local columns of N entries, id[] (entry u * 1024 + threadIdx.x in id[u]), by 16384 buckets of equal id ranges (about one id each
+// when n is large): counted (8 bits per bucket), scanned, every id to its bucket's places, and there compared with the few
+// others: an entry's first possible place, bucket's start + smaller ids in it, gets a bit, and its column is the number of
+// bits before.  Returns false, with key[] as it was, when a bucket holds more than kSmCrowd ids (a hub that many rows
+// sampled, ids crowded into a narrow range): the counting passes take those.  key: cap words that may be overwritten; the counters
+// and the bits are zero on entry.
+template <int ROUNDS>
+__device__ __forceinline__ bool small_rank_buckets(const NwSmall &a, const uint32_t (&id)[ROUNDS], uint32_t (&col)[ROUNDS],
+                                                   uint32_t *key, uint32_t *work, int32_t N, uint32_t *wsum, uint32_t *crowded_s,
+                                                   uint32_t &distinct)
 {
     const int tid = threadIdx.x;
     uint32_t *cnt = work;                                               // 4 counters of 8 bits per word
     uint16_t *start = reinterpret_cast<uint16_t *>(work + kSmBuckets / 4); // ids before the word's first bucket
-    auto bucket = [&](uint32_t id) { return a.bucket_mul ? __umulhi(id, a.bucket_mul) : id; };
-    reinterpret_cast<uint4 *>(cnt)[tid] = make_uint4(0, 0, 0, 0); // kSmBuckets / 4 = 4 words per thread
-    if (tid == 0)
-        *crowded_s = 0;
-    __syncthreads();
-    for (int32_t e = tid; e < N; e += kSmThreads) {
-        const uint32_t d = bucket(key[e]), sh = 8u * (d & 3u);
-        const uint32_t slot = (atomicAdd(&cnt[d >> 2], 1u << sh) >> sh) & 255u;
-        if (slot >= (uint32_t)kSmCrowd)
-            *crowded_s = 1; // seen by whoever adds the first id too many, before the counter can run over
-        pb[e] = (uint16_t)slot;
-    }
+    uint32_t *mask = work + kSmSort, *before = mask + kSmMaskWords;
+    auto bucket = [&](uint32_t x) { return a.bucket_mul ? __umulhi(x, a.bucket_mul) : x; };
+    const int32_t mine = N - tid; // entries from the thread's first on
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u)
+        if (u * kSmThreads < mine) {
+            const uint32_t d = bucket(id[u]);
+            col[u] = atomicAdd(&cnt[d >> 2], 1u << (8u * (d & 3u)));
+        }
+    bool crowded = false; // seen by whoever adds the first id too many, whatever the counter does after that
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u)
+        if (u * kSmThreads < mine) {
+            col[u] = (col[u] >> (8u * (bucket(id[u]) & 3u))) & 255u;
+            crowded |= col[u] >= (uint32_t)kSmCrowd;
+        }
+    if (crowded)
+        *crowded_s = 1;
     __syncthreads();
     if (*crowded_s)
-        return nullptr; // the same for the whole workgroup
+        return false; // the same for the whole workgroup
     {
-        const uint4 w = reinterpret_cast<const uint4 *>(cnt)[tid];
+        const uint4 w = reinterpret_cast<const uint4 *>(cnt)[tid]; // kSmBuckets / 4 = 4 words per thread
         const uint32_t x[4] = {w.x, w.y, w.z, w.w};
         uint32_t c[4], sum = 0;
 #pragma unroll
@@ -151,36 +156,46 @@ __device__ __forceinline__ uint16_t *small_sort_buckets(const NwSmall &a, const 
         }
     }
     __syncthreads();
-    // first place and size of bucket d
-    auto place = [&](uint32_t d, uint32_t &n) {
-        const uint32_t w = cnt[d >> 2], sh = 8u * (d & 3u);
-        n = (w >> sh) & 255u;
-        const uint32_t lower = w & ((1u << sh) - 1u); // counters of the word's buckets before d: at most three of them
-        return (uint32_t)start[d >> 2] + (lower & 255u) + ((lower >> 8) & 255u) + ((lower >> 16) & 255u);
-    };
-    for (int32_t e = tid; e < N; e += kSmThreads) {
-        uint32_t n;
-        pa[place(bucket(key[e]), n) + pb[e]] = (uint16_t)e;
-    }
-    __syncthreads();
-    for (int32_t t = tid; t < N; t += kSmThreads) {
-        const uint32_t p = pa[t], id = key[p];
-        uint32_t n, to = (uint32_t)t;
-        const uint32_t s0 = place(bucket(id), n);
-        if (n > 1u) {
-            to = s0;
-            for (uint32_t q = s0; q < s0 + n; ++q) {
-                const uint32_t o = key[pa[q]];
-                to += (o < id || (o == id && q < (uint32_t)t)) ? 1u : 0u;
-            }
+    // col[u]: first place (14 bits) and size of the entry's bucket
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u)
+        if (u * kSmThreads < mine) {
+            const uint32_t d = bucket(id[u]), w = cnt[d >> 2], sh = 8u * (d & 3u);
+            const uint32_t lower = w & ((1u << sh) - 1u); // counters of the word's buckets before d: at most three of them
+            const uint32_t s0 = (uint32_t)start[d >> 2] + (lower & 255u) + ((lower >> 8) & 255u) + ((lower >> 16) & 255u);
+            key[s0 + col[u]] = id[u];
+            col[u] = s0 | ((w >> sh) & 255u) << 14;
         }
-        pb[to] = (uint16_t)p;
-    }
     __syncthreads();
-    return pb;
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u)
+        if (u * kSmThreads < mine) {
+            const uint32_t s0 = col[u] & 16383u, n = col[u] >> 14;
+            uint32_t to = s0;
+            if (n > 1u) {
+                const uint32_t x0 = key[s0], x1 = key[s0 + 1], x2 = key[s0 + min(2u, n - 1u)], x3 = key[s0 + min(3u, n - 1u)];
+                to += (x0 < id[u] ? 1u : 0u) + (x1 < id[u] ? 1u : 0u) + (n > 2u && x2 < id[u] ? 1u : 0u) +
+                      (n > 3u && x3 < id[u] ? 1u : 0u);
+                for (uint32_t q = 4; q < n; ++q)
+                    to += key[s0 + q] < id[u] ? 1u : 0u;
+            }
+            atomicOr(&mask[to >> 5], 1u << (to & 31u));
+            col[u] = to;
+        }
+    __syncthreads();
+    const uint32_t bits = tid < kSmMaskWords ? (uint32_t)__popc(mask[tid < kSmMaskWords ? tid : 0]) : 0u;
+    const uint32_t ex = block_exclusive_scan<uint32_t, kSmThreads>(bits, wsum, distinct);
+    if (tid < kSmMaskWords)
+        before[tid] = ex;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u)
+        if (u * kSmThreads < mine)
+            col[u] = before[col[u] >> 5] + (uint32_t)__popc(mask[col[u] >> 5] & ((1u << (col[u] & 31u)) - 1u));
+    return true;
 }
 
-// The same by stable counting passes of 8 bits, whatever the ids: the permutation moves from one array to the other.
+// Sorted order of N ids by stable counting passes of 8 bits, whatever the ids: the permutation moves from one array to the other.
 __device__ __forceinline__ uint16_t *small_sort_radix(int32_t idbits, const uint32_t *key, uint16_t *from, uint16_t *to,
                                                       uint32_t *hist, int32_t N, int32_t e0, int32_t e1, int wave, uint32_t *wsum)
 {
@@ -240,22 +255,106 @@ __device__ __forceinline__ uint16_t *small_sort_radix(int32_t idbits, const uint
     return from;
 }
 
+// The same by the sorted order: heads of its runs of equal ids, counted.  pos: 2 cap words of 16 bits; key[]: the ids.
+template <int ROUNDS>
+__device__ __forceinline__ void small_rank_radix(const NwSmall &a, uint32_t (&col)[ROUNDS], const uint32_t *key, uint16_t *pos,
+                                                 uint32_t *work, int32_t N, uint32_t *wsum, uint32_t &distinct)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave); // the same in every lane: loop bounds stay scalar
+    const uint64_t below = (1ull << lane) - 1ull;
+    // every wave owns `per` consecutive places, 64 of them in each of its steps
+    const int32_t per = ((N + kSmWaves - 1) / kSmWaves + kWave - 1) / kWave * kWave;
+    const int32_t e0 = wave * per, e1 = min(e0 + per, N);
+    uint16_t *by = small_sort_radix(a.idbits, key, pos, pos + a.cap, work, N, e0, e1, wave, wsum);
+    uint16_t *rank_of = by == pos ? pos + a.cap : pos; // the other array is free
+    unsigned long long *mask = reinterpret_cast<unsigned long long *>(work); // one mask per step
+    uint32_t heads = 0;                                                      // of this wave's part
+    for (int32_t eb = e0; eb < e1; eb += kWave) {
+        const int32_t e = eb + lane;
+        const uint32_t id = e < e1 ? key[by[e]] : 0u;
+        uint32_t prev = __shfl_up(id, 1, kWave);
+        if (lane == 0 && e > 0)
+            prev = key[by[e - 1]];
+        const uint64_t hm = __ballot(e < e1 && (e == 0 || prev != id));
+        if (lane == 0)
+            mask[eb / kWave] = hm;
+        heads += (uint32_t)__popcll(hm);
+    }
+    if (lane == 0)
+        wsum[wave] = heads;
+    __syncthreads();
+    uint32_t run = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kSmWaves; ++w) {
+        run += w < wave ? wsum[w] : 0u;
+        all += wsum[w];
+    }
+    distinct = all;
+    const int32_t mine = N - tid;
+    for (int32_t eb = e0; eb < e1; eb += kWave) {
+        const uint64_t hm = mask[eb / kWave];
+        if (eb + lane < e1)
+            rank_of[by[eb + lane]] = (uint16_t)(run + (uint32_t)__popcll(hm & (below | (1ull << lane))) - 1u);
+        run += (uint32_t)__popcll(hm);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < ROUNDS; ++u)
+        if (u * kSmThreads < mine)
+            col[u] = rank_of[u * kSmThreads + tid];
+}
+
+// Sums over the workgroup of three values per thread (a wave's fit 32 bits); `room`: 3 * kSmWaves words
+__device__ __forceinline__ void small_sums(uint32_t x, uint32_t y, uint32_t z, uint32_t *room, int64_t &sx, int64_t &sy, int64_t &sz)
+{
+    const int wave = threadIdx.x / kWave;
+    x = wave_inclusive_scan_dpp(x);
+    y = wave_inclusive_scan_dpp(y);
+    z = wave_inclusive_scan_dpp(z);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) {
+        room[wave] = x;
+        room[kSmWaves + wave] = y;
+        room[2 * kSmWaves + wave] = z;
+    }
+    __syncthreads();
+    sx = sy = sz = 0;
+#pragma unroll
+    for (int w = 0; w < kSmWaves; ++w) {
+        sx += room[w];
+        sy += room[kSmWaves + w];
+        sz += room[2 * kSmWaves + w];
+    }
+}
+
+// One compute unit, a chain of trips to memory and barriers, and for thousands of entries LDS.  Entries stay in
+// registers from the gather to the output, so that an entry's column costs about a dozen LDS accesses and no indirect ones (each
+// id was looked up through a permutation in LDS before); the extract exists for 1, 4 and 16 entries per thread, as the code of
+// rounds that a hop does not have costs too: about 0.5 us in each of 8 phases, fetching instructions only to jump over them.
+// First hop of 1024 seeds, fanout 15, 11 k entries: 43 -> 33 us (gather 7 -> 2, extract 20 -> 11, output 5 -> 2.5); two hops (5, 5)
+// of 4 x 64: 27.5 -> 22.3 us.
 // SMAX: the largest fanout of the hops, 16 or 32 (the position lists of 32 draws spill; 16 do not)
 template <bool REPLACE, int SMAX>
 __global__ __launch_bounds__(kSmThreads) void nw_small_kernel(NwSmall a)
 {
-    extern __shared__ uint32_t small_lds[]; // key[cap], pos[2][cap] (16 bits), work[kSmWork]
-    __shared__ uint32_t wsum[kSmWaves];
-    __shared__ int64_t wsum64[kSmWaves];
+    extern __shared__ uint32_t small_lds[]; // key[cap], front[cap] (which change places from hop to hop), work[kSmWork]
+    __shared__ uint32_t wsum[kSmWaves], sums_s[3 * kSmWaves];
     __shared__ uint32_t take_s, crowded_s;
-    uint32_t *key = small_lds;
-    uint16_t *pos = reinterpret_cast<uint16_t *>(small_lds + a.cap);
-    uint32_t *work = small_lds + 2 * a.cap;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave); // the same in every lane: loop bounds stay scalar
-    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t *key = small_lds, *front = small_lds + a.cap, *work = small_lds + 2 * a.cap;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     if (tid == 0)
         take_s = atomicAdd(a.ticket, 1u) - a.ticket0;
+    auto clear = [&] { // bucket counters and place bits
+        reinterpret_cast<uint4 *>(work)[tid] = make_uint4(0, 0, 0, 0); // kSmBuckets / 4 = 4 words per thread
+        if (tid < kSmMaskWords)
+            work[kSmSort + tid] = 0;
+        if (tid == 0)
+            crowded_s = 0;
+    };
+    clear();
+    const int32_t slots = a.seed_slots; // power of two >= 2 b, within key[]
+    for (int32_t x = tid; x < slots; x += kSmThreads)
+        key[x] = kSmEmpty;
     __syncthreads();
     const int32_t i = __builtin_amdgcn_readfirstlane((int)take_s);
     const bool last = i == a.k - 1;
@@ -266,137 +365,152 @@ __global__ __launch_bounds__(kSmThreads) void nw_small_kernel(NwSmall a)
             a.slots[63] = 0;
     }
 
-    // seeds
+    // seeds; the extents of the first of them are fetched meanwhile
     int32_t R = a.b;
     int64_t row0 = (int64_t)i * a.b; // first stacked row
-    {
-        const int32_t slots = a.seed_slots; // power of two >= 2 b, within key[]
-        for (int32_t x = tid; x < slots; x += kSmThreads)
-            key[x] = kSmEmpty;
-        if (tid == 0)
-            a.mb_rowoff0[i] = row0;
-        if (last && tid == 0)
-            a.mb_rowoff0[a.k] = row0 + a.b;
-        __syncthreads();
-        for (int32_t j = tid; j < a.b; j += kSmThreads) {
-            const int32_t v = a.batches[row0 + j];
-            a.row_vertex0[row0 + j] = v;
-            if (v < 0 || (int64_t)v >= a.n) {
-                a.seed_flags[0] = 1;
-                continue;
-            }
-            uint32_t slot = ((uint32_t)v * 0x9E3779B1u) >> a.seed_shift;
-            while (true) {
-                const uint32_t old = atomicCAS(&key[slot], kSmEmpty, (uint32_t)v);
-                if (old == kSmEmpty)
-                    break;
-                if (old == (uint32_t)v) {
-                    a.seed_flags[1] = 1;
-                    break;
-                }
-                slot = (slot + 1u) & (uint32_t)(slots - 1);
-            }
+    int32_t v = tid < R ? a.batches[row0 + tid] : -1;
+    int64x2_a8 extent = small_extent(a, v);
+    if (tid == 0)
+        a.mb_rowoff0[i] = row0;
+    if (last && tid == 0)
+        a.mb_rowoff0[a.k] = row0 + a.b;
+    for (int32_t j = tid; j < a.b; j += kSmThreads) {
+        const int32_t x = j == tid ? v : a.batches[row0 + j];
+        front[j] = (uint32_t)x;
+        a.row_vertex0[row0 + j] = x;
+        if (x < 0 || (int64_t)x >= a.n) {
+            a.seed_flags[0] = 1;
+            continue;
         }
-        __syncthreads();
+        uint32_t slot = ((uint32_t)x * 0x9E3779B1u) >> a.seed_shift;
+        while (true) {
+            const uint32_t old = atomicCAS(&key[slot], kSmEmpty, (uint32_t)x);
+            if (old == kSmEmpty)
+                break;
+            if (old == (uint32_t)x) {
+                a.seed_flags[1] = 1;
+                break;
+            }
+            slot = (slot + 1u) & (uint32_t)(slots - 1);
+        }
     }
+    __syncthreads();
 
-    const int32_t *rows = a.row_vertex0 + row0;
     int64_t rows_total = (int64_t)a.k * a.b; // (of the last minibatch only)
     for (int32_t h = 0; h < a.nhops; ++h) {
         const NwSmallHop &H = a.hop[h];
         const uint32_t mb = a.mb_base + (uint32_t)i;
-        int64_t *rowptr = H.rowptr + row0;
         int32_t nnz;
         if (H.s <= 4)
-            nnz = small_sample_rows<4, REPLACE>(a, H.hopkey, H.s, mb, rows, R, rowptr, key, wsum);
+            nnz = small_sample_rows<4, REPLACE>(a, H.hopkey, H.s, mb, R, v, extent, front, key, wsum);
         else if (H.s <= 8)
-            nnz = small_sample_rows<8, REPLACE>(a, H.hopkey, H.s, mb, rows, R, rowptr, key, wsum);
+            nnz = small_sample_rows<8, REPLACE>(a, H.hopkey, H.s, mb, R, v, extent, front, key, wsum);
         else if (SMAX == 16 || H.s <= 16)
-            nnz = small_sample_rows<16, REPLACE>(a, H.hopkey, H.s, mb, rows, R, rowptr, key, wsum);
+            nnz = small_sample_rows<16, REPLACE>(a, H.hopkey, H.s, mb, R, v, extent, front, key, wsum);
         else
-            nnz = small_sample_rows<SMAX, REPLACE>(a, H.hopkey, H.s, mb, rows, R, rowptr, key, wsum);
+            nnz = small_sample_rows<SMAX, REPLACE>(a, H.hopkey, H.s, mb, R, v, extent, front, key, wsum);
         const int32_t self = a.self_entry ? R : 0; // entries [0, self): the rows' own vertices, then the sampled ones
-        const int32_t N = nnz + self;
+        const int32_t N = __builtin_amdgcn_readfirstlane(nnz + self); // the same in all lanes
         __syncthreads();
 
-        // sorted order of the entries by id: by[x] = position of the x-th smallest.  Every wave owns `per` consecutive
-        // places, 64 of them in each of its steps
-        const int32_t per = ((N + kSmWaves - 1) / kSmWaves + kWave - 1) / kWave * kWave;
-        const int32_t e0 = wave * per, e1 = min(e0 + per, N);
-        uint16_t *by = small_sort_buckets(a, key, pos, pos + a.cap, work, N, wsum, &crowded_s);
-        if (!by)
-            by = small_sort_radix(a.idbits, key, pos, pos + a.cap, work, N, e0, e1, wave, wsum);
-        uint16_t *rank_of = by == pos ? pos + a.cap : pos; // the other array is free
-
-        // heads of the runs of equal ids, one mask per step
-        unsigned long long *mask = reinterpret_cast<unsigned long long *>(work);
-        uint32_t heads = 0; // of this wave's part
-        for (int32_t eb = e0; eb < e1; eb += kWave) {
-            const int32_t e = eb + lane;
-            const uint32_t id = e < e1 ? key[by[e]] : 0u;
-            uint32_t prev = __shfl_up(id, 1, kWave);
-            if (lane == 0 && e > 0)
-                prev = key[by[e - 1]];
-            const uint64_t hm = __ballot(e < e1 && (e == 0 || prev != id));
-            if (lane == 0)
-                mask[eb / kWave] = hm;
-            heads += (uint32_t)__popcll(hm);
-        }
-        if (lane == 0)
-            wsum[wave] = heads;
-        __syncthreads();
-        uint32_t before = 0, U = 0;
+        uint32_t U; // distinct ids = columns
+        const bool tiles_wanted = h == a.nhops - 1 && a.next_tileoff; // of the hop that follows on the chip-wide path
+        int64_t edge0 = 0, col0 = 0, tile0 = 0; // entries, columns and row tiles of the minibatches before this one
+        int32_t most = 0;
+        // EXTRACT of N <= ROUNDS * 1024 entries.  By buckets, or, with the ids in key[], by the sort.  False: the ids crowd some
+        // buckets; they are in key[] and nothing else has been done.
+        auto extract = [&](auto rounds, auto sorted) __attribute__((always_inline))
+        {
+            constexpr int ROUNDS = decltype(rounds)::value;
+            constexpr bool SORTED = decltype(sorted)::value;
+            // the entries' ids, in registers from here on: places in A_col -> the neighbours there, the picks of a row in
+            // neighbouring lanes (one request per line), all of them on their way at once
+            uint32_t id[ROUNDS], col[ROUNDS];
+            const int32_t mine = N - tid, sampled = self - tid; // the thread has entry u when u * 1024 < mine, a sampled one from `sampled` on
 #pragma unroll
-        for (int w = 0; w < kSmWaves; ++w) {
-            before += w < wave ? wsum[w] : 0u;
-            U += wsum[w];
-        }
-        // sizes of this minibatch for everyone after it
-        unsigned long long *status = a.status + (int64_t)h * a.k;
-        if (tid == 0)
-            __hip_atomic_store(status + i, ((unsigned long long)a.epoch << 32) | ((unsigned long long)(uint32_t)nnz << 16) | U,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // local columns by position
-        uint32_t run = before;
-        for (int32_t eb = e0; eb < e1; eb += kWave) {
-            const uint64_t hm = mask[eb / kWave];
-            if (eb + lane < e1)
-                rank_of[by[eb + lane]] = (uint16_t)(run + (uint32_t)__popcll(hm & (below | (1ull << lane))) - 1u);
-            run += (uint32_t)__popcll(hm);
-        }
-        // entries, columns and row tiles of the minibatches before this one
-        int64_t sum_e = 0, sum_c = 0, sum_t = 0;
-        int32_t most = (int32_t)((U + kRowTile - 1) / kRowTile);
-        for (int32_t j = tid; j < i; j += kSmThreads) {
-            unsigned long long w;
-            while ((uint32_t)((w = __hip_atomic_load(status + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != a.epoch)
-                __builtin_amdgcn_s_sleep(2);
-            const int32_t cols = (int32_t)(w & 0xFFFFu), tiles = (cols + kRowTile - 1) / kRowTile;
-            sum_e += (int64_t)((w >> 16) & 0xFFFFu);
-            sum_c += cols;
-            sum_t += tiles;
-            most = tiles > most ? tiles : most;
-        }
-        int64_t total;
-        (void)block_exclusive_scan<int64_t, kSmThreads>(sum_e, wsum64, total);
-        const int64_t edge0 = total;
-        (void)block_exclusive_scan<int64_t, kSmThreads>(sum_c, wsum64, total);
-        const int64_t col0 = total;
-        __syncthreads();
-
-        for (int32_t r = tid; r < R; r += kSmThreads)
-            rowptr[r] += edge0; // written by this thread
-        for (int32_t e = tid; e < nnz; e += kSmThreads)
-            H.col[edge0 + e] = (int32_t)rank_of[self + e];
-        for (int32_t r = tid; r < self; r += kSmThreads)
-            H.row_self[row0 + r] = (int32_t)rank_of[r];
-        run = before;
-        for (int32_t eb = e0; eb < e1; eb += kWave) {
-            const uint64_t hm = mask[eb / kWave];
-            if ((hm >> lane) & 1ull)
-                H.col_vertex[col0 + run + (uint32_t)__popcll(hm & below)] = (int32_t)key[by[eb + lane]];
-            run += (uint32_t)__popcll(hm);
-        }
+            for (int u = 0; u < ROUNDS; ++u)
+                id[u] = u * kSmThreads < mine ? key[u * kSmThreads + tid] : 0u;
+            if (!SORTED && a.flat && nnz > 0) {
+#pragma unroll
+                for (int u = 0; u < ROUNDS; ++u)
+                    if (u * kSmThreads < N) // self entries read place 0
+                        col[u] = (uint32_t)a.A_col[u * kSmThreads >= sampled && u * kSmThreads < mine ? id[u] : 0u];
+#pragma unroll
+                for (int u = 0; u < ROUNDS; ++u)
+                    if (u * kSmThreads < N)
+                        id[u] = u * kSmThreads >= sampled ? col[u] : id[u];
+            }
+            if constexpr (SORTED) {
+                for (int32_t r = tid; r < R; r += kSmThreads) // front[] serves as the order meanwhile
+                    H.rowptr[row0 + r] = front[r];
+                __syncthreads();
+                small_rank_radix<ROUNDS>(a, col, key, reinterpret_cast<uint16_t *>(front), work, N, wsum, U);
+                __syncthreads();
+                for (int32_t r = tid; r < R; r += kSmThreads)
+                    front[r] = (uint32_t)H.rowptr[row0 + r]; // written by this thread
+            } else if (!small_rank_buckets<ROUNDS>(a, id, col, key, work, N, wsum, &crowded_s, U)) {
+#pragma unroll
+                for (int u = 0; u < ROUNDS; ++u)
+                    if (u * kSmThreads < mine)
+                        key[u * kSmThreads + tid] = id[u];
+                __syncthreads();
+                return false;
+            }
+            // sizes of this minibatch for everyone after it
+            unsigned long long *status = a.status + (int64_t)h * a.k;
+            if (tid == 0)
+                __hip_atomic_store(status + i, ((unsigned long long)a.epoch << 32) | ((unsigned long long)(uint32_t)nnz << 16) | U,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // the distinct ids in order, which are the next hop's rows (equal entries write the same)
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u)
+                if (u * kSmThreads < mine)
+                    key[col[u]] = id[u];
+            most = (int32_t)((U + kRowTile - 1) / kRowTile);
+            if (i > 0) {
+                uint32_t sum_e = 0, sum_c = 0, sum_t = 0;
+                for (int32_t j = tid; j < i; j += kSmThreads) {
+                    unsigned long long w;
+                    while ((uint32_t)((w = __hip_atomic_load(status + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != a.epoch)
+                        __builtin_amdgcn_s_sleep(2);
+                    const int32_t cols = (int32_t)(w & 0xFFFFu), tiles = (cols + kRowTile - 1) / kRowTile;
+                    sum_e += (uint32_t)((w >> 16) & 0xFFFFu);
+                    sum_c += (uint32_t)cols;
+                    sum_t += (uint32_t)tiles;
+                    most = tiles > most ? tiles : most;
+                }
+                small_sums(sum_e, sum_c, sum_t, sums_s, edge0, col0, tile0);
+            } else {
+                __syncthreads(); // key[] is whole
+            }
+            if (h + 1 < a.nhops) { // extents of the next hop's first rows
+                v = tid < (int32_t)U ? (int32_t)key[tid] : -1;
+                extent = small_extent(a, v);
+            }
+            int64_t *rowptr = H.rowptr + row0;
+            for (int32_t r = tid; r < R; r += kSmThreads)
+                rowptr[r] = edge0 + front[r];
+#pragma unroll
+            for (int u = 0; u < ROUNDS; ++u) {
+                if (u * kSmThreads < sampled)
+                    (H.row_self + row0 + u * kSmThreads)[tid] = (int32_t)col[u];
+                else if (u * kSmThreads < mine)
+                    (H.col + edge0 - self + u * kSmThreads)[tid] = (int32_t)col[u];
+            }
+            for (int32_t r = tid; r < (int32_t)U; r += kSmThreads)
+                H.col_vertex[col0 + r] = (int32_t)key[r];
+            return true;
+        };
+        using std::integral_constant;
+        bool done;
+        if (N <= kSmThreads)
+            done = extract(integral_constant<int, 1>{}, std::false_type{});
+        else if (N <= 4 * kSmThreads)
+            done = extract(integral_constant<int, 4>{}, std::false_type{});
+        else
+            done = extract(integral_constant<int, kSmRounds>{}, std::false_type{});
+        if (!done)
+            extract(integral_constant<int, kSmRounds>{}, std::true_type{});
         if (tid == 0) {
             H.mb_coloff[i] = col0;
             if (a.host_off) {
@@ -411,23 +525,20 @@ __global__ __launch_bounds__(kSmThreads) void nw_small_kernel(NwSmall a)
                 }
             }
         }
-        if (h == a.nhops - 1 && a.next_tileoff) { // row tiles of the hop that follows on the chip-wide path
-            (void)block_exclusive_scan<int64_t, kSmThreads>(sum_t, wsum64, total);
+        if (tiles_wanted) {
             if (tid == 0)
-                a.next_tileoff[i] = total;
+                a.next_tileoff[i] = tile0;
             if (last) {
-                const int64_t tiles_before = total;
 #pragma unroll
                 for (int d = kWave / 2; d > 0; d >>= 1)
                     most = max(most, __shfl_xor(most, d, kWave));
-                __syncthreads();
                 if (lane == 0)
                     wsum[wave] = (uint32_t)most;
                 __syncthreads();
                 if (tid == 0) {
                     for (int w = 0; w < kSmWaves; ++w)
                         most = max(most, (int32_t)wsum[w]);
-                    a.next_tileoff[a.k] = tiles_before + (U + kRowTile - 1) / kRowTile;
+                    a.next_tileoff[a.k] = tile0 + (U + kRowTile - 1) / kRowTile;
                     a.next_tileoff[a.k + 1] = most;
                 }
             }
@@ -445,10 +556,15 @@ __global__ __launch_bounds__(kSmThreads) void nw_small_kernel(NwSmall a)
             }
             rows_total = col0 + U;
         }
-        rows = H.col_vertex + col0;
         row0 = col0;
         R = (int32_t)U;
-        __syncthreads(); // the next frontier is in memory for every wave of this workgroup; LDS is free
+        if (h + 1 < a.nhops) {
+            clear();
+            __syncthreads(); // front[] has been read, the counters are clear
+            uint32_t *rows = key;
+            key = front;
+            front = rows;
+        }
     }
     if (a.arrived)
         announce(a.ticket + 1, (uint32_t)a.k, a.arrived, a.arrival);

@@ -558,3 +558,26 @@ def test_row_tiles_of_minibatches_of_very_different_size(mods, k, replace):
     for extract in ("sort", "bitmap"):
         res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (30, 4, 3), 5, extract=extract, replace=replace)
         assert_hops_equal(res.hops(), ref, what="extract=%s" % extract)
+
+
+@pytest.mark.parametrize("hub", [False, True])
+@pytest.mark.parametrize("b,fanouts,union_dst", [(1024, (1, 1, 1), False), (205, (5, 3), False), (93, (10, 15), True), (1024, (4, 4), False),
+                                                 (1025, (4, 3), True), (1024, (16,), False), (963, (16,), True), (5, (7, 9, 11), False)])
+def test_one_workgroup_hops_around_their_round_counts(mods, b, fanouts, union_dst, hub):
+    # a thread keeps 1, up to 4 or up to 16 entries of 1024 each; `hub`: a vertex that every row has, which crowds its bucket, so
+    # that the hop is ranked by the sort, in between hops that are not
+    O, bms, _ = mods
+    rng = np.random.default_rng(b)
+    n, degree = 40_000, 16
+    rows = [rng.choice(n // 2 - 20, degree, replace=False) + 20 for _ in range(n)]
+    if hub:
+        for r in rows[:n // 2]: # (17 is in no row otherwise)
+            r[rng.integers(degree)] = 17
+    rowptr = np.arange(n + 1, dtype=np.int64) * degree
+    col = np.concatenate([np.sort(r) for r in rows]).astype(np.int32)
+    batches = np.stack([rng.permutation(n)[:b] for _ in range(3)]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    for replace in (False, True):
+        ref = O.sample_nodewise(rowptr, col, batches, fanouts, 3, 1, union_dst=union_dst, replace=replace)
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 3, mb_base=1, union_dst=union_dst, replace=replace)
+        assert_hops_equal(res.hops(), ref, what="replace=%s" % replace)
