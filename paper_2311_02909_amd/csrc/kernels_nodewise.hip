@@ -267,7 +267,7 @@ void launch_nw_rows(const Launch &L, const NwHop &a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// SAMPLE, one row per lane, fanout <= S (compile-time capacity of the per-lane position list).
+// SAMPLE, one row per lane, fanout <= S (compile-time capacity of the per-lane position list; S > 32: launch_nw_sample_impl).
 //
 // Draws: nw_draws.h.
 //
@@ -551,12 +551,23 @@ static void launch_nw_sample_wide(const Launch &L, const NwHop &a, const VSet &v
         hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, 0>), dim3(grid_for(L, tiles * parts, 4)), block, 0, L.stream, a, vs, parts);
 }
 
+// Fanouts of 33 .. 64 by one row per lane from this many rows on.  A draw is two instructions per place then, for 64 rows at once,
+// where a row that has the wave to itself spends some ten on it; but with fewer rows most of the chip's waves have none.  Whole
+// calls of one hop on 2.4 M vertices of 38 neighbours, by lanes and by waves, us:
+//   rows      s = 33      s = 40      s = 48      s = 64
+//   16384    221, 222    214, 209    197, 184    230, 190
+//   32768    202, 223    175, 178    183, 180    231, 201
+//   65536    169, 194    188, 219    210, 216    215, 233
+//   131072   241, 293    234, 283    246, 309    256, 303
+// 8 minibatches of 512, (40, 40), 2.4 M vertices of 51: the second hop's sampling 76 -> 34 us, and it counts per segment, which
+// saves 9 us more.
+constexpr int64_t kWideLaneRows = 65536;
 template <bool SET, bool REPLACE>
 static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet &vs)
 {
     NwHop a = a_in;
     const int64_t tiles = a.rows_bound / kRowTile + a.k;
-    if (a.s > 32) {
+    if (a.s > (!REPLACE && a.rows_bound >= kWideLaneRows ? 64 : 32)) {
         a.seg_cnt = nullptr; // one row per wave: its workgroups walk the tiles in stacked order, across minibatches
         launch_nw_sample_wide<SET, REPLACE>(L, a, vs, tiles);
         return false;
@@ -577,8 +588,12 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
         hipLaunchKernelGGL((nw_sample_kernel<8, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
     else if (a.s <= 16)
         hipLaunchKernelGGL((nw_sample_kernel<16, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
-    else
+    else if (REPLACE || a.s <= 32)
         hipLaunchKernelGGL((nw_sample_kernel<32, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
+    else if (a.s <= 48)
+        hipLaunchKernelGGL((nw_sample_kernel<REPLACE ? 32 : 48, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
+    else
+        hipLaunchKernelGGL((nw_sample_kernel<REPLACE ? 32 : 64, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
     return a.seg_cnt != nullptr;
 }
 

@@ -581,3 +581,22 @@ def test_one_workgroup_hops_around_their_round_counts(mods, b, fanouts, union_ds
         ref = O.sample_nodewise(rowptr, col, batches, fanouts, 3, 1, union_dst=union_dst, replace=replace)
         res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 3, mb_base=1, union_dst=union_dst, replace=replace)
         assert_hops_equal(res.hops(), ref, what="replace=%s" % replace)
+
+
+@pytest.mark.parametrize("s", [33, 48, 49, 64])
+@pytest.mark.parametrize("k,variant", [(2, {}), (9, {}), (9, dict(union_dst=True))])
+def test_wide_fanouts_one_lane_per_row(mods, s, k, variant):
+    # so many rows (65536 by their bound) that fanouts of 33 .. 64 are drawn one row per lane; degrees around s, ragged tiles;
+    # k = 2: the sampling kernel sets bits
+    O, bms, _ = mods
+    rng = np.random.default_rng(s)
+    n, b = 40_000, 8192 // k + 5
+    degree = rng.choice([0, 1, s - 1, s, s + 1, 90], n)
+    rowptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, d, replace=False)) for d in degree]).astype(np.int32)
+    batches = random_batches(n, k, b, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, (8, s), 11, **variant)
+    for extract in (None, "sort", "bitmap"):
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (8, s), 11, extract=extract, **variant)
+        assert_hops_equal(res.hops(), ref, what="extract=%s" % extract)
