@@ -38,8 +38,8 @@ constexpr int kMarkRows = 8;      // 4-byte loads
 constexpr int kMostParts = 32;
 constexpr int kTableQuads = 4864; // quads of a lookup table: 4 words of 8 bytes each, 152 KB
 constexpr int kTablePer = (kTableQuads + kRgThreads - 1) / kRgThreads;
-constexpr int kEmitQuads = 256; // quads per step of emit: 32768 ids, 64 KB of 16-bit places
-static_assert(kEmitQuads * 4 == kRgThreads && kRangeQuads % kEmitQuads == 0 && kRangeQuads % kRgThreads == 0, "steps out of step");
+constexpr int kEmitQuads = 16; // quads per step of a wave of emit: 2048 ids, 4 KB of 16-bit places
+static_assert(kEmitQuads * 4 == kWave && kRangeQuads % kRgThreads == 0 && kRgThreads % kEmitQuads == 0, "steps out of step");
 
 __device__ inline uint32_t quad_popc(const uint4 &q) { return __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w); }
 
@@ -295,65 +295,74 @@ __global__ __launch_bounds__(kRgThreads) void rg_count_kernel(RangeArgs a)
         ranges_place<kRgThreads>(a);
 }
 
-// Set bits -> ids, workgroup x of nx: steps of kEmitQuads quads of a minibatch, a word per thread.  places: LDS, kEmitQuads
-// * 128 16-bit values.
-__device__ inline void emit_steps(const RangeArgs &a, int32_t *__restrict__ col_vertex, uint16_t *places, int64_t x, int64_t nx)
+// Set bits -> ids, wave x of nx: steps of kEmitQuads quads of a minibatch, a word per lane.  The set bits before a quad are known,
+// so a wave needs no other and waits for none.  places: LDS of this wave, kEmitQuads * 128 16-bit values.
+// Half vector instructions (100 per step and ten per round of bits), half the step's own chain.  Two hops of 32 x 1024 seeds, (15,
+// 10, 5), 2.4 M vertices (2 and 9 million columns): 54 us by workgroups of 1024 in steps of 32768 ids with three barriers, 38.5 so;
+// eighths of the steps per die, or the range's first column fetched a step ahead, change nothing.
+__device__ inline void emit_steps(const RangeArgs &a, int32_t *__restrict__ col_vertex, uint16_t *places, uint32_t x, uint32_t nx)
 {
-    __shared__ uint32_t span_s[2]; // columns of the range before the step, after it
-    const int tid = threadIdx.x;
-    const int64_t steps = (a.quads + kEmitQuads - 1) / kEmitQuads; // per minibatch
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t steps = (uint32_t)((a.quads + kEmitQuads - 1) / kEmitQuads); // per minibatch
     const uint32_t *__restrict__ words = reinterpret_cast<const uint32_t *>(a.bits);
     uint32_t word = 0, pre = 0, word_next = 0, pre_next = 0;
-    auto fetch = [&](int64_t step, uint32_t &wd, uint32_t &p) {
-        if (step < steps * a.k) {
-            const int64_t q = step / steps * a.stride + step % steps * kEmitQuads + (tid >> 2);
-            wd = words[q * 4 + (tid & 3)];
-            p = a.pre[q];
+    auto fetch = [&](uint32_t i, uint32_t step, uint32_t &wd, uint32_t &p) {
+        if (i < (uint32_t)a.k) {
+            const int64_t q = i * a.stride + (int64_t)step * kEmitQuads;
+            wd = (words + q * 4)[lane];
+            p = (a.pre + q)[lane >> 2];
         }
     };
-    fetch(x, word, pre);
-    for (int64_t step = x; step < steps * a.k; step += nx, word = word_next, pre = pre_next) {
-        fetch(step + nx, word_next, pre_next);
-        const int64_t i = step / steps, s = step % steps;
-        const int64_t first = a.first[i * a.H + range_of(a, (uint32_t)(s * kEmitQuads))];
-        const uint32_t pc = __popc(word);
+    uint32_t i = x / steps, step = x % steps;
+    const uint32_t more_i = nx / steps, more_step = nx % steps;
+    fetch(i, step, word, pre);
+    while (i < (uint32_t)a.k) {
+        uint32_t i_next = i + more_i, step_next = step + more_step;
+        if (step_next >= steps) {
+            step_next -= steps;
+            ++i_next;
+        }
+        fetch(i_next, step_next, word_next, pre_next);
+        const int64_t first = uniform_load(a.first + (int64_t)i * a.H + range_of(a, step * kEmitQuads));
         // set bits of the quad's words before this one
-        uint32_t lower = 0, y = __shfl_up(pc, 1, 4);
-        lower += (tid & 3) >= 1 ? y : 0u;
-        y = __shfl_up(pc, 2, 4);
-        lower += (tid & 3) >= 2 ? y : 0u;
-        y = __shfl_up(pc, 3, 4);
-        lower += (tid & 3) >= 3 ? y : 0u;
-        if (tid == 0)
-            span_s[0] = pre;
-        if (tid == kRgThreads - 1)
-            span_s[1] = pre + lower + pc;
-        __syncthreads();
-        const uint32_t p0 = span_s[0], count = span_s[1] - p0;
-        uint32_t at = pre + lower - p0;
+        const int pc = __popc(word);
+        const int back1 = __builtin_amdgcn_update_dpp(0, pc, 0x90 /* quad_perm:[0,0,1,2] */, 0xF, 0xF, true);
+        const int back2 = __builtin_amdgcn_update_dpp(0, pc, 0x40 /* quad_perm:[0,0,0,1] */, 0xF, 0xF, true);
+        const int back3 = __builtin_amdgcn_update_dpp(0, pc, 0x00 /* quad_perm:[0,0,0,0] */, 0xF, 0xF, true);
+        const int lower = ((lane & 3) >= 1 ? back1 : 0) + ((lane & 3) >= 2 ? back2 : 0) + ((lane & 3) >= 3 ? back3 : 0);
+        const uint32_t p0 = scalar(pre);
+        uint32_t at = pre + (uint32_t)lower - p0;
+        const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)(at + (uint32_t)pc), kWave - 1);
         for (uint32_t wd = word; wd; wd &= wd - 1u)
-            places[at++] = (uint16_t)(tid * 32 + (__ffs((int)wd) - 1));
-        __syncthreads();
+            places[at++] = (uint16_t)(lane * 32 + (__ffs((int)wd) - 1));
+        __builtin_amdgcn_wave_barrier();
         int32_t *__restrict__ out = col_vertex + first + p0;
-        const int32_t id0 = (int32_t)(s * kEmitQuads * 128);
-        for (uint32_t j = tid; j < count; j += kRgThreads)
+        const int32_t id0 = (int32_t)(step * kEmitQuads * 128u);
+        for (uint32_t j = lane; j < count; j += kWave)
             out[j] = id0 + (int32_t)places[j];
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
+        i = i_next;
+        step = step_next;
+        word = word_next;
+        pre = pre_next;
     }
 }
 
-__global__ __launch_bounds__(kRgThreads) void rg_emit_kernel(RangeArgs a, int32_t *__restrict__ col_vertex)
+constexpr int kEmitThreads = 256;
+__global__ __launch_bounds__(kEmitThreads) void rg_emit_kernel(RangeArgs a, int32_t *__restrict__ col_vertex)
 {
-    __shared__ uint16_t places[kEmitQuads * 128];
-    emit_steps(a, col_vertex, places, blockIdx.x, gridDim.x);
+    __shared__ uint16_t places[kEmitThreads / kWave][kEmitQuads * 128];
+    const uint32_t wave = scalar(threadIdx.x / kWave);
+    emit_steps(a, col_vertex, places[wave], blockIdx.x * (kEmitThreads / kWave) + wave, gridDim.x * (kEmitThreads / kWave));
 }
 
 // Few entries: the first `emitters` workgroups emit, the others look entries up one by one, 4 per thread in flight.
 __global__ __launch_bounds__(kRgThreads) void rg_emit_gather_kernel(RangeArgs a, int32_t *__restrict__ col_vertex, int emitters)
 {
-    __shared__ uint16_t places[kEmitQuads * 128];
+    __shared__ uint16_t places[kRgWaves][kEmitQuads * 128];
     if ((int)blockIdx.x < emitters) {
-        emit_steps(a, col_vertex, places, blockIdx.x, emitters);
+        const uint32_t wave = scalar(threadIdx.x / kWave);
+        emit_steps(a, col_vertex, places[wave], blockIdx.x * kRgWaves + wave, (uint32_t)emitters * kRgWaves);
         return;
     }
     const int64_t x = (int64_t)blockIdx.x - emitters, nx = (int64_t)gridDim.x - emitters;
@@ -541,13 +550,14 @@ void launch_ranges_count(const Launch &L, const RangeArgs &a)
 void launch_ranges_emit(const Launch &L, const RangeArgs &a, int32_t *col_vertex)
 {
     const int64_t steps = (int64_t)a.k * ((a.quads + kEmitQuads - 1) / kEmitQuads);
-    hipLaunchKernelGGL(rg_emit_kernel, dim3(grid_for(L, steps, 2)), dim3(kRgThreads), 0, L.stream, a, col_vertex);
+    const int64_t waves = kEmitThreads / kWave;
+    hipLaunchKernelGGL(rg_emit_kernel, dim3(grid_for(L, (steps + waves - 1) / waves, 8)), dim3(kEmitThreads), 0, L.stream, a, col_vertex);
 }
 
 void launch_ranges_emit_gather(const Launch &L, const RangeArgs &a, int32_t *col_vertex, int64_t entries)
 {
     const int64_t steps = (int64_t)a.k * ((a.quads + kEmitQuads - 1) / kEmitQuads);
-    const int emitters = grid_for(L, steps, 1), gatherers = grid_for(L, entries / kRgThreads + 1, 1);
+    const int emitters = grid_for(L, (steps + kRgWaves - 1) / kRgWaves, 1), gatherers = grid_for(L, entries / kRgThreads + 1, 1);
     hipLaunchKernelGGL(rg_emit_gather_kernel, dim3(emitters + gatherers), dim3(kRgThreads), 0, L.stream, a, col_vertex, emitters);
 }
 

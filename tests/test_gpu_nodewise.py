@@ -600,3 +600,18 @@ def test_wide_fanouts_one_lane_per_row(mods, s, k, variant):
     for extract in (None, "sort", "bitmap"):
         res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (8, s), 11, extract=extract, **variant)
         assert_hops_equal(res.hops(), ref, what="extract=%s" % extract)
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 6145, 131_200])
+@pytest.mark.parametrize("k", [1, 5, 40])
+def test_vertex_ranges_written_out_wave_by_wave(mods, n, k):
+    # columns leave in steps of 2048 ids: nearly all vertices sampled (small n, up to all ids of a step), few of them (large n)
+    rng = np.random.default_rng(n + k)
+    degree = 40
+    col = np.concatenate([np.sort(rng.choice(n, degree, replace=False)) for _ in range(n)]).astype(np.int32)
+    rowptr = np.arange(n + 1, dtype=np.int64) * degree
+    batches = random_batches(n, k, 1100, rng)
+    O, bms, _ = mods
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (16, 20), 2)
+    assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, (16, 20), 2))
