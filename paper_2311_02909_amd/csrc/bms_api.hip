@@ -1034,6 +1034,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         NwHop a{};
         a.A_rowptr = csr->rowptr;
         a.A_col = csr->col;
+        a.A_nnz = csr->nnz;
         a.n = csr->n;
         a.k = c.k;
         a.s = fanouts[h];

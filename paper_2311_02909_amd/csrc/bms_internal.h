@@ -71,7 +71,7 @@ void launch_vset_clear(const Launch &, const VSet &, int32_t k, const int64_t *m
 struct NwHop {
     const int64_t *A_rowptr;
     const int32_t *A_col;
-    int64_t n;
+    int64_t n, A_nnz;
     int32_t k;
     int32_t s;
     uint64_t hopkey;

@@ -574,8 +574,13 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     }
     // Four workgroups per compute unit: their 1024 rows hold more reads than the unit keeps in flight (about 92), and the
     // fewer rows are in progress on the chip, the narrower the part of A that the minibatches read at the same time: with
-    // eight, it no longer fits the 256 MB last-level cache on the larger graphs.
-    int grid = grid_for(L, tiles, 4);
+    // eight, it no longer fits the 256 MB last-level cache on the larger graphs.  Six where A's columns take four times that
+    // cache at most, so that most of what several minibatches read is kept anyhow, and fanouts of up to 8 (above, five workgroups
+    // fill LDS).  Last hop, by four and by six: 490 MB of columns 332 and 323 us, with own vertices 231 and 212, with replacement
+    // 127 and 118; 5.3 GB (128 minibatches) 1185 and 1377 us, 6.4 GB 790 and 809.  Between, uniform graphs of 1 to 4 GB: 1 or 2 %
+    // in six's favour, which is not worth what the larger skewed ones lose.
+    const bool small_graph = a.A_nnz * (int64_t)sizeof(int32_t) <= (int64_t)1 << 30;
+    int grid = grid_for(L, tiles, small_graph && a.s <= 8 ? 6 : 4);
     // counting per segment needs every workgroup to stay with one minibatch: tile v belongs to minibatch v % k,
     // so a grid that is a multiple of k does it
     if (a.seg_cnt && a.seg_C <= kMaxFusedSegments && a.k <= L.num_cu * 8)
