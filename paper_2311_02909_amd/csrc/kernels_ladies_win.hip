@@ -87,26 +87,35 @@ __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb,
     __shared__ int64_t smem[kLwRows / kWave];
     __shared__ uint32_t number_s;
     const int tid = threadIdx.x;
-    const uint32_t t = take_number(lb, &number_s);
-    const int64_t R = a.mb_rowoff[a.k];
-    if (t > 0 && (int64_t)t * kLwRows >= R)
+    const uint32_t t = scalar(take_number(lb, &number_s));
+    const int64_t R = uniform_load(a.mb_rowoff + a.k);
+    const int64_t r0 = (int64_t)t * kLwRows, r = r0 + tid;
+    if (t > 0 && r0 >= R)
         return; // nobody with rows comes after
-    const int64_t r = (int64_t)t * kLwRows + tid;
-    int64_t beg = 0, deg = 0;
-    if (r < R) {
-        const int32_t v = a.row_vertex[r];
-        if (v >= 0 && (int64_t)v < a.n) {
-            beg = a.A_rowptr[v];
-            deg = a.A_rowptr[v + 1] - beg;
-        }
+    const int32_t v = r < R ? a.row_vertex[r] : -1;
+    // the minibatch of the first row, while the vertices are on their way; mostly that of all rows
+    int lo = 0;
+    for (int hi = a.k; hi - lo > 1;) {
+        const int mid = (lo + hi) >> 1;
+        if (uniform_load(a.mb_rowoff + mid) <= r0)
+            lo = mid;
+        else
+            hi = mid;
     }
+    int64x2_a8 extent = {0, 0};
+    if (v >= 0 && (int64_t)v < a.n)
+        extent = row_extent(a.A_rowptr, v);
+    int mb = lo;
+    if (uniform_load(a.mb_rowoff + lo + 1) < min(r0 + kLwRows, R) && r < R)
+        mb = locate_segment(a.mb_rowoff, a.k, r);
+    const int64_t beg = extent[0], deg = extent[1] - extent[0];
     int64_t total;
     const int64_t ex = block_exclusive_scan<int64_t, kLwRows>(deg, smem, total);
     const int64_t before = sum_before<kLwRows>(lb, t, total, smem);
     if (r < R) {
         a.row_beg[r] = beg;
         a.gather_off[r] = before + ex;
-        a.row_mb[r] = locate_segment(a.mb_rowoff, a.k, r);
+        a.row_mb[r] = mb;
         a.out_rowptr[r] = 0; // per-row counters of the extraction pass
     }
     if ((int64_t)(t + 1) * kLwRows >= R && tid == 0) {
@@ -356,19 +365,29 @@ __global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int plann
             a.tile_queue[i * kQueueStride] = 0;
         }
     }
-    const int64_t ntiles = u.p.tileoff[a.k];
-    for (int64_t x = (int64_t)blockIdx.x * 256 + tid; x < ntiles; x += (int64_t)planners * 256) {
-        const int i = locate_segment(u.p.tileoff, a.k, x);
-        const int64_t g0 = u.p.goff[i] + (x - u.p.tileoff[i]) * a.tile;
-        int64_t lo = a.mb_rowoff[i], hi = a.mb_rowoff[i + 1];
-        while (hi - lo > 1) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (a.gather_off[mid] <= g0)
-                lo = mid;
-            else
-                hi = mid;
+    // A row holds the first positions of the tiles that start inside it: mostly none or one, found without a search (9 steps
+    // through memory per tile of 512 rows); a row that holds many is given to the whole wave.
+    const int64_t R = uniform_load(a.mb_rowoff + a.k);
+    const int shift = __ffs(a.tile) - 1, lane = tid & (kWave - 1);
+    for (int64_t r0 = (int64_t)blockIdx.x * 256 + (tid - lane); r0 < R; r0 += (int64_t)planners * 256) {
+        const int64_t r = r0 + lane;
+        int64_t from = 0, count = 0; // tiles
+        if (r < R) {
+            const int64_t begin = a.gather_off[r], end = a.gather_off[r + 1];
+            const int i = a.row_mb[r];
+            const int64_t y = (begin - u.p.goff[i] + a.tile - 1) >> shift;
+            from = u.p.tileoff[i] + y;
+            count = ((end - u.p.goff[i] + a.tile - 1) >> shift) - y;
         }
-        a.tile_row[x] = lo;
+        for (uint64_t many = __ballot(count > 8); many; many &= many - 1ull) {
+            const int owner = __ffsll((unsigned long long)many) - 1;
+            const int64_t x0 = lane_value(from, owner), n = lane_value(count, owner);
+            for (int64_t x = lane; x < n; x += kWave)
+                a.tile_row[x0 + x] = r0 + owner;
+        }
+        if (count <= 8)
+            for (int64_t x = 0; x < count; ++x)
+                a.tile_row[from + x] = r;
     }
 }
 
@@ -675,13 +694,16 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
 }
 
 // one workgroup per minibatch: columns and weight of every window (the sums of its parts), before each of its
-// parts, and before each window; columns of the minibatch
-__global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a, int64_t *pnnz_out)
+// parts, and before each window; columns of the minibatch.  A part per thread, so 16 lanes per window.
+// Three layers of 32 x 512 seeds, 37 windows: 26 us with a window per thread, which read its 16 parts one after the other, 20 so.
+constexpr int kScanThreads = 1024;
+__global__ __launch_bounds__(kScanThreads) void ldw_win_scan_kernel(LwHop a, int64_t *pnnz_out)
 {
-    __shared__ uint64_t smem[4];
-    __shared__ uint64_t carry_c, carry_w;
+    static_assert(kWinParts == 16, "a window's parts are 16 lanes");
+    __shared__ uint64_t smem[kScanThreads / kWave];
+    __shared__ uint32_t smem_c[kScanThreads / kWave];
     __shared__ uint32_t last_s;
-    const int i = blockIdx.x, tid = threadIdx.x;
+    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     // the workgroup that comes here last turns the minibatches' counts into p_off
     auto finish = [&](int64_t count) {
         if (tid == 0) {
@@ -692,11 +714,11 @@ __global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a, int64_t *pnn
         if (!last_s)
             return;
         uint64_t carry = 0;
-        for (int32_t base = 0; base < a.k; base += 256) {
+        for (int32_t base = 0; base < a.k; base += kScanThreads) {
             const int32_t j = base + tid;
             const uint64_t v = j < a.k ? (uint64_t)__hip_atomic_load(a.mb_count + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
             uint64_t total;
-            const uint64_t ex = carry + block_exclusive_scan<uint64_t, 256>(v, smem, total);
+            const uint64_t ex = carry + block_exclusive_scan<uint64_t, kScanThreads>(v, smem, total);
             if (j < a.k)
                 a.p_off[j] = (int64_t)ex;
             carry += total;
@@ -710,40 +732,45 @@ __global__ __launch_bounds__(256) void ldw_win_scan_kernel(LwHop a, int64_t *pnn
         finish(0);
         return;
     }
-    if (tid == 0) {
-        carry_c = 0;
-        carry_w = 0;
-    }
-    __syncthreads();
-    for (int base = 0; base < a.nwin; base += 256) {
-        const int w = base + tid;
-        const int64_t x = (int64_t)i * a.nwin + w;
-        uint64_t c = 0, wt = 0;
-        if (w < a.nwin) {
-            for (int q = 0; q < kWinParts; ++q) {
-                const int64_t part = x * kWinParts + q;
-                a.part_off[part] = (uint32_t)c;
-                a.part_woff[part] = wt;
-                c += a.part_cnt[part];
-                wt += a.part_wt[part];
+    uint64_t carry_c = 0, carry_w = 0;
+    const int32_t parts = a.nwin * kWinParts;
+    const int64_t first = (int64_t)i * parts;
+    for (int32_t base = 0; base < parts; base += kScanThreads) {
+        const int32_t q = base + tid;
+        const uint32_t c = q < parts ? a.part_cnt[first + q] : 0u; // of one minibatch, so all of them are no more than n
+        const uint64_t wt = q < parts ? a.part_wt[first + q] : 0ull;
+        const uint32_t upto_c = wave_inclusive_scan_dpp(c);
+        const uint64_t upto_w = wave_inclusive_scan(wt);
+        __syncthreads(); // the sums of the steps before have been read
+        if (lane == kWave - 1) {
+            smem_c[wave] = upto_c;
+            smem[wave] = upto_w;
+        }
+        __syncthreads();
+        uint64_t before_c = carry_c, before_w = carry_w;
+#pragma unroll
+        for (int x = 0; x < kScanThreads / kWave; ++x) {
+            before_c += x < wave ? smem_c[x] : 0u;
+            before_w += x < wave ? smem[x] : 0ull;
+            carry_c += smem_c[x];
+            carry_w += smem[x];
+        }
+        const int head = lane & ~(kWinParts - 1);
+        const uint32_t head_c = (uint32_t)__shfl((int)(upto_c - c), head, kWave);
+        const uint64_t head_w = __shfl(upto_w - wt, head, kWave);
+        if (q < parts) {
+            a.part_off[first + q] = upto_c - c - head_c;
+            a.part_woff[first + q] = upto_w - wt - head_w;
+            const int64_t x = (first + q) / kWinParts;
+            if (lane == head) {
+                a.win_poff[x] = (int64_t)(before_c + head_c);
+                a.win_woff[x] = before_w + head_w;
             }
-            a.win_cnt[x] = (uint32_t)c;
-            a.win_wt[x] = wt;
+            if (lane == head + kWinParts - 1) {
+                a.win_cnt[x] = upto_c - head_c;
+                a.win_wt[x] = upto_w - head_w;
+            }
         }
-        uint64_t tc, tw;
-        const uint64_t ec = block_exclusive_scan<uint64_t, 256>(c, smem, tc);
-        const uint64_t ew = block_exclusive_scan<uint64_t, 256>(wt, smem, tw);
-        const uint64_t cc = carry_c, cw = carry_w;
-        if (w < a.nwin) {
-            a.win_poff[x] = (int64_t)(cc + ec);
-            a.win_woff[x] = cw + ew;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            carry_c = cc + tc;
-            carry_w = cw + tw;
-        }
-        __syncthreads();
     }
     finish((int64_t)carry_c);
 }
@@ -1334,34 +1361,41 @@ __global__ __launch_bounds__(256) void ldw_extract_copy_kernel(LwHop a)
 }
 
 // The scan of the rows' counts and the copy in one launch: 256 rows per workgroup, the rows before summed up by sum_before,
-// then one entry per lane and step, whose row is found in the offsets in LDS.
+// then one entry per lane and step, whose row is found in the offsets in LDS.  Chains of trips to memory: what leads to a row's
+// later pieces is fetched before the sum of the rows before, not after it (three layers of 32 x 512 seeds: 43 -> 37 us).
 __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Lookback lb, int64_t *nnz_out)
 {
     __shared__ int64_t smem[kLwRows / kWave];
     __shared__ uint32_t number_s;
-    __shared__ int64_t gather_l[kLwRows];
+    __shared__ int64_t gather_l[kLwRows], tile_l[kLwRows], pos_l[kLwRows]; // of a row: first kept neighbour, tile, that tile's first position
     __shared__ uint32_t off_l[kLwRows + 1], first_l[kLwRows];
+    __shared__ int32_t up_s; // the flag as this workgroup sees it: it may go up meanwhile
     const int tid = threadIdx.x;
-    const uint32_t t = take_number(lb, &number_s);
-    const int64_t R = a.mb_rowoff[a.k];
+    if (tid == 0)
+        up_s = a.giveup ? *a.giveup : 0;
+    const uint32_t t = scalar(take_number(lb, &number_s));
+    const int64_t R = uniform_load(a.mb_rowoff + a.k);
     const int64_t r0 = (int64_t)t * kLwRows, r = r0 + tid;
     if (t > 0 && r0 >= R)
         return;
-    __shared__ int32_t up_s; // the flag as this workgroup sees it: it may go up meanwhile
-    if (tid == 0)
-        up_s = a.giveup ? *a.giveup : 0;
-    __syncthreads();
-    int64_t cnt = 0;
+    const int shift = __ffs(a.tile) - 1;
+    int64_t cnt = 0, g = 0, gm = 0, xm = 0;
     if (!up_s && r < R) {
+        const int i = a.row_mb[r];
         cnt = a.out_rowptr[r];
-        gather_l[tid] = a.gather_off[r];
+        g = a.gather_off[r];
         first_l[tid] = a.first_cnt[r];
+        gm = a.mb_goff[i];
+        xm = a.mb_gtileoff[i];
     }
     int64_t total;
     const int64_t ex = block_exclusive_scan<int64_t, kLwRows>(cnt, smem, total);
     off_l[tid] = (uint32_t)ex; // < 2^32: at most 256 rows of at most 4096 entries
     if (tid == 0)
         off_l[kLwRows] = (uint32_t)total;
+    gather_l[tid] = g;
+    tile_l[tid] = xm + ((g - gm) >> shift);
+    pos_l[tid] = gm + ((g - gm) >> shift << shift);
     const int64_t before = sum_before<kLwRows>(lb, t, total, smem);
     if (r < R)
         a.out_rowptr[r] = before + ex;
@@ -1386,14 +1420,13 @@ __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Loo
         uint32_t x = e - off_l[lo], piece = first_l[lo];
         int64_t g = gather_l[lo];
         if (x >= piece) { // in a later piece of the row: one per tile that it reaches into
-            const int i = a.row_mb[r0 + lo];
-            const int64_t gm = a.mb_goff[i], xm = a.mb_gtileoff[i];
-            int64_t tile = (g - gm) / a.tile;
+            const int64_t tile0 = tile_l[lo];
+            int64_t tile = tile0;
             do {
                 x -= piece;
-                piece = a.tile_cnt[xm + ++tile];
+                piece = a.tile_cnt[++tile];
             } while (x >= piece);
-            g = gm + tile * a.tile;
+            g = pos_l[lo] + ((tile - tile0) << shift);
         }
         a.out_col[before + e] = a.xtmp[g + x];
     }
@@ -1429,7 +1462,7 @@ void launch_ldw_bounds(const Launch &L, const LwHop &a)
 {
     const int64_t ttiles = (((int64_t)a.nwin + 64) / 64) * ((a.rows_bound + 63) / 64);
     if (a.index && a.k < kPlanMb) {
-        const int planners = grid_for(L, (a.tiles_bound + 255) / 256, 1);
+        const int planners = grid_for(L, (a.rows_bound + 1023) / 1024, 1);
         hipLaunchKernelGGL(ldw_plan_bounds_kernel, dim3(planners + grid_for(L, ttiles, 8)), dim3(256), 0, L.stream, a, planners);
         return;
     }
@@ -1460,7 +1493,7 @@ int launch_ldw_accumulate(const Launch &L, const LwHop &a, int64_t *pnnz_out)
                        ldw_accumulate_lds_bytes(), L.stream, a);
     if (hipGetLastError() != hipSuccess)
         return -1;
-    hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k), dim3(256), 0, L.stream, a, pnnz_out);
+    hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k), dim3(kScanThreads), 0, L.stream, a, pnnz_out);
     return 0;
 }
 

@@ -267,3 +267,21 @@ def test_draws_from_hardly_any_entries_to_many_blocks(mods, n, degree, squared, 
     col = np.concatenate([np.sort(rng.choice(n, degree, replace=False)) for _ in range(n)]).astype(np.int32)
     batches = random_batches(n, 3, min(n // 4, 900), rng)
     _run_both(mods, rowptr, col, batches, (s,), 7, mb_base=1, squared=squared)
+
+
+@pytest.mark.parametrize("n,k,degree", [(200_000, 3, 30_000), (4_300_000, 2, 500), (50, 40, 3)])
+def test_rows_over_many_tiles_and_windows(mods, n, k, degree):
+    # rows that hold the starts of many tiles of the gathered order next to rows that hold none and empty rows; more parts of
+    # windows (66 windows) than the scan has threads; minibatches smaller than a workgroup's rows
+    rng = np.random.default_rng(n)
+    rows = min(n // 2, 60)
+    deg = np.zeros(n, dtype=np.int64)
+    deg[:rows] = rng.choice([0, 1, degree // 3, degree], rows)
+    deg[0] = degree
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, d, replace=False)) for d in deg[:rows]]).astype(np.int32)
+    batches = np.stack([rng.permutation(rows)[:rows // 2] for _ in range(k)]).astype(np.int32)
+    batches[:, 0] = 0
+    for i in range(k):
+        batches[i, 1:] = rng.permutation(np.arange(1, rows))[:rows // 2 - 1]
+    _run_both(mods, rowptr, col, batches, (300,), 13, mb_base=4)
