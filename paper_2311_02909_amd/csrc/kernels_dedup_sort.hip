@@ -294,13 +294,14 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
 //      hands the segment to the bitmap kernel, or the hop to the per-minibatch kernel when the segment is too
 //      wide for that
 //   3  every id goes to its bucket's place in LDS
-//   4  every id looks at the few ids of its bucket: `less` of them are smaller, `eqb` are equal and came before
-//      it; with eqb = 0 it is the head of its run of equal ids and sets bit (bucket start + less) = the run's
-//      place in ascending order
-//   5  popcount prefix over the head bits: the rank of an id among the distinct ones = heads before its run
-//   6  ranks leave in slot order; the heads leave their ids at their rank, copied out as the distinct ids
+//   4  every id looks at the few ids of its bucket and sets bit (bucket start + smaller ones) = the place of its run of equal
+//      ids in ascending order
+//   5  popcount prefix over the bits: the rank of an id among the distinct ones = runs before its own
+//   6  ranks leave in slot order; the ids go to their rank, copied out as the distinct ids
 // A chain of dependent LDS steps, so what counts is how many workgroups share a compute unit: 80 registers let three do so (two
 // before).  256 x 240 k ids of 111 M: 343 us with two, 296 with three, 309 with four, which spill and cannot fetch ahead.
+// Four reads of the bucket at once instead of one by one: two hops of that call 391 -> 374 us.  About 13 LDS accesses per id are
+// two thirds of it.
 constexpr int kRankCap = 4096;    // ids of a segment that one workgroup of the ranking kernel takes
 constexpr int kRankThreads = 512;
 constexpr int kRankBucketBits = 12; // at most 4096 buckets
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
 {
     constexpr int NT = kRankThreads, NW = NT / kWave, PER = kRankCap / NT, NB = 1 << kRankBucketBits;
     __shared__ uint4 cnt4[NB / 4 + 1];           // bucket sizes, then bucket starts; start[nb] = m
-    __shared__ uint32_t sorted[kRankCap];        // ids by bucket (relative to the segment's first id); then the distinct ones
+    __shared__ uint32_t sorted[kRankCap + 3];    // ids by bucket (relative to the segment's first id); then the distinct ones
     __shared__ uint32_t hbits[kRankCap / 32], hpre[kRankCap / 32];
     __shared__ uint32_t wtot[NW];
     uint32_t *cnt = reinterpret_cast<uint32_t *>(cnt4);
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
             hbits[x] = 0;
         __syncthreads();
         fetch(s0_next, m_next, e0_next, key_next);
-        uint32_t at[PER]; // slot in the bucket << 16; then start of the bucket below it; from step 4 on: place of the id's run
+        uint32_t at[PER]; // slot in the bucket; then the bucket's start, size (from bit 13) and the slot; from step 4 on: place of the id's run
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (key[q] != 0xFFFFFFFFu)
@@ -448,32 +449,49 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (key[q] != 0xFFFFFFFFu) {
-                const uint32_t bs = cnt[key[q] >> bshift];
+                const uint32_t bucket = key[q] >> bshift, bs = cnt[bucket], be = cnt[bucket + 1u];
                 sorted[bs + at[q]] = key[q];
-                at[q] = at[q] << 16 | bs;
+                at[q] = at[q] << 19 | (be - bs) << 13 | bs;
             }
+        if (tid < 3)
+            sorted[m + tid] = 0xFFFFFFFFu; // (step 4 reads that far)
         __syncthreads();
         // place of every id's run of equal ids in ascending order; heads
         if (bshift == 0) { // one id per bucket: the run is the bucket
 #pragma unroll
             for (int q = 0; q < PER; ++q)
-                if (key[q] != 0xFFFFFFFFu && at[q] < 0x10000u)
-                    atomicOr(&hbits[at[q] >> 5], 1u << (at[q] & 31u));
-        } else {
-#pragma unroll
-            for (int q = 0; q < PER; ++q)
                 if (key[q] != 0xFFFFFFFFu) {
-                    const uint32_t be = cnt[(key[q] >> bshift) + 1u], bs = at[q] & 0xFFFFu, me = bs + (at[q] >> 16);
-                    uint32_t less = 0, eqb = 0;
-                    for (uint32_t t = bs; t < be; ++t) {
-                        const uint32_t o = sorted[t];
-                        less += o < key[q] ? 1u : 0u;
-                        eqb += (o == key[q] && t < me) ? 1u : 0u;
-                    }
-                    at[q] = eqb << 16 | (bs + less); // from here on: 0 in the upper half marks the head of a run
-                    if (eqb == 0)
-                        atomicOr(&hbits[at[q] >> 5], 1u << (at[q] & 31u));
+                    const uint32_t p = at[q] & 8191u;
+                    if (at[q] >> 19 == 0)
+                        atomicOr(&hbits[p >> 5], 1u << (p & 31u));
+                    at[q] = p;
                 }
+        } else {
+            // the ids after a bucket are larger than its own: four reads each, of two ids at a time, whatever the bucket's size
+#pragma unroll
+            for (int q0 = 0; q0 < PER; q0 += 2) {
+                uint32_t o[2][4];
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        o[u][t] = sorted[(key[q0 + u] != 0xFFFFFFFFu ? at[q0 + u] & 8191u : 0u) + t];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int q = q0 + u;
+                    if (key[q] == 0xFFFFFFFFu)
+                        continue;
+                    const uint32_t bs = at[q] & 8191u, n = (at[q] >> 13) & 63u;
+                    uint32_t p = bs;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        p += o[u][t] < key[q] ? 1u : 0u;
+                    for (uint32_t t = 4; t < n; ++t)
+                        p += sorted[bs + t] < key[q] ? 1u : 0u;
+                    atomicOr(&hbits[p >> 5], 1u << (p & 31u));
+                    at[q] = p;
+                }
+            }
         }
         __syncthreads();
         const uint32_t nwd = (m + 31u) / 32u; // <= 128 words of head bits
@@ -499,11 +517,10 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
 #pragma unroll
         for (int q = 0; q < PER; ++q)
             if (key[q] != 0xFFFFFFFFu) {
-                const uint32_t p = at[q] & 0xFFFFu;
+                const uint32_t p = at[q];
                 const uint32_t r = hpre[p >> 5] + __popc(hbits[p >> 5] & ((1u << (p & 31u)) - 1u));
                 ranks[q * NT + tid] = (uint16_t)r;
-                if (at[q] < 0x10000u)
-                    sorted[r] = key[q]; // every id has been looked at (step 4): their place now takes the distinct ones
+                sorted[r] = key[q]; // every id has been looked at (step 4): their place now takes the distinct ones
             }
         __syncthreads();
         uint32_t *__restrict__ uids = a.uids + e0 + s0;

@@ -615,3 +615,25 @@ def test_vertex_ranges_written_out_wave_by_wave(mods, n, k):
     csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
     res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (16, 20), 2)
     assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, (16, 20), 2))
+
+
+@pytest.mark.parametrize("share,spread", [(1.0, 1), (0.5, 3), (0.2, 700)])
+def test_sort_extract_buckets_of_equal_and_near_ids(mods, share, spread):
+    # buckets of 1 to 32 ids, many of them equal or next to each other, at the ends of segments and of the id range
+    O, bms, _ = mods
+    rng = np.random.default_rng(spread)
+    n, b = 900_000, 900
+    near = (rng.integers(0, n // 1000, 400) * 1000 + rng.integers(0, spread, 400)) % n
+    near[:4] = (0, 1, n - 2, n - 1)
+    rows = []
+    for _ in range(b):
+        r = rng.choice(n, 24, replace=False)
+        m = int(24 * share * 0.5)
+        r[:m] = rng.choice(near, m)
+        rows.append(np.unique(r))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[:b] = [r.size for r in rows]
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    col = np.concatenate(rows).astype(np.int32)
+    batches = np.stack([rng.permutation(b) for _ in range(5)]).astype(np.int32)
+    _run_both(mods, rowptr, col, batches, (20,), 3)
