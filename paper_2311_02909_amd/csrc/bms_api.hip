@@ -1046,6 +1046,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         a.row_beg = csr->row_beg.as<int64_t>();
         a.row_deg = csr->row_deg.as<int32_t>();
         a.tile_off = csr->tile_off.as<int64_t>();
+        a.nnz_out = slot(c, h, 0);
         // with BMS_UNION_DST the hop is built with one more entry per row (the row's own vertex) in scratch
         // and moved to the result's arrays without it at the end of the hop
         a.out_rowptr = self_in_rows ? csr->un_rowptr.as<int64_t>() : hb.rowptr.as<int64_t>();
@@ -1070,8 +1071,12 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         launch_nw_rows(c.launch, a);
         BMS_TRY(prof.end());
         BMS_TRY(prof.begin("scan_tiles", h));
-        launch_scan_i64(c.launch, a.tile_off, a.mb_tileoff + c.k, slot(c, h, 0), a.out_rowptr, mb_rowoff + c.k,
-                        rows_bound / kRowTile + c.k);
+        // a few tiles whose sizes nobody asks for before the columns are written (nor their offsets after that: nw_relabel and
+        // nw_strip_self do): the sampling kernel does it
+        a.sum_tiles = no_wait && tiles_bound <= kMostSummedTiles && buckets && !self_in_rows && !staged_by(c, BMS_PROFILE | BMS_PROFILE_MAIN);
+        if (!a.sum_tiles)
+            launch_scan_i64(c.launch, a.tile_off, a.mb_tileoff + c.k, slot(c, h, 0), a.out_rowptr, mb_rowoff + c.k,
+                            rows_bound / kRowTile + c.k);
         BMS_TRY(prof.end());
 
         // nnz sizes the column buffers: read back (the only host round trip of the hop), or in the

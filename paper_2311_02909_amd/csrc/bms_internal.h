@@ -82,6 +82,8 @@ struct NwHop {
     int64_t *row_beg;          // scratch, rows
     int32_t *row_deg;          // scratch, rows
     int64_t *tile_off;         // scratch, tiles+1
+    int32_t sum_tiles;         // 1: tile_off holds the tiles' sums as nw_rows left them, no more than kMostSummedTiles of them;
+                               // the sampling kernel adds up those before a tile itself, and writes nnz_out and out_rowptr[rows]
     int64_t *out_rowptr;       // rows+1
     int32_t *out_col;          // nnz
     int64_t *nnz_out;          // device scalar
@@ -101,6 +103,7 @@ struct NwHop {
     const uint16_t *seg_tab;   // not nullptr: segment of an id = seg_tab[id >> seg_shift] (kMaxCells + 1 entries at most)
 };
 constexpr int kMaxFusedSegments = 512;
+constexpr int kMostSummedTiles = 1024;
 void launch_nw_rows(const Launch &, const NwHop &);
 // set_bits: also mark every sampled vertex in the minibatch's vertex set (bitmap EXTRACT path).
 // Returns true when the kernel also took the per-segment counts asked for in NwHop::seg_cnt (it can when every

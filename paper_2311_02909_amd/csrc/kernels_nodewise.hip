@@ -266,6 +266,47 @@ void launch_nw_rows(const Launch &L, const NwHop &a)
         hipLaunchKernelGGL(nw_rows_replace_wide_kernel<false>, dim3(grid_for(L, tiles, 1)), dim3(kWideRowsThreads), 0, L.stream, a);
 }
 
+// Sum of the tiles before tile t, for all threads of a workgroup (sum_tiles); `room`: a word per wave.  Up to four sums per thread
+// out of L2 instead of a launch of the scan.  Calls of (15, 10, 5) for one minibatch of 1024 seeds 139 -> 134 us, (40, 40) for 8 of
+// 512 205 -> 193; with 1950 tiles, twice what the chip has workgroups for, 721 -> 726, so not more than kMostSummedTiles.
+__device__ __forceinline__ int64_t tiles_before(const NwHop &a, int64_t t, int64_t *room)
+{
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid)); // (places: computed anew for every tile, not kept in registers)
+    constexpr int kEach = kMostSummedTiles / kRowTile; // consecutive ones, two to a read (tile t itself may be read)
+    const int left = (int)t - (int)tid * kEach;
+    const longlong2 *from = reinterpret_cast<const longlong2 *>(a.tile_off) + tid * (kEach / 2);
+    longlong2 two[kEach / 2];
+#pragma unroll
+    for (int u = 0; u < kEach / 2; ++u) {
+        two[u] = make_longlong2(0, 0);
+        if (2 * u < left)
+            two[u] = from[u];
+    }
+    int64_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < kEach / 2; ++u)
+        sum += two[u].x + (2 * u + 1 < left ? two[u].y : 0);
+    // 64 lanes' sums of low and of high bits fit 32 bits each (a tile has fewer than 2^40 entries)
+    const uint32_t low = wave_inclusive_scan_dpp((uint32_t)sum & 0xFFFFFFu), high = wave_inclusive_scan_dpp((uint32_t)(sum >> 24));
+    __syncthreads();
+    if ((tid & (kWave - 1)) == kWave - 1)
+        room[tid / kWave] = ((int64_t)high << 24) + low;
+    __syncthreads();
+    sum = 0;
+#pragma unroll
+    for (int w = 0; w < kRowTile / kWave; ++w)
+        sum += room[w];
+    return sum;
+}
+
+// entries in all, by one thread of the launch
+__device__ __forceinline__ void leave_total(const NwHop &a, int64_t total)
+{
+    *a.nnz_out = total;
+    a.out_rowptr[a.mb_rowoff[a.k]] = total;
+}
+
 // ---------------------------------------------------------------------------------------------
 // SAMPLE, one row per lane, fanout <= S (compile-time capacity of the per-lane position list; S > 32: launch_nw_sample_impl).
 //
@@ -280,11 +321,13 @@ void launch_nw_rows(const Launch &L, const NwHop &a)
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kSelfMark = 0x80000000u; // staged entry: a vertex id, not a place in A_col
 constexpr int kGatherUnroll = 5;
-template <int S, bool SET, bool REPLACE>
+// SUM: a.sum_tiles; kernels of their own, as the sums' registers would cost the others a workgroup per compute unit
+template <int S, bool SET, bool REPLACE, bool SUM>
 __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
 {
     __shared__ uint32_t stage[kRowTile * (S + 1)]; // + 1: the row's own vertex when rows carry it
     __shared__ int32_t wsum[kRowTile / kWave];
+    __shared__ int64_t tsum[SUM ? kRowTile / kWave : 1];
     __shared__ uint32_t seg_hist[kMaxFusedSegments]; // sampled ids per id-range segment, of this workgroup's minibatch
     __shared__ uint16_t seg_tab_l[kMaxCells + 1];    // segment of every cell of ids, when the segments differ in width
     const int tid = threadIdx.x;
@@ -317,6 +360,8 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
             }
         }
     };
+    if (SUM && most == 0 && blockIdx.x == 0 && tid == 0)
+        leave_total(a, 0);
     int64_t beg, beg_next;
     int32_t deg, deg_next;
     extent(blockIdx.x, beg, deg);
@@ -341,7 +386,9 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
         }
         int32_t tot;
         const int32_t loc = block_exclusive_scan<int32_t, kRowTile>(valid ? cnt + a.self_entry : 0, wsum, tot);
-        const int64_t base = a.tile_off[t];
+        const int64_t base = SUM ? tiles_before(a, t, tsum) : a.tile_off[t];
+        if (SUM && tid == 0 && t == a.mb_tileoff[a.k] - 1)
+            leave_total(a, base + tot);
         if (valid)
             a.out_rowptr[r] = base + loc;
         if (SET && valid && a.mark_self) {
@@ -422,6 +469,8 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
     volatile uint32_t *chosen = chosen_all + (K ? 0 : wave * kMaxSampledFanout);
     const int64_t nwork = a.mb_tileoff[a.k] * parts;
     const int32_t s = a.s;
+    if (a.sum_tiles && nwork == 0 && blockIdx.x == 0 && tid == 0)
+        leave_total(a, 0);
     for (int64_t v = blockIdx.x; v < nwork; v += gridDim.x) {
         const int64_t t = v / parts;
         const int part = (int)(v % parts);
@@ -436,7 +485,9 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
         }
         int64_t tot;
         const int64_t loc = block_exclusive_scan<int64_t, kRowTile>(cnt, wsum, tot);
-        const int64_t base = a.tile_off[t];
+        const int64_t base = a.sum_tiles ? tiles_before(a, t, wsum) : a.tile_off[t];
+        if (a.sum_tiles && tid == 0 && v == nwork - 1)
+            leave_total(a, base + tot);
         if (r < rend && part == 0)
             a.out_rowptr[r] = base + loc;
         row_loc[tid] = base + loc;
@@ -551,6 +602,19 @@ static void launch_nw_sample_wide(const Launch &L, const NwHop &a, const VSet &v
         hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, 0>), dim3(grid_for(L, tiles * parts, 4)), block, 0, L.stream, a, vs, parts);
 }
 
+template <bool SET, bool REPLACE, bool SUM>
+static void launch_nw_sample_lanes(const Launch &L, const NwHop &a, const VSet &vs, int grid)
+{
+    void (*const kernels[6])(NwHop, VSet) = {nw_sample_kernel<4, SET, REPLACE, SUM>,
+                                             nw_sample_kernel<8, SET, REPLACE, SUM>,
+                                             nw_sample_kernel<16, SET, REPLACE, SUM>,
+                                             nw_sample_kernel<32, SET, REPLACE, SUM>,
+                                             nw_sample_kernel<REPLACE ? 32 : 48, SET, REPLACE, SUM>,
+                                             nw_sample_kernel<REPLACE ? 32 : 64, SET, REPLACE, SUM>};
+    const int which = a.s <= 4 ? 0 : a.s <= 8 ? 1 : a.s <= 16 ? 2 : a.s <= 32 ? 3 : a.s <= 48 ? 4 : 5;
+    hipLaunchKernelGGL(kernels[which], dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
+}
+
 // Fanouts of 33 .. 64 by one row per lane from this many rows on.  A draw is two instructions per place then, for 64 rows at once,
 // where a row that has the wave to itself spends some ten on it; but with fewer rows most of the chip's waves have none.  Whole
 // calls of one hop on 2.4 M vertices of 38 neighbours, by lanes and by waves, us:
@@ -587,18 +651,10 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
         grid = std::max(grid / a.k, 1) * a.k;
     else
         a.seg_cnt = nullptr;
-    if (a.s <= 4)
-        hipLaunchKernelGGL((nw_sample_kernel<4, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
-    else if (a.s <= 8)
-        hipLaunchKernelGGL((nw_sample_kernel<8, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
-    else if (a.s <= 16)
-        hipLaunchKernelGGL((nw_sample_kernel<16, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
-    else if (REPLACE || a.s <= 32)
-        hipLaunchKernelGGL((nw_sample_kernel<32, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
-    else if (a.s <= 48)
-        hipLaunchKernelGGL((nw_sample_kernel<REPLACE ? 32 : 48, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
+    if (a.sum_tiles)
+        launch_nw_sample_lanes<SET, REPLACE, true>(L, a, vs, grid);
     else
-        hipLaunchKernelGGL((nw_sample_kernel<REPLACE ? 32 : 64, SET, REPLACE>), dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
+        launch_nw_sample_lanes<SET, REPLACE, false>(L, a, vs, grid);
     return a.seg_cnt != nullptr;
 }
 

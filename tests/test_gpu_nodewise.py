@@ -637,3 +637,21 @@ def test_sort_extract_buckets_of_equal_and_near_ids(mods, share, spread):
     col = np.concatenate(rows).astype(np.int32)
     batches = np.stack([rng.permutation(b) for _ in range(5)]).astype(np.int32)
     _run_both(mods, rowptr, col, batches, (20,), 3)
+
+
+@pytest.mark.parametrize("k,b,fanouts", [(1, 300, (16, 16, 2)), (1, 1, (17, 40)), (5, 2000, (17, 3)), (4, 16000, (17, 2)), (5, 600, (40, 33))])
+def test_tiles_summed_by_the_sampling_kernel(mods, k, b, fanouts):
+    # recycled calls: 1 to 1024 tiles of rows and more, one row per lane and per wave; no rows at all (seeds without neighbours)
+    rng = np.random.default_rng(b)
+    n = 70_000
+    degree = rng.integers(0, 60, n)
+    degree[:3000] = 0
+    rowptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, d, replace=False)) for d in degree]).astype(np.int32)
+    O, bms, _ = mods
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for seed, pool in ((1, np.arange(n)), (2, np.arange(n)), (3, np.arange(3000) if k * b <= 3000 else np.arange(n)), (4, np.arange(n))):
+        batches = random_batches(n, k, b, rng, candidates=pool)
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, seed, recycle=res)
+        assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, fanouts, seed), what="seed=%d" % seed)
