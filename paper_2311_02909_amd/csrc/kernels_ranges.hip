@@ -46,14 +46,67 @@ __device__ inline uint32_t quad_popc(const uint4 &q) { return __popc(q.x) + __po
 // range of a quad: exact, as quads * qw < 2^32 unless qw is a power of two
 __device__ inline uint32_t range_of(const RangeArgs &a, uint32_t quad) { return __umulhi(quad, a.qw_inverse); }
 
-// The counts of all (minibatch, range) pairs are in a.cnt; run by one workgroup of NT threads.
+// The counts of all (minibatch, range) pairs are in a.cnt; run by one workgroup of NT threads, which everything after it waits
+// for.  room: NT + 1 words of LDS.
+// Up to NT pairs without going through memory and in 32 bits (a range has no more than 1.3 million ids): 6 us of a hop before, 1.5 so (count
+// kernel of one minibatch 10 -> 5.2 us, mark kernels 3 to 5 us less).
 template <int NT>
-__device__ inline void ranges_place(const RangeArgs &a)
+__device__ inline void ranges_place(const RangeArgs &a, uint32_t *room)
 {
     __shared__ int64_t smem[NT / kWave];
     __shared__ int32_t most_s;
     const int tid = threadIdx.x;
     const int64_t m = (int64_t)a.k * a.H;
+    if (m <= NT) {
+        uint32_t *wsum = reinterpret_cast<uint32_t *>(smem); // two sums per wave
+        const int lane = tid & (kWave - 1), wave = tid / kWave;
+        // exclusive scan, the total; half: which of the two words per wave
+        auto scan = [&](uint32_t v, int half, uint32_t &total) {
+            const uint32_t upto = wave_inclusive_scan_dpp(v);
+            if (lane == kWave - 1)
+                wsum[half * (NT / kWave) + wave] = upto;
+            __syncthreads();
+            uint32_t before = 0;
+            total = 0;
+#pragma unroll
+            for (int x = 0; x < NT / kWave; ++x) {
+                const uint32_t sum = wsum[half * (NT / kWave) + x];
+                before += x < wave ? sum : 0u;
+                total += sum;
+            }
+            return before + upto - v;
+        };
+        if (tid == 0)
+            most_s = 0;
+        const uint32_t v = tid < m ? __hip_atomic_load(a.cnt + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        uint32_t columns, tiles_all;
+        const uint32_t ex = scan(v, 0, columns);
+        room[tid] = ex;
+        if (tid == 0)
+            room[NT] = columns;
+        __syncthreads();
+        uint32_t tiles = 0, c0 = 0;
+        if (tid < a.k) {
+            c0 = room[tid * a.H];
+            tiles = (room[tid + 1 < a.k ? (tid + 1) * a.H : NT] - c0 + kRowTile - 1) / kRowTile;
+            atomicMax(&most_s, (int32_t)tiles);
+        }
+        const uint32_t tile0 = scan(tiles, 1, tiles_all);
+        if (tid < m)
+            a.first[tid] = ex;
+        if (tid < a.k) {
+            a.mb_coloff[tid] = c0;
+            a.next_tileoff[tid] = tile0;
+        }
+        if (tid == 0) {
+            a.first[m] = columns;
+            a.mb_coloff[a.k] = columns;
+            *a.ncols_out = columns;
+            a.next_tileoff[a.k] = tiles_all;
+            a.next_tileoff[a.k + 1] = most_s;
+        }
+        return;
+    }
     int64_t carry = 0;
     for (int64_t base = 0; base < m; base += NT) {
         const int64_t x = base + tid;
@@ -246,7 +299,7 @@ __global__ __launch_bounds__(kRgThreads) void rg_mark_kernel(RangeArgs a, int32_
             }
         __syncthreads();
         if (last_s)
-            ranges_place<kRgThreads>(a);
+            ranges_place<kRgThreads>(a, words); // (the bitmap has left)
         return;
     }
     uint4 *__restrict__ out = a.bits + ((int64_t)part * a.k + i) * a.stride;
@@ -263,7 +316,7 @@ __global__ __launch_bounds__(kRgThreads) void rg_mark_kernel(RangeArgs a, int32_
 __global__ __launch_bounds__(kRgThreads) void rg_count_kernel(RangeArgs a)
 {
     constexpr int ITS = kRangeQuads / kRgThreads;
-    __shared__ uint32_t wtot[kRgWaves];
+    __shared__ uint32_t wtot[kRgWaves], room[kRgThreads + 1];
     __shared__ uint32_t last_s;
     const int tid = threadIdx.x;
     const int i = (int)(blockIdx.x % (uint32_t)a.k), w = (int)(blockIdx.x / (uint32_t)a.k);
@@ -292,7 +345,7 @@ __global__ __launch_bounds__(kRgThreads) void rg_count_kernel(RangeArgs a)
     }
     __syncthreads();
     if (last_s)
-        ranges_place<kRgThreads>(a);
+        ranges_place<kRgThreads>(a, room);
 }
 
 // Set bits -> ids, wave x of nx: steps of kEmitQuads quads of a minibatch, a word per lane.  The set bits before a quad are known,

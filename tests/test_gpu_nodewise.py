@@ -655,3 +655,20 @@ def test_tiles_summed_by_the_sampling_kernel(mods, k, b, fanouts):
         batches = random_batches(n, k, b, rng, candidates=pool)
         res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, seed, recycle=res)
         assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, fanouts, seed), what="seed=%d" % seed)
+
+
+@pytest.mark.parametrize("k,n", [(1025, 3000), (400, 400_000), (100, 1_400_000)])
+def test_column_offsets_of_many_minibatches_and_ranges(mods, k, n):
+    # around 1024 pairs of (minibatch, range of ids), which are placed at once up to there
+    rng = np.random.default_rng(k)
+    degree = 30
+    rows = rng.permutation(n)[:2000]
+    deg = np.zeros(n, dtype=np.int64)
+    deg[rows] = degree
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, degree, replace=False)) for _ in range(2000)]).astype(np.int32)
+    batches = random_batches(n, k, 20 if k > 1024 else 700, rng, candidates=rows)
+    O, bms, _ = mods
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (25, 4), 6)
+    assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, (25, 4), 6))
