@@ -33,37 +33,37 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 3_314_966_720,
-    ("dense_ladies", "ldw_p_copy"): 3_143_346_976,
-    ("dense_ladies", "ldw_extract"): 2_022_134_848,
-    ("dense_sage", "nw_sample"): 9_763_640_864,
-    ("dense_sage", "nw_rows"): 1_355_784_128,
-    ("dense_sage", "dd_split"): 1_121_184_672,
-    ("dense_sage", "dd_unsplit"): 991_191_232,
-    ("dense_sage", "dd_rank"): 845_958_336,
-    ("dense_sage", "dd_front"): 603_921_568,
-    ("large_sage", "nw_sample"): 5_021_632_416,
-    ("large_sage", "nw_rows"): 1_607_832_576,
-    ("large_sage", "dd_split"): 740_146_848,
-    ("large_sage", "dd_unsplit"): 676_007_648,
-    ("large_sage", "dd_rank"): 587_625_664,
-    ("large_sage", "dd_front"): 464_219_072,
-    ("mid_ladies", "ldw_p_copy"): 172_208_800,
-    ("mid_ladies", "ldw_accumulate"): 150_433_568,
-    ("mid_ladies", "ldw_extract"): 85_108_928,
-    ("mid_sage", "nw_sample"): 2_607_554_240,
-    ("mid_sage", "nw_rows"): 342_199_840,
-    ("mid_sage", "rg_lookup"): 329_944_928,
-    ("mid_sage", "rg_mark"): 190_089_152,
-    ("mid_sage", "rg_emit"): 147_362_912,
+    ("dense_ladies", "ldw_accumulate"): 3_419_158_336,
+    ("dense_ladies", "ldw_p_copy"): 3_152_821_120,
+    ("dense_ladies", "ldw_extract"): 2_022_081_248,
+    ("dense_sage", "nw_sample"): 9_757_779_360,
+    ("dense_sage", "nw_rows"): 426_292_800,
+    ("dense_sage", "dd_split"): 1_121_317_184,
+    ("dense_sage", "dd_unsplit"): 992_679_648,
+    ("dense_sage", "dd_rank"): 845_933_664,
+    ("dense_sage", "dd_front"): 603_942_176,
+    ("large_sage", "nw_sample"): 5_021_728_960,
+    ("large_sage", "nw_rows"): 1_256_466_656,
+    ("large_sage", "dd_split"): 739_783_488,
+    ("large_sage", "dd_unsplit"): 674_898_880,
+    ("large_sage", "dd_rank"): 587_770_816,
+    ("large_sage", "dd_front"): 464_181_536,
+    ("mid_ladies", "ldw_p_copy"): 167_682_560,
+    ("mid_ladies", "ldw_accumulate"): 148_399_488,
+    ("mid_ladies", "ldw_extract"): 85_025_536,
+    ("mid_sage", "nw_sample"): 2_680_505_664,
+    ("mid_sage", "nw_rows"): 144_805_568,
+    ("mid_sage", "rg_lookup"): 330_158_624,
+    ("mid_sage", "rg_mark"): 190_080_576,
+    ("mid_sage", "rg_emit"): 150_483_616,
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 9_286_762_752,
-    "dense_sage": 14_776_709_536,
-    "large_sage": 9_185_574_016,
-    "mid_ladies": 464_460_416,
-    "mid_sage": 3_651_671_040,
+    "dense_ladies": 9_399_476_096,
+    "dense_sage": 13_840_762_784,
+    "large_sage": 8_828_308_640,
+    "mid_ladies": 456_880_608,
+    "mid_sage": 3_529_696_384,
 }
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 

@@ -123,7 +123,7 @@ struct TileWalk {
 // of distinct picks.
 // What bounds it is the number of rowptr lines on their way.  A wave takes a tile of its own, four rows per lane, and needs no
 // barrier.  Two hops each: 256 x 1024 seeds, (15, 10, 5), 111 M vertices: 265 -> 235 us; 128 minibatches on 8.7 M vertices:
-// 236 -> 186 us; 32 on 2.4 M: 71 -> 56 us.  Of workgroups per compute unit, 4 are best: 1, 2, 4 and 16 take 238, 199, 186 and
+// 236 -> 186 us; 64 on 2.4 M: 71 -> 56 us.  Of workgroups per compute unit, 4 are best: 1, 2, 4 and 16 take 238, 199, 186 and
 // 193 us (8.7 M vertices), 77, 63, 56 us (2.4 M): fewer have too few lines on their way, more touch a larger part of the ids.
 constexpr int kTileRounds = kRowTile / kWave;
 template <int S>
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
 // A row's draws are one chain, so what counts is the instructions per draw and how many rows are in progress: across the
 // lanes a draw takes about 8 vector instructions and no trip to LDS, and `parts` workgroups share the rows of a tile so
 // that hops of few rows still fill the chip.  8 minibatches of 512, fanouts (40, 40), 2.4 M vertices: the two hops took
-// 547 + 1353 us with the list in LDS and one workgroup per tile, 9 + 73 us so.
+// 547 + 1353 us with the list in LDS and one workgroup per tile, 9 + 73 us so (the second one row per lane now: launch_nw_sample_impl).
 // ---------------------------------------------------------------------------------------------
 template <bool SET, bool REPLACE, int K>
 __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet vs, int32_t parts)

@@ -350,8 +350,8 @@ __global__ __launch_bounds__(kRgThreads) void rg_count_kernel(RangeArgs a)
 
 // Set bits -> ids, wave x of nx: steps of kEmitQuads quads of a minibatch, a word per lane.  The set bits before a quad are known,
 // so a wave needs no other and waits for none.  places: LDS of this wave, kEmitQuads * 128 16-bit values.
-// Half vector instructions (100 per step and ten per round of bits), half the step's own chain.  Two hops of 32 x 1024 seeds, (15,
-// 10, 5), 2.4 M vertices (2 and 9 million columns): 54 us by workgroups of 1024 in steps of 32768 ids with three barriers, 38.5 so;
+// Half vector instructions (100 per step and ten per round of bits), half the step's own chain.  Two hops of 64 x 1024 seeds, (15,
+// 10, 5), 2.4 M vertices: 54 us by workgroups of 1024 in steps of 32768 ids with three barriers, 38.5 so;
 // eighths of the steps per die, or the range's first column fetched a step ahead, change nothing.
 __device__ inline void emit_steps(const RangeArgs &a, int32_t *__restrict__ col_vertex, uint16_t *places, uint32_t x, uint32_t nx)
 {

@@ -15,12 +15,12 @@
 //            started earlier and wait for nobody after them: every wait ends, whatever else runs on the chip.
 // Measured on 2.4 M vertices, one hop per call, s = 16, whole calls: k minibatches of b seeds here and by the chip-wide path
 //   k     b = 64     b = 256    b = 512    b = 1000 (11 k entries per minibatch)
-//   1     26, 42     28, 50     34, 50     46, 51 us
-//   4     26, 51     28, 61     34, 63     48, 63
-//   16    25, 67     29, 81     35, 74     48, 76
-//   64    27, 68     31, 84     37, 78     52, 85
-//   256   37, 80     45, 96     54, 98     73, 123
-// so it takes every hop that fits its LDS (kSmallCap), whatever the number of minibatches; two hops (5, 5) of 4 x 64: 57 us.
+//   1     22, 32     23, 37     27, 39     32, 39 us
+//   4     22, 38     24, 48     26, 49     35, 52
+//   16    23, 62     24, 69     27, 76     35, 70
+//   64    24, 63     26, 71     28, 80     38, 76
+//   256   33, 66     36, 78     42, 93     56, 99
+// so it takes every hop that fits its LDS (kSmallCap), whatever the number of minibatches; two hops (5, 5) of 4 x 64: 28, 62 us.
 #include "bms_device.h"
 #include "bms_internal.h"
 #include "nw_draws.h"

@@ -285,3 +285,18 @@ def test_rows_over_many_tiles_and_windows(mods, n, k, degree):
     for i in range(k):
         batches[i, 1:] = rng.permutation(np.arange(1, rows))[:rows // 2 - 1]
     _run_both(mods, rowptr, col, batches, (300,), 13, mb_base=4)
+
+
+@pytest.mark.parametrize("n,degree,squared", [(40_000, 21_000, False), (2_600_000, 1_200_000, False), (4_500_000, 2_400_000, True)])
+def test_draws_through_sums_of_blocks_and_groups(mods, n, degree, squared):
+    # rows of P of just over 2048 blocks of 16 entries, and of over 2 and 4 million entries (groups of 2, 128 and 256 blocks in LDS,
+    # the place in the group found by one and by three rounds of probes); the minibatches begin and end anywhere in a block
+    rng = np.random.default_rng(n)
+    rows = 6
+    deg = np.zeros(n, dtype=np.int64)
+    deg[:rows] = degree - np.arange(rows) * 77
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.permutation(n)[:d]) for d in deg[:rows]]).astype(np.int32)
+    batches = np.array([[0, 1, 2], [3, 4, 5], [0, 3, 4]], dtype=np.int32)
+    for s in ((700,), (2048,), (4096,)):
+        _run_both(mods, rowptr, col, batches, s, 5, mb_base=2, squared=squared)
