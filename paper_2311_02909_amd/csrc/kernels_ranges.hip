@@ -18,8 +18,9 @@
 // launches a hop) the ids are read twice and written once, in 6 launches, 5 for few entries.  What bounds mark and lookup
 // are the instructions per entry and range (about 10, however few of 64 ids are inside the range).  The work
 // grows with the number of ranges, so this is the path of graphs of a few million vertices (ranges_apply in bms_api.hip).
-// Measured on the last hop of 64 x 1024 seeds, (15, 10, 5), 2.4 M vertices (27.9 M entries, 18.8 M columns): mark 52, emit 32,
-// lookup 76 us where the cut takes 288 us; 8 minibatches 61 and 82 us, one (442 k entries) 22 and 66.
+// Measured on the last hop of 64 x 1024 seeds, (15, 10, 5), 2.4 M vertices (27.9 M entries, 18.8 M columns): mark 50, emit 22,
+// lookup 73 us where the cut took 288 us; 8 minibatches 61 and 82 us, one (442 k entries) 22 and 66 when they were compared (5 to
+// 10 us less on this side since).
 // With BMS_UNION_DST the frontier's own vertices are marked and looked up as well, straight from the frontier: rows carry
 // no extra entry.
 #include "bms_device.h"
