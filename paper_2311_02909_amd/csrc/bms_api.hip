@@ -896,7 +896,12 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
 //      3 x 30 M 174 and 177, 1 x 111 M 159 and 162, 4 x 30 M 199 and 179, 4 x 111 M 316 and 175)
 //   2  the ranges take up to 8 tables (4.9 million ids: a look-up costs about 0.5 ps per entry and table, the cut into segments
 //      9), and the bitmaps are no larger than what the entries themselves move in a few passes (16 bytes of ids and counts
-//      per 128 ids, against the segments' 30 bytes per entry)
+//      per 128 ids, against the segments' 30 bytes per entry); or the bitmaps are so small, k n up to 150 million, that four
+//      launches instead of nine decide (hops of up to 4096 entries a minibatch have a kernel of their own instead).  Calls of
+//      one hop of (40) over 2.4 M vertices, by segments and so: 8 minibatches of 128, 256, 512 seeds 74, 79, 75 and 52, 53, 55 us,
+//      60 of them (k n = 144 M) 85, 106, 113 and 74, 83, 99; over 4.8 M vertices 8: 72, 78, 85 and 64, 64, 67, 30 (144 M):
+//      77, 87, 103 and 79, 84, 93; at k n = 307 M and 70 ids per entry, 64 of 4.8 M 144 and 155 us, 128 of 2.4 M 141 and 130
+constexpr double kMostIdsMarked = 1.5e8;
 int ranges_apply(const CallCtx &c, double entries)
 {
     const int64_t n = c.csr->n;
@@ -907,7 +912,10 @@ int ranges_apply(const CallCtx &c, double entries)
         return 0;
     if (c.k <= kRangesFewMb && entries <= 1.5e6 && (double)c.k * (double)n <= kMostIdsInMemory)
         return 1;
-    return ranges_passes(n) <= 8 && (double)c.k * (double)n <= 64.0 * entries ? 2 : 0;
+    if (ranges_passes(n) > 8)
+        return 0;
+    const double ids = (double)c.k * (double)n;
+    return ids <= 64.0 * entries || (ids <= kMostIdsMarked && entries > 4096.0 * c.k) ? 2 : 0;
 }
 
 // One attempt.  *redo receives the hops (bits) whose EXTRACT by id-range segments gave up (ids crowded into a narrow

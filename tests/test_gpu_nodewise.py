@@ -672,3 +672,30 @@ def test_column_offsets_of_many_minibatches_and_ranges(mods, k, n):
     csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
     res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (25, 4), 6)
     assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, (25, 4), 6))
+
+
+@pytest.mark.parametrize("n,k,b,fanouts", [(1_300_000, 6, 200, (40,)), (4_900_000, 5, 150, (33, 2)), (2_000_000, 74, 104, (40,)), (2_000_000, 76, 104, (40,))])
+@pytest.mark.parametrize("variant", [{}, dict(union_dst=True), dict(replace=True)], ids=lambda v: "+".join(v))
+def test_hops_whose_bitmaps_are_small_go_by_ranges(mods, n, k, b, fanouts, variant):
+    # many more than 64 ids of [0, n) per entry: by ranges up to 150 million ids in all minibatches' bitmaps (and the same
+    # just above), entries at both ends of the id range
+    rng = np.random.default_rng(n + k)
+    rows = np.unique(np.concatenate([[0, n - 1], rng.choice(n, 1500, replace=False)]))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[rows] = rng.integers(30, 60, rows.size)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    parts = []
+    for d in deg[rows]:
+        c = np.unique(np.concatenate([rng.choice(n, d - 2, replace=False), [0, n - 1]]))
+        while c.size < d:
+            c = np.unique(np.append(c, rng.integers(0, n)))
+        parts.append(c)
+    col = np.concatenate(parts).astype(np.int32)
+    batches = random_batches(n, k, b, rng, candidates=rows)
+    O, bms, _ = mods
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, fanouts, 8, **variant)
+    res = None
+    for _ in range(2):
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 8, recycle=res, **variant)
+        assert_hops_equal(res.hops(), ref)
