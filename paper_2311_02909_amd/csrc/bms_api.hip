@@ -1241,13 +1241,18 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             g.rowptr = a.out_rowptr;
             g.col = a.out_col;
             g.row_self = union_dst ? hb.row_self.as<int32_t>() : nullptr;
+            // Few entries are looked up one by one in memory, beside the launch that writes the columns out: about 30 ps per entry,
+            // where a table of the look-up in LDS takes some 6 us and all its launch.  Level at 0.4, 0.6, 0.9 and 1.7 million entries
+            // for 1, 2, 4 and 8 tables.  Calls of one hop of (40), 2.4 M vertices (4 tables), by tables and so: 8 x 128, 256, 512 seeds
+            // 49, 50, 54 and 40, 42, 46 us; 60 x 512 (1 million entries) 96 and 98; (15, 10) of 16 x 1024 (1.6 million) 134 and 139.
+            const bool gather = ranges == 1 || (expected <= 2e5 * (1 + ranges_passes(csr->n)) && c.k <= kMostGatheredMb);
             BMS_TRY(prof.begin(ranges == 1 ? "rg_count" : "rg_mark", h));
             if (ranges == 1)
                 launch_ranges_count(c.launch, g);
             else if (launch_ranges_mark(c.launch, g) != 0)
                 return fail(BMS_EHIP, "launch of the range bitmap kernel was refused");
-            BMS_TRY(prof.mark(ranges == 1 ? "rg_emit_gather" : "rg_emit", h));
-            if (ranges == 1) {
+            BMS_TRY(prof.mark(gather ? "rg_emit_gather" : "rg_emit", h));
+            if (gather) {
                 launch_ranges_emit_gather(c.launch, g, hb.col_vertex.as<int32_t>(), (int64_t)expected);
             } else {
                 launch_ranges_emit(c.launch, g, hb.col_vertex.as<int32_t>());

@@ -162,6 +162,7 @@ int launch_nw_small(const Launch &, const NwSmall &, bool replace); // -1: launc
 
 // EXTRACT by bitmaps of vertex ranges (kernels_ranges.hip)
 constexpr int32_t kRangeQuads = 4096;  // quads of 128 ids per range of the count kernel
+constexpr int32_t kMostGatheredMb = 8191; // minibatches whose entries may be looked up one by one
 constexpr int32_t kRangesFewMb = 4;    // so few minibatches: the sampling kernel sets the bits in memory
 struct RangeArgs {
     int64_t n;

@@ -410,7 +410,8 @@ __global__ __launch_bounds__(kEmitThreads) void rg_emit_kernel(RangeArgs a, int3
     emit_steps(a, col_vertex, places[wave], blockIdx.x * (kEmitThreads / kWave) + wave, gridDim.x * (kEmitThreads / kWave));
 }
 
-// Few entries: the first `emitters` workgroups emit, the others look entries up one by one, 4 per thread in flight.
+static_assert((kMostGatheredMb + 1) * sizeof(int64_t) <= kRgWaves * kEmitQuads * 128 * sizeof(uint16_t), "minibatches out of step");
+// Few entries: the first `emitters` workgroups emit, the others look entries up one by one.
 __global__ __launch_bounds__(kRgThreads) void rg_emit_gather_kernel(RangeArgs a, int32_t *__restrict__ col_vertex, int emitters)
 {
     __shared__ uint16_t places[kRgWaves][kEmitQuads * 128];
@@ -431,15 +432,21 @@ __global__ __launch_bounds__(kRgThreads) void rg_emit_gather_kernel(RangeArgs a,
         return (int32_t)(a.first[i * a.H + r] - a.first[i * a.H]) +
                (int32_t)(a.pre[q] + (w > 0 ? __popc(v.x) : 0) + (w > 1 ? __popc(v.y) : 0) + (w > 2 ? __popc(v.z) : 0) + __popc(word & below));
     };
-    for (int32_t i = 0; i < a.k; ++i) {
-        const int64_t r0 = a.mb_rowoff[i], r1 = a.mb_rowoff[i + 1];
-        const int64_t e0 = a.rowptr[r0], e1 = a.rowptr[r1];
-        for (int64_t e = e0 + x * kRgThreads + threadIdx.x; e < e1; e += nx * kRgThreads)
-            a.col[e] = column(i, (uint32_t)a.col[e]);
-        if (a.row_self)
-            for (int64_t r = r0 + x * kRgThreads + threadIdx.x; r < r1; r += nx * kRgThreads)
-                a.row_self[r] = column(i, (uint32_t)a.row_vertex[r]);
-    }
+    // the entries (then the rows) of all minibatches one after the other, whose minibatch is found in LDS
+    int64_t *begin = reinterpret_cast<int64_t *>(places); // k + 1 <= kMostGatheredMb
+    for (int32_t i = threadIdx.x; i <= a.k; i += kRgThreads)
+        begin[i] = a.rowptr[a.mb_rowoff[i]];
+    __syncthreads();
+    for (int64_t e = begin[0] + x * kRgThreads + threadIdx.x; e < begin[a.k]; e += nx * kRgThreads)
+        a.col[e] = column(locate_segment(begin, a.k, e), (uint32_t)a.col[e]);
+    if (!a.row_self)
+        return;
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i <= a.k; i += kRgThreads)
+        begin[i] = a.mb_rowoff[i];
+    __syncthreads();
+    for (int64_t r = begin[0] + x * kRgThreads + threadIdx.x; r < begin[a.k]; r += nx * kRgThreads)
+        a.row_self[r] = column(locate_segment(begin, a.k, r), (uint32_t)a.row_vertex[r]);
 }
 
 // Chunks of PER * 1024 entries of a minibatch (and, with row_self, of its rows behind them), in registers; `chunks`
