@@ -902,13 +902,14 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
 //      60 of them (k n = 144 M) 85, 106, 113 and 74, 83, 99; over 4.8 M vertices 8: 72, 78, 85 and 64, 64, 67, 30 (144 M):
 //      77, 87, 103 and 79, 84, 93; at k n = 307 M and 70 ids per entry, 64 of 4.8 M 144 and 155 us, 128 of 2.4 M 141 and 130
 constexpr double kMostIdsMarked = 1.5e8;
+constexpr int64_t kLeastRangeQuads = 1024; // quads of a range, between this and 9 times as many
+inline int64_t most_range_quads(int64_t n) { return (n + 127) / 128 + 9 * kLeastRangeQuads; } // with what rounds the last range up
 int ranges_apply(const CallCtx &c, double entries)
 {
     const int64_t n = c.csr->n;
     if (n < 1 || (c.flags & (BMS_EXTRACT_SORT | BMS_EXTRACT_BUCKETS | BMS_EXTRACT_BITMAP)) || staged_by(c, BMS_PROFILE))
         return 0;
-    const int64_t most_quads = (n + 127) / 128 + 9 * 1024; // with what rounds the last range up
-    if ((int64_t)c.k * most_quads * 20 > c.scratch_limit / 4) // one bitmap per minibatch; plan_ranges takes more as they fit
+    if ((int64_t)c.k * most_range_quads(n) * 20 > c.scratch_limit / 4) // one bitmap per minibatch; plan_ranges takes more as they fit
         return 0;
     if (c.k <= kRangesFewMb && entries <= 1.5e6 && (double)c.k * (double)n <= kMostIdsInMemory)
         return 1;
@@ -916,6 +917,38 @@ int ranges_apply(const CallCtx &c, double entries)
         return 0;
     const double ids = (double)c.k * (double)n;
     return ids <= 64.0 * entries || (ids <= kMostIdsMarked && entries > 4096.0 * c.k) ? 2 : 0;
+}
+
+// Bitmaps and counts of a hop by ranges (g: its plan), and in the same allocation of the later hops that may go by ranges: `entries`
+// bounds the entries of this hop, on recycled calls the remembered sizes say those of all.  A hop's bitmaps can be 16 times the ones
+// before (a minibatch's ids marked by several workgroups), and buffers that grow in the middle of a call are freed there, which waits
+// for the device, and allocated again, which takes the runtime 0.3 ms for a size that it has not at hand: the first call of 8
+// minibatches of 512, (40, 40), 2.4 M vertices (2.5 MB, then 42) 1.1 ms, 0.46 in one piece.  The bound of a later hop asks for no more
+// than a quarter of the scratch limit, like its plan.
+int reserve_ranges(CallCtx &c, const RangeArgs &g, const int32_t *fanouts, int32_t h, double entries, bool no_wait)
+{
+    bms_csr *csr = c.csr;
+    const int64_t most_stride = most_range_quads(g.n); // whatever the width of the ranges
+    const double all = (double)c.k * (double)g.n, self = (c.flags & BMS_UNION_DST) ? 1.0 : 0.0;
+    int64_t quads = g.parts * g.stride, stride = g.stride;
+    int32_t H = g.H;
+    for (int32_t x = h + 1; x < c.L; ++x) {
+        entries = no_wait ? (double)std::max<int64_t>(c.res->hint_nnz[x], 1)
+                          : std::min(entries, all) * ((double)std::min<int64_t>(fanouts[x], std::max<int64_t>(csr->max_degree, 1)) + self);
+        const int ranges = ranges_apply(c, entries);
+        if (!ranges)
+            continue;
+        RangeArgs later = g;
+        later.parts = 1;
+        if (ranges == 2)
+            plan_ranges(later, csr->num_cu, entries / c.k, c.scratch_limit / 4);
+        quads = std::max({quads, most_stride, later.parts * ((g.quads + kRangeQuads - 1) / kRangeQuads * kRangeQuads)});
+        stride = most_stride;
+        H = std::max<int32_t>(H, (int32_t)(g.quads / kLeastRangeQuads) + 1);
+    }
+    BMS_TRY(csr->rg_bits.ensure((size_t)c.k * quads * sizeof(uint4)));
+    BMS_TRY(csr->rg_pre.ensure((size_t)c.k * stride * sizeof(uint32_t)));
+    return csr->rg_count.ensure(((size_t)c.k * H + 1) * (sizeof(int64_t) + sizeof(uint32_t)) + 64);
 }
 
 // One attempt.  *redo receives the hops (bits) whose EXTRACT by id-range segments gave up (ids crowded into a narrow
@@ -1019,9 +1052,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             g.qw_inverse = (uint32_t)((0x100000000ULL + g.qw - 1) / g.qw);
             g.H = (int32_t)((g.quads + g.qw - 1) / g.qw);
             g.stride = (int64_t)g.H * g.qw;
-            BMS_TRY(csr->rg_bits.ensure((size_t)g.parts * c.k * g.stride * sizeof(uint4)));
-            BMS_TRY(csr->rg_pre.ensure((size_t)c.k * g.stride * sizeof(uint32_t)));
-            BMS_TRY(csr->rg_count.ensure(((size_t)c.k * g.H + 1) * (sizeof(int64_t) + sizeof(uint32_t)) + 64));
+            BMS_TRY(reserve_ranges(c, g, fanouts, h, expected, no_wait));
             g.bits = csr->rg_bits.as<uint4>();
             g.pre = csr->rg_pre.as<uint32_t>();
             g.first = csr->rg_count.as<int64_t>();

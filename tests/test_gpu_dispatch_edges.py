@@ -218,3 +218,27 @@ def test_bitmaps_of_vertex_ranges_stay_inside_the_scratch_limit():
         ref = ref or got
         for a, b in zip(got, ref):
             assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_bitmaps_of_all_hops_are_allocated_before_the_first_one_runs():
+    # hop 0 takes one bitmap per minibatch, hop 1 several: what the handle holds is looked at when the result's buffers are allocated
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(21)
+    rowptr, col = random_csr(300_000, 14.0, rng)
+    batches = random_batches(300_000, 5, 1500, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    held, allocator = [], bms.TorchAllocator()
+    alloc = allocator.alloc
+
+    def look(nbytes, ctx):
+        held.append(csr.held_bytes())
+        return alloc(nbytes, ctx)
+    allocator.alloc = bms.ALLOC_FN(look)
+    res = bms.sample_nodewise(csr, batches, (40, 40), 3, allocator=allocator)
+    assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, (40, 40), 3), what="two hops by ranges")
+    assert len(held) == 2 + 2 * 4   # seeds and their offsets, then per hop row and column offsets, columns and their vertices
+    rows = res.hop(0).nnz           # the bound of hop 1's rows: 12 bytes each, and 8 per tile of 256
+    assert held[-1] - held[5] <= 13 * rows + 4096, held
+    parts = bms.sample_nodewise(csr, batches, (40, 40), 3, recycle=res, profile="as_run")
+    assert {(x, h) for x, h, _ in parts.stages()} >= {("rg_mark", 0), ("rg_mark", 1)}
