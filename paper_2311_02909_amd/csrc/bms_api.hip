@@ -239,7 +239,7 @@ struct bms_result {
     // next call enqueue every hop without waiting for the device (buffers sized by upper bounds)
     uint64_t hint_csr = 0; // serial number of the handle; 0: none
     std::vector<int32_t> hint_shape; // k, b, fanouts...
-    std::vector<int64_t> hint_nnz;   // per hop
+    std::vector<int64_t> hint_nnz, hint_rows; // per hop (rows: node-wise calls)
     int32_t attempts = 1; // how often the call that wrote this result enqueued its kernels
     std::vector<int64_t> hint_gathered, hint_pnnz; // per hop, layer-wise calls: gathered neighbours D, nnz(P)
     // how each hop's EXTRACT went before: 0 = segments of equal width did, 1 = ids crowd parts of [0, n): segments of
@@ -704,17 +704,19 @@ int finish_nodewise(bms_result *res, const PendingNodewise &pn, const int64_t *h
             *redo |= 1u << h;
     if (*redo)
         return BMS_OK; // the call is repeated
-    std::vector<int64_t> seen_nnz((size_t)pn.L, 0);
+    std::vector<int64_t> seen_nnz((size_t)pn.L, 0), seen_rows((size_t)pn.L, 0);
     for (int32_t h = 0; h < pn.L; ++h) {
         bms_hop_view &v = res->hops[h].view;
         v.nnz = host[h * 4 + 0];
         v.ncols = host[h * 4 + 1];
         v.rows = h == 0 ? (int64_t)pn.k * pn.b : host[(h - 1) * 4 + 1];
         seen_nnz[h] = v.nnz + (pn.union_dst ? v.rows : 0); // the entries EXTRACT worked on
+        seen_rows[h] = v.rows;
     }
     res->hint_csr = pn.csr;
     res->hint_shape = pn.shape;
     res->hint_nnz = seen_nnz;
+    res->hint_rows = seen_rows;
     res->hint_mode = pn.mode;
     res->hint_table_C = pn.table_built;
     res->hint_table_ready.assign((size_t)pn.L, 0);
@@ -1119,18 +1121,24 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         BMS_TRY(prof.end());
 
         // nnz sizes the column buffers: read back (the only host round trip of the hop), or in the
-        // steady state bounded from above; nnz_tune only picks tuning parameters
+        // steady state bounded from above; nnz_tune and rows_tune only pick tuning parameters
         int64_t nnz, nnz_tune;
+        a.rows_tune = rows_bound;
         if (no_wait) { // with BMS_UNION_DST nnz counts the rows' own entries too, until the hop's last step
             nnz = rows_bound * (most_per_row + a.self_entry);
             nnz_tune = std::max<int64_t>(c.res->hint_nnz[h], 1);
+            if (h)
+                a.rows_tune = std::min(rows_bound, c.res->hint_rows[h]);
         } else {
             BMS_TRY(read_scalars(c));
             if (!seeds_checked)
                 BMS_TRY(seed_flag_error(csr->n, csr->host_pinned, c.res->host));
             seeds_checked = true;
             nnz = nnz_tune = host_slot(c, h, 0);
+            if (h)
+                a.rows_tune = host_slot(c, h - 1, 1);
         }
+        a.entries_tune = nnz_tune;
         const int64_t ncols_bound = std::min<int64_t>(nnz + (union_dst && ranges ? rows_bound : 0), (int64_t)c.k * csr->n);
         BMS_TRY(hb.col.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(int32_t)));
         BMS_TRY(hb.col_vertex.ensure((size_t)std::max<int64_t>(ncols_bound, 1) * sizeof(int32_t)));

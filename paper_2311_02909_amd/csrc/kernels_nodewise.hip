@@ -583,13 +583,14 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_wide_kernel(NwHop a, VSet 
 }
 
 // Registers per lane by fanout; above 256 positions the list's upkeep costs more than the binary search in LDS.  With
-// independent draws only the one-register form is used (64 draws sorted across the lanes).
+// independent draws only the one-register form is used (64 draws sorted across the lanes).  parts by the likely rows: by their bound
+// the workgroups that have any were too few (hops of 7000 to 18000 rows, bound 65536: calls of 94 to 122 us now 73 to 108).
 template <bool SET, bool REPLACE>
 static void launch_nw_sample_wide(const Launch &L, const NwHop &a, const VSet &vs, int64_t tiles)
 {
-    const int64_t wanted = (int64_t)L.num_cu * 8;
+    const int64_t wanted = (int64_t)L.num_cu * 8, likely = a.rows_tune / kRowTile + a.k;
     int32_t parts = 1;
-    while (parts < kRowTile / (kRowTile / kWave) && tiles * parts < wanted)
+    while (parts < kRowTile / (kRowTile / kWave) && likely * parts < wanted)
         parts <<= 1;
     const dim3 block(kRowTile);
     if (a.s <= kWave)
@@ -615,23 +616,34 @@ static void launch_nw_sample_lanes(const Launch &L, const NwHop &a, const VSet &
     hipLaunchKernelGGL(kernels[which], dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
 }
 
-// Fanouts of 33 .. 64 by one row per lane from this many rows on.  A draw is two instructions per place then, for 64 rows at once,
-// where a row that has the wave to itself spends some ten on it; but with fewer rows most of the chip's waves have none.  Whole
-// calls of one hop on 2.4 M vertices of 38 neighbours, by lanes and by waves, us:
-//   rows      s = 33      s = 40      s = 48      s = 64
-//   16384    221, 222    214, 209    197, 184    230, 190
-//   32768    202, 223    175, 178    183, 180    231, 201
-//   65536    169, 194    188, 219    210, 216    215, 233
-//   131072   241, 293    234, 283    246, 309    256, 303
-// 8 minibatches of 512, (40, 40), 2.4 M vertices of 51: the second hop's sampling 76 -> 34 us, and it counts per segment, which
-// saves 9 us more.
-constexpr int64_t kWideLaneRows = 65536;
+// Fanouts of 33 .. 64 by one row per lane from this many rows or entries on.  A draw is two instructions per place then, for 64
+// rows at once, where a row that has the wave to itself spends some ten on it; but with fewer rows most of the chip's waves have
+// none, and rows that are copied whole take a lane as long as the others.  Whole calls on 2.4 M vertices, by lanes and by waves, us:
+//   one hop, 8 minibatches       s = 33     s = 40     s = 48     s = 64
+//   38 neighbours,  24576 rows   57,  62    60,  62    62,  63    79,  66
+//                   40960        61,  69    64,  73    67,  74    84,  77
+//                   65536        72,  90    74,  93    77,  94    88, 102
+//   14 neighbours,  40960        62,  63    66,  65    69,  65    83,  65
+//                   65536        67,  76    70,  75    74,  77    85,  78
+//   two hops, the second one's million entries, 6 minibatches
+//                   0.4 to 0.5  135, 132   138, 132   131, 122   147, 132
+//                   0.7 to 0.8   96, 103   139, 137   149, 150    96,  87
+//                   1.0 to 1.1  104, 113   118, 132   121, 124   120, 115
+//                   1.4 to 1.5                        126, 140   135, 143
+// Where the kernel also sets bits (few minibatches), by waves up to the 1.4 million: 0.8 million entries 109, 101, 1.4 million 145, 142.
+// The rows and entries of later hops are what they are or were in the call before, not their bounds: 1024 seeds with (64, 64), 15000
+// rows where k b s is 65536, took 114 us by lanes and take 100.  8 minibatches of 512, (40, 40), 51 neighbours: the second hop's
+// sampling 76 -> 34 us by lanes, and it counts per segment, which saves 9 us more.
+static bool wide_by_lanes(const NwHop &a, bool set)
+{
+    return a.rows_tune >= 65536 || a.entries_tune >= (a.s <= 48 && !set ? 15'000 * a.s : 1'400'000);
+}
 template <bool SET, bool REPLACE>
 static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet &vs)
 {
     NwHop a = a_in;
     const int64_t tiles = a.rows_bound / kRowTile + a.k;
-    if (a.s > (!REPLACE && a.rows_bound >= kWideLaneRows ? 64 : 32)) {
+    if (a.s > (!REPLACE && wide_by_lanes(a, SET) ? 64 : 32)) {
         a.seg_cnt = nullptr; // one row per wave: its workgroups walk the tiles in stacked order, across minibatches
         launch_nw_sample_wide<SET, REPLACE>(L, a, vs, tiles);
         return false;

@@ -242,3 +242,33 @@ def test_bitmaps_of_all_hops_are_allocated_before_the_first_one_runs():
     assert held[-1] - held[5] <= 13 * rows + 4096, held
     parts = bms.sample_nodewise(csr, batches, (40, 40), 3, recycle=res, profile="as_run")
     assert {(x, h) for x, h, _ in parts.stages()} >= {("rg_mark", 0), ("rg_mark", 1)}
+
+
+def _kernels(call):
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in profile.events() if "nw_sample" in e.name]
+
+
+@pytest.mark.parametrize("degree,b,s,wide", [(12.0, 1024, 64, True), (12.0, 400, 40, True), (100.0, 276, 48, False)])
+def test_wide_fanouts_by_the_rows_there_are(degree, b, s, wide):
+    # the second hop's rows are 54000, 21000 and 60000 where k b s bounds them by more than 65536: by waves, or by lanes for their
+    # 3 million entries, in the first call and in recycled ones
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(b)
+    rowptr, col = random_csr(120_000, degree, rng)
+    batches = random_batches(120_000, 5, b, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, (s, s), 3)
+    res, names = None, []
+    for call in range(3):
+        def once():
+            nonlocal res
+            res = bms.sample_nodewise(csr, batches, (s, s), 3, recycle=res)
+        names.append(_kernels(once))
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+    rows, entries, _ = res.sizes()[1]
+    assert len(batches) * b * s > 65536 > rows and (entries < 900_000) == wide, (rows, entries)
+    assert all(len(x) == 2 and ("wide" in x[1]) == wide for x in names), names
