@@ -306,7 +306,7 @@ class Result:
         if stream is None:
             stream = torch.cuda.current_stream().cuda_stream
         _check(lib().bms_result_minibatch_offsets(self.handle, h, out[0].ctypes.data, out[1].ctypes.data,
-                                                  out[2].ctypes.data, stream))
+                                                  out[2].ctypes.data, _raw(stream)))
         return out
 
     def hops(self) -> List[Hop]:
@@ -352,18 +352,26 @@ def _profile_flag(profile) -> int:
     return PROFILE if profile else 0
 
 
-def _on(stream):
+def _raw(stream) -> int:
+    """The hipStream_t of a torch stream, a c_void_p or a number."""
+    stream = getattr(stream, "_as_parameter_", stream)
+    return int((stream.value or 0) if isinstance(stream, C.c_void_p) else stream)
+
+
+def _on(stream: int):
     """The raw stream as torch's current one: what is allocated or copied for work on it (a contiguous copy of the
     inputs, outputs, the buffers of a TorchAllocator) is ordered with that work, and its memory is not reused before."""
     # (torch takes a null pointer for a request of a stream from its pool)
-    return torch.cuda.stream(torch.cuda.ExternalStream(int(stream)) if int(stream) else torch.cuda.default_stream())
+    return torch.cuda.stream(torch.cuda.ExternalStream(stream) if stream else torch.cuda.default_stream())
 
 
 def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, mb_base, stream, recycle, flags,
             scratch_limit, allocator=None):
-    if stream is not None and torch.cuda.current_stream().cuda_stream != int(stream):
-        with _on(stream):
-            return _sample(ladies, csr, batches, params, seed, mb_base, stream, recycle, flags, scratch_limit, allocator)
+    if stream is not None:
+        stream = _raw(stream)
+        if torch.cuda.current_stream().cuda_stream != stream:
+            with _on(stream):
+                return _sample(ladies, csr, batches, params, seed, mb_base, stream, recycle, flags, scratch_limit, allocator)
     if isinstance(batches, np.ndarray):
         batches = torch.from_numpy(np.ascontiguousarray(batches, dtype=np.int32))
     if batches.dtype != torch.int32 or batches.dim() != 2:
@@ -426,13 +434,13 @@ def fetch_features(H: torch.Tensor, ids: torch.Tensor, out: Optional[torch.Tenso
     n, f = H.shape
     m = ids.shape[0]
     if out is None:
-        with _on(stream) if stream is not None else contextlib.nullcontext():
+        with _on(_raw(stream)) if stream is not None else contextlib.nullcontext():
             out = torch.empty((m, f), dtype=torch.float32, device=H.device)
     elif out.dtype != torch.float32 or tuple(out.shape) != (m, f) or not out.is_cuda or not out.is_contiguous():
         raise TypeError("out must be a contiguous m x f float32 device tensor")
     if stream is None:
         stream = torch.cuda.current_stream().cuda_stream
-    _check(lib().bms_fetch_features(H.data_ptr(), n, f, ids.data_ptr(), m, out.data_ptr(), stream))
+    _check(lib().bms_fetch_features(H.data_ptr(), n, f, ids.data_ptr(), m, out.data_ptr(), _raw(stream)))
     return out
 
 
@@ -446,11 +454,11 @@ def aggregate_hop(res: "Result", hop: int, X: torch.Tensor, mean: bool = True, o
         raise ValueError("X has %d rows, the hop has %d columns" % (X.shape[0], ncols))
     f = X.shape[1]
     if out is None:
-        with _on(stream) if stream is not None else contextlib.nullcontext():
+        with _on(_raw(stream)) if stream is not None else contextlib.nullcontext():
             out = torch.empty((rows, f), dtype=torch.float32, device=X.device)
     elif out.dtype != torch.float32 or tuple(out.shape) != (rows, f) or not out.is_cuda or not out.is_contiguous():
         raise TypeError("out must be a contiguous rows x f float32 device tensor")
     if stream is None:
         stream = torch.cuda.current_stream().cuda_stream
-    _check(lib().bms_aggregate_hop(res.handle, hop, X.data_ptr(), f, 1 if mean else 0, out.data_ptr(), stream))
+    _check(lib().bms_aggregate_hop(res.handle, hop, X.data_ptr(), f, 1 if mean else 0, out.data_ptr(), _raw(stream)))
     return out

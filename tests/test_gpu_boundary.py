@@ -1,5 +1,6 @@
 """The boundary's two steady-state features, through the C ABI: a caller's allocator for the result buffers, and
 asynchronous calls (BMS_ASYNC) whose sizes, errors and times are read when the result is first looked at."""
+import ctypes
 import time
 
 import numpy as np
@@ -253,3 +254,24 @@ def test_work_on_a_stream_that_is_not_current(mods, given):
             torch.cuda.synchronize()
             assert_hops_equal(res.hops(), ref, what="strided seeds on a side stream, call %d" % call)
             assert torch.equal(out, wanted) and bool((kept == call).all())
+
+
+@pytest.mark.parametrize("given", [lambda s: s, lambda s: s.cuda_stream, lambda s: s._as_parameter_, lambda s: torch.cuda.default_stream(),
+                                   lambda s: ctypes.c_void_p(0)], ids=["stream", "number", "pointer", "default stream", "null pointer"])
+def test_every_form_of_a_stream(mods, given):
+    O, bms = mods
+    rng = np.random.default_rng(86)
+    rowptr, col = random_csr(5000, 14.0, rng)
+    seeds = random_batches(5000, 4, 100, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    H = torch.randn((5000, 16), device="cuda")
+    torch.cuda.synchronize()
+    stream = given(torch.cuda.Stream())
+    res = bms.sample_nodewise(csr, seeds, (6, 5), 3, stream=stream)
+    assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, seeds, (6, 5), 3))
+    assert_hops_equal(bms.sample_ladies(csr, seeds, (9,), 3, stream=stream).hops(), O.sample_ladies(rowptr, col, seeds, (9,), 3), with_p=True)
+    x = bms.fetch_features(H, res.hop(1).col_vertex, stream=stream)
+    y = bms.aggregate_hop(res, 1, x, stream=stream)
+    offsets = res.minibatch_offsets(1, stream=stream)
+    torch.cuda.synchronize()
+    assert torch.equal(x, H[res.hop(1).col_vertex.long()]) and y.shape == (res.hop(1).rows, 16) and offsets[1, -1] == res.hop(1).nnz
