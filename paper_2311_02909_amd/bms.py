@@ -359,7 +359,7 @@ def _raw(stream) -> int:
 
 
 def _on(stream: int):
-    """The raw stream as torch's current one: what is allocated or copied for work on it (a contiguous copy of the
+    """The raw stream of the current device as torch's current one: what is allocated or copied for work on it (a contiguous copy of the
     inputs, outputs, the buffers of a TorchAllocator) is ordered with that work, and its memory is not reused before."""
     # (torch takes a null pointer for a request of a stream from its pool)
     return torch.cuda.stream(torch.cuda.ExternalStream(stream) if stream else torch.cuda.default_stream())
@@ -367,6 +367,9 @@ def _on(stream: int):
 
 def _sample(ladies: bool, csr: Csr, batches, params: Sequence[int], seed: int, mb_base, stream, recycle, flags,
             scratch_limit, allocator=None):
+    if torch.cuda.current_device() != csr.device:   # streams, allocations and the library's launches are the current device's
+        with torch.cuda.device(csr.device):
+            return _sample(ladies, csr, batches, params, seed, mb_base, stream, recycle, flags, scratch_limit, allocator)
     if stream is not None:
         stream = _raw(stream)
         if torch.cuda.current_stream().cuda_stream != stream:
@@ -429,6 +432,9 @@ def fetch_features(H: torch.Tensor, ids: torch.Tensor, out: Optional[torch.Tenso
     """bms_fetch_features: out[j, :] = H[ids[j], :] (device tensors; H n x f fp32, ids int32)."""
     if H.dtype != torch.float32 or H.dim() != 2 or not H.is_cuda or not H.is_contiguous():
         raise TypeError("H must be a contiguous n x f float32 device tensor")
+    if torch.cuda.current_device() != H.device.index:
+        with torch.cuda.device(H.device):
+            return fetch_features(H, ids, out, stream)
     if ids.dtype != torch.int32 or ids.dim() != 1 or not ids.is_cuda or not ids.is_contiguous():
         raise TypeError("ids must be a contiguous int32 device vector")
     n, f = H.shape
@@ -449,6 +455,9 @@ def aggregate_hop(res: "Result", hop: int, X: torch.Tensor, mean: bool = True, o
     """bms_aggregate_hop: out[r, :] = mean (or sum) of X over the sampled columns of stacked row r of `hop`."""
     if X.dtype != torch.float32 or X.dim() != 2 or not X.is_cuda or not X.is_contiguous():
         raise TypeError("X must be a contiguous ncols x f float32 device tensor")
+    if torch.cuda.current_device() != X.device.index:
+        with torch.cuda.device(X.device):
+            return aggregate_hop(res, hop, X, mean, out, stream)
     rows, _, ncols = res.sizes()[hop]
     if X.shape[0] != ncols:
         raise ValueError("X has %d rows, the hop has %d columns" % (X.shape[0], ncols))
