@@ -738,16 +738,23 @@ void empty_result(bms_result *r, bool keep_hints)
     r->mb_offsets.clear();
 }
 
-// First look at the result of a BMS_ASYNC call: waits for it and returns what the call would have returned.
+int finish_pending(bms_result *res, uint32_t *redo)
+try {
+    HIP_TRY(hipSetDevice(res->device));
+    HIP_TRY(hipEventSynchronize(res->done_ev));
+    return finish_nodewise(res, res->deferred, res->host, true, redo);
+}
+BMS_CATCH
+
+// First look at the result of a BMS_ASYNC call: waits for it and returns what the call would have returned.  Whatever went wrong, host
+// memory included, the result is empty then: its views still hold bounds instead of sizes.
 int settle_result(bms_result *res)
 {
     if (!res->pending)
         return BMS_OK;
     res->pending = false;
-    HIP_TRY(hipSetDevice(res->device));
-    HIP_TRY(hipEventSynchronize(res->done_ev));
     uint32_t redo = 0;
-    const int rc = finish_nodewise(res, res->deferred, res->host, true, &redo);
+    const int rc = finish_pending(res, &redo);
     if (rc != BMS_OK) {
         empty_result(res, false);
         return rc;

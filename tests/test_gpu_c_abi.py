@@ -94,3 +94,12 @@ def test_c_client_drives_the_consumer_calls_and_the_layerwise_sampler(tmp_path):
             assert np.array_equal(np.fromfile(fh, dtype=np.int32, count=pnnz), hop.p_col)
             assert np.array_equal(np.fromfile(fh, dtype=np.uint32, count=pnnz), hop.p_cnt)
         assert fh.read() == b""
+
+
+def test_first_look_at_an_asynchronous_result_without_host_memory(tmp_path):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    exe, lib = str(tmp_path / "no_host_memory_async"), os.path.join(root, "paper_2311_02909_amd")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-I", os.path.join(root, "include"), "-o", exe,
+                           os.path.join(root, "tests", "host", "no_host_memory_async.cpp"), "-L", lib, "-l:libbms.so", "-ldl", "-Wl,-rpath," + lib])
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stdout + run.stderr
