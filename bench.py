@@ -65,6 +65,8 @@ MEASURED_CALL_TRAFFIC = {
     "mid_ladies": 456_880_608,
     "mid_sage": 3_529_696_384,
 }
+# the part of it that nw_sample reads, MB: the "read MB" of its launches in the same files
+NW_SAMPLE_READ_MB = {"dense_sage": 9255.1, "large_sage": 4693.0, "mid_sage": 2490.8}
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 
 
@@ -356,7 +358,7 @@ def run_workload(workload: str, steps: int, warmup: int, variant: str, cpu: bool
     roofline = {
         "bound": "hbm", "kernel": dominant, "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 5),
-        # measured HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated), average over the launches
+        # profiled bytes between L2 and the memory fabric per launch, average over the launches
         "traffic": (MEASURED_TRAFFIC[(traffic_key, dominant)] // dom["launches"])
         if (traffic_key, dominant) in MEASURED_TRAFFIC else None,
         "algorithmic_bytes_per_launch": int(dom["bytes"] / dom["launches"]),
@@ -370,13 +372,13 @@ def run_workload(workload: str, steps: int, warmup: int, variant: str, cpu: bool
     if dominant == "nw_sample":
         # what bounds this kernel is memory lines per second, not bytes asked for: every sampled neighbour of a long
         # row is a 4-byte read that costs one 128-byte line.  Short rows at random places are read at 4.72e10 lines/s
-        # on this chip (bench.py --line-probe 30, profiles/random_line_probe.txt); the kernel's own lines per
-        # second follow from its fabric traffic
-        lines = MEASURED_TRAFFIC.get((traffic_key, dominant))
+        # on this chip (bench.py --line-probe 30, profiles/random_line_probe.txt), more where several dies read the same lines;
+        # the kernel's own lines per second follow from what it reads over the fabric
+        lines = NW_SAMPLE_READ_MB.get(traffic_key, 0.0) * 1e6
         roofline["sampled_reads"] = {
             "per_sec": round(edges / (dom["ms"] * 1e-3), 1),
             "lines_per_sec": round(lines / 128.0 / (dom["ms"] * 1e-3), 1) if lines else None,
-            "line_probe_lines_per_sec": 4.72e10,   # reads of short rows that share no line (measured ceiling)
+            "line_probe_lines_per_sec": 4.72e10,   # reads of short rows that share no line, from 4 GiB
         }
     # whole call: algorithmic bytes of all stages ("effective") and the profiled HBM bytes ("achieved"),
     # both over the sum of the kernel times measured in this run

@@ -36,3 +36,12 @@ def test_profiled_workloads_are_used_by_the_benchmark():
     _, call = _profiled()
     for key in call:
         assert key in bench.MEASURED_CALL_TRAFFIC, "profiles/ holds call(%s) but bench.py does not use it" % key
+
+
+def test_lines_read_by_the_sampling_kernel():
+    # ceilings are reads: written bytes are not lines fetched
+    for key, value in bench.NW_SAMPLE_READ_MB.items():
+        text = open(os.path.join(ROOT, "profiles", key + "_hbm_traffic.txt")).read()
+        reads = [float(x) for x in re.findall(r"nw_sample\S*_kernel<[^>]*>\s+\d+\s+([\d.]+)\s+[\d.]+$", text, re.M)]
+        assert len(reads) == 2 and abs(sum(reads) - value) < 0.05, (key, reads, value)
+    assert {key for key, stage in bench.MEASURED_TRAFFIC if stage == "nw_sample"} == set(bench.NW_SAMPLE_READ_MB)
