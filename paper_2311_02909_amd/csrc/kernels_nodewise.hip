@@ -71,22 +71,27 @@ __device__ inline int32_t wave_replace_draws(volatile uint32_t *buf, uint64_t ke
     return m;
 }
 
-// The row tiles that a wave visits.  Tiles of all minibatches are put in order of their place in the minibatch (of `most` steps,
-// the number that the largest has, those of a smaller one are spread evenly), minibatch by minibatch within a step, and each die
-// takes an eighth of that order.  The rows of a minibatch ascend by vertex id, so what runs at the same time on a die touches one
-// part of the id range in all minibatches: a line of rowptr that several minibatches need is fetched once and is in the die's own
-// cache when the next one asks.
+// The row tiles that a wave or workgroup visits: of all minibatches, in order of their place in the minibatch, minibatch by
+// minibatch within a step.
+//   stacked: tile j of every minibatch in step j, the steps dealt out to all of the launch's workgroups in turn
+//   by dies: `most` steps, the number that the largest minibatch has, those of a smaller one spread evenly, and each die takes an
+//            eighth of that order.  The rows of a minibatch ascend by vertex id, so what runs at the same time on a die touches
+//            one part of the id range in all minibatches: a line that several minibatches need is fetched once and is in the
+//            die's own cache when the next one asks.
 constexpr int kDies = 8;
 struct TileWalk {
     int32_t k, i, step_i, left; // i: minibatch
     int64_t j, most, step_j;
-    // workgroups are dealt to the dies in turn; wave `part` of `parts` in the workgroup; gridDim.x is a multiple of kDies
-    __device__ TileWalk(const NwHop &a, uint32_t part, uint32_t parts) : k(a.k), most(uniform_load(a.mb_tileoff + a.k + 1))
+    bool spread;
+    // workgroups are dealt to the dies in turn; wave `part` of `parts` in the workgroup; by dies gridDim.x is a multiple of kDies
+    __device__ TileWalk(const NwHop &a, uint32_t part, uint32_t parts, bool by_dies)
+        : k(a.k), most(uniform_load(a.mb_tileoff + a.k + 1)), spread(by_dies && most < 65536) // (larger ones: tile q in step q)
     {
-        const int64_t items = most * k, per = (items + kDies - 1) / kDies;
-        const int64_t lo = (blockIdx.x % kDies) * per, hi = min<int64_t>(lo + per, items);
-        const int64_t pos = lo + (blockIdx.x / kDies) * parts + part;
-        const int32_t step = gridDim.x / kDies * parts;
+        const uint32_t dies = by_dies ? kDies : 1;
+        const int64_t items = most * k, per = (items + dies - 1) / dies;
+        const int64_t lo = (blockIdx.x % dies) * per, hi = min<int64_t>(lo + per, items);
+        const int64_t pos = lo + (blockIdx.x / dies) * parts + part;
+        const int32_t step = gridDim.x / dies * parts;
         left = pos < hi ? (int32_t)((hi - pos + step - 1) / step) : 0;
         i = (int32_t)(pos % k);
         j = pos / k;
@@ -108,10 +113,11 @@ struct TileWalk {
     __device__ int64_t tile(const NwHop &a, int64_t &r0, int32_t &rows) const
     {
         const int64_t t0 = uniform_load(a.mb_tileoff + i), tiles = uniform_load(a.mb_tileoff + i + 1) - t0;
+        const bool apart = spread && tiles != most;
         int64_t jj = j;
-        if (tiles != most && most < 65536) // tile q is visited in step floor(q most / tiles) (larger ones: in step q)
+        if (apart) // tile q is visited in step floor(q most / tiles)
             jj = ((uint32_t)j * (uint32_t)tiles + (uint32_t)most - 1u) / (uint32_t)most;
-        if (jj >= tiles || (tiles != most && most < 65536 && ((uint32_t)jj * (uint32_t)most) / (uint32_t)tiles != j))
+        if (jj >= tiles || (apart && ((uint32_t)jj * (uint32_t)most) / (uint32_t)tiles != j))
             return -1;
         r0 = uniform_load(a.mb_rowoff + i) + jj * kRowTile;
         rows = (int32_t)min<int64_t>(uniform_load(a.mb_rowoff + i + 1) - r0, kRowTile);
@@ -132,7 +138,7 @@ __global__ __launch_bounds__(kRowTile) void nw_rows_kernel(NwHop a)
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     for (int64_t q = (int64_t)blockIdx.x * kRowTile + tid; q < a.zero_quads; q += (int64_t)gridDim.x * kRowTile)
         a.zero[q] = make_uint4(0, 0, 0, 0);
-    for (TileWalk walk(a, scalar((uint32_t)(tid / kWave)), kRowTile / kWave); walk.more(); walk.next()) {
+    for (TileWalk walk(a, scalar((uint32_t)(tid / kWave)), kRowTile / kWave, true); walk.more(); walk.next()) {
         int64_t r0;
         int32_t rows;
         const int64_t t = walk.tile(a, r0, rows);
@@ -331,7 +337,6 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
     __shared__ uint32_t seg_hist[kMaxFusedSegments]; // sampled ids per id-range segment, of this workgroup's minibatch
     __shared__ uint16_t seg_tab_l[kMaxCells + 1];    // segment of every cell of ids, when the segments differ in width
     const int tid = threadIdx.x;
-    const int64_t most = a.mb_tileoff[a.k + 1];
     const int32_t s = a.s;
     const bool count = a.seg_cnt != nullptr; // then gridDim.x is a multiple of k: every tile of this workgroup belongs
                                              // to minibatch blockIdx.x % k
@@ -347,36 +352,33 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
         __syncthreads();
     }
     // the extent of the lane's row in the workgroup's next tile is fetched while the current tile is sampled
-    auto extent = [&](int64_t v, int64_t &beg, int32_t &deg) {
-        beg = 0;
-        deg = 0;
-        if (v < most * a.k) {
-            const int i = (int)(v % a.k);
-            const int64_t j = v / a.k;
-            const int64_t r = a.mb_rowoff[i] + j * kRowTile + tid;
-            if (j < a.mb_tileoff[i + 1] - a.mb_tileoff[i] && r < a.mb_rowoff[i + 1]) {
-                beg = a.row_beg[r];
-                deg = a.row_deg[r];
-            }
-        }
-    };
-    if (SUM && most == 0 && blockIdx.x == 0 && tid == 0)
-        leave_total(a, 0);
+    TileWalk walk(a, 0, 1, a.by_dies != 0);
+    int64_t t, t_next, r0, r0_next;
+    int32_t rows, rows_next;
     int64_t beg, beg_next;
     int32_t deg, deg_next;
-    extent(blockIdx.x, beg, deg);
-    for (int64_t v = blockIdx.x; v < most * a.k; v += gridDim.x, beg = beg_next, deg = deg_next) {
-        // tile j of every minibatch before tile j + 1 of any.  TileWalk's order would more than halve the lines read on a graph of
-        // 0.5 GB of columns (64 x 1024 seeds, last hop: 320 -> 260 us), but costs 789 -> 925 us on 111 M vertices and nothing either
-        // way on 5.3 GB of long lists
-        extent(v + gridDim.x, beg_next, deg_next);
-        const int i = (int)(v % a.k);
-        const int64_t j = v / a.k;
-        if (j >= a.mb_tileoff[i + 1] - a.mb_tileoff[i])
+    auto extent = [&](int64_t &t, int64_t &r0, int32_t &rows, int64_t &beg, int32_t &deg) {
+        t = -1;
+        r0 = beg = 0;
+        rows = deg = 0;
+        if (walk.more())
+            t = walk.tile(a, r0, rows);
+        if (t >= 0 && tid < rows) {
+            beg = a.row_beg[r0 + tid];
+            deg = a.row_deg[r0 + tid];
+        }
+    };
+    if (SUM && walk.most == 0 && blockIdx.x == 0 && tid == 0)
+        leave_total(a, 0);
+    extent(t, r0, rows, beg, deg);
+    for (; walk.more(); t = t_next, r0 = r0_next, rows = rows_next, beg = beg_next, deg = deg_next) {
+        const int i = walk.i;
+        walk.next();
+        extent(t_next, r0_next, rows_next, beg_next, deg_next);
+        if (t < 0)
             continue;
-        const int64_t t = a.mb_tileoff[i] + j;
-        const int64_t r = a.mb_rowoff[i] + j * kRowTile + tid;
-        const bool valid = r < a.mb_rowoff[i + 1];
+        const int64_t r = r0 + tid;
+        const bool valid = tid < rows;
         int32_t cnt = 0;
         uint32_t c[S];
         if (valid) {
@@ -654,8 +656,8 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // fewer rows are in progress on the chip, the narrower the part of A that the minibatches read at the same time: with
     // eight, it no longer fits the 256 MB last-level cache on the larger graphs.  Six where A's columns take four times that
     // cache at most, so that most of what several minibatches read is kept anyhow, and fanouts of up to 8 (above, five workgroups
-    // fill LDS).  Last hop, by four and by six: 490 MB of columns 332 and 323 us, with own vertices 231 and 212, with replacement
-    // 127 and 118; 5.3 GB (128 minibatches) 1185 and 1377 us, 6.4 GB 790 and 809.  Between, uniform graphs of 1 to 4 GB: 1 or 2 %
+    // fill LDS).  Last hop, stacked (by_dies below), by four and by six: 490 MB of columns 332 and 323 us, with own vertices 231 and
+    // 212, with replacement 127 and 118; 5.3 GB (128 minibatches) 1185 and 1377 us, 6.4 GB 790 and 809.  Between, uniform graphs of 1 to 4 GB: 1 or 2 %
     // in six's favour, which is not worth what the larger skewed ones lose.
     const bool small_graph = a.A_nnz * (int64_t)sizeof(int32_t) <= (int64_t)1 << 30;
     int grid = grid_for(L, tiles, small_graph && a.s <= 8 ? 6 : 4);
@@ -665,6 +667,13 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
         grid = std::max(grid / a.k, 1) * a.k;
     else
         a.seg_cnt = nullptr;
+    // By dies from one row for every two vertices on: then the minibatches' rows at the same place share lines.  Whole calls of
+    // (15, 10, 5), stacked and by dies: 2.4 M vertices, rows / n 0.43 253 and 248 us, 0.86 368 and 351, 1.1 446 and 416, 2.3 719 and
+    // 635 (the last hop's sampling 323 and 246); 4 M of 150 neighbours 0.46 484 and 482, 1.8 1224 and 1184; 0.5 M 0.65 125 and 118;
+    // (15, 20) with 0.27 260 and 260.  Counting per segment rules it out, and is worth more (8.7 M of 12 neighbours, 0.91: 1064 and 1094).
+    a.by_dies = !a.seg_cnt && a.k >= kDies && 2 * a.rows_tune >= a.n;
+    if (a.by_dies)
+        grid = (grid + kDies - 1) / kDies * kDies;
     if (a.sum_tiles)
         launch_nw_sample_lanes<SET, REPLACE, true>(L, a, vs, grid);
     else

@@ -43,6 +43,25 @@ def test_hops_of_one_workgroup_per_minibatch(k, b, fanouts):
         _check(rowptr, col, random_batches(n, min(k, 8), b, rng), fanouts, replace=True, calls=1)
 
 
+# hops whose tiles are sampled by dies (2 rows >= n, 8 minibatches and more; seven: in stacked order), the second one with minibatches
+# of no, few and many tiles, which take different steps of the walk
+@pytest.mark.parametrize("k", [7, 8, 9, 37])
+@pytest.mark.parametrize("variant", [{}, {"replace": True}, {"union_dst": True}], ids=lambda v: "+".join(v))
+def test_tiles_by_dies_with_minibatches_of_unequal_length(k, variant):
+    rng = np.random.default_rng(900 + k)
+    n, b = 20_000, 1500
+    lists = [np.zeros(0, dtype=np.int64)] * n
+    for v in range(2000, 11_000):      # many tiles
+        lists[v] = np.unique(rng.integers(0, n, size=40))
+    for v in range(11_000, n):         # two tiles
+        lists[v] = np.unique(rng.integers(11_000, 11_300, size=40))
+    rowptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    col = np.concatenate(lists).astype(np.int32)
+    groups = [np.arange(2000, 11_000), np.arange(11_000, n), np.arange(2000), np.arange(2000, n)]
+    batches = np.stack([rng.choice(groups[i % 4], size=b, replace=False) for i in range(k)]).astype(np.int32)
+    _check(rowptr, col, batches, (14, 5), **variant)
+
+
 @pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 16384, 16385, 70_000, 3_000_000])
 def test_one_workgroup_hops_over_vertex_ranges_and_hubs(n):
     # a few hubs that every row samples crowd one bucket of ids: the counting passes take over
