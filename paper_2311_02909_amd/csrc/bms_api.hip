@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -858,12 +859,7 @@ int run_small_hops(CallCtx &c, const int32_t *batches, const int32_t *fanouts, i
         rows = cols;
         cap = std::max(cap, entries);
     }
-    a.seed_slots = 64;
-    a.seed_shift = 26;
-    while (a.seed_slots < 2 * c.b) {
-        a.seed_slots <<= 1;
-        --a.seed_shift;
-    }
+    seed_table(c.b, a.seed_slots, a.seed_shift);
     a.cap = (int32_t)((std::max<int64_t>(cap, a.seed_slots) + 63) / 64 * 64);
     while (csr->n > 1 && a.idbits < 31 && ((csr->n - 1) >> a.idbits) != 0)
         ++a.idbits;
@@ -1488,14 +1484,27 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     const size_t nw = (size_t)c.k * nwin;
     BMS_TRY(csr->lw_win.ensure(nw * (sizeof(uint32_t) + 3 * sizeof(int64_t)) + 64));
     BMS_TRY(csr->lw_parts.ensure(nw * kWinParts * (2 * sizeof(uint32_t) + 3 * sizeof(uint64_t))));
-    BMS_TRY(csr->lw_count.ensure(((3 + kQueueStride) * ((size_t)c.k + 1) + 16) * sizeof(int64_t)));
+    BMS_TRY(csr->lw_count.ensure(((4 + kQueueStride) * ((size_t)c.k + 1) + 16) * sizeof(int64_t)));
     if (!csr->lw_index_tried && !(c.flags & BMS_LADIES_NO_INDEX))
         BMS_TRY(build_window_index(c, nwin));
     const uint32_t *index = csr->lw_index_ready && !(c.flags & BMS_LADIES_NO_INDEX) ? csr->lw_index.as<uint32_t>() : nullptr;
     const size_t blists = index ? 1 : 2; // boundary lists held per hop: window-major only, or row-major as well
-    BMS_TRY(stage_seeds(c, batches, prof, false));
 
     int64_t rows_bound = (int64_t)c.k * c.b;
+    // the seeds staged by the first hop's rows kernel, whose workgroups with 32 KB of LDS still share a compute unit
+    const bool seeds_with_rows = c.b <= 4096 && rows_bound <= (int64_t)kMostLookback * kLwRows;
+    const int32_t *seeds = batches;
+    if (seeds_with_rows) {
+        HopBufs &h0 = c.res->hops[0];
+        BMS_TRY(h0.row_vertex.ensure((size_t)rows_bound * sizeof(int32_t)));
+        BMS_TRY(h0.mb_rowoff.ensure(((size_t)c.k + 1) * sizeof(int64_t)));
+        if (!is_device_pointer(batches)) {
+            HIP_TRY(hipMemcpyAsync(h0.row_vertex.p, batches, (size_t)rows_bound * sizeof(int32_t), hipMemcpyHostToDevice, c.stream));
+            seeds = h0.row_vertex.as<int32_t>();
+        }
+    } else {
+        BMS_TRY(stage_seeds(c, batches, prof, false));
+    }
     const int32_t *row_vertex = c.res->hops[0].row_vertex.as<int32_t>();
     const int64_t *mb_rowoff = c.res->hops[0].mb_rowoff.as<int64_t>();
 
@@ -1573,7 +1582,8 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.mb_count = csr->lw_count.as<int64_t>();
         w.mb_goff = w.mb_count + c.k + 1;
         w.mb_gtileoff = w.mb_goff + c.k + 1;
-        w.tile_queue = reinterpret_cast<unsigned long long *>(csr->lw_count.as<int64_t>() + (3 * ((size_t)c.k + 1) + 15) / 16 * 16);
+        w.mb_wt = reinterpret_cast<uint64_t *>(w.mb_gtileoff + c.k + 1);
+        w.tile_queue = reinterpret_cast<unsigned long long *>(csr->lw_count.as<int64_t>() + (4 * ((size_t)c.k + 1) + 15) / 16 * 16);
         w.row_mb = a.row_mb;
         w.p_off = hb.p_off.as<int64_t>();
         w.sel_tmp = csr->lw_sel.as<int32_t>();
@@ -1586,6 +1596,17 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         Lookback lb{};
         uint32_t workgroups = 0;
         BMS_TRY(next_lookback(c, lb));
+        if (h == 0 && seeds_with_rows) {
+            w.seeds = seeds;
+            w.b = c.b;
+            seed_table(c.b, w.seed_slots, w.seed_shift);
+            w.seed_copy = c.res->hops[0].row_vertex.as<int32_t>();
+            w.seed_flags = reinterpret_cast<int32_t *>(c.res->host + 64);
+            w.seed_rowoff = c.res->hops[0].mb_rowoff.as<int64_t>();
+            w.scalars = csr->scalars.as<int64_t>();
+        }
+        w.giveup = giveup;
+        w.gathered_cap = no_wait ? with_margin(c.res->hint_gathered[h]) : std::numeric_limits<int64_t>::max();
         if (launch_ldw_rows(c.launch, w, lb, slot(c, h, 3), &workgroups) == 0) {
             lookback_used(c, workgroups);
         } else { // too many rows for that
@@ -1601,7 +1622,6 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
                 BMS_TRY(seed_flag_error(csr->n, csr->host_pinned, c.res->host));
             D = host_slot(c, h, 3);
         }
-        w.giveup = giveup;
         w.gathered_cap = D;
         const int64_t tmp_cap = std::max<int64_t>(std::min<int64_t>(D, (int64_t)c.k * n1), 1); // entries of P
         const size_t tbytes = (size_t)tmp_cap * 4 + (size_t)std::max<int64_t>(D, 1) * 4;
@@ -1626,16 +1646,21 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.tile_row = csr->lw_tiles.as<int64_t>();
         w.tile_cnt = reinterpret_cast<uint32_t *>(w.tile_row + w.tiles_bound);
         w.first_cnt = csr->lw_rowcnt.as<uint32_t>();
-        BMS_TRY(prof.begin("ldw_bounds", h));
-        launch_ldw_bounds(c.launch, w);
-        BMS_TRY(prof.end());
+        if (!ldw_fused(w)) {
+            BMS_TRY(prof.begin("ldw_bounds", h));
+            launch_ldw_bounds(c.launch, w);
+            BMS_TRY(prof.end());
+        }
         BMS_TRY(prof.begin("ldw_accumulate", h));
-        if (launch_ldw_accumulate(c.launch, w, slot(c, h, 2)) != 0)
+        if (launch_ldw_accumulate(c.launch, w) != 0)
             return fail(BMS_EHIP, "launch of the LDS accumulation kernel was refused");
+        int64_t pnnz = std::max<int64_t>(std::min<int64_t>(D, (int64_t)c.k * n1), 1);
+        w.place_pairs = ldw_may_place(w) && (no_wait || pnnz <= kNoWaitEntries) ? 1 : 0;
+        if (!w.place_pairs)
+            launch_ldw_win_scan(c.launch, w, slot(c, h, 2));
         BMS_TRY(prof.end());
         // nnz(P) sizes P and its prefix sums.  When its bound min(D, k n) is modest the buffers take the bound
         // and the size is read back with everything else at the end of the call; else it is read back now.
-        int64_t pnnz = std::max<int64_t>(std::min<int64_t>(D, (int64_t)c.k * n1), 1);
         if (no_wait) {
             pnnz = std::min<int64_t>(pnnz, with_margin(c.res->hint_pnnz[h]));
         } else if (pnnz > kNoWaitEntries) {
@@ -1650,7 +1675,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.p_cnt = hb.p_cnt.as<uint32_t>();
         w.prefix = csr->ld_prefix.as<uint64_t>();
         BMS_TRY(prof.begin("ldw_p_copy", h));
-        launch_ldw_p_copy(c.launch, w);
+        launch_ldw_p_copy(c.launch, w, slot(c, h, 2));
         BMS_TRY(prof.end());
         // NORM (implicit) + SAMPLE
         BMS_TRY(prof.begin("ldw_draw", h));

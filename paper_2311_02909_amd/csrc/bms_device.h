@@ -247,6 +247,38 @@ __device__ inline void announce(uint32_t *done, uint32_t parts, int64_t *arrived
     }
 }
 
+// Minibatch i's b seeds by a workgroup of NT threads: copied, and passed through a hash table of `slots` words in LDS, a power of two
+// >= 2 b, shift = 32 - its log2; flags[0]: one lies outside [0, n), flags[1]: one is repeated.
+template <int NT>
+__device__ inline void check_seeds(const int32_t *seeds, int i, int32_t b, int64_t n, int32_t slots, int32_t shift, uint32_t *key,
+                                   int32_t *copy, int32_t *flags)
+{
+    const int tid = threadIdx.x;
+    const int64_t row0 = (int64_t)i * b;
+    for (int32_t x = tid; x < slots; x += NT)
+        key[x] = 0xFFFFFFFFu;
+    __syncthreads();
+    for (int32_t j = tid; j < b; j += NT) {
+        const int32_t v = seeds[row0 + j];
+        copy[row0 + j] = v;
+        if (v < 0 || (int64_t)v >= n) {
+            flags[0] = 1;
+            continue;
+        }
+        uint32_t slot = ((uint32_t)v * 0x9E3779B1u) >> shift;
+        while (true) {
+            const uint32_t old = atomicCAS(&key[slot], 0xFFFFFFFFu, (uint32_t)v);
+            if (old == 0xFFFFFFFFu)
+                break;
+            if (old == (uint32_t)v) {
+                flags[1] = 1;
+                break;
+            }
+            slot = (slot + 1u) & (uint32_t)(slots - 1);
+        }
+    }
+}
+
 // Largest i in [0,k) with off[i] <= t, given off[0] <= t < off[k] (off ascending, k >= 1).
 __device__ inline int locate_segment(const int64_t *__restrict__ off, int k, int64_t t)
 {

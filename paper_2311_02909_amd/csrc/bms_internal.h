@@ -42,6 +42,7 @@ struct PublishArgs {
 void launch_publish(const Launch &, const PublishArgs &);
 
 int grid_for(const Launch &L, int64_t blocks, int per_cu);
+void seed_table(int32_t b, int32_t &slots, int32_t &shift); // of the hash table that checks b seeds (check_seeds)
 // called by multi-kernel launchers before each kernel (group) so that it can be timed on its own
 using StageMark = std::function<void(const char *)>;
 
@@ -333,6 +334,7 @@ constexpr int kWinParts = 16;            // a window leaves the accumulation in 
 constexpr int32_t kMaxWinRows = 65535;   // frontier rows per minibatch (a 16-bit counter cannot overflow)
 constexpr int32_t kMaxWinSampled = 4096; // columns sampled per minibatch (sorted, then hashed, in LDS)
 constexpr int kQueueStride = 16;         // a counter per 128-byte line
+constexpr int kLwRows = 256;             // rows per workgroup of the rows kernel
 constexpr int kLwTileMax = 4096;         // positions of the gathered order streamed by one wave at a time: at most
 constexpr int kLwTileMin = 1024;         // ... and at least (hops that gather little use small tiles to fill the chip)
 struct LwHop {
@@ -344,12 +346,19 @@ struct LwHop {
     int squared;
     uint64_t hopkey;
     uint32_t mb_base;
+    // First hop when the rows kernel stages the seeds as well (else null): it reads them here, copies them to seed_copy, checks them
+    // (slots of the hash table, flags in host memory), writes seed_rowoff and clears the call's scalars
+    const int32_t *seeds;
+    int32_t b, seed_slots, seed_shift;
+    int32_t *seed_copy, *seed_flags;
+    int64_t *seed_rowoff, *scalars;
     const int32_t *row_vertex; // stacked frontier
     const int64_t *mb_rowoff;  // k+1
     int64_t rows_bound;
     int64_t *row_beg;          // rows
     int64_t *gather_off;       // rows+1: exclusive scan of the degrees
     int32_t *row_mb;           // rows: minibatch of each row
+    uint64_t *mb_wt;           // k: weight of the minibatch's columns of P
     uint32_t *done;            // a device word, zero between launches
     int64_t *mb_goff;          // k+1: gathered position where each minibatch starts
     int64_t *mb_gtileoff;      // k+1: tiles before each minibatch
@@ -379,6 +388,7 @@ struct LwHop {
     int32_t *p_col;
     uint32_t *p_cnt;
     uint64_t *prefix;          // pnnz, inclusive, restarts per minibatch
+    int32_t place_pairs;       // 1: launch_ldw_p_copy finds the places of the parts itself
     int32_t *sel_tmp;          // k * s
     int64_t *mb_coloff;        // k+1
     int32_t *col_vertex;
@@ -394,12 +404,17 @@ struct LwHop {
     int32_t *out_col;
 };
 struct Lookback; // bms_device.h
-// the launches with a Lookback: at most kMostLookback workgroups, else -1 (nothing launched); *workgroups: how many
+// With the index, few enough minibatches and rows the rows kernel also leaves the rows' lists window-major, and the plan is made
+// behind the accumulation (by launch_ldw_win_scan or launch_ldw_p_copy); else launch_ldw_bounds does both, after the rows.
+bool ldw_fused(const LwHop &);
+// the launches with a Lookback: at most kMostLookback workgroups, else -1 (nothing launched); *workgroups: those with numbers
 int launch_ldw_rows(const Launch &, const LwHop &, const Lookback &, int64_t *gathered_out, uint32_t *workgroups);
 void launch_ldw_bounds(const Launch &, const LwHop &); // with an index: the rows' lists are copied from it
 void launch_ldw_index(const Launch &, const LwHop &);  // boundary lists of the rows of a hop that is the whole graph
-int launch_ldw_accumulate(const Launch &, const LwHop &, int64_t *pnnz_out); // also scans the windows, p_off; -1: launch refused
-void launch_ldw_p_copy(const Launch &, const LwHop &);
+int launch_ldw_accumulate(const Launch &, const LwHop &); // -1: launch refused
+bool ldw_may_place(const LwHop &);               // few enough pairs: LwHop::place_pairs, and no launch_ldw_win_scan
+void launch_ldw_win_scan(const Launch &, const LwHop &, int64_t *pnnz_out); // places of the parts, p_off
+void launch_ldw_p_copy(const Launch &, const LwHop &, int64_t *pnnz_out);
 // lb == null: sel_tmp and mb_count only (launch_offsets_from_counts and launch_ldw_sel_copy follow)
 void launch_ldw_draw(const Launch &, const LwHop &, const Lookback *lb, int64_t *ncols_out);
 void launch_ldw_sel_copy(const Launch &, const LwHop &);

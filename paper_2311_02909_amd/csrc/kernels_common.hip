@@ -5,6 +5,16 @@
 
 namespace bms {
 
+void seed_table(int32_t b, int32_t &slots, int32_t &shift)
+{
+    slots = 64;
+    shift = 26;
+    while (slots < 2 * b) {
+        slots <<= 1;
+        --shift;
+    }
+}
+
 int grid_for(const Launch &L, int64_t blocks, int per_cu)
 {
     int64_t cap = (int64_t)L.num_cu * per_cu;
@@ -574,13 +584,10 @@ __global__ __launch_bounds__(1024) void stage_seeds_kernel(const int32_t *seeds,
 {
     extern __shared__ uint32_t seed_key[];
     const int i = blockIdx.x, tid = threadIdx.x;
-    const int64_t row0 = (int64_t)i * b;
-    for (int32_t x = tid; x < slots; x += 1024)
-        seed_key[x] = 0xFFFFFFFFu;
     if (i == 0 && tid < 64)
         scalars[tid] = 0;
     if (tid == 0) {
-        const int64_t tiles = (b + kRowTile - 1) / kRowTile;
+        const int64_t row0 = (int64_t)i * b, tiles = (b + kRowTile - 1) / kRowTile;
         mb_rowoff[i] = row0;
         if (tileoff)
             tileoff[i] = i * tiles;
@@ -592,36 +599,14 @@ __global__ __launch_bounds__(1024) void stage_seeds_kernel(const int32_t *seeds,
             }
         }
     }
-    __syncthreads();
-    for (int32_t j = tid; j < b; j += 1024) {
-        const int32_t v = seeds[row0 + j];
-        row_vertex[row0 + j] = v;
-        if (v < 0 || (int64_t)v >= n) {
-            seed_flags[0] = 1;
-            continue;
-        }
-        uint32_t slot = ((uint32_t)v * 0x9E3779B1u) >> shift;
-        while (true) {
-            const uint32_t old = atomicCAS(&seed_key[slot], 0xFFFFFFFFu, (uint32_t)v);
-            if (old == 0xFFFFFFFFu)
-                break;
-            if (old == (uint32_t)v) {
-                seed_flags[1] = 1;
-                break;
-            }
-            slot = (slot + 1u) & (uint32_t)(slots - 1);
-        }
-    }
+    check_seeds<1024>(seeds, i, b, n, slots, shift, seed_key, row_vertex, seed_flags);
 }
 
 void launch_stage_seeds(const Launch &L, const int32_t *seeds, int32_t k, int32_t b, int64_t n, int32_t *row_vertex,
                         int64_t *mb_rowoff, int64_t *scalars, int32_t *seed_flags, int64_t *tileoff)
 {
-    int32_t slots = 64, shift = 26; // a power of two >= 2 b, 32 - its log2
-    while (slots < 2 * b) {
-        slots <<= 1;
-        --shift;
-    }
+    int32_t slots, shift;
+    seed_table(b, slots, shift);
     hipLaunchKernelGGL(stage_seeds_kernel, dim3(k), dim3(1024), (size_t)slots * sizeof(uint32_t), L.stream, seeds, k, b, n, slots,
                        shift, row_vertex, mb_rowoff, scalars, seed_flags, tileoff);
 }

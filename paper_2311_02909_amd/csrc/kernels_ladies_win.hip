@@ -67,6 +67,7 @@ struct AccWave {
 struct AccShared {
     AccWave wave[kAccWaves];
     unsigned long long claimed; // where the pair's entries start in the staging array
+    unsigned long long weight;  // of the pair's columns
     uint32_t cnt[kAccWaves];    // columns in the waves' parts
 };
 constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
@@ -81,32 +82,57 @@ __device__ inline uint64_t ldw_weight(uint32_t cnt, int squared)
 // ---------------------------------------------------------------------------------------------
 // Rows: extents, the gathered order (exclusive scan of the degrees), 256 rows per workgroup
 // ---------------------------------------------------------------------------------------------
-constexpr int kLwRows = 256;
-__global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb, int64_t *gathered_out)
+__device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t (*tile)[65], int64_t x, int64_t nx);
+
+// The first `tiles` workgroups take the rows.  With the index, workgroups behind them turn the rows' lists window-major for the
+// accumulation (a launch of its own before, 6 us of every hop; both only need the frontier).  In the first hop (a.seeds) the frontier
+// is the seeds themselves, and k workgroups in between check those of a minibatch each, copy them and leave where it begins (a launch
+// before, 4 us of every call): nobody in this launch reads what they write.
+__global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb, int64_t *gathered_out, int tiles)
 {
+    extern __shared__ uint32_t rows_lds[]; // hash table of the seeds, or 64 x 65 words
     __shared__ int64_t smem[kLwRows / kWave];
     __shared__ uint32_t number_s;
     const int tid = threadIdx.x;
+    const int32_t *row_vertex = a.seeds ? a.seeds : a.row_vertex;
+    if ((int)blockIdx.x >= tiles) {
+        const int checks = a.seeds ? a.k : 0, x = (int)blockIdx.x - tiles;
+        if (x < checks) {
+            if (tid == 0) {
+                a.seed_rowoff[x] = (int64_t)x * a.b;
+                if (x == a.k - 1)
+                    a.seed_rowoff[a.k] = (int64_t)a.k * a.b;
+            }
+            check_seeds<kLwRows>(a.seeds, x, a.b, a.n, a.seed_slots, a.seed_shift, rows_lds, a.seed_copy, a.seed_flags);
+        } else {
+            const int64_t nrows = a.seeds ? (int64_t)a.k * a.b : uniform_load(a.mb_rowoff + a.k);
+            transpose_bounds(a, row_vertex, nrows, reinterpret_cast<uint32_t (*)[65]>(rows_lds), x - checks, (int64_t)gridDim.x - tiles - checks);
+        }
+        return;
+    }
     const uint32_t t = scalar(take_number(lb, &number_s));
-    const int64_t R = uniform_load(a.mb_rowoff + a.k);
+    const int64_t R = a.seeds ? (int64_t)a.k * a.b : uniform_load(a.mb_rowoff + a.k);
     const int64_t r0 = (int64_t)t * kLwRows, r = r0 + tid;
     if (t > 0 && r0 >= R)
         return; // nobody with rows comes after
-    const int32_t v = r < R ? a.row_vertex[r] : -1;
+    const int32_t v = r < R ? row_vertex[r] : -1;
     // the minibatch of the first row, while the vertices are on their way; mostly that of all rows
     int lo = 0;
-    for (int hi = a.k; hi - lo > 1;) {
-        const int mid = (lo + hi) >> 1;
-        if (uniform_load(a.mb_rowoff + mid) <= r0)
-            lo = mid;
-        else
-            hi = mid;
-    }
+    if (!a.seeds)
+        for (int hi = a.k; hi - lo > 1;) {
+            const int mid = (lo + hi) >> 1;
+            if (uniform_load(a.mb_rowoff + mid) <= r0)
+                lo = mid;
+            else
+                hi = mid;
+        }
     int64x2_a8 extent = {0, 0};
     if (v >= 0 && (int64_t)v < a.n)
         extent = row_extent(a.A_rowptr, v);
     int mb = lo;
-    if (uniform_load(a.mb_rowoff + lo + 1) < min(r0 + kLwRows, R) && r < R)
+    if (a.seeds)
+        mb = (int)((uint32_t)r / (uint32_t)a.b); // fewer than 2^18 rows
+    else if (uniform_load(a.mb_rowoff + lo + 1) < min(r0 + kLwRows, R) && r < R)
         mb = locate_segment(a.mb_rowoff, a.k, r);
     const int64_t beg = extent[0], deg = extent[1] - extent[0];
     int64_t total;
@@ -118,10 +144,24 @@ __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb,
         a.row_mb[r] = mb;
         a.out_rowptr[r] = 0; // per-row counters of the extraction pass
     }
-    if ((int64_t)(t + 1) * kLwRows >= R && tid == 0) {
-        a.gather_off[R] = before + total;
+    if ((int64_t)(t + 1) * kLwRows < R)
+        return;
+    const int64_t all = before + total;
+    const bool too_many = a.giveup && all > a.gathered_cap; // the kernels after this one see it
+    if (tid == 0) {
+        a.gather_off[R] = all;
         a.out_rowptr[R] = 0;
-        *gathered_out = before + total;
+    }
+    if (a.seeds) { // the call's scalars start anew, the staging cursor among them
+        if (tid < 64) {
+            int64_t *slot = a.scalars + tid;
+            *slot = slot == gathered_out ? all : (too_many && slot == reinterpret_cast<int64_t *>(a.giveup)) ? 1 : 0;
+        }
+    } else if (tid == 0) {
+        *gathered_out = all;
+        *a.cursor = 0;
+        if (too_many)
+            *a.giveup = 1;
     }
 }
 
@@ -271,10 +311,9 @@ __global__ __launch_bounds__(256) void ldw_bounds_kernel(LwHop a)
 // all rows at a time.  64 rows x 64 windows at a time through LDS, both sides coalesced.  The list of row r comes from this
 // hop's boundary pass, or, when the graph carries an index of every vertex's list, from the index entry of
 // the row's vertex (all zeros for vertices without neighbours, and so here for their rows).  Workgroup x of nx.
-__device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65], int64_t x, int64_t nx)
+__device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t (*tile)[65], int64_t x, int64_t nx)
 {
     const int64_t ncols = a.nwin + 1;
-    const int64_t nrows = a.mb_rowoff[a.k];
     const int64_t tiles_c = (ncols + 63) / 64, tiles_r = (nrows + 63) / 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int64_t t = x; t < tiles_c * tiles_r; t += nx) {
@@ -283,7 +322,7 @@ __device__ inline void transpose_bounds(const LwHop &a, uint32_t (&tile)[64][65]
             int64_t v[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                v[q] = r0 + ty + 4 * q < nrows ? (int64_t)a.row_vertex[r0 + ty + 4 * q] : -1;
+                v[q] = r0 + ty + 4 * q < nrows ? (int64_t)row_vertex[r0 + ty + 4 * q] : -1;
             uint32_t y[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) // a seed outside [0, n) is an error reported elsewhere; its row has no neighbours
@@ -309,85 +348,63 @@ __global__ __launch_bounds__(256) void ldw_bounds_transpose_kernel(LwHop a)
     __shared__ uint32_t tile[64][65];
     if (a.giveup && *a.giveup)
         return;
-    transpose_bounds(a, tile, blockIdx.x, gridDim.x);
+    transpose_bounds(a, a.row_vertex, a.mb_rowoff[a.k], tile, blockIdx.x, gridDim.x);
 }
 
-// Plan, tile rows and the transposed lists in one launch, when the lists come from the index and k < kPlanMb: the first
-// `planners` workgroups each make the plan for themselves (the first one leaves it for the kernels that follow) and then find
-// tile rows, the others transpose.
+// Plan and tile rows by workgroups of a launch that does something else as well (hops with the index, k < kPlanMb): planner x of
+// nx makes the plan for itself (the first one leaves it for the kernels that follow) and then finds tile rows.  NT threads.
 constexpr int kPlanMb = 1024;
-__global__ __launch_bounds__(256) void ldw_plan_bounds_kernel(LwHop a, int planners)
+struct PlanShared {
+    int64_t goff[kPlanMb], tileoff[kPlanMb];
+};
+template <int NT>
+__device__ inline void plan_tiles(const LwHop &a, PlanShared &p, int64_t *smem /* NT / 64 */, int x, int nx)
 {
-    __shared__ union {
-        uint32_t tile[64][65];
-        struct {
-            int64_t goff[kPlanMb], tileoff[kPlanMb];
-        } p;
-    } u;
-    __shared__ int64_t smem[4];
-    __shared__ int32_t up_s; // the flag as this workgroup sees it: it may go up meanwhile
-    if (threadIdx.x == 0)
-        up_s = a.giveup ? *a.giveup : 0;
-    __syncthreads();
-    if (up_s)
-        return;
-    if ((int)blockIdx.x >= planners) {
-        transpose_bounds(a, u.tile, (int64_t)blockIdx.x - planners, (int64_t)gridDim.x - planners);
-        return;
-    }
     const int tid = threadIdx.x;
-    const bool first = blockIdx.x == 0;
-    for (int32_t i = tid; i <= a.k; i += 256)
-        u.p.goff[i] = a.gather_off[a.mb_rowoff[i]];
+    const bool first = x == 0;
+    for (int32_t i = tid; i <= a.k; i += NT)
+        p.goff[i] = a.gather_off[a.mb_rowoff[i]];
     __syncthreads();
-    if (a.giveup && u.p.goff[a.k] > a.gathered_cap) { // the kernels after this one see it
-        if (first && tid == 0)
-            *a.giveup = 1;
-        return;
-    }
     int64_t carry = 0;
-    for (int32_t base = 0; base <= a.k; base += 256) {
+    for (int32_t base = 0; base <= a.k; base += NT) {
         const int32_t i = base + tid;
-        const int64_t cnt = i < a.k ? (u.p.goff[i + 1] - u.p.goff[i] + a.tile - 1) / a.tile : 0;
+        const int64_t cnt = i < a.k ? (p.goff[i + 1] - p.goff[i] + a.tile - 1) / a.tile : 0;
         int64_t total;
-        const int64_t ex = carry + block_exclusive_scan<int64_t, 256>(cnt, smem, total);
+        const int64_t ex = carry + block_exclusive_scan<int64_t, NT>(cnt, smem, total);
         if (i <= a.k)
-            u.p.tileoff[i] = ex; // entry k: all tiles
+            p.tileoff[i] = ex; // entry k: all tiles
         carry += total;
     }
     __syncthreads();
-    if (first) {
-        if (tid == 0)
-            *a.cursor = 0;
-        for (int32_t i = tid; i <= a.k; i += 256) {
-            a.mb_goff[i] = u.p.goff[i];
-            a.mb_gtileoff[i] = u.p.tileoff[i];
+    if (first)
+        for (int32_t i = tid; i <= a.k; i += NT) {
+            a.mb_goff[i] = p.goff[i];
+            a.mb_gtileoff[i] = p.tileoff[i];
             a.tile_queue[i * kQueueStride] = 0;
         }
-    }
     // A row holds the first positions of the tiles that start inside it: mostly none or one, found without a search (9 steps
     // through memory per tile of 512 rows); a row that holds many is given to the whole wave.
     const int64_t R = uniform_load(a.mb_rowoff + a.k);
     const int shift = __ffs(a.tile) - 1, lane = tid & (kWave - 1);
-    for (int64_t r0 = (int64_t)blockIdx.x * 256 + (tid - lane); r0 < R; r0 += (int64_t)planners * 256) {
+    for (int64_t r0 = (int64_t)x * NT + (tid - lane); r0 < R; r0 += (int64_t)nx * NT) {
         const int64_t r = r0 + lane;
         int64_t from = 0, count = 0; // tiles
         if (r < R) {
             const int64_t begin = a.gather_off[r], end = a.gather_off[r + 1];
             const int i = a.row_mb[r];
-            const int64_t y = (begin - u.p.goff[i] + a.tile - 1) >> shift;
-            from = u.p.tileoff[i] + y;
-            count = ((end - u.p.goff[i] + a.tile - 1) >> shift) - y;
+            const int64_t y = (begin - p.goff[i] + a.tile - 1) >> shift;
+            from = p.tileoff[i] + y;
+            count = ((end - p.goff[i] + a.tile - 1) >> shift) - y;
         }
         for (uint64_t many = __ballot(count > 8); many; many &= many - 1ull) {
             const int owner = __ffsll((unsigned long long)many) - 1;
             const int64_t x0 = lane_value(from, owner), n = lane_value(count, owner);
-            for (int64_t x = lane; x < n; x += kWave)
-                a.tile_row[x0 + x] = r0 + owner;
+            for (int64_t y = lane; y < n; y += kWave)
+                a.tile_row[x0 + y] = r0 + owner;
         }
         if (count <= 8)
-            for (int64_t x = 0; x < count; ++x)
-                a.tile_row[from + x] = r;
+            for (int64_t y = 0; y < count; ++y)
+                a.tile_row[from + y] = r;
     }
 }
 
@@ -437,6 +454,8 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
     const uint32_t nwin = (uint32_t)a.nwin, nblk = (uint32_t)a.k * nwin; // (at most 2^16 minibatches and 2^15 windows)
     for (int x = tid; x < kWinWords / 4; x += kAccThreads)
         acc_lds[x] = make_uint4(0, 0, 0, 0);
+    if (tid == 0)
+        sh.weight = 0;
     __syncthreads();
     // Workgroups are handed to the chip's 8 dies in turn, and each die has its own last-level cache.  Within a
     // round of gridDim.x (minibatch, window) pairs, die x takes a run of consecutive windows, so the memory
@@ -650,7 +669,14 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
         const uint64_t wave_w = wave_sum(SQUARED ? w64 : (uint64_t)w32);
         if (tid == 0)
             sh.claimed = claim;
+        if (lane == 0)
+            atomicAdd(&sh.weight, (unsigned long long)wave_w);
         __syncthreads();
+        if (tid == 0) {
+            a.win_cnt[blk] = pair_c;
+            a.win_wt[blk] = sh.weight;
+            sh.weight = 0; // (two barriers before the next pair's)
+        }
         const int64_t claimed = scalar((int64_t)sh.claimed) + before_c;
         if (lane == 0) {
             const int64_t part = (int64_t)blk * kWinParts + wave;
@@ -693,8 +719,8 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
     }
 }
 
-// one workgroup per minibatch: columns and weight of every window (the sums of its parts), before each of its
-// parts, and before each window; columns of the minibatch.  A part per thread, so 16 lanes per window.
+// Workgroups 0 .. k - 1, one per minibatch: columns and weight before each part of every window, and before each window; columns
+// and weight of the minibatch.  A part per thread, so 16 lanes per window.  The others plan (plan_tiles).
 // Three layers of 32 x 512 seeds, 37 windows: 26 us with a window per thread, which read its 16 parts one after the other, 20 so.
 constexpr int kScanThreads = 1024;
 __global__ __launch_bounds__(kScanThreads) void ldw_win_scan_kernel(LwHop a, int64_t *pnnz_out)
@@ -703,6 +729,12 @@ __global__ __launch_bounds__(kScanThreads) void ldw_win_scan_kernel(LwHop a, int
     __shared__ uint64_t smem[kScanThreads / kWave];
     __shared__ uint32_t smem_c[kScanThreads / kWave];
     __shared__ uint32_t last_s;
+    __shared__ PlanShared plan;
+    if ((int)blockIdx.x >= a.k) {
+        if (!(a.giveup && *a.giveup)) // (it went up before this launch or not at all)
+            plan_tiles<kScanThreads>(a, plan, reinterpret_cast<int64_t *>(smem), (int)blockIdx.x - a.k, (int)gridDim.x - a.k);
+        return;
+    }
     const int i = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     // the workgroup that comes here last turns the minibatches' counts into p_off
     auto finish = [&](int64_t count) {
@@ -766,20 +798,53 @@ __global__ __launch_bounds__(kScanThreads) void ldw_win_scan_kernel(LwHop a, int
                 a.win_poff[x] = (int64_t)(before_c + head_c);
                 a.win_woff[x] = before_w + head_w;
             }
-            if (lane == head + kWinParts - 1) {
-                a.win_cnt[x] = upto_c - head_c;
-                a.win_wt[x] = upto_w - head_w;
-            }
         }
     }
+    if (tid == 0)
+        a.mb_wt[i] = carry_w;
     finish((int64_t)carry_c);
 }
 
-// Windows to their place in P, with the inclusive prefix sums of the weights.  A window left the accumulation in
-// kWinParts parts (one per wave) whose sizes and weights are on record, so every part has a known place and a
-// known weight before it: one wave per part streams it, 64 entries at a time, with lane scans for the sums and
-// no workgroup barrier.
+// A part to its place in P with the inclusive prefix sums of the weights, by one wave: `cw` entries at src, 64 at a time, with lane
+// scans for the sums and no workgroup barrier.  carry: weight of the minibatch before the part.
 constexpr int kCopyUnroll = 4;
+__device__ inline void fetch_entries(const uint32_t *__restrict__ src, uint32_t x0, uint32_t cw, uint32_t (&ent)[kCopyUnroll])
+{
+#pragma unroll
+    for (int u = 0; u < kCopyUnroll; ++u) {
+        const uint32_t x = x0 + u * kWave + (threadIdx.x & (kWave - 1));
+        ent[u] = x < cw ? src[x] : 0u;
+    }
+}
+template <bool SQUARED>
+__device__ inline void place_entries(const LwHop &a, const uint32_t (&ent)[kCopyUnroll], uint32_t x0, uint32_t cw, int64_t dst, int32_t id0,
+                                     uint64_t &carry)
+{
+#pragma unroll
+    for (int u = 0; u < kCopyUnroll; ++u) {
+        const uint32_t x = x0 + u * kWave + (threadIdx.x & (kWave - 1));
+        const uint32_t c = ent[u] & 0xFFFFu;
+        // e_v < 2^16: sums of 64 weights e_v fit 32 bits; e_v^2 is summed as two 16-bit halves
+        uint64_t inc;
+        if (SQUARED) {
+            const uint32_t wq = c * c;
+            inc = ((uint64_t)wave_inclusive_scan_dpp(wq >> 16) << 16) + wave_inclusive_scan_dpp(wq & 0xFFFFu);
+        } else {
+            inc = wave_inclusive_scan_dpp(c);
+        }
+        if (x < cw) {
+            a.p_col[dst + x] = id0 + (int32_t)(ent[u] >> 16);
+            a.p_cnt[dst + x] = c;
+            // the draws find their block of kPrefixBlock entries of P by these sums and walk the weights
+            // inside it: only the sum at the last entry of every such block (absolute index in P) is kept
+            if (((dst + x) & (kPrefixBlock - 1)) == kPrefixBlock - 1)
+                a.prefix[(dst + x) / kPrefixBlock] = carry + inc;
+        }
+        carry += __shfl(inc, kWave - 1, kWave);
+    }
+}
+
+// Many pairs: a window left the accumulation in kWinParts parts (one per wave) whose places are on record (ldw_win_scan).
 template <bool SQUARED>
 __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 {
@@ -792,7 +857,6 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
             return;
         }
     }
-    const int lane = threadIdx.x & (kWave - 1);
     const int64_t nparts = (int64_t)a.k * a.nwin * kWinParts;
     for (int64_t part = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave; part < nparts; part += (int64_t)gridDim.x * 4) {
         const int64_t blk = part / kWinParts;
@@ -807,33 +871,101 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
         uint64_t carry = a.win_woff[blk] + a.part_woff[part];
         for (uint32_t x0 = 0; x0 < cw; x0 += kCopyUnroll * kWave) {
             uint32_t ent[kCopyUnroll];
+            fetch_entries(src, x0, cw, ent);
+            place_entries<SQUARED>(a, ent, x0, cw, dst, id0, carry);
+        }
+    }
+}
+
+// Up to kMostPlacedPairs pairs: scan, copy and plan in one launch.  The first `planners` workgroups plan, each of the others takes a
+// pair and adds up the sizes of those before it (P is stacked like the pairs) while the entries are on their way.
+constexpr int kMostPlacedPairs = 2048;
+template <bool SQUARED, int NT>
+__global__ __launch_bounds__(NT) void ldw_p_place_kernel(LwHop a, int planners, int64_t *pnnz_out)
+{
+    constexpr int NW = NT / kWave, EACH = kWinParts / NW; // parts per wave
+    __shared__ PlanShared plan;
+    __shared__ int64_t smem[NW];
+    __shared__ uint64_t smem_w[NW];
+    __shared__ int32_t up_s; // the flag as this workgroup sees it: it may go up meanwhile
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = (int)scalar((uint32_t)tid / kWave);
+    if (tid == 0)
+        up_s = a.giveup ? *a.giveup : 0;
+    __syncthreads();
+    if (up_s)
+        return;
+    if ((int)blockIdx.x < planners) {
+        plan_tiles<NT>(a, plan, smem, (int)blockIdx.x, planners);
+        return;
+    }
+    const uint32_t pair = blockIdx.x - (uint32_t)planners, i = pair / (uint32_t)a.nwin, head = i * (uint32_t)a.nwin;
+    const int64_t part0 = (int64_t)pair * kWinParts;
+    const uint32_t cnt = lane < kWinParts ? a.part_cnt[part0 + lane] : 0u;
+    const uint64_t wt = lane < kWinParts ? a.part_wt[part0 + lane] : 0ull;
+    const int64_t base = lane < kWinParts ? a.part_base[part0 + lane] : 0;
+    uint32_t c = 0; // of all pairs: fewer than 2^32
+    uint64_t w = 0;
 #pragma unroll
-            for (int u = 0; u < kCopyUnroll; ++u) {
-                const uint32_t x = x0 + u * kWave + lane;
-                ent[u] = x < cw ? src[x] : 0u;
-            }
+    for (uint32_t q = tid; q < (uint32_t)kMostPlacedPairs; q += NT)
+        if (q < pair) {
+            c += a.win_cnt[q];
+            w += q >= head ? a.win_wt[q] : 0ull;
+        }
+    uint32_t ent[EACH][kCopyUnroll];
 #pragma unroll
-            for (int u = 0; u < kCopyUnroll; ++u) {
-                const uint32_t x = x0 + u * kWave + lane;
-                const uint32_t c = ent[u] & 0xFFFFu;
-                // e_v < 2^16: sums of 64 weights e_v fit 32 bits; e_v^2 is summed as two 16-bit halves
-                uint64_t inc;
-                if (SQUARED) {
-                    const uint32_t wq = c * c;
-                    inc = ((uint64_t)wave_inclusive_scan_dpp(wq >> 16) << 16) + wave_inclusive_scan_dpp(wq & 0xFFFFu);
-                } else {
-                    inc = wave_inclusive_scan_dpp(c);
-                }
-                if (x < cw) {
-                    a.p_col[dst + x] = id0 + (int32_t)(ent[u] >> 16);
-                    a.p_cnt[dst + x] = c;
-                    // the draws find their block of kPrefixBlock entries of P by these sums and walk the weights
-                    // inside it: only the sum at the last entry of every such block (absolute index in P) is kept
-                    if (((dst + x) & (kPrefixBlock - 1)) == kPrefixBlock - 1)
-                        a.prefix[(dst + x) / kPrefixBlock] = carry + inc;
-                }
-                carry += __shfl(inc, kWave - 1, kWave);
-            }
+    for (int e = 0; e < EACH; ++e) {
+        const int q = wave * EACH + e;
+        fetch_entries(a.tmp_ent + lane_value(base, q), 0, (uint32_t)__builtin_amdgcn_readlane((int)cnt, q), ent[e]);
+    }
+    const uint32_t upto_c = wave_inclusive_scan_dpp(cnt);
+    const uint64_t upto_w = wave_inclusive_scan(wt);
+    const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)upto_c, kWinParts - 1);
+    const uint64_t pair_w = (uint64_t)lane_value((int64_t)upto_w, kWinParts - 1);
+    const uint32_t wave_c = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(c), kWave - 1);
+    const uint64_t wave_w = wave_sum(w);
+    if (lane == 0) {
+        smem[wave] = wave_c;
+        smem_w[wave] = wave_w;
+    }
+    __syncthreads();
+    int64_t before = 0;
+    uint64_t before_w = 0;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+        before += smem[x];
+        before_w += smem_w[x];
+    }
+    if (tid == 0) {
+        if (pair == head)
+            a.p_off[i] = before;
+        if (pair == head + (uint32_t)a.nwin - 1u)
+            a.mb_wt[i] = before_w + pair_w;
+        if (pair == (uint32_t)a.k * (uint32_t)a.nwin - 1u) {
+            a.p_off[a.k] = before + pair_c;
+            *pnnz_out = before + pair_c;
+        }
+    }
+    if (a.giveup && before + pair_c > a.p_cap) { // P does not fit what was provided
+        if (tid == 0)
+            *a.giveup = 1;
+        return;
+    }
+    const int32_t id0 = (int32_t)(pair - head) << kWinShift;
+#pragma unroll
+    for (int e = 0; e < EACH; ++e) {
+        const int q = wave * EACH + e;
+        const uint32_t cw = (uint32_t)__builtin_amdgcn_readlane((int)cnt, q);
+        if (cw == 0)
+            continue;
+        const uint32_t *__restrict__ src = a.tmp_ent + lane_value(base, q);
+        const int64_t dst = before + (uint32_t)__builtin_amdgcn_readlane((int)(upto_c - cnt), q);
+        uint64_t carry = before_w + (uint64_t)lane_value((int64_t)(upto_w - wt), q);
+        place_entries<SQUARED>(a, ent[e], 0, cw, dst, id0, carry);
+        for (uint32_t x0 = kCopyUnroll * kWave; x0 < cw; x0 += kCopyUnroll * kWave) {
+            uint32_t more[kCopyUnroll];
+            fetch_entries(src, x0, cw, more);
+            place_entries<SQUARED>(a, more, x0, cw, dst, id0, carry);
         }
     }
 }
@@ -1015,8 +1147,7 @@ __global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookbac
     d.nb = (d.p0 + d.C) / kPrefixBlock - d.B0;
     d.pre = a.prefix + d.B0;
     d.squared = a.squared;
-    const int64_t last_win = (int64_t)i * a.nwin + a.nwin - 1;
-    const uint64_t W = uniform_load(a.win_woff + last_win) + uniform_load(a.win_wt + last_win);
+    const uint64_t W = uniform_load(a.mb_wt + i);
     const uint64_t rk = row_key(a.hopkey, a.mb_base + (uint32_t)i, kNoVertex);
     // Every draw searches the recorded sums.  Those at the end of every group of 2^st blocks (at most kDrawTop groups) are copied
     // to LDS first: a draw finds its group there and only the last st bits are looked for in memory.
@@ -1448,24 +1579,29 @@ static void launch_ldw_tiles(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_tile_rows_kernel, dim3(grid_for(L, (a.tiles_bound + 255) / 256, 8)), dim3(256), 0, L.stream, a);
 }
 
+bool ldw_fused(const LwHop &a) { return a.index && a.k < kPlanMb && (a.rows_bound + kLwRows - 1) / kLwRows <= kMostLookback; }
+
 int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *gathered_out, uint32_t *workgroups)
 {
     const int64_t tiles = (a.rows_bound + kLwRows - 1) / kLwRows;
     if (tiles > kMostLookback)
         return -1;
     *workgroups = (uint32_t)tiles;
-    hipLaunchKernelGGL(ldw_rows_kernel, dim3((unsigned)tiles), dim3(kLwRows), 0, L.stream, a, lb, gathered_out);
+    int64_t more = a.seeds ? a.k : 0;
+    size_t lds = 0;
+    if (ldw_fused(a)) {
+        more += grid_for(L, (((int64_t)a.nwin + 64) / 64) * ((a.rows_bound + 63) / 64), 8);
+        lds = 64 * 65 * sizeof(uint32_t);
+    }
+    if (a.seeds)
+        lds = std::max(lds, (size_t)a.seed_slots * sizeof(uint32_t));
+    hipLaunchKernelGGL(ldw_rows_kernel, dim3((unsigned)(tiles + more)), dim3(kLwRows), lds, L.stream, a, lb, gathered_out, (int)tiles);
     return 0;
 }
 
 void launch_ldw_bounds(const Launch &L, const LwHop &a)
 {
     const int64_t ttiles = (((int64_t)a.nwin + 64) / 64) * ((a.rows_bound + 63) / 64);
-    if (a.index && a.k < kPlanMb) {
-        const int planners = grid_for(L, (a.rows_bound + 1023) / 1024, 1);
-        hipLaunchKernelGGL(ldw_plan_bounds_kernel, dim3(planners + grid_for(L, ttiles, 8)), dim3(256), 0, L.stream, a, planners);
-        return;
-    }
     launch_ldw_tiles(L, a);
     if (!a.index)
         hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
@@ -1478,7 +1614,7 @@ void launch_ldw_index(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
 
-int launch_ldw_accumulate(const Launch &L, const LwHop &a, int64_t *pnnz_out)
+int launch_ldw_accumulate(const Launch &L, const LwHop &a)
 {
     void (*const kernels[2])(LwHop) = {ldw_accumulate_kernel<false>, ldw_accumulate_kernel<true>};
     static bool attr_set = false;
@@ -1491,14 +1627,29 @@ int launch_ldw_accumulate(const Launch &L, const LwHop &a, int64_t *pnnz_out)
     }
     hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, (int64_t)a.k * a.nwin, 1)), dim3(kAccThreads),
                        ldw_accumulate_lds_bytes(), L.stream, a);
-    if (hipGetLastError() != hipSuccess)
-        return -1;
-    hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k), dim3(kScanThreads), 0, L.stream, a, pnnz_out);
-    return 0;
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-void launch_ldw_p_copy(const Launch &L, const LwHop &a)
+bool ldw_may_place(const LwHop &a) { return ldw_fused(a) && (int64_t)a.k * a.nwin <= kMostPlacedPairs; }
+
+void launch_ldw_win_scan(const Launch &L, const LwHop &a, int64_t *pnnz_out)
 {
+    const int planners = ldw_fused(a) ? grid_for(L, (a.rows_bound + 4 * kScanThreads - 1) / (4 * kScanThreads), 1) : 0;
+    hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k + planners), dim3(kScanThreads), 0, L.stream, a, pnnz_out);
+}
+
+void launch_ldw_p_copy(const Launch &L, const LwHop &a, int64_t *pnnz_out)
+{
+    if (a.place_pairs) {
+        void (*const kernels[2][2])(LwHop, int, int64_t *) = {{ldw_p_place_kernel<false, 1024>, ldw_p_place_kernel<false, 256>},
+                                                              {ldw_p_place_kernel<true, 1024>, ldw_p_place_kernel<true, 256>}};
+        const int64_t pairs = (int64_t)a.k * a.nwin;
+        const int nt = pairs <= 2 * L.num_cu ? 1024 : 256;
+        const int planners = grid_for(L, (a.rows_bound + 4 * nt - 1) / (4 * nt), 1);
+        hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][nt == 1024 ? 0 : 1], dim3((unsigned)(pairs + planners)), dim3(nt), 0, L.stream, a,
+                           planners, pnnz_out);
+        return;
+    }
     void (*const kernels[2])(LwHop) = {ldw_p_copy_kernel<false>, ldw_p_copy_kernel<true>};
     hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
