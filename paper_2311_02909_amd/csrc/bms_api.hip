@@ -2,6 +2,7 @@
 #include "../../include/bms.h"
 #include "bms_device.h"
 #include "bms_internal.h"
+#include "publish.h"
 
 #include <algorithm>
 #include <atomic>
@@ -515,7 +516,7 @@ try {
         c.res->host[kArrivedSlot] = c.res->arrival;
     }
     c.res->host_off = false;
-    c.res->host[64] = 0;
+    c.res->host[64] = c.res->host[kRaisedSlot] = 0;
     BMS_TRY(csr->sm_ticket.ensure(256));
     if (!csr->tickets_known) { // (a workgroup's number decides what it writes: never one of another launch)
         HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
@@ -666,8 +667,12 @@ int wait_arrival(CallCtx &c)
     return BMS_OK;
 }
 
-// The call's scalars and the minibatches' offsets -> pinned memory of the result, in stream order.
-void publish(CallCtx &c)
+// Workgroups of a last kernel that publishes the call, at most: its stores go past the caches.  The layer-wise one with 6 and 64
+// workgroups saves 3 us of calls of 69 and 377 us, with 512 it costs as much as it saves.
+constexpr int64_t kMostPublishing = 128;
+// The call's scalars and the minibatches' offsets -> pinned memory of the result: by the call's last kernel, or in stream order by one
+// of its own.
+PublishArgs publish_args(CallCtx &c)
 {
     PublishArgs p{};
     p.arrived = c.res->host + kArrivedSlot;
@@ -684,9 +689,10 @@ void publish(CallCtx &c)
         p.rowoff[h] = v.mb_rowoff;
         p.coloff[h] = v.mb_coloff;
     }
-    launch_publish(c.launch, p);
     c.res->host_off = p.off != nullptr;
+    return p;
 }
+void publish(CallCtx &c) { launch_publish(c.launch, publish_args(c)); }
 
 // scalar slots: per hop 4 int64: [0] nnz, [1] ncols, [2] pnnz, [3] gathered D ; slot 63 = seed flag
 inline int64_t *slot(CallCtx &c, int32_t hop, int which) { return c.csr->scalars.as<int64_t>() + hop * 4 + which; }
@@ -1514,7 +1520,8 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
     const bool no_wait = may_skip_waits && !c.fresh_result && c.res->hint_csr == csr->serial && c.res->hint_shape == shape &&
                          (int32_t)c.res->hint_gathered.size() == c.L && (int32_t)c.res->hint_pnnz.size() == c.L &&
                          (int32_t)c.res->hint_nnz.size() == c.L;
-    int32_t *giveup = reinterpret_cast<int32_t *>(csr->scalars.as<int64_t>() + 60);
+    int32_t *giveup = reinterpret_cast<int32_t *>(csr->scalars.as<int64_t>() + kRaisedSlot);
+    bool published = false;
 
     for (int32_t h = 0; h < c.L; ++h) {
         HopBufs &hb = c.res->hops[h];
@@ -1707,15 +1714,6 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.col_cap = std::max<int64_t>(nnz, 1);
         BMS_TRY(hb.col.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(int32_t)));
         w.out_col = hb.col.as<int32_t>();
-        BMS_TRY(prof.begin("ldw_extract_copy", h));
-        if (placed) {
-            BMS_TRY(next_lookback(c, lb));
-            (void)launch_ldw_extract_place(c.launch, w, lb, slot(c, h, 0), &workgroups);
-            lookback_used(c, workgroups);
-        } else {
-            launch_ldw_extract_copy(c.launch, w);
-        }
-        BMS_TRY(prof.end());
 
         hb.view = bms_hop_view{}; // the sizes follow after the last read-back
         hb.view.mb_rowoff = mb_rowoff;
@@ -1728,16 +1726,29 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         hb.view.p_col = hb.p_col.as<int32_t>();
         hb.view.p_cnt = hb.p_cnt.as<uint32_t>();
 
+        BMS_TRY(prof.begin("ldw_extract_copy", h));
+        if (placed) {
+            published = h + 1 == c.L && rows_bound <= kMostPublishing * kLwRows;
+            const PublishArgs p = published ? publish_args(c) : PublishArgs{};
+            BMS_TRY(next_lookback(c, lb));
+            (void)launch_ldw_extract_place(c.launch, w, lb, slot(c, h, 0), published ? &p : nullptr, &workgroups);
+            lookback_used(c, workgroups);
+        } else {
+            launch_ldw_extract_copy(c.launch, w);
+        }
+        BMS_TRY(prof.end());
+
         row_vertex = hb.col_vertex.as<int32_t>();
         mb_rowoff = hb.mb_coloff.as<int64_t>();
         rows_bound = std::max<int64_t>(ncols_bound, 1);
     }
-    publish(c);
+    if (!published)
+        publish(c);
     BMS_TRY(wait_arrival(c));
     const int64_t *host = c.res->host;
     if (no_wait) {
         BMS_TRY(seed_flag_error(csr->n, host, host));
-        if ((int32_t)(host[60] & 0xFFFFFFFF)) { // a size went past what the remembered call needed
+        if ((int32_t)(host[kRaisedSlot] & 0xFFFFFFFF)) { // a size went past what the remembered call needed
             *redo = true;
             return BMS_OK;
         }

@@ -420,7 +420,8 @@ void launch_ldw_draw(const Launch &, const LwHop &, const Lookback *lb, int64_t 
 void launch_ldw_sel_copy(const Launch &, const LwHop &);
 void launch_ldw_extract(const Launch &, const LwHop &);
 void launch_ldw_extract_copy(const Launch &, const LwHop &); // after a scan of out_rowptr
-int launch_ldw_extract_place(const Launch &, const LwHop &, const Lookback &, int64_t *nnz_out, uint32_t *workgroups); // does both
+// does both, and with p publishes the call
+int launch_ldw_extract_place(const Launch &, const LwHop &, const Lookback &, int64_t *nnz_out, const PublishArgs *p, uint32_t *workgroups);
 
 // ---- feature fetching ----
 // out[j, :] = H[ids[j], :]; *flag (device-visible, zeroed by the caller) is set when an id lies outside [0, n);

@@ -36,6 +36,7 @@
 // A call that sizes its buffers from an earlier call of the same shape runs all of these behind LwHop::giveup.
 #include "bms_device.h"
 #include "bms_internal.h"
+#include "publish.h"
 #include <algorithm>
 
 namespace bms {
@@ -1494,8 +1495,15 @@ __global__ __launch_bounds__(256) void ldw_extract_copy_kernel(LwHop a)
 // The scan of the rows' counts and the copy in one launch: 256 rows per workgroup, the rows before summed up by sum_before,
 // then one entry per lane and step, whose row is found in the offsets in LDS.  Chains of trips to memory: what leads to a row's
 // later pieces is fetched before the sum of the rows before, not after it (three layers of 32 x 512 seeds: 43 -> 37 us).
-__global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Lookback lb, int64_t *nnz_out)
+template <bool PUBLISH>
+__device__ inline void extract_place(const LwHop &a, const Lookback &lb, int64_t *nnz_out, const PublishArgs &p)
 {
+    auto put = [](auto *p, auto v) {
+        if (PUBLISH)
+            store_through(p, v);
+        else
+            *p = v;
+    };
     __shared__ int64_t smem[kLwRows / kWave];
     __shared__ uint32_t number_s;
     __shared__ int64_t gather_l[kLwRows], tile_l[kLwRows], pos_l[kLwRows]; // of a row: first kept neighbour, tile, that tile's first position
@@ -1511,8 +1519,9 @@ __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Loo
         return;
     const int shift = __ffs(a.tile) - 1;
     int64_t cnt = 0, g = 0, gm = 0, xm = 0;
+    int i = -1;
     if (!up_s && r < R) {
-        const int i = a.row_mb[r];
+        i = a.row_mb[r];
         cnt = a.out_rowptr[r];
         g = a.gather_off[r];
         first_l[tid] = a.first_cnt[r];
@@ -1528,15 +1537,28 @@ __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Loo
     tile_l[tid] = xm + ((g - gm) >> shift);
     pos_l[tid] = gm + ((g - gm) >> shift << shift);
     const int64_t before = sum_before<kLwRows>(lb, t, total, smem);
-    if (r < R)
-        a.out_rowptr[r] = before + ex;
-    if (r0 + kLwRows >= R && tid == 0) {
-        a.out_rowptr[R] = before + total;
-        *nnz_out = before + total;
+    int64_t *host_off = PUBLISH && p.off ? p.off + ((int64_t)(p.L - 1) * 3 + 1) * (a.k + 1) : nullptr; // first entries of the minibatches
+    if (r < R) {
+        put(a.out_rowptr + r, before + ex);
+        for (; host_off && i >= 0 && a.mb_rowoff[i] == r; --i) // (and of those without rows before it)
+            put(host_off + i, before + ex);
     }
+    if (r0 + kLwRows >= R && tid == 0) {
+        put(a.out_rowptr + R, before + total);
+        put(nnz_out, before + total);
+        if (PUBLISH)
+            put(p.host + (nnz_out - p.scalars), before + total);
+        for (i = a.k; host_off && i >= 0 && a.mb_rowoff[i] == R; --i)
+            put(host_off + i, before + total);
+    }
+    if (PUBLISH && t == 0)
+        publish_before<kLwRows>(p, nnz_out);
     if (a.giveup && before + total > a.col_cap) { // the kept neighbours do not fit what was provided
-        if (tid == 0)
-            *a.giveup = 1;
+        if (tid == 0) {
+            put(a.giveup, 1);
+            if (PUBLISH)
+                put(reinterpret_cast<int32_t *>(p.host + kRaisedSlot), 1);
+        }
         return;
     }
     for (uint32_t e = tid; e < (uint32_t)total; e += kLwRows) {
@@ -1559,8 +1581,17 @@ __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Loo
             } while (x >= piece);
             g = pos_l[lo] + ((tile - tile0) << shift);
         }
-        a.out_col[before + e] = a.xtmp[g + x];
+        put(a.out_col + before + e, a.xtmp[g + x]);
     }
+}
+
+// PUBLISH: the call's last launch, which leaves the sizes for the host as well
+template <bool PUBLISH>
+__global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Lookback lb, int64_t *nnz_out, PublishArgs p)
+{
+    extract_place<PUBLISH>(a, lb, nnz_out, p);
+    if (PUBLISH)
+        announce_through(p, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1689,13 +1720,16 @@ void launch_ldw_extract(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_extract_kernel, dim3((unsigned)per_mb, a.k), dim3(kExtThreads), lds, L.stream, a, slots, filter_bits);
 }
 
-int launch_ldw_extract_place(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *nnz_out, uint32_t *workgroups)
+int launch_ldw_extract_place(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *nnz_out, const PublishArgs *p, uint32_t *workgroups)
 {
     const int64_t tiles = (a.rows_bound + kLwRows - 1) / kLwRows;
     if (tiles > kMostLookback)
         return -1;
     *workgroups = (uint32_t)tiles;
-    hipLaunchKernelGGL(ldw_extract_place_kernel, dim3((unsigned)tiles), dim3(kLwRows), 0, L.stream, a, lb, nnz_out);
+    if (p)
+        hipLaunchKernelGGL(ldw_extract_place_kernel<true>, dim3((unsigned)tiles), dim3(kLwRows), 0, L.stream, a, lb, nnz_out, *p);
+    else
+        hipLaunchKernelGGL(ldw_extract_place_kernel<false>, dim3((unsigned)tiles), dim3(kLwRows), 0, L.stream, a, lb, nnz_out, PublishArgs{});
     return 0;
 }
 
