@@ -11,6 +11,12 @@ constexpr int kLineWords = 16;     // a vertex-set "line": 16 x 32-bit words = 5
 constexpr int kLineBits = 512;
 constexpr int kChunkLines = 256;   // lines ranked by one workgroup (131072 vertex ids)
 
+// T in device memory.  A pointer that was computed as a number, or comes from LDS, is not known to lead there: its loads count as
+// accesses of LDS too, and every later access of LDS waits for all of them.
+template <class T>
+using InMemory = __attribute__((address_space(1))) T;
+using U32x4 = uint32_t __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------------------------------------
 // Counter-based random stream: a stateless hash of (seed, hop, minibatch, vertex, draw index).
 // 64-bit work happens once per distribution (the key); every draw is 32-bit arithmetic.

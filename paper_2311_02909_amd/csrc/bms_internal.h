@@ -411,7 +411,8 @@ bool ldw_fused(const LwHop &);
 int launch_ldw_rows(const Launch &, const LwHop &, const Lookback &, int64_t *gathered_out, uint32_t *workgroups);
 void launch_ldw_bounds(const Launch &, const LwHop &); // with an index: the rows' lists are copied from it
 void launch_ldw_index(const Launch &, const LwHop &);  // boundary lists of the rows of a hop that is the whole graph
-int launch_ldw_accumulate(const Launch &, const LwHop &); // -1: launch refused
+// most: about the largest e_v there will be; -1: launch refused
+int launch_ldw_accumulate(const Launch &, const LwHop &, double most);
 bool ldw_may_place(const LwHop &);               // few enough pairs: LwHop::place_pairs, and no launch_ldw_win_scan
 void launch_ldw_win_scan(const Launch &, const LwHop &, int64_t *pnnz_out); // places of the parts, p_off
 void launch_ldw_p_copy(const Launch &, const LwHop &, int64_t *pnnz_out);

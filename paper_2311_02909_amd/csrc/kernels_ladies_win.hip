@@ -14,10 +14,10 @@
 //                   graph) and a hop only copies the lists of its rows; else the hop streams its rows for them.
 //                   Either way the lists are turned window-major for the next kernel (with the index and k < 1024 plan,
 //                   tile rows and this are one launch, ldw_plan_bounds)
-//   ldw_accumulate  one workgroup per (minibatch, window): 2^16 packed 16-bit counters in LDS (128 KB); every
-//                   row's piece of the window adds 1 per neighbour (e_v cannot exceed the number of frontier
-//                   rows, which this path keeps below 2^16); each wave then takes its sixteenth of the window
-//                   (a part) out: the nonzero counters leave in ascending column order as 4-byte entries
+//   ldw_accumulate  one workgroup per (minibatch, window): 2^16 packed counters of 16 bits (128 KB) or 8 bits in LDS;
+//                   every row's piece of the window adds 1 per neighbour (e_v cannot exceed the number of frontier
+//                   rows, which this path keeps below 2^16); the waves then take its sixteenths
+//                   (parts) out: the nonzero counters leave in ascending column order as 4-byte entries
 //                   (column - window start, e_v) into room claimed from a device-wide cursor
 //   ldw_win_scan    per minibatch: columns and weight of every window, before each of its parts, before the window
 //   ldw_p_copy      parts copied to their place in P, one wave per part; inclusive prefix sums of the integer
@@ -42,21 +42,18 @@
 namespace bms {
 
 constexpr int kWinIds = 1 << kWinShift;
-constexpr int kWinWords = kWinIds / 2; // two 16-bit counters per LDS word
-constexpr int kAccThreads = 1024;
-constexpr int kAccWaves = kAccThreads / kWave;
-static_assert(kAccWaves == kWinParts, "one part of a window per wave of the accumulation");
-constexpr int kWaveWords = kWinWords / kAccWaves; // counter words compacted by one wave
+constexpr int kPartIds = kWinIds / kWinParts; // a part of a window
+constexpr int kWaveWords = 2048;         // counter words that a wave of the accumulation takes out: a part in 16 bits, two in 8
 constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;
 constexpr int kExtThreads = 1024; // the waves of a workgroup share one hash table
 constexpr int kExtWaves = kExtThreads / kWave;
 constexpr int kAccUnroll = 8;              // 16-byte loads per lane and span
 constexpr int kAccChunks = kWave * kAccUnroll; // aligned 16-byte chunks per span: one per lane and load
 constexpr int kAccFlush = 4;               // entries per lane on their way out at a time
-constexpr int kAccListed = 896;            // counters in use that a wave lists in LDS at a time
+constexpr int kAccListed = 960;            // counters in use that a wave lists in LDS at a time
 struct AccPiece {                          // one nonempty piece of a wave's rows
     int64_t origin;                        // byte address of its first chunk - 16 * chunks of the batch before it
-    uint32_t lo_rel, hi_rel;               // its bytes, relative to origin
+    int32_t lo, hi;                        // its first entry and the one behind its last, counted from origin
 };
 struct AccWave {
     union { // in turn
@@ -65,12 +62,25 @@ struct AccWave {
     };
     uint32_t starts[2 * kAccUnroll]; // a bit per chunk of a span: a piece starts there
 };
+// A workgroup of the accumulation: 16 waves with counters of 16 bits (a compute unit holds one), or 8 with counters of 8 bits
+// (it holds two).
+template <bool NARROW>
+constexpr int kAccThreads = NARROW ? 512 : 1024;
+template <bool NARROW>
 struct AccShared {
-    AccWave wave[kAccWaves];
+    static constexpr int kWaves = kAccThreads<NARROW> / kWave;
+    AccWave wave[kWaves];
     unsigned long long claimed; // where the pair's entries start in the staging array
     unsigned long long weight;  // of the pair's columns
-    uint32_t cnt[kAccWaves];    // columns in the waves' parts
+    uint32_t cnt[kWinParts];    // columns in the parts
+    uint32_t missing[kWaves];   // with 8 bits: neighbours in the wave's rows - those that its counters show
 };
+template <bool NARROW>
+struct AccLds {
+    alignas(16) uint32_t cnt[AccShared<NARROW>::kWaves * kWaveWords]; // packed counters
+    AccShared<NARROW> sh;
+};
+static_assert(sizeof(AccLds<false>) <= 160 * 1024 && 2 * sizeof(AccLds<true>) <= 160 * 1024, "does not fit a compute unit");
 constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
 constexpr int kStreamUnroll = 8; // neighbours per lane in flight in the two streaming passes
 constexpr int kDrawTop = 2048;                    // recorded weight sums of P that a drawing workgroup keeps in LDS
@@ -425,36 +435,38 @@ __device__ inline uint32_t at_most_one(uint32_t x)
     return v.whole;
 }
 
-// A compute unit holds one workgroup (the counters fill its LDS), so nothing but its own waves hides what they wait for, and
-// all of them are in the same phase:
+// A compute unit's LDS holds one workgroup with counters of 16 bits, whose waves are all in the same phase, or two with counters of
+// 8 bits (NARROW), which fill one another's waits:
 //   gather   a pair's first span of chunks is asked for while the counters of the pair before it leave
-//   count    64 consecutive counters per lane: a bit for each that is in use, columns and weight of the wave's part
+//   count    64 consecutive counters per lane: a bit for each that is in use, columns and weight of the wave's parts.  8 bits: a
+//            pair with a counter that passed 255 is found by the sum of all counters, and counted anew half by half in 16 bits
 //   write    a lane lists its counters in use, in column order, in LDS; the entries leave 64 to a store, into room claimed for
 //            exactly as many (the claim is on its way while the lists are made)
-// Bound by the lines of the pieces, which arrive in bursts (dense: 9 of 18 us per pair for 2900 of them), then by vector
-// instructions.  Few rows lie in half waves, so that all waves have some.  Weights e_v and e_v^2 are kernels of their own: decided
-// inside, at every word, the branch kept the LDS reads from overlapping.  Three layers of 32 x 512 seeds, 512 samples, 2.4 M
-// vertices: 171 -> 127 us (and 55 -> 44 in the copy of P, as parts lie one after the other); 64 x 1024 seeds, 2048 samples,
-// 8.7 M vertices (27 k neighbours per pair): 1600 -> 1540.
-// Tried and slower: two spans of fewer loads in flight (1.15 times on the latter), the next pair's loads dealt out between the
+// Bound by vector instructions (two thirds of the time) and the lines of the pieces.  Few rows lie in half waves, so that all waves
+// have some.  Weights e_v and e_v^2 are kernels of their own: decided inside, at every word, the branch kept the LDS reads from
+// overlapping.  The chunks are read from addresses that the compiler knows to be memory: read from just any, each LDS addition waited
+// for the one before it.  64 x 1024 seeds, 2048 samples, 8.7 M vertices (27 k neighbours per pair), one hop: 650 us, 560 by that and
+// the shorter instruction sequences, 472 by counters of 8 bits as well; 32 x 512 seeds, 512 samples, 2.4 M vertices: 45 -> 36.
+// Tried and slower: two spans of fewer loads in flight (1.15 times on the former), the next pair's loads dealt out between the
 // steps of the count (1.14), all 64 lanes adding, those without an entry nothing (1.04: an LDS addition costs by active lanes),
 // P written here at its final place, found by looking back over the sizes of the pairs before (1.2 to 1.7 times accumulation
 // and copy together: it ties all workgroups to the slowest one of every round).
-template <bool SQUARED>
-__global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
+template <bool SQUARED, bool NARROW>
+__global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(LwHop a)
 {
-    extern __shared__ uint4 acc_lds[];
+    __shared__ AccLds<NARROW> lds; // (at a place that the compiler knows: an addition less per neighbour)
     if (a.giveup && *a.giveup)
         return;
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(acc_lds); // kWinWords packed counters
-    AccShared &sh = *reinterpret_cast<AccShared *>(cnt + kWinWords);
+    constexpr int NT = kAccThreads<NARROW>, NW = NT / kWave;
+    uint32_t *cnt = lds.cnt;
+    AccShared<NARROW> &sh = lds.sh;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = (int)scalar((uint32_t)tid / kWave);
     AccWave &me = sh.wave[wave];
     const int64_t A0 = (int64_t)reinterpret_cast<uintptr_t>(a.A_col);
     const uint32_t nwin = (uint32_t)a.nwin, nblk = (uint32_t)a.k * nwin; // (at most 2^16 minibatches and 2^15 windows)
-    for (int x = tid; x < kWinWords / 4; x += kAccThreads)
-        acc_lds[x] = make_uint4(0, 0, 0, 0);
+    for (int x = tid; x < NW * kWaveWords / 4; x += NT)
+        reinterpret_cast<uint4 *>(cnt)[x] = make_uint4(0, 0, 0, 0);
     if (tid == 0)
         sh.weight = 0;
     __syncthreads();
@@ -475,6 +487,7 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
     // they are used: the loads have until then)
     uint32_t bound0 = 0, bound1 = 0;
     int64_t row_beg = 0;
+    uint32_t have = 0;               // neighbours in the pieces of this lane
     uint32_t u0 = 0, total = 0, ustart = 0; // chunks of the batch: those asked for, all, before the lane's piece
     auto fetch_pieces = [&]() {
         bound0 = bound1 = 0;
@@ -495,7 +508,7 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
             window = blk - i * nwin;
             r0 = uniform_load(a.mb_rowoff + i);
             all = (int32_t)(uniform_load(a.mb_rowoff + i + 1) - r0);
-            rows = all <= kAccWaves * (kWave / 2) ? kWave / 2 : kWave;
+            rows = all <= NW * (kWave / 2) ? kWave / 2 : kWave;
             first = wave * rows;
         }
         fetch_pieces();
@@ -510,7 +523,7 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
     // neighbouring windows' or rows') are masked; an aligned 16-byte read that holds at least one entry of
     // the piece stays inside that entry's page.
     struct Span {
-        uint4 v[kAccUnroll];
+        U32x4 v[kAccUnroll];
         uint32_t keep;  // 4 bits per load: which of the 4 entries belong to the piece
         uint32_t chunks;
     };
@@ -526,6 +539,8 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
             const uint32_t nc = len ? (uint32_t)((hi_byte - 1 - chunk0) >> 4) + 1u : 0u;
             const bool nonempty = nc != 0;
             if (u0 == 0) {
+                if (NARROW)
+                    have += len;
                 const uint32_t inc = wave_inclusive_scan_dpp(nc);
                 total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
                 ustart = inc - nc;
@@ -537,8 +552,8 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
                 if (nonempty) {
                     AccPiece rec;
                     rec.origin = chunk0 - (int64_t)ustart * 16; // chunk j of the batch starts at origin + 16 j
-                    rec.lo_rel = (uint32_t)(lo_byte - rec.origin);
-                    rec.hi_rel = (uint32_t)(hi_byte - rec.origin);
+                    rec.lo = (int32_t)((lo_byte - rec.origin) >> 2);
+                    rec.hi = (int32_t)((hi_byte - rec.origin) >> 2);
                     me.piece[bits_below(ne_mask)] = rec;
                 }
                 if (lane < 2 * kAccUnroll)
@@ -560,38 +575,48 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
                     rank += __popcll(m);
                     if (j0 + u * kWave < s.chunks) {
                         const AccPiece rec = me.piece[mine];
-                        const uint32_t off = (u0 + j0 + u * kWave) * 16u; // of the lane's 16 bytes, from origin
-                        uint32_t k4 = 0;
-#pragma unroll
-                        for (uint32_t e = 0; e < 4; ++e)
-                            k4 |= (off + 4u * e >= rec.lo_rel && off + 4u * e < rec.hi_rel) ? 1u << e : 0u;
-                        s.v[u] = *reinterpret_cast<const uint4 *>(rec.origin + (int64_t)off);
-                        s.keep |= k4 << (4 * u);
+                        const uint32_t x = u0 + j0 + u * kWave; // the lane's chunk, from origin
+                        const int from = max(rec.lo - (int)(4 * x), 0), to = min(rec.hi - (int)(4 * x), 4); // its entries in the piece
+                        s.v[u] = *reinterpret_cast<const InMemory<U32x4> *>(rec.origin + (int64_t)x * 16);
+                        s.keep |= ((1u << to) - (1u << from)) << (4 * u);
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
                 u0 += kAccChunks;
             }
             if (u0 >= total) { // the next batch's pieces are fetched for the next call
-                first += kAccWaves * rows;
+                first += NW * rows;
                 fetch_pieces();
             }
             if (s.chunks)
                 break;
         }
     };
-    auto add = [&](const Span &s, uint32_t id0) {
+    // NARROW: all counters of the window in 8 bits (half < 0), or, where that was too little, those of one half of it in 16.
+    // (An id's place in the window are its last 16 bits.)
+    int half = -1;
+    auto add = [&](const Span &s) {
+        auto each = [&](auto body) {
 #pragma unroll
-        for (int u = 0; u < kAccUnroll; ++u) {
-            if ((uint32_t)(u * kWave) >= s.chunks)
-                break;
-            const uint32_t xs[4] = {s.v[u].x, s.v[u].y, s.v[u].z, s.v[u].w};
+            for (int u = 0; u < kAccUnroll; ++u) {
+                if ((uint32_t)(u * kWave) >= s.chunks)
+                    break;
+                const U32x4 xs = s.v[u];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if ((s.keep >> (4 * u + e)) & 1u) {
-                    const uint32_t x = xs[e] - id0;
-                    atomicAdd(&cnt[x >> 1], 1u << ((x & 1u) * 16));
-                }
+                for (int e = 0; e < 4; ++e)
+                    if ((s.keep >> (4 * u + e)) & 1u)
+                        body(xs[e]);
+            }
+        };
+        if (!NARROW) {
+            each([&](uint32_t x) { atomicAdd(&cnt[(x & 0xFFFFu) >> 1], 1u << ((x << 4) & 31u)); });
+        } else if (half < 0) {
+            each([&](uint32_t x) { atomicAdd(&cnt[(x & 0xFFFFu) >> 2], 1u << ((x << 3) & 31u)); });
+        } else {
+            each([&](uint32_t x) {
+                if ((int)((x >> 15) & 1u) == half)
+                    atomicAdd(&cnt[(x & 0x7FFFu) >> 1], 1u << ((x << 4) & 31u));
+            });
         }
     };
 
@@ -599,121 +624,206 @@ __global__ __launch_bounds__(kAccThreads) void ldw_accumulate_kernel(LwHop a)
     begin_pair(blk);
     ask(s0);
     while (blk < nblk) {
-        const uint32_t id0 = window << kWinShift, blk_next = pair_of(++round);
-        add(s0, id0);
+        add(s0);
         while (more()) {
             ask(s0);
-            add(s0, id0);
+            add(s0);
         }
         __syncthreads();
-        // A bit per counter in use; lane x of the wave has counters 64 x .. 64 x + 63 of its part, 16 bytes at a time, and
+        // A bit per counter in use; lane x of the wave has counters 64 x .. 64 x + 63 of a part, 16 bytes at a time, and
         // begins elsewhere among them than the lanes 2 .. 14 further on: all of LDS's banks have work.
-        constexpr int kQuads = kWaveWords / 4 / kWave;
-        static_assert(kQuads == 8, "64 counters per lane");
+        constexpr int PARTS = NARROW ? 2 : 1; // of the wave; one only of half a window
+        const bool bytes = NARROW && half < 0;
+        const int parts = bytes ? 2 : 1;
+        const uint32_t part0 = bytes ? 2u * (uint32_t)wave : (NARROW && half == 1 ? (uint32_t)NW : 0u) + (uint32_t)wave; // the first, in the window
         uint32_t lane_now = (uint32_t)lane;
         asm volatile("" : "+v"(lane_now)); // (places: computed here, not kept in registers)
-        const uint4 *mine4 = reinterpret_cast<const uint4 *>(cnt + wave * kWaveWords) + lane_now * kQuads;
-        uint32_t used[2] = {0, 0}, w32 = 0; // e_v: 64 values below 2^16
-        uint64_t w64 = 0;                   // e_v^2
+        const uint4 *wave4 = reinterpret_cast<const uint4 *>(cnt + wave * kWaveWords);
+        uint32_t used[PARTS][2] = {}, w32[PARTS] = {}; // weight: e_v, or e_v^2 of counters of 8 bits
+        uint64_t w64 = 0;                              // e_v^2 of counters of 16 bits
+        uint32_t shown = 0;                            // e_v
+        if (bytes) {
 #pragma unroll
-        for (int it = 0; it < kQuads; ++it) {
-            const uint32_t at = (it + lane_now / 2) & (kQuads - 1);
-            const uint4 q = mine4[at];
-            const uint32_t xs[4] = {q.x, q.y, q.z, q.w};
-            uint32_t bits = 0; // of the lower counters at 0, 2, 4, 6, of the upper ones at 16, 18, 20, 22
+            for (int q = 0; q < PARTS; ++q) {
+                constexpr int kQuads = kPartIds / 16 / kWave;
+                static_assert(kQuads == 4, "64 counters per lane");
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bits |= at_most_one(xs[u]) << (2 * u);
-                if (SQUARED) {
-                    const uint32_t lo = xs[u] & 0xFFFFu, hi = xs[u] >> 16;
-                    w64 += (uint64_t)(lo * lo) + (uint64_t)(hi * hi);
-                } else {
-                    w32 = __builtin_amdgcn_sad_u16(xs[u], 0u, w32); // + both halves
+                for (int it = 0; it < kQuads; ++it) {
+                    const uint32_t at = (it + lane_now / 4) & (kQuads - 1);
+                    const uint4 v = wave4[q * (kPartIds / 16) + lane_now * kQuads + at];
+                    const uint32_t xs[4] = {v.x, v.y, v.z, v.w};
+                    uint32_t bits[2] = {0, 0}; // 8 counters each
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const uint32_t nonzero = ((xs[u] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | xs[u]; // bit 7 of each byte
+                        bits[u / 2] = __builtin_amdgcn_udot4((nonzero >> 7) & 0x01010101u, u % 2 ? 0x80402010u : 0x08040201u, bits[u / 2], false);
+                        shown = __builtin_amdgcn_sad_u8(xs[u], 0u, shown); // + all four bytes
+                        if (SQUARED)
+                            w32[q] = __builtin_amdgcn_udot4(xs[u], xs[u], w32[q], false);
+                    }
+                    const uint32_t both = (bits[0] | bits[1] << 8) << (16 * (at & 1u));
+                    used[q][0] |= at < 2 ? both : 0u;
+                    used[q][1] |= at < 2 ? 0u : both;
                 }
+                if (!SQUARED)
+                    w32[q] = shown - (q ? w32[0] : 0u);
             }
-            bits = ((bits & 0x55u) | ((bits >> 15) & 0xAAu)) << (8 * (at & 3u));
-            used[0] |= at < 4 ? bits : 0u;
-            used[1] |= at < 4 ? 0u : bits;
+        } else {
+            constexpr int kQuads = kWaveWords / 4 / kWave;
+            static_assert(kQuads == 8, "64 counters per lane");
+#pragma unroll
+            for (int it = 0; it < kQuads; ++it) {
+                const uint32_t at = (it + lane_now / 2) & (kQuads - 1);
+                const uint4 v = wave4[lane_now * kQuads + at];
+                const uint32_t xs[4] = {v.x, v.y, v.z, v.w};
+                uint32_t bits = 0; // of the lower counters at 0, 2, 4, 6, of the upper ones at 16, 18, 20, 22
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    bits |= at_most_one(xs[u]) << (2 * u);
+                    if (SQUARED) {
+                        const uint32_t lo = xs[u] & 0xFFFFu, hi = xs[u] >> 16;
+                        w64 += (uint64_t)(lo * lo) + (uint64_t)(hi * hi);
+                    } else {
+                        w32[0] = __builtin_amdgcn_sad_u16(xs[u], 0u, w32[0]); // + both halves
+                    }
+                }
+                bits = ((bits & 0x55u) | ((bits >> 15) & 0xAAu)) << (8 * (at & 3u));
+                used[0][0] |= at < 4 ? bits : 0u;
+                used[0][1] |= at < 4 ? 0u : bits;
+            }
         }
-        const uint32_t mine = __popc(used[0]) + __popc(used[1]);
-        const uint32_t upto = wave_inclusive_scan_dpp(mine);
-        const uint32_t wave_c = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
-        if (lane == 0)
-            sh.cnt[wave] = wave_c;
+        uint32_t mine[PARTS], upto[PARTS], part_c[PARTS];
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q) {
+            mine[q] = __popc(used[q][0]) + __popc(used[q][1]);
+            upto[q] = wave_inclusive_scan_dpp(mine[q]);
+            part_c[q] = (uint32_t)__builtin_amdgcn_readlane((int)upto[q], kWave - 1);
+            if (lane == 0 && q < parts)
+                sh.cnt[wave * parts + q] = part_c[q];
+        }
+        if (bytes) {
+            const uint32_t missing = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(have - shown), kWave - 1);
+            if (lane == 0)
+                sh.missing[wave] = missing;
+        }
+        have = 0;
         __syncthreads();
-        // room for the pair's entries; the parts lie in it one after the other
-        const uint32_t sums = wave_inclusive_scan_dpp(lane < kAccWaves ? sh.cnt[lane] : 0u);
-        const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)sums, kAccWaves - 1);
-        const uint32_t before_c = (uint32_t)__builtin_amdgcn_readlane((int)sums, wave) - wave_c;
+        uint4 *part4 = reinterpret_cast<uint4 *>(cnt + wave * kWaveWords) + lane_now;
+        auto clear = [&]() {
+#pragma unroll
+            for (int it = 0; it < kWaveWords / 4 / kWave; ++it)
+                part4[it * kWave] = make_uint4(0, 0, 0, 0);
+        };
+        // A counter that passed 255 carried into its neighbour or out of its word: that takes 255 or 256 from the sum of all
+        // counters, so the sum is that of the neighbours if and only if none did.
+        if (bytes && __builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(lane < NW ? sh.missing[lane] : 0u), NW - 1) != 0) {
+            half = 0; // the pair anew, one half after the other
+            clear();
+            begin_pair(blk);
+            ask(s0);
+            __syncthreads();
+            continue;
+        }
+        // room for the entries; the parts lie in it one after the other
+        const int np = NW * parts;
+        const uint32_t sums = wave_inclusive_scan_dpp(lane < np ? sh.cnt[lane] : 0u);
+        const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)sums, np - 1);
         unsigned long long claim = 0;
         if (tid == 0 && pair_c) {
             unsigned long long *cursor = a.cursor;
             asm volatile("" : "+v"(cursor)); // (an address known to be the same in all lanes has the wave wait for the answer here)
-            claim = atomicAdd(cursor, (unsigned long long)pair_c);
+            claim = __hip_atomic_fetch_add((InMemory<unsigned long long> *)cursor, (unsigned long long)pair_c, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
         }
+        const int half_now = half;
+        half = half == 0 ? 1 : -1;
+        const uint32_t blk_next = half == 1 ? blk : pair_of(++round);
         begin_pair(blk_next);
-        // All lanes' counters are listed at once, or, of a part with more in use, those of 8 lanes at a time.
+        // All lanes' counters are listed at once, or, of a part with more in use, those of half of the lanes or of 8 at a time.
         static_assert(8 * 64 <= kAccListed, "8 lanes' counters");
-        const int lanes = wave_c <= (uint32_t)kAccListed ? kWave : 8;
-        auto list_up = [&](int lane0, uint32_t listed) {
+        auto lanes_of = [&](int q) {
+            const uint32_t lower = (uint32_t)__builtin_amdgcn_readlane((int)upto[q], kWave / 2 - 1);
+            return part_c[q] <= (uint32_t)kAccListed ? kWave : max(lower, part_c[q] - lower) <= (uint32_t)kAccListed ? kWave / 2 : 8;
+        };
+        auto list_up = [&](int q, int lane0, uint32_t listed) {
             __builtin_amdgcn_wave_barrier();
-            if (lane >= lane0 && lane < lane0 + lanes) {
-                uint16_t *to = me.list + (upto - mine - listed);
-                for (uint32_t m = used[0]; m; m &= m - 1u)
+            if (lane >= lane0 && lane < lane0 + lanes_of(q)) {
+                uint16_t *to = me.list + (upto[q] - mine[q] - listed);
+                for (uint32_t m = used[q][0]; m; m &= m - 1u)
                     *to++ = (uint16_t)(lane * 64 + __ffs((int)m) - 1);
-                for (uint32_t m = used[1]; m; m &= m - 1u)
+                for (uint32_t m = used[q][1]; m; m &= m - 1u)
                     *to++ = (uint16_t)(lane * 64 + 31 + __ffs((int)m));
             }
             __builtin_amdgcn_wave_barrier();
         };
-        list_up(0, 0);
-        const uint64_t wave_w = wave_sum(SQUARED ? w64 : (uint64_t)w32);
+        list_up(0, 0, 0);
+        uint64_t part_w[PARTS], wave_w = 0;
+#pragma unroll
+        for (int q = 0; q < PARTS; ++q) {
+            if (SQUARED && !bytes)
+                part_w[q] = q ? 0ull : wave_sum(w64);
+            else // (32 bits: 4096 values, below 2^16 or squares of less than 2^8)
+                part_w[q] = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(w32[q]), kWave - 1);
+            wave_w += part_w[q];
+        }
         if (tid == 0)
             sh.claimed = claim;
         if (lane == 0)
             atomicAdd(&sh.weight, (unsigned long long)wave_w);
         __syncthreads();
         if (tid == 0) {
-            a.win_cnt[blk] = pair_c;
-            a.win_wt[blk] = sh.weight;
+            const bool second = NARROW && half_now == 1; // half of the window
+            a.win_cnt[blk] = pair_c + (second ? a.win_cnt[blk] : 0u);
+            a.win_wt[blk] = sh.weight + (second ? a.win_wt[blk] : 0ull);
             sh.weight = 0; // (two barriers before the next pair's)
         }
-        const int64_t claimed = scalar((int64_t)sh.claimed) + before_c;
-        if (lane == 0) {
-            const int64_t part = (int64_t)blk * kWinParts + wave;
-            a.part_base[part] = claimed;
-            a.part_cnt[part] = wave_c;
-            a.part_wt[part] = wave_w;
-        }
-        if (wave_c) {
-            uint32_t *__restrict__ out = a.tmp_ent + claimed;
-            const uint16_t *cnt16 = reinterpret_cast<const uint16_t *>(cnt + wave * kWaveWords);
-            const uint32_t part_id = (uint32_t)wave * (2 * kWaveWords);
-            for (int lane0 = 0; lane0 < kWave; lane0 += lanes) {
-                const uint32_t listed = lane0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, lane0 - 1) : 0u;
-                const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, lane0 + lanes - 1) - listed;
-                if (lane0)
-                    list_up(lane0, listed);
-                for (uint32_t x0 = lane; x0 < n; x0 += kAccFlush * kWave) {
-                    uint32_t id[kAccFlush], c[kAccFlush];
+        const int64_t claimed = scalar((int64_t)sh.claimed);
 #pragma unroll
-                    for (int u = 0; u < kAccFlush; ++u)
-                        id[u] = me.list[min(x0 + u * kWave, n - 1u)];
-#pragma unroll
-                    for (int u = 0; u < kAccFlush; ++u)
-                        c[u] = cnt16[id[u]];
-#pragma unroll
-                    for (int u = 0; u < kAccFlush; ++u)
-                        if (x0 + u * kWave < n)
-                            out[listed + x0 + u * kWave] = (part_id + id[u]) << 16 | c[u];
-                }
+        for (int q = 0; q < PARTS; ++q) {
+            if (q >= parts)
+                continue;
+            const int64_t base = claimed + (uint32_t)__builtin_amdgcn_readlane((int)sums, wave * parts + q) - part_c[q];
+            if (lane == 0) {
+                const int64_t part = (int64_t)blk * kWinParts + part0 + q;
+                a.part_base[part] = base;
+                a.part_cnt[part] = part_c[q];
+                a.part_wt[part] = part_w[q];
             }
-            __builtin_amdgcn_wave_barrier();
-            uint4 *part4 = reinterpret_cast<uint4 *>(cnt + wave * kWaveWords) + lane_now;
+            if (part_c[q] == 0)
+                continue;
+            uint32_t *__restrict__ out = a.tmp_ent + base;
+            const uint16_t *cnt16 = reinterpret_cast<const uint16_t *>(wave4);
+            const uint8_t *cnt8 = reinterpret_cast<const uint8_t *>(wave4 + q * (kPartIds / 16));
+            const uint32_t part_id = (part0 + q) * kPartIds;
+            const int lanes = lanes_of(q);
+            for (int lane0 = 0; lane0 < kWave; lane0 += lanes) {
+                const uint32_t listed = lane0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto[q], lane0 - 1) : 0u;
+                const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto[q], lane0 + lanes - 1) - listed;
+                if (lane0 || q)
+                    list_up(q, lane0, listed);
+                auto leave = [&](auto *counters) {
+                    for (uint32_t x0 = lane; x0 < n; x0 += kAccFlush * kWave) {
+                        uint32_t id[kAccFlush], c[kAccFlush];
 #pragma unroll
-            for (int it = 0; it < kQuads; ++it) // the next pair begins at zero
-                part4[it * kWave] = make_uint4(0, 0, 0, 0);
+                        for (int u = 0; u < kAccFlush; ++u)
+                            id[u] = me.list[min(x0 + u * kWave, n - 1u)];
+#pragma unroll
+                        for (int u = 0; u < kAccFlush; ++u)
+                            c[u] = counters[id[u]];
+#pragma unroll
+                        for (int u = 0; u < kAccFlush; ++u)
+                            if (x0 + u * kWave < n)
+                                out[listed + x0 + u * kWave] = (part_id + id[u]) << 16 | c[u];
+                    }
+                };
+                if (bytes)
+                    leave(cnt8);
+                else
+                    leave(cnt16);
+            }
         }
+        __builtin_amdgcn_wave_barrier();
+        clear(); // the next pair begins at zero
         ask(s0); // of the next pair
         __syncthreads();
         blk = blk_next;
@@ -1597,13 +1707,6 @@ __global__ __launch_bounds__(kLwRows) void ldw_extract_place_kernel(LwHop a, Loo
 // ---------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------
-size_t ldw_accumulate_lds_bytes()
-{
-    return (size_t)kWinWords * sizeof(uint32_t) + sizeof(AccShared);
-}
-
-static_assert((size_t)kWinWords * sizeof(uint32_t) + sizeof(AccShared) <= 160 * 1024, "does not fit a compute unit");
-
 static void launch_ldw_tiles(const Launch &L, const LwHop &a)
 {
     hipLaunchKernelGGL(ldw_plan_kernel, dim3(1), dim3(1024), 0, L.stream, a);
@@ -1645,20 +1748,25 @@ void launch_ldw_index(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
 
-int launch_ldw_accumulate(const Launch &L, const LwHop &a)
+template <bool NARROW>
+static int launch_accumulate(const Launch &L, const LwHop &a)
 {
-    void (*const kernels[2])(LwHop) = {ldw_accumulate_kernel<false>, ldw_accumulate_kernel<true>};
-    static bool attr_set = false;
-    if (!attr_set) {
-        for (auto *kernel : kernels)
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)ldw_accumulate_lds_bytes()) != hipSuccess)
-                (void)hipGetLastError(); // not required on every runtime; the launch below reports real failures
-        attr_set = true;
-    }
-    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, (int64_t)a.k * a.nwin, 1)), dim3(kAccThreads),
-                       ldw_accumulate_lds_bytes(), L.stream, a);
+    void (*const kernels[2])(LwHop) = {ldw_accumulate_kernel<false, NARROW>, ldw_accumulate_kernel<true, NARROW>};
+    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, (int64_t)a.k * a.nwin, NARROW ? 2 : 1)), dim3(kAccThreads<NARROW>),
+                       0, L.stream, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Counters of 8 bits where there are pairs for two workgroups per compute unit and few of them will be counted three times.
+// `most`: the largest counter that is to be expected, a number that is off by up to 2 either way.  Whole calls of two layers, 16 and
+// 8 bits: 266 pairs, 40 expected: 144 and 133 us; 320, 244: 234 and 208; 1064, 223: 279 and 268; 532, 462 (2 pairs overflow): 256 and
+// 255; 920, 318 (12 overflow): 437 and 453; 532, 887 (92 overflow): 370 and 407.  With many pairs for every workgroup the few that
+// overflow cost less: three layers, 8512 pairs, 325 expected (35 overflow): 3000 and 2820.
+int launch_ldw_accumulate(const Launch &L, const LwHop &a, double most)
+{
+    const int64_t pairs = (int64_t)a.k * a.nwin;
+    const bool narrow = pairs > L.num_cu && most <= (pairs >= 8 * L.num_cu ? 384.0 : 256.0);
+    return narrow ? launch_accumulate<true>(L, a) : launch_accumulate<false>(L, a);
 }
 
 bool ldw_may_place(const LwHop &a) { return ldw_fused(a) && (int64_t)a.k * a.nwin <= kMostPlacedPairs; }

@@ -300,3 +300,26 @@ def test_draws_through_sums_of_blocks_and_groups(mods, n, degree, squared):
     batches = np.array([[0, 1, 2], [3, 4, 5], [0, 3, 4]], dtype=np.int32)
     for s in ((700,), (2048,), (4096,)):
         _run_both(mods, rowptr, col, batches, s, 5, mb_base=2, squared=squared)
+
+
+# 64 x 4 (minibatch, window) pairs count in 16 bits, 65 x 4 in 8; vertices that reach 8 bits' limit, pass it and wrap round to 0, in every
+# place of a counter word, at the ends of both halves of a window, beside one another and alone
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("k,b", [(64, 600), (65, 255), (65, 256), (65, 600)])
+def test_counters_of_8_bits(mods, k, b, squared):
+    rng = np.random.default_rng(k + b)
+    n = 200_000
+    rows = {255: (0, 32767, 65535, 65539), 256: (65536, 65537, 98307, 131070), 257: (98303, 98304, 131071), 512: (131074, 131075),
+            600: (196607, 196608, 199999)}
+    lists = []
+    for t in range(b):          # neighbours of a minibatch's seed t
+        lists.append([v for count, ids in rows.items() if t < count for v in ids])
+    col, rowptr = [], np.zeros(n + 1, dtype=np.int64)
+    for v in range(n):
+        own = set(rng.integers(0, n, 2).tolist())
+        if v < k * b:
+            own |= set(lists[v % b])
+        col.append(np.array(sorted(own), dtype=np.int32))
+        rowptr[v + 1] = rowptr[v] + len(own)
+    batches = np.arange(k * b, dtype=np.int32).reshape(k, b)
+    _run_both(mods, rowptr, np.concatenate(col), batches, (300, 40), 7, squared=squared)
