@@ -14,7 +14,7 @@ constexpr int kChunkLines = 256;   // lines ranked by one workgroup (131072 vert
 // T in device memory.  A pointer that was computed as a number, or comes from LDS, is not known to lead there: its loads count as
 // accesses of LDS too, and every later access of LDS waits for all of them.
 template <class T>
-using InMemory = __attribute__((address_space(1))) T;
+using Global = __attribute__((address_space(1))) T;
 using U32x4 = uint32_t __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------------

@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
                         const AccPiece rec = me.piece[mine];
                         const uint32_t x = u0 + j0 + u * kWave; // the lane's chunk, from origin
                         const int from = max(rec.lo - (int)(4 * x), 0), to = min(rec.hi - (int)(4 * x), 4); // its entries in the piece
-                        s.v[u] = *reinterpret_cast<const InMemory<U32x4> *>(rec.origin + (int64_t)x * 16);
+                        s.v[u] = *reinterpret_cast<const Global<U32x4> *>(rec.origin + (int64_t)x * 16);
                         s.keep |= ((1u << to) - (1u << from)) << (4 * u);
                     }
                 }
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
         if (tid == 0 && pair_c) {
             unsigned long long *cursor = a.cursor;
             asm volatile("" : "+v"(cursor)); // (an address known to be the same in all lanes has the wave wait for the answer here)
-            claim = __hip_atomic_fetch_add((InMemory<unsigned long long> *)cursor, (unsigned long long)pair_c, __ATOMIC_RELAXED,
+            claim = __hip_atomic_fetch_add((Global<unsigned long long> *)cursor, (unsigned long long)pair_c, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
         }
         const int half_now = half;
@@ -1354,9 +1354,19 @@ __global__ __launch_bounds__(256) void ldw_sel_copy_kernel(LwHop a)
 // ---------------------------------------------------------------------------------------------
 // EXTRACT: blockIdx.y = minibatch; the workgroups of a minibatch share its tiles wave by wave
 // ---------------------------------------------------------------------------------------------
-// Hash of a column: its leading bits index the filter bitmap (2^17 bits, 16 KB: with 2048 sampled columns about 1.5 % of the
-// neighbours pass; 2^16 above that, so that two workgroups fit a compute unit), its low ones the table (load factor <= 1/2).
-__device__ inline uint32_t ldw_hash(uint32_t v, int filter_bits) { return (v * 0x9E3779B1u) >> (32 - filter_bits); }
+// Hash of a column: its leading bits are a word of the filter (2^17 bits, 16 KB; 2^16 above 2048 sampled columns, so that two
+// workgroups fit a compute unit) and one bit in it, five bits further down another one (with one bit 1.5 % of the neighbours passed,
+// 2048 columns sampled, with two 0.25); its low ones are the place in the table (load factor <= 1/2).
+// (A product of the last 24 bits is one step of the vector unit, of all 32 it is four; ids that differ further up only share a place.)
+__device__ inline uint32_t ldw_hash(uint32_t v) { return (v & 0xFFFFFFu) * 0x9E3779u; }
+__device__ inline uint32_t ldw_slot(uint32_t v, int32_t slots) { return (ldw_hash(v) >> 15) & (uint32_t)(slots - 1); }
+struct FilterPlace {
+    uint32_t word, bit, bit2;
+};
+__device__ inline FilterPlace ldw_filter(uint32_t hash, int filter_bits)
+{
+    return {hash >> (37 - filter_bits), (hash >> (32 - filter_bits)) & 31u, (hash >> (27 - filter_bits)) & 31u};
+}
 
 // A wave takes the positions of its tile 512 at a time, whatever rows they lie in: a row list of 64 rows at a time is held
 // across the lanes, and where it matters (a step with more than one row) the row of a position follows from counting row
@@ -1365,6 +1375,9 @@ __device__ inline uint32_t ldw_hash(uint32_t v, int filter_bits) { return (v * 0
 // Two workgroups per compute unit leave 64 registers.  The tile, its rows and what else a wave's lanes have in common are scalar;
 // in every lane they cost 12 registers more, which went to memory and back (0.6 of 2.6 GB on 64 x 1024 seeds of 8.7 M vertices; 32 x
 // 512 seeds, 3 layers of 512 of 2.4 M vertices: 86 us with, 69 us without).
+// 64 x 1024 seeds of 8.7 M vertices, 237 M neighbours in a hop: 247 us with one bit of the filter per column, 221 with two; without
+// whatever follows the filter it is 195 (4.9 TB/s), and a shorter filter step alone (29 -> 17 instructions per neighbour and lane) changed
+// nothing.
 struct ExtWave {
     int64_t shift[kWave];     // by rank among the list's rows with neighbours: A_col index of tile position 0 if it lay in the row
     uint32_t starts[kStreamUnroll * 2]; // one bit per position of a step: a row starts there
@@ -1378,9 +1391,9 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
 {
     extern __shared__ int64_t ext_lds[];
     ExtWave *waves = reinterpret_cast<ExtWave *>(ext_lds);
-    uint32_t *hkey = reinterpret_cast<uint32_t *>(waves + kExtWaves); // [slots]
-    uint32_t *maybe = hkey + slots;                                   // bit h set: some sampled column hashes to h
-    uint16_t *hval = reinterpret_cast<uint16_t *>(maybe + (1 << filter_bits) / 32); // [slots]
+    uint32_t *maybe = reinterpret_cast<uint32_t *>(waves + kExtWaves); // the filter: ldw_filter's bits of the sampled columns
+    uint32_t *hkey = maybe + (1 << filter_bits) / 32;                  // [slots]
+    uint16_t *hval = reinterpret_cast<uint16_t *>(hkey + slots);       // [slots]
     if (a.giveup && *a.giveup)
         return;
     const int i = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -1397,9 +1410,10 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
         maybe[x] = 0;
     __syncthreads();
     for (int j = tid; j < ns; j += kExtThreads) {
-        const uint32_t v = (uint32_t)a.col_vertex[c0 + j], h = ldw_hash(v, filter_bits);
-        atomicOr(&maybe[h >> 5], 1u << (h & 31u));
-        uint32_t slot = h & (uint32_t)(slots - 1);
+        const uint32_t v = (uint32_t)a.col_vertex[c0 + j];
+        const FilterPlace f = ldw_filter(ldw_hash(v), filter_bits);
+        atomicOr(&maybe[f.word], 1u << f.bit | 1u << f.bit2);
+        uint32_t slot = ldw_slot(v, slots);
         while (atomicCAS(&hkey[slot], kEmptySlot, v) != kEmptySlot)
             slot = (slot + 1) & (uint32_t)(slots - 1);
         hval[slot] = (uint16_t)j;
@@ -1451,7 +1465,7 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
                 const int rk = mine ? (int)me.queue_rank[lane] : -1;
                 int32_t local = -1;
                 if (mine) {
-                    uint32_t slot = ldw_hash(val, filter_bits) & (uint32_t)(slots - 1);
+                    uint32_t slot = ldw_slot(val, slots);
                     uint32_t kx;
                     while ((kx = hkey[slot]) != kEmptySlot) {
                         if (kx == val) {
@@ -1494,12 +1508,18 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
                 uint32_t v[kStreamUnroll];
                 uint32_t ranks[kStreamUnroll / 4] = {}; // 8 bits each
                 if (one) {
-                    const int32_t *__restrict__ from = a.A_col + (me.shift[rank0] + p) + lane;
+                    const int32_t *__restrict__ from = a.A_col + (scalar(me.shift[rank0]) + p);
+                    if (n == kStreamUnroll * kWave) {
 #pragma unroll
-                    for (int u = 0; u < kStreamUnroll; ++u) {
-                        v[u] = kEmptySlot;
-                        if (left > u * kWave)
-                            v[u] = (uint32_t)from[u * kWave];
+                        for (int u = 0; u < kStreamUnroll; ++u)
+                            v[u] = (uint32_t)from[lane + u * kWave];
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < kStreamUnroll; ++u) {
+                            v[u] = 0;
+                            if (left > u * kWave)
+                                v[u] = (uint32_t)from[lane + u * kWave];
+                        }
                     }
                 } else {
                     __builtin_amdgcn_wave_barrier();
@@ -1514,28 +1534,30 @@ __global__ __launch_bounds__(kExtThreads, 8) void ldw_extract_kernel(LwHop a, in
                         const uint64_t m = reinterpret_cast<const uint64_t *>(me.starts)[u];
                         const int rk = rank0 + __popcll(m & below_incl);
                         rank0 += __popcll(m);
-                        v[u] = kEmptySlot;
+                        v[u] = 0;
                         if (left > u * kWave)
                             v[u] = (uint32_t)a.A_col[me.shift[rk] + (p + lane + u * kWave)];
                         ranks[u / 4] |= (uint32_t)rk << (8 * (u % 4));
                     }
                 }
-                // almost no neighbour is a sampled column: one bit per hash value answers "certainly not" for
+                // almost no neighbour is a sampled column: two bits of a word answer "certainly not" for
                 // nearly all of them with a single LDS read each (all of a step's reads in flight together).
                 // The few that pass are queued in row order; the table is searched a full wave of them at a
                 // time (and at the end of the row list), not step by step
                 uint32_t word[kStreamUnroll];
 #pragma unroll
                 for (int u = 0; u < kStreamUnroll; ++u)
-                    word[u] = maybe[ldw_hash(v[u], filter_bits) >> 5];
+                    word[u] = maybe[ldw_filter(ldw_hash(v[u]), filter_bits).word];
 #pragma unroll
                 for (int u = 0; u < kStreamUnroll; ++u) {
-                    const bool pass = v[u] != kEmptySlot && ((word[u] >> (ldw_hash(v[u], filter_bits) & 31u)) & 1u);
-                    const uint64_t pm = __ballot(pass);
+                    const int valid = n - u * kWave; // lanes
+                    const FilterPlace f = ldw_filter(ldw_hash(v[u]), filter_bits);
+                    const uint64_t pm = __ballot(((word[u] >> f.bit) & (word[u] >> f.bit2) & 1u) != 0u) &
+                                        (valid >= kWave ? ~0ull : valid > 0 ? (1ull << valid) - 1ull : 0ull);
                     if (pm == 0)
                         continue;
-                    if (pass) {
-                        const uint32_t at = qn + __popcll(pm & below);
+                    if (__builtin_amdgcn_inverse_ballot_w64(pm)) {
+                        const uint32_t at = qn + bits_below(pm);
                         me.queue[at] = v[u];
                         me.queue_rank[at] = (uint8_t)(one ? (uint32_t)rank0 : ranks[u / 4] >> (8 * (u % 4)));
                     }
