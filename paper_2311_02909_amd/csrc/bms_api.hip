@@ -1158,7 +1158,6 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         DedupArgs d{};
         bool counted = false;
         if (buckets && !ranges) {
-            BMS_TRY(csr->dd_pairs.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t)));
             BMS_TRY(csr->dd_utmp.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t)));
             // segments = id ranges of 2^cshift ids holding 1500..3000 sampled ids each on average (one workgroup ranks
             // up to 4096 in LDS; the longer a segment, the longer the runs the cut appends to it per tile),
@@ -1204,6 +1203,9 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             const size_t stride = (size_t)std::max<int64_t>(nbuckets, C);
             const size_t kC = (size_t)c.k * (size_t)C;
             const int64_t xtiles = nnz / kCutTile + c.k; // tiles of the cut
+            const size_t loc_at = ((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint32_t) + 127) / 128 * 128; // behind ids_seg
+            BMS_TRY(csr->dd_pairs.ensure(std::max((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t),
+                                                  C ? loc_at + (size_t)xtiles * kCutTile * sizeof(uint16_t) : 0)));
             BMS_TRY(csr->dd_uniq.ensure((size_t)c.k * stride * sizeof(uint32_t)));
             BMS_TRY(csr->dd_seg.ensure((3 * kC + (size_t)c.k + 16) * sizeof(uint32_t)));
             BMS_TRY(csr->dd_segcnt.ensure(std::max<size_t>(kC, 1) * sizeof(uint32_t)));
@@ -1251,10 +1253,10 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             d.seg_off = csr->dd_seg.as<uint32_t>();
             d.seg_cursor = d.seg_off + kC + c.k;
             d.big_list = d.seg_cursor + kC;
-            // the segment path keeps the ids grouped by segment and the per-position words in the first buffer,
+            // the segment path keeps the ids grouped by segment and the places of the cut in the first buffer,
             // the distinct ids and the 16-bit ranks in the second (the per-minibatch path uses both as 8-byte entries)
             d.ids_seg = csr->dd_pairs.as<uint32_t>();
-            d.loc = d.ids_seg + std::max<int64_t>(nnz, 1);
+            d.loc = reinterpret_cast<uint16_t *>(csr->dd_pairs.as<char>() + loc_at);
             d.uids = csr->dd_utmp.as<uint32_t>();
             d.ranks = reinterpret_cast<uint16_t *>(d.uids + std::max<int64_t>(nnz, 1));
             d.run_gpos = csr->dd_runs.as<uint32_t>();

@@ -235,7 +235,7 @@ struct DedupArgs {
     uint32_t *big_count; // device counter of big_list (the word after `fallback`)
     int32_t *fallback;   // device flag: a segment fits neither ranking kernel, the per-minibatch kernel takes the hop
     uint32_t *ids_seg;   // nnz: the sampled ids grouped by segment (minibatch i, segment c at mb_edgeoff[i] + seg_off[c])
-    uint32_t *loc;       // nnz, by position: segment << 14 | place inside the run its tile appended to that segment
+    uint16_t *loc;       // tiles * kCutTile, by position in the tile: its place in the tile's ids sorted by segment
     uint32_t *run_gpos;  // tiles * C: where the run of (tile, segment) starts inside the minibatch's part of ids_seg
     uint32_t *run_cnt;   // tiles * C: its length
     uint16_t *ranks;     // nnz, parallel to ids_seg: rank of the id among the distinct ids of its segment

@@ -245,11 +245,6 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
                 const uint32_t c = seg_of(a, tab_l, id[q]);
                 lpos[q] = (c << kLocShift) | atomicAdd(&cnt[c], 1u);
             }
-        uint32_t *__restrict__ loc = a.loc + e0;
-#pragma unroll
-        for (int q = 0; q < TILE / NT; ++q)
-            if (id[q] != 0xFFFFFFFFu)
-                loc[j0 + q * NT + tid] = lpos[q];
         __syncthreads();
         uint32_t *__restrict__ run_gpos = a.run_gpos + t * a.C, *__restrict__ run_cnt = a.run_cnt + t * a.C;
         for (int base = 0; base < a.C; base += NT) {
@@ -272,10 +267,14 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
                 carry_s = carry + total;
             __syncthreads();
         }
+        uint16_t *__restrict__ loc = a.loc + t * TILE;
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q)
-            if (id[q] != 0xFFFFFFFFu)
-                stage[off[lpos[q] >> kLocShift] + (lpos[q] & (TILE - 1))] = id[q];
+            if (id[q] != 0xFFFFFFFFu) {
+                const uint32_t at = off[lpos[q] >> kLocShift] + (lpos[q] & (TILE - 1));
+                stage[at] = id[q];
+                loc[q * NT + tid] = (uint16_t)at;
+            }
         __syncthreads();
         uint32_t *__restrict__ ids_seg = a.ids_seg + e0;
         for (uint32_t sidx = tid; sidx < jend - j0; sidx += NT) {
@@ -823,81 +822,87 @@ __global__ __launch_bounds__(256) void dd_base_scan_kernel(DedupArgs a, int64_t 
 template <int TILE, int NT>
 __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
 {
-    extern __shared__ uint32_t unsplit_lds[]; // stage[TILE]; then 3 C words: start in the tile, start in global - start in the tile, base
+    // stage[TILE]; a bit per place of the cut's order where a run begins; then, by rank among the tile's runs, 2 C words: start in
+    // global - start in the tile, base
+    extern __shared__ uint32_t unsplit_lds[];
     __shared__ uint32_t smem[NT / kWave];
     __shared__ uint32_t carry_s;
     if (*a.fallback)
         return;
-    uint32_t *stage = unsplit_lds;
-    uint32_t *off = unsplit_lds + TILE, *delta = off + a.C, *base_l = off + 2 * a.C;
+    static_assert(TILE <= 1 << 16 && TILE / kWave == 2 * kWave, "two words of 64 places per lane");
+    uint32_t *stage = unsplit_lds, *starts = unsplit_lds + TILE;
+    uint32_t *delta = starts + TILE / 32, *base_l = delta + a.C;
     const int64_t ntiles = tileoff[a.k];
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid)); // (places: computed anew for every tile, not kept in registers)
+        __builtin_assume(tid < NT);
+        const uint32_t lane = tid & (kWave - 1), wave = scalar(tid / kWave);
         const int i = locate_segment(tileoff, a.k, t);
         const int64_t e0 = a.mb_edgeoff[i];
         const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
         const uint32_t j0 = (uint32_t)(t - tileoff[i]) * TILE;
-        const uint32_t jend = (j0 + TILE < N) ? j0 + TILE : N;
-        const uint32_t *__restrict__ loc = a.loc + e0;
-        uint32_t lc[TILE / NT];
+        const int n = (int)scalar(min(N - j0, (uint32_t)TILE));
+        int left = n - (int)tid;
+        const uint16_t *__restrict__ loc = a.loc + scalar(t) * TILE;
+        uint32_t place[TILE / NT]; // in the cut's order; later the run that has place q NT + tid, in the upper half
 #pragma unroll
-        for (int q = 0; q < TILE / NT; ++q) {
-            const uint32_t j = j0 + q * NT + tid;
-            lc[q] = j < jend ? loc[j] : 0xFFFFFFFFu;
-        }
+        for (int q = 0; q < TILE / NT; ++q)
+            place[q] = left > q * NT ? (loc + q * NT)[tid] : 0;
         if (tid == 0)
             carry_s = 0;
+        if (tid < TILE / 32)
+            starts[tid] = 0;
         __syncthreads();
         const uint32_t *__restrict__ run_gpos = a.run_gpos + t * a.C, *__restrict__ run_cnt = a.run_cnt + t * a.C;
         for (int base = 0; base < a.C; base += NT) {
             const int c = base + (int)tid;
             const uint32_t v = c < a.C ? run_cnt[c] : 0u;
+            const uint32_t one = v ? 1u << 16 | v : 0u; // runs and entries (the last run's sum does not count)
             uint32_t total;
-            const uint32_t ex = block_exclusive_scan<uint32_t, NT>(v, smem, total);
-            const uint32_t carry = carry_s;
-            if (c < a.C) {
-                off[c] = carry + ex;
-                delta[c] = run_gpos[c] - (carry + ex);
-                base_l[c] = a.bin_base[(int64_t)i * a.stride + c];
+            const uint32_t ex = carry_s + block_exclusive_scan<uint32_t, NT>(one, smem, total);
+            if (v) {
+                const uint32_t rank = ex >> 16, off = ex & 0xFFFFu;
+                delta[rank] = run_gpos[c] - off;
+                base_l[rank] = a.bin_base[(int64_t)i * a.stride + c];
+                atomicOr(&starts[off >> 5], 1u << (off & 31u));
             }
             __syncthreads();
             if (tid == 0)
-                carry_s = carry + total;
+                carry_s += total;
             __syncthreads();
         }
-#pragma unroll
-        for (int q = 0; q < TILE / NT; ++q)
-            if (lc[q] != 0xFFFFFFFFu) {
-                const uint32_t c = lc[q] >> kLocShift;
-                stage[off[c] + (lc[q] & (TILE - 1))] = (c << kLocShift) | (uint32_t)(q * NT + tid);
-            }
-        __syncthreads();
-        // all of a thread's rank loads in flight; the columns then take the places of what was staged
-        const uint16_t *__restrict__ ranks = a.ranks + e0;
+        // runs that begin before each word of 64 places: every wave for itself, word x in lane x, word x + 64 in its upper half
+        const uint64_t *words = reinterpret_cast<const uint64_t *>(starts);
+        const uint64_t low = words[lane], high = words[lane + kWave];
+        const uint32_t low_c = __popcll(low), high_c = __popcll(high);
+        const uint32_t low_upto = wave_inclusive_scan_dpp(low_c);
+        const uint32_t high_upto = wave_inclusive_scan_dpp(high_c) + (uint32_t)__builtin_amdgcn_readlane((int)low_upto, kWave - 1);
+        const uint16_t *__restrict__ ranks = a.ranks + scalar(e0);
         uint32_t r[TILE / NT];
 #pragma unroll
-        for (int q = 0; q < TILE / NT; ++q) {
-            const uint32_t sidx = q * NT + tid;
-            r[q] = sidx < jend - j0 ? ranks[delta[stage[sidx] >> kLocShift] + sidx] : 0;
+        for (int q = 0; q < TILE / NT; ++q) { // all of a thread's rank loads in flight
+            const int word = q * (NT / kWave) + (int)wave;
+            const int of = word & (kWave - 1);
+            if (q % 4 == 0)
+                asm volatile("" : "+v"(tid), "+v"(left) : : "memory"); // (four at a time: all of their places at once do not fit the registers)
+            const bool upper = q * (NT / kWave) >= kWave;
+            const uint64_t m = (uint64_t)lane_value((int64_t)(upper ? high : low), of);
+            const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(upper ? high_upto - high_c : low_upto - low_c), of);
+            const uint32_t run = before + (uint32_t)(m & 1u) + bits_below(m >> 1) - 1u;
+            r[q] = left > q * NT ? ranks[delta[run] + q * NT + tid] : 0;
+            place[q] |= run << 16;
         }
-        asm volatile("" ::: "memory"); // (what was staged is read again: held in registers beside the ranks it spills)
-#pragma unroll
-        for (int q = 0; q < TILE / NT; ++q) {
-            const uint32_t sidx = q * NT + tid;
-            lc[q] = sidx < jend - j0 ? stage[sidx] : 0xFFFFFFFFu;
-            if (lc[q] != 0xFFFFFFFFu)
-                r[q] += base_l[lc[q] >> kLocShift];
-        }
-        __syncthreads();
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q)
-            if (lc[q] != 0xFFFFFFFFu)
-                stage[lc[q] & (TILE - 1)] = r[q];
+            if (left > q * NT)
+                stage[q * NT + tid] = r[q] + base_l[place[q] >> 16];
         __syncthreads();
-        int32_t *__restrict__ col = a.col + e0 + j0;
-        for (uint32_t idx = tid; idx < jend - j0; idx += NT)
-            col[idx] = (int32_t)stage[idx];
+        int32_t *__restrict__ col = a.col + scalar(e0 + j0);
+#pragma unroll
+        for (int q = 0; q < TILE / NT; ++q)
+            if (left > q * NT)
+                (col + q * NT)[tid] = (int32_t)stage[place[q] & 0xFFFFu];
         __syncthreads();
     }
 }
@@ -1070,11 +1075,11 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
 void launch_nw_dedup_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
 {
     static bool attr_set = false;
-    const size_t lds = (size_t)kCutTile * sizeof(uint32_t) + (3 * (size_t)a.C + 1) * sizeof(uint32_t);
+    const size_t lds = (size_t)kCutTile * sizeof(uint32_t) + kCutTile / 8 + 2 * (size_t)a.C * sizeof(uint32_t);
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(dd_unsplit_kernel<kCutTile, 512>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(kCutTile * sizeof(uint32_t) + (3 * kMaxSegments + 1) * sizeof(uint32_t))) != hipSuccess)
+                                (int)(kCutTile * sizeof(uint32_t) + kCutTile / 8 + 2 * kMaxSegments * sizeof(uint32_t))) != hipSuccess)
             (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
         attr_set = true;
     }
