@@ -1202,7 +1202,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             }
             const size_t stride = (size_t)std::max<int64_t>(nbuckets, C);
             const size_t kC = (size_t)c.k * (size_t)C;
-            const int64_t xtiles = nnz / kCutTile + c.k; // tiles of the cut
+            const int64_t xtiles = cut_tiles_bound(nnz, c.k);
             const size_t loc_at = ((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint32_t) + 127) / 128 * 128; // behind ids_seg
             BMS_TRY(csr->dd_pairs.ensure(std::max((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t),
                                                   C ? loc_at + (size_t)xtiles * kCutTile * sizeof(uint16_t) : 0)));

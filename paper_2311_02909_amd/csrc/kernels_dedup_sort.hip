@@ -32,6 +32,20 @@ namespace bms {
 constexpr int kLocShift = 13; // bits of the place inside a run (a tile holds 2^13 positions)
 static_assert(kCutTile == (1 << kLocShift) && kMaxSegments <= (1 << (32 - kLocShift)), "loc word out of step");
 
+// Tiles of a minibatch's N positions, which begin at e0 of the stacked columns: all but the first one begin at a memory line (of an
+// array that does), so that a tile's columns are read and written by whole lines.
+constexpr int kLineEntries = 32;
+__device__ inline int64_t cut_tiles(int64_t e0, int64_t N)
+{
+    return N ? (N + (e0 & (kLineEntries - 1)) + kCutTile - 1) / kCutTile : 0;
+}
+__device__ inline void cut_tile(int64_t e0, uint32_t N, uint32_t x, uint32_t &j0, uint32_t &jend) // tile x: positions j0 .. jend
+{
+    const uint32_t head = (uint32_t)e0 & (kLineEntries - 1);
+    j0 = x ? x * kCutTile - head : 0;
+    jend = (uint32_t)min<uint64_t>((uint64_t)(x + 1) * kCutTile - head, N);
+}
+
 // The table of segments of unequal width, copied to LDS by the kernels that look ids up (tab_l: kMaxCells + 1 entries).
 __device__ inline void load_seg_table(const DedupArgs &a, uint16_t *tab_l, int nthreads)
 {
@@ -70,7 +84,8 @@ __global__ __launch_bounds__(NT) void dd_count_kernel(DedupArgs a, const int64_t
         const int i = locate_segment(tileoff, a.k, t);
         const int64_t e0 = a.mb_edgeoff[i];
         const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
-        const uint32_t j0 = (uint32_t)(t - tileoff[i]) * TILE;
+        uint32_t j0, jend;
+        cut_tile(e0, N, (uint32_t)(t - tileoff[i]), j0, jend);
         const int32_t *__restrict__ col = a.col + e0;
         for (int c = tid; c < a.C; c += NT)
             hist[c] = 0;
@@ -79,7 +94,7 @@ __global__ __launch_bounds__(NT) void dd_count_kernel(DedupArgs a, const int64_t
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q) {
             const uint32_t j = j0 + q * NT + tid;
-            g[q] = (j < N && j < j0 + TILE) ? (uint32_t)col[j] : 0xFFFFFFFFu;
+            g[q] = j < jend ? (uint32_t)col[j] : 0xFFFFFFFFu;
         }
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q)
@@ -181,7 +196,7 @@ __global__ __launch_bounds__(256) void dd_plan_kernel(DedupArgs a, const int64_t
             a.mb_edgeoff[i] = e0;
             if (i == a.k - 1)
                 a.mb_edgeoff[a.k] = e1;
-            cnt = (e1 - e0 + kCutTile - 1) / kCutTile;
+            cnt = cut_tiles(e0, e1 - e0);
         }
         int64_t total;
         const int64_t ex = block_exclusive_scan<int64_t, 256>(cnt, smem64, total);
@@ -224,8 +239,8 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
         const int i = locate_segment(tileoff, a.k, t);
         const int64_t e0 = a.mb_edgeoff[i];
         const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
-        const uint32_t j0 = (uint32_t)(t - tileoff[i]) * TILE;
-        const uint32_t jend = (j0 + TILE < N) ? j0 + TILE : N;
+        uint32_t j0, jend;
+        cut_tile(e0, N, (uint32_t)(t - tileoff[i]), j0, jend);
         const int32_t *__restrict__ col = a.col + e0;
         for (int c = tid; c < a.C; c += NT)
             cnt[c] = 0;
@@ -841,8 +856,9 @@ __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const in
         const int i = locate_segment(tileoff, a.k, t);
         const int64_t e0 = a.mb_edgeoff[i];
         const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
-        const uint32_t j0 = (uint32_t)(t - tileoff[i]) * TILE;
-        const int n = (int)scalar(min(N - j0, (uint32_t)TILE));
+        uint32_t j0, jend;
+        cut_tile(e0, N, (uint32_t)(t - tileoff[i]), j0, jend);
+        const int n = (int)scalar(jend - j0);
         int left = n - (int)tid;
         const uint16_t *__restrict__ loc = a.loc + scalar(t) * TILE;
         uint32_t place[TILE / NT]; // in the cut's order; later the run that has place q NT + tid, in the upper half
@@ -1019,7 +1035,7 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
                                 uint32_t *done, int64_t nnz, bool counted, const StageMark &mark)
 {
     mark("dd_plan");
-    const int64_t tiles = nnz / kCutTile + a.k;
+    const int64_t tiles = cut_tiles_bound(nnz, a.k);
     hipLaunchKernelGGL(dd_plan_kernel, dim3(a.k + 1), dim3(256), 0, L.stream, a, out_rowptr, mb_rowoff, counted ? 1 : 0);
     if (!counted) {
         hipLaunchKernelGGL((dd_count_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, 4)), dim3(512), 0, L.stream, a,
@@ -1083,7 +1099,7 @@ void launch_nw_dedup_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
             (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
         attr_set = true;
     }
-    const int64_t tiles = nnz / kCutTile + a.k;
+    const int64_t tiles = cut_tiles_bound(nnz, a.k);
     hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, 4)), dim3(512), lds, L.stream, a,
                        a.big_tileoff);
 }
