@@ -568,6 +568,19 @@ int next_lookback(CallCtx &c, Lookback &lb)
 }
 void lookback_used(CallCtx &c, uint32_t workgroups) { c.csr->lb_taken += workgroups; }
 
+// launch_scan_i64 with the handle's words for sums over workgroups
+int scan_i64(CallCtx &c, int64_t *vals, const int64_t *count, int64_t *total_out, int64_t *tail_ptr, const int64_t *tail_idx, int64_t count_bound)
+{
+    if (scan_i64_by_lookback(count_bound)) {
+        Lookback lb{};
+        BMS_TRY(next_lookback(c, lb));
+        lookback_used(c, launch_scan_i64_lookback(c.launch, vals, count, total_out, tail_ptr, tail_idx, count_bound, lb));
+    } else {
+        launch_scan_i64(c.launch, vals, count, total_out, tail_ptr, tail_idx, count_bound);
+    }
+    return BMS_OK;
+}
+
 // Copies the seeds into hop 0's row_vertex, builds mb_rowoff = i*b and verifies the seeds; tileoff (without a vertex set): the
 // hop's row tiles as well.
 int stage_seeds(CallCtx &c, const int32_t *batches, Profiler &prof, bool use_vset = true, int64_t *tileoff = nullptr)
@@ -1125,8 +1138,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         // nw_strip_self do): the sampling kernel does it
         a.sum_tiles = no_wait && tiles_bound <= kMostSummedTiles && buckets && !self_in_rows && !staged_by(c, BMS_PROFILE | BMS_PROFILE_MAIN);
         if (!a.sum_tiles)
-            launch_scan_i64(c.launch, a.tile_off, a.mb_tileoff + c.k, slot(c, h, 0), a.out_rowptr, mb_rowoff + c.k,
-                            rows_bound / kRowTile + c.k);
+            BMS_TRY(scan_i64(c, a.tile_off, a.mb_tileoff + c.k, slot(c, h, 0), a.out_rowptr, mb_rowoff + c.k, rows_bound / kRowTile + c.k));
         BMS_TRY(prof.end());
 
         // nnz sizes the column buffers: read back (the only host round trip of the hop), or in the
@@ -1710,7 +1722,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
             nnz = std::min<int64_t>(nnz, with_margin(c.res->hint_nnz[h]));
         const bool placed = (no_wait || nnz <= kNoWaitEntries) && (rows_bound + 255) / 256 <= kMostLookback; // scan and copy in one
         if (!placed)
-            launch_scan_i64(c.launch, w.out_rowptr, mb_rowoff + c.k, slot(c, h, 0), nullptr, nullptr, rows_bound);
+            BMS_TRY(scan_i64(c, w.out_rowptr, mb_rowoff + c.k, slot(c, h, 0), nullptr, nullptr, rows_bound));
         BMS_TRY(prof.end());
         if (!no_wait && nnz > kNoWaitEntries) {
             BMS_TRY(read_scalars(c));

@@ -63,6 +63,11 @@ void launch_plan_tiles3(const Launch &, const int64_t *seg_off, int32_t k, int32
 // long arrays are scanned by many workgroups when the launch context carries scratch for it
 void launch_scan_i64(const Launch &, int64_t *vals, const int64_t *count, int64_t *total_out, int64_t *tail_ptr,
                      const int64_t *tail_idx, int64_t count_bound = 0);
+struct Lookback; // bms_device.h
+// the same in one launch, where scan_i64_by_lookback says so; returns its workgroups
+bool scan_i64_by_lookback(int64_t count_bound);
+uint32_t launch_scan_i64_lookback(const Launch &, int64_t *vals, const int64_t *count, int64_t *total_out, int64_t *tail_ptr,
+                                  const int64_t *tail_idx, int64_t count_bound, const Lookback &);
 void launch_vset_rank(const Launch &, const VSet &, int32_t k, int64_t *mb_coloff /*k+1*/, int32_t *col_vertex,
                       int64_t *ncols_out);
 void launch_vset_clear(const Launch &, const VSet &, int32_t k, const int64_t *mb_coloff, const int32_t *col_vertex,
@@ -404,7 +409,6 @@ struct LwHop {
     int64_t *out_rowptr;       // rows+1
     int32_t *out_col;
 };
-struct Lookback; // bms_device.h
 // With the index, few enough minibatches and rows the rows kernel also leaves the rows' lists window-major, and the plan is made
 // behind the accumulation (by launch_ldw_win_scan or launch_ldw_p_copy); else launch_ldw_bounds does both, after the rows.
 bool ldw_fused(const LwHop &);

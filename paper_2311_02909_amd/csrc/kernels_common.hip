@@ -406,10 +406,54 @@ __global__ __launch_bounds__(1024) void scan_i64_add_self_kernel(int64_t *vals, 
     }
 }
 
+// The same in one launch: the chunks' workgroups add up those before them (sum_before).  A chunk per workgroup.
+__global__ __launch_bounds__(1024) void scan_i64_lookback_kernel(int64_t *vals, const int64_t *__restrict__ count, int64_t *total_out,
+                                                                 int64_t *tail_ptr, const int64_t *__restrict__ tail_idx, Lookback lb)
+{
+    __shared__ int64_t smem[16];
+    __shared__ uint32_t number_s;
+    const uint32_t c = scalar(take_number(lb, &number_s));
+    const int64_t m = *count;
+    if (c > 0 && (int64_t)c * 4096 >= m)
+        return; // nobody with values comes after
+    const int64_t i0 = (int64_t)c * 4096 + (int64_t)threadIdx.x * 4;
+    int64_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        v[q] = (i0 + q < m) ? vals[i0 + q] : 0;
+    int64_t total;
+    int64_t ex = block_exclusive_scan<int64_t, 1024>(v[0] + v[1] + v[2] + v[3], smem, total);
+    const int64_t before = sum_before<1024>(lb, c, total, smem);
+    ex += before;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (i0 + q < m)
+            vals[i0 + q] = ex;
+        ex += v[q];
+    }
+    if ((int64_t)(c + 1) * 4096 >= m && threadIdx.x == 0) {
+        vals[m] = before + total;
+        if (total_out)
+            *total_out = before + total;
+        if (tail_ptr)
+            tail_ptr[*tail_idx] = before + total;
+    }
+}
+
 __global__ void scan_i64_count_kernel(const int64_t *__restrict__ count, int64_t *nchunks_plus_one)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0)
         *nchunks_plus_one = (*count + 4095) / 4096 + 1;
+}
+
+bool scan_i64_by_lookback(int64_t count_bound) { return count_bound > 32768 && (count_bound + 4095) / 4096 <= kMostLookback; }
+
+uint32_t launch_scan_i64_lookback(const Launch &L, int64_t *vals, const int64_t *count, int64_t *total_out, int64_t *tail_ptr,
+                                  const int64_t *tail_idx, int64_t count_bound, const Lookback &lb)
+{
+    const uint32_t chunks = (uint32_t)((count_bound + 4095) / 4096);
+    hipLaunchKernelGGL(scan_i64_lookback_kernel, dim3(chunks), dim3(1024), 0, L.stream, vals, count, total_out, tail_ptr, tail_idx, lb);
+    return chunks;
 }
 
 void launch_scan_i64(const Launch &L, int64_t *vals, const int64_t *count, int64_t *total_out, int64_t *tail_ptr,
