@@ -834,7 +834,7 @@ __global__ __launch_bounds__(256) void dd_base_scan_kernel(DedupArgs a, int64_t 
 // LDS), and the tile's local column indices leave in position order.  Latency of the scattered short runs bounds it: all 16
 // ranks of a thread are in flight at once, and one stage used twice in place of two lets four workgroups of 63 registers share
 // a compute unit.  128 x 586 k ids: 299 us with two workgroups and four loads in flight, 170 now.
-template <int TILE, int NT>
+template <int TILE, int NT, bool PAST>
 __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
 {
     // stage[TILE]; a bit per place of the cut's order where a run begins; then, by rank among the tile's runs, 2 C words: start in
@@ -917,8 +917,13 @@ __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const in
         int32_t *__restrict__ col = a.col + scalar(e0 + j0);
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q)
-            if (left > q * NT)
-                (col + q * NT)[tid] = (int32_t)stage[place[q] & 0xFFFFu];
+            if (left > q * NT) {
+                const int32_t column = (int32_t)stage[place[q] & 0xFFFFu];
+                if (PAST) // a.past
+                    __builtin_nontemporal_store(column, (col + q * NT) + tid);
+                else
+                    (col + q * NT)[tid] = column;
+            }
         __syncthreads();
     }
 }
@@ -1088,20 +1093,29 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
     launch_nw_dedup_unsplit(L, a, nnz);
 }
 
-void launch_nw_dedup_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
+template <bool PAST>
+static void launch_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
 {
     static bool attr_set = false;
     const size_t lds = (size_t)kCutTile * sizeof(uint32_t) + kCutTile / 8 + 2 * (size_t)a.C * sizeof(uint32_t);
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(dd_unsplit_kernel<kCutTile, 512>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(dd_unsplit_kernel<kCutTile, 512, PAST>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(kCutTile * sizeof(uint32_t) + kCutTile / 8 + 2 * kMaxSegments * sizeof(uint32_t))) != hipSuccess)
             (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
         attr_set = true;
     }
     const int64_t tiles = cut_tiles_bound(nnz, a.k);
-    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, 4)), dim3(512), lds, L.stream, a,
+    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512, PAST>), dim3(grid_for(L, tiles, 4)), dim3(512), lds, L.stream, a,
                        a.big_tileoff);
+}
+
+void launch_nw_dedup_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
+{
+    if (a.past)
+        launch_unsplit<true>(L, a, nnz);
+    else
+        launch_unsplit<false>(L, a, nnz);
 }
 
 } // namespace bms
