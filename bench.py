@@ -33,40 +33,40 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 3_419_158_336,
-    ("dense_ladies", "ldw_p_copy"): 3_152_821_120,
-    ("dense_ladies", "ldw_extract"): 2_022_081_248,
-    ("dense_sage", "nw_sample"): 9_757_779_360,
-    ("dense_sage", "nw_rows"): 426_292_800,
-    ("dense_sage", "dd_split"): 1_121_317_184,
-    ("dense_sage", "dd_unsplit"): 992_679_648,
-    ("dense_sage", "dd_rank"): 845_933_664,
-    ("dense_sage", "dd_front"): 603_942_176,
-    ("large_sage", "nw_sample"): 5_021_728_960,
-    ("large_sage", "nw_rows"): 1_256_466_656,
-    ("large_sage", "dd_split"): 739_783_488,
-    ("large_sage", "dd_unsplit"): 674_898_880,
-    ("large_sage", "dd_rank"): 587_770_816,
-    ("large_sage", "dd_front"): 464_181_536,
-    ("mid_ladies", "ldw_p_copy"): 167_682_560,
-    ("mid_ladies", "ldw_accumulate"): 148_399_488,
-    ("mid_ladies", "ldw_extract"): 85_025_536,
-    ("mid_sage", "nw_sample"): 2_680_505_664,
-    ("mid_sage", "nw_rows"): 144_805_568,
-    ("mid_sage", "rg_lookup"): 330_158_624,
-    ("mid_sage", "rg_mark"): 190_080_576,
-    ("mid_sage", "rg_emit"): 150_483_616,
+    ("dense_ladies", "ldw_accumulate"): 3_495_973_568,
+    ("dense_ladies", "ldw_p_copy"): 3_086_191_104,
+    ("dense_ladies", "ldw_extract"): 2_023_595_648,
+    ("dense_sage", "nw_sample"): 9_810_059_648,
+    ("dense_sage", "nw_rows"): 430_223_904,
+    ("dense_sage", "dd_split"): 936_111_296,
+    ("dense_sage", "dd_unsplit"): 803_492_608,
+    ("dense_sage", "dd_rank"): 845_650_816,
+    ("dense_sage", "dd_front"): 603_900_544,
+    ("large_sage", "nw_sample"): 5_020_875_808,
+    ("large_sage", "nw_rows"): 1_260_488_512,
+    ("large_sage", "dd_split"): 620_035_968,
+    ("large_sage", "dd_unsplit"): 554_376_000,
+    ("large_sage", "dd_rank"): 587_241_280,
+    ("large_sage", "dd_front"): 464_209_056,
+    ("mid_ladies", "ldw_p_copy"): 164_266_560,
+    ("mid_ladies", "ldw_accumulate"): 143_446_656,
+    ("mid_ladies", "ldw_extract"): 85_302_624,
+    ("mid_sage", "nw_sample"): 1_568_832_032,
+    ("mid_sage", "nw_rows"): 144_791_456,
+    ("mid_sage", "rg_lookup"): 330_189_024,
+    ("mid_sage", "rg_mark"): 190_075_328,
+    ("mid_sage", "rg_emit"): 150_484_928,
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 9_399_476_096,
-    "dense_sage": 13_840_762_784,
-    "large_sage": 8_828_308_640,
-    "mid_ladies": 456_880_608,
-    "mid_sage": 3_529_696_384,
+    "dense_ladies": 9_421_415_360,
+    "dense_sage": 13_521_589_120,
+    "large_sage": 8_590_655_616,
+    "mid_ladies": 447_843_680,
+    "mid_sage": 2_417_672_352,
 }
 # the part of it that nw_sample reads, MB: the "read MB" of its launches in the same files
-NW_SAMPLE_READ_MB = {"dense_sage": 9255.1, "large_sage": 4693.0, "mid_sage": 2490.8}
+NW_SAMPLE_READ_MB = {"dense_sage": 9309.1, "large_sage": 4692.8, "mid_sage": 1380.0}
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 
 

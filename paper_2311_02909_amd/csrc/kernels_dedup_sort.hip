@@ -1,9 +1,9 @@
 // EXTRACT for the node-wise sampler, main path (Sec. 4.1.3: "remove empty columns"): every
 // minibatch's sampled ids are cut into C id ranges ("segments") small enough to be ranked inside
 // LDS, so that all random accesses of the dedup happen in LDS and global memory only sees
-// coalesced traffic.  Positions never travel with the ids: the cut remembers, per position, which
-// segment its id went to and where inside the run that its tile appended to that segment, so the
-// ranks come back along the same runs.  All kernels run on every compute unit, whatever the
+// coalesced traffic.  Positions never travel with the ids: the cut remembers, per position, its place
+// in the tile's ids sorted by segment, and per (tile, segment) where that run went, so the ranks come
+// back along the same runs.  All kernels run on every compute unit, whatever the
 // number of minibatches.
 //
 //   count    per tile of 8192 positions: LDS histogram over the C segments -> global counts
@@ -12,7 +12,7 @@
 //            narrow range) -- then these kernels do nothing and the per-minibatch kernel of
 //            kernels_dedup.hip does the hop instead
 //   split    per tile: counting sort by segment in LDS, every segment's run of ids appended to the
-//            segment with wide stores; per position (segment, place in run); per (tile, segment)
+//            segment with wide stores; per position its place in the tile's order; per (tile, segment)
 //            where the run went
 //   rank     per (minibatch, segment): a workgroup counts the segment's ids into buckets of about
 //            one id (LDS), every id compares itself with the few ids of its bucket, head bits and a
@@ -20,8 +20,8 @@
 //            ids are written in rank order at the head of the segment's slots
 //   bitmap   the listed segments: rank = set bits below the id in a bitmap of the segment's id range
 //   base     per minibatch: scan of the segments' distinct counts
-//   un-split per tile: the runs' ranks read back with wide loads, base of the segment added, scattered
-//            to their positions inside LDS, written out as the tile's local column indices
+//   un-split per tile: the runs' ranks read back with wide loads, base of the segment added in LDS, read
+//            from there by position, written out as the tile's local column indices
 #include "bms_device.h"
 #include "bms_internal.h"
 
@@ -829,11 +829,12 @@ __global__ __launch_bounds__(256) void dd_base_scan_kernel(DedupArgs a, int64_t 
 }
 
 // The cut in reverse: tile t appended, for every segment c, one run of ids to the segment; the ranks of those
-// ids lie at the same places.  Per tile: the runs' ranks are read back run by run (wide loads), the distinct
-// ids before the segment are added, the value goes to the position that put the id there (scatter inside
-// LDS), and the tile's local column indices leave in position order.  Latency of the scattered short runs bounds it: all 16
-// ranks of a thread are in flight at once, and one stage used twice in place of two lets four workgroups of 63 registers share
-// a compute unit.  128 x 586 k ids: 299 us with two workgroups and four loads in flight, 170 now.
+// ids lie at the same places.  Per tile: the runs' ranks are read back in the order of the cut (wide loads; the run of a place
+// follows from a bit per place where a run begins), the distinct ids before the segment are added, and every position reads its
+// column from the place that the cut left for it.  Memory and the latency of the scattered short runs bound it: all 16 ranks of a
+// thread are in flight at once, a run's number and a position's place share a register, so that four workgroups of 64 registers
+// share a compute unit.  128 x 586 k ids: 299 us with two workgroups and four loads in flight, 171 with four and a word of 32 bits
+// per position that scattered the ranks, 161 with 16 bits and one random access of LDS per entry, 137 since tiles begin at lines.
 template <int TILE, int NT, bool PAST>
 __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
 {

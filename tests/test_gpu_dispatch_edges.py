@@ -291,3 +291,38 @@ def test_wide_fanouts_by_the_rows_there_are(degree, b, s, wide):
     rows, entries, _ = res.sizes()[1]
     assert len(batches) * b * s > 65536 > rows and (entries < 900_000) == wide, (rows, entries)
     assert all(len(x) == 2 and ("wide" in x[1]) == wide for x in names), names
+
+
+# EXTRACT by segments: minibatches that begin anywhere in a memory line of 32 entries, of one tile of 8192 entries, a few more and a few
+# less, of several tiles and of none
+@pytest.mark.parametrize("variant", [{}, {"union_dst": True}], ids=lambda v: "+".join(v))
+def test_tiles_of_the_cut_at_memory_lines(variant):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(77)
+    n, b = 60_000, 40
+    sizes = [8192, 1, 8161, 8160, 0, 8192, 8193, 8191 + 31, 8192 + 31, 16384 - 7, 33, 16384 + 1, 31, 24576]
+    rows = []
+    for size in sizes:                  # the seeds of a minibatch have `size` neighbours together, all of them kept
+        parts = np.full(b, size // b)
+        parts[:size % b] += 1
+        rows += [np.sort(rng.choice(n, p, replace=False)) for p in parts]
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:len(rows) + 1] = np.cumsum([len(r) for r in rows])
+    rowptr[len(rows) + 1:] = rowptr[len(rows)]
+    col = np.concatenate(rows).astype(np.int32)
+    batches = np.arange(len(rows), dtype=np.int32).reshape(len(sizes), b)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, (1024,), 5, 0, **variant)
+    res = None
+    for call in range(2):
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (1024,), 5, extract="sort", recycle=res, **variant)
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+
+
+# more tiles of rows than one workgroup scans (32768), a chunk of 4096 and one more or less of them
+@pytest.mark.parametrize("k", [32768, 32769, 36864, 36865])
+def test_scans_over_many_tiles(k):
+    rng = np.random.default_rng(k)
+    rowptr, col = random_csr(3000, 6.0, rng)
+    _check(rowptr, col, random_batches(3000, k, 2, rng), (3, 2))

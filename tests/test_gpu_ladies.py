@@ -323,3 +323,26 @@ def test_counters_of_8_bits(mods, k, b, squared):
         rowptr[v + 1] = rowptr[v] + len(own)
     batches = np.arange(k * b, dtype=np.int32).reshape(k, b)
     _run_both(mods, rowptr, np.concatenate(col), batches, (300, 40), 7, squared=squared)
+
+
+# more than 2048 (minibatch, window) pairs: the copy of P by parts, which begin anywhere in a memory line and hold from no entry to a
+# few hundred; 512 workgroups take several pairs each, some of which are counted by halves (b = 300)
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("k,b,shared", [(520, 250, 60), (520, 300, 60), (513, 40, 0), (693, 17, 5)])
+def test_many_pairs(mods, k, b, shared, squared):
+    O, bms, _ = mods
+    rng = np.random.default_rng(k + b)
+    n = 200_000
+    common = rng.choice(n, shared, replace=False)
+    rows = [np.unique(np.concatenate([common, rng.integers(0, n, int(rng.integers(0, 120)))])) for _ in range(3 * b)]
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:len(rows) + 1] = np.cumsum([len(r) for r in rows])
+    rowptr[len(rows) + 1:] = rowptr[len(rows)]
+    col = np.concatenate(rows).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(2):       # the first call of a shape and a recycled one
+        batches = np.stack([rng.permutation(3 * b)[:b] for _ in range(k)]).astype(np.int32)
+        ref = O.sample_ladies(rowptr, col, batches, (50,), 11 + call, 0, squared)
+        res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (50,), 11 + call, squared=squared, recycle=res)
+        assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
