@@ -79,6 +79,7 @@ __device__ inline int32_t wave_replace_draws(volatile uint32_t *buf, uint64_t ke
 //            one part of the id range in all minibatches: a line that several minibatches need is fetched once and is in the
 //            die's own cache when the next one asks.
 constexpr int kDies = 8;
+static_assert(kDies == 1 << 3, "die_bits");
 struct TileWalk {
     int32_t k, i, step_i, left; // i: minibatch
     int64_t j, most, step_j;
@@ -87,14 +88,23 @@ struct TileWalk {
     __device__ TileWalk(const NwHop &a, uint32_t part, uint32_t parts, bool by_dies)
         : k(a.k), most(uniform_load(a.mb_tileoff + a.k + 1)), spread(by_dies && most < 65536) // (larger ones: tile q in step q)
     {
-        const uint32_t dies = by_dies ? kDies : 1;
-        const int64_t items = most * k, per = (items + dies - 1) / dies;
-        const int64_t lo = (blockIdx.x % dies) * per, hi = min<int64_t>(lo + per, items);
-        const int64_t pos = lo + (blockIdx.x / dies) * parts + part;
-        const int32_t step = gridDim.x / dies * parts;
-        left = pos < hi ? (int32_t)((hi - pos + step - 1) / step) : 0;
-        i = (int32_t)(pos % k);
-        j = pos / k;
+        const int die_bits = by_dies ? 3 : 0;
+        const uint32_t dies = 1u << die_bits;
+        const int64_t items = most * k, per = (items + dies - 1) >> die_bits;
+        const int64_t lo = (blockIdx.x & (dies - 1)) * per, hi = min<int64_t>(lo + per, items);
+        const int64_t pos = lo + (blockIdx.x >> die_bits) * parts + part;
+        const int32_t step = (gridDim.x >> die_bits) * parts;
+        left = 0;
+        if (pos < hi && hi >> 31 == 0) { // (divisions of 64 bits are half a microsecond at the start of a workgroup)
+            left = (int32_t)((uint32_t)(hi - pos + step - 1) / (uint32_t)step);
+            j = (uint32_t)pos / (uint32_t)k;
+            i = (int32_t)((uint32_t)pos - (uint32_t)j * (uint32_t)k);
+        } else {
+            if (pos < hi)
+                left = (int32_t)((hi - pos + step - 1) / step);
+            i = (int32_t)(pos % k);
+            j = pos / k;
+        }
         step_i = step % k;
         step_j = step / k;
     }
