@@ -840,7 +840,7 @@ __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const in
 {
     // stage[TILE]; a bit per place of the cut's order where a run begins; then, by rank among the tile's runs, 2 C words: start in
     // global - start in the tile, base
-    extern __shared__ uint32_t unsplit_lds[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t unsplit_lds[]; // (read by 64 bits as well)
     __shared__ uint32_t smem[NT / kWave];
     __shared__ uint32_t carry_s;
     if (*a.fallback)
