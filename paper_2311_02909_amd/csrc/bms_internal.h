@@ -95,7 +95,6 @@ struct NwHop {
     int64_t *nnz_out;          // device scalar
     int64_t rows_bound;        // host-side upper bound of the row count
     int64_t rows_tune, entries_tune; // what launch_nw_sample chooses kernels for: rows and entries, or what they were in the call before
-    int32_t by_dies;           // set by launch_nw_sample: tiles of all minibatches by place, an eighth of the places per die
     int32_t max_degree;
     int32_t self_entry;        // 1: every row carries its own vertex as one more entry after the sampled ones
     int32_t replace;           // 1: the s draws of a row are independent, the row keeps the distinct picks

@@ -78,25 +78,30 @@ __device__ inline int32_t wave_replace_draws(volatile uint32_t *buf, uint64_t ke
 //            eighth of that order.  The rows of a minibatch ascend by vertex id, so what runs at the same time on a die touches
 //            one part of the id range in all minibatches: a line that several minibatches need is fetched once and is in the
 //            die's own cache when the next one asks.
+// Each has kernels of its own: by dies a workgroup computes for half a microsecond before its first read (one minibatch, 74 seeds,
+// (13, 19): a call 72.9 us with both in one kernel, 72.2 so; the second hop's sampling of 7 x 653, (13, 11): 8.4 to 9.0 and 8.0).
 constexpr int kDies = 8;
-static_assert(kDies == 1 << 3, "die_bits");
+template <bool DIES>
 struct TileWalk {
-    int32_t k, i, step_i, left; // i: minibatch
+    int32_t k, i, step_i, left; // i: minibatch; left: visits, by dies
     int64_t j, most, step_j;
-    bool spread;
     // workgroups are dealt to the dies in turn; wave `part` of `parts` in the workgroup; by dies gridDim.x is a multiple of kDies
-    __device__ TileWalk(const NwHop &a, uint32_t part, uint32_t parts, bool by_dies)
-        : k(a.k), most(uniform_load(a.mb_tileoff + a.k + 1)), spread(by_dies && most < 65536) // (larger ones: tile q in step q)
+    __device__ TileWalk(const NwHop &a, uint32_t part, uint32_t parts) : k(a.k), left(0), most(uniform_load(a.mb_tileoff + a.k + 1))
     {
-        const int die_bits = by_dies ? 3 : 0;
-        const uint32_t dies = 1u << die_bits;
-        const int64_t items = most * k, per = (items + dies - 1) >> die_bits;
-        const int64_t lo = (blockIdx.x & (dies - 1)) * per, hi = min<int64_t>(lo + per, items);
-        const int64_t pos = lo + (blockIdx.x >> die_bits) * parts + part;
-        const int32_t step = (gridDim.x >> die_bits) * parts;
-        left = 0;
+        const uint32_t step = (DIES ? gridDim.x / kDies : gridDim.x) * parts;
+        step_j = scalar(step / (uint32_t)k);
+        step_i = (int32_t)(step - (uint32_t)step_j * (uint32_t)k);
+        if (!DIES) {
+            const uint32_t pos = blockIdx.x * parts + part, q = scalar(pos / (uint32_t)k);
+            j = q;
+            i = (int32_t)(pos - q * (uint32_t)k);
+            return;
+        }
+        const int64_t items = most * k, per = (items + kDies - 1) / kDies;
+        const int64_t lo = (blockIdx.x % kDies) * per, hi = min<int64_t>(lo + per, items);
+        const int64_t pos = lo + (blockIdx.x / kDies) * parts + part;
         if (pos < hi && hi >> 31 == 0) { // (divisions of 64 bits are half a microsecond at the start of a workgroup)
-            left = (int32_t)((uint32_t)(hi - pos + step - 1) / (uint32_t)step);
+            left = (int32_t)((uint32_t)(hi - pos + step - 1) / step);
             j = (uint32_t)pos / (uint32_t)k;
             i = (int32_t)((uint32_t)pos - (uint32_t)j * (uint32_t)k);
         } else {
@@ -105,10 +110,8 @@ struct TileWalk {
             i = (int32_t)(pos % k);
             j = pos / k;
         }
-        step_i = step % k;
-        step_j = step / k;
     }
-    __device__ bool more() const { return left > 0; }
+    __device__ bool more() const { return DIES ? left > 0 : j < most; }
     __device__ void next()
     {
         --left;
@@ -122,15 +125,18 @@ struct TileWalk {
     // number of the tile among all, or -1 when the minibatch has none at this step; its rows
     __device__ int64_t tile(const NwHop &a, int64_t &r0, int32_t &rows) const
     {
-        const int64_t t0 = uniform_load(a.mb_tileoff + i), tiles = uniform_load(a.mb_tileoff + i + 1) - t0;
-        const bool apart = spread && tiles != most;
+        int64_t t0 = uniform_load(a.mb_tileoff + i), t1 = uniform_load(a.mb_tileoff + i + 1);
+        const int64_t row0 = uniform_load(a.mb_rowoff + i), row1 = uniform_load(a.mb_rowoff + i + 1);
+        asm volatile("" : "+s"(t0), "+s"(t1) : "s"(row0), "s"(row1)); // (all on their way at once, the rows not a trip to memory later)
+        const int64_t tiles = t1 - t0;
+        const bool apart = DIES && most < 65536 && tiles != most; // (of larger minibatches: tile q in step q)
         int64_t jj = j;
         if (apart) // tile q is visited in step floor(q most / tiles)
             jj = ((uint32_t)j * (uint32_t)tiles + (uint32_t)most - 1u) / (uint32_t)most;
         if (jj >= tiles || (apart && ((uint32_t)jj * (uint32_t)most) / (uint32_t)tiles != j))
             return -1;
-        r0 = uniform_load(a.mb_rowoff + i) + jj * kRowTile;
-        rows = (int32_t)min<int64_t>(uniform_load(a.mb_rowoff + i + 1) - r0, kRowTile);
+        r0 = row0 + jj * kRowTile;
+        rows = row1 - r0 < kRowTile ? (int32_t)(row1 - r0) : kRowTile;
         return t0 + jj;
     }
 };
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(kRowTile) void nw_rows_kernel(NwHop a)
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     for (int64_t q = (int64_t)blockIdx.x * kRowTile + tid; q < a.zero_quads; q += (int64_t)gridDim.x * kRowTile)
         a.zero[q] = make_uint4(0, 0, 0, 0);
-    for (TileWalk walk(a, scalar((uint32_t)(tid / kWave)), kRowTile / kWave, true); walk.more(); walk.next()) {
+    for (TileWalk<true> walk(a, scalar((uint32_t)(tid / kWave)), kRowTile / kWave); walk.more(); walk.next()) {
         int64_t r0;
         int32_t rows;
         const int64_t t = walk.tile(a, r0, rows);
@@ -337,7 +343,7 @@ __device__ __forceinline__ void leave_total(const NwHop &a, int64_t total)
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kSelfMark = 0x80000000u; // staged entry: a vertex id, not a place in A_col
 // SUM: a.sum_tiles; kernels of their own, as the sums' registers would cost the others a workgroup per compute unit
-template <int S, bool SET, bool REPLACE, bool SUM>
+template <int S, bool SET, bool REPLACE, bool SUM, bool DIES>
 __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
 {
     __shared__ uint32_t stage[kRowTile * (S + 1)]; // + 1: the row's own vertex when rows carry it
@@ -361,7 +367,7 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
         __syncthreads();
     }
     // the extent of the lane's row in the workgroup's next tile is fetched while the current tile is sampled
-    TileWalk walk(a, 0, 1, a.by_dies != 0);
+    TileWalk<DIES> walk(a, 0, 1);
     int64_t t, t_next, r0, r0_next;
     int32_t rows, rows_next;
     int64_t beg, beg_next;
@@ -621,15 +627,15 @@ static void launch_nw_sample_wide(const Launch &L, const NwHop &a, const VSet &v
         hipLaunchKernelGGL((nw_sample_wide_kernel<SET, REPLACE, 0>), dim3(grid_for(L, tiles * parts, 4)), block, 0, L.stream, a, vs, parts);
 }
 
-template <bool SET, bool REPLACE, bool SUM>
+template <bool SET, bool REPLACE, bool SUM, bool DIES>
 static void launch_nw_sample_lanes(const Launch &L, const NwHop &a, const VSet &vs, int grid)
 {
-    void (*const kernels[6])(NwHop, VSet) = {nw_sample_kernel<4, SET, REPLACE, SUM>,
-                                             nw_sample_kernel<8, SET, REPLACE, SUM>,
-                                             nw_sample_kernel<16, SET, REPLACE, SUM>,
-                                             nw_sample_kernel<32, SET, REPLACE, SUM>,
-                                             nw_sample_kernel<REPLACE ? 32 : 48, SET, REPLACE, SUM>,
-                                             nw_sample_kernel<REPLACE ? 32 : 64, SET, REPLACE, SUM>};
+    void (*const kernels[6])(NwHop, VSet) = {nw_sample_kernel<4, SET, REPLACE, SUM, DIES>,
+                                             nw_sample_kernel<8, SET, REPLACE, SUM, DIES>,
+                                             nw_sample_kernel<16, SET, REPLACE, SUM, DIES>,
+                                             nw_sample_kernel<32, SET, REPLACE, SUM, DIES>,
+                                             nw_sample_kernel<REPLACE ? 32 : 48, SET, REPLACE, SUM, DIES>,
+                                             nw_sample_kernel<REPLACE ? 32 : 64, SET, REPLACE, SUM, DIES>};
     const int which = a.s <= 4 ? 0 : a.s <= 8 ? 1 : a.s <= 16 ? 2 : a.s <= 32 ? 3 : a.s <= 48 ? 4 : 5;
     hipLaunchKernelGGL(kernels[which], dim3(grid), dim3(kRowTile), 0, L.stream, a, vs);
 }
@@ -684,14 +690,15 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // By dies from one row for every two vertices on: then the minibatches' rows at the same place share lines.  Whole calls of
     // (15, 10, 5), stacked and by dies: 2.4 M vertices, rows / n 0.43 253 and 248 us, 0.86 368 and 351, 1.1 446 and 416, 2.3 719 and
     // 635 (the last hop's sampling 323 and 246); 4 M of 150 neighbours 0.46 484 and 482, 1.8 1224 and 1184; 0.5 M 0.65 125 and 118;
-    // (15, 20) with 0.27 260 and 260.  Counting per segment rules it out, and is worth more (8.7 M of 12 neighbours, 0.91: 1064 and 1094).
-    a.by_dies = !a.seg_cnt && a.k >= kDies && 2 * a.rows_tune >= a.n;
-    if (a.by_dies)
+    // (15, 20) with 0.27 260 and 260; hops of few tiles, 100 x 400 seeds, (5, 15), of 0.2 M vertices 107 and 100; 20 x 600, (10, 10), of
+    // 30 thousand 89 and 86.  Counting per segment rules it out, and is worth more (8.7 M of 12 neighbours, 0.91: 1064 and 1094).
+    const bool by_dies = !a.seg_cnt && a.k >= kDies && 2 * a.rows_tune >= a.n;
+    if (by_dies)
         grid = (grid + kDies - 1) / kDies * kDies;
-    if (a.sum_tiles)
-        launch_nw_sample_lanes<SET, REPLACE, true>(L, a, vs, grid);
-    else
-        launch_nw_sample_lanes<SET, REPLACE, false>(L, a, vs, grid);
+    void (*const launch[2][2])(const Launch &, const NwHop &, const VSet &, int) = {
+        {launch_nw_sample_lanes<SET, REPLACE, false, false>, launch_nw_sample_lanes<SET, REPLACE, false, true>},
+        {launch_nw_sample_lanes<SET, REPLACE, true, false>, launch_nw_sample_lanes<SET, REPLACE, true, true>}};
+    launch[a.sum_tiles ? 1 : 0][by_dies ? 1 : 0](L, a, vs, grid);
     return a.seg_cnt != nullptr;
 }
 

@@ -13,10 +13,10 @@ MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 KERNELS = ["feature_fetch_kernel", "dd_bitmap_kernel", "ldw_extract_kernel", "aggregate_kernel"]
 
 
-def _scratch_bytes(tmp_path):
-    """kernel name -> bytes of scratch per lane, from the notes of the gfx950 code objects in the library"""
+def _code_objects(tmp_path):
+    """the gfx950 code objects in the library, as files"""
     data = open(LIB, "rb").read()
-    found = {}
+    objects = []
     at = data.find(MAGIC)
     while at >= 0:
         entries, = struct.unpack_from("<Q", data, at + len(MAGIC))
@@ -27,16 +27,32 @@ def _scratch_bytes(tmp_path):
             p += 24 + name_len
             if "gfx950" not in name or not size:
                 continue
-            obj = tmp_path / ("code%d" % len(found))
-            obj.write_bytes(data[at + offset:at + offset + size])
-            notes = subprocess.run([READELF, "--notes", str(obj)], check=True, capture_output=True, text=True).stdout
-            for kernel in re.split(r"\n\s*- \.", notes):
-                name = re.search(r"\.?name:\s+(_ZN3bms\S+)\n", kernel)
-                bytes_ = re.search(r"private_segment_fixed_size:\s+(\d+)", kernel)
-                if name and bytes_:
-                    found[name.group(1)] = int(bytes_.group(1))
+            objects.append(tmp_path / ("code%d" % len(objects)))
+            objects[-1].write_bytes(data[at + offset:at + offset + size])
         at = data.find(MAGIC, at + 1)
+    return objects
+
+
+def _readelf(what, obj):
+    return subprocess.run([READELF, what, "--wide", str(obj)], check=True, capture_output=True, text=True).stdout
+
+
+def _scratch_bytes(tmp_path):
+    """kernel name -> bytes of scratch per lane, from the notes of the code objects"""
+    found = {}
+    for obj in _code_objects(tmp_path):
+        for kernel in re.split(r"\n\s*- \.", _readelf("--notes", obj)):
+            name = re.search(r"\.?name:\s+(_ZN3bms\S+)\n", kernel)
+            bytes_ = re.search(r"private_segment_fixed_size:\s+(\d+)", kernel)
+            if name and bytes_:
+                found[name.group(1)] = int(bytes_.group(1))
     return found
+
+
+def _code_bytes(tmp_path):
+    """kernel name -> bytes of its instructions"""
+    return {name: int(size) for obj in _code_objects(tmp_path)
+            for size, name in re.findall(r"\s(\d+)\s+FUNC\s.*\s(_ZN3bms\S+)\n", _readelf("--dyn-syms", obj))}
 
 
 @pytest.mark.skipif(not (os.path.exists(LIB) and os.path.exists(READELF)), reason="library or tools not here")
@@ -44,3 +60,13 @@ def _scratch_bytes(tmp_path):
 def test_kernel_does_not_spill(kernel, tmp_path):
     found = {name: size for name, size in _scratch_bytes(tmp_path).items() if kernel in name}
     assert found and not any(found.values())
+
+
+# a launch that does not go by dies, as those of small hops, carries nothing of that walk, which is two kilobytes of instructions
+@pytest.mark.skipif(not (os.path.exists(LIB) and os.path.exists(READELF)), reason="library or tools not here")
+def test_sampling_in_stacked_order_has_kernels_of_its_own(tmp_path):
+    size = {name: n for name, n in _code_bytes(tmp_path).items() if "nw_sample_kernelILi" in name}
+    stacked = [name for name in size if "ELb0EEEv" in name]
+    assert len(stacked) == 40 and len(size) == 80
+    for name in stacked:
+        assert size[name] + 1000 < size[name.replace("ELb0EEEv", "ELb1EEEv")], name
