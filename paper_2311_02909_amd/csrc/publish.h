@@ -46,6 +46,7 @@ __device__ inline void announce_through(const PublishArgs &a, uint32_t parts)
     __syncthreads();
     if (threadIdx.x == 0 && __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1u) {
         __hip_atomic_store(a.done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // a call that the host makes now, on another stream, counts from zero
         store_through(a.arrived, a.arrival);
     }
 }

@@ -9,6 +9,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_2311_02909_amd", "libbms.so")
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 KERNELS = ["feature_fetch_kernel", "dd_bitmap_kernel", "ldw_extract_kernel", "aggregate_kernel"]
 
@@ -70,3 +71,22 @@ def test_sampling_in_stacked_order_has_kernels_of_its_own(tmp_path):
     assert len(stacked) == 40 and len(size) == 80
     for name in stacked:
         assert size[name] + 1000 < size[name.replace("ELb0EEEv", "ELb1EEEv")], name
+
+
+# the workgroup that is done last sets its counter back, waits until that is where the next call's kernels find it, and only then tells
+# the host, which may make that call on another stream at once
+@pytest.mark.skipif(not (os.path.exists(LIB) and os.path.exists(OBJDUMP)), reason="library or tools not here")
+def test_a_call_is_announced_behind_the_counter_of_its_workgroups(tmp_path):
+    kernel = "_ZN3bms24ldw_extract_place_kernelILb1EEEvNS_5LwHopENS_8LookbackEPlNS_11PublishArgsE"
+    for obj in _code_objects(tmp_path):
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--disassemble-symbols=" + kernel, str(obj)], check=True,
+                              capture_output=True, text=True).stdout
+        if kernel + ">:" not in text:
+            continue
+        code = [line.split("//")[0].strip() for line in text.splitlines()]
+        added, = [x for x, line in enumerate(code) if line.startswith("global_atomic_add ") and " sc0" in line and
+                  any(other.startswith("s_endpgm") for other in code[x:x + 40])]
+        tail = [line for line in code[added:] if line.startswith(("global_store", "s_waitcnt vmcnt(0)"))]
+        assert [line.split()[0] for line in tail] == ["s_waitcnt", "global_store_dword", "s_waitcnt", "global_store_dwordx2"], tail
+        return
+    raise AssertionError("kernel not found")
