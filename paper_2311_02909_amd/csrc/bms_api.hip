@@ -683,6 +683,11 @@ int wait_arrival(CallCtx &c)
 // Workgroups of a last kernel that publishes the call, at most: its stores go past the caches.  The layer-wise one with 6 and 64
 // workgroups saves 3 us of calls of 69 and 377 us, with 512 it costs as much as it saves.
 constexpr int64_t kMostPublishing = 128;
+// ... and hops times offsets (of minibatches) per hop that it leaves for the host, at most: one of its workgroups looks them up, where
+// the launch of its own has a workgroup per hop.  Calls of minibatches of 4 to 64 seeds, by a launch of its own and so: one hop of 241
+// offsets 83 and 82 us, 501 102.0 and 101.8, 3001 314 and 319, 7001 577 and 592; two hops 242 176.7 and 174.5, 502 187 and 187; three
+// hops 303 230.2 and 229.5, 483 239 and 239, 723 237 and 239, 1023 288 and 293, 3003 392 and 406, 21003 1676 and 1790.
+constexpr int64_t kMostPublishedOffsets = 512;
 // The call's scalars and the minibatches' offsets -> pinned memory of the result: by the call's last kernel, or in stream order by one
 // of its own.
 PublishArgs publish_args(CallCtx &c)
@@ -1748,7 +1753,8 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
 
         BMS_TRY(prof.begin("ldw_extract_copy", h));
         if (placed) {
-            published = h + 1 == c.L && rows_bound <= kMostPublishing * kLwRows;
+            published = h + 1 == c.L && rows_bound <= kMostPublishing * kLwRows &&
+                        (!host_offsets(c) || (int64_t)c.L * (c.k + 1) <= kMostPublishedOffsets);
             const PublishArgs p = published ? publish_args(c) : PublishArgs{};
             BMS_TRY(next_lookback(c, lb));
             (void)launch_ldw_extract_place(c.launch, w, lb, slot(c, h, 0), published ? &p : nullptr, &workgroups);

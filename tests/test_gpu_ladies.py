@@ -346,3 +346,29 @@ def test_many_pairs(mods, k, b, shared, squared):
         ref = O.sample_ladies(rowptr, col, batches, (50,), 11 + call, 0, squared)
         res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (50,), 11 + call, squared=squared, recycle=res)
         assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
+
+
+# the call's sizes and the minibatches' offsets left for the host by the last kernel, or, of more than 512 offsets, by a launch of its
+# own (that there are no offsets for the host any more is the case of 22000 minibatches)
+@pytest.mark.parametrize("k,b,s,own", [(511, 3, (5,), False), (512, 3, (5,), True), (169, 4, (6, 5, 4), False), (170, 4, (6, 5, 4), True),
+                                       (7000, 2, (2, 2, 3), True), (22_000, 1, (1,), False)])
+def test_offsets_left_for_the_host(mods, k, b, s, own):
+    O, bms, _ = mods
+    rng = np.random.default_rng(k)
+    rowptr, col = random_csr(3000, 6.0, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(3):
+        batches = random_batches(3000, k, b, rng)
+        ref = O.sample_ladies(rowptr, col, batches, s, 21 + call)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), s, 21 + call, recycle=res)
+            torch.cuda.synchronize()
+        assert any("publish_kernel" in e.name for e in profile.events()) == own
+        assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
+        for hop, want in enumerate(ref):
+            for i in (0, 1, k // 2, k - 2, k - 1):
+                m = res.minibatch(hop, i)
+                r0, r1, c0, c1 = want.mb_rowoff[i], want.mb_rowoff[i + 1], want.mb_coloff[i], want.mb_coloff[i + 1]
+                assert (m.row0, m.rows, m.col0, m.ncols) == (r0, r1 - r0, c0, c1 - c0)
+                assert (m.edge0, m.nnz) == (want.rowptr[r0], want.rowptr[r1] - want.rowptr[r0])
