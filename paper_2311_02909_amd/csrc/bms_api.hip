@@ -1220,9 +1220,9 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             const size_t stride = (size_t)std::max<int64_t>(nbuckets, C);
             const size_t kC = (size_t)c.k * (size_t)C;
             const int64_t xtiles = cut_tiles_bound(nnz, c.k);
-            const size_t loc_at = ((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint32_t) + 127) / 128 * 128; // behind ids_seg
-            BMS_TRY(csr->dd_pairs.ensure(std::max((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t),
-                                                  C ? loc_at + (size_t)xtiles * kCutTile * sizeof(uint16_t) : 0)));
+            // (and lines of slack for the places of the cut, which begin at one behind the ids)
+            const size_t loc_at = ((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint32_t) + 127) / 128 * 128;
+            BMS_TRY(csr->dd_pairs.ensure((size_t)std::max<int64_t>(nnz, 1) * sizeof(uint64_t) + 128));
             BMS_TRY(csr->dd_uniq.ensure((size_t)c.k * stride * sizeof(uint32_t)));
             BMS_TRY(csr->dd_seg.ensure((3 * kC + (size_t)c.k + 16) * sizeof(uint32_t)));
             BMS_TRY(csr->dd_segcnt.ensure(std::max<size_t>(kC, 1) * sizeof(uint32_t)));

@@ -239,7 +239,7 @@ struct DedupArgs {
     uint32_t *big_count; // device counter of big_list (the word after `fallback`)
     int32_t *fallback;   // device flag: a segment fits neither ranking kernel, the per-minibatch kernel takes the hop
     uint32_t *ids_seg;   // nnz: the sampled ids grouped by segment (minibatch i, segment c at mb_edgeoff[i] + seg_off[c])
-    uint16_t *loc;       // tiles * kCutTile, by position in the tile: its place in the tile's ids sorted by segment
+    uint16_t *loc;       // nnz, by position: its place in its tile's ids sorted by segment
     uint32_t *run_gpos;  // tiles * C: where the run of (tile, segment) starts inside the minibatch's part of ids_seg
     uint32_t *run_cnt;   // tiles * C: its length
     uint16_t *ranks;     // nnz, parallel to ids_seg: rank of the id among the distinct ids of its segment
@@ -247,7 +247,9 @@ struct DedupArgs {
     uint32_t *uids;      // nnz: the distinct ids of a segment in ascending order, at the head of the segment's slots
 };
 constexpr int kCutTile = 8192; // positions per tile of the count, split and un-split kernels
-inline int64_t cut_tiles_bound(int64_t nnz, int32_t k) { return nnz / kCutTile + 2 * (int64_t)k; } // at most this many
+constexpr int kLineEntries = 32; // columns in a memory line: a minibatch's tiles after its first begin at one
+// at most this many tiles: a minibatch's last one and the entries that its first one leaves out count as a tile and 31 entries more
+inline int64_t cut_tiles_bound(int64_t nnz, int32_t k) { return (nnz + (int64_t)k * (kCutTile - 1 + kLineEntries - 1)) / kCutTile; }
 constexpr int kSegCap = 65535;      // most entries a segment may hold: the rank of an id inside its segment has 16 bits
 constexpr int kMaxSegments = 2560;  // 3 words each beside the staging of the split / un-split kernels must fit in 160 KB of LDS
 constexpr int kMaxCells = 4096;      // cells of the table that maps ids to segments of unequal width

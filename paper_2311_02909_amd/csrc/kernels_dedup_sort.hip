@@ -34,7 +34,6 @@ static_assert(kCutTile == (1 << kLocShift) && kMaxSegments <= (1 << (32 - kLocSh
 
 // Tiles of a minibatch's N positions, which begin at e0 of the stacked columns: all but the first one begin at a memory line (of an
 // array that does), so that a tile's columns are read and written by whole lines.
-constexpr int kLineEntries = 32;
 __device__ inline int64_t cut_tiles(int64_t e0, int64_t N)
 {
     return N ? (N + (e0 & (kLineEntries - 1)) + kCutTile - 1) / kCutTile : 0;
@@ -282,7 +281,7 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
                 carry_s = carry + total;
             __syncthreads();
         }
-        uint16_t *__restrict__ loc = a.loc + t * TILE;
+        uint16_t *__restrict__ loc = a.loc + e0 + j0;
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q)
             if (id[q] != 0xFFFFFFFFu) {
@@ -861,7 +860,7 @@ __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const in
         cut_tile(e0, N, (uint32_t)(t - tileoff[i]), j0, jend);
         const int n = (int)scalar(jend - j0);
         int left = n - (int)tid;
-        const uint16_t *__restrict__ loc = a.loc + scalar(t) * TILE;
+        const uint16_t *__restrict__ loc = a.loc + scalar(e0 + j0);
         uint32_t place[TILE / NT]; // in the cut's order; later the run that has place q NT + tid, in the upper half
 #pragma unroll
         for (int q = 0; q < TILE / NT; ++q)

@@ -320,6 +320,24 @@ def test_tiles_of_the_cut_at_memory_lines(variant):
         assert_hops_equal(res.hops(), ref, what="call %d" % call)
 
 
+def test_scratch_of_the_cut_goes_by_entries():
+    # many minibatches of hardly any entries: scratch by what they hold, not by a tile each (16 KB)
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(78)
+    k = 20_000
+    rowptr, col = random_csr(3000, 6.0, rng)
+    batches = random_batches(3000, k, 2, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_nodewise(rowptr, col, batches, (4, 3), 5)
+    res = None
+    for call in range(2):
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (4, 3), 5, extract="sort", recycle=res)
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+    bound = 2 * k * 4 * 3           # entries of the second hop, at most
+    assert csr.held_bytes() <= 64 * bound + 512 * k
+
+
 # more tiles of rows than one workgroup scans (32768), a chunk of 4096 and one more or less of them
 @pytest.mark.parametrize("k", [32768, 32769, 36864, 36865])
 def test_scans_over_many_tiles(k):
