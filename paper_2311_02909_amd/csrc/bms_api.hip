@@ -1495,6 +1495,11 @@ std::vector<int32_t> ladies_shape(const CallCtx &c, const int32_t *s_per_layer)
     return shape;
 }
 
+// Entries of a hop's P that are stored past the caches, at least.  The draws search P next and find a smaller one there, the more of
+// it the more draws there are.  Calls of one layer, through the caches and past them: 37 MB, 32 x 1024 seeds and 2048 draws, 205 and 213
+// us; 18 MB, 16 x 1024 and 1024, 143 and 146; 75 MB, 64 x 1024 and 2048 323 and 328, and 512 297 and 295; 98 MB, 256 x 1024 and 2048 406
+// and 404, and 512 379 and 371; 150 MB, 128 x 1024 and 2048 599 and 587; two layers of 13 and 83 MB, 64 x 512 and 512, 285 and 282.
+constexpr int64_t kPastEntries = 10'000'000;
 // room provided for a size that an earlier call of the same shape put at `seen`
 inline int64_t with_margin(int64_t seen) { return seen + seen / 4 + 65536; }
 
@@ -1706,6 +1711,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.p_col = hb.p_col.as<int32_t>();
         w.p_cnt = hb.p_cnt.as<uint32_t>();
         w.prefix = csr->ld_prefix.as<uint64_t>();
+        w.p_past = (no_wait ? c.res->hint_pnnz[h] : pnnz) >= kPastEntries ? 1 : 0;
         BMS_TRY(prof.begin("ldw_p_copy", h));
         launch_ldw_p_copy(c.launch, w, slot(c, h, 2));
         BMS_TRY(prof.end());

@@ -397,6 +397,7 @@ struct LwHop {
     uint32_t *p_cnt;
     uint64_t *prefix;          // pnnz, inclusive, restarts per minibatch
     int32_t place_pairs;       // 1: launch_ldw_p_copy finds the places of the parts itself
+    int32_t p_past;            // 1: P is stored past the caches (not with place_pairs)
     int32_t *sel_tmp;          // k * s
     int64_t *mb_coloff;        // k+1
     int32_t *col_vertex;

@@ -927,7 +927,7 @@ __device__ inline void fetch_entries(const uint32_t *__restrict__ src, uint32_t 
         ent[u] = x < cw ? src[x] : 0u;
     }
 }
-template <bool SQUARED, bool MANY>
+template <bool SQUARED, bool PAST>
 __device__ inline void place_entries(const LwHop &a, const uint32_t (&ent)[kCopyUnroll], uint32_t x0, uint32_t cw, int64_t dst, int32_t id0,
                                      uint64_t &carry)
 {
@@ -947,7 +947,7 @@ __device__ inline void place_entries(const LwHop &a, const uint32_t (&ent)[kCopy
             inc = wave_inclusive_scan_dpp(c);
         }
         if (x0 + u * kWave + lane < cw) {
-            if (MANY) { // past the caches, which the draws (80 -> 70 us) and the next kernels use: dense graph, a call 2689 -> 2616 us
+            if (PAST) { // the caches (LwHop::p_past)
                 __builtin_nontemporal_store(id0 + (int32_t)(ent[u] >> 16), col + u * kWave + lane);
                 __builtin_nontemporal_store(c, cnt + u * kWave + lane);
             } else {
@@ -967,7 +967,7 @@ __device__ inline void place_entries(const LwHop &a, const uint32_t (&ent)[kCopy
 // Many pairs: a window left the accumulation in kWinParts parts (one per wave) whose places are on record (ldw_win_scan).
 // Whole lines of P to a store: a wave's first 32 places are those of the line that the part begins in (x0 < 0: lanes before it have
 // none).  115 M entries, 8.7 M vertices: 348 -> 312 us (4.6 TB/s).
-template <bool SQUARED>
+template <bool SQUARED, bool PAST>
 __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 {
     if (a.giveup) {
@@ -994,7 +994,7 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
         for (int32_t x0 = -(int32_t)(dst & 31); x0 < (int32_t)cw; x0 += kCopyUnroll * kWave) {
             uint32_t ent[kCopyUnroll];
             fetch_entries(src, (uint32_t)x0, cw, ent);
-            place_entries<SQUARED, true>(a, ent, (uint32_t)x0, cw, dst, id0, carry);
+            place_entries<SQUARED, PAST>(a, ent, (uint32_t)x0, cw, dst, id0, carry);
         }
     }
 }
@@ -1822,8 +1822,10 @@ void launch_ldw_p_copy(const Launch &L, const LwHop &a, int64_t *pnnz_out)
                            planners, pnnz_out);
         return;
     }
-    void (*const kernels[2])(LwHop) = {ldw_p_copy_kernel<false>, ldw_p_copy_kernel<true>};
-    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256), 0, L.stream, a);
+    void (*const kernels[2][2])(LwHop) = {{ldw_p_copy_kernel<false, false>, ldw_p_copy_kernel<false, true>},
+                                          {ldw_p_copy_kernel<true, false>, ldw_p_copy_kernel<true, true>}};
+    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][a.p_past ? 1 : 0], dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256),
+                       0, L.stream, a);
 }
 
 void launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)

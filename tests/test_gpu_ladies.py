@@ -348,6 +348,28 @@ def test_many_pairs(mods, k, b, shared, squared):
         assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
 
 
+# P of 10 million entries and more is stored past the caches, a smaller one, which the draws then find there, is not, whatever the number
+# of (minibatch, window) pairs; in the first call, where a bound of its size decides, and in recycled ones
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("k,b,past", [(520, 40, False), (640, 460, True)])
+def test_large_p_past_the_caches(mods, k, b, past, squared):
+    O, bms, _ = mods
+    rng = np.random.default_rng(k)
+    n = 200_000
+    rowptr, col = random_csr(n, 50.0, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(2):
+        batches = random_batches(n, k, b, rng)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (30,), 17 + call, squared=squared, recycle=res)
+            torch.cuda.synchronize()
+        name, = [e.name for e in profile.events() if "ldw_p_copy_kernel" in e.name]
+        assert "<%s, %s>" % (str(squared).lower(), str(past).lower()) in name, name
+        assert (res.hop(0).pnnz >= 10_000_000) == past
+        assert_hops_equal(res.hops(), O.sample_ladies(rowptr, col, batches, (30,), 17 + call, 0, squared), with_p=True, what="call %d" % call)
+
+
 # the call's sizes and the minibatches' offsets left for the host by the last kernel, or, of more than 512 offsets, by a launch of its
 # own (that there are no offsets for the host any more is the case of 22000 minibatches)
 @pytest.mark.parametrize("k,b,s,own", [(511, 3, (5,), False), (512, 3, (5,), True), (169, 4, (6, 5, 4), False), (170, 4, (6, 5, 4), True),
