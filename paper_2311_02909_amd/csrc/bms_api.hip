@@ -1274,8 +1274,10 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             // the distinct ids and the 16-bit ranks in the second (the per-minibatch path uses both as 8-byte entries)
             d.ids_seg = csr->dd_pairs.as<uint32_t>();
             d.loc = reinterpret_cast<uint16_t *>(csr->dd_pairs.as<char>() + loc_at);
-            // columns that the 256 MB cache would not hold for whoever reads them next anyhow: 49 M entries of 111 M vertices, a call
-            // 1957 -> 1942 us; 78 M of 8.7 M 2500 -> 2480
+            // Past the caches where whoever reads the columns next is no slower for it.  Calls, alone and with bms_aggregate_hop of 4
+            // features behind them, through the caches and past them: 6 M entries 400 and 396 us, 493 and 497; 12 M 649 and 643, 816
+            // and 821; 22 M 978 and 971, 1276 and 1273; 26 M 1160 and 1152, 1521 and 1517; 49 M 1949 and 1934, 2646 and 2639; on 8.7 M
+            // vertices 19 M 855 and 850, 1097 and 1098; 28 M 1182 and 1171, 1550 and 1544; 56 M 2056 and 2037, 2833 and 2831.
             d.past = nnz_tune >= (25LL << 20) ? 1 : 0;
             d.uids = csr->dd_utmp.as<uint32_t>();
             d.ranks = reinterpret_cast<uint16_t *>(d.uids + std::max<int64_t>(nnz, 1));
@@ -1635,6 +1637,8 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
             w.b = c.b;
             seed_table(c.b, w.seed_slots, w.seed_shift);
             w.seed_copy = c.res->hops[0].row_vertex.as<int32_t>();
+            if (w.seed_copy == seeds) // they lie there already, from the host or as the rows of a result that is called with again
+                w.seed_copy = nullptr;
             w.seed_flags = reinterpret_cast<int32_t *>(c.res->host + 64);
             w.seed_rowoff = c.res->hops[0].mb_rowoff.as<int64_t>();
             w.scalars = csr->scalars.as<int64_t>();

@@ -253,7 +253,7 @@ __device__ inline void announce(uint32_t *done, uint32_t parts, int64_t *arrived
     }
 }
 
-// Minibatch i's b seeds by a workgroup of NT threads: copied, and passed through a hash table of `slots` words in LDS, a power of two
+// Minibatch i's b seeds by a workgroup of NT threads: copied (copy not null), and passed through a hash table of `slots` words in LDS, a power of two
 // >= 2 b, shift = 32 - its log2; flags[0]: one lies outside [0, n), flags[1]: one is repeated.
 template <int NT>
 __device__ inline void check_seeds(const int32_t *seeds, int i, int32_t b, int64_t n, int32_t slots, int32_t shift, uint32_t *key,
@@ -266,7 +266,8 @@ __device__ inline void check_seeds(const int32_t *seeds, int i, int32_t b, int64
     __syncthreads();
     for (int32_t j = tid; j < b; j += NT) {
         const int32_t v = seeds[row0 + j];
-        copy[row0 + j] = v;
+        if (copy)
+            copy[row0 + j] = v;
         if (v < 0 || (int64_t)v >= n) {
             flags[0] = 1;
             continue;

@@ -354,7 +354,7 @@ struct LwHop {
     int squared;
     uint64_t hopkey;
     uint32_t mb_base;
-    // First hop when the rows kernel stages the seeds as well (else null): it reads them here, copies them to seed_copy, checks them
+    // First hop when the rows kernel stages the seeds as well (else null): it reads them here, copies them to seed_copy (unless null), checks them
     // (slots of the hash table, flags in host memory), writes seed_rowoff and clears the call's scalars
     const int32_t *seeds;
     int32_t b, seed_slots, seed_shift;

@@ -348,6 +348,22 @@ def test_many_pairs(mods, k, b, shared, squared):
         assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
 
 
+# seeds that lie in the result's own rows when the first kernel reads them: copied there from the host, or the rows of the call before
+@pytest.mark.parametrize("k,b", [(3, 300), (9, 64), (2, 4096)])
+def test_seeds_in_the_rows_of_the_result(mods, k, b):
+    O, bms, _ = mods
+    rng = np.random.default_rng(b)
+    rowptr, col = random_csr(100_000, 9.0, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    batches = random_batches(100_000, k, b, rng)
+    seeds, res = batches, None
+    for call in range(4):
+        res = bms.sample_ladies(csr, seeds, (40, 20), 3 + call, recycle=res)
+        assert_hops_equal(res.hops(), O.sample_ladies(rowptr, col, batches, (40, 20), 3 + call), with_p=True, what="call %d" % call)
+        rows = res.hop(0).row_vertex
+        seeds = rows.view(k, b) if call else batches
+
+
 # P of 10 million entries and more is stored past the caches, a smaller one, which the draws then find there, is not, whatever the number
 # of (minibatch, window) pairs; in the first call, where a bound of its size decides, and in recycled ones
 @pytest.mark.parametrize("squared", [False, True])
