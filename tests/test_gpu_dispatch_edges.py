@@ -293,20 +293,31 @@ def test_wide_fanouts_by_the_rows_there_are(degree, b, s, wide):
     assert all(len(x) == 2 and ("wide" in x[1]) == wide for x in names), names
 
 
+def _segments(n, per_minibatch):
+    """id ranges that EXTRACT by segments cuts a hop of so many entries per minibatch into"""
+    dense = n <= 128 * (per_minibatch + 1)
+    shift = 0
+    while shift < (18 if dense else 31) and (2 << shift) * (per_minibatch + 1) <= (16384 if dense else 3000) * n:
+        shift += 1
+    return -(-n // (1 << shift))
+
+
 # EXTRACT by segments: minibatches that begin anywhere in a memory line of 32 entries, of one tile of 8192 entries, a few more and a few
-# less, of several tiles and of none
+# less, of several tiles and of none; one segment, so that a tile is one run, some, and more than the 512 that a workgroup takes at a time
 @pytest.mark.parametrize("variant", [{}, {"union_dst": True}], ids=lambda v: "+".join(v))
-def test_tiles_of_the_cut_at_memory_lines(variant):
+@pytest.mark.parametrize("n,b,base,segments", [(60_000, 40, 0, 1), (14_000_000, 130, 98_304, 54), (200_000_000, 1400, 1_310_720, 763)])
+def test_tiles_of_the_cut_at_memory_lines(n, b, base, segments, variant):
     from oracle import bms_oracle as O
     from paper_2311_02909_amd import bms
     rng = np.random.default_rng(77)
-    n, b = 60_000, 40
     sizes = [8192, 1, 8161, 8160, 0, 8192, 8193, 8191 + 31, 8192 + 31, 16384 - 7, 33, 16384 + 1, 31, 24576]
+    sizes = [base + size if size else 0 for size in (sizes if segments < 512 else sizes[:4])]
+    assert _segments(n, sum(sizes) / len(sizes)) == segments
     rows = []
     for size in sizes:                  # the seeds of a minibatch have `size` neighbours together, all of them kept
         parts = np.full(b, size // b)
-        parts[:size % b] += 1
-        rows += [np.sort(rng.choice(n, p, replace=False)) for p in parts]
+        parts[:size % b] += 1           # (one neighbour out of each of as many stretches of the ids)
+        rows += [np.arange(p) * (n // max(p, 1)) + rng.integers(0, n // max(p, 1), p) for p in parts]
     rowptr = np.zeros(n + 1, dtype=np.int64)
     rowptr[1:len(rows) + 1] = np.cumsum([len(r) for r in rows])
     rowptr[len(rows) + 1:] = rowptr[len(rows)]

@@ -243,7 +243,7 @@ def test_shapes_around_the_window_and_part_boundaries(mods):
 
 @pytest.mark.parametrize("rows,degree,squared", [(512, 300, False), (513, 300, True), (1025, 12, False), (600, 4000, False)])
 def test_windows_from_empty_to_nearly_full(mods, rows, degree, squared):
-    # a wave's rows are 32 (up to 512 in all) or 64; its 4096 counters are listed at once up to 896 in use, else 8 lanes at a time:
+    # a wave's rows are 32 (up to 512 in all) or 64; its 4096 counters are listed at once up to 960 in use, else 32 or 8 lanes at a time:
     # no neighbours beyond id 90000, `degree` a row below 20000 (crowded: up to every counter), two a row in between
     rng = np.random.default_rng(rows + degree)
     n = 140_000
@@ -325,6 +325,33 @@ def test_counters_of_8_bits(mods, k, b, squared):
     _run_both(mods, rowptr, np.concatenate(col), batches, (300, 40), 7, squared=squared)
 
 
+# counters of 8 bits, two parts of a window per wave: parts of 4096 counters with none to all of them in use, evenly and in one half, so
+# that they are listed at once, by halves of the lanes and by 8 lanes; up to 256 rows are taken 32 at a time, more 64 at a time
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("b", [5, 256, 257])
+def test_crowded_counters_of_8_bits(mods, b, squared):
+    O, bms, _ = mods
+    rng = np.random.default_rng(b)
+    n, k = 131_072, 130
+    used = []
+    for part, count in enumerate([0, 1, 500, 959, 960, 961, 1500, 1920, 1921, 2047, 2048, 2049, 3000, 3841, 4095, 4096] * 2):
+        among = 4096 if part < 16 or count > 2048 else 2048      # second window: in the lower half of the part
+        used.append(part * 4096 + np.sort(rng.choice(among, count, replace=False)))
+    used = np.concatenate(used)
+    # row 0 has all of them, where few rows make no large counters likely; many rows have most of them together
+    rows = [used if b == 5 else used[::b]] + [used[rng.random(len(used)) < 2.0 / b] for _ in range(3 * b)]
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:len(rows) + 1] = np.cumsum([len(r) for r in rows])
+    rowptr[len(rows) + 1:] = rowptr[len(rows)]
+    col = np.concatenate(rows).astype(np.int32)
+    batches = np.stack([np.append(rng.permutation(3 * b)[:b - 1] + 1, 0) for _ in range(k)]).astype(np.int32)
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+        _run_both(mods, rowptr, col, batches, (200,), 5, squared=squared)
+        torch.cuda.synchronize()
+    names = [e.name for e in profile.events() if "ldw_accumulate_kernel" in e.name]
+    assert len(names) == 2 and all("<%s, true>" % str(squared).lower() in x for x in names), names
+
+
 # more than 2048 (minibatch, window) pairs: the copy of P by parts, which begin anywhere in a memory line and hold from no entry to a
 # few hundred; 512 workgroups take several pairs each, some of which are counted by halves (b = 300)
 @pytest.mark.parametrize("squared", [False, True])
@@ -335,17 +362,24 @@ def test_many_pairs(mods, k, b, shared, squared):
     n = 200_000
     common = rng.choice(n, shared, replace=False)
     rows = [np.unique(np.concatenate([common, rng.integers(0, n, int(rng.integers(0, 120)))])) for _ in range(3 * b)]
-    rowptr = np.zeros(n + 1, dtype=np.int64)
-    rowptr[1:len(rows) + 1] = np.cumsum([len(r) for r in rows])
-    rowptr[len(rows) + 1:] = rowptr[len(rows)]
-    col = np.concatenate(rows).astype(np.int32)
+    lengths = np.full(n, 3)             # (so that the graph has the columns for an index)
+    lengths[:len(rows)] = [len(r) for r in rows]
+    rowptr = np.concatenate([[0], np.cumsum(lengths)])
+    rest = np.sort(rng.integers(0, n // 3, (n - len(rows), 3)) + np.arange(3) * (n // 3), axis=1)
+    col = np.concatenate(rows + [rest.ravel()]).astype(np.int32)
     csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
-    res = None
-    for call in range(2):       # the first call of a shape and a recycled one
-        batches = np.stack([rng.permutation(3 * b)[:b] for _ in range(k)]).astype(np.int32)
-        ref = O.sample_ladies(rowptr, col, batches, (50,), 11 + call, 0, squared)
-        res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (50,), 11 + call, squared=squared, recycle=res)
-        assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
+    for index in (False, True):         # the rows' lists found by the hop, or taken from the index beside the rows
+        res = None
+        for call in range(2):           # the first call of a shape and a recycled one
+            batches = np.stack([rng.permutation(3 * b)[:b] for _ in range(k)]).astype(np.int32)
+            ref = O.sample_ladies(rowptr, col, batches, (50,), 11 + call, 0, squared)
+            with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+                res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (50,), 11 + call, squared=squared, recycle=res, index=index)
+                torch.cuda.synchronize()
+            names = " ".join(e.name for e in profile.events())
+            assert "ldw_win_scan_kernel" in names and "ldw_p_copy_kernel" in names
+            assert call == 0 or ("ldw_bounds_transpose_kernel" in names) != index, names
+            assert_hops_equal(res.hops(), ref, with_p=True, what="index %s call %d" % (index, call))
 
 
 # seeds that lie in the result's own rows when the first kernel reads them: copied there from the host, or the rows of the call before
