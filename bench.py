@@ -33,40 +33,40 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 3_495_973_568,
-    ("dense_ladies", "ldw_p_copy"): 3_086_191_104,
-    ("dense_ladies", "ldw_extract"): 2_023_595_648,
-    ("dense_sage", "nw_sample"): 9_810_059_648,
-    ("dense_sage", "nw_rows"): 430_223_904,
-    ("dense_sage", "dd_split"): 936_111_296,
-    ("dense_sage", "dd_unsplit"): 803_492_608,
-    ("dense_sage", "dd_rank"): 845_650_816,
-    ("dense_sage", "dd_front"): 603_900_544,
-    ("large_sage", "nw_sample"): 5_020_875_808,
-    ("large_sage", "nw_rows"): 1_260_488_512,
-    ("large_sage", "dd_split"): 620_035_968,
-    ("large_sage", "dd_unsplit"): 554_376_000,
-    ("large_sage", "dd_rank"): 587_241_280,
-    ("large_sage", "dd_front"): 464_209_056,
-    ("mid_ladies", "ldw_p_copy"): 164_266_560,
-    ("mid_ladies", "ldw_accumulate"): 143_446_656,
-    ("mid_ladies", "ldw_extract"): 85_302_624,
-    ("mid_sage", "nw_sample"): 1_568_832_032,
-    ("mid_sage", "nw_rows"): 144_791_456,
-    ("mid_sage", "rg_lookup"): 330_189_024,
-    ("mid_sage", "rg_mark"): 190_075_328,
-    ("mid_sage", "rg_emit"): 150_484_928,
+    ("dense_ladies", "ldw_accumulate"): 3_488_284_544,
+    ("dense_ladies", "ldw_p_copy"): 3_075_043_008,
+    ("dense_ladies", "ldw_extract"): 2_024_934_048,
+    ("dense_sage", "nw_sample"): 9_804_974_624,
+    ("dense_sage", "nw_rows"): 433_276_640,
+    ("dense_sage", "dd_split"): 936_015_488,
+    ("dense_sage", "dd_unsplit"): 802_812_224,
+    ("dense_sage", "dd_rank"): 845_656_448,
+    ("dense_sage", "dd_front"): 603_924_064,
+    ("large_sage", "nw_sample"): 5_019_769_856,
+    ("large_sage", "nw_rows"): 1_271_366_784,
+    ("large_sage", "dd_split"): 619_421_440,
+    ("large_sage", "dd_unsplit"): 555_927_744,
+    ("large_sage", "dd_rank"): 587_214_656,
+    ("large_sage", "dd_front"): 464_218_848,
+    ("mid_ladies", "ldw_p_copy"): 164_302_240,
+    ("mid_ladies", "ldw_accumulate"): 143_482_656,
+    ("mid_ladies", "ldw_extract"): 85_281_952,
+    ("mid_sage", "nw_sample"): 1_578_091_488,
+    ("mid_sage", "nw_rows"): 144_796_960,
+    ("mid_sage", "rg_lookup"): 330_144_064,
+    ("mid_sage", "rg_mark"): 190_076_224,
+    ("mid_sage", "rg_emit"): 150_484_896,
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 9_421_415_360,
-    "dense_sage": 13_521_589_120,
-    "large_sage": 8_590_655_616,
-    "mid_ladies": 447_843_680,
-    "mid_sage": 2_417_672_352,
+    "dense_ladies": 9_403_960_832,
+    "dense_sage": 13_518_808_064,
+    "large_sage": 8_601_343_680,
+    "mid_ladies": 447_919_552,
+    "mid_sage": 2_426_881_952,
 }
 # the part of it that nw_sample reads, MB: the "read MB" of its launches in the same files
-NW_SAMPLE_READ_MB = {"dense_sage": 9309.1, "large_sage": 4692.8, "mid_sage": 1380.0}
+NW_SAMPLE_READ_MB = {"dense_sage": 9304.0, "large_sage": 4691.7, "mid_sage": 1389.3}
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 
 

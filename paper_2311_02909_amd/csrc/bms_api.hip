@@ -680,8 +680,10 @@ int wait_arrival(CallCtx &c)
     return BMS_OK;
 }
 
-// Workgroups of a last kernel that publishes the call, at most: its stores go past the caches.  The layer-wise one with 6 and 64
-// workgroups saves 3 us of calls of 69 and 377 us, with 512 it costs as much as it saves.
+// Workgroups of a last kernel that publishes the call, at most: its stores go past the caches, and with 512 workgroups that costs as
+// much as the launch that it saves.  Layer-wise calls by a launch of its own and so: 6 workgroups 60.3 and 59.1 us, 32 79.0 and 77.0,
+// 64 85.2 and 82.9, 128 98.9 and 96.8, 256 137.7 and 136.3; two layers 64 197.5 and 195.6, 128 278.8 and 278.3, 256 441.7 and 440.7; on
+// 0.3 M vertices 128 72.6 and 70.4; on 8.7 M 64 141.9 and 140.0, 256 304.4 and 302.7.
 constexpr int64_t kMostPublishing = 128;
 // ... and hops times offsets (of minibatches) per hop that it leaves for the host, at most: one of its workgroups looks them up, where
 // the launch of its own has a workgroup per hop.  Calls of minibatches of 4 to 64 seeds, by a launch of its own and so: one hop of 241

@@ -3,7 +3,8 @@
 //
 // The rows of A are sorted by column, so the neighbours of a frontier row that fall into a window
 // of 2^16 vertex ids form one contiguous piece of its adjacency list.  One hop, all k minibatches:
-//   ldw_rows        extents of the frontier's rows, exclusive scan of their degrees = the gathered order
+//   ldw_rows        extents of the frontier's rows, exclusive scan of their degrees = the gathered order; in the first hop
+//                   the frontier is the seeds, which are checked and copied beside it
 //   ldw_plan, ldw_tile_rows
 //                   the gathered order (the neighbour lists of the stacked frontier laid end to end) cut into
 //                   tiles of 1024..4096 positions (few gathered neighbours: small tiles, so that every wave still
@@ -12,17 +13,20 @@
 //                   depends on its vertex alone: when the lists of all n vertices fit in memory they are computed
 //                   once per graph (one wave per tile streams its pieces of rows, the "hop" being the whole
 //                   graph) and a hop only copies the lists of its rows; else the hop streams its rows for them.
-//                   Either way the lists are turned window-major for the next kernel (with the index and k < 1024 plan,
-//                   tile rows and this are one launch, ldw_plan_bounds)
+//                   Either way the lists are turned window-major for the next kernel.  With the index and k < 1024 there
+//                   are none of these launches: further workgroups of ldw_rows copy the lists, further ones of
+//                   ldw_p_place or ldw_win_scan make the plan and find the tile rows, which the extraction needs first
 //   ldw_accumulate  one workgroup per (minibatch, window): 2^16 packed counters of 16 bits (128 KB) or 8 bits in LDS;
 //                   every row's piece of the window adds 1 per neighbour (e_v cannot exceed the number of frontier
 //                   rows, which this path keeps below 2^16); the waves then take its sixteenths
 //                   (parts) out: the nonzero counters leave in ascending column order as 4-byte entries
-//                   (column - window start, e_v) into room claimed from a device-wide cursor
-//   ldw_win_scan    per minibatch: columns and weight of every window, before each of its parts, before the window
-//   ldw_p_copy      parts copied to their place in P, one wave per part; inclusive prefix sums of the integer
-//                   weights (e_v or e_v^2) on the way, one kept per 16 entries (NORM stays implicit: draws are
-//                   integers below the row sum)
+//                   (column - window start, e_v) into room claimed from a device-wide cursor; columns and weight of
+//                   every part and window are recorded
+//   ldw_p_place     the parts copied to their place in P; inclusive prefix sums of the integer weights (e_v or e_v^2) on
+//                   the way, one kept per 16 entries (NORM stays implicit: draws are integers below the row sum).  A
+//                   workgroup takes a pair and adds up the sizes of those before it
+//   ldw_win_scan, ldw_p_copy
+//                   the same of more than 2048 pairs: the places by a launch of their own, a wave per part
 //   ldw_draw        SAMPLE (Sec. 4.2.2): one workgroup per minibatch: s draws, each the smallest t
 //                   with prefix[t] > r, sorted in LDS, duplicates dropped -> sampled columns, at their place in the stack
 //   ldw_extract     EXTRACT (Sec. 4.2.3): the sampled columns of the minibatch sit in an LDS hash
@@ -32,7 +36,7 @@
 //                   copied to their place (ldw_extract_place)
 // A launch costs about 5 us on the device however little it does, and most of these do little: where a kernel needs sums over
 // its own workgroups (rows, minibatches), the workgroups add up those before them (sum_before) instead of leaving it to a
-// kernel in between.  32 x 512 seeds, 3 x 512 samples, 2.4 M vertices: 18 -> 8 launches a hop.
+// kernel in between.  32 x 512 seeds, 3 x 512 samples, 2.4 M vertices: 18 -> 6 launches a hop.
 // A call that sizes its buffers from an earlier call of the same shape runs all of these behind LwHop::giveup.
 #include "bms_device.h"
 #include "bms_internal.h"
@@ -442,9 +446,9 @@ __device__ inline uint32_t at_most_one(uint32_t x)
 //            pair with a counter that passed 255 is found by the sum of all counters, and counted anew half by half in 16 bits
 //   write    a lane lists its counters in use, in column order, in LDS; the entries leave 64 to a store, into room claimed for
 //            exactly as many (the claim is on its way while the lists are made)
-// Bound by vector instructions (two thirds of the time) and the lines of the pieces.  Few rows lie in half waves, so that all waves
-// have some.  Weights e_v and e_v^2 are kernels of their own: decided inside, at every word, the branch kept the LDS reads from
-// overlapping.  The chunks are read from addresses that the compiler knows to be memory: read from just any, each LDS addition waited
+// Bound by vector instructions (half of the time), LDS (a third) and the lines of the pieces, none of them alone.  Few rows lie in half
+// waves, so that all waves have some.  Weights e_v and e_v^2 are kernels of their own: decided inside, at every word, the branch kept the
+// LDS reads from overlapping.  The chunks are read from addresses that the compiler knows to be memory: read from just any, each LDS addition waited
 // for the one before it.  64 x 1024 seeds, 2048 samples, 8.7 M vertices (27 k neighbours per pair), one hop: 650 us, 560 by that and
 // the shorter instruction sequences, 472 by counters of 8 bits as well; 32 x 512 seeds, 512 samples, 2.4 M vertices: 45 -> 36.
 // Tried and slower: two spans of fewer loads in flight (1.15 times on the former), the next pair's loads dealt out between the

@@ -433,8 +433,10 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
         }
         __syncthreads();
         uint32_t *__restrict__ words = vs.words + (int64_t)i * vs.nw;
-        // whole lines of the output to a store, where neither atomics nor the draws bound it: 64 x 1024 seeds on 2.4 M vertices 223 ->
-        // 214 us; fanouts of 40 a hundredth slower
+        // Whole lines of the output to a store, where neither atomics nor the draws bound it.  Calls without and with it, on 2.4 M
+        // vertices: 64 x 1024 seeds, (15, 10, 5) 626 and 612 us, (4, 4, 4) 205 and 206; 32 x 1024, (15, 15, 3) 430 and 424, (16, 16)
+        // 163 and 164; on 0.3 M, 32 x 1024, (16, 16) 102.1 and 103.5; on 8.7 M, (15, 10, 5) 852 and 853.  Of more than 16: 32 x 1024,
+        // (20, 20) 208 and 214, 64 x 512, (10, 30) 162 and 166, on 0.3 M, 32 x 512, (30, 30) 124 and 127
         constexpr bool LINES = !SET && S <= 16;
         constexpr int kGatherUnroll = LINES ? 6 : 5;
         const int32_t head = LINES ? (int32_t)(base & 31) : 0;
