@@ -1695,10 +1695,10 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         // e_v of the vertex with the most neighbours, were its neighbours as likely in a frontier as others of their degree
         const double gathered = (double)(no_wait ? c.res->hint_gathered[h] : D);
         const double most = std::min<double>((double)(rows_bound / c.k), gathered / c.k * (double)csr->max_degree / (double)std::max<int64_t>(csr->nnz, 1));
-        if (launch_ldw_accumulate(c.launch, w, most) != 0)
-            return fail(BMS_EHIP, "launch of the LDS accumulation kernel was refused");
         int64_t pnnz = std::max<int64_t>(std::min<int64_t>(D, (int64_t)c.k * n1), 1);
         w.place_pairs = ldw_may_place(w) && (no_wait || pnnz <= kNoWaitEntries) ? 1 : 0;
+        if (launch_ldw_accumulate(c.launch, w, most) != 0)
+            return fail(BMS_EHIP, "launch of the LDS accumulation kernel was refused");
         if (!w.place_pairs)
             launch_ldw_win_scan(c.launch, w, slot(c, h, 2));
         BMS_TRY(prof.end());

@@ -384,13 +384,14 @@ struct LwHop {
     uint64_t *win_wt;          // k * nwin: their weight
     int64_t *win_poff;         // k * nwin: columns of the minibatch before the window
     uint64_t *win_woff;        // k * nwin: weight of the minibatch before the window
-    int64_t *part_base;        // k * nwin * kWinParts: where the part's entries start in tmp_ent
+    int64_t *part_base;        // k * nwin * kWinParts: 2 x the part's first word in tmp_ent, + its form
     uint32_t *part_cnt;        // k * nwin * kWinParts: columns of P in the part
     uint64_t *part_wt;         // k * nwin * kWinParts: their weight
     uint32_t *part_off;        // k * nwin * kWinParts: columns of the window before the part
     uint64_t *part_woff;       // k * nwin * kWinParts: their weight
-    unsigned long long *cursor; // device scalar: entries of tmp_* in use
-    uint32_t *tmp_ent;         // entries of P, part by part: (column - the window's first id) << 16 | e_v
+    unsigned long long *cursor; // device scalar: words of tmp_ent in use
+    uint32_t *tmp_ent;         // P, part by part: a word per entry, or a bit per column and a byte per entry
+    uint32_t mask_from;        // columns from which on a part takes the latter form (launch_ldw_accumulate)
     int64_t *mb_count;         // k
     int64_t *p_off;            // k+1
     int32_t *p_col;

@@ -20,8 +20,8 @@
 //                   every row's piece of the window adds 1 per neighbour (e_v cannot exceed the number of frontier
 //                   rows, which this path keeps below 2^16); the waves then take its sixteenths
 //                   (parts) out: the nonzero counters leave in ascending column order as 4-byte entries
-//                   (column - window start, e_v) into room claimed from a device-wide cursor; columns and weight of
-//                   every part and window are recorded
+//                   (column - window start, e_v), or as a bit per column and a byte per entry, into room claimed from a
+//                   device-wide cursor; columns and weight of every part and window are recorded
 //   ldw_p_place     the parts copied to their place in P; inclusive prefix sums of the integer weights (e_v or e_v^2) on
 //                   the way, one kept per 16 entries (NORM stays implicit: draws are integers below the row sum).  A
 //                   workgroup takes a pair and adds up the sizes of those before it
@@ -54,7 +54,7 @@ constexpr int kExtWaves = kExtThreads / kWave;
 constexpr int kAccUnroll = 8;              // 16-byte loads per lane and span
 constexpr int kAccChunks = kWave * kAccUnroll; // aligned 16-byte chunks per span: one per lane and load
 constexpr int kAccFlush = 4;               // entries per lane on their way out at a time
-constexpr int kAccListed = 960;            // counters in use that a wave lists in LDS at a time
+constexpr int kAccListed = 956;            // counters in use that a wave lists in LDS at a time
 struct AccPiece {                          // one nonempty piece of a wave's rows
     int64_t origin;                        // byte address of its first chunk - 16 * chunks of the batch before it
     int32_t lo, hi;                        // its first entry and the one behind its last, counted from origin
@@ -62,7 +62,7 @@ struct AccPiece {                          // one nonempty piece of a wave's row
 struct AccWave {
     union { // in turn
         AccPiece piece[kWave];     // one record per nonempty piece of a batch, by rank
-        uint16_t list[kAccListed];
+        alignas(8) uint16_t list[kAccListed + 4]; // (entries that leave four to a word: up to three behind the listing before)
     };
     uint32_t starts[2 * kAccUnroll]; // a bit per chunk of a span: a piece starts there
 };
@@ -85,6 +85,21 @@ struct AccLds {
     AccShared<NARROW> sh;
 };
 static_assert(sizeof(AccLds<false>) <= 160 * 1024 && 2 * sizeof(AccLds<true>) <= 160 * 1024, "does not fit a compute unit");
+// A part is staged in one of two forms (part_base: 2 x its first word in tmp_ent, + 1 with masks):
+//   entries  a word each, (column - the window's first id) << 16 | e_v
+//   masks    a bit per column of the part in use, then a byte per entry: e_v.  Only of counters of 8 bits, and of parts with at
+//            least LwHop::mask_from columns, where it is the shorter one (so that what holds the entries holds either form)
+constexpr uint32_t kMaskWords = kPartIds / 32;
+constexpr uint32_t kMaskFrom = 256;
+static_assert(kMaskWords + (kMaskFrom + 3) / 4 <= kMaskFrom, "not the shorter one");
+__device__ inline uint32_t staged_words(uint32_t columns, uint32_t mask_from)
+{
+    return columns >= mask_from ? kMaskWords + (columns + 3u) / 4u : columns;
+}
+using FourPlaces = uint64_t __attribute__((may_alias));
+using I32x2_a4 = int32_t __attribute__((ext_vector_type(2), aligned(4)));
+using U32x2_a4 = uint32_t __attribute__((ext_vector_type(2), aligned(4)));
+
 constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
 constexpr int kStreamUnroll = 8; // neighbours per lane in flight in the two streaming passes
 constexpr int kDrawTop = 2048;                    // recorded weight sums of P that a drawing workgroup keeps in LDS
@@ -444,8 +459,9 @@ __device__ inline uint32_t at_most_one(uint32_t x)
 //   gather   a pair's first span of chunks is asked for while the counters of the pair before it leave
 //   count    64 consecutive counters per lane: a bit for each that is in use, columns and weight of the wave's parts.  8 bits: a
 //            pair with a counter that passed 255 is found by the sum of all counters, and counted anew half by half in 16 bits
-//   write    a lane lists its counters in use, in column order, in LDS; the entries leave 64 to a store, into room claimed for
-//            exactly as many (the claim is on its way while the lists are made)
+//   write    a lane lists its counters in use, in column order, in LDS; the entries leave 64 to a store, or their bytes 256 to a
+//            store behind the bits of the count, into room claimed for exactly as many (the claim is on its way while the lists
+//            are made).  The latter writes 0.46 instead of 0.97 GB in three layers of 64 x 1024 seeds (1.14 -> 1.05 ms)
 // Bound by vector instructions (half of the time), LDS (a third) and the lines of the pieces, none of them alone.  Few rows lie in half
 // waves, so that all waves have some.  Weights e_v and e_v^2 are kernels of their own: decided inside, at every word, the branch kept the
 // LDS reads from overlapping.  The chunks are read from addresses that the compiler knows to be memory: read from just any, each LDS addition waited
@@ -730,13 +746,16 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
         }
         // room for the entries; the parts lie in it one after the other
         const int np = NW * parts;
-        const uint32_t sums = wave_inclusive_scan_dpp(lane < np ? sh.cnt[lane] : 0u);
-        const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)sums, np - 1);
+        const uint32_t mask_from = bytes ? a.mask_from : 0xFFFFFFFFu;
+        const uint32_t of_part = lane < np ? sh.cnt[lane] : 0u;
+        const uint32_t sums = wave_inclusive_scan_dpp(staged_words(of_part, mask_from));
+        const uint32_t pair_words = (uint32_t)__builtin_amdgcn_readlane((int)sums, np - 1);
+        const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(of_part), np - 1);
         unsigned long long claim = 0;
         if (tid == 0 && pair_c) {
             unsigned long long *cursor = a.cursor;
             asm volatile("" : "+v"(cursor)); // (an address known to be the same in all lanes has the wave wait for the answer here)
-            claim = __hip_atomic_fetch_add((Global<unsigned long long> *)cursor, (unsigned long long)pair_c, __ATOMIC_RELAXED,
+            claim = __hip_atomic_fetch_add((Global<unsigned long long> *)cursor, (unsigned long long)pair_words, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
         }
         const int half_now = half;
@@ -749,10 +768,10 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
             const uint32_t lower = (uint32_t)__builtin_amdgcn_readlane((int)upto[q], kWave / 2 - 1);
             return part_c[q] <= (uint32_t)kAccListed ? kWave : max(lower, part_c[q] - lower) <= (uint32_t)kAccListed ? kWave / 2 : 8;
         };
-        auto list_up = [&](int q, int lane0, uint32_t listed) {
+        auto list_up = [&](int q, int lane0, uint32_t from) { // the lanes' first entry at place 0 of the list: from
             __builtin_amdgcn_wave_barrier();
             if (lane >= lane0 && lane < lane0 + lanes_of(q)) {
-                uint16_t *to = me.list + (upto[q] - mine[q] - listed);
+                uint16_t *to = me.list + (upto[q] - mine[q] - from);
                 for (uint32_t m = used[q][0]; m; m &= m - 1u)
                     *to++ = (uint16_t)(lane * 64 + __ffs((int)m) - 1);
                 for (uint32_t m = used[q][1]; m; m &= m - 1u)
@@ -786,10 +805,11 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
         for (int q = 0; q < PARTS; ++q) {
             if (q >= parts)
                 continue;
-            const int64_t base = claimed + (uint32_t)__builtin_amdgcn_readlane((int)sums, wave * parts + q) - part_c[q];
+            const bool masks = part_c[q] >= mask_from;
+            const int64_t base = claimed + (uint32_t)__builtin_amdgcn_readlane((int)sums, wave * parts + q) - staged_words(part_c[q], mask_from);
             if (lane == 0) {
                 const int64_t part = (int64_t)blk * kWinParts + part0 + q;
-                a.part_base[part] = base;
+                a.part_base[part] = 2 * base + (masks ? 1 : 0);
                 a.part_cnt[part] = part_c[q];
                 a.part_wt[part] = part_w[q];
             }
@@ -800,6 +820,38 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
             const uint8_t *cnt8 = reinterpret_cast<const uint8_t *>(wave4 + q * (kPartIds / 16));
             const uint32_t part_id = (part0 + q) * kPartIds;
             const int lanes = lanes_of(q);
+            if (masks) {
+                U32x2_a4 bits;
+                bits.x = used[q][0];
+                bits.y = used[q][1];
+                reinterpret_cast<U32x2_a4 *>(out)[lane] = bits;
+                uint32_t *__restrict__ bytes_out = out + kMaskWords;
+                uint32_t left = 0; // a place of those listed before that do not fill a word, by lane
+                for (int lane0 = 0; lane0 < kWave; lane0 += lanes) {
+                    const uint32_t listed = lane0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto[q], lane0 - 1) : 0u;
+                    const uint32_t upto_here = (uint32_t)__builtin_amdgcn_readlane((int)upto[q], lane0 + lanes - 1);
+                    const uint32_t from = listed & ~3u, n = upto_here - from; // places in the list
+                    if (lane0 || q)
+                        list_up(q, lane0, from);
+                    if ((uint32_t)lane < (listed & 3u))
+                        me.list[lane] = (uint16_t)left;
+                    __builtin_amdgcn_wave_barrier();
+                    const bool end = lane0 + lanes == kWave;
+                    const uint32_t words = end ? (n + 3u) / 4u : n / 4u;
+                    for (uint32_t x = lane; x < words; x += kWave) {
+                        // (behind the last entry there is anything in the list)
+                        const uint64_t ids = reinterpret_cast<const FourPlaces *>(me.list)[x];
+                        uint32_t word = 0;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            word |= (uint32_t)cnt8[(uint32_t)(ids >> (16 * e)) & (kPartIds - 1u)] << (8 * e);
+                        bytes_out[from / 4u + x] = word;
+                    }
+                    if (!end)
+                        left = me.list[(n & ~3u) + (lane & 3u)]; // (three places behind the list's end at most: it has them)
+                }
+                continue;
+            }
             for (int lane0 = 0; lane0 < kWave; lane0 += lanes) {
                 const uint32_t listed = lane0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto[q], lane0 - 1) : 0u;
                 const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto[q], lane0 + lanes - 1) - listed;
@@ -968,12 +1020,39 @@ __device__ inline void place_entries(const LwHop &a, const uint32_t (&ent)[kCopy
     }
 }
 
-// Many pairs: a window left the accumulation in kWinParts parts (one per wave) whose places are on record (ldw_win_scan).
-// Whole lines of P to a store: a wave's first 32 places are those of the line that the part begins in (x0 < 0: lanes before it have
-// none).  115 M entries, 8.7 M vertices: 348 -> 312 us (4.6 TB/s).
+// A wave's view of a part in masks, up to kCopyListed entries at a time: the columns and e_v of those at places 32 w .. of P, where the first
+// of them lies in the 32 places (a memory line) from place 0 on
+constexpr uint32_t kCopyListed = 992;
+struct CopyWave {
+    alignas(16) uint8_t cnt[kCopyListed + 32];
+    uint16_t list[kCopyListed + 32];
+};
+using U16_any = uint16_t __attribute__((may_alias));
+using U32_any = uint32_t __attribute__((may_alias));
+using U32x4_any = uint32_t __attribute__((ext_vector_type(4), may_alias));
+using U32x4_a1 = uint32_t __attribute__((ext_vector_type(4), aligned(1)));
+constexpr int64_t kMostCopying = 1 << 18; // workgroups (a launch has fewer than 2^32 threads)
+template <bool PAST, class T>
+__device__ inline void store_p(T x, T *to) // PAST: past the caches (LwHop::p_past)
+{
+    if (PAST)
+        __builtin_nontemporal_store(x, to);
+    else
+        *to = x;
+}
+
+// Many pairs: a window left the accumulation in kWinParts parts whose places are on record (ldw_win_scan).  A part per wave (above
+// 65536 pairs several), started in the order of P: what the chip writes at a time then lies close together, and the next workgroups fill the waits.  Whole lines of P
+// to a store: a wave's first 32 places are those of the line that the part begins in.  Of a part in masks all e_v (of up to
+// kCopyListed entries) are read before the first store (a load that is asked for behind stores is only there when they are done),
+// and a lane has two entries: half the stores and lane scans.
+// 115 M entries, 8.7 M vertices, all of the call's hops (3 GB with parts as entries, 2.6 with masks): 688 us with 17 parts a wave,
+// one after the other and 64 entries to a store; 620 from masks, 587 by two entries a lane and reads ahead of stores, 531 with 2 parts
+// a wave, 509 with one (5.1 TB/s).
 template <bool SQUARED, bool PAST>
 __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
 {
+    __shared__ CopyWave waves[256 / kWave];
     if (a.giveup) {
         if (*a.giveup)
             return;
@@ -983,22 +1062,92 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
             return;
         }
     }
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = scalar(threadIdx.x / kWave);
+    CopyWave &me = waves[wave];
     const int64_t nparts = (int64_t)a.k * a.nwin * kWinParts;
-    for (int64_t part = (int64_t)blockIdx.x * 4 + threadIdx.x / kWave; part < nparts; part += (int64_t)gridDim.x * 4) {
-        const int64_t blk = part / kWinParts;
-        const uint32_t cw = a.part_cnt[part];
+    for (int64_t part = (int64_t)blockIdx.x * (256 / kWave) + wave; part < nparts; part += (int64_t)gridDim.x * (256 / kWave)) {
+        const uint32_t cw = uniform_load(a.part_cnt + part);
         if (cw == 0)
             continue;
-        const uint32_t o0 = a.part_off[part];
-        const int i = (int)(blk / a.nwin);
-        const int32_t id0 = (int32_t)(blk % a.nwin) << kWinShift;
-        const uint32_t *__restrict__ src = a.tmp_ent + a.part_base[part];
-        const int64_t dst = a.p_off[i] + a.win_poff[blk] + o0;
-        uint64_t carry = a.win_woff[blk] + a.part_woff[part];
-        for (int32_t x0 = -(int32_t)(dst & 31); x0 < (int32_t)cw; x0 += kCopyUnroll * kWave) {
-            uint32_t ent[kCopyUnroll];
-            fetch_entries(src, (uint32_t)x0, cw, ent);
-            place_entries<SQUARED, PAST>(a, ent, (uint32_t)x0, cw, dst, id0, carry);
+        const int64_t blk = part / kWinParts;
+        const int32_t i = (int32_t)((uint32_t)blk / (uint32_t)a.nwin); // (at most 2^16 minibatches and 2^15 windows)
+        const int32_t window = (int32_t)blk - i * a.nwin;
+        const int64_t base = uniform_load(a.part_base + part);
+        const int64_t dst = uniform_load(a.p_off + i) + uniform_load(a.win_poff + blk) + uniform_load(a.part_off + part);
+        uint64_t carry = uniform_load(a.win_woff + blk) + uniform_load(a.part_woff + part);
+        const uint32_t *__restrict__ src = a.tmp_ent + (base >> 1);
+        if (!(base & 1)) {
+            for (int32_t x0 = -(int32_t)(dst & 31); x0 < (int32_t)cw; x0 += kCopyUnroll * kWave) {
+                uint32_t ent[kCopyUnroll];
+                fetch_entries(src, (uint32_t)x0, cw, ent);
+                place_entries<SQUARED, PAST>(a, ent, (uint32_t)x0, cw, dst, window << kWinShift, carry);
+            }
+            continue;
+        }
+        const uint32_t id0 = (uint32_t)window << kWinShift | (uint32_t)(part % kWinParts) * kPartIds;
+        // e_v of the entries from `from` on, and of the places before them in their line of P
+        auto fetch_counts = [&](uint32_t from) {
+            const uint32_t head = (uint32_t)(dst + from) & 31u;
+            const uint8_t *counts = reinterpret_cast<const uint8_t *>(src + kMaskWords) + from;
+            U32x4_a1 x = {0, 0, 0, 0};
+            if (16 * lane < cw - from + head) // (up to 15 bytes behind the part, which is 64 words shorter than the room there is for it)
+                x = *reinterpret_cast<const U32x4_a1 *>(counts + ((int32_t)(16 * lane) - (int32_t)head));
+            return x;
+        };
+        const U32x2_a4 bits = reinterpret_cast<const U32x2_a4 *>(src)[lane]; // 64 columns a lane
+        U32x4_a1 counts = fetch_counts(0);
+        const uint32_t used = __popc(bits.x) + __popc(bits.y), upto = wave_inclusive_scan_dpp(used);
+        const uint32_t lower = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave / 2 - 1);
+        static_assert(8 * 64 <= kCopyListed, "8 lanes' columns");
+        const uint32_t lanes = cw <= kCopyListed ? kWave : max(lower, cw - lower) <= kCopyListed ? kWave / 2 : 8;
+        for (uint32_t lane0 = 0; lane0 < kWave; lane0 += lanes) {
+            const uint32_t from = lane0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)lane0 - 1) : 0u;
+            const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)(lane0 + lanes) - 1), n = to - from;
+            const uint32_t head = (uint32_t)(dst + from) & 31u;
+            __builtin_amdgcn_wave_barrier();
+            reinterpret_cast<U32x4_any *>(me.cnt)[lane] = counts;
+            if (lane - lane0 < lanes) {
+                uint16_t *to_lo = me.list + head + (upto - used - from), *to_hi = to_lo + __popc(bits.x);
+                const uint32_t id = lane * 64u;
+                for (uint32_t lo = bits.x, hi = bits.y; lo | hi;) {
+                    if (lo) {
+                        *to_lo++ = (uint16_t)(id + (uint32_t)__ffs((int)lo) - 1u);
+                        lo &= lo - 1u;
+                    }
+                    if (hi) {
+                        *to_hi++ = (uint16_t)(id + (uint32_t)__ffs((int)hi) + 31u);
+                        hi &= hi - 1u;
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (lane0 + lanes < kWave)
+                counts = fetch_counts(to);
+            const int64_t line = scalar(dst + from - head); // a multiple of 32
+            for (uint32_t x = 0; x < head + n; x += 2 * kWave) {
+                const uint32_t y = x + 2 * lane;
+                const uint32_t ids = *reinterpret_cast<const U32_any *>(me.list + y);
+                const uint32_t both = *reinterpret_cast<const U16_any *>(me.cnt + y);
+                const bool in0 = y - head < n, in1 = y + 1u - head < n;
+                const uint32_t c0 = in0 ? both & 0xFFu : 0u, c1 = in1 ? both >> 8 : 0u;
+                const uint32_t inc = wave_inclusive_scan_dpp(SQUARED ? c0 * c0 + c1 * c1 : c0 + c1); // (128 weights of less than 2^16)
+                int32_t *col = a.p_col + line + x;
+                uint32_t *cnt = a.p_cnt + line + x;
+                const int32_t v0 = (int32_t)(id0 + (ids & 0xFFFFu)), v1 = (int32_t)(id0 + (ids >> 16));
+                if (in0 && in1) {
+                    const I32x2_a4 v = {v0, v1};
+                    const U32x2_a4 c = {c0, c1};
+                    store_p<PAST>(v, reinterpret_cast<I32x2_a4 *>(col) + lane);
+                    store_p<PAST>(c, reinterpret_cast<U32x2_a4 *>(cnt) + lane);
+                } else if (in0 || in1) {
+                    const uint32_t at = 2 * lane + (in0 ? 0u : 1u);
+                    store_p<PAST>(in0 ? v0 : v1, col + at);
+                    store_p<PAST>(in0 ? c0 : c1, cnt + at);
+                }
+                if (in1 && (lane & 7u) == 7u) // the last of kPrefixBlock entries
+                    a.prefix[(line + x + 2 * lane) / kPrefixBlock] = carry + inc;
+                carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+            }
         }
     }
 }
@@ -1042,7 +1191,7 @@ __global__ __launch_bounds__(NT) void ldw_p_place_kernel(LwHop a, int planners, 
 #pragma unroll
     for (int e = 0; e < EACH; ++e) {
         const int q = wave * EACH + e;
-        fetch_entries(a.tmp_ent + lane_value(base, q), 0, (uint32_t)__builtin_amdgcn_readlane((int)cnt, q), ent[e]);
+        fetch_entries(a.tmp_ent + (lane_value(base, q) >> 1), 0, (uint32_t)__builtin_amdgcn_readlane((int)cnt, q), ent[e]);
     }
     const uint32_t upto_c = wave_inclusive_scan_dpp(cnt);
     const uint64_t upto_w = wave_inclusive_scan(wt);
@@ -1084,7 +1233,7 @@ __global__ __launch_bounds__(NT) void ldw_p_place_kernel(LwHop a, int planners, 
         const uint32_t cw = (uint32_t)__builtin_amdgcn_readlane((int)cnt, q);
         if (cw == 0)
             continue;
-        const uint32_t *__restrict__ src = a.tmp_ent + lane_value(base, q);
+        const uint32_t *__restrict__ src = a.tmp_ent + (lane_value(base, q) >> 1);
         const int64_t dst = before + (uint32_t)__builtin_amdgcn_readlane((int)(upto_c - cnt), q);
         uint64_t carry = before_w + (uint64_t)lane_value((int64_t)(upto_w - wt), q);
         place_entries<SQUARED, false>(a, ent[e], 0, cw, dst, id0, carry);
@@ -1799,8 +1948,11 @@ static int launch_accumulate(const Launch &L, const LwHop &a)
 // 8 bits: 266 pairs, 40 expected: 144 and 133 us; 320, 244: 234 and 208; 1064, 223: 279 and 268; 532, 462 (2 pairs overflow): 256 and
 // 255; 920, 318 (12 overflow): 437 and 453; 532, 887 (92 overflow): 370 and 407.  With many pairs for every workgroup the few that
 // overflow cost less: three layers, 8512 pairs, 325 expected (35 overflow): 3000 and 2820.
-int launch_ldw_accumulate(const Launch &L, const LwHop &a, double most)
+int launch_ldw_accumulate(const Launch &L, const LwHop &hop, double most)
 {
+    LwHop a = hop;
+    // Few pairs' entries stay in the caches until the copy has read them, and that is made for short parts: no masks there
+    a.mask_from = hop.place_pairs ? 0xFFFFFFFFu : kMaskFrom;
     const int64_t pairs = (int64_t)a.k * a.nwin;
     const bool narrow = pairs > L.num_cu && most <= (pairs >= 8 * L.num_cu ? 384.0 : 256.0);
     return narrow ? launch_accumulate<true>(L, a) : launch_accumulate<false>(L, a);
@@ -1828,8 +1980,8 @@ void launch_ldw_p_copy(const Launch &L, const LwHop &a, int64_t *pnnz_out)
     }
     void (*const kernels[2][2])(LwHop) = {{ldw_p_copy_kernel<false, false>, ldw_p_copy_kernel<false, true>},
                                           {ldw_p_copy_kernel<true, false>, ldw_p_copy_kernel<true, true>}};
-    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][a.p_past ? 1 : 0], dim3(grid_for(L, ((int64_t)a.k * a.nwin * kWinParts + 3) / 4, 8)), dim3(256),
-                       0, L.stream, a);
+    const int64_t workgroups = std::min<int64_t>(((int64_t)a.k * a.nwin * kWinParts + 3) / 4, kMostCopying);
+    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][a.p_past ? 1 : 0], dim3((unsigned)workgroups), dim3(256), 0, L.stream, a);
 }
 
 void launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)

@@ -382,6 +382,50 @@ def test_many_pairs(mods, k, b, shared, squared):
             assert_hops_equal(res.hops(), ref, with_p=True, what="index %s call %d" % (index, call))
 
 
+# more than 2048 pairs with counters of 8 bits: parts from 256 columns on are staged as a bit per column and a byte per entry.  Parts of
+# 4096 columns with none to all of them in use, evenly and in their lower half: listed at once, by halves of the lanes and by 8 lanes on
+# the way out, whose words of four bytes then begin in one listing and end in the next; at once or by halves (2048) on the way back
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("b", [5, 257])
+def test_parts_as_masks(mods, b, squared):
+    O, bms, _ = mods
+    rng = np.random.default_rng(b)
+    n, k = 131_072, 1025
+    used = []
+    for part, count in enumerate([0, 1, 255, 256, 257, 955, 956, 957, 1500, 1911, 1913, 2047, 2048, 2049, 3000, 4096] * 2):
+        among = 4096 if part < 16 or count > 2048 else 2048      # second window: in the lower half of the part
+        used.append(part * 4096 + np.sort(rng.choice(among, count, replace=False)))
+    used = np.concatenate(used)
+    rows = [used if b == 5 else used[::b]] + [used[rng.random(len(used)) < 2.0 / b] for _ in range(3 * b)]
+    rowptr = np.zeros(n + 1, dtype=np.int64)
+    rowptr[1:len(rows) + 1] = np.cumsum([len(r) for r in rows])
+    rowptr[len(rows) + 1:] = rowptr[len(rows)]
+    col = np.concatenate(rows).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(2):
+        batches = np.stack([np.append(rng.permutation(3 * b)[:b - 1] + 1, 0) for _ in range(k)]).astype(np.int32)
+        ref = O.sample_ladies(rowptr, col, batches, (200,), 5, 0, squared)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (200,), 5, squared=squared, recycle=res)
+            torch.cuda.synchronize()
+        names = " ".join(e.name for e in profile.events())
+        assert "ldw_accumulate_kernel<%s, true>" % str(squared).lower() in names and "ldw_p_copy_kernel" in names, names
+        assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
+
+
+# more parts than a launch of the copy of P has waves
+def test_more_pairs_than_workgroups_copy(mods):
+    O, bms, _ = mods
+    rng = np.random.default_rng(8)
+    n, k = 100_000, 33_000
+    rowptr, col = random_csr(n, 20.0, rng)
+    batches = random_batches(n, k, 2, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (5,), 3)
+    assert_hops_equal(res.hops(), O.sample_ladies(rowptr, col, batches, (5,), 3), with_p=True, what="k=%d" % k)
+
+
 # seeds that lie in the result's own rows when the first kernel reads them: copied there from the host, or the rows of the call before
 @pytest.mark.parametrize("k,b", [(3, 300), (9, 64), (2, 4096)])
 def test_seeds_in_the_rows_of_the_result(mods, k, b):
