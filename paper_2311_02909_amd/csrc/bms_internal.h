@@ -42,6 +42,9 @@ struct PublishArgs {
 void launch_publish(const Launch &, const PublishArgs &);
 
 int grid_for(const Launch &L, int64_t blocks, int per_cu);
+// per_cu where a workgroup has one tile as a rule.  A workgroup that goes on to another tile first waits for its stores (a load that
+// is asked for behind them is only there when they are done); one that ends does not, and the next one starts.
+constexpr int kOnePass = 256;
 void seed_table(int32_t b, int32_t &slots, int32_t &shift); // of the hash table that checks b seeds (check_seeds)
 // called by multi-kernel launchers before each kernel (group) so that it can be timed on its own
 using StageMark = std::function<void(const char *)>;

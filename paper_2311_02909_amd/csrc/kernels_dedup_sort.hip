@@ -1058,7 +1058,7 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
                 (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
             attr_set = true;
         }
-        hipLaunchKernelGGL((dd_split_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, 4)), dim3(512), lds,
+        hipLaunchKernelGGL((dd_split_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, kOnePass)), dim3(512), lds,
                            L.stream, a, a.big_tileoff);
     }
     mark("dd_rank");
@@ -1078,10 +1078,10 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
     const int bm_per_cu = (int)std::max<size_t>(1, std::min<size_t>(2, (size_t)(156 * 1024) / bm_lds));
     const uint32_t places = (uint32_t)bm_places(a.wbits_max <= kMaxBitmapShift ? a.wbits_max : kMaxBitmapShift);
     if (a.by_bitmap) {
-        hipLaunchKernelGGL(dd_bitmap_kernel<false>, dim3(grid_for(L, (int64_t)a.k * a.C, bm_per_cu)), dim3(kBmThreads),
+        hipLaunchKernelGGL(dd_bitmap_kernel<false>, dim3(grid_for(L, (int64_t)a.k * a.C, kOnePass)), dim3(kBmThreads),
                            bm_lds, L.stream, a, places);
     } else {
-        hipLaunchKernelGGL(dd_rank_kernel, dim3(grid_for(L, (int64_t)a.k * a.C, 3)), dim3(kRankThreads), 0, L.stream, a);
+        hipLaunchKernelGGL(dd_rank_kernel, dim3(grid_for(L, (int64_t)a.k * a.C, kOnePass)), dim3(kRankThreads), 0, L.stream, a);
         if (a.tab || a.cshift <= kMaxBitmapShift) // segments the counting kernel did not take (none can be listed otherwise)
             hipLaunchKernelGGL(dd_bitmap_kernel<true>, dim3(grid_for(L, nnz / 1024 + 1, bm_per_cu)), dim3(kBmThreads),
                                bm_lds, L.stream, a, places);
@@ -1106,7 +1106,7 @@ static void launch_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
         attr_set = true;
     }
     const int64_t tiles = cut_tiles_bound(nnz, a.k);
-    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512, PAST>), dim3(grid_for(L, tiles, 4)), dim3(512), lds, L.stream, a,
+    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512, PAST>), dim3(grid_for(L, tiles, kOnePass)), dim3(512), lds, L.stream, a,
                        a.big_tileoff);
 }
 

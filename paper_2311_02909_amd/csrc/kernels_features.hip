@@ -300,7 +300,7 @@ void launch_aggregate(const Launch &L, const AggArgs &a)
     int tile_rows = kFeatRows; // fewer where that leaves workgroups without a tile or with one more than others
     while (tile_rows > 4 && a.rows < (int64_t)tile_rows * L.num_cu * 64 && tile_rows * ((a.f + 3) / 4) > kFeatThreads)
         tile_rows /= 2;
-    const int grid = grid_for(L, (a.rows + tile_rows - 1) / tile_rows, 8);
+    const int grid = grid_for(L, (a.rows + tile_rows - 1) / tile_rows, kOnePass);
     if (a.f >= 4)
         hipLaunchKernelGGL(aggregate_kernel<4>, dim3(grid), dim3(kFeatThreads), 0, L.stream, a, tile_rows);
     else
