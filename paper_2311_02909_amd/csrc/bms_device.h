@@ -137,7 +137,7 @@ __device__ inline T block_exclusive_scan(T v, T *smem, T &total)
 {
     constexpr int NW = NT / kWave;
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     T inc = wave_inclusive_scan(v);
     __syncthreads(); // protects smem against readers of a previous call
     if (lane == kWave - 1)
@@ -293,6 +293,20 @@ __device__ inline int locate_segment(const int64_t *__restrict__ off, int k, int
     while (hi - lo > 1) {
         int mid = (lo + hi) >> 1;
         if (off[mid] <= t)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+// The same through the scalar unit: off is not written during the launch, t the same in all lanes.
+__device__ inline int locate_uniform(const int64_t *off, int k, int64_t t)
+{
+    int lo = 0, hi = k;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (uniform_load(off + mid) <= t)
             lo = mid;
         else
             hi = mid;

@@ -247,6 +247,7 @@ struct DedupArgs {
     uint32_t *run_cnt;   // tiles * C: its length
     uint16_t *ranks;     // nnz, parallel to ids_seg: rank of the id among the distinct ids of its segment
     int32_t past;        // 1: the local columns are stored past the caches
+    int64_t nnz_tune;    // entries there are likely to be
     uint32_t *uids;      // nnz: the distinct ids of a segment in ascending order, at the head of the segment's slots
 };
 constexpr int kCutTile = 8192; // positions per tile of the count, split and un-split kernels

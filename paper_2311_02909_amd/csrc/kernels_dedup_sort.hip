@@ -29,8 +29,7 @@
 
 namespace bms {
 
-constexpr int kLocShift = 13; // bits of the place inside a run (a tile holds 2^13 positions)
-static_assert(kCutTile == (1 << kLocShift) && kMaxSegments <= (1 << (32 - kLocShift)), "loc word out of step");
+static_assert(kCutTile <= 1 << 16, "places of the cut in 16 bits");
 
 // Tiles of a minibatch's N positions, which begin at e0 of the stacked columns: all but the first one begin at a memory line (of an
 // array that does), so that a tile's columns are read and written by whole lines.
@@ -219,46 +218,66 @@ __global__ __launch_bounds__(256) void dd_seg_scan_kernel(DedupArgs a)
 }
 
 // TILE positions per workgroup step, NT threads.  The larger the tile, the longer the run every segment gets
-// in one step (a step's ids spread over all C segments), i.e. the wider the stores.
-template <int TILE, int NT>
-__global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
+// in one step (a step's ids spread over all C segments), i.e. the wider the stores.  Three workgroups share a compute unit (four, in
+// 64 registers, spill: 0.152 ms for 0.133).  Two hops of 256 x 1024 seeds, (15, 10, 5), 111 M vertices, 58 M entries: 0.160 ms with a
+// thousand workgroups that go from tile to tile, 0.143 with a tile each, 0.133 without a mask per id in whole tiles and with the
+// table of segments as a kernel of its own; of 128 on 8.7 M, 86 M entries: 0.238, 0.203 and 0.190.
+constexpr int kSplitThreads = 512;
+template <int TILE, int NT, bool TAB>
+__global__ __launch_bounds__(NT, 6) void dd_split_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
 {
-    extern __shared__ uint32_t split_lds[]; // stage[TILE]; then 3 C words: per-segment count, start in the tile, start in global - start in the tile
+    // stage[TILE]; then 3 C words: per-segment count, start in the tile, start in global - start in the tile; then the table of
+    // segments, if there is one (TAB: a.tab; four workgroups share a compute unit without it)
+    extern __shared__ uint32_t split_lds[];
     __shared__ uint32_t smem[NT / kWave];
     __shared__ uint32_t carry_s;
-    __shared__ uint16_t tab_l[kMaxCells + 1];
     if (*a.fallback)
         return;
     uint32_t *stage = split_lds;
     uint32_t *cnt = split_lds + TILE, *off = cnt + a.C, *gpos = cnt + 2 * a.C;
-    const int tid = threadIdx.x;
-    load_seg_table(a, tab_l, NT);
-    const int64_t ntiles = tileoff[a.k];
+    uint16_t *tab_l = reinterpret_cast<uint16_t *>(cnt + 3 * a.C);
+    if (TAB)
+        load_seg_table(a, tab_l, NT);
+    const int shift = TAB ? a.fshift : a.cshift;
+    auto segment = [&](uint32_t id) { return TAB ? (uint32_t)tab_l[id >> shift] : id >> shift; };
+    const int64_t ntiles = uniform_load(tileoff + a.k);
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int i = locate_segment(tileoff, a.k, t);
-        const int64_t e0 = a.mb_edgeoff[i];
-        const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid)); // (places: computed anew for every tile, not kept in registers)
+        const int i = locate_uniform(tileoff, a.k, t);
+        const int64_t e0 = uniform_load(a.mb_edgeoff + i);
+        const uint32_t N = (uint32_t)(uniform_load(a.mb_edgeoff + i + 1) - e0);
         uint32_t j0, jend;
-        cut_tile(e0, N, (uint32_t)(t - tileoff[i]), j0, jend);
-        const int32_t *__restrict__ col = a.col + e0;
+        cut_tile(e0, N, (uint32_t)(t - uniform_load(tileoff + i)), j0, jend);
+        const int n = (int)scalar(jend - j0), left = n - tid;
+        const int32_t *__restrict__ col = a.col + scalar(e0 + j0);
+        uint16_t *__restrict__ loc = a.loc + scalar(e0 + j0);
+        uint32_t id[TILE / NT]; // (< 2^31)
+        uint32_t place[TILE / NT]; // in the tile's run for the segment
+#pragma unroll
+        for (int q = 0; q < TILE / NT; ++q) {
+            id[q] = left > q * NT ? (uint32_t)(col + q * NT)[tid] : 0;
+            place[q] = 0;
+        }
         for (int c = tid; c < a.C; c += NT)
             cnt[c] = 0;
         if (tid == 0)
             carry_s = 0;
         __syncthreads();
-        uint32_t id[TILE / NT];
-        uint32_t lpos[TILE / NT]; // segment << kLocShift | place in the tile's run for that segment
+        // (whole tiles without a mask per id)
+        auto each = [&](auto body) {
+            if (n == TILE) {
 #pragma unroll
-        for (int q = 0; q < TILE / NT; ++q) {
-            const uint32_t j = j0 + q * NT + tid;
-            id[q] = j < jend ? (uint32_t)col[j] : 0xFFFFFFFFu; // ids are < 2^31
-        }
+                for (int q = 0; q < TILE / NT; ++q)
+                    body(q);
+            } else {
 #pragma unroll
-        for (int q = 0; q < TILE / NT; ++q)
-            if (id[q] != 0xFFFFFFFFu) {
-                const uint32_t c = seg_of(a, tab_l, id[q]);
-                lpos[q] = (c << kLocShift) | atomicAdd(&cnt[c], 1u);
+                for (int q = 0; q < TILE / NT; ++q)
+                    if (left > q * NT)
+                        body(q);
             }
+        };
+        each([&](int q) { place[q] = atomicAdd(&cnt[segment(id[q])], 1u); });
         __syncthreads();
         uint32_t *__restrict__ run_gpos = a.run_gpos + t * a.C, *__restrict__ run_cnt = a.run_cnt + t * a.C;
         for (int base = 0; base < a.C; base += NT) {
@@ -281,20 +300,17 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
                 carry_s = carry + total;
             __syncthreads();
         }
-        uint16_t *__restrict__ loc = a.loc + e0 + j0;
-#pragma unroll
-        for (int q = 0; q < TILE / NT; ++q)
-            if (id[q] != 0xFFFFFFFFu) {
-                const uint32_t at = off[lpos[q] >> kLocShift] + (lpos[q] & (TILE - 1));
-                stage[at] = id[q];
-                loc[q * NT + tid] = (uint16_t)at;
-            }
+        each([&](int q) {
+            const uint32_t at = off[segment(id[q])] + place[q];
+            stage[at] = id[q];
+            (loc + q * NT)[tid] = (uint16_t)at;
+        });
         __syncthreads();
         uint32_t *__restrict__ ids_seg = a.ids_seg + e0;
-        for (uint32_t sidx = tid; sidx < jend - j0; sidx += NT) {
-            const uint32_t g = stage[sidx];
-            ids_seg[gpos[seg_of(a, tab_l, g)] + sidx] = g;
-        }
+        each([&](int q) {
+            const uint32_t g = (stage + q * NT)[tid];
+            ids_seg[gpos[segment(g)] + (uint32_t)(q * NT + tid)] = g;
+        });
         __syncthreads();
     }
 }
@@ -311,17 +327,18 @@ __global__ __launch_bounds__(NT) void dd_split_kernel(DedupArgs a, const int64_t
 //      ids in ascending order
 //   5  popcount prefix over the bits: the rank of an id among the distinct ones = runs before its own
 //   6  ranks leave in slot order; the ids go to their rank, copied out as the distinct ids
-// A chain of dependent LDS steps, so what counts is how many workgroups share a compute unit: 80 registers let three do so (two
-// before).  256 x 240 k ids of 111 M: 343 us with two, 296 with three, 309 with four, which spill and cannot fetch ahead.
-// Four reads of the bucket at once instead of one by one: two hops of that call 391 -> 374 us.  About 13 LDS accesses per id are
-// two thirds of it.
+// A chain of dependent LDS steps, so what counts is how many workgroups share a compute unit.  256 x 240 k ids of 111 M: 343 us with
+// two, 296 with three that went from one segment to the next and fetched its ids ahead (80 registers).  A workgroup per segment
+// needs no loop, whose carried values and places cost half of the registers (45 without), so that four share a unit, and nobody waits
+// for a segment's stores: two hops of that call 384 us so far, 349 started per segment with the loop, 280 without.  About 13 LDS
+// accesses per id bound it.
 constexpr int kRankCap = 4096;    // ids of a segment that one workgroup of the ranking kernel takes
 constexpr int kRankThreads = 512;
 constexpr int kRankBucketBits = 12; // at most 4096 buckets
 constexpr int kRankMaxInBucket = 32;
 static_assert(kRankCap == kRankCapFwd, "segment capacity out of step");
 
-__global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
+__global__ __launch_bounds__(kRankThreads, 8) void dd_rank_kernel(DedupArgs a)
 {
     constexpr int NT = kRankThreads, NW = NT / kWave, PER = kRankCap / NT, NB = 1 << kRankBucketBits;
     __shared__ uint4 cnt4[NB / 4 + 1];           // bucket sizes, then bucket starts; start[nb] = m
@@ -331,219 +348,182 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
     uint32_t *cnt = reinterpret_cast<uint32_t *>(cnt4);
     if (*a.fallback)
         return;
-    int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int64_t nseg = (int64_t)a.k * a.C;
-    // The ids of the segment after this one are fetched while this one is ranked (a workgroup's segments follow one
-    // another as chains of dependent steps, and only three workgroups fit a compute unit).
-    // where segment w lies: first slot, ids, where its minibatch's ids start
-    auto where = [&](int64_t w, uint32_t &s0, uint32_t &m, int64_t &e0) {
-        s0 = m = 0;
-        e0 = 0;
-        if (w < nseg) {
-            const int64_t i = w % a.k; // workgroups that run at the same time take segments of different minibatches
-            const uint32_t cseg = (uint32_t)(w / a.k);
-            const uint32_t *__restrict__ soff = a.seg_off + i * (a.C + 1);
-            s0 = soff[cseg];
-            m = soff[cseg + 1] - s0;
-            e0 = a.mb_edgeoff[i];
-        }
-    };
-    // its ids as the kernel keeps them: slot j = q NT + tid, unused slots all ones (no segment, or one that another
-    // kernel ranks: nothing is read)
-    auto fetch = [&](uint32_t s0, uint32_t m, int64_t e0, uint32_t (&key)[PER]) {
-        const uint32_t *__restrict__ ids = a.ids_seg + e0 + s0;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const uint32_t j = q * NT + tid;
-            key[q] = (m <= (uint32_t)kRankCap && j < m) ? ids[j] : 0xFFFFFFFFu;
-        }
-    };
-    uint32_t s0, m, s0_next, m_next;
-    int64_t e0, e0_next;
-    uint32_t key[PER], key_next[PER];
-    where(blockIdx.x, s0, m, e0);
-    fetch(s0, m, e0, key);
-    for (int64_t w = blockIdx.x; w < nseg; w += gridDim.x, s0 = s0_next, m = m_next, e0 = e0_next) {
-        asm volatile("" : "+v"(tid), "+v"(lane)); // (places: computed anew for every segment, not kept in registers)
-        where(w + gridDim.x, s0_next, m_next, e0_next);
-        const int64_t i = w % a.k;
-        const uint32_t cseg = (uint32_t)(w / a.k);
-        const int64_t sg = i * a.C + cseg;
-        if (m > (uint32_t)kRankCap || m == 0) { // listed for the bitmap kernel by the scan, or empty
-            if (m == 0 && tid == 0)
-                a.seg_cnt[sg] = 0;
-            fetch(s0_next, m_next, e0_next, key);
-            continue;
-        }
-        uint32_t id0;
-        int wbits;
-        seg_range(a, cseg, id0, wbits);
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (key[q] != 0xFFFFFFFFu)
-                key[q] -= id0;
-        // buckets: a power of two >= m, 512..4096, no more than the segment has ids
-        int nbits = 32 - __clz(m - 1u); // ceil(log2 m); m = 1: __clz(0) = 32
-        if (m == 1u || nbits < 9)
-            nbits = 9;
-        if (nbits > kRankBucketBits)
-            nbits = kRankBucketBits;
-        if (nbits > wbits)
-            nbits = wbits;
-        const int bshift = wbits - nbits;
-        const int nb = 1 << nbits;
-        const int nqd = nb >= 4 ? nb / 4 : 1;                  // 16-byte quads of counters
-        const int qw = (nqd + NW - 1) / NW;                    // per wave
-        const int its = (qw + kWave - 1) / kWave;              // per lane: 1 or 2
-        for (int qd = tid; qd < nqd; qd += NT)
-            cnt4[qd] = make_uint4(0, 0, 0, 0);
-        for (uint32_t x = tid; x < (m + 31u) / 32u; x += NT)
-            hbits[x] = 0;
-        __syncthreads();
-        fetch(s0_next, m_next, e0_next, key_next);
-        uint32_t at[PER]; // slot in the bucket; then the bucket's start, size (from bit 13) and the slot; from step 4 on: place of the id's run
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (key[q] != 0xFFFFFFFFu)
-                at[q] = atomicAdd(&cnt[key[q] >> bshift], 1u);
-        __syncthreads();
-        // exclusive scan of the bucket sizes, in place
-        uint4 cv[2];
-        uint32_t inc[2], mine[2];
-        uint32_t wave_total = 0;
-        bool crowded = false;
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            cv[it] = make_uint4(0, 0, 0, 0);
-            mine[it] = inc[it] = 0;
-            if (it < its) {
-                const int lq = it * kWave + lane; // quad inside this wave's part
-                if (lq < qw && wave * qw + lq < nqd)
-                    cv[it] = cnt4[wave * qw + lq];
-                crowded |= cv[it].x > (uint32_t)kRankMaxInBucket || cv[it].y > (uint32_t)kRankMaxInBucket ||
-                           cv[it].z > (uint32_t)kRankMaxInBucket || cv[it].w > (uint32_t)kRankMaxInBucket;
-                mine[it] = cv[it].x + cv[it].y + cv[it].z + cv[it].w;
-                inc[it] = wave_inclusive_scan_dpp(mine[it]) + wave_total;
-                wave_total = (uint32_t)__builtin_amdgcn_readlane((int)inc[it], kWave - 1);
-            }
-        }
-        if (lane == 0)
-            wtot[wave] = wave_total;
-        if (__syncthreads_or(crowded)) { // uniform for the workgroup
-            if (tid == 0) {
-                if (wbits <= a.wbits_max)
-                    a.big_list[atomicAdd(a.big_count, 1u)] = (uint32_t)sg;
-                else
-                    atomicOr(a.fallback, 1);
-            }
-#pragma unroll
-            for (int q = 0; q < PER; ++q)
-                key[q] = key_next[q];
-            continue;
-        }
-        uint32_t run = 0;
-#pragma unroll
-        for (int w2 = 0; w2 < NW; ++w2)
-            run += w2 < wave ? wtot[w2] : 0u;
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            if (it < its) {
-                const int lq = it * kWave + lane;
-                if (lq < qw && wave * qw + lq < nqd) {
-                    const uint32_t s = run + inc[it] - mine[it];
-                    cnt4[wave * qw + lq] = make_uint4(s, s + cv[it].x, s + cv[it].x + cv[it].y, s + cv[it].x + cv[it].y + cv[it].z);
-                }
-            }
-        }
-        if (tid == 0)
-            cnt[nb] = m;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (key[q] != 0xFFFFFFFFu) {
-                const uint32_t bucket = key[q] >> bshift, bs = cnt[bucket], be = cnt[bucket + 1u];
-                sorted[bs + at[q]] = key[q];
-                at[q] = at[q] << 19 | (be - bs) << 13 | bs;
-            }
-        if (tid < 3)
-            sorted[m + tid] = 0xFFFFFFFFu; // (step 4 reads that far)
-        __syncthreads();
-        // place of every id's run of equal ids in ascending order; heads
-        if (bshift == 0) { // one id per bucket: the run is the bucket
-#pragma unroll
-            for (int q = 0; q < PER; ++q)
-                if (key[q] != 0xFFFFFFFFu) {
-                    const uint32_t p = at[q] & 8191u;
-                    if (at[q] >> 19 == 0)
-                        atomicOr(&hbits[p >> 5], 1u << (p & 31u));
-                    at[q] = p;
-                }
-        } else {
-            // the ids after a bucket are larger than its own: four reads each, of two ids at a time, whatever the bucket's size
-#pragma unroll
-            for (int q0 = 0; q0 < PER; q0 += 2) {
-                uint32_t o[2][4];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        o[u][t] = sorted[(key[q0 + u] != 0xFFFFFFFFu ? at[q0 + u] & 8191u : 0u) + t];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int q = q0 + u;
-                    if (key[q] == 0xFFFFFFFFu)
-                        continue;
-                    const uint32_t bs = at[q] & 8191u, n = (at[q] >> 13) & 63u;
-                    uint32_t p = bs;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        p += o[u][t] < key[q] ? 1u : 0u;
-                    for (uint32_t t = 4; t < n; ++t)
-                        p += sorted[bs + t] < key[q] ? 1u : 0u;
-                    atomicOr(&hbits[p >> 5], 1u << (p & 31u));
-                    at[q] = p;
-                }
-            }
-        }
-        __syncthreads();
-        const uint32_t nwd = (m + 31u) / 32u; // <= 128 words of head bits
-        if (wave == 0) {
-            uint32_t carry = 0;
-#pragma unroll
-            for (int it = 0; it < 2; ++it) {
-                const uint32_t x = it * kWave + lane;
-                const uint32_t pcw = x < nwd ? __popc(hbits[x]) : 0u;
-                const uint32_t in2 = wave_inclusive_scan_dpp(pcw) + carry;
-                if (x < nwd)
-                    hpre[x] = in2 - pcw;
-                carry = (uint32_t)__builtin_amdgcn_readlane((int)in2, kWave - 1);
-            }
-            if (lane == 0) {
-                wtot[0] = carry;
-                a.seg_cnt[sg] = carry;
-            }
-        }
-        __syncthreads();
-        const uint32_t cnt_distinct = wtot[0];
-        uint16_t *__restrict__ ranks = a.ranks + e0 + s0;
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (key[q] != 0xFFFFFFFFu) {
-                const uint32_t p = at[q];
-                const uint32_t r = hpre[p >> 5] + __popc(hbits[p >> 5] & ((1u << (p & 31u)) - 1u));
-                ranks[q * NT + tid] = (uint16_t)r;
-                sorted[r] = key[q]; // every id has been looked at (step 4): their place now takes the distinct ones
-            }
-        __syncthreads();
-        uint32_t *__restrict__ uids = a.uids + e0 + s0;
-        for (uint32_t r = tid; r < cnt_distinct; r += NT)
-            uids[r] = id0 + sorted[r];
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            key[q] = key_next[q];
-        __syncthreads();
+    const uint32_t cseg = blockIdx.y;
+    const int64_t i = blockIdx.x; // workgroups that run at the same time take segments of different minibatches
+    const int64_t sg = i * a.C + cseg;
+    const uint32_t s0 = uniform_load(a.seg_off + i * (a.C + 1) + cseg), m = uniform_load(a.seg_off + i * (a.C + 1) + cseg + 1) - s0;
+    const int64_t e0 = uniform_load(a.mb_edgeoff + i);
+    if (m > (uint32_t)kRankCap || m == 0) { // listed for the bitmap kernel by the scan, or empty
+        if (m == 0 && tid == 0)
+            a.seg_cnt[sg] = 0;
+        return;
     }
+    uint32_t key[PER]; // slot j = q NT + tid, unused slots all ones
+    const uint32_t *__restrict__ ids = a.ids_seg + e0 + s0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        key[q] = (uint32_t)(q * NT + tid) < m ? ids[q * NT + tid] : 0xFFFFFFFFu;
+    uint32_t id0;
+    int wbits;
+    seg_range(a, cseg, id0, wbits);
+    // buckets: a power of two >= m, 512..4096, no more than the segment has ids
+    int nbits = 32 - __clz(m - 1u); // ceil(log2 m); m = 1: __clz(0) = 32
+    if (m == 1u || nbits < 9)
+        nbits = 9;
+    if (nbits > kRankBucketBits)
+        nbits = kRankBucketBits;
+    if (nbits > wbits)
+        nbits = wbits;
+    const int bshift = wbits - nbits;
+    const int nb = 1 << nbits;
+    const int nqd = nb >= 4 ? nb / 4 : 1;                  // 16-byte quads of counters
+    const int qw = (nqd + NW - 1) / NW;                    // per wave
+    const int its = (qw + kWave - 1) / kWave;              // per lane: 1 or 2
+    for (int qd = tid; qd < nqd; qd += NT)
+        cnt4[qd] = make_uint4(0, 0, 0, 0);
+    for (uint32_t x = tid; x < (m + 31u) / 32u; x += NT)
+        hbits[x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (key[q] != 0xFFFFFFFFu)
+            key[q] -= id0;
+    uint32_t at[PER]; // slot in the bucket; then the bucket's start, size (from bit 13) and the slot; from step 4 on: place of the id's run
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (key[q] != 0xFFFFFFFFu)
+            at[q] = atomicAdd(&cnt[key[q] >> bshift], 1u);
+    __syncthreads();
+    // exclusive scan of the bucket sizes, in place
+    uint4 cv[2];
+    uint32_t inc[2], mine[2];
+    uint32_t wave_total = 0;
+    bool crowded = false;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        cv[it] = make_uint4(0, 0, 0, 0);
+        mine[it] = inc[it] = 0;
+        if (it < its) {
+            const int lq = it * kWave + lane; // quad inside this wave's part
+            if (lq < qw && wave * qw + lq < nqd)
+                cv[it] = cnt4[wave * qw + lq];
+            crowded |= cv[it].x > (uint32_t)kRankMaxInBucket || cv[it].y > (uint32_t)kRankMaxInBucket ||
+                       cv[it].z > (uint32_t)kRankMaxInBucket || cv[it].w > (uint32_t)kRankMaxInBucket;
+            mine[it] = cv[it].x + cv[it].y + cv[it].z + cv[it].w;
+            inc[it] = wave_inclusive_scan_dpp(mine[it]) + wave_total;
+            wave_total = (uint32_t)__builtin_amdgcn_readlane((int)inc[it], kWave - 1);
+        }
+    }
+    if (lane == 0)
+        wtot[wave] = wave_total;
+    if (__syncthreads_or(crowded)) { // uniform for the workgroup
+        if (tid == 0) {
+            if (wbits <= a.wbits_max)
+                a.big_list[atomicAdd(a.big_count, 1u)] = (uint32_t)sg;
+            else
+                atomicOr(a.fallback, 1);
+        }
+        return;
+    }
+    uint32_t run = 0;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2)
+        run += w2 < wave ? wtot[w2] : 0u;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        if (it < its) {
+            const int lq = it * kWave + lane;
+            if (lq < qw && wave * qw + lq < nqd) {
+                const uint32_t s = run + inc[it] - mine[it];
+                cnt4[wave * qw + lq] = make_uint4(s, s + cv[it].x, s + cv[it].x + cv[it].y, s + cv[it].x + cv[it].y + cv[it].z);
+            }
+        }
+    }
+    if (tid == 0)
+        cnt[nb] = m;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (key[q] != 0xFFFFFFFFu) {
+            const uint32_t bucket = key[q] >> bshift, bs = cnt[bucket], be = cnt[bucket + 1u];
+            sorted[bs + at[q]] = key[q];
+            at[q] = at[q] << 19 | (be - bs) << 13 | bs;
+        }
+    if (tid < 3)
+        sorted[m + tid] = 0xFFFFFFFFu; // (step 4 reads that far)
+    __syncthreads();
+    // place of every id's run of equal ids in ascending order; heads
+    if (bshift == 0) { // one id per bucket: the run is the bucket
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (key[q] != 0xFFFFFFFFu) {
+                const uint32_t p = at[q] & 8191u;
+                if (at[q] >> 19 == 0)
+                    atomicOr(&hbits[p >> 5], 1u << (p & 31u));
+                at[q] = p;
+            }
+    } else {
+        // the ids after a bucket are larger than its own: four reads each, of two ids at a time, whatever the bucket's size
+#pragma unroll
+        for (int q0 = 0; q0 < PER; q0 += 2) {
+            uint32_t o[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    o[u][t] = sorted[(key[q0 + u] != 0xFFFFFFFFu ? at[q0 + u] & 8191u : 0u) + t];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int q = q0 + u;
+                if (key[q] == 0xFFFFFFFFu)
+                    continue;
+                const uint32_t bs = at[q] & 8191u, n = (at[q] >> 13) & 63u;
+                uint32_t p = bs;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    p += o[u][t] < key[q] ? 1u : 0u;
+                for (uint32_t t = 4; t < n; ++t)
+                    p += sorted[bs + t] < key[q] ? 1u : 0u;
+                atomicOr(&hbits[p >> 5], 1u << (p & 31u));
+                at[q] = p;
+            }
+        }
+    }
+    __syncthreads();
+    const uint32_t nwd = (m + 31u) / 32u; // <= 128 words of head bits
+    if (wave == 0) {
+        uint32_t carry = 0;
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            const uint32_t x = it * kWave + lane;
+            const uint32_t pcw = x < nwd ? __popc(hbits[x]) : 0u;
+            const uint32_t in2 = wave_inclusive_scan_dpp(pcw) + carry;
+            if (x < nwd)
+                hpre[x] = in2 - pcw;
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)in2, kWave - 1);
+        }
+        if (lane == 0) {
+            wtot[0] = carry;
+            a.seg_cnt[sg] = carry;
+        }
+    }
+    __syncthreads();
+    const uint32_t cnt_distinct = wtot[0];
+    uint16_t *__restrict__ ranks = a.ranks + e0 + s0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (key[q] != 0xFFFFFFFFu) {
+            const uint32_t p = at[q];
+            const uint32_t r = hpre[p >> 5] + __popc(hbits[p >> 5] & ((1u << (p & 31u)) - 1u));
+            ranks[q * NT + tid] = (uint16_t)r;
+            sorted[r] = key[q]; // every id has been looked at (step 4): their place now takes the distinct ones
+        }
+    __syncthreads();
+    uint32_t *__restrict__ uids = a.uids + e0 + s0;
+    for (uint32_t r = tid; r < cnt_distinct; r += NT)
+        uids[r] = id0 + sorted[r];
 }
 
 // Ranking through a bitmap of the segment's id range in LDS (2^cshift bits, at most 128 KB): no sort.  The rank
@@ -561,7 +541,7 @@ __global__ __launch_bounds__(kRankThreads, 6) void dd_rank_kernel(DedupArgs a)
 // What bounds it is latency: trips to memory for ids that are not in registers, and, before step 3 did it, the stores of the
 // distinct ids straight from the bitmap, scattered over a wave's lanes (128 x 586 k ids of 8.7 M: 475 us so, 262 us without).
 // Two workgroups share a compute unit, which leaves 64 registers: enough as long as what the lanes have in common is in scalar
-// ones.  With a segment's place and length in every lane 14 registers went to memory and back, as many bytes again as the ids
+// ones, and a workgroup has one segment (282 us for the two hops when it could have several, 255 so).  With a segment's place and length in every lane 14 registers went to memory and back, as many bytes again as the ids
 // themselves: the last two hops of 128 x 1024 seeds, (15, 10, 5), took 373 us so and 281 us without.
 constexpr int kBmThreads = 1024;
 constexpr int kBmWaves = kBmThreads / kWave;
@@ -599,13 +579,13 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
     uint32_t *place = reinterpret_cast<uint32_t *>(bm_lds + nq);
     uint16_t *qpre = reinterpret_cast<uint16_t *>(place + places);
     const uint32_t q_wave = (uint32_t)wave * (uint32_t)(its * kWave); // first quad of this wave's part
-    const uint32_t nwork = LISTED ? *a.big_count : (uint32_t)a.k * (uint32_t)a.C; // (fits: the list holds segments in 32 bits)
-    if (blockIdx.x >= nwork)
+    const uint32_t nwork = LISTED ? *a.big_count : 0u;
+    if (LISTED && blockIdx.x >= nwork)
         return; // usually nothing is listed
     for (int it = 0; it < its; ++it)
         quads[q_wave + it * kWave + lane] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    // where a segment lies; its first ids are fetched while the segment before it is worked on
+    // where a segment lies; the first ids of a listed one are fetched while the segment before it is worked on
     struct Seg {
         int64_t e0;
         uint32_t sg, s0, m, id0;
@@ -613,13 +593,15 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
     auto locate = [&](uint32_t x, Seg &g) {
         g.m = g.s0 = g.id0 = g.sg = 0;
         g.e0 = 0;
-        if (x >= nwork)
+        if (LISTED && x >= nwork)
             return;
-        if (LISTED)
+        uint32_t i = blockIdx.x, c = blockIdx.y; // workgroups that run at the same time take segments of different minibatches
+        g.sg = i * (uint32_t)a.C + c;            // (fits: the list holds segments in 32 bits)
+        if (LISTED) {
             g.sg = scalar(a.big_list[x]);
-        else // workgroups that run at the same time take segments of different minibatches
-            g.sg = (x % (uint32_t)a.k) * (uint32_t)a.C + x / (uint32_t)a.k;
-        const uint32_t i = g.sg / (uint32_t)a.C, c = g.sg % (uint32_t)a.C;
+            i = g.sg / (uint32_t)a.C;
+            c = g.sg % (uint32_t)a.C;
+        }
         const uint32_t *__restrict__ soff = a.seg_off + (int64_t)i * (a.C + 1);
         int wbits;
         seg_range(a, c, g.id0, wbits);
@@ -641,9 +623,11 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
     uint32_t keep[kBmKeep], next[kBmKeep];
     locate(blockIdx.x, cur);
     fetch(cur, next);
-    for (uint32_t x = blockIdx.x; x < nwork; x += gridDim.x, cur = nxt) {
-        asm volatile("" : "+v"(tid), "+v"(lane)); // (places: computed anew for every segment, not kept in registers)
-        locate(x + gridDim.x, nxt);
+    for (uint32_t x = blockIdx.x; !LISTED || x < nwork; x += gridDim.x, cur = nxt) {
+        if (LISTED) {
+            asm volatile("" : "+v"(tid), "+v"(lane)); // (places: computed anew for every segment, not kept in registers)
+            locate(x + gridDim.x, nxt);
+        }
         const uint32_t m = cur.m, id0 = cur.id0;
 #pragma unroll
         for (int q = 0; q < kBmKeep; ++q)
@@ -651,6 +635,8 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
         if (m == 0) {
             if (tid == 0)
                 a.seg_cnt[cur.sg] = 0;
+            if (!LISTED)
+                return;
             fetch(nxt, next);
             continue;
         }
@@ -667,7 +653,8 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
             atomicOr(&words[b >> 5], 1u << (b & 31u));
         }
         __syncthreads();
-        fetch(nxt, next);
+        if (LISTED)
+            fetch(nxt, next);
         // 2: counts before every quad
         uint32_t inc[kBmIts];
         uint32_t wave_total = 0;
@@ -723,6 +710,8 @@ __global__ __launch_bounds__(kBmThreads, 8) void dd_bitmap_kernel(DedupArgs a, u
         if (placed)
             for (uint32_t r = tid; r < cnt; r += kBmThreads)
                 uids[r] = place[r];
+        if (!LISTED)
+            return;
         // 4: clear
         if (m * 4u < nq) {
 #pragma unroll
@@ -847,17 +836,17 @@ __global__ __launch_bounds__(NT, 8) void dd_unsplit_kernel(DedupArgs a, const in
     static_assert(TILE <= 1 << 16 && TILE / kWave == 2 * kWave, "two words of 64 places per lane");
     uint32_t *stage = unsplit_lds, *starts = unsplit_lds + TILE;
     uint32_t *delta = starts + TILE / 32, *base_l = delta + a.C;
-    const int64_t ntiles = tileoff[a.k];
+    const int64_t ntiles = uniform_load(tileoff + a.k);
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid)); // (places: computed anew for every tile, not kept in registers)
         __builtin_assume(tid < NT);
         const uint32_t lane = tid & (kWave - 1), wave = scalar(tid / kWave);
-        const int i = locate_segment(tileoff, a.k, t);
-        const int64_t e0 = a.mb_edgeoff[i];
-        const uint32_t N = (uint32_t)(a.mb_edgeoff[i + 1] - e0);
+        const int i = locate_uniform(tileoff, a.k, t);
+        const int64_t e0 = uniform_load(a.mb_edgeoff + i);
+        const uint32_t N = (uint32_t)(uniform_load(a.mb_edgeoff + i + 1) - e0);
         uint32_t j0, jend;
-        cut_tile(e0, N, (uint32_t)(t - tileoff[i]), j0, jend);
+        cut_tile(e0, N, (uint32_t)(t - uniform_load(tileoff + i)), j0, jend);
         const int n = (int)scalar(jend - j0);
         int left = n - (int)tid;
         const uint16_t *__restrict__ loc = a.loc + scalar(e0 + j0);
@@ -1035,6 +1024,13 @@ void launch_nw_dedup_table(const Launch &L, const int32_t *col, const int64_t *n
                        (int32_t)max_cells, tab, seg_first);
 }
 
+// Workgroups for the tiles of the cut: one each of as many as there are likely to be.  (Of a call that reads no sizes back nnz is a
+// bound, several times what there is; a workgroup without a tile takes its time as well.)
+static int cut_grid(const Launch &L, const DedupArgs &a, int64_t nnz)
+{
+    return grid_for(L, cut_tiles_bound(std::min(nnz, a.nnz_tune + a.nnz_tune / 8), a.k), kOnePass);
+}
+
 void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64_t *out_rowptr, const int64_t *mb_rowoff,
                                 int64_t *mb_coloff, int32_t *col_vertex, int64_t *ncols_out, int64_t *next_tileoff,
                                 uint32_t *done, int64_t nnz, bool counted, const StageMark &mark)
@@ -1049,17 +1045,18 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
     }
     mark("dd_split");
     { // 8192 ids per step, workgroups of 8 waves, several per compute unit
+        void (*const kernels[2])(DedupArgs, const int64_t *) = {dd_split_kernel<kCutTile, kSplitThreads, false>, dd_split_kernel<kCutTile, kSplitThreads, true>};
         static bool attr_set = false;
-        const size_t lds = (size_t)kCutTile * sizeof(uint32_t) + 3 * (size_t)a.C * sizeof(uint32_t);
+        const size_t table = ((size_t)kMaxCells + 2) * sizeof(uint16_t);
         if (!attr_set) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(dd_split_kernel<kCutTile, 512>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)(kCutTile * sizeof(uint32_t) + 3 * kMaxSegments * sizeof(uint32_t))) != hipSuccess)
-                (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
+            for (auto *kernel : kernels)
+                if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)(kCutTile * sizeof(uint32_t) + 3 * kMaxSegments * sizeof(uint32_t) + table)) != hipSuccess)
+                    (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
             attr_set = true;
         }
-        hipLaunchKernelGGL((dd_split_kernel<kCutTile, 512>), dim3(grid_for(L, tiles, kOnePass)), dim3(512), lds,
-                           L.stream, a, a.big_tileoff);
+        const size_t lds = (size_t)kCutTile * sizeof(uint32_t) + 3 * (size_t)a.C * sizeof(uint32_t) + (a.tab ? table : 0);
+        hipLaunchKernelGGL(kernels[a.tab ? 1 : 0], dim3(cut_grid(L, a, nnz)), dim3(kSplitThreads), lds, L.stream, a, a.big_tileoff);
     }
     mark("dd_rank");
     static bool big_attr_set = false;
@@ -1078,10 +1075,10 @@ void launch_nw_extract_segments(const Launch &L, const DedupArgs &a, const int64
     const int bm_per_cu = (int)std::max<size_t>(1, std::min<size_t>(2, (size_t)(156 * 1024) / bm_lds));
     const uint32_t places = (uint32_t)bm_places(a.wbits_max <= kMaxBitmapShift ? a.wbits_max : kMaxBitmapShift);
     if (a.by_bitmap) {
-        hipLaunchKernelGGL(dd_bitmap_kernel<false>, dim3(grid_for(L, (int64_t)a.k * a.C, kOnePass)), dim3(kBmThreads),
+        hipLaunchKernelGGL(dd_bitmap_kernel<false>, dim3(a.k, a.C), dim3(kBmThreads),
                            bm_lds, L.stream, a, places);
     } else {
-        hipLaunchKernelGGL(dd_rank_kernel, dim3(grid_for(L, (int64_t)a.k * a.C, kOnePass)), dim3(kRankThreads), 0, L.stream, a);
+        hipLaunchKernelGGL(dd_rank_kernel, dim3(a.k, a.C), dim3(kRankThreads), 0, L.stream, a);
         if (a.tab || a.cshift <= kMaxBitmapShift) // segments the counting kernel did not take (none can be listed otherwise)
             hipLaunchKernelGGL(dd_bitmap_kernel<true>, dim3(grid_for(L, nnz / 1024 + 1, bm_per_cu)), dim3(kBmThreads),
                                bm_lds, L.stream, a, places);
@@ -1105,8 +1102,7 @@ static void launch_unsplit(const Launch &L, const DedupArgs &a, int64_t nnz)
             (void)hipGetLastError(); // not required on every runtime; a refused launch shows in the caller's error check
         attr_set = true;
     }
-    const int64_t tiles = cut_tiles_bound(nnz, a.k);
-    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512, PAST>), dim3(grid_for(L, tiles, kOnePass)), dim3(512), lds, L.stream, a,
+    hipLaunchKernelGGL((dd_unsplit_kernel<kCutTile, 512, PAST>), dim3(cut_grid(L, a, nnz)), dim3(512), lds, L.stream, a,
                        a.big_tileoff);
 }
 

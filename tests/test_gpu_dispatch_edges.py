@@ -331,6 +331,26 @@ def test_tiles_of_the_cut_at_memory_lines(n, b, base, segments, variant):
         assert_hops_equal(res.hops(), ref, what="call %d" % call)
 
 
+# the cut starts a workgroup for every tile that the call before makes likely: a call of three times the entries has more
+@pytest.mark.parametrize("n", [400_000, 20_000_000])    # segments by bitmaps, and by counting
+def test_more_tiles_than_the_call_before(n):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(79)
+    b, few, many = 2000, 30, 60 if n > 1_000_000 else 90    # (by counting, a segment takes twice what it is made for)
+    lengths = np.zeros(n, dtype=np.int64)
+    lengths[:2 * b], lengths[2 * b:4 * b] = few, many
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    col = np.concatenate([np.arange(x) * (n // x) + rng.integers(0, n // x, x) for x in lengths[:4 * b]]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(3):
+        batches = (np.arange(2 * b, dtype=np.int32) + (2 * b if call == 1 else 0)).reshape(2, b)
+        res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (100,), 5, extract="sort", recycle=res)
+        assert_hops_equal(res.hops(), O.sample_nodewise(rowptr, col, batches, (100,), 5), what="call %d" % call)
+        assert res.attempts() == 1
+
+
 def test_scratch_of_the_cut_goes_by_entries():
     # many minibatches of hardly any entries: scratch by what they hold, not by a tile each (16 KB)
     from oracle import bms_oracle as O
