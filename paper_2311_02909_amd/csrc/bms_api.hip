@@ -36,6 +36,7 @@ constexpr int32_t kHostScalars = 72; // the 64 scalars of a call, then the seed 
 constexpr int kArrivedSlot = 66;
 constexpr int64_t kSpinMicros = 20000; // how long a call looks at that word before it leaves the waiting to the runtime
 constexpr size_t kMostHostOffsets = 1 << 16; // per-minibatch offsets that a call leaves in host memory: at most (512 KB)
+constexpr int kDrawDoneWord = 32, kTicketWords = kDrawDoneWord + kMostSharedDraws; // bms_csr::sm_ticket
 constexpr int64_t kScanTmpLen = 1 << 17; // partial sums of multi-workgroup scans: arrays up to 2^29 values
 
 thread_local char g_err[512] = "";
@@ -192,7 +193,8 @@ struct bms_csr {
     BMS_BUF(lw_bounds); BMS_BUF(lw_win); BMS_BUF(lw_tmpcol); BMS_BUF(lw_parts); BMS_BUF(lw_sel); BMS_BUF(lw_xtmp);
     BMS_BUF(lw_count); BMS_BUF(lw_tiles); BMS_BUF(lw_rowcnt); // LADIES by LDS windows
     BMS_BUF(sm_status); // hops done by one workgroup per minibatch: sizes published
-    BMS_BUF(sm_ticket); // counters: 0 next minibatch of those, 1 workgroups done (announce), 2 numbers (Lookback), 3 done (layer-wise)
+    BMS_BUF(sm_ticket); // counters: 0 next minibatch of those, 1 workgroups done (announce), 2 numbers (Lookback), 3 done (layer-wise),
+                        // from kDrawDoneWord on those of the draws
     bool tickets_known = false;              // ... are what sm_taken and lb_taken say; lost when a call fails
     uint32_t sm_epoch = 0, sm_taken = 0;     // launches so far, minibatches handed out by them
     BMS_BUF(lb_status);                      // values that workgroups of a launch bring (Lookback)
@@ -517,9 +519,9 @@ try {
     }
     c.res->host_off = false;
     c.res->host[64] = c.res->host[kRaisedSlot] = 0;
-    BMS_TRY(csr->sm_ticket.ensure(256));
+    BMS_TRY(csr->sm_ticket.ensure(kTicketWords * sizeof(uint32_t)));
     if (!csr->tickets_known) { // (a workgroup's number decides what it writes: never one of another launch)
-        HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, 256, c.stream));
+        HIP_TRY(hipMemsetAsync(csr->sm_ticket.p, 0, kTicketWords * sizeof(uint32_t), c.stream));
         csr->sm_taken = csr->lb_taken = 0;
         csr->tickets_known = true;
     }
@@ -1612,6 +1614,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.win_poff = reinterpret_cast<int64_t *>(w.win_woff + nw);
         w.win_cnt = reinterpret_cast<uint32_t *>(w.win_poff + nw);
         w.done = csr->sm_ticket.as<uint32_t>() + 3;
+        w.draw_done = csr->sm_ticket.as<uint32_t>() + kDrawDoneWord;
         w.part_woff = csr->lw_parts.as<uint64_t>();
         w.part_wt = w.part_woff + nw * kWinParts;
         w.part_base = reinterpret_cast<int64_t *>(w.part_wt + nw * kWinParts);
@@ -1726,8 +1729,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         BMS_TRY(prof.begin("ldw_draw", h));
         if (c.k <= kMostLookback) {
             BMS_TRY(next_lookback(c, lb));
-            launch_ldw_draw(c.launch, w, &lb, slot(c, h, 1));
-            lookback_used(c, (uint32_t)c.k);
+            lookback_used(c, (uint32_t)launch_ldw_draw(c.launch, w, &lb, slot(c, h, 1)));
         } else {
             launch_ldw_draw(c.launch, w, nullptr, nullptr);
             launch_offsets_from_counts(c.launch, w.mb_count, c.k, w.mb_coloff, slot(c, h, 1));

@@ -349,6 +349,7 @@ constexpr int kQueueStride = 16;         // a counter per 128-byte line
 constexpr int kLwRows = 256;             // rows per workgroup of the rows kernel
 constexpr int kLwTileMax = 4096;         // positions of the gathered order streamed by one wave at a time: at most
 constexpr int kLwTileMin = 1024;         // ... and at least (hops that gather little use small tiles to fill the chip)
+constexpr int32_t kMostSharedDraws = 128; // most minibatches whose draws several workgroups find
 struct LwHop {
     const int64_t *A_rowptr;
     const int32_t *A_col;
@@ -404,6 +405,7 @@ struct LwHop {
     int32_t place_pairs;       // 1: launch_ldw_p_copy finds the places of the parts itself
     int32_t p_past;            // 1: P is stored past the caches (not with place_pairs)
     int32_t *sel_tmp;          // k * s
+    uint32_t *draw_done;       // kMostSharedDraws words, zero between launches: workgroups of a minibatch that have found their draws
     int64_t *mb_coloff;        // k+1
     int32_t *col_vertex;
     int32_t *xtmp;             // D entries: the kept neighbours of row r start at gather_off[r]
@@ -430,7 +432,7 @@ bool ldw_may_place(const LwHop &);               // few enough pairs: LwHop::pla
 void launch_ldw_win_scan(const Launch &, const LwHop &, int64_t *pnnz_out); // places of the parts, p_off
 void launch_ldw_p_copy(const Launch &, const LwHop &, int64_t *pnnz_out);
 // lb == null: sel_tmp and mb_count only (launch_offsets_from_counts and launch_ldw_sel_copy follow)
-void launch_ldw_draw(const Launch &, const LwHop &, const Lookback *lb, int64_t *ncols_out);
+int launch_ldw_draw(const Launch &, const LwHop &, const Lookback *lb, int64_t *ncols_out); // workgroups
 void launch_ldw_sel_copy(const Launch &, const LwHop &);
 void launch_ldw_extract(const Launch &, const LwHop &);
 void launch_ldw_extract_copy(const Launch &, const LwHop &); // after a scan of out_rowptr

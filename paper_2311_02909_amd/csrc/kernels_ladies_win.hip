@@ -27,7 +27,7 @@
 //                   workgroup takes a pair and adds up the sizes of those before it
 //   ldw_win_scan, ldw_p_copy
 //                   the same of more than 2048 pairs: the places by a launch of their own, a wave per part
-//   ldw_draw        SAMPLE (Sec. 4.2.2): one workgroup per minibatch: s draws, each the smallest t
+//   ldw_draw        SAMPLE (Sec. 4.2.2): one workgroup per minibatch, or several with a share of the draws each: s draws, each the smallest t
 //                   with prefix[t] > r, sorted in LDS, duplicates dropped -> sampled columns, at their place in the stack
 //   ldw_extract     EXTRACT (Sec. 4.2.3): the sampled columns of the minibatch sit in an LDS hash
 //                   table (column -> local index); one wave per tile streams the gathered order a
@@ -1246,7 +1246,7 @@ __global__ __launch_bounds__(NT) void ldw_p_place_kernel(LwHop a, int planners, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// SAMPLE: one workgroup per minibatch
+// SAMPLE: one workgroup per minibatch, or several
 // ---------------------------------------------------------------------------------------------
 constexpr int kDrawThreads = 1024;
 // The value of lane ^ X: by the vector unit where it can, else through LDS's crossbar
@@ -1377,14 +1377,25 @@ __device__ inline void find_entries(const LwHop &a, const DrawRow &d, const uint
     }
 }
 
+// The entry of one draw, where P has fewer than 16
+__device__ inline int64_t walk_entries(const LwHop &a, const DrawRow &d, uint64_t r)
+{
+    int64_t e = d.p0;
+    for (uint64_t acc = ldw_weight(a.p_cnt[e], a.squared); acc <= r; acc += ldw_weight(a.p_cnt[e], a.squared))
+        ++e;
+    return e;
+}
+
 // PLACE: the sampled columns go to their place in the stack at once, behind those of the minibatches before (sum_before).
 // PER: places of the sort per thread, 1024 PER >= s.  A chain of trips to memory and barriers on one compute unit: the
 // draws of a thread search side by side, the 16 entries of a block arrive together, and most steps of the sort need no barrier.
 // 3 minibatches, 512 draws: 21 -> 9 us (sort 11 -> 2.5, entries of a block one by one 3 -> 1).  64 minibatches, 2048 draws from
 // 115 thousand blocks: 75 -> 71 us; there the sums and entries looked up, some 14 thousand lines per compute unit, are the bound
 // (50 us of it, whatever their order), and the sort went from 16 to 5 us.
-template <bool PLACE, int PER>
-__global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookback lb, int64_t *ncols_out)
+// SHARED (with PLACE): `parts` workgroups of a minibatch find a share of its draws each, and the one that is done last sorts and places
+// them all (launch_ldw_draw): 71 -> 42 us, four of them.
+template <bool PLACE, int PER, bool SHARED>
+__global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookback lb, int64_t *ncols_out, int parts)
 {
     __shared__ uint32_t ex[2 * PER * kDrawThreads];
     __shared__ uint64_t top[kDrawTop];
@@ -1392,7 +1403,9 @@ __global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookbac
     __shared__ uint32_t heads_of[PER * kDrawThreads / kWave];
     __shared__ uint32_t number_s;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int i = PLACE ? (int)scalar(take_number(lb, &number_s)) : (int)blockIdx.x;
+    const int number = PLACE ? (int)scalar(take_number(lb, &number_s)) : (int)blockIdx.x;
+    // (in the order of starting: who places waits only for minibatches all of whose workgroups have started)
+    const int i = SHARED ? number / parts : number, part = SHARED ? number - i * parts : 0;
     // where the minibatch's `count` columns begin
     auto place = [&](uint32_t count) {
         const int64_t before = sum_before<kDrawThreads>(lb, (uint32_t)i, count, smem64);
@@ -1408,9 +1421,10 @@ __global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookbac
     DrawRow d;
     d.pnnz = uniform_load(a.p_off + a.k);
     if (a.giveup && (uniform_load(a.giveup) || d.pnnz > a.p_cap)) { // no P: the minibatch gets no columns
-        if (PLACE)
-            place(0);
-        else if (tid == 0)
+        if (PLACE) {
+            if (part == 0)
+                place(0);
+        } else if (tid == 0)
             a.mb_count[i] = 0;
         return;
     }
@@ -1441,7 +1455,35 @@ __global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookbac
         top[q * kDrawThreads + tid] = sums[q];
     __syncthreads();
     uint32_t key[PER];
-    if (d.C > 0 && d.pnnz >= kPrefixBlock) {
+    if (SHARED) {
+        int32_t *__restrict__ found = a.sel_tmp + (int64_t)i * a.s;
+        const int each = (a.s + parts - 1) / parts, end = min((part + 1) * each, a.s);
+        for (int j = part * each + tid; j < end; j += kDrawThreads) {
+            const uint64_t r[1] = {bounded64(draw64(rk, (uint32_t)j), W)};
+            uint32_t column = kEmptySlot;
+            if (d.C > 0) {
+                int64_t e[1];
+                if (d.pnnz >= kPrefixBlock)
+                    find_entries<1>(a, d, top, r, e);
+                else
+                    e[0] = walk_entries(a, d, r[0]);
+                column = (uint32_t)a.p_col[e[0]];
+            }
+            __hip_atomic_store(found + j, (int32_t)column, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // what each wave found is where other dies see it
+        __syncthreads();
+        if (tid == 0)
+            number_s = arrive_last(a.draw_done + i, (uint32_t)parts) ? 1u : 0u;
+        __syncthreads();
+        if (!number_s)
+            return;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int j = q * kDrawThreads + tid;
+            key[q] = j < a.s ? (uint32_t)__hip_atomic_load(found + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kEmptySlot;
+        }
+    } else if (d.C > 0 && d.pnnz >= kPrefixBlock) {
         constexpr int N = PER < 2 ? PER : 2; // draws side by side
 #pragma unroll
         for (int q = 0; q < PER; q += N) {
@@ -1467,10 +1509,7 @@ __global__ __launch_bounds__(kDrawThreads) void ldw_draw_kernel(LwHop a, Lookbac
             key[q] = kEmptySlot;
             if (j < (uint32_t)a.s && d.C > 0) {
                 const uint64_t r = bounded64(draw64(rk, j), W);
-                int64_t e = d.p0;
-                for (uint64_t acc = ldw_weight(a.p_cnt[e], a.squared); acc <= r; acc += ldw_weight(a.p_cnt[e], a.squared))
-                    ++e;
-                key[q] = (uint32_t)a.p_col[e];
+                key[q] = (uint32_t)a.p_col[walk_entries(a, d, r)];
             }
         }
     }
@@ -1984,14 +2023,22 @@ void launch_ldw_p_copy(const Launch &L, const LwHop &a, int64_t *pnnz_out)
     hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][a.p_past ? 1 : 0], dim3((unsigned)workgroups), dim3(256), 0, L.stream, a);
 }
 
-void launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)
+int launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)
 {
-    void (*const kernels[2][3])(LwHop, Lookback, int64_t *) = {
-        {ldw_draw_kernel<false, 1>, ldw_draw_kernel<false, 2>, ldw_draw_kernel<false, 4>},
-        {ldw_draw_kernel<true, 1>, ldw_draw_kernel<true, 2>, ldw_draw_kernel<true, 4>}};
+    void (*const kernels[3][3])(LwHop, Lookback, int64_t *, int) = {
+        {ldw_draw_kernel<false, 1, false>, ldw_draw_kernel<false, 2, false>, ldw_draw_kernel<false, 4, false>},
+        {ldw_draw_kernel<true, 1, false>, ldw_draw_kernel<true, 2, false>, ldw_draw_kernel<true, 4, false>},
+        {ldw_draw_kernel<true, 1, true>, ldw_draw_kernel<true, 2, true>, ldw_draw_kernel<true, 4, true>}};
     static_assert(kMaxWinSampled <= 4 * kDrawThreads, "the sort is too short");
     const int per = a.s <= kDrawThreads ? 0 : a.s <= 2 * kDrawThreads ? 1 : 2;
-    hipLaunchKernelGGL(kernels[lb ? 1 : 0][per], dim3(a.k), dim3(kDrawThreads), 0, L.stream, a, lb ? *lb : Lookback{}, ncols_out);
+    // 512 draws and more for each of several workgroups, as far as there are compute units: fewer gain less than the trip to memory and
+    // back costs (32 minibatches, 512 draws, 256 for each of two: three hops 43 and 46 us).  Whole calls by one and by several, 2.4 M
+    // vertices: 8 x 512 seeds, (1024, 1024) 159 and 156 us; 32 x 1024, (1024, 1024) 261 and 258; 128 x 512, (1024, 1024) 573 and 571;
+    // 64 x 1024, (2048, 2048) 536 and 515; 3 x 512, (4096) 96 and 85.  Two for every compute unit: 123 for 100 us of three hops.
+    const int parts = lb && a.k <= kMostSharedDraws ? std::max(1, std::min({8, a.s / 512, L.num_cu / a.k})) : 1;
+    hipLaunchKernelGGL(kernels[parts > 1 ? 2 : lb ? 1 : 0][per], dim3(a.k * parts), dim3(kDrawThreads), 0, L.stream, a, lb ? *lb : Lookback{},
+                       ncols_out, parts);
+    return a.k * parts;
 }
 
 void launch_ldw_sel_copy(const Launch &L, const LwHop &a)

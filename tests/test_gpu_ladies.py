@@ -414,6 +414,28 @@ def test_parts_as_masks(mods, b, squared):
         assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
 
 
+# the draws of a minibatch by one workgroup and by two, four and eight, which count one another in every call anew; some minibatches have
+# no neighbours to draw from, and P of the third call is more than what was provided for it, so that there are no draws
+@pytest.mark.parametrize("k,s", [(128, 1023), (128, 1024), (129, 1024), (64, 2049), (3, 4095), (31, 4096)])
+def test_draws_by_several_workgroups(mods, k, s):
+    O, bms, _ = mods
+    rng = np.random.default_rng(s + k)
+    n, b = 30_000, 20
+    lengths = np.concatenate([np.zeros(b, dtype=np.int64), rng.integers(20, 60, 10_000), np.full(n - 10_000 - b, 400)])
+    lengths[12_000:] = 0
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, x, replace=False)) for x in lengths]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(4):
+        ids = np.arange(10_000 + b, 12_000) if call == 2 else np.arange(b, 10_000)
+        batches = np.stack([rng.permutation(ids)[:b] for _ in range(k)]).astype(np.int32)
+        batches[k // 2] = np.arange(b)
+        res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (s, 7), 3 + call, recycle=res)
+        assert_hops_equal(res.hops(), O.sample_ladies(rowptr, col, batches, (s, 7), 3 + call), with_p=True, what="call %d" % call)
+        assert res.attempts() == (2 if call == 2 else 1)
+
+
 # more parts than a launch of the copy of P has waves
 def test_more_pairs_than_workgroups_copy(mods):
     O, bms, _ = mods
