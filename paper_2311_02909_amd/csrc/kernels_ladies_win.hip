@@ -98,6 +98,7 @@ __device__ inline uint32_t staged_words(uint32_t columns, uint32_t mask_from)
 }
 using FourPlaces = uint64_t __attribute__((may_alias));
 using I32x2_a4 = int32_t __attribute__((ext_vector_type(2), aligned(4)));
+using U32x4_a4 = uint32_t __attribute__((ext_vector_type(4), aligned(4)));
 using U32x2_a4 = uint32_t __attribute__((ext_vector_type(2), aligned(4)));
 
 constexpr int kPrefixBlock = 16; // entries of P per kept prefix sum
@@ -1908,13 +1909,19 @@ __device__ inline void extract_place(const LwHop &a, const Lookback &lb, int64_t
         uint32_t x = e - off_l[lo], piece = first_l[lo];
         int64_t g = gather_l[lo];
         if (x >= piece) { // in a later piece of the row: one per tile that it reaches into
-            const int64_t tile0 = tile_l[lo];
-            int64_t tile = tile0;
+            int32_t tile = 0; // after the row's first
+            const uint32_t *__restrict__ counts = a.tile_cnt + tile_l[lo] + 1;
             do {
-                x -= piece;
-                piece = a.tile_cnt[++tile];
+                const U32x4_a4 c0 = *reinterpret_cast<const U32x4_a4 *>(counts + tile), c1 = *reinterpret_cast<const U32x4_a4 *>(counts + tile + 4);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const bool later = x >= piece;
+                    x -= later ? piece : 0u;
+                    piece = later ? (q < 4 ? c0[q % 4] : c1[q % 4]) : piece;
+                    tile += later ? 1 : 0;
+                }
             } while (x >= piece);
-            g = pos_l[lo] + ((tile - tile0) << shift);
+            g = pos_l[lo] + ((int64_t)tile << shift);
         }
         put(a.out_col + before + e, a.xtmp[g + x]);
     }
