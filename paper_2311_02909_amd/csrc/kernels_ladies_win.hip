@@ -1897,33 +1897,48 @@ __device__ inline void extract_place(const LwHop &a, const Lookback &lb, int64_t
         }
         return;
     }
-    for (uint32_t e = tid; e < (uint32_t)total; e += kLwRows) {
-        int lo = 0, hi = kLwRows; // last row whose entries begin at or before e: rows without entries share their begin
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (off_l[mid] <= e)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        uint32_t x = e - off_l[lo], piece = first_l[lo];
-        int64_t g = gather_l[lo];
-        if (x >= piece) { // in a later piece of the row: one per tile that it reaches into
-            int32_t tile = 0; // after the row's first
-            const uint32_t *__restrict__ counts = a.tile_cnt + tile_l[lo] + 1;
-            do {
-                const U32x4_a4 c0 = *reinterpret_cast<const U32x4_a4 *>(counts + tile), c1 = *reinterpret_cast<const U32x4_a4 *>(counts + tile + 4);
+    constexpr int kEach = 4; // entries per thread whose places are looked up before any of them is stored
+    for (uint32_t x0 = 0; x0 < (uint32_t)total; x0 += kEach * kLwRows) {
+        const uint32_t e0 = x0 + tid;
+        int64_t from[kEach];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const bool later = x >= piece;
-                    x -= later ? piece : 0u;
-                    piece = later ? (q < 4 ? c0[q % 4] : c1[q % 4]) : piece;
-                    tile += later ? 1 : 0;
-                }
-            } while (x >= piece);
-            g = pos_l[lo] + ((int64_t)tile << shift);
+        for (int u = 0; u < kEach; ++u) {
+            if (u && x0 + u * kLwRows >= (uint32_t)total) { // (no entry for any lane)
+                from[u] = from[0];
+                continue;
+            }
+            const uint32_t e = min(e0 + u * kLwRows, (uint32_t)total - 1u);
+            int lo = 0; // last row whose entries begin at or before e: rows without entries share their begin
+#pragma unroll
+            for (int step = kLwRows / 2; step > 0; step /= 2)
+                lo += off_l[lo + step] <= e ? step : 0;
+            uint32_t x = e - off_l[lo], piece = first_l[lo];
+            from[u] = gather_l[lo];
+            if (x >= piece) { // in a later piece of the row: one per tile that it reaches into
+                int32_t tile = 0; // after the row's first
+                const uint32_t *__restrict__ counts = a.tile_cnt + tile_l[lo] + 1;
+                do {
+                    const U32x4_a4 c0 = *reinterpret_cast<const U32x4_a4 *>(counts + tile), c1 = *reinterpret_cast<const U32x4_a4 *>(counts + tile + 4);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const bool later = x >= piece;
+                        x -= later ? piece : 0u;
+                        piece = later ? (q < 4 ? c0[q % 4] : c1[q % 4]) : piece;
+                        tile += later ? 1 : 0;
+                    }
+                } while (x >= piece);
+                from[u] = pos_l[lo] + ((int64_t)tile << shift);
+            }
+            from[u] += x;
         }
-        put(a.out_col + before + e, a.xtmp[g + x]);
+        int32_t column[kEach];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            column[u] = a.xtmp[from[u]];
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            if (e0 + u * kLwRows < (uint32_t)total)
+                put(a.out_col + before + e0 + u * kLwRows, column[u]);
     }
 }
 
