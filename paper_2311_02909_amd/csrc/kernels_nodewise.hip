@@ -353,8 +353,8 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
     __shared__ uint16_t seg_tab_l[kMaxCells + 1];    // segment of every cell of ids, when the segments differ in width
     const int tid = threadIdx.x;
     const int32_t s = a.s;
-    const bool count = a.seg_cnt != nullptr; // then gridDim.x is a multiple of k: every tile of this workgroup belongs
-                                             // to minibatch blockIdx.x % k
+    const bool count = !(DIES && REPLACE) && a.seg_cnt != nullptr; // by dies after every tile; else gridDim.x is a multiple of k: every tile of this
+                                             // workgroup belongs to minibatch blockIdx.x % k
     const bool by_table = count && a.seg_tab != nullptr;
     const bool flat = a.flat != 0;
     const uint32_t self_mark = a.self_entry ? kSelfMark : 0u;
@@ -366,6 +366,14 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
                 seg_tab_l[x] = a.seg_tab[x];
         __syncthreads();
     }
+    auto leave_counts = [&](int i) { // (barriers between this and the next tile's additions)
+        uint32_t *__restrict__ out = a.seg_cnt + (int64_t)i * a.seg_C;
+        for (int c = tid; c < a.seg_C; c += kRowTile)
+            if (seg_hist[c]) {
+                atomicAdd(&out[c], seg_hist[c]);
+                seg_hist[c] = 0;
+            }
+    };
     // the extent of the lane's row in the workgroup's next tile is fetched while the current tile is sampled
     TileWalk<DIES> walk(a, 0, 1);
     int64_t t, t_next, r0, r0_next;
@@ -464,13 +472,11 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
             }
         }
         __syncthreads();
+        if (DIES && count)
+            leave_counts(i);
     }
-    if (count) {
-        uint32_t *__restrict__ out = a.seg_cnt + (int64_t)(blockIdx.x % a.k) * a.seg_C;
-        for (int c = tid; c < a.seg_C; c += kRowTile)
-            if (seg_hist[c])
-                atomicAdd(&out[c], seg_hist[c]);
-    }
+    if (!DIES && count)
+        leave_counts((int)(blockIdx.x % a.k));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -660,6 +666,7 @@ static void launch_nw_sample_lanes(const Launch &L, const NwHop &a, const VSet &
 // The rows and entries of later hops are what they are or were in the call before, not their bounds: 1024 seeds with (64, 64), 15000
 // rows where k b s is 65536, took 114 us by lanes and take 100.  8 minibatches of 512, (40, 40), 51 neighbours: the second hop's
 // sampling 76 -> 34 us by lanes, and it counts per segment, which saves 9 us more.
+constexpr int32_t kMostSegmentsByDies = 128;
 static bool wide_by_lanes(const NwHop &a, bool set)
 {
     return a.rows_tune >= 65536 || a.entries_tune >= (a.s <= 48 && !set ? 15'000 * a.s : 1'400'000);
@@ -685,18 +692,27 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     int grid = grid_for(L, tiles, small_graph && a.s <= 8 ? 6 : 4);
     // counting per segment needs every workgroup to stay with one minibatch: tile v belongs to minibatch v % k,
     // so a grid that is a multiple of k does it
-    if (a.seg_cnt && a.seg_C <= kMaxFusedSegments && a.k <= L.num_cu * 8)
-        grid = std::max(grid / a.k, 1) * a.k;
-    else
+    if (!(a.seg_cnt && a.seg_C <= kMaxFusedSegments && a.k <= L.num_cu * 8))
         a.seg_cnt = nullptr;
     // By dies from one row for every two vertices on: then the minibatches' rows at the same place share lines.  Whole calls of
     // (15, 10, 5), stacked and by dies: 2.4 M vertices, rows / n 0.43 253 and 248 us, 0.86 368 and 351, 1.1 446 and 416, 2.3 719 and
     // 635 (the last hop's sampling 323 and 246); 4 M of 150 neighbours 0.46 484 and 482, 1.8 1224 and 1184; 0.5 M 0.65 125 and 118;
     // (15, 20) with 0.27 260 and 260; hops of few tiles, 100 x 400 seeds, (5, 15), of 0.2 M vertices 107 and 100; 20 x 600, (10, 10), of
-    // 30 thousand 89 and 86.  Counting per segment rules it out, and is worth more (8.7 M of 12 neighbours, 0.91: 1064 and 1094).
-    const bool by_dies = !a.seg_cnt && a.k >= kDies && 2 * a.rows_tune >= a.n;
+    // 30 thousand 89 and 86.  Below that the second hop of 64 x 1024 seeds, 0.37, loses 5 us.
+    // Counting per segment, a workgroup by dies leaves its counts after every tile: up to kMostSegmentsByDies of them, and from one row
+    // for every eight vertices on.  Calls of (15, 10, 5), 8.7 M vertices: 154 neighbours, 1.7 2452 and 2410, 0.8 1254 and 1244, 0.4 760
+    // and 761; 53 neighbours, 1.1 1300 and 1168, 0.5 757 and 721; 12 neighbours, 0.44 562 and 543, 0.22 359 and 343; 20 M of 30
+    // neighbours, 0.45 1184 and 1141, 0.2 710 and 700.
+    // A workgroup by dies has one tile as a rule: those in progress then are neighbours, where workgroups that go on drift apart
+    // (64 x 1024 seeds, 2.4 M vertices: two hops 305 us with six workgroups per compute unit that go on, 322 with four, 295 so;
+    // independent draws, 32 x 777, are left going on: the call 334.5 so, 336.3 with a tile each).
+    const bool by_dies = a.k >= kDies && (a.seg_cnt ? !REPLACE && a.seg_C <= kMostSegmentsByDies && 8 * a.rows_tune >= a.n : 2 * a.rows_tune >= a.n);
+    if (by_dies && !REPLACE)
+        grid = grid_for(L, (int64_t)a.k * (a.rows_tune / a.k / kRowTile + 2), kOnePass);
     if (by_dies)
         grid = (grid + kDies - 1) / kDies * kDies;
+    else if (a.seg_cnt)
+        grid = std::max(grid / a.k, 1) * a.k;
     void (*const launch[2][2])(const Launch &, const NwHop &, const VSet &, int) = {
         {launch_nw_sample_lanes<SET, REPLACE, false, false>, launch_nw_sample_lanes<SET, REPLACE, false, true>},
         {launch_nw_sample_lanes<SET, REPLACE, true, false>, launch_nw_sample_lanes<SET, REPLACE, true, true>}};

@@ -62,6 +62,44 @@ def test_tiles_by_dies_with_minibatches_of_unequal_length(k, variant):
     _check(rowptr, col, batches, (14, 5), **variant)
 
 
+# the same of hops whose entries are counted per segment (8 rows >= n, up to 128 segments): by dies after every tile, or, of independent
+# draws and of more segments, in stacked order; the second call has more tiles than the first makes likely
+@pytest.mark.parametrize("variant", [{}, {"union_dst": True}, {"replace": True}], ids=lambda v: "+".join(v))
+@pytest.mark.parametrize("n,per_mb", [(60_000, 45_000), (5_000_000, 16384 * 128), (5_400_000, 16384 * 138)])
+def test_tiles_by_dies_that_count_per_segment(n, per_mb, variant):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(n)
+    k, b = 9, 1200
+    first = 60 if n < 1_000_000 else 200            # the first hop's neighbours, so that the second has rows for every eighth vertex
+    second = per_mb // (b * first) + 1
+    few = second // 2 + 1                           # neighbours of what the first call reaches
+    half = n // 2                                   # vertices 0 .. half - 1 lead to one another, and so do the others
+    lengths = np.full(n, second)
+    lengths[:half] = few
+    lengths[:k * b], lengths[half:half + k * b] = first // 2, first
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lengths)
+    at = np.arange(len(row)) - rowptr[row]          # one neighbour out of each of as many stretches of the half
+    stretch = half // lengths[row]
+    col = (at * stretch + rng.integers(0, 1 << 30, len(row)) % stretch + np.where(row < half, 0, half)).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    fanouts = (first, 8)
+    res = None
+    for call in range(3):
+        batches = (np.arange(k * b, dtype=np.int32) + (half if call == 1 else 0)).reshape(k, b)
+        ref = O.sample_nodewise(rowptr, col, batches, fanouts, 5, **variant)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 5, extract="sort", recycle=res, **variant)
+            torch.cuda.synchronize()
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+        name = [e.name for e in profile.events() if "nw_sample_kernel<8," in e.name][-1]
+        by_dies = "true>" in name.split("(")[0].split(",")[-1]
+        assert 8 * res.sizes()[1][0] >= n
+        if n == 60_000 or (n == 5_400_000 and call == 2):   # (by the entries that the call before had)
+            assert by_dies == (n == 60_000 and "replace" not in variant), name
+
+
 @pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 16384, 16385, 70_000, 3_000_000])
 def test_one_workgroup_hops_over_vertex_ranges_and_hubs(n):
     # a few hubs that every row samples crowd one bucket of ids: the counting passes take over
