@@ -1123,6 +1123,7 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         // and moved to the result's arrays without it at the end of the hop
         a.out_rowptr = self_in_rows ? csr->un_rowptr.as<int64_t>() : hb.rowptr.as<int64_t>();
         a.rows_bound = rows_bound;
+        a.rows_tune = no_wait && h ? std::min(rows_bound, c.res->hint_rows[h]) : rows_bound;
         a.self_entry = self_in_rows ? 1 : 0;
         a.mark_self = union_dst && ranges == 1 ? 1 : 0;
         if (ranges == 1) {
@@ -1153,12 +1154,9 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
         // nnz sizes the column buffers: read back (the only host round trip of the hop), or in the
         // steady state bounded from above; nnz_tune and rows_tune only pick tuning parameters
         int64_t nnz, nnz_tune;
-        a.rows_tune = rows_bound;
         if (no_wait) { // with BMS_UNION_DST nnz counts the rows' own entries too, until the hop's last step
             nnz = rows_bound * (most_per_row + a.self_entry);
             nnz_tune = std::max<int64_t>(c.res->hint_nnz[h], 1);
-            if (h)
-                a.rows_tune = std::min(rows_bound, c.res->hint_rows[h]);
         } else {
             BMS_TRY(read_scalars(c));
             if (!seeds_checked)

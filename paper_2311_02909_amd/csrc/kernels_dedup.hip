@@ -22,6 +22,8 @@
 #include "bms_device.h"
 #include "bms_internal.h"
 
+#include <algorithm>
+
 namespace bms {
 
 constexpr int kBinWords = 1 << (kBucketBits - 5);  // 1024 words = 4 KB: a bin's bitmap, per wave
@@ -524,9 +526,9 @@ int launch_nw_dedup_bucket(const Launch &L, const DedupArgs &a, const int64_t *o
 
 void launch_nw_dedup_front(const Launch &L, const DedupArgs &a, const int64_t *mb_coloff, int32_t *col_vertex, int64_t nnz)
 {
-    int gx = (int)((nnz / a.k + 2047) / 2048) + 1; // about one workgroup per 2048 entries of a minibatch
-    if (gx > 64)
-        gx = 64;
+    // A workgroup for every 2048 entries that a minibatch is likely to have: one that has more waits for its stores
+    const int64_t likely = a.C > 0 ? std::min(nnz, a.nnz_tune + a.nnz_tune / 16) : nnz;
+    const int gx = (int)std::min<int64_t>((likely / a.k + 2047) / 2048 + 1, a.C > 0 ? 1024 : 64);
     hipLaunchKernelGGL(nw_dedup_front_kernel, dim3(gx, a.k), dim3(256), (2 * (size_t)a.C + 1) * sizeof(uint32_t), L.stream, a,
                        mb_coloff, col_vertex);
 }

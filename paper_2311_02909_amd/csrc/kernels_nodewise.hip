@@ -145,8 +145,9 @@ struct TileWalk {
 // of distinct picks.
 // What bounds it is the number of rowptr lines on their way.  A wave takes a tile of its own, four rows per lane, and needs no
 // barrier.  Two hops each: 256 x 1024 seeds, (15, 10, 5), 111 M vertices: 265 -> 235 us; 128 minibatches on 8.7 M vertices:
-// 236 -> 186 us; 64 on 2.4 M: 71 -> 56 us.  Of workgroups per compute unit, 4 are best: 1, 2, 4 and 16 take 238, 199, 186 and
-// 193 us (8.7 M vertices), 77, 63, 56 us (2.4 M): fewer have too few lines on their way, more touch a larger part of the ids.
+// 236 -> 186 us; 64 on 2.4 M: 71 -> 56 us.  Of workgroups per compute unit that go from tile to tile, 4 are best: 1, 2, 4 and 16 take
+// 238, 199, 186 and 193 us (8.7 M vertices), 77, 63, 56 us (2.4 M): fewer have too few lines on their way, more drift apart over a
+// larger part of the ids.  Started in order with a tile per wave they stay together: 180 -> 174 us, 57 -> 55, 220 either way (111 M).
 constexpr int kTileRounds = kRowTile / kWave;
 template <int S>
 __global__ __launch_bounds__(kRowTile) void nw_rows_kernel(NwHop a)
@@ -270,8 +271,10 @@ __global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(
 void launch_nw_rows(const Launch &L, const NwHop &a)
 {
     const int64_t tiles = std::max(a.rows_bound / kRowTile + a.k, a.zero_quads / (8 * kRowTile));
-    const int64_t wgs = std::max((a.rows_bound / kRowTile + a.k) / (kRowTile / kWave) + 1, a.zero_quads / (8 * kRowTile));
-    const dim3 grid((grid_for(L, wgs, 4) + kDies - 1) / kDies * kDies), block(kRowTile);
+    // A tile per wave as a rule, of as many as the minibatches had in the call before; of a bound of the rows, four workgroups per
+    // compute unit.
+    const int64_t wgs = std::max((int64_t)a.k * (a.rows_tune / a.k / kRowTile + 2) / (kRowTile / kWave) + 1, a.zero_quads / (8 * kRowTile));
+    const dim3 grid((grid_for(L, wgs, a.rows_tune < a.rows_bound ? kOnePass : 4) + kDies - 1) / kDies * kDies), block(kRowTile);
     if (!a.replace)
         hipLaunchKernelGGL(nw_rows_kernel<0>, grid, block, 0, L.stream, a);
     else if (a.s <= 4)
