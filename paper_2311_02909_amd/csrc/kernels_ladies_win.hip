@@ -113,7 +113,7 @@ __device__ inline uint64_t ldw_weight(uint32_t cnt, int squared)
 // ---------------------------------------------------------------------------------------------
 // Rows: extents, the gathered order (exclusive scan of the degrees), 256 rows per workgroup
 // ---------------------------------------------------------------------------------------------
-__device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t (*tile)[65], int64_t x, int64_t nx);
+__device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t *room, int64_t x, int64_t nx);
 
 // The first `tiles` workgroups take the rows.  With the index, workgroups behind them turn the rows' lists window-major for the
 // accumulation (a launch of its own before, 6 us of every hop; both only need the frontier).  In the first hop (a.seeds) the frontier
@@ -121,7 +121,7 @@ __device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_verte
 // before, 4 us of every call): nobody in this launch reads what they write.
 __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb, int64_t *gathered_out, int tiles)
 {
-    extern __shared__ uint32_t rows_lds[]; // hash table of the seeds, or 64 x 65 words
+    extern __shared__ uint32_t rows_lds[]; // hash table of the seeds, or bounds_room words
     __shared__ int64_t smem[kLwRows / kWave];
     __shared__ uint32_t number_s;
     const int tid = threadIdx.x;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb,
             check_seeds<kLwRows>(a.seeds, x, a.b, a.n, a.seed_slots, a.seed_shift, rows_lds, a.seed_copy, a.seed_flags);
         } else {
             const int64_t nrows = a.seeds ? (int64_t)a.k * a.b : uniform_load(a.mb_rowoff + a.k);
-            transpose_bounds(a, row_vertex, nrows, reinterpret_cast<uint32_t (*)[65]>(rows_lds), x - checks, (int64_t)gridDim.x - tiles - checks);
+            transpose_bounds(a, row_vertex, nrows, rows_lds, x - checks, (int64_t)gridDim.x - tiles - checks);
         }
         return;
     }
@@ -342,44 +342,81 @@ __global__ __launch_bounds__(256) void ldw_bounds_kernel(LwHop a)
 // all rows at a time.  64 rows x 64 windows at a time through LDS, both sides coalesced.  The list of row r comes from this
 // hop's boundary pass, or, when the graph carries an index of every vertex's list, from the index entry of
 // the row's vertex (all zeros for vertices without neighbours, and so here for their rows).  Workgroup x of nx.
-__device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t (*tile)[65], int64_t x, int64_t nx)
+// 64 rows at a time, and as equal shares of their lists as 128 boundaries a piece allow: a list is read as a whole (its memory lines
+// once), its words dealt to the lanes in their order, whatever the number of windows.  room: bounds_room words of LDS.  256 threads.
+// Three layers of 64 x 1024 seeds, 133 windows: the launch 154 -> 130 us, in squares of 64 x 64 before, whose last ones had 6 of 64
+// words and which read the lists' lines twice; 32 x 512, 38 windows: 38 -> 33.  Pieces of up to 160: 134.
+constexpr int kBoundsRows = 64, kMostBounds = 128;
+static int64_t bounds_pieces(int64_t ncols) { return (ncols + kMostBounds - 1) / kMostBounds; }
+static size_t bounds_room(int64_t ncols) // rows of an odd number of words: their words at one place are in different banks
 {
-    const int64_t ncols = a.nwin + 1;
-    const int64_t tiles_c = (ncols + 63) / 64, tiles_r = (nrows + 63) / 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int64_t t = x; t < tiles_c * tiles_r; t += nx) {
-        const int64_t r0 = (t / tiles_c) * 64, c0 = (t % tiles_c) * 64;
-        if (a.index) { // the rows' vertices first, then all of a thread's 16 reads of the index in flight together
-            int64_t v[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                v[q] = r0 + ty + 4 * q < nrows ? (int64_t)row_vertex[r0 + ty + 4 * q] : -1;
-            uint32_t y[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) // a seed outside [0, n) is an error reported elsewhere; its row has no neighbours
-                y[q] = (v[q] >= 0 && v[q] < a.n && c0 + tx < ncols) ? a.index[v[q] * ncols + c0 + tx] : 0u;
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                tile[ty + 4 * q][tx] = y[q];
-        } else {
-            for (int y = ty; y < 64; y += 4) // (a row without neighbours has no boundaries on record)
-                if (r0 + y < nrows && c0 + tx < ncols)
-                    tile[y][tx] = a.gather_off[r0 + y + 1] != a.gather_off[r0 + y] ? a.bounds[(r0 + y) * ncols + c0 + tx] : 0u;
+    const int64_t width = (ncols + bounds_pieces(ncols) - 1) / bounds_pieces(ncols);
+    return kBoundsRows * (size_t)(width | 1) + kBoundsRows;
+}
+__device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t *room, int64_t x, int64_t nx)
+{
+    constexpr int NT = 256, kEach = 16; // reads in flight per thread
+    const uint32_t ncols = (uint32_t)a.nwin + 1u, pieces = (ncols + kMostBounds - 1) / kMostBounds, width = (ncols + pieces - 1) / pieces;
+    const uint32_t stride = width | 1u;
+    int32_t *list_of = reinterpret_cast<int32_t *>(room + kBoundsRows * stride); // whose list a row has; -1: none
+    const int64_t tiles = (int64_t)pieces * ((nrows + kBoundsRows - 1) / kBoundsRows);
+    const uint32_t *lists = a.index ? a.index : a.bounds;
+    const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
+    for (int64_t t = x; t < tiles; t += nx) {
+        const int64_t r0 = t / pieces * kBoundsRows;
+        const uint32_t c0 = (uint32_t)(t % pieces) * width, w = min(width, ncols - c0);
+        if (tid < kBoundsRows) {
+            const int64_t r = r0 + tid;
+            int32_t of = -1;
+            if (r < nrows && a.index) { // a seed outside [0, n) is an error reported elsewhere; its row has no neighbours
+                const int32_t v = row_vertex[r];
+                of = v >= 0 && (int64_t)v < a.n ? v : -1;
+            } else if (r < nrows) { // (a row without neighbours has no boundaries on record)
+                of = a.gather_off[r + 1] != a.gather_off[r] ? tid : -1;
+            }
+            list_of[tid] = of;
         }
         __syncthreads();
-        for (int y = ty; y < 64; y += 4)
-            if (c0 + y < ncols && r0 + tx < nrows)
-                a.bounds_t[(c0 + y) * a.rows_bound + r0 + tx] = tile[tx][y];
+        const int64_t first = a.index ? 0 : r0; // list of number 0
+        uint32_t row = (uint32_t)tid / w, col = (uint32_t)tid - row * w;
+        const uint32_t row_step = NT / w, col_step = NT - row_step * w;
+        while (row < (uint32_t)kBoundsRows) { // (of some threads: the others have no more)
+            uint32_t y[kEach], place[kEach];
+#pragma unroll
+            for (int q = 0; q < kEach; ++q) {
+                y[q] = 0;
+                place[q] = row * stride + col;
+                const int32_t of = row < (uint32_t)kBoundsRows ? list_of[row] : -1;
+                if (of >= 0)
+                    y[q] = lists[(first + of) * ncols + c0 + col];
+                if (row >= (uint32_t)kBoundsRows)
+                    place[q] = ~0u;
+                row += row_step;
+                col += col_step;
+                if (col >= w) {
+                    col -= w;
+                    ++row;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kEach; ++q)
+                if (place[q] != ~0u)
+                    room[place[q]] = y[q];
+        }
+        __syncthreads();
+        for (uint32_t y = ty; y < w; y += NT / 64)
+            if (r0 + tx < nrows)
+                a.bounds_t[(int64_t)(c0 + y) * a.rows_bound + r0 + tx] = room[tx * stride + y];
         __syncthreads();
     }
 }
 
 __global__ __launch_bounds__(256) void ldw_bounds_transpose_kernel(LwHop a)
 {
-    __shared__ uint32_t tile[64][65];
+    extern __shared__ uint32_t bounds_lds[];
     if (a.giveup && *a.giveup)
         return;
-    transpose_bounds(a, a.row_vertex, a.mb_rowoff[a.k], tile, blockIdx.x, gridDim.x);
+    transpose_bounds(a, a.row_vertex, a.mb_rowoff[a.k], bounds_lds, blockIdx.x, gridDim.x);
 }
 
 // Plan and tile rows by workgroups of a launch that does something else as well (hops with the index, k < kPlanMb): planner x of
@@ -1971,8 +2008,8 @@ int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t
     int64_t more = a.seeds ? a.k : 0;
     size_t lds = 0;
     if (ldw_fused(a)) {
-        more += grid_for(L, (((int64_t)a.nwin + 64) / 64) * ((a.rows_bound + 63) / 64), 8);
-        lds = 64 * 65 * sizeof(uint32_t);
+        more += grid_for(L, bounds_pieces(a.nwin + 1) * ((a.rows_bound + kBoundsRows - 1) / kBoundsRows), 8);
+        lds = bounds_room(a.nwin + 1) * sizeof(uint32_t);
     }
     if (a.seeds)
         lds = std::max(lds, (size_t)a.seed_slots * sizeof(uint32_t));
@@ -1982,11 +2019,12 @@ int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t
 
 void launch_ldw_bounds(const Launch &L, const LwHop &a)
 {
-    const int64_t ttiles = (((int64_t)a.nwin + 64) / 64) * ((a.rows_bound + 63) / 64);
+    const int64_t ttiles = bounds_pieces(a.nwin + 1) * ((a.rows_bound + kBoundsRows - 1) / kBoundsRows);
     launch_ldw_tiles(L, a);
     if (!a.index)
         hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
-    hipLaunchKernelGGL(ldw_bounds_transpose_kernel, dim3(grid_for(L, ttiles, 8)), dim3(256), 0, L.stream, a);
+    hipLaunchKernelGGL(ldw_bounds_transpose_kernel, dim3(grid_for(L, ttiles, 8)), dim3(256), bounds_room(a.nwin + 1) * sizeof(uint32_t),
+                       L.stream, a);
 }
 
 void launch_ldw_index(const Launch &L, const LwHop &a)

@@ -436,6 +436,26 @@ def test_draws_by_several_workgroups(mods, k, s):
         assert res.attempts() == (2 if call == 2 else 1)
 
 
+# lists of window boundaries in one piece and in several (up to 128 boundaries each); rows that fill no tile of 64
+@pytest.mark.parametrize("windows", [1, 2, 126, 127, 128, 255, 256])
+def test_lists_of_boundaries_in_pieces(mods, windows):
+    O, bms, _ = mods
+    rng = np.random.default_rng(windows)
+    n = windows * 65536 - 7
+    lengths = np.zeros(n, dtype=np.int64)
+    some = np.unique(np.concatenate([rng.integers(0, n, 400), [0, n - 1]]))
+    lengths[some] = rng.integers(0, 90, len(some))
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(some, x, replace=False)) for x in lengths[some]]).astype(np.int32)
+    batches = np.stack([rng.permutation(some)[:37] for _ in range(5)]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    ref = O.sample_ladies(rowptr, col, batches, (50, 20), 7)
+    res = None
+    for call in range(2):
+        res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (50, 20), 7, recycle=res)
+        assert_hops_equal(res.hops(), ref, with_p=True, what="%d windows, call %d" % (windows, call))
+
+
 # more parts than a launch of the copy of P has waves
 def test_more_pairs_than_workgroups_copy(mods):
     O, bms, _ = mods
