@@ -137,7 +137,7 @@ __device__ inline T block_exclusive_scan(T v, T *smem, T &total)
 {
     constexpr int NW = NT / kWave;
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int wave = threadIdx.x / kWave;
     T inc = wave_inclusive_scan(v);
     __syncthreads(); // protects smem against readers of a previous call
     if (lane == kWave - 1)

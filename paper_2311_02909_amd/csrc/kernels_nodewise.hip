@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kRowTile) void nw_sample_kernel(NwHop a, VSet vs)
     __shared__ uint16_t seg_tab_l[kMaxCells + 1];    // segment of every cell of ids, when the segments differ in width
     const int tid = threadIdx.x;
     const int32_t s = a.s;
-    const bool count = !(DIES && REPLACE) && a.seg_cnt != nullptr; // by dies after every tile; else gridDim.x is a multiple of k: every tile of this
+    const bool count = a.seg_cnt != nullptr; // by dies after every tile; else gridDim.x is a multiple of k: every tile of this
                                              // workgroup belongs to minibatch blockIdx.x % k
     const bool by_table = count && a.seg_tab != nullptr;
     const bool flat = a.flat != 0;
@@ -708,8 +708,8 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // neighbours, 0.45 1184 and 1141, 0.2 710 and 700.
     // A workgroup by dies has one tile as a rule: those in progress then are neighbours, where workgroups that go on drift apart
     // (64 x 1024 seeds, 2.4 M vertices: two hops 305 us with six workgroups per compute unit that go on, 322 with four, 295 so;
-    // independent draws, 32 x 777, are left going on: the call 334.5 so, 336.3 with a tile each).
-    const bool by_dies = a.k >= kDies && (a.seg_cnt ? !REPLACE && a.seg_C <= kMostSegmentsByDies && 8 * a.rows_tune >= a.n : 2 * a.rows_tune >= a.n);
+    // independent draws, 32 x 777, are left going on: the call 333.3 so, 333.8 with a tile each).
+    const bool by_dies = a.k >= kDies && (a.seg_cnt ? a.seg_C <= kMostSegmentsByDies && 8 * a.rows_tune >= a.n : 2 * a.rows_tune >= a.n);
     if (by_dies && !REPLACE)
         grid = grid_for(L, (int64_t)a.k * (a.rows_tune / a.k / kRowTile + 2), kOnePass);
     if (by_dies)
