@@ -268,12 +268,20 @@ __global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(
     }
 }
 
+// Visits of a walk by dies, k times the tiles of the largest minibatch, which has an eighth and three tiles more than the others at most
+// (of 6 minibatches with 40 tiles, one tile too few for the largest had a wave go on to a second one: 5.0 -> 6.6 us).
+static int64_t likely_visits(const NwHop &a)
+{
+    const int64_t tiles = a.rows_tune / a.k / kRowTile;
+    return (int64_t)a.k * (tiles + tiles / 8 + 3);
+}
+
 void launch_nw_rows(const Launch &L, const NwHop &a)
 {
     const int64_t tiles = std::max(a.rows_bound / kRowTile + a.k, a.zero_quads / (8 * kRowTile));
     // A tile per wave as a rule, of as many as the minibatches had in the call before; of a bound of the rows, four workgroups per
     // compute unit.
-    const int64_t wgs = std::max((int64_t)a.k * (a.rows_tune / a.k / kRowTile + 2) / (kRowTile / kWave) + 1, a.zero_quads / (8 * kRowTile));
+    const int64_t wgs = std::max(likely_visits(a) / (kRowTile / kWave) + 1, a.zero_quads / (8 * kRowTile));
     const dim3 grid((grid_for(L, wgs, a.rows_tune < a.rows_bound ? kOnePass : 4) + kDies - 1) / kDies * kDies), block(kRowTile);
     if (!a.replace)
         hipLaunchKernelGGL(nw_rows_kernel<0>, grid, block, 0, L.stream, a);
@@ -703,15 +711,17 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // (15, 20) with 0.27 260 and 260; hops of few tiles, 100 x 400 seeds, (5, 15), of 0.2 M vertices 107 and 100; 20 x 600, (10, 10), of
     // 30 thousand 89 and 86.  Below that the second hop of 64 x 1024 seeds, 0.37, loses 5 us.
     // Counting per segment, a workgroup by dies leaves its counts after every tile: up to kMostSegmentsByDies of them, and from one row
-    // for every eight vertices on.  Calls of (15, 10, 5), 8.7 M vertices: 154 neighbours, 1.7 2452 and 2410, 0.8 1254 and 1244, 0.4 760
+    // for every eight vertices on, four with fanouts above 8 (20 M vertices, (10, 10, 10), 0.4 and more 1091 and 1034; a hop of ten with
+    // 0.19, on 8.7 M, 288 and 298).  Calls of (15, 10, 5), 8.7 M vertices: 154 neighbours, 1.7 2452 and 2410, 0.8 1254 and 1244, 0.4 760
     // and 761; 53 neighbours, 1.1 1300 and 1168, 0.5 757 and 721; 12 neighbours, 0.44 562 and 543, 0.22 359 and 343; 20 M of 30
     // neighbours, 0.45 1184 and 1141, 0.2 710 and 700.
     // A workgroup by dies has one tile as a rule: those in progress then are neighbours, where workgroups that go on drift apart
     // (64 x 1024 seeds, 2.4 M vertices: two hops 305 us with six workgroups per compute unit that go on, 322 with four, 295 so;
     // independent draws, 32 x 777, are left going on: the call 333.3 so, 333.8 with a tile each).
-    const bool by_dies = a.k >= kDies && (a.seg_cnt ? a.seg_C <= kMostSegmentsByDies && 8 * a.rows_tune >= a.n : 2 * a.rows_tune >= a.n);
+    const bool by_dies = a.k >= kDies && (a.seg_cnt ? a.seg_C <= kMostSegmentsByDies && (a.s <= 8 ? 8 : 4) * a.rows_tune >= a.n
+                                                    : 2 * a.rows_tune >= a.n);
     if (by_dies && !REPLACE)
-        grid = grid_for(L, (int64_t)a.k * (a.rows_tune / a.k / kRowTile + 2), kOnePass);
+        grid = grid_for(L, likely_visits(a), kOnePass);
     if (by_dies)
         grid = (grid + kDies - 1) / kDies * kDies;
     else if (a.seg_cnt)
