@@ -33,40 +33,40 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 3_488_284_544,
-    ("dense_ladies", "ldw_p_copy"): 3_075_043_008,
-    ("dense_ladies", "ldw_extract"): 2_024_934_048,
-    ("dense_sage", "nw_sample"): 9_804_974_624,
-    ("dense_sage", "nw_rows"): 433_276_640,
-    ("dense_sage", "dd_split"): 936_015_488,
-    ("dense_sage", "dd_unsplit"): 802_812_224,
-    ("dense_sage", "dd_rank"): 845_656_448,
-    ("dense_sage", "dd_front"): 603_924_064,
-    ("large_sage", "nw_sample"): 5_019_769_856,
-    ("large_sage", "nw_rows"): 1_271_366_784,
-    ("large_sage", "dd_split"): 619_421_440,
-    ("large_sage", "dd_unsplit"): 555_927_744,
-    ("large_sage", "dd_rank"): 587_214_656,
-    ("large_sage", "dd_front"): 464_218_848,
-    ("mid_ladies", "ldw_p_copy"): 164_302_240,
-    ("mid_ladies", "ldw_accumulate"): 143_482_656,
-    ("mid_ladies", "ldw_extract"): 85_281_952,
-    ("mid_sage", "nw_sample"): 1_578_091_488,
-    ("mid_sage", "nw_rows"): 144_796_960,
-    ("mid_sage", "rg_lookup"): 330_144_064,
-    ("mid_sage", "rg_mark"): 190_076_224,
-    ("mid_sage", "rg_emit"): 150_484_896,
+    ("dense_ladies", "ldw_accumulate"): 2_922_689_600,
+    ("dense_ladies", "ldw_p_copy"): 2_500_447_360,
+    ("dense_ladies", "ldw_extract"): 2_021_371_744,
+    ("dense_sage", "nw_sample"): 9_027_953_472,
+    ("dense_sage", "nw_rows"): 422_471_424,
+    ("dense_sage", "dd_split"): 935_828_704,
+    ("dense_sage", "dd_unsplit"): 799_925_312,
+    ("dense_sage", "dd_rank"): 844_439_328,
+    ("dense_sage", "dd_front"): 603_922_464,
+    ("large_sage", "nw_sample"): 5_020_917_792,
+    ("large_sage", "nw_rows"): 1_092_976_512,
+    ("large_sage", "dd_split"): 619_775_488,
+    ("large_sage", "dd_unsplit"): 552_797_216,
+    ("large_sage", "dd_rank"): 583_427_488,
+    ("large_sage", "dd_front"): 464_212_384,
+    ("mid_ladies", "ldw_p_copy"): 164_317_248,
+    ("mid_ladies", "ldw_accumulate"): 143_546_816,
+    ("mid_ladies", "ldw_extract"): 85_254_688,
+    ("mid_sage", "nw_sample"): 1_243_132_768,
+    ("mid_sage", "nw_rows"): 144_485_152,
+    ("mid_sage", "rg_lookup"): 330_328_800,
+    ("mid_sage", "rg_mark"): 190_074_944,
+    ("mid_sage", "rg_emit"): 150_484_256,
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 9_403_960_832,
-    "dense_sage": 13_518_808_064,
-    "large_sage": 8_601_343_680,
-    "mid_ladies": 447_919_552,
-    "mid_sage": 2_426_881_952,
+    "dense_ladies": 8_260_520_256,
+    "dense_sage": 12_726_694_368,
+    "large_sage": 8_417_530_304,
+    "mid_ladies": 448_055_936,
+    "mid_sage": 2_091_803_360,
 }
 # the part of it that nw_sample reads, MB: the "read MB" of its launches in the same files
-NW_SAMPLE_READ_MB = {"dense_sage": 9304.0, "large_sage": 4691.7, "mid_sage": 1389.3}
+NW_SAMPLE_READ_MB = {"dense_sage": 8508.0, "large_sage": 4692.8, "mid_sage": 1053.5}
 OTHER_WORKLOADS = ("mid_sage", "dense_sage", "mid_ladies", "dense_ladies", "tiny_sage")
 
 
