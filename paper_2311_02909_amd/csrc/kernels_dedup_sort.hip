@@ -537,7 +537,8 @@ __global__ __launch_bounds__(kRankThreads, 8) void dd_rank_kernel(DedupArgs a)
 //      (16 bits, kept in LDS)
 //   3  rank of an id = count before its quad + set bits below it inside the quad; every id goes to its rank's place in LDS
 //      (equal ids to the same one), from where the distinct ids leave in order
-//   4  the bitmap is cleared again: word by word through the ids when they are few, else as a whole
+//   4  LISTED, where a workgroup may have several segments: the bitmap is cleared again, word by word through the ids when they are
+//      few, else as a whole
 // What bounds it is latency: trips to memory for ids that are not in registers, and, before step 3 did it, the stores of the
 // distinct ids straight from the bitmap, scattered over a wave's lanes (128 x 586 k ids of 8.7 M: 475 us so, 262 us without).
 // Two workgroups share a compute unit, which leaves 64 registers: enough as long as what the lanes have in common is in scalar
