@@ -715,10 +715,14 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // 0.19, on 8.7 M, 288 and 298).  Calls of (15, 10, 5), 8.7 M vertices: 154 neighbours, 1.7 2452 and 2410, 0.8 1254 and 1244, 0.4 760
     // and 761; 53 neighbours, 1.1 1300 and 1168, 0.5 757 and 721; 12 neighbours, 0.44 562 and 543, 0.22 359 and 343; 20 M of 30
     // neighbours, 0.45 1184 and 1141, 0.2 710 and 700.
+    // With a table of segments, that is, where the sampled ids crowd a part of the id range, in stacked order: the die that has that part
+    // has the rows of most entries, and the table is copied to LDS for every tile.  Ids by descending degree, stacked and by dies: 8.7 M
+    // vertices, 154 neighbours, (8, 8, 8) 0.83 1920 and 2034, (6, 6, 6) 0.24 661 and 674; 53 neighbours, (8, 8, 8) 0.59 1174 and 1217,
+    // (15, 10, 5) 0.27 544 and 564, 1.1 1509 and 1510; 12 neighbours, 0.48 685 and 713.
     // A workgroup by dies has one tile as a rule: those in progress then are neighbours, where workgroups that go on drift apart
     // (64 x 1024 seeds, 2.4 M vertices: two hops 305 us with six workgroups per compute unit that go on, 322 with four, 295 so;
     // independent draws, 32 x 777, are left going on: the call 333.3 so, 333.8 with a tile each).
-    const bool by_dies = a.k >= kDies && (a.seg_cnt ? a.seg_C <= kMostSegmentsByDies && (a.s <= 8 ? 8 : 4) * a.rows_tune >= a.n
+    const bool by_dies = a.k >= kDies && (a.seg_cnt ? !a.seg_tab && a.seg_C <= kMostSegmentsByDies && (a.s <= 8 ? 8 : 4) * a.rows_tune >= a.n
                                                     : 2 * a.rows_tune >= a.n);
     if (by_dies && !REPLACE)
         grid = grid_for(L, likely_visits(a), kOnePass);

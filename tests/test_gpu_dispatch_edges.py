@@ -100,6 +100,36 @@ def test_tiles_by_dies_that_count_per_segment(n, per_mb, variant):
             assert by_dies == (n == 60_000 or "replace" in variant), name
 
 
+# ids that crowd a part of the range: the second hop's segments are of unequal width, its entries are counted through their table, and
+# its tiles are sampled in stacked order, also where there are rows for every vertex and few segments
+@pytest.mark.parametrize("variant", [{}, {"union_dst": True}, {"replace": True}], ids=lambda v: "+".join(v))
+def test_tiles_in_stacked_order_with_a_table_of_segments(variant):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(41)
+    n, k, b = 60_000, 9, 1200
+    lists = [np.unique(rng.integers(0, n, size=64)) for _ in range(k * b)]
+    lists += [np.unique(np.concatenate([rng.integers(0, 900, size=36), rng.integers(0, n, size=4)])) for _ in range(n - k * b)]
+    rowptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    col = np.concatenate(lists).astype(np.int32)
+    batches = np.arange(k * b, dtype=np.int32).reshape(k, b)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(3):
+        ref = O.sample_nodewise(rowptr, col, batches, (60, 8), 5 + call, **variant)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (60, 8), 5 + call, extract="sort", recycle=res, **variant)
+            torch.cuda.synchronize()
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+        names = [e.name.split("(")[0] for e in profile.events()]
+        sample = [x for x in names if "nw_sample_kernel<8," in x][-1]
+        assert 2 * res.sizes()[1][0] >= n
+        if call:        # the table is at hand
+            assert res.attempts() == 1 and any("dd_split_kernel" in x and "true>" in x for x in names), names
+            assert not any("dd_count_kernel" in x for x in names[names.index(sample):]), names
+            assert "false>" in sample.split(",")[-1], sample
+
+
 @pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 16384, 16385, 70_000, 3_000_000])
 def test_one_workgroup_hops_over_vertex_ranges_and_hubs(n):
     # a few hubs that every row samples crowd one bucket of ids: the counting passes take over
