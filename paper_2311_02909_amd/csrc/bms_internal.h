@@ -385,6 +385,7 @@ struct LwHop {
     uint32_t *bounds;          // rows_bound * (nwin+1), one list per row
     const uint32_t *index;     // n * (nwin+1): the list of every vertex's whole row, built once per graph; or null
     uint32_t *bounds_t;        // (nwin+1) * rows_bound, the same window-major
+    int32_t bounds_width;      // boundaries of a list turned at a time (the launchers choose it)
     uint32_t *win_cnt;         // k * nwin: columns of P inside the window
     uint64_t *win_wt;          // k * nwin: their weight
     int64_t *win_poff;         // k * nwin: columns of the minibatch before the window

@@ -121,7 +121,7 @@ __device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_verte
 // before, 4 us of every call): nobody in this launch reads what they write.
 __global__ __launch_bounds__(kLwRows) void ldw_rows_kernel(LwHop a, Lookback lb, int64_t *gathered_out, int tiles)
 {
-    extern __shared__ uint32_t rows_lds[]; // hash table of the seeds, or bounds_room words
+    extern __shared__ uint32_t rows_lds[]; // hash table of the seeds, or room for transpose_bounds
     __shared__ int64_t smem[kLwRows / kWave];
     __shared__ uint32_t number_s;
     const int tid = threadIdx.x;
@@ -339,24 +339,34 @@ __global__ __launch_bounds__(256) void ldw_bounds_kernel(LwHop a)
 }
 
 // The boundary lists turned window-major (bounds_t[w * rows_bound + r]): the accumulation reads one window of
-// all rows at a time.  64 rows x 64 windows at a time through LDS, both sides coalesced.  The list of row r comes from this
-// hop's boundary pass, or, when the graph carries an index of every vertex's list, from the index entry of
-// the row's vertex (all zeros for vertices without neighbours, and so here for their rows).  Workgroup x of nx.
-// 64 rows at a time, and as equal shares of their lists as 128 boundaries a piece allow: a list is read as a whole (its memory lines
-// once), its words dealt to the lanes in their order, whatever the number of windows.  room: bounds_room words of LDS.  256 threads.
+// all rows at a time.  The list of row r comes from this hop's boundary pass, or, when the graph carries an index of every vertex's
+// list, from the index entry of the row's vertex (all zeros for vertices without neighbours, and so here for their rows).  64 rows and
+// a.bounds_width boundaries at a time through LDS, both sides coalesced: a list is read as few pieces of equal width, its words dealt to the
+// lanes in their order.  room: BoundsPieces::lds bytes of LDS.  256 threads, workgroup x of nx.
 // Three layers of 64 x 1024 seeds, 133 windows: the launch 154 -> 130 us, in squares of 64 x 64 before, whose last ones had 6 of 64
-// words and which read the lists' lines twice; 32 x 512, 38 windows: 38 -> 33.  Pieces of up to 160: 134.
-constexpr int kBoundsRows = 64, kMostBounds = 128;
-static int64_t bounds_pieces(int64_t ncols) { return (ncols + kMostBounds - 1) / kMostBounds; }
-static size_t bounds_room(int64_t ncols) // rows of an odd number of words: their words at one place are in different banks
+// words and which read the lists' lines twice; 32 x 512, 38 windows: 38 -> 33.
+constexpr int kBoundsRows = 64;
+struct BoundsPieces {
+    int32_t width;
+    int64_t tiles;
+    size_t lds;
+};
+// Pieces of up to 64 boundaries are one trip to memory for a thread's 16 reads, those of up to 128 are two, with the lists' lines cut
+// less often.  The trip counts as long as the chip holds all of the pieces at a time (four workgroups per compute unit).  Two layers, the launches by
+// 128 and by 64: 8 x 64 seeds, 134 boundaries 16.4 and 12.2 us, 1695 20.6 and 14.6; 32 x 512, 81 19.4 and 16.0, 224 22.6 and 19.2; 64 x 1024,
+// 81 39.4 and 41.6, 224 51.3 and 55.0; 64 x 512, 1695 170 and 180.
+static BoundsPieces bounds_pieces(const Launch &L, const LwHop &a)
 {
-    const int64_t width = (ncols + bounds_pieces(ncols) - 1) / bounds_pieces(ncols);
-    return kBoundsRows * (size_t)(width | 1) + kBoundsRows;
+    const int64_t ncols = (int64_t)a.nwin + 1, row_tiles = (a.rows_bound + kBoundsRows - 1) / kBoundsRows;
+    const int64_t most = row_tiles * ((ncols + 63) / 64) <= (int64_t)L.num_cu * 4 ? 64 : 128;
+    const int64_t pieces = (ncols + most - 1) / most, width = (ncols + pieces - 1) / pieces;
+    // (rows of an odd number of words: their words at one place are in different banks)
+    return {(int32_t)width, pieces * row_tiles, (kBoundsRows * (size_t)(width | 1) + kBoundsRows) * sizeof(uint32_t)};
 }
 __device__ inline void transpose_bounds(const LwHop &a, const int32_t *row_vertex, int64_t nrows, uint32_t *room, int64_t x, int64_t nx)
 {
     constexpr int NT = 256, kEach = 16; // reads in flight per thread
-    const uint32_t ncols = (uint32_t)a.nwin + 1u, pieces = (ncols + kMostBounds - 1) / kMostBounds, width = (ncols + pieces - 1) / pieces;
+    const uint32_t ncols = (uint32_t)a.nwin + 1u, width = (uint32_t)a.bounds_width, pieces = (ncols + width - 1) / width;
     const uint32_t stride = width | 1u;
     int32_t *list_of = reinterpret_cast<int32_t *>(room + kBoundsRows * stride); // whose list a row has; -1: none
     const int64_t tiles = (int64_t)pieces * ((nrows + kBoundsRows - 1) / kBoundsRows);
@@ -1999,8 +2009,9 @@ static void launch_ldw_tiles(const Launch &L, const LwHop &a)
 
 bool ldw_fused(const LwHop &a) { return a.index && a.k < kPlanMb && (a.rows_bound + kLwRows - 1) / kLwRows <= kMostLookback; }
 
-int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t *gathered_out, uint32_t *workgroups)
+int launch_ldw_rows(const Launch &L, const LwHop &hop, const Lookback &lb, int64_t *gathered_out, uint32_t *workgroups)
 {
+    LwHop a = hop;
     const int64_t tiles = (a.rows_bound + kLwRows - 1) / kLwRows;
     if (tiles > kMostLookback)
         return -1;
@@ -2008,8 +2019,10 @@ int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t
     int64_t more = a.seeds ? a.k : 0;
     size_t lds = 0;
     if (ldw_fused(a)) {
-        more += grid_for(L, bounds_pieces(a.nwin + 1) * ((a.rows_bound + kBoundsRows - 1) / kBoundsRows), 8);
-        lds = bounds_room(a.nwin + 1) * sizeof(uint32_t);
+        const BoundsPieces pieces = bounds_pieces(L, a);
+        a.bounds_width = pieces.width;
+        more += grid_for(L, pieces.tiles, 8);
+        lds = pieces.lds;
     }
     if (a.seeds)
         lds = std::max(lds, (size_t)a.seed_slots * sizeof(uint32_t));
@@ -2017,14 +2030,15 @@ int launch_ldw_rows(const Launch &L, const LwHop &a, const Lookback &lb, int64_t
     return 0;
 }
 
-void launch_ldw_bounds(const Launch &L, const LwHop &a)
+void launch_ldw_bounds(const Launch &L, const LwHop &hop)
 {
-    const int64_t ttiles = bounds_pieces(a.nwin + 1) * ((a.rows_bound + kBoundsRows - 1) / kBoundsRows);
+    LwHop a = hop;
+    const BoundsPieces pieces = bounds_pieces(L, a);
+    a.bounds_width = pieces.width;
     launch_ldw_tiles(L, a);
     if (!a.index)
         hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
-    hipLaunchKernelGGL(ldw_bounds_transpose_kernel, dim3(grid_for(L, ttiles, 8)), dim3(256), bounds_room(a.nwin + 1) * sizeof(uint32_t),
-                       L.stream, a);
+    hipLaunchKernelGGL(ldw_bounds_transpose_kernel, dim3(grid_for(L, pieces.tiles, 8)), dim3(256), pieces.lds, L.stream, a);
 }
 
 void launch_ldw_index(const Launch &L, const LwHop &a)

@@ -436,9 +436,10 @@ def test_draws_by_several_workgroups(mods, k, s):
         assert res.attempts() == (2 if call == 2 else 1)
 
 
-# lists of window boundaries in one piece and in several (up to 128 boundaries each); rows that fill no tile of 64
-@pytest.mark.parametrize("windows", [1, 2, 126, 127, 128, 255, 256])
-def test_lists_of_boundaries_in_pieces(mods, windows):
+# lists of window boundaries in one piece and in several (up to 64 boundaries each, of many rows up to 128); rows that fill no tile of 64
+@pytest.mark.parametrize("windows,k", [(1, 5), (2, 5), (62, 5), (63, 5), (64, 5), (126, 5), (127, 5), (128, 5), (63, 1800), (126, 900),
+                                       (127, 900), (128, 900), (255, 500), (256, 500)])
+def test_lists_of_boundaries_in_pieces(mods, windows, k):
     O, bms, _ = mods
     rng = np.random.default_rng(windows)
     n = windows * 65536 - 7
@@ -447,7 +448,7 @@ def test_lists_of_boundaries_in_pieces(mods, windows):
     lengths[some] = rng.integers(0, 90, len(some))
     rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
     col = np.concatenate([np.sort(rng.choice(some, x, replace=False)) for x in lengths[some]]).astype(np.int32)
-    batches = np.stack([rng.permutation(some)[:37] for _ in range(5)]).astype(np.int32)
+    batches = np.stack([rng.permutation(some)[:37] for _ in range(k)]).astype(np.int32)
     csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
     ref = O.sample_ladies(rowptr, col, batches, (50, 20), 7)
     res = None
