@@ -1699,6 +1699,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         const double most = std::min<double>((double)(rows_bound / c.k), gathered / c.k * (double)csr->max_degree / (double)std::max<int64_t>(csr->nnz, 1));
         int64_t pnnz = std::max<int64_t>(std::min<int64_t>(D, (int64_t)c.k * n1), 1);
         w.place_pairs = ldw_may_place(w) && (no_wait || pnnz <= kNoWaitEntries) ? 1 : 0;
+        w.p_tune = no_wait ? c.res->hint_pnnz[h] : pnnz;
         if (launch_ldw_accumulate(c.launch, w, most) != 0)
             return fail(BMS_EHIP, "launch of the LDS accumulation kernel was refused");
         if (!w.place_pairs)
@@ -1710,7 +1711,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
             pnnz = std::min<int64_t>(pnnz, with_margin(c.res->hint_pnnz[h]));
         } else if (pnnz > kNoWaitEntries) {
             BMS_TRY(read_scalars(c));
-            pnnz = host_slot(c, h, 2);
+            pnnz = w.p_tune = host_slot(c, h, 2);
         }
         w.p_cap = pnnz;
         BMS_TRY(hb.p_col.ensure((size_t)std::max<int64_t>(pnnz, 1) * sizeof(int32_t)));
@@ -1719,7 +1720,7 @@ int sample_ladies_windows_once(CallCtx &c, const int32_t *batches, const int32_t
         w.p_col = hb.p_col.as<int32_t>();
         w.p_cnt = hb.p_cnt.as<uint32_t>();
         w.prefix = csr->ld_prefix.as<uint64_t>();
-        w.p_past = (no_wait ? c.res->hint_pnnz[h] : pnnz) >= kPastEntries ? 1 : 0;
+        w.p_past = w.p_tune >= kPastEntries ? 1 : 0;
         BMS_TRY(prof.begin("ldw_p_copy", h));
         launch_ldw_p_copy(c.launch, w, slot(c, h, 2));
         BMS_TRY(prof.end());

@@ -397,7 +397,6 @@ struct LwHop {
     uint64_t *part_woff;       // k * nwin * kWinParts: their weight
     unsigned long long *cursor; // device scalar: words of tmp_ent in use
     uint32_t *tmp_ent;         // P, part by part: a word per entry, or a bit per column and a byte per entry
-    uint32_t mask_from;        // columns from which on a part takes the latter form (launch_ldw_accumulate)
     int64_t *mb_count;         // k
     int64_t *p_off;            // k+1
     int32_t *p_col;
@@ -405,6 +404,8 @@ struct LwHop {
     uint64_t *prefix;          // pnnz, inclusive, restarts per minibatch
     int32_t place_pairs;       // 1: launch_ldw_p_copy finds the places of the parts itself
     int32_t p_past;            // 1: P is stored past the caches (not with place_pairs)
+    int64_t p_tune;            // entries P is likely to have
+    int32_t p_masks;           // 1: parts may be staged as masks (launch_ldw_accumulate chooses)
     int32_t *sel_tmp;          // k * s
     uint32_t *draw_done;       // kMostSharedDraws words, zero between launches: workgroups of a minibatch that have found their draws
     int64_t *mb_coloff;        // k+1
@@ -428,7 +429,7 @@ int launch_ldw_rows(const Launch &, const LwHop &, const Lookback &, int64_t *ga
 void launch_ldw_bounds(const Launch &, const LwHop &); // with an index: the rows' lists are copied from it
 void launch_ldw_index(const Launch &, const LwHop &);  // boundary lists of the rows of a hop that is the whole graph
 // most: about the largest e_v there will be; -1: launch refused
-int launch_ldw_accumulate(const Launch &, const LwHop &, double most);
+int launch_ldw_accumulate(const Launch &, LwHop &, double most);
 bool ldw_may_place(const LwHop &);               // few enough pairs: LwHop::place_pairs, and no launch_ldw_win_scan
 void launch_ldw_win_scan(const Launch &, const LwHop &, int64_t *pnnz_out); // places of the parts, p_off
 void launch_ldw_p_copy(const Launch &, const LwHop &, int64_t *pnnz_out);

@@ -88,13 +88,14 @@ static_assert(sizeof(AccLds<false>) <= 160 * 1024 && 2 * sizeof(AccLds<true>) <=
 // A part is staged in one of two forms (part_base: 2 x its first word in tmp_ent, + 1 with masks):
 //   entries  a word each, (column - the window's first id) << 16 | e_v
 //   masks    a bit per column of the part in use, then a byte per entry: e_v.  Only of counters of 8 bits, and of parts with at
-//            least LwHop::mask_from columns, where it is the shorter one (so that what holds the entries holds either form)
+//            least kMaskFrom columns, where it is the shorter one (so that what holds the entries holds either form)
 constexpr uint32_t kMaskWords = kPartIds / 32;
 constexpr uint32_t kMaskFrom = 256;
 static_assert(kMaskWords + (kMaskFrom + 3) / 4 <= kMaskFrom, "not the shorter one");
-__device__ inline uint32_t staged_words(uint32_t columns, uint32_t mask_from)
+constexpr int64_t kMaskEntries = 256; // of a part on average, from which on (launch_ldw_accumulate)
+__device__ inline uint32_t staged_words(uint32_t columns, bool as_masks)
 {
-    return columns >= mask_from ? kMaskWords + (columns + 3u) / 4u : columns;
+    return as_masks && columns >= kMaskFrom ? kMaskWords + (columns + 3u) / 4u : columns;
 }
 using FourPlaces = uint64_t __attribute__((may_alias));
 using I32x2_a4 = int32_t __attribute__((ext_vector_type(2), aligned(4)));
@@ -519,8 +520,8 @@ __device__ inline uint32_t at_most_one(uint32_t x)
 // steps of the count (1.14), all 64 lanes adding, those without an entry nothing (1.04: an LDS addition costs by active lanes),
 // P written here at its final place, found by looking back over the sizes of the pairs before (1.2 to 1.7 times accumulation
 // and copy together: it ties all workgroups to the slowest one of every round).
-template <bool SQUARED, bool NARROW>
-__global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(LwHop a)
+template <bool SQUARED, bool NARROW, bool MASKS>
+__device__ __forceinline__ void accumulate(const LwHop &a)
 {
     __shared__ AccLds<NARROW> lds; // (at a place that the compiler knows: an addition less per neighbour)
     if (a.giveup && *a.giveup)
@@ -794,11 +795,11 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
         }
         // room for the entries; the parts lie in it one after the other
         const int np = NW * parts;
-        const uint32_t mask_from = bytes ? a.mask_from : 0xFFFFFFFFu;
+        const bool as_masks = MASKS && bytes;
         const uint32_t of_part = lane < np ? sh.cnt[lane] : 0u;
-        const uint32_t sums = wave_inclusive_scan_dpp(staged_words(of_part, mask_from));
+        const uint32_t sums = wave_inclusive_scan_dpp(staged_words(of_part, as_masks));
         const uint32_t pair_words = (uint32_t)__builtin_amdgcn_readlane((int)sums, np - 1);
-        const uint32_t pair_c = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(of_part), np - 1);
+        const uint32_t pair_c = MASKS ? (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan_dpp(of_part), np - 1) : pair_words;
         unsigned long long claim = 0;
         if (tid == 0 && pair_c) {
             unsigned long long *cursor = a.cursor;
@@ -853,8 +854,8 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
         for (int q = 0; q < PARTS; ++q) {
             if (q >= parts)
                 continue;
-            const bool masks = part_c[q] >= mask_from;
-            const int64_t base = claimed + (uint32_t)__builtin_amdgcn_readlane((int)sums, wave * parts + q) - staged_words(part_c[q], mask_from);
+            const bool masks = as_masks && part_c[q] >= kMaskFrom;
+            const int64_t base = claimed + (uint32_t)__builtin_amdgcn_readlane((int)sums, wave * parts + q) - staged_words(part_c[q], as_masks);
             if (lane == 0) {
                 const int64_t part = (int64_t)blk * kWinParts + part0 + q;
                 a.part_base[part] = 2 * base + (masks ? 1 : 0);
@@ -933,6 +934,15 @@ __global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(
         blk = blk_next;
     }
 }
+
+// A hop whose parts may be masks: kernels of their own, whose longer code the others need not run through
+struct LwMasks {
+    LwHop hop;
+};
+template <bool SQUARED, bool NARROW>
+__global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(LwHop a) { accumulate<SQUARED, NARROW, false>(a); }
+template <bool SQUARED, bool NARROW>
+__global__ __launch_bounds__(kAccThreads<NARROW>, 4) void ldw_accumulate_kernel(LwMasks a) { accumulate<SQUARED, NARROW, true>(a.hop); }
 
 // Workgroups 0 .. k - 1, one per minibatch: columns and weight before each part of every window, and before each window; columns
 // and weight of the minibatch.  A part per thread, so 16 lanes per window.  The others plan (plan_tiles).
@@ -1089,18 +1099,32 @@ __device__ inline void store_p(T x, T *to) // PAST: past the caches (LwHop::p_pa
         *to = x;
 }
 
-// Many pairs: a window left the accumulation in kWinParts parts whose places are on record (ldw_win_scan).  A part per wave (above
-// 65536 pairs several), started in the order of P: what the chip writes at a time then lies close together, and the next workgroups fill the waits.  Whole lines of P
-// to a store: a wave's first 32 places are those of the line that the part begins in.  Of a part in masks all e_v (of up to
-// kCopyListed entries) are read before the first store (a load that is asked for behind stores is only there when they are done),
-// and a lane has two entries: half the stores and lane scans.
-// 115 M entries, 8.7 M vertices, all of the call's hops (3 GB with parts as entries, 2.6 with masks): 688 us with 17 parts a wave,
-// one after the other and 64 entries to a store; 620 from masks, 587 by two entries a lane and reads ahead of stores, 531 with 2 parts
-// a wave, 509 with one (5.1 TB/s).
-template <bool SQUARED, bool PAST>
-__global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
+// Many pairs: a window left the accumulation in kWinParts parts whose places are on record (ldw_win_scan).  Whole lines of P
+// to a store: a wave's first 32 places are those of the line that the part begins in.
+//   MASKS  (LwHop::p_masks: parts hold many entries, most of them in masks) a part per wave (above 65536 pairs several), started in the
+//          order of P: what the chip writes at a time then lies close together, and the next workgroups fill the waits.  All e_v of a part (of up to
+//          kCopyListed entries) are read before the first store (a load that is asked for behind stores is only there when they are done),
+//          and a lane has two entries: half the stores and lane scans.  115 M entries, 8.7 M vertices, all of the call's hops (3 GB with
+//          parts as entries, 2.6 with masks): 688 us with 17 parts a wave, one after the other and 64 entries to a store; 620 from masks, 587 by
+//          two entries a lane and reads ahead of stores, 531 with 2 parts a wave, 509 with one (5.1 TB/s).
+//   else   eight workgroups per compute unit that go from part to part: of parts of a few entries a launch of a wave each costs more than the
+//          waits, and their records are read by the vector unit, which has more reads on their way than the scalar one.  64 x 64 seeds, two
+//          hops, 4 and 50 entries a part: 94 us by the kernel for masks, 80 so; 200 x 256 on 2.4 M vertices, 21 entries: 42 and 36; ids by descending
+//          degree, 64 x 256, 3 and 39 entries: 107 and 72.  The records by the vector unit with masks: 437 -> 457 us of three layers of 64 x 1024.
+template <bool MASKS, class T>
+__device__ inline T part_record(const T *p)
 {
-    __shared__ CopyWave waves[256 / kWave];
+    if constexpr (MASKS)
+        return uniform_load(p);
+    else if constexpr (sizeof(T) == 4)
+        return (T)scalar((uint32_t)*p);
+    else
+        return (T)scalar((int64_t)*p);
+}
+template <bool SQUARED, bool PAST, bool MASKS>
+__device__ __forceinline__ void copy_parts(const LwHop &a)
+{
+    __shared__ CopyWave waves[MASKS ? 256 / kWave : 1];
     if (a.giveup) {
         if (*a.giveup)
             return;
@@ -1111,20 +1135,20 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
         }
     }
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = scalar(threadIdx.x / kWave);
-    CopyWave &me = waves[wave];
+    CopyWave &me = waves[MASKS ? wave : 0];
     const int64_t nparts = (int64_t)a.k * a.nwin * kWinParts;
     for (int64_t part = (int64_t)blockIdx.x * (256 / kWave) + wave; part < nparts; part += (int64_t)gridDim.x * (256 / kWave)) {
-        const uint32_t cw = uniform_load(a.part_cnt + part);
+        const uint32_t cw = part_record<MASKS>(a.part_cnt + part);
         if (cw == 0)
             continue;
         const int64_t blk = part / kWinParts;
         const int32_t i = (int32_t)((uint32_t)blk / (uint32_t)a.nwin); // (at most 2^16 minibatches and 2^15 windows)
         const int32_t window = (int32_t)blk - i * a.nwin;
-        const int64_t base = uniform_load(a.part_base + part);
-        const int64_t dst = uniform_load(a.p_off + i) + uniform_load(a.win_poff + blk) + uniform_load(a.part_off + part);
-        uint64_t carry = uniform_load(a.win_woff + blk) + uniform_load(a.part_woff + part);
+        const int64_t base = part_record<MASKS>(a.part_base + part);
+        const int64_t dst = part_record<MASKS>(a.p_off + i) + part_record<MASKS>(a.win_poff + blk) + part_record<MASKS>(a.part_off + part);
+        uint64_t carry = part_record<MASKS>(a.win_woff + blk) + part_record<MASKS>(a.part_woff + part);
         const uint32_t *__restrict__ src = a.tmp_ent + (base >> 1);
-        if (!(base & 1)) {
+        if (!MASKS || !(base & 1)) {
             for (int32_t x0 = -(int32_t)(dst & 31); x0 < (int32_t)cw; x0 += kCopyUnroll * kWave) {
                 uint32_t ent[kCopyUnroll];
                 fetch_entries(src, (uint32_t)x0, cw, ent);
@@ -1199,6 +1223,10 @@ __global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a)
         }
     }
 }
+template <bool SQUARED, bool PAST>
+__global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwHop a) { copy_parts<SQUARED, PAST, false>(a); }
+template <bool SQUARED, bool PAST>
+__global__ __launch_bounds__(256) void ldw_p_copy_kernel(LwMasks a) { copy_parts<SQUARED, PAST, true>(a.hop); }
 
 // Up to kMostPlacedPairs pairs: scan, copy and plan in one launch.  The first `planners` workgroups plan, each of the others takes a
 // pair and adds up the sizes of those before it (P is stacked like the pairs) while the entries are on their way.
@@ -2047,12 +2075,12 @@ void launch_ldw_index(const Launch &L, const LwHop &a)
     hipLaunchKernelGGL(ldw_bounds_kernel, dim3(grid_for(L, (a.tiles_bound + 3) / 4, 8)), dim3(256), 0, L.stream, a);
 }
 
-template <bool NARROW>
+template <bool NARROW, class Hop>
 static int launch_accumulate(const Launch &L, const LwHop &a)
 {
-    void (*const kernels[2])(LwHop) = {ldw_accumulate_kernel<false, NARROW>, ldw_accumulate_kernel<true, NARROW>};
+    void (*const kernels[2])(Hop) = {ldw_accumulate_kernel<false, NARROW>, ldw_accumulate_kernel<true, NARROW>};
     hipLaunchKernelGGL(kernels[a.squared ? 1 : 0], dim3(grid_for(L, (int64_t)a.k * a.nwin, NARROW ? 2 : 1)), dim3(kAccThreads<NARROW>),
-                       0, L.stream, a);
+                       0, L.stream, Hop{a});
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -2061,14 +2089,19 @@ static int launch_accumulate(const Launch &L, const LwHop &a)
 // 8 bits: 266 pairs, 40 expected: 144 and 133 us; 320, 244: 234 and 208; 1064, 223: 279 and 268; 532, 462 (2 pairs overflow): 256 and
 // 255; 920, 318 (12 overflow): 437 and 453; 532, 887 (92 overflow): 370 and 407.  With many pairs for every workgroup the few that
 // overflow cost less: three layers, 8512 pairs, 325 expected (35 overflow): 3000 and 2820.
-int launch_ldw_accumulate(const Launch &L, const LwHop &hop, double most)
+//
+// Masks from kMaskEntries of a part on average on: below, the longer code costs 2 or 3 % of the accumulation and the copy gains nothing.  Calls of
+// two layers, 64 minibatches, without and with them (entries a part in the second hop): 137 863 and 870 us, 151 226 and 228, 183 535 and 540, 246
+// level, 268 level, 319 673 and 650, 439 342 and 338, 537 943 and 865.  Nor where few pairs' entries stay in the caches until the copy has read
+// them, which is made for short parts.
+int launch_ldw_accumulate(const Launch &L, LwHop &a, double most)
 {
-    LwHop a = hop;
-    // Few pairs' entries stay in the caches until the copy has read them, and that is made for short parts: no masks there
-    a.mask_from = hop.place_pairs ? 0xFFFFFFFFu : kMaskFrom;
     const int64_t pairs = (int64_t)a.k * a.nwin;
     const bool narrow = pairs > L.num_cu && most <= (pairs >= 8 * L.num_cu ? 384.0 : 256.0);
-    return narrow ? launch_accumulate<true>(L, a) : launch_accumulate<false>(L, a);
+    a.p_masks = narrow && !a.place_pairs && a.p_tune >= kMaskEntries * kWinParts * pairs ? 1 : 0;
+    if (!narrow)
+        return launch_accumulate<false, LwHop>(L, a);
+    return a.p_masks ? launch_accumulate<true, LwMasks>(L, a) : launch_accumulate<true, LwHop>(L, a);
 }
 
 bool ldw_may_place(const LwHop &a) { return ldw_fused(a) && (int64_t)a.k * a.nwin <= kMostPlacedPairs; }
@@ -2077,6 +2110,14 @@ void launch_ldw_win_scan(const Launch &L, const LwHop &a, int64_t *pnnz_out)
 {
     const int planners = ldw_fused(a) ? grid_for(L, (a.rows_bound + 4 * kScanThreads - 1) / (4 * kScanThreads), 1) : 0;
     hipLaunchKernelGGL(ldw_win_scan_kernel, dim3(a.k + planners), dim3(kScanThreads), 0, L.stream, a, pnnz_out);
+}
+
+template <class Hop>
+static void launch_copy_parts(const Launch &L, const LwHop &a, int64_t workgroups)
+{
+    void (*const kernels[2][2])(Hop) = {{ldw_p_copy_kernel<false, false>, ldw_p_copy_kernel<false, true>},
+                                        {ldw_p_copy_kernel<true, false>, ldw_p_copy_kernel<true, true>}};
+    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][a.p_past ? 1 : 0], dim3((unsigned)workgroups), dim3(256), 0, L.stream, Hop{a});
 }
 
 void launch_ldw_p_copy(const Launch &L, const LwHop &a, int64_t *pnnz_out)
@@ -2091,10 +2132,11 @@ void launch_ldw_p_copy(const Launch &L, const LwHop &a, int64_t *pnnz_out)
                            planners, pnnz_out);
         return;
     }
-    void (*const kernels[2][2])(LwHop) = {{ldw_p_copy_kernel<false, false>, ldw_p_copy_kernel<false, true>},
-                                          {ldw_p_copy_kernel<true, false>, ldw_p_copy_kernel<true, true>}};
-    const int64_t workgroups = std::min<int64_t>(((int64_t)a.k * a.nwin * kWinParts + 3) / 4, kMostCopying);
-    hipLaunchKernelGGL(kernels[a.squared ? 1 : 0][a.p_past ? 1 : 0], dim3((unsigned)workgroups), dim3(256), 0, L.stream, a);
+    const int64_t workgroups = ((int64_t)a.k * a.nwin * kWinParts + 3) / 4;
+    if (a.p_masks)
+        launch_copy_parts<LwMasks>(L, a, std::min<int64_t>(workgroups, kMostCopying));
+    else
+        launch_copy_parts<LwHop>(L, a, grid_for(L, workgroups, 8));
 }
 
 int launch_ldw_draw(const Launch &L, const LwHop &a, const Lookback *lb, int64_t *ncols_out)

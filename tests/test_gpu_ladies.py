@@ -414,6 +414,30 @@ def test_parts_as_masks(mods, b, squared):
         assert_hops_equal(res.hops(), ref, with_p=True, what="call %d" % call)
 
 
+# parts as masks from 256 entries a part on, by what P had in the call before: long and short parts where the other kind was likely
+@pytest.mark.parametrize("squared", [False, True])
+def test_masks_by_the_entries_of_a_part(mods, squared):
+    O, bms, _ = mods
+    rng = np.random.default_rng(77)
+    n, k, b = 131_072, 1025, 20
+    lengths = np.zeros(n, dtype=np.int64)
+    lengths[:2000], lengths[2000:4000] = 600, 30
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(n, x, replace=False)) for x in lengths[:4000]]).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call, (first, masks) in enumerate([(0, True), (0, True), (2000, True), (2000, False), (0, True), (0, True)]):
+        batches = np.stack([first + rng.permutation(2000)[:b] for _ in range(k)]).astype(np.int32)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_ladies(csr, torch.from_numpy(batches).cuda(), (40,), 9 + call, squared=squared, recycle=res)
+            torch.cuda.synchronize()
+        for kernel in ("ldw_accumulate_kernel", "ldw_p_copy_kernel"):       # (the last attempt's)
+            name = [e.name for e in profile.events() if kernel in e.name][-1]
+            assert ("LwMasks" in name) == masks, (call, name)
+        assert res.attempts() == (2 if call == 4 else 1)
+        assert_hops_equal(res.hops(), O.sample_ladies(rowptr, col, batches, (40,), 9 + call, 0, squared), with_p=True, what="call %d" % call)
+
+
 # the draws of a minibatch by one workgroup and by two, four and eight, which count one another in every call anew; some minibatches have
 # no neighbours to draw from, and P of the third call is more than what was provided for it, so that there are no draws
 @pytest.mark.parametrize("k,s", [(128, 1023), (128, 1024), (129, 1024), (64, 2049), (3, 4095), (31, 4096)])
