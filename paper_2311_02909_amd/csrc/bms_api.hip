@@ -1276,11 +1276,11 @@ int sample_nodewise_once(CallCtx &c, const int32_t *batches, const int32_t *fano
             // the distinct ids and the 16-bit ranks in the second (the per-minibatch path uses both as 8-byte entries)
             d.ids_seg = csr->dd_pairs.as<uint32_t>();
             d.loc = reinterpret_cast<uint16_t *>(csr->dd_pairs.as<char>() + loc_at);
+            d.nnz_tune = nnz_tune;
             // Past the caches where whoever reads the columns next is no slower for it.  Calls, alone and with bms_aggregate_hop of 4
             // features behind them, through the caches and past them: 6 M entries 400 and 396 us, 493 and 497; 12 M 649 and 643, 816
             // and 821; 22 M 978 and 971, 1276 and 1273; 26 M 1160 and 1152, 1521 and 1517; 49 M 1949 and 1934, 2646 and 2639; on 8.7 M
             // vertices 19 M 855 and 850, 1097 and 1098; 28 M 1182 and 1171, 1550 and 1544; 56 M 2056 and 2037, 2833 and 2831.
-            d.nnz_tune = nnz_tune;
             d.past = nnz_tune >= (25LL << 20) ? 1 : 0;
             d.uids = csr->dd_utmp.as<uint32_t>();
             d.ranks = reinterpret_cast<uint16_t *>(d.uids + std::max<int64_t>(nnz, 1));

@@ -97,7 +97,8 @@ struct NwHop {
     int32_t *out_col;          // nnz
     int64_t *nnz_out;          // device scalar
     int64_t rows_bound;        // host-side upper bound of the row count
-    int64_t rows_tune, entries_tune; // what launch_nw_sample chooses kernels for: rows and entries, or what they were in the call before
+    int64_t rows_tune, entries_tune; // rows and entries, or what they were in the call before: what launch_nw_sample chooses kernels for
+                                     // and grids are sized by
     int32_t max_degree;
     int32_t self_entry;        // 1: every row carries its own vertex as one more entry after the sampled ones
     int32_t replace;           // 1: the s draws of a row are independent, the row keeps the distinct picks

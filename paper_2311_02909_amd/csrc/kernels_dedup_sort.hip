@@ -218,8 +218,8 @@ __global__ __launch_bounds__(256) void dd_seg_scan_kernel(DedupArgs a)
 }
 
 // TILE positions per workgroup step, NT threads.  The larger the tile, the longer the run every segment gets
-// in one step (a step's ids spread over all C segments), i.e. the wider the stores.  Three workgroups share a compute unit (four, in
-// 64 registers, spill: 0.152 ms for 0.133).  Two hops of 256 x 1024 seeds, (15, 10, 5), 111 M vertices, 58 M entries: 0.160 ms with a
+// in one step (a step's ids spread over all C segments), i.e. the wider the stores.  Three workgroups share a compute unit, with 70
+// registers (four, in 64, spill: 0.152 ms for 0.133).  Two hops of 256 x 1024 seeds, (15, 10, 5), 111 M vertices, 58 M entries: 0.160 ms with a
 // thousand workgroups that go from tile to tile, 0.143 with a tile each, 0.133 without a mask per id in whole tiles and with the
 // table of segments as a kernel of its own; of 128 on 8.7 M, 86 M entries: 0.238, 0.203 and 0.190.
 constexpr int kSplitThreads = 512;
@@ -227,7 +227,7 @@ template <int TILE, int NT, bool TAB>
 __global__ __launch_bounds__(NT, 6) void dd_split_kernel(DedupArgs a, const int64_t *__restrict__ tileoff)
 {
     // stage[TILE]; then 3 C words: per-segment count, start in the tile, start in global - start in the tile; then the table of
-    // segments, if there is one (TAB: a.tab; four workgroups share a compute unit without it)
+    // segments, if there is one (TAB: a.tab; without it the segment of an id is a shift, and nothing is copied first)
     extern __shared__ uint32_t split_lds[];
     __shared__ uint32_t smem[NT / kWave];
     __shared__ uint32_t carry_s;

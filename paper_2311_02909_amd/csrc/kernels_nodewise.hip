@@ -268,8 +268,9 @@ __global__ __launch_bounds__(kWideRowsThreads) void nw_rows_replace_wide_kernel(
     }
 }
 
-// Visits of a walk by dies, k times the tiles of the largest minibatch, which has an eighth and three tiles more than the others at most
-// (of 6 minibatches with 40 tiles, one tile too few for the largest had a wave go on to a second one: 5.0 -> 6.6 us).
+// Visits that a walk by dies is likely to have: k times the tiles of the largest minibatch, taken to be an eighth and three tiles more
+// than the mean (of 6 minibatches with 40 tiles, one tile too few for the largest had a wave go on to a second one: 5.0 -> 6.6 us).
+// Nothing depends on it: where there are more, workgroups go on to another tile.
 static int64_t likely_visits(const NwHop &a)
 {
     const int64_t tiles = a.rows_tune / a.k / kRowTile;
