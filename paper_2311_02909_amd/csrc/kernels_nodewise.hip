@@ -678,11 +678,12 @@ static void launch_nw_sample_lanes(const Launch &L, const NwHop &a, const VSet &
 // The rows and entries of later hops are what they are or were in the call before, not their bounds: 1024 seeds with (64, 64), 15000
 // rows where k b s is 65536, took 114 us by lanes and take 100.  8 minibatches of 512, (40, 40), 51 neighbours: the second hop's
 // sampling 76 -> 34 us by lanes, and it counts per segment, which saves 9 us more.
-constexpr int32_t kMostSegmentsByDies = 128;
 static bool wide_by_lanes(const NwHop &a, bool set)
 {
     return a.rows_tune >= 65536 || a.entries_tune >= (a.s <= 48 && !set ? 15'000 * a.s : 1'400'000);
 }
+constexpr int32_t kMostSegmentsByDies = 128;
+constexpr int64_t kMostStepBytes = 27 << 20;
 template <bool SET, bool REPLACE>
 static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet &vs)
 {
@@ -716,6 +717,11 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // 0.19, on 8.7 M, 288 and 298).  Calls of (15, 10, 5), 8.7 M vertices: 154 neighbours, 1.7 2452 and 2410, 0.8 1254 and 1244, 0.4 760
     // and 761; 53 neighbours, 1.1 1300 and 1168, 0.5 757 and 721; 12 neighbours, 0.44 562 and 543, 0.22 359 and 343; 20 M of 30
     // neighbours, 0.45 1184 and 1141, 0.2 710 and 700.
+    // Of many minibatches with few tiles each a step spans more of the ids: up to kMostStepBytes of A's columns, so that the eight dies'
+    // places fit the last-level cache together.  Last hop of (10, 10, 5), stacked and by dies: 8.7 M vertices of 154 neighbours, 200
+    // minibatches (24 MB) 902 and 893 us, 256 (30) 892 and 939, 512 (58) 906 and 1063, 1000 (119) 937 and 1125; of 29 neighbours, 512 (17)
+    // 430 and 401, 1000 (33) 433 and 450, 2000 (69) 500 and 541; of 7, 1000 (17) 151 and 144, 2000 (36) 165 and 187; 20 M of 21, 320 (26) 343
+    // and 334, 430 (34) 365 and 354, 512 (40) 346 and 378, 1000 (81) 350 and 418.
     // With a table of segments, that is, where the sampled ids crowd a part of the id range, in stacked order: the die that has that part
     // has the rows of most entries, and the table is copied to LDS for every tile.  Ids by descending degree, stacked and by dies: 8.7 M
     // vertices, 154 neighbours, (8, 8, 8) 0.83 1920 and 2034, (6, 6, 6) 0.24 661 and 674; 53 neighbours, (8, 8, 8) 0.59 1174 and 1217,
@@ -723,8 +729,9 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // A workgroup by dies has one tile as a rule: those in progress then are neighbours, where workgroups that go on drift apart
     // (64 x 1024 seeds, 2.4 M vertices: two hops 305 us with six workgroups per compute unit that go on, 322 with four, 295 so;
     // independent draws, 32 x 777, are left going on: the call 333.3 so, 333.8 with a tile each).
-    const bool by_dies = a.k >= kDies && (a.seg_cnt ? !a.seg_tab && a.seg_C <= kMostSegmentsByDies && (a.s <= 8 ? 8 : 4) * a.rows_tune >= a.n
-                                                    : 2 * a.rows_tune >= a.n);
+    const int64_t step_bytes = a.A_nnz * (int64_t)sizeof(int32_t) / std::max<int64_t>(a.rows_tune / a.k / kRowTile, 1);
+    const bool counted_by_dies = !a.seg_tab && a.seg_C <= kMostSegmentsByDies && (a.s <= 8 ? 8 : 4) * a.rows_tune >= a.n && step_bytes <= kMostStepBytes;
+    const bool by_dies = a.k >= kDies && (a.seg_cnt ? counted_by_dies : 2 * a.rows_tune >= a.n);
     if (by_dies && !REPLACE)
         grid = grid_for(L, likely_visits(a), kOnePass);
     if (by_dies)

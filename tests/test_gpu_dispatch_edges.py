@@ -100,6 +100,33 @@ def test_tiles_by_dies_that_count_per_segment(n, per_mb, variant):
             assert by_dies == (n == 60_000 or "replace" in variant), name
 
 
+# ... and up to 27 MB of columns per tile of a minibatch: many minibatches whose rows fill one tile and part of a second
+@pytest.mark.parametrize("more", [0, 1])
+def test_tiles_by_dies_of_many_minibatches_with_few_rows(more):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(43)
+    n, k, b, entries = 150_000, 72, 100, (27 << 20) // 4 + more
+    lengths = np.full(n, entries // n)
+    lengths[:entries - lengths.sum()] += 1
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    row = np.repeat(np.arange(n), lengths)
+    stretch = n // lengths[row]
+    col = ((np.arange(entries) - rowptr[row]) * stretch + rng.integers(0, 1 << 30, entries) % stretch).astype(np.int32)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(3):
+        batches = random_batches(n, k, b, rng)
+        ref = O.sample_nodewise(rowptr, col, batches, (5, 8), 5 + call)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (5, 8), 5 + call, extract="sort", recycle=res)
+            torch.cuda.synchronize()
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+        assert res.sizes()[1][0] // k // 256 == 1 and 8 * res.sizes()[1][0] >= n
+        sample = [e.name.split("(")[0] for e in profile.events() if "nw_sample_kernel<8," in e.name][-1]
+        assert ("true>" in sample.split(",")[-1]) == (not more), (call, sample)
+
+
 # ids that crowd a part of the range: the second hop's segments are of unequal width, its entries are counted through their table, and
 # its tiles are sampled in stacked order, also where there are rows for every vertex and few segments
 @pytest.mark.parametrize("variant", [{}, {"union_dst": True}, {"replace": True}], ids=lambda v: "+".join(v))
