@@ -730,12 +730,16 @@ static bool launch_nw_sample_impl(const Launch &L, const NwHop &a_in, const VSet
     // (15, 10, 5) 0.27 544 and 564, 1.1 1509 and 1510; 12 neighbours, 0.48 685 and 713.
     // A workgroup by dies has one tile as a rule: those in progress then are neighbours, where workgroups that go on drift apart
     // (64 x 1024 seeds, 2.4 M vertices: two hops 305 us with six workgroups per compute unit that go on, 322 with four, 295 so;
-    // independent draws, 32 x 777, are left going on: the call 333.3 so, 333.8 with a tile each).
+    // independent draws, 32 x 777, are left going on: the call 333.3 so, 333.8 with a tile each).  But not where that is between 1.2 and 2
+    // rounds of what the chip holds at a time: a second round that is half empty costs more than that.  0.5 M vertices of 78 neighbours, second
+    // hop, going on and a tile each: 100 x 512 seeds, (10, 10, 5) (1.6 rounds), 39.4 and 43.9 us, 30 x 500, (40, 10) (1.7), 31.0 and 33.4;
+    // 65 x 512, (10, 10) (1.1) 30.1 and 26.6, 130 x 512 (2.1) 46.3 and 43.5.
     const int64_t step_bytes = a.A_nnz * (int64_t)sizeof(int32_t) / std::max<int64_t>(a.rows_tune / a.k / kRowTile, 1);
     const bool counted_by_dies = !a.seg_tab && a.seg_C <= kMostSegmentsByDies && (a.s <= 8 ? 8 : 4) * a.rows_tune >= a.n && step_bytes <= kMostStepBytes;
     const bool by_dies = a.k >= kDies && (a.seg_cnt ? counted_by_dies : 2 * a.rows_tune >= a.n);
-    if (by_dies && !REPLACE)
-        grid = grid_for(L, likely_visits(a), kOnePass);
+    const int64_t visits = likely_visits(a), at_a_time = (int64_t)L.num_cu * (a.s <= 8 ? 7 : a.s <= 16 ? 5 : a.s <= 32 ? 3 : 2); // (registers, LDS)
+    if (by_dies && !REPLACE && (5 * visits <= 6 * at_a_time || visits >= 2 * at_a_time))
+        grid = grid_for(L, visits, kOnePass);
     if (by_dies)
         grid = (grid + kDies - 1) / kDies * kDies;
     else if (a.seg_cnt)

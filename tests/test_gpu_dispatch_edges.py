@@ -127,6 +127,32 @@ def test_tiles_by_dies_of_many_minibatches_with_few_rows(more):
         assert ("true>" in sample.split(",")[-1]) == (not more), (call, sample)
 
 
+# tiles by dies in one round of what the chip holds at a time, in a second that is half empty (workgroups go on then), and in more
+@pytest.mark.parametrize("variant", [{}, {"union_dst": True}], ids=lambda v: "+".join(v))
+@pytest.mark.parametrize("k", [20, 30, 40])
+def test_rounds_of_tiles_by_dies(k, variant):
+    from oracle import bms_oracle as O
+    from paper_2311_02909_amd import bms
+    rng = np.random.default_rng(44)
+    n, b = 20_000, 1000
+    col = ((np.arange(n * 40) % 40) * (n // 40) + rng.integers(0, n // 40, n * 40)).astype(np.int32)
+    rowptr = np.arange(0, n * 40 + 1, 40, dtype=np.int64)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = None
+    for call in range(3):
+        batches = random_batches(n, k, b, rng)
+        ref = O.sample_nodewise(rowptr, col, batches, (30, 10), 5 + call, **variant)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
+            res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (30, 10), 5 + call, recycle=res, **variant)
+            torch.cuda.synchronize()
+        assert_hops_equal(res.hops(), ref, what="call %d" % call)
+        sample = [e.name.split("(")[0] for e in profile.events() if "nw_sample_kernel<16," in e.name][-1]
+        assert "true>" in sample.split(",")[-1], sample
+        tiles = res.sizes()[1][0] // k // 256
+        rounds = k * (tiles + tiles // 8 + 3) / (5 * torch.cuda.get_device_properties(0).multi_processor_count)
+        assert (1.2 < rounds < 2) == (k == 30), rounds
+
+
 # ids that crowd a part of the range: the second hop's segments are of unequal width, its entries are counted through their table, and
 # its tiles are sampled in stacked order, also where there are rows for every vertex and few segments
 @pytest.mark.parametrize("variant", [{}, {"union_dst": True}, {"replace": True}], ids=lambda v: "+".join(v))
