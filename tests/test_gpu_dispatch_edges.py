@@ -63,9 +63,10 @@ def test_tiles_by_dies_with_minibatches_of_unequal_length(k, variant):
 
 
 # the same of hops whose entries are counted per segment (8 rows >= n, up to 128 segments): by dies after every tile, or, of more
-# segments, in stacked order; the second call has more tiles than the first makes likely
+# segments, in stacked order; the second call has more tiles than the first makes likely, and the third as many segments as the
+# second had entries for: 128 and 129 of the larger graphs (independent draws 64 and 65)
 @pytest.mark.parametrize("variant", [{}, {"union_dst": True}, {"replace": True}], ids=lambda v: "+".join(v))
-@pytest.mark.parametrize("n,per_mb", [(60_000, 45_000), (5_000_000, 16384 * 128), (5_400_000, 16384 * 138)])
+@pytest.mark.parametrize("n,per_mb", [(60_000, 45_000), (128 * 32768, 16384 * 128), (128 * 32768 + 1, 16384 * 128)])
 def test_tiles_by_dies_that_count_per_segment(n, per_mb, variant):
     from oracle import bms_oracle as O
     from paper_2311_02909_amd import bms
@@ -74,30 +75,34 @@ def test_tiles_by_dies_that_count_per_segment(n, per_mb, variant):
     first = 60 if n < 1_000_000 else 200            # the first hop's neighbours, so that the second has rows for every eighth vertex
     second = per_mb // (b * first) + 1
     few = second // 2 + 1                           # neighbours of what the first call reaches
-    half = n // 2                                   # vertices 0 .. half - 1 lead to one another, and so do the others
+    half = n // 2                                   # even vertices lead to one another, and so do odd ones
     lengths = np.full(n, second)
-    lengths[:half] = few
-    lengths[:k * b], lengths[half:half + k * b] = first // 2, first
+    lengths[::2] = few
+    lengths[:2 * k * b:2], lengths[1:2 * k * b:2] = first // 2, first
     rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
     row = np.repeat(np.arange(n), lengths)
-    at = np.arange(len(row)) - rowptr[row]          # one neighbour out of each of as many stretches of the half
+    at = np.arange(len(row)) - rowptr[row]          # one neighbour out of each of as many stretches of its kind
     stretch = half // lengths[row]
-    col = (at * stretch + rng.integers(0, 1 << 30, len(row)) % stretch + np.where(row < half, 0, half)).astype(np.int32)
+    col = (2 * (at * stretch + rng.integers(0, 1 << 30, len(row)) % stretch) + row % 2).astype(np.int32)
     csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
     fanouts = (first, 8)
     res = None
     for call in range(3):
-        batches = (np.arange(k * b, dtype=np.int32) + (half if call == 1 else 0)).reshape(k, b)
+        batches = (2 * np.arange(k * b, dtype=np.int32) + (1 if call == 1 else 0)).reshape(k, b)
         ref = O.sample_nodewise(rowptr, col, batches, fanouts, 5, **variant)
         with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as profile:
             res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), fanouts, 5, extract="sort", recycle=res, **variant)
             torch.cuda.synchronize()
         assert_hops_equal(res.hops(), ref, what="call %d" % call)
-        name = [e.name for e in profile.events() if "nw_sample_kernel<8," in e.name][-1]
-        by_dies = "true>" in name.split("(")[0].split(",")[-1]
-        assert 8 * res.sizes()[1][0] >= n
-        if n == 60_000 or (n == 5_400_000 and call == 2):   # (by the entries that the call before had)
-            assert by_dies == (n == 60_000 or "replace" in variant), name
+        names = [e.name.split("(")[0] for e in profile.events()]
+        sample = [x for x in names if "nw_sample_kernel<8," in x][-1]
+        by_dies = "true>" in sample.split(",")[-1]
+        assert 8 * res.sizes()[1][0] >= n and res.attempts() == 1
+        # (segments by the entries that the call before had)
+        assert by_dies == (n <= 128 * 32768 or call < 2 or "replace" in variant), sample
+        # ... and the sampling kernel counted: no pass over the entries does
+        after = names[len(names) - names[::-1].index(sample):]
+        assert any("dd_split_kernel" in x for x in after) and not any("dd_count_kernel" in x for x in after), after
 
 
 # ... and up to 27 MB of columns per tile of a minibatch: many minibatches whose rows fill one tile and part of a second
