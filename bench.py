@@ -33,9 +33,9 @@ HBM_PEAK_GBS = 8000.0
 # the line "bench constant ..." of profiles/<workload>_hbm_traffic.txt (tests/test_bench_constants.py compares
 # them); a kernel that has changed since its profile was taken has no entry (None in the output).
 MEASURED_TRAFFIC = {
-    ("dense_ladies", "ldw_accumulate"): 2_922_689_600,
-    ("dense_ladies", "ldw_p_copy"): 2_500_447_360,
-    ("dense_ladies", "ldw_extract"): 2_021_371_744,
+    ("dense_ladies", "ldw_accumulate"): 2_917_450_560,
+    ("dense_ladies", "ldw_p_copy"): 2_509_065_696,
+    ("dense_ladies", "ldw_extract"): 2_023_022_496,
     ("dense_sage", "nw_sample"): 9_027_953_472,
     ("dense_sage", "nw_rows"): 422_471_424,
     ("dense_sage", "dd_split"): 935_828_704,
@@ -48,9 +48,9 @@ MEASURED_TRAFFIC = {
     ("large_sage", "dd_unsplit"): 552_797_216,
     ("large_sage", "dd_rank"): 583_427_488,
     ("large_sage", "dd_front"): 464_212_384,
-    ("mid_ladies", "ldw_p_copy"): 164_317_248,
-    ("mid_ladies", "ldw_accumulate"): 143_546_816,
-    ("mid_ladies", "ldw_extract"): 85_254_688,
+    ("mid_ladies", "ldw_p_copy"): 164_315_776,
+    ("mid_ladies", "ldw_accumulate"): 143_496_352,
+    ("mid_ladies", "ldw_extract"): 85_218_048,
     ("mid_sage", "nw_sample"): 1_243_132_768,
     ("mid_sage", "nw_rows"): 144_485_152,
     ("mid_sage", "rg_lookup"): 330_328_800,
@@ -59,10 +59,10 @@ MEASURED_TRAFFIC = {
 }
 # the same summed over every kernel of one bulk call (bytes per step)
 MEASURED_CALL_TRAFFIC = {
-    "dense_ladies": 8_260_520_256,
+    "dense_ladies": 8_265_496_992,
     "dense_sage": 12_726_694_368,
     "large_sage": 8_417_530_304,
-    "mid_ladies": 448_055_936,
+    "mid_ladies": 447_971_968,
     "mid_sage": 2_091_803_360,
 }
 # the part of it that nw_sample reads, MB: the "read MB" of its launches in the same files

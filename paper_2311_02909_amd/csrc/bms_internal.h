@@ -44,6 +44,8 @@ void launch_publish(const Launch &, const PublishArgs &);
 int grid_for(const Launch &L, int64_t blocks, int per_cu);
 // per_cu where a workgroup has one tile as a rule.  A workgroup that goes on to another tile first waits for its stores (a load that
 // is asked for behind them is only there when they are done); one that ends does not, and the next one starts.
+// (Of more tiles than such a grid has workgroups they go on.  256 x 1024 seeds, (15, 10, 5), 8.7 M vertices of 154 neighbours, 132 thousand
+// likely visits of the last hop by 65536: 4554 us, 4750 by a thousand workgroups; 128 x 1024, all of whose tiles have one: 2345 and 2490.)
 constexpr int kOnePass = 256;
 void seed_table(int32_t b, int32_t &slots, int32_t &shift); // of the hash table that checks b seeds (check_seeds)
 // called by multi-kernel launchers before each kernel (group) so that it can be timed on its own
