@@ -52,6 +52,21 @@ def test_nodewise_hops_mean_and_sum(mods, f):
             _check(O, bms, res, ref, h, X, mean)
 
 
+# more tiles than workgroups that go on: full tiles of 16 and 4 rows; tiles of 4 rows that leave threads idle have a workgroup each
+@pytest.mark.parametrize("f", [64, 256, 200])
+def test_many_tiles(mods, f):
+    O, bms = mods
+    rng = np.random.default_rng(f)
+    rowptr, col = random_csr(20000, 14.0, rng)
+    batches = random_batches(20000, 8, 800, rng)
+    csr = bms.Csr(torch.from_numpy(rowptr).cuda(), torch.from_numpy(col).cuda())
+    res = bms.sample_nodewise(csr, torch.from_numpy(batches).cuda(), (10, 3), 3)
+    ref = O.sample_nodewise(rowptr, col, batches, (10, 3), 3)
+    assert res.sizes()[1][0] > 2048 * 16
+    X = rng.standard_normal((ref[1].ncols, f)).astype(np.float32)
+    _check(O, bms, res, ref, 1, X, True)
+
+
 def test_small_integer_features_sum_exactly(mods):
     O, bms = mods
     rng = np.random.default_rng(12)
